@@ -41,16 +41,11 @@ N_SIMD = 256 * 4
 CLOCK_HZ = 2.4e9
 VALU_PEAK_TLANEOPS = N_SIMD * 128 / 6.0 * CLOCK_HZ / 1e12  # 52.43
 VALU_PEAK_NOMINAL_4CLK = N_SIMD * 16 * CLOCK_HZ / 1e12     # 39.32
+# Dense ceiling of the 4-bit floating-point matrix instruction the GEMM runs on: V_MFMA_F32_32X32X64_F8F6F4 is
+# 32 x 32 x 64 multiply-adds in 32 clocks of a SIMD's matrix unit.
+#   1024 SIMDs x 2 x 65536 / 32 clk x 2.4 GHz = 10066 T ops/s
+FP4_PEAK_TOPS = N_SIMD * 2 * 65536 / 32.0 * CLOCK_HZ / 1e12
 BOPS_PER_LANEOP = 32.0  # 2 lane-instructions (xor, popcount-accumulate) per 32 bit-MACs = 64 binary ops
-
-# HBM bytes per launch of xnor_gemm_kernel from rocprofv3 counters, valid for the default workload only
-# (profiles/xnor_gemm_cfg4_fused_stack_b256.md, average of the five launches of a step).  Reads: the
-# L2's read requests by size class, 128 B x a + 64 B x b = 2751 KiB (exact: the same counters read
-# 1 GiB for a 1 GiB copy); writes: WRITE_SIZE 972.8 KiB.  The FETCH_SIZE metric scaled by the copy
-# kernel's factor (x 2.00) over-prices this kernel's 64-byte requests and would give 4.83e6.
-GEMM_TRAFFIC_BYTES = 3.81e6
-GEMM_TRAFFIC_BYTES_FETCH_SIZE_SCALED = 4.83e6
-
 
 NO_GRAPHS = False
 
@@ -442,14 +437,16 @@ def mfma_ablation():
         C3 = torch.empty((M, N), dtype=torch.int32, device=dev)
         C4 = torch.empty((M, N), dtype=torch.int32, device=dev)
         A4, B4 = B.bnn_expand_fp4(A, K), B.bnn_expand_fp4(Bm, K)
-        tv, _ = time_steps(lambda: B.bnn_xnor_gemm(A, Bm, K, C), 200, 100)
+        tp, _ = time_steps(lambda: B.bnn_xnor_gemm(A, Bm, K, C), 200, 100)
+        tv, _ = time_steps(lambda: B.bnn_xnor_gemm(A, Bm, K, C, cfg=3), 200, 100)
         tm, _ = time_steps(lambda: B.bnn_xnor_gemm_mfma_i8(A, Bm, K, C2), 200, 100)
         t4, _ = time_steps(lambda: B.bnn_xnor_gemm_mfma_fp4(A, Bm, K, C3), 200, 100)
         tx, _ = time_steps(lambda: B.bnn_xnor_gemm_mfma_fp4_expanded(A4, B4, K, C4), 200, 100)
         te, _ = time_steps(lambda: B.bnn_expand_fp4(Bm, K, out=B4), 200, 100)
         bops = 2.0 * M * N * K
         moved = A4.numel() + B4.numel() + 4 * M * N   # bytes the expanded form reads and writes once
-        out[name] = {"valu_TBOPS": round(bops / (tv / 200) / 1e12, 1), "mfma_i8_TBOPS": round(bops / (tm / 200) / 1e12, 1),
+        out[name] = {"product_path_TBOPS": round(bops / (tp / 200) / 1e12, 1),
+                     "valu_TBOPS": round(bops / (tv / 200) / 1e12, 1), "mfma_i8_TBOPS": round(bops / (tm / 200) / 1e12, 1),
                      "mfma_fp4_TBOPS": round(bops / (t4 / 200) / 1e12, 1),
                      "mfma_fp4_expanded_TBOPS": round(bops / (tx / 200) / 1e12, 1),
                      "bit_identical": bool((C == C2).all().item() and (C == C3).all().item()
@@ -472,11 +469,13 @@ def mfma_ablation():
         w4 = B.bnn_expand_fp4(wp, 9 * Cc)
         o1 = torch.empty((N, D, H, W), dtype=torch.int32, device=dev)
         o2 = torch.empty((N, D, H, W), dtype=torch.int32, device=dev)
-        tv, _ = time_steps(lambda: B.bnn_conv2d_packed(xp, wp, Cc, D, 3, 3, (1, 1), (1, 1), out="i32", out_buf=o1), 200, 100)
+        tp, _ = time_steps(lambda: B.bnn_conv2d_packed(xp, wp, Cc, D, 3, 3, (1, 1), (1, 1), out="i32", out_buf=o1), 200, 100)
+        tv, _ = time_steps(lambda: B.bnn_conv2d_packed(xp, wp, Cc, D, 3, 3, (1, 1), (1, 1), out="i32", out_buf=o1, cfg=3), 200, 100)
         tx, _ = time_steps(lambda: B.bnn_conv2d_mfma_fp4_expanded(x4, w4, Cc, D, 3, 3, (1, 1), (1, 1), out=o2), 200, 100)
         te = graph_time(lambda: B.bnn_expand_fp4(xp.view(N * H * W, Cw), Cc, out=x4.view(N * H * W, Cc // 2)))
         bops = 2.0 * N * H * W * D * 9 * Cc
-        out[name] = {"valu_TBOPS": round(bops / (tv / 200) / 1e12, 1),
+        out[name] = {"product_path_TBOPS": round(bops / (tp / 200) / 1e12, 1),
+                     "valu_TBOPS": round(bops / (tv / 200) / 1e12, 1),
                      "mfma_fp4_expanded_TBOPS": round(bops / (tx / 200) / 1e12, 1),
                      "bit_identical": bool((o1 == o2).all().item()),
                      "mfma_fp4_expanded_frac_of_fp4_dense_peak": round(bops / (tx / 200) / 10.1e15, 4),
@@ -544,7 +543,7 @@ def other_configs(args):
         lane = sum(gemm_laneops(*sh) for sh in wl["gemm_shapes"])
         out[name] = {"TBOPS_end_to_end": round(wl["bops"] / per / 1e12, 2), "ms": round(per * 1e3, 4),
                      "gemm_ms": round(g * 1e3, 4), "TBOPS_gemm_only": round(wl["bops"] / g / 1e12, 2),
-                     "gemm_frac_valu_peak": round(lane / g / 1e12 / VALU_PEAK_TLANEOPS, 4),
+                     "gemm_frac_fp4_peak": round(lane * BOPS_PER_LANEOP / g / 1e12 / FP4_PEAK_TOPS, 4),
                      "kernels_ms_event_hook": {k: round(v * 1e3, 4) for k, v in kt.items()}}
         if name == "cfg5b":
             sh = inputs_shape("cfg5b")
@@ -607,45 +606,49 @@ def main():
     dom_s, dom_ops, dom_n = by_name[dom]
     gemm_s = sum(t for _, t, _ in launches)
     method = "one HIP-event pair around each launch inside a pass of the stack (library hook)"
-    per_launch = [{"kernel": n, "ms": round(t * 1e3, 4), "frac": round(ops / t / 1e12 / VALU_PEAK_TLANEOPS, 4)}
+    matrix = dom == "xnor_gemm_fp4"
+    peak = FP4_PEAK_TOPS if matrix else VALU_PEAK_TLANEOPS
+
+    def rate(ops, t):
+        # lane-ops per second, or binary operations per second on the matrix cores
+        return ops * (BOPS_PER_LANEOP if matrix else 1.0) / t / 1e12
+
+    per_launch = [{"kernel": n, "ms": round(t * 1e3, 4), "TBOPS": round(ops * BOPS_PER_LANEOP / t / 1e12, 1)}
                   for n, t, ops in launches]
     if wl.get("replay"):
-        # the stack's xnor_gemm_kernel launches, each replayed back to back between one event pair
-        idx = [i for i, (n, _, _) in enumerate(launches) if n == dom]
+        # the stack's convolution launches, each replayed back to back between one event pair
+        idx = [i for i, (n, _, _) in enumerate(launches) if n == dom][:len(wl["replay"])]
         assert len(idx) == len(wl["replay"]), (len(idx), len(wl["replay"]))
         rt = replay_launches(wl["replay"])
-        dom_s = sum(rt)
-        gemm_s = gemm_s - sum(launches[i][1] for i in idx) + dom_s
+        dom_s = sum(rt) + sum(t for i, (n, t, _) in enumerate(launches) if n == dom and i not in idx)
+        gemm_s = gemm_s - sum(launches[i][1] for i in idx) + sum(rt)
         for i, t in zip(idx, rt):
             per_launch[i]["ms_replayed"] = round(t * 1e3, 4)
-            per_launch[i]["frac"] = round(launches[i][2] / t / 1e12 / VALU_PEAK_TLANEOPS, 4)
+            per_launch[i]["TBOPS"] = round(launches[i][2] * BOPS_PER_LANEOP / t / 1e12, 1)
         method = "each launch of the step replayed 50x back to back between one HIP-event pair on the launch stream"
-    achieved = dom_ops / dom_s / 1e12
-    default_wl = args.workload == "cfg4" and args.reading == "A" and args.stack == "fused"
+    for e, (_, _, ops) in zip(per_launch, launches):
+        e["frac"] = round(e["TBOPS"] / (FP4_PEAK_TOPS if e["kernel"] == "xnor_gemm_fp4" else VALU_PEAK_TLANEOPS * BOPS_PER_LANEOP), 4)
+    achieved = rate(dom_ops, dom_s)
     probes = valu_probes()
-    fracs = [achieved / VALU_PEAK_TLANEOPS] + [e["frac"] for e in per_launch]
+    fracs = [achieved / peak] + [e["frac"] for e in per_launch]
     if max(fracs) > 1.0:
         print(f"bench.py: WARNING roofline fraction above 1 ({max(fracs):.4f}): the derived peak is not a ceiling",
               file=sys.stderr)
     roofline = {
-        "kernel": {"xnor_gemm": "xnor_gemm_kernel", "xnor_gemm_small": "xnor_gemm_direct_kernel / 32x64 tiles"}.get(dom, dom),
-        "bound": "alu", "achieved": round(achieved, 3), "peak": round(VALU_PEAK_TLANEOPS, 2),
-        "unit": "Tlaneop/s", "frac": round(achieved / VALU_PEAK_TLANEOPS, 4),
-        "peak_nominal_4clk": round(VALU_PEAK_NOMINAL_4CLK, 2),
-        "peak_measured": probes["gemm_rows_tn4"], "frac_of_peak_measured": round(achieved / probes["gemm_rows_tn4"], 4),
+        "kernel": {"xnor_gemm": "xnor_gemm_kernel", "xnor_gemm_fp4": "xnor_gemm_fp4_kernel"}.get(dom, dom),
+        "bound": "mfma" if matrix else "alu", "achieved": round(achieved, 3), "peak": round(peak, 2),
+        "unit": "TOP/s" if matrix else "Tlaneop/s", "frac": round(achieved / peak, 4),
+        "valu_peak_Tlaneops": round(VALU_PEAK_TLANEOPS, 2), "valu_peak_nominal_4clk": round(VALU_PEAK_NOMINAL_4CLK, 2),
         "valu_probes_Tlaneops": probes,
         "all_fracs_le_1": bool(max(fracs) <= 1.0),
-        "traffic": GEMM_TRAFFIC_BYTES if default_wl else None,
-        "traffic_fetch_size_x2": GEMM_TRAFFIC_BYTES_FETCH_SIZE_SCALED if default_wl else None,
         "launches_per_step": dom_n, "avg_launch_ms": round(dom_s / dom_n * 1e3, 4),
         "per_launch": per_launch,
         "gemm_only_TBOPS": round(wl["bops"] / gemm_s / 1e12, 2),
         "timing": method,
-        "note": "achieved = 2*M*N*ceil(K/32) lane-ops of the dominant kernel's launches in one step / their summed "
-                "duration; peak = 1024 SIMDs x (2 x 64 lane-ops per xor+popcount pair) / (2 + 4 clocks) x 2.4 GHz: the issue "
-                "ceiling of the method's instruction pair; peak_nominal_4clk = 16 lanes per clock and SIMD; peak_measured = "
-                "the GEMM's row statements from registers, no loads, timed in this run; traffic = HBM bytes per launch of that kernel (rocprofv3: read requests by size class + WRITE_SIZE; "
-                "traffic_fetch_size_x2 = FETCH_SIZE scaled by the copy kernel's factor + WRITE_SIZE, an over-estimate here)",
+        "note": "matrix-core GEMM: achieved = 2*M*N*32*ceil(K/32) binary operations of the dominant kernel's launches in one "
+                "step / their summed duration; peak = 1024 SIMDs x one 32x32x64 fp4 matrix instruction per 32 clocks x 2.4 GHz "
+                "(the chip runs near 2.0 GHz under this load).  VALU kernels: lane-ops against the issue ceiling of the "
+                "xor + popcount pair (1024 SIMDs x (2 x 64 lane-ops) / (2 + 4 clocks) x 2.4 GHz)",
     }
 
     cpu = None

@@ -28,10 +28,12 @@ extern "C" {
  *   19, 20  the latency form of the implicit-GEMM convolution (32 x 64 tiles, one column per lane,
  *       the reduction axis split over 4 / 2 slices inside a workgroup); needs an even number of
  *       words per pixel
+ *   21 .. 24  the matrix-core GEMM (packed operands, expanded to 4-bit floating point in the wave that
+ *       multiplies them): 128 x 256 tiles on four waves, 128 x 256 on eight, 128 x 128, 64 x 256
  *   10  the short-row kernel (rows of two or four words, four consecutive columns per lane,
  *       16-byte stores), 8 rows per wave;   11, 12  the same with 16 / 32 rows per wave
  * A value that a call cannot use (the packed epilogue needs a 32- or 64-row tile with two or
- * four column groups; 7 to 18 exist for an explicit B with int32 / fp32 output only, 10 to 12
+ * four column groups, or one of 21 to 24; 7 to 18 exist for an explicit B with int32 / fp32 output only, 10 to 12
  * only where N, the leading dimensions and the pixels per image are multiples of 4) selects the
  * heuristic for that call.
  * `lean`: 1 = convolutions whose geometry allows it gather their patches with the table-driven

@@ -28,7 +28,8 @@ enum KernelId : int {
   KID_XNOR_CONV_LATENCY = 16,
   KID_EXPAND_FP4 = 17,
   KID_XNOR_GEMM_MFMA_FP4X = 18,
-  KID_COUNT = 19
+  KID_XNOR_GEMM_FP4 = 19,
+  KID_COUNT = 20
 };
 
 // Timing hook: records an event pair around a launch when profiling is on.
@@ -85,6 +86,19 @@ struct ConvGeom {
   FastDiv divOW, divOH; // output dims, or pooled output dims when pool == 2
 };
 
+// Matrix-core convolution: the input region of a tile of output pixels, kept in LDS as [word][pixel].
+struct HaloGeom {
+  int Wp;              // region pixels per row: every column a tap of any output column of a row reads
+  int units;           // units per image: output rows, or pairs of them when pooling
+  int ustep, uspan;    // input rows between units, input rows of one unit
+  int full;            // input rows of a whole image's units
+  int ppp;             // word pairs per pixel
+  int nch;             // runs of 64 word pairs per region row
+  uint32_t plane;      // bytes between the planes of two words
+  uint32_t bytes;      // of the region
+  FastDiv divNch, divPpp, divFull;
+};
+
 struct GemmParams {
   const uint32_t *A;   // [M, lda32] dwords
   const uint64_t *B;   // [N, ldb] words (explicit B only)
@@ -110,6 +124,7 @@ struct GemmParams {
   int colperm;         // 256-column tiles, int32 / fp32 output: LDS row 64 * j + l holds tile column 4 * l + j,
                        // so a lane's four columns are consecutive and go out as one 16-byte store per row
   ConvGeom g;          // implicit B only
+  HaloGeom halo;       // matrix-core convolution only
   uint64_t *outp;      // packed-sign output [pixels, cw_out] (packed epilogue only)
   int cw_out;
 };
@@ -139,6 +154,10 @@ bnn_status launch_lowk(GemmParams &p, int groups, hipStream_t s);
 // over ks (2 or 4) slices inside a workgroup.  emode as for run_gemm.
 bool latency_applicable(const GemmParams &p);
 bnn_status launch_latency(GemmParams &p, int emode, int ks, hipStream_t s);
+
+// Matrix-core GEMM on packed operands (gemm_fp4.hip): bmode / emode as for run_gemm; shape: tile number.
+bool fp4_applicable(const GemmParams &p);
+bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, int shape);
 
 // Conv helpers (im2col.hip).  check_conv_geometry validates shapes and 32-bit limits;
 // run_im2col launches encode (+ gather) with already validated arguments.

@@ -1,0 +1,255 @@
+// A wave's tile of the binarized GEMM on the fp4 matrix instruction: bit expansion, accumulators and the
+// two epilogues (int32 / fp32 maps; max-pool + affine map + sign packed NHWC).
+#pragma once
+#include "common.h"
+
+namespace bnn {
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// 32 bits -> 32 E2M1 codes (bit 0: +1.0 = 0x2, bit 1: -1.0 = 0xA), value 4j + 3 - s in nibble j of dword s.
+// The bit-field insert is written out: the optimizer splits it into an and and an or with literals.
+__device__ __forceinline__ v8i expand_e2m1(uint32_t x) {
+  const uint32_t sign = 0x88888888u, one = 0x22222222u;
+  v8i r = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    uint32_t d;
+    asm volatile("v_bfi_b32 %0, %1, %2, %3" : "=v"(d) : "s"(sign), "v"(x << s), "v"(one));
+    r[s] = (int)d;
+  }
+  return r;
+}
+
+// One step of 64 values for a 32 x 32 block: both operands E2M1 (format 4), no block scales.
+__device__ __forceinline__ v16f mfma_e2m1(const v8i &a, const v8i &b, const v16f &c) {
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 4, 4, 0, 0, 0, 0);
+}
+
+template <int WTM, int WTN>
+struct Fp4Acc {
+  v16f v[WTM][WTN];
+  __device__ __forceinline__ void init(float x) {
+#pragma unroll
+    for (int i = 0; i < WTM; ++i)
+#pragma unroll
+      for (int j = 0; j < WTN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[i][j][r] = x;
+  }
+};
+
+// One step of 64 values with the expanded operands (a, b), and beside it the expansion of the next step's
+// bits (xa, xb) into (na, nb) and whatever side(k) issues (staging, reading ahead), k = 0 .. WTM * WTN - 1.
+// Vector instructions issue in the shadow of a matrix instruction (32 clocks), not beside a run of them, so the
+// order is pinned: after each matrix instruction its share of everything else.  (Left to the compiler, the
+// expansions of a step form one block and the matrix instructions another, which do not overlap.)
+template <int WTM, int WTN, class Side>
+__device__ __forceinline__ void multiply_and_expand(Fp4Acc<WTM, WTN> &acc, const v8i (&a)[WTM], const v8i (&b)[WTN],
+                                                    const uint32_t (&xa)[WTM], const uint32_t (&xb)[WTN], v8i (&na)[WTM],
+                                                    v8i (&nb)[WTN], const Side &side) {
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < WTM * WTN; ++k) {
+    const int i = k / WTN, j = k % WTN;
+    acc.v[i][j] = mfma_e2m1(a[i], b[j], acc.v[i][j]);
+    asm volatile("" : "+v"(acc.v[i][j]));  // emits nothing; keeps the instruction here among the volatile statements
+    side(k);
+    // fragments k * F / n .. (k + 1) * F / n - 1 of the F = WTM + WTN
+#pragma unroll
+    for (int f = k * (WTM + WTN) / (WTM * WTN); f < (k + 1) * (WTM + WTN) / (WTM * WTN); ++f) {
+      if (f < WTM) na[f] = expand_e2m1(xa[f]);
+      else nb[f - WTM] = expand_e2m1(xb[f - WTM]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// The matrix instructions' results may be read by a written-out instruction only some wait states later (the
+// compiler pads only its own).  Two long no-ops, and every accumulator passes through them.
+__device__ __forceinline__ void settle(Fp4Acc<2, 4> &a) {
+  asm volatile("s_nop 15\n\ts_nop 15"
+               : "+v"(a.v[0][0]), "+v"(a.v[0][1]), "+v"(a.v[0][2]), "+v"(a.v[0][3]), "+v"(a.v[1][0]), "+v"(a.v[1][1]),
+                 "+v"(a.v[1][2]), "+v"(a.v[1][3]));
+}
+__device__ __forceinline__ void settle(Fp4Acc<2, 2> &a) {
+  asm volatile("s_nop 15\n\ts_nop 15" : "+v"(a.v[0][0]), "+v"(a.v[0][1]), "+v"(a.v[1][0]), "+v"(a.v[1][1]));
+}
+
+// One map (int32, or fp32 through the affine map) of a wave's tile.  AFF: 0 int32, 1 fp32 with per-row
+// constants, 2 fp32 with per-column constants.  VEC: a lane's WTN columns go out as one store.  FULL: no row
+// of the tile is past M.
+template <int WTM, int WTN, int AFF, bool VEC, bool FULL>
+__device__ __forceinline__ void store_map(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n, int half,
+                                          const float *sSc, const float *sBi, const int64_t (&off)[WTN]) {
+  typedef int vi __attribute__((ext_vector_type(WTN)));
+  int32_t *base = AFF == 0 ? p.C : reinterpret_cast<int32_t *>(p.Y);
+  const int64_t ld = AFF == 0 ? p.ldc : p.ldy;
+  float csc[WTN], cbi[WTN];
+  if constexpr (AFF == 2) {
+#pragma unroll
+    for (int j = 0; j < WTN; ++j) {
+      csc[j] = p.scale[min(n + j, p.N - 1)];
+      cbi[j] = p.bias[min(n + j, p.N - 1)];
+    }
+  }
+  int32_t *ptr[WTN];
+#pragma unroll
+  for (int j = 0; j < (VEC ? 1 : WTN); ++j) ptr[j] = base + off[j] + (int64_t)(m0 + 4 * half) * ld;
+#pragma unroll
+  for (int i = 0; i < WTM; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float4 sc, bi;
+      if constexpr (AFF == 1) {
+        sc = *reinterpret_cast<const float4 *>(sSc + 32 * i + 8 * q + 4 * half);
+        bi = *reinterpret_cast<const float4 *>(sBi + 32 * i + 8 * q + 4 * half);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        vi o;
+#pragma unroll
+        for (int j = 0; j < WTN; ++j) {
+          const float v = acc.v[i][j][4 * q + e];
+          if constexpr (AFF == 0) o[j] = (int)v;
+          else if constexpr (AFF == 1) o[j] = __float_as_int(fmaf((&sc.x)[e], v, (&bi.x)[e]));
+          else o[j] = __float_as_int(fmaf(csc[j], v, cbi[j]));
+        }
+        if (FULL || m0 + 32 * i + 8 * q + 4 * half + e < p.M) {
+          const int64_t row = (int64_t)(32 * i + 8 * q + e) * ld;  // uniform
+          if constexpr (VEC) {
+            __builtin_nontemporal_store(o, reinterpret_cast<vi *>(ptr[0] + row));
+          } else {
+#pragma unroll
+            for (int j = 0; j < WTN; ++j)
+              if (n + j < p.N) ptr[j][row] = o[j];
+          }
+        }
+      }
+    }
+}
+
+template <int WTM, int WTN, int AFF>
+__device__ __forceinline__ void store_map_by(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n, int half,
+                                             const float *sSc, const float *sBi, const int64_t (&off)[WTN]) {
+  if (p.colperm && m0 + 32 * WTM <= p.M) store_map<WTM, WTN, AFF, true, true>(p, acc, m0, n, half, sSc, sBi, off);
+  else if (p.colperm) store_map<WTM, WTN, AFF, true, false>(p, acc, m0, n, half, sSc, sBi, off);
+  else store_map<WTM, WTN, AFF, false, false>(p, acc, m0, n, half, sSc, sBi, off);
+}
+
+// int32 and / or fp32 output of a wave's tile: rows m0.., columns n0.. (row-major, or NCHW planes).
+template <int WTM, int WTN>
+__device__ __forceinline__ void store_maps(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n0, int lane,
+                                           const float *sSc, const float *sBi) {
+  const int half = lane >> 5;
+  const int n = n0 + WTN * (lane & 31);
+  if (m0 >= p.M || n >= p.N) return;
+  int64_t off[WTN];
+#pragma unroll
+  for (int j = 0; j < WTN; ++j) {
+    const int nc = min(n + j, p.N - 1);
+    off[j] = nc;
+    if (p.img_stride != 0) {  // NCHW planes
+      const uint32_t img = fdiv((uint32_t)nc, p.divOHW);
+      off[j] = (int64_t)img * p.img_stride + ((uint32_t)nc - img * p.OHW);
+    }
+  }
+  if (p.C) store_map_by<WTM, WTN, 0>(p, acc, m0, n, half, sSc, sBi, off);
+  if (p.Y && p.axis == BNN_CH_ROW) store_map_by<WTM, WTN, 1>(p, acc, m0, n, half, sSc, sBi, off);
+  else if (p.Y) store_map_by<WTM, WTN, 2>(p, acc, m0, n, half, sSc, sBi, off);
+}
+
+// nibble q of a 16-bit mask -> bits 8q .. 8q + 3
+__device__ __forceinline__ uint32_t spread_nibbles(uint32_t m) {
+  return (m & 0xFu) | ((m & 0xF0u) << 4) | ((m & 0xF00u) << 8) | ((m & 0xF000u) << 12);
+}
+
+// 64 channel bits of one column from the two row halves' bits (bit 16 i + 4 q + e of half h = row
+// 32 i + 8 q + 4 h + e).
+__device__ __forceinline__ uint64_t sign_word(uint32_t h0, uint32_t h1) {
+  const uint32_t lo = spread_nibbles(h0 & 0xFFFFu) | (spread_nibbles(h1 & 0xFFFFu) << 4);
+  const uint32_t hi = spread_nibbles(h0 >> 16) | (spread_nibbles(h1 >> 16) << 4);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// bits = 2 * bits + (fma(scale, v, bias) >= 0): rows are taken in descending order, one add-with-carry each.
+__device__ __forceinline__ void shift_in_sign(uint32_t &bits, float scale, float v, float bias) {
+  const float y = fmaf(scale, v, bias);
+  asm("v_cmp_le_f32 vcc, 0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(y) : "vcc");
+}
+
+// Binarizing epilogue: affine map, sign; packed NHWC words.  Tile rows are output channels, 64 of them
+// (WTM = 2): one word per output pixel.
+template <int WTM, int WTN, bool DEALT>
+__device__ __forceinline__ void store_signs(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n0, int lane,
+                                            const float *sSc, const float *sBi) {
+  static_assert(WTM == 2 && WTN % 2 == 0, "one 64-channel word per wave");
+  const int half = lane >> 5, l32 = lane & 31;
+  const int word = m0 >> 6;
+  if (word >= p.cw_out) return;  // wave-uniform
+  uint32_t bits[WTN];
+#pragma unroll
+  for (int j = 0; j < WTN; ++j) bits[j] = 0u;
+#pragma unroll
+  for (int i = 1; i >= 0; --i)
+#pragma unroll
+    for (int q = 3; q >= 0; --q) {
+      const float4 sc = *reinterpret_cast<const float4 *>(sSc + 32 * i + 8 * q + 4 * half);
+      const float4 bi = *reinterpret_cast<const float4 *>(sBi + 32 * i + 8 * q + 4 * half);
+#pragma unroll
+      for (int e = 3; e >= 0; --e)
+#pragma unroll
+        for (int j = 0; j < WTN; ++j) shift_in_sign(bits[j], (&sc.x)[e], acc.v[i][j][4 * q + e], (&bi.x)[e]);
+    }
+  // lanes l and l + 32 hold the two row halves of the same columns: the lower lanes assemble the first half of
+  // the columns, the upper lanes the second
+#pragma unroll
+  for (int j = 0; j < WTN / 2; ++j) {
+    const auto x = __builtin_amdgcn_permlane32_swap(bits[j], bits[j + WTN / 2], false, false);
+    const int jj = half ? j + WTN / 2 : j;
+    const int n = n0 + (DEALT ? WTN * l32 + jj : 32 * jj + l32);
+    if (n < p.N) p.outp[(int64_t)n * p.cw_out + word] = sign_word(x[0], x[1]);
+  }
+}
+
+// The same on the 2x2 maximum.  Columns are window-major: a lane of a 4-block wave holds whole windows, a
+// lane of a 2-block wave one row of a window, its neighbour the other.
+template <int WTM, int WTN>
+__device__ __forceinline__ void store_signs_pooled(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n0,
+                                                   int lane, const float *sSc, const float *sBi) {
+  static_assert(WTM == 2 && (WTN == 2 || WTN == 4), "one 64-channel word per wave");
+  const int half = lane >> 5, l32 = lane & 31;
+  const int word = m0 >> 6;
+  if (word >= p.cw_out) return;  // wave-uniform
+  uint32_t bits = 0u;
+#pragma unroll
+  for (int i = 1; i >= 0; --i)
+#pragma unroll
+    for (int q = 3; q >= 0; --q) {
+      const float4 sc = *reinterpret_cast<const float4 *>(sSc + 32 * i + 8 * q + 4 * half);
+      const float4 bi = *reinterpret_cast<const float4 *>(sBi + 32 * i + 8 * q + 4 * half);
+#pragma unroll
+      for (int e = 3; e >= 0; --e) {
+        const int r = 4 * q + e;
+        float m;
+        // the counts are finite: no need for the canonicalization that fmaxf brings
+        asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(acc.v[i][0][r]), "v"(acc.v[i][1][r]));
+        if constexpr (WTN == 4) {
+          asm("v_max3_f32 %0, %0, %1, %2" : "+v"(m) : "v"(acc.v[i][2][r]), "v"(acc.v[i][3][r]));
+        } else {
+          const float o = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(m), 0xB1, 0xF, 0xF, true));
+          asm("v_max_f32 %0, %0, %1" : "+v"(m) : "v"(o));
+        }
+        shift_in_sign(bits, (&sc.x)[e], m, (&bi.x)[e]);
+      }
+    }
+  const auto x = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
+  const int w = WTN == 4 ? (n0 >> 2) + l32 : (n0 >> 2) + (l32 >> 1);  // pooled pixel
+  if (half == 0 && (WTN == 4 || (l32 & 1) == 0) && w < (p.N >> 2))
+    p.outp[(int64_t)w * p.cw_out + word] = sign_word(x[0], x[1]);
+}
+
+}  // namespace bnn

@@ -1231,6 +1231,19 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
     if (lt <= (int64_t)p.n_cu) return launch_latency(p, emode, 4, s);
     if (p.g.pool && lt <= 2 * (int64_t)p.n_cu) return launch_latency(p, emode, 2, s);
   }
+  if ((cfg < 0 || (cfg >= 21 && cfg <= 24)) && fp4_applicable(p)) {
+    // The matrix cores, unless the outputs are so few that the kernels below, which split the reduction axis,
+    // occupy the chip better (256 x 1024 x 8192: 7.9 us there, 17 us here).
+    const int64_t t32 = (int64_t)((p.M + 31) / 32) * ((p.N + 127) / 128);
+    if (cfg >= 21 || bmode == 1 || t32 >= full) {
+      p.colperm = (emode == 0 && (p.N & 3) == 0 && (!p.C || (p.ldc & 3) == 0) && (!p.Y || (p.ldy & 3) == 0) &&
+                   (p.img_stride == 0 || ((p.OHW & 3u) == 0 && (p.img_stride & 3) == 0)))
+                      ? 1
+                      : 0;
+      return launch_gemm_fp4(p, bmode, emode, s, cfg >= 21 ? cfg - 21 : -1);
+    }
+  }
+  if (cfg >= 21) cfg = -1;
   if (bmode == 1 && tune.lean) {
     // lean gather: 16-byte pieces never straddle a tap (even Cw), one validity bit per tap in a
     // 32-bit mask, 32-bit byte offsets into the packed image

@@ -1,0 +1,537 @@
+// Xnor-Bitcount GEMM (section 3.2) and implicit-GEMM convolution on the matrix cores, operands kept
+// at 1 bit per value in memory and in LDS.
+//
+// sum_k a_k * b_k over +-1 values IS K - 2 * popcount(a XOR b), and V_MFMA_F32_32X32X64_F8F6F4 with both
+// operands in E2M1 adds 64 such products per output and instruction, exactly in its fp32 accumulator while
+// the sum stays below 2^24.  What decides the speed is turning bits into E2M1 codes: a code is 4 bits,
+// sign first, so with x a dword of 32 bits,  (x << s) & 0x88888888 | 0x22222222  (s = 0..3) are four dwords
+// of eight codes +1.0 (0x2, bit 0) or -1.0 (0xA, bit 1): 3 shifts + 4 bit-field inserts per 32 values.
+// (The signs of both operands are flipped against section 3.1's convention; the products are not.)  The
+// order of the values within a dword changes, alike for both operands, which a sum does not see.
+//
+// Bound: the matrix instructions, with the expansion beside them.  A wave multiplies 32*WTM x 32*WTN
+// outputs; per 64 values it needs WTM + WTN expanded fragments (7 vector instructions each) for
+// WTM * WTN matrix instructions, so tall wave tiles matter: from registers, with the expansion, 2 x 4
+// blocks sustain 8.0 PFLOP/s, 2 x 2 7.5, 1 x 4 6.6, and 9.6 without any expansion.  Expanding in the wave
+// that uses a fragment, not when staging it, keeps LDS and its traffic at 1 bit per value, and the
+// operand traffic from the L2s, which bounds a GEMM on operands stored at 4 bits, falls by 4.
+//
+// Values past the end of a row are staged as 0 bits in both operands: each adds (+1)(+1), so the
+// accumulators start at -(padded length - K) and end at the result.
+//
+// Lanes of a 32 x 32 block: operand fragments hold row (or column) l % 32 of the block, 64-bit word l / 32
+// of the 128-bit piece, one dword of it per instruction; the accumulator's register r holds row
+// 8*(r/4) + 4*(l/32) + r%4 of column l % 32.  Column block j, lane l of a wave is tile column WTN*(l%32)+j:
+// a lane's WTN columns are consecutive and leave as one 16- or 8-byte store per row, and with columns
+// ordered window-major (column = 4 * window + member) a lane of a 4-block wave holds whole pooling windows.
+#include <algorithm>
+
+#include "common.h"
+#include "fp4_tile.h"
+
+namespace bnn {
+
+// Where operand B comes from.
+//   GM_EXPL16 / GM_EXPL8  explicit rows, read with 16-byte / 8-byte loads
+//   GM_HALO   packed NHWC image; the input pixels that the tile's output pixels see (halo and padding
+//             included) are copied to LDS once and every tap reads them there at a uniform distance
+//   GM_ANY    packed NHWC image, every word of every patch gathered from memory (regions that do not fit LDS)
+// GM_HALO against gathering per tap through staged tiles: the gather decodes a tap, tests a mask and pads
+// every 16 bytes kH*kW times over, about 200 vector instructions per 512 bits of K beside the 336 of the
+// expansion.
+enum : int { GM_EXPL16 = 0, GM_EXPL8 = 1, GM_HALO = 2, GM_ANY = 3 };
+// What leaves: int32 / fp32 maps; packed signs; packed signs of the 2x2 maximum.
+enum : int { EM_MAPS = 0, EM_SIGN = 1, EM_POOL = 2 };
+
+template <int WTM_, int WTN_, int WGM_, int WGN_, int GM_>
+struct Fp4Cfg {
+  static constexpr int WTM = WTM_, WTN = WTN_, WGM = WGM_, WGN = WGN_, S = 4;  // S pieces (512 bits of K) per stage
+  static constexpr int T = 64 * WGM * WGN;
+  static constexpr int BM = 32 * WTM * WGM, BN = 32 * WTN * WGN;
+  static constexpr bool STAGEB = GM_ != GM_HALO;
+  static constexpr int REGS = BM / 32 + (STAGEB ? BN / 32 : 0);  // 32-row regions of 16-byte pieces
+  static constexpr int R16 = 33;                                 // region stride in 16-byte units (one of padding)
+  // plane (one piece of every row) stride = 2 mod 8 units: the four pieces of consecutive rows that a
+  // staging wave writes then fall on distinct banks
+  static constexpr int P16 = REGS * R16 + ((2 - REGS * R16) % 8 + 8) % 8;
+  static constexpr int PA = BM * S / T, PB = STAGEB ? BN * S / T : 0;  // pieces per thread and stage
+  static constexpr int STAGE_BYTES = 3 * S * P16 * 16;
+  static constexpr int FIXED_BYTES = STAGE_BYTES + 2 * BM * 4 + (GM_ == GM_HALO ? BN * 4 : 0);
+  static_assert(BM * S % T == 0 && BN * S % T == 0 && T % S == 0, "staging must divide evenly");
+};
+
+// Output pixel of GEMM column n: image, row and column of the map.
+__device__ __forceinline__ void column_pixel(const ConvGeom &g, uint32_t n, bool pool, uint32_t &img, uint32_t &oh,
+                                             uint32_t &ow) {
+  if (!pool) {
+    const uint32_t t = fdiv(n, g.divOW);
+    ow = n - t * (uint32_t)g.OW;
+    img = fdiv(t, g.divOH);
+    oh = t - img * (uint32_t)g.OH;
+  } else {  // window-major: column = 4 * window + member
+    const uint32_t j = n & 3u, w = n >> 2;
+    const uint32_t t = fdiv(w, g.divOW);
+    ow = 2u * (w - t * (uint32_t)(g.OW >> 1)) + (j & 1u);
+    img = fdiv(t, g.divOH);
+    oh = 2u * (t - img * (uint32_t)(g.OH >> 1)) + (j >> 1);
+  }
+}
+
+// Copies the input rows 0 .. rows - 1 of a tile's region to LDS planes [word][pixel]; taps outside the image are
+// +1 in every real channel.  EVEN: words per pixel in pairs, 16-byte loads.  A lane keeps one word pair of one
+// region column and the workgroup's waves walk the rows, so that what depends on the row is uniform (scalar unit)
+// and eight loads are in flight per lane.
+template <int T, bool EVEN>
+__device__ __forceinline__ void load_region(const ConvGeom &g, const HaloGeom &hg, char *sReg, int i0, int ih_first, int rows0,
+                                            int rows, uint64_t part, int wave, int lane) {
+  constexpr int NW = T / 64, BATCH = 8;
+  const int rowitems = hg.Wp * hg.ppp;
+  const size_t rowbytes = (size_t)g.W * (size_t)g.Cw * 8u;
+#pragma unroll 1
+  for (int ch = 0; ch < hg.nch; ++ch) {
+    const int idx = ch * 64 + lane;
+    const uint32_t px = fdiv((uint32_t)idx, hg.divPpp), cw = 2u * ((uint32_t)idx - px * (uint32_t)hg.ppp);
+    const int iw = (int)px - g.pW;
+    const bool cok = iw >= 0 && iw < g.W;
+    const bool two = EVEN || cw + 1u < (uint32_t)g.Cw;
+    const uint32_t off = ((cok ? (uint32_t)iw : 0u) * (uint32_t)g.Cw + cw) * 8u;
+    const uint64_t p0 = cw + 1u == (uint32_t)g.Cw ? part : ~0ull, p1 = cw + 2u == (uint32_t)g.Cw ? part : ~0ull;
+    char *const dst = sReg + cw * hg.plane + px * 8u;
+#pragma unroll 1
+    for (int r0 = wave; r0 < rows; r0 += BATCH * NW) {
+      u32x4 v[BATCH];
+      uint32_t rok = 0u;
+#pragma unroll
+      for (int b = 0; b < BATCH; ++b) {
+        const int r = min(r0 + b * NW, rows - 1);  // past the end: the last row again
+        // image of the row: i0, then `full` rows of each image that follows (branch-free; host: full >= 2)
+        const int t = max(r - rows0, 0);
+        const uint32_t h = __umulhi((uint32_t)t, hg.divFull.mul);
+        const int k = (int)((h + (((uint32_t)t - h) >> 1)) >> hg.divFull.shift);
+        const bool first = r < rows0;
+        const int ih = first ? ih_first + r : t - k * hg.full - g.pH;
+        const int img = first ? i0 : i0 + 1 + k;
+        const bool ok = ih >= 0 && ih < g.H;
+        rok |= (uint32_t)ok << b;
+        const char *src = reinterpret_cast<const char *>(g.act) + ((size_t)img * (size_t)g.H + (size_t)(ok ? ih : 0)) * rowbytes;
+        if constexpr (EVEN) {
+          v[b] = *reinterpret_cast<const u32x4 *>(src + off);
+        } else {
+          v[b].lo = *reinterpret_cast<const u32x2 *>(src + off);
+          v[b].hi = *reinterpret_cast<const u32x2 *>(src + off + (two ? 8u : 0u));
+        }
+      }
+#pragma unroll
+      for (int b = 0; b < BATCH; ++b) {
+        const int r = min(r0 + b * NW, rows - 1);
+        const bool ok = cok && ((rok >> b) & 1u);
+        u32x4 x = v[b];
+        x.x = ok ? x.x : (uint32_t)p0;
+        x.y = ok ? x.y : (uint32_t)(p0 >> 32);
+        x.z = ok ? x.z : (uint32_t)p1;
+        x.w = ok ? x.w : (uint32_t)(p1 >> 32);
+        char *const d = dst + (uint32_t)r * (uint32_t)hg.Wp * 8u;
+        if (idx < rowitems) {
+          *reinterpret_cast<u32x2 *>(d) = x.lo;
+          if (two) *reinterpret_cast<u32x2 *>(d + hg.plane) = x.hi;
+        }
+      }
+    }
+  }
+}
+
+template <int WTM, int WTN, int WGM, int WGN, int GM, int EMODE, int MINW>
+__global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(GemmParams p) {
+  using Cfg = Fp4Cfg<WTM, WTN, WGM, WGN, GM>;
+  constexpr int T = Cfg::T, BM = Cfg::BM, BN = Cfg::BN, PA = Cfg::PA, PB = Cfg::PB, S = Cfg::S;
+  constexpr bool POOL = EMODE == EM_POOL;
+  // columns of a wave dealt to (block j, lane l): WTN * l + j, so that a lane's columns are consecutive; signs
+  // from an LDS region take 32 * j + l (lanes on consecutive pixels: no bank conflicts)
+  constexpr bool DEALT = !(GM == GM_HALO && EMODE == EM_SIGN);
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  float *const sSc = reinterpret_cast<float *>(smem + Cfg::STAGE_BYTES);
+  float *const sBi = sSc + BM;
+  uint32_t *const sCol = reinterpret_cast<uint32_t *>(sBi + BM);      // GM_HALO: region offset of every column
+  char *const sReg = smem + Cfg::FIXED_BYTES;                           // GM_HALO: [word][pixel] 8-byte words
+  uint32_t *const sOff = reinterpret_cast<uint32_t *>(sReg + p.halo.bytes);  // GM_HALO: distance of every word of a row
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;
+
+  // ---- tile: row tiles of one column tile are neighbours, and each XCD gets a contiguous run ----------
+  const uint32_t nwg = gridDim.x;
+  uint32_t bid = blockIdx.x;
+  {
+    const uint32_t q = nwg >> 3, r = nwg & 7u, xcd = bid & 7u, i = bid >> 3;
+    bid = xcd * q + min(xcd, r) + i;
+  }
+  const int mi = (int)(bid % (uint32_t)p.tilesM), ni = (int)(bid / (uint32_t)p.tilesM);
+  const int m0 = mi * BM, n0 = ni * BN;
+  const ConvGeom &g = p.g;
+  const HaloGeom &hg = p.halo;
+
+  // ---- staging: thread t moves piece t % S of rows t / S, + T / S, ... --------------------------------
+  const int pc = tid % S;           // this thread's piece of every stage
+  const int row0 = tid / S;
+  const int npieces = (p.Kw64 + 1) >> 1;
+  const int nst = (npieces + S - 1) / S;
+  uint32_t aoff[PA];                // byte offset of the row (host: operand A is at most 4 GiB)
+#pragma unroll
+  for (int i = 0; i < PA; ++i) aoff[i] = (uint32_t)min(m0 + row0 + i * (T / S), p.M - 1) * ((uint32_t)p.lda32 * 4u);
+  u32x4 ra[PA];
+  const bool a16 = GM == GM_EXPL16 || (GM >= GM_HALO && p.b_vec16);  // uniform: whole 16-byte pieces of A
+  auto load_a = [&](int st) {
+    const int e = st * S + pc;  // piece of the row: words 2e, 2e + 1
+    const char *ab = reinterpret_cast<const char *>(p.A);
+    if (a16) {
+      const uint32_t eo = (uint32_t)min(e, (p.Kw64 >> 1) - 1) * 16u;
+#pragma unroll
+      for (int i = 0; i < PA; ++i) ra[i] = *reinterpret_cast<const u32x4 *>(ab + (aoff[i] + eo));
+    } else {
+      const uint32_t w0 = (uint32_t)min(2 * e, p.Kw64 - 1) * 8u, w1 = (uint32_t)min(2 * e + 1, p.Kw64 - 1) * 8u;
+#pragma unroll
+      for (int i = 0; i < PA; ++i) {
+        ra[i].lo = *reinterpret_cast<const u32x2 *>(ab + (size_t)aoff[i] + w0);
+        ra[i].hi = *reinterpret_cast<const u32x2 *>(ab + (size_t)aoff[i] + w1);
+      }
+    }
+  };
+  load_a(0);
+
+  // staged B (explicit rows, or patches gathered word by word)
+  constexpr int NB = PB > 0 ? PB : 1;
+  const char *brow[NB];   // explicit row, or the pixel's image
+  int bih[NB], biw[NB];   // GM_ANY: pixel under tap (0, 0)
+  u32x4 rb[NB];
+#pragma unroll
+  for (int i = 0; i < PB; ++i) {
+    const int n = min(n0 + row0 + i * (T / S), p.N - 1);  // columns past N recompute column N - 1
+    if constexpr (GM == GM_ANY) {
+      uint32_t img, oh, ow;
+      column_pixel(g, (uint32_t)n, POOL, img, oh, ow);
+      brow[i] = reinterpret_cast<const char *>(g.act + (size_t)img * (size_t)g.H * (size_t)g.W * (size_t)g.Cw);
+      bih[i] = (int)oh * g.sH - g.pH;
+      biw[i] = (int)ow * g.sW - g.pW;
+    } else {
+      brow[i] = reinterpret_cast<const char *>(p.B) + (size_t)n * (size_t)p.ldb * 8u;
+    }
+  }
+  const uint64_t part = (g.C & 63) ? (1ull << (g.C & 63)) - 1ull : ~0ull;  // real channels of a tap's last word
+  auto load_b = [&](int st) {
+    const int e = st * S + pc;
+    if constexpr (GM == GM_EXPL16) {
+      const uint32_t eo = (uint32_t)min(e, (p.Kw64 >> 1) - 1) * 16u;
+#pragma unroll
+      for (int i = 0; i < PB; ++i) rb[i] = *reinterpret_cast<const u32x4 *>(brow[i] + eo);
+    } else if constexpr (GM == GM_EXPL8) {
+      const uint32_t w0 = (uint32_t)min(2 * e, p.Kw64 - 1) * 8u, w1 = (uint32_t)min(2 * e + 1, p.Kw64 - 1) * 8u;
+#pragma unroll
+      for (int i = 0; i < PB; ++i) {
+        rb[i].lo = *reinterpret_cast<const u32x2 *>(brow[i] + w0);
+        rb[i].hi = *reinterpret_cast<const u32x2 *>(brow[i] + w1);
+      }
+    } else if constexpr (GM == GM_ANY) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t w = (uint32_t)min(2 * e + h, p.Kw64 - 1);
+        const uint32_t tap = fdiv(w, g.divCw), cw = w - tap * (uint32_t)g.Cw;
+        const uint32_t kh = fdiv(tap, g.divKW), kw = tap - kh * (uint32_t)g.kW;
+        const uint64_t pad = cw + 1u == (uint32_t)g.Cw ? part : ~0ull;  // taps outside the image: +1 in every channel
+#pragma unroll
+        for (int i = 0; i < PB; ++i) {
+          const int ih = bih[i] + (int)kh, iw = biw[i] + (int)kw;
+          u32x2 v = {(uint32_t)pad, (uint32_t)(pad >> 32)};
+          if (ih >= 0 && ih < g.H && iw >= 0 && iw < g.W)
+            v = *reinterpret_cast<const u32x2 *>(brow[i] + (((size_t)ih * (size_t)g.W + (size_t)iw) * (size_t)g.Cw + cw) * 8u);
+          if (h == 0) rb[i].lo = v;
+          else rb[i].hi = v;
+        }
+      }
+    }
+  };
+  load_b(0);
+  // bits past the end of the row become 0 in both operands (last stage only)
+  auto mask_stage = [&](int st) {
+    const int e = st * S + pc;
+    u32x4 m;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const int left = p.Kbits - (4 * e + d) * 32;  // bits of this dword that exist (host: Kbits < 2^24)
+      m[d] = left >= 32 ? 0xffffffffu : (left <= 0 ? 0u : (1u << left) - 1u);
+    }
+#pragma unroll
+    for (int i = 0; i < PA; ++i) ra[i] &= m;
+#pragma unroll
+    for (int i = 0; i < PB; ++i) rb[i] &= m;
+  };
+  // registers -> LDS buffer; T / S rows apart is a constant distance in LDS
+  constexpr int RPT = T / S;  // rows between a thread's pieces
+  static_assert(RPT % 32 == 0 && (PB == 0 || (32 * WTN) % RPT == 0 || RPT % (32 * WTN) == 0), "constant LDS distances");
+  char *const wrA = smem + (pc * Cfg::P16 + (row0 >> 5) * Cfg::R16 + (row0 & 31)) * 16;
+  const int col0 = row0 % (32 * WTN);
+  char *const wrB = smem + (pc * Cfg::P16 + (BM / 32 + (row0 / (32 * WTN)) * WTN + col0 % WTN) * Cfg::R16 + col0 / WTN) * 16;
+  auto store_piece = [&](int i, uint32_t buf) {  // i < PA: A, else B
+    if (i < PA) {
+      *reinterpret_cast<u32x4 *>(wrA + buf + i * (RPT / 32) * Cfg::R16 * 16) = ra[i];
+    } else if (i < PA + PB) {
+      const int c = (i - PA) * RPT;  // columns from the first one
+      *reinterpret_cast<u32x4 *>(wrB + buf + ((c / (32 * WTN)) * WTN * Cfg::R16 + (c % (32 * WTN)) / WTN) * 16) = rb[i - PA];
+    }
+  };
+  // the tile's per-row scale / bias, requested now and written to LDS below; rows past M get the constants whose
+  // sign bit is 0
+  static_assert(BM <= T, "one row per thread");
+  const bool affine = EMODE != EM_MAPS || (p.Y && p.axis == BNN_CH_ROW);  // uniform
+  float fsc = 0.0f, fbi = -1.0f;
+  if (affine && tid < BM && m0 + tid < p.M) {
+    fsc = p.scale[m0 + tid];
+    fbi = p.bias[m0 + tid];
+  }
+
+  // ---- GM_HALO: the tile's input region -> LDS -----------------------------------------------------------
+  // A unit is an output row (pooled: a pair of them).  An image's units of this tile need consecutive input
+  // rows; images follow each other in LDS.  Region row 0 is input row ih_first of image i0.
+  if constexpr (GM == GM_HALO) {
+    const int nlast = min(n0 + BN, p.N) - 1;
+    uint32_t i0, oh0, ow0, i1, oh1, ow1;
+    column_pixel(g, (uint32_t)n0, POOL, i0, oh0, ow0);
+    column_pixel(g, (uint32_t)nlast, POOL, i1, oh1, ow1);
+    const int u0 = (int)oh0 >> (POOL ? 1 : 0), u1 = (int)oh1 >> (POOL ? 1 : 0);
+    const int ulast0 = i0 == i1 ? u1 : hg.units - 1;           // last unit of the first image
+    const int rows0 = (ulast0 - u0) * hg.ustep + hg.uspan;      // its input rows
+    const int rows = i0 == i1 ? rows0
+                              : rows0 + ((int)(i1 - i0) - 1) * hg.full + u1 * hg.ustep + hg.uspan;
+    const int ih_first = u0 * hg.ustep - g.pH;
+    if ((g.Cw & 1) == 0) load_region<T, true>(g, hg, sReg, (int)i0, ih_first, rows0, rows, part, wave, lane);
+    else load_region<T, false>(g, hg, sReg, (int)i0, ih_first, rows0, rows, part, wave, lane);
+    // distance of every word of a patch row from the same lane's pixel under tap (0, 0)
+    for (int w = tid; w < 2 * npieces; w += T) {
+      const uint32_t tap = fdiv((uint32_t)w, g.divCw), cw = (uint32_t)w - tap * (uint32_t)g.Cw;
+      const uint32_t kh = fdiv(tap, g.divKW), kw = tap - kh * (uint32_t)g.kW;
+      sOff[w] = w < p.Kw64 ? cw * hg.plane + (kh * (uint32_t)hg.Wp + kw) * 8u : (uint32_t)g.Cw * hg.plane;
+    }
+    // rows of an odd number of words end in the middle of a piece: the missing word is read from a plane of zeros
+    if (p.Kw64 & 1)
+      for (uint32_t i = (uint32_t)tid * 8u; i < hg.plane; i += T * 8u)
+        *reinterpret_cast<u32x2 *>(sReg + (uint32_t)g.Cw * hg.plane + i) = u32x2{0u, 0u};
+    // region offset of every column's pixel under tap (0, 0)
+    for (int c = tid; c < BN; c += T) {
+      uint32_t img, oh, ow;
+      column_pixel(g, (uint32_t)min(n0 + c, p.N - 1), POOL, img, oh, ow);
+      // row of the pixel's tap (0, 0) inside its image's part of the region
+      const int r = img == i0 ? (int)oh * g.sH - u0 * hg.ustep
+                              : rows0 + (int)(img - i0 - 1u) * hg.full + (int)oh * g.sH;
+      sCol[c] = (uint32_t)(r * hg.Wp + (int)ow * g.sW) * 8u;
+    }
+  }
+
+  if (affine && tid < BM) {
+    sSc[tid] = fsc;
+    sBi[tid] = fbi;
+  }
+
+  Fp4Acc<WTM, WTN> acc;
+  acc.init(-(float)(npieces * 128 - p.Kformula));
+
+  // Stage st sits in LDS buffer st % 3.  It is written during piece 0 of the stage before it, a barrier stands
+  // between pieces 1 and 2, and piece 3 already reads ahead into the next stage; the buffer that a stage is
+  // written to was last read two stages ago, before the previous barrier.
+  constexpr uint32_t BUF = S * Cfg::P16 * 16;  // bytes of a buffer
+  const uint32_t fbase = (uint32_t)(lane & 31) * 16u + (uint32_t)(lane >> 5) * 8u;
+  const char *const fragA = smem + fbase + (uint32_t)(wm * WTM * Cfg::R16) * 16u;
+  const char *const fragB = smem + fbase + (uint32_t)((BM / 32 + wn * WTN) * Cfg::R16) * 16u;
+  if (nst == 1) mask_stage(0);
+#pragma unroll
+  for (int i = 0; i < PA + PB; ++i) store_piece(i, 0u);
+  load_a(1);  // past the last stage: its last piece again, not used
+  load_b(1);
+  __syncthreads();
+  const char *regB[WTN];
+  const uint32_t *const offp = sOff + (lane >> 5);
+  uint32_t woff = 0u;  // GM_HALO: distance of this lane's word of the piece that is read next
+  if constexpr (GM == GM_HALO) {
+#pragma unroll
+    for (int j = 0; j < WTN; ++j)
+      regB[j] = sReg + sCol[wn * WTN * 32 + (DEALT ? WTN * (lane & 31) + j : 32 * j + (lane & 31))];
+  }
+  // fragment f of a piece: bits of the wave's row blocks, then of its column blocks
+  auto read_frag = [&](int f, uint32_t plane, u32x2(&a)[WTM], u32x2(&b)[WTN]) {
+    if (f < WTM) a[f] = *reinterpret_cast<const u32x2 *>(fragA + plane + f * Cfg::R16 * 16);
+    else if (GM == GM_HALO) b[f - WTM] = *reinterpret_cast<const u32x2 *>(regB[f - WTM] + woff);
+    else b[f - WTM] = *reinterpret_cast<const u32x2 *>(fragB + plane + (f - WTM) * Cfg::R16 * 16);
+  };
+  v8i ea[WTM], eb[WTN];         // expanded operands of the next 64 values
+  uint32_t ya[WTM], yb[WTN];    // bits of the 64 values after them
+  {
+    if constexpr (GM == GM_HALO) woff = offp[0];
+    u32x2 a[WTM], b[WTN];
+#pragma unroll
+    for (int f = 0; f < WTM + WTN; ++f) read_frag(f, 0u, a, b);
+    if constexpr (GM == GM_HALO) {
+      woff = offp[npieces > 1 ? 2 : 0];
+    }
+#pragma unroll
+    for (int i = 0; i < WTM; ++i) {
+      ea[i] = expand_e2m1(a[i].x);
+      ya[i] = a[i].y;
+    }
+#pragma unroll
+    for (int j = 0; j < WTN; ++j) {
+      eb[j] = expand_e2m1(b[j].x);
+      yb[j] = b[j].y;
+    }
+  }
+  uint32_t rbuf = 0u;  // byte offset of the stage's buffer
+#pragma unroll 1
+  for (int st = 0; st < nst; ++st) {
+    const uint32_t wbuf = rbuf == 2 * BUF ? 0u : rbuf + BUF;  // the next stage's
+    if (st + 2 == nst) mask_stage(st + 1);
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+      const int q = st * S + k;
+      if (k > 0 && q >= npieces) break;  // uniform; the first piece of a stage always exists
+      if (k == S / 2) __syncthreads();
+      constexpr int MM = WTM * WTN, FR = WTM + WTN;
+      u32x2 na[WTM], nb[WTN];  // the next piece (past the last one: whatever is there, not used)
+      const uint32_t next = k + 1 < S ? rbuf + (k + 1) * Cfg::P16 * 16 : wbuf;
+      v8i fa[WTM], fb[WTN];
+      multiply_and_expand<WTM, WTN>(acc, ea, eb, ya, yb, fa, fb, [&](int m) {
+#pragma unroll
+        for (int f = m * FR / MM; f < (m + 1) * FR / MM; ++f) read_frag(f, next, na, nb);
+      });
+      uint32_t xa[WTM], xb[WTN];
+#pragma unroll
+      for (int i = 0; i < WTM; ++i) {
+        xa[i] = na[i].x;
+        ya[i] = na[i].y;
+      }
+#pragma unroll
+      for (int j = 0; j < WTN; ++j) {
+        xb[j] = nb[j].x;
+        yb[j] = nb[j].y;
+      }
+      multiply_and_expand<WTM, WTN>(acc, fa, fb, xa, xb, ea, eb, [&](int m) {
+        if (k == 0) {  // the next stage's pieces, from registers
+#pragma unroll
+          for (int i = m * (PA + PB) / MM; i < (m + 1) * (PA + PB) / MM; ++i) store_piece(i, wbuf);
+        }
+        if (k == 1 && m == 0) {
+          load_a(st + 2);
+          load_b(st + 2);
+        }
+        if (GM == GM_HALO && m == MM / 2) woff = offp[2 * min(q + 2, npieces - 1)];
+      });
+    }
+    rbuf = wbuf;
+  }
+
+  settle(acc);
+  const int mw = m0 + 32 * WTM * wm, nw = n0 + 32 * WTN * wn;
+  const float *sc = sSc + 32 * WTM * wm, *bi = sBi + 32 * WTM * wm;
+  if constexpr (EMODE == EM_MAPS) store_maps<WTM, WTN>(p, acc, mw, nw, lane, sc, bi);
+  else if constexpr (EMODE == EM_SIGN) store_signs<WTM, WTN, DEALT>(p, acc, mw, nw, lane, sc, bi);
+  else store_signs_pooled<WTM, WTN>(p, acc, mw, nw, lane, sc, bi);
+}
+
+// ---- host side -----------------------------------------------------------------------------------------
+template <int WTM, int WTN, int WGM, int WGN, int GM, int EMODE, int MINW>
+static bnn_status launch_fp4(GemmParams &p, hipStream_t s) {
+  using Cfg = Fp4Cfg<WTM, WTN, WGM, WGN, GM>;
+  p.tilesM = (p.M + Cfg::BM - 1) / Cfg::BM;
+  const int64_t tn = ((int64_t)p.N + Cfg::BN - 1) / Cfg::BN;
+  const int64_t blocks = p.tilesM * tn;
+  if (blocks > 0x7fffffffLL) return BNN_ERR_UNSUPPORTED;
+  p.tilesN = (int)tn;
+  const size_t lds = Cfg::FIXED_BYTES + (GM == GM_HALO ? (size_t)p.halo.bytes + (size_t)(p.Kw64 + 1) / 2 * 8 : 0);
+  ProfScope ps(KID_XNOR_GEMM_FP4, s);
+  hipLaunchKernelGGL((xnor_gemm_fp4_kernel<WTM, WTN, WGM, WGN, GM, EMODE, MINW>), dim3((unsigned)blocks), dim3(Cfg::T),
+                     lds, s, p);
+  return launch_status();
+}
+
+// Upper bound of the number of aligned-grid cells of length `cell` that a run of `len` columns starting at a
+// multiple of `len` touches.
+static int64_t cells_touched(int64_t len, int64_t cell) {
+  if (len % cell == 0) return len / cell;
+  if (cell % len == 0) return 1;
+  return (len - 2) / cell + 2;
+}
+
+// Fills p.halo for column tiles of bn; whether the region (and the table of word distances) is of a size to keep in LDS.
+static bool halo_region(GemmParams &p, int bn, bool pool) {
+  const ConvGeom &g = p.g;
+  HaloGeom &h = p.halo;
+  const int us = pool ? 2 : 1;
+  const int64_t Wp = (int64_t)(g.OW - 1) * g.sW + g.kW, units = g.OH / us, ustep = (int64_t)us * g.sH,
+                uspan = (int64_t)(us - 1) * g.sH + g.kH;
+  const int64_t full = (units - 1) * ustep + uspan;
+  const int64_t ucols = (int64_t)us * us * (g.OW / us);
+  const int64_t nu = cells_touched(bn, ucols);
+  const int64_t ni = std::min(nu, cells_touched(bn, ucols * units));
+  // the rows of nu units cut into 1 .. ni images: linear in the number of images, so largest at an end
+  const int64_t rows = std::max((nu - 1) * ustep + uspan, (nu - ni) * ustep + ni * uspan);
+  const int64_t ppp = (g.Cw + 1) / 2;
+  if (p.Kw64 > 4096 || rows > 4096 || Wp > 4096 || ppp > 64 || full < 2 || full > (1 << 24)) return false;
+  // plane stride in 8-byte words: the word pairs of one pixel that neighbouring lanes write fall on distinct banks
+  const int64_t plane8 = (rows * Wp + 31) / 32 * 32 + std::max<int64_t>(1, 16 / ppp);
+  const int64_t bytes = (plane8 * 8 * (g.Cw + (p.Kw64 & 1)) + 15) / 16 * 16;
+  if (bytes > 100 * 1024) return false;
+  h.Wp = (int)Wp; h.units = (int)units; h.ustep = (int)ustep; h.uspan = (int)uspan; h.full = (int)full;
+  h.ppp = (int)ppp;
+  h.nch = (int)((Wp * ppp + 63) / 64);
+  h.plane = (uint32_t)(plane8 * 8);
+  h.bytes = (uint32_t)bytes;
+  h.divNch = FastDiv((uint32_t)h.nch);
+  h.divPpp = FastDiv((uint32_t)h.ppp);
+  h.divFull = FastDiv((uint32_t)h.full);
+  return true;
+}
+
+template <int WTM, int WTN, int WGM, int WGN, int MINW>
+static bnn_status launch_fp4_shape(GemmParams &p, int bmode, int emode, hipStream_t s) {
+  using H = Fp4Cfg<WTM, WTN, WGM, WGN, GM_HALO>;
+  const int em = emode == 0 ? EM_MAPS : (p.g.pool ? EM_POOL : EM_SIGN);
+  if (bmode == 0) {
+    const bool v16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0 && p.ldb % 2 == 0;
+    if (em == EM_MAPS)
+      return v16 ? launch_fp4<WTM, WTN, WGM, WGN, GM_EXPL16, EM_MAPS, MINW>(p, s)
+                 : launch_fp4<WTM, WTN, WGM, WGN, GM_EXPL8, EM_MAPS, MINW>(p, s);
+    return BNN_ERR_UNSUPPORTED;
+  }
+  p.b_vec16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0;
+  if (halo_region(p, H::BN, em == EM_POOL)) {
+    if (em == EM_MAPS) return launch_fp4<WTM, WTN, WGM, WGN, GM_HALO, EM_MAPS, MINW>(p, s);
+    if (em == EM_SIGN) return launch_fp4<WTM, WTN, WGM, WGN, GM_HALO, EM_SIGN, MINW>(p, s);
+    return launch_fp4<WTM, WTN, WGM, WGN, GM_HALO, EM_POOL, MINW>(p, s);
+  }
+  if (em == EM_MAPS) return launch_fp4<WTM, WTN, WGM, WGN, GM_ANY, EM_MAPS, MINW>(p, s);
+  if (em == EM_SIGN) return launch_fp4<WTM, WTN, WGM, WGN, GM_ANY, EM_SIGN, MINW>(p, s);
+  return launch_fp4<WTM, WTN, WGM, WGN, GM_ANY, EM_POOL, MINW>(p, s);
+}
+
+bool fp4_applicable(const GemmParams &p) {
+  // exact fp32 counts: every partial sum is below 2^24 in magnitude
+  return (int64_t)((p.Kw64 + 1) / 2) * 128 < (1 << 24);
+}
+
+bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, int shape) {
+  if (shape < 0) {
+    // 128 x 256 tiles of 64 x 128 per wave need the fewest expansions per matrix instruction and win once every
+    // compute unit gets two of them (128 x 262144 x 1152 pooled: 23.8 us against 24.6 to 26.4; 256 x 65536 x 2304:
+    // 17.1 against 19.3 to 20.5); with fewer, the same tile on eight waves while every unit gets one
+    // (512 x 16384 x 2304: 12.2 against 12.8; 4608: 18.5 = 18.5), then 128 x 128 (a quarter of that batch:
+    // 10.2 against 13.3 and 14.0 against 18.9).  Up to 64 rows there is only one row of 64 x 256 tiles to fill
+    // (64 x 100352 x 576: 7.6 against 10.2).
+    const int64_t t = (((int64_t)p.M + 127) / 128) * (((int64_t)p.N + 255) / 256);
+    shape = p.M <= 64 ? 3 : t >= 2 * (int64_t)p.n_cu ? 0 : t >= (int64_t)p.n_cu ? 1 : 2;
+  }
+  switch (shape) {
+    case 0: return launch_fp4_shape<2, 4, 2, 2, 2>(p, bmode, emode, s);  // 128 x 256, 4 waves of 64 x 128
+    case 1: return launch_fp4_shape<2, 2, 2, 4, 2>(p, bmode, emode, s);  // 128 x 256, 8 waves of 64 x 64
+    case 2: return launch_fp4_shape<2, 2, 2, 2, 3>(p, bmode, emode, s);  // 128 x 128, 4 waves of 64 x 64
+    default: return launch_fp4_shape<2, 2, 1, 4, 2>(p, bmode, emode, s); // 64 x 256, 4 waves of 64 x 64
+  }
+}
+
+}  // namespace bnn

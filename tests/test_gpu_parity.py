@@ -1059,3 +1059,62 @@ def test_heuristic_kernel_selection_on_random_packed_convs():
         got = as_u64(B.bnn_conv2d_packed(xp, wp, C, D, k, k, (1, 1), (p, p), pool=2, scale=dev(sc),
                                          bias=dev(d["bias"]), out="packed"))
         assert np.array_equal(got, oracle.pack_nhwc(oracle.scale_bias(oracle.maxpool2x2_i32(ref), sc, d["bias"], "nchw")))
+
+
+# ---------------------------------------------------------------- matrix-core GEMM on packed operands
+@pytest.mark.parametrize("cfg", [21, 22, 23, 24])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (129, 257, 128), (128, 256, 512), (65, 300, 129), (37, 152, 640 + 33),
+                                   (200, 515, 1024), (64, 1028, 2321), (257, 130, 512 * 3 + 1)])
+def test_gemm_matrix_core_tiles(M, N, K, cfg):
+    """Edges of tiles and of the 512-bit stages, rows that end anywhere in a 128-bit piece; int32 and both
+    affine axes, padded strides.  Exact: the counts are integers below 2^24, the affine map one fma."""
+    print(f"gemm matrix core M={M} N={N} K={K} cfg={cfg}", flush=True)
+    _gemm_case(M, N, K, seed=M + 3 * N + 7 * K, cfg=cfg)
+    rng = np.random.default_rng(M + N + K)
+    A, Bm = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    ref = oracle.gemm_pm1(A, Bm)
+    Kw = B.packed_words(K)
+    Ap = torch.randint(-2**62, 2**62, (M, Kw + 1), dtype=torch.int64, device=DEV)  # odd or even stride, garbage past K
+    Bp = torch.randint(-2**62, 2**62, (N, Kw + 3), dtype=torch.int64, device=DEV)
+    Ap[:, :Kw], Bp[:, :Kw] = B.bnn_encode(dev(A)), B.bnn_encode(dev(Bm))
+    for axis, n in ((B.CH_ROW, M), (B.CH_COL, N)):
+        sc, bi = inputs.rand_scale(n, inputs._gen(K)), inputs.rand_bias(n, inputs._gen(K + 1))
+        C, Y = B.bnn_xnor_gemm_epilogue(Ap, Bp, K, dev(sc), dev(bi), axis, want_int=True, cfg=cfg)
+        assert np.array_equal(host(C), ref)
+        assert np.array_equal(host(Y), oracle.scale_bias(ref, sc, bi, "row" if axis == B.CH_ROW else "col"))
+
+
+MATRIX_CONV_CASES = [  # N, C, H, W, D, kH, kW, sH, sW, pH, pW
+    (3, 64, 9, 7, 70, 3, 3, 1, 1, 1, 1),      # one word per pixel: the row ends in the middle of a piece
+    (2, 200, 12, 12, 130, 3, 3, 1, 1, 1, 1),  # pad bits inside a tap's last word
+    (40, 128, 4, 4, 128, 3, 3, 1, 1, 1, 1),   # many images per tile
+    (1, 128, 40, 130, 64, 3, 3, 1, 1, 1, 1),  # rows longer than half a tile
+    (2, 320, 17, 16, 65, 5, 3, 2, 1, 2, 0),   # strides and paddings that differ, odd words per pixel
+    (5, 256, 10, 6, 256, 3, 3, 2, 2, 1, 1),
+    (2, 128, 8, 8, 40, 1, 1, 1, 1, 0, 0),     # pointwise
+    (3, 40, 6, 8, 33, 1, 3, 1, 1, 0, 1),      # one row of taps
+    (1, 2048, 40, 60, 40, 3, 3, 1, 1, 1, 1),  # region larger than LDS: the general gather
+    (2, 65, 14, 14, 20, 7, 7, 1, 1, 3, 3),    # 49 taps
+]
+
+
+@pytest.mark.parametrize("cfg", [21, 22, 23, 24])
+@pytest.mark.parametrize("case", MATRIX_CONV_CASES)
+def test_conv_matrix_core_tiles(case, cfg):
+    """int32, fp32, signs and pooled signs against the oracle, bit for bit."""
+    N, C, H, W, D, kH, kW, sH, sW, pH, pW = case
+    print(f"conv matrix core {case} cfg={cfg}", flush=True)
+    d = inputs.conv_inputs(inputs.ConvShape(*case), seed=sum(case))
+    x = inputs.inject_specials(d["x"], 3, frac=0.001)
+    st, pd = (sH, sW), (pH, pW)
+    ref = oracle.conv2d_pm1(x, d["w"], st, pd)
+    xp, wp = _u64dev(oracle.pack_nhwc(x)), B.bnn_pack_conv_weight(dev(d["w"]))
+    sc, bi = dev(d["scale"]), dev(d["bias"])
+    run = lambda **kw: B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, scale=sc, bias=bi, cfg=cfg, **kw)
+    assert np.array_equal(host(run(out="i32")), ref)
+    yref = oracle.scale_bias(ref, d["scale"], d["bias"], "nchw")
+    assert np.array_equal(host(run(out="f32")), yref)
+    assert np.array_equal(host(run(out="packed")).view(np.uint64), oracle.pack_nhwc(yref))
+    if ref.shape[2] % 2 == 0 and ref.shape[3] % 2 == 0:
+        pref = oracle.pack_nhwc(oracle.scale_bias(oracle.maxpool2x2_i32(ref), d["scale"], d["bias"], "nchw"))
+        assert np.array_equal(host(run(out="packed", pool=2)).view(np.uint64), pref)
