@@ -29,7 +29,8 @@ extern "C" {
  *       the reduction axis split over 4 / 2 slices inside a workgroup); needs an even number of
  *       words per pixel
  *   21 .. 24  the matrix-core GEMM (packed operands, expanded to 4-bit floating point in the wave that
- *       multiplies them): 128 x 256 tiles on four waves, 128 x 256 on eight, 128 x 128, 64 x 256
+ *       multiplies them): 128 x 256 tiles on four waves, 128 x 256 on eight (both only with the packed epilogue),
+ *       128 x 128, 64 x 256
  *   10  the short-row kernel (rows of two or four words, four consecutive columns per lane,
  *       16-byte stores), 8 rows per wave;   11, 12  the same with 16 / 32 rows per wave
  * A value that a call cannot use (the packed epilogue needs a 32- or 64-row tile with two or

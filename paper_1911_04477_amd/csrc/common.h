@@ -118,6 +118,7 @@ struct GemmParams {
   FastDiv divOHW;
   int64_t img_stride;  // elements between images in C / Y
   int tilesM, tilesN;
+  FastDiv divTilesM;   // matrix-core GEMM only
   int prio_from;       // workgroups with id >= prio_from lower their wave priority as they advance through K
   int n_cu;            // compute units of the device (host only: launch heuristics)
   int nt_store;        // int32 / fp32 tile stores are line-aligned: use non-temporal stores

@@ -31,6 +31,8 @@
 
 namespace bnn {
 
+typedef const uint32_t __attribute__((address_space(4))) *cu32_args;
+
 // Where operand B comes from.
 //   GM_EXPL16 / GM_EXPL8  explicit rows, read with 16-byte / 8-byte loads
 //   GM_HALO   packed NHWC image; the input pixels that the tile's output pixels see (halo and padding
@@ -60,60 +62,74 @@ struct Fp4Cfg {
   static_assert(BM * S % T == 0 && BN * S % T == 0 && T % S == 0, "staging must divide evenly");
 };
 
+// fdiv without the branch on a divisor of 1 (uniform divisors: one select).
+__device__ __forceinline__ uint32_t fdiv_sel(uint32_t n, const FastDiv &f) {
+  const uint32_t t = __umulhi(n, f.mul);
+  const uint32_t q = (t + ((n - t) >> 1)) >> f.shift;
+  return f.d == 1 ? n : q;
+}
+
 // Output pixel of GEMM column n: image, row and column of the map.
 __device__ __forceinline__ void column_pixel(const ConvGeom &g, uint32_t n, bool pool, uint32_t &img, uint32_t &oh,
                                              uint32_t &ow) {
-  if (!pool) {
-    const uint32_t t = fdiv(n, g.divOW);
-    ow = n - t * (uint32_t)g.OW;
-    img = fdiv(t, g.divOH);
-    oh = t - img * (uint32_t)g.OH;
-  } else {  // window-major: column = 4 * window + member
-    const uint32_t j = n & 3u, w = n >> 2;
-    const uint32_t t = fdiv(w, g.divOW);
-    ow = 2u * (w - t * (uint32_t)(g.OW >> 1)) + (j & 1u);
-    img = fdiv(t, g.divOH);
-    oh = 2u * (t - img * (uint32_t)(g.OH >> 1)) + (j >> 1);
+  // window-major when pooling: column = 4 * window + member
+  const uint32_t j = pool ? n & 3u : 0u, w = pool ? n >> 2 : n;
+  const uint32_t PW = pool ? (uint32_t)g.OW >> 1 : (uint32_t)g.OW, PH = pool ? (uint32_t)g.OH >> 1 : (uint32_t)g.OH;
+  const uint32_t t = fdiv_sel(w, g.divOW);
+  ow = w - t * PW;
+  img = fdiv_sel(t, g.divOH);
+  oh = t - img * PH;
+  if (pool) {
+    ow = 2u * ow + (j & 1u);
+    oh = 2u * oh + (j >> 1);
   }
 }
 
 // Copies the input rows 0 .. rows - 1 of a tile's region to LDS planes [word][pixel]; taps outside the image are
 // +1 in every real channel.  EVEN: words per pixel in pairs, 16-byte loads.  A lane keeps one word pair of one
-// region column and the workgroup's waves walk the rows, so that what depends on the row is uniform (scalar unit)
-// and eight loads are in flight per lane.
-template <int T, bool EVEN>
+// region column, the workgroup's waves walk the rows, and up to BATCH loads are in flight per lane; what depends
+// on the row is decoded once, lane i for the wave's i-th row, and read back as scalars.  between() runs after the
+// first batch of loads has been issued: work that the loads' latency hides.
+template <int T, bool EVEN, class Between>
 __device__ __forceinline__ void load_region(const ConvGeom &g, const HaloGeom &hg, char *sReg, int i0, int ih_first, int rows0,
-                                            int rows, uint64_t part, int wave, int lane) {
+                                            int rows, uint64_t part, int wave, int lane, const Between &between) {
   constexpr int NW = T / 64, BATCH = 8;
   const int rowitems = hg.Wp * hg.ppp;
-  const size_t rowbytes = (size_t)g.W * (size_t)g.Cw * 8u;
+  const uint32_t rowbytes = (uint32_t)g.W * (uint32_t)g.Cw * 8u;
+  bool pending = true;
 #pragma unroll 1
-  for (int ch = 0; ch < hg.nch; ++ch) {
-    const int idx = ch * 64 + lane;
-    const uint32_t px = fdiv((uint32_t)idx, hg.divPpp), cw = 2u * ((uint32_t)idx - px * (uint32_t)hg.ppp);
-    const int iw = (int)px - g.pW;
-    const bool cok = iw >= 0 && iw < g.W;
-    const bool two = EVEN || cw + 1u < (uint32_t)g.Cw;
-    const uint32_t off = ((cok ? (uint32_t)iw : 0u) * (uint32_t)g.Cw + cw) * 8u;
-    const uint64_t p0 = cw + 1u == (uint32_t)g.Cw ? part : ~0ull, p1 = cw + 2u == (uint32_t)g.Cw ? part : ~0ull;
-    char *const dst = sReg + cw * hg.plane + px * 8u;
+  for (int rr = wave; rr < rows; rr += BATCH * NW) {
+    // lane i: the wave's i-th row of this batch
+    uint32_t alo, ahi, aok;
+    {
+      const int r = min(rr + lane * NW, rows - 1);
+      const int t = max(r - rows0, 0);  // rows past the first image's: `full` rows of each image that follows
+      const uint32_t h = __umulhi((uint32_t)t, hg.divFull.mul);
+      const int k = (int)((h + (((uint32_t)t - h) >> 1)) >> hg.divFull.shift);  // host: full >= 2
+      const bool first = r < rows0;
+      const int ih = first ? ih_first + r : t - k * hg.full - g.pH;
+      const uint32_t img = (uint32_t)(first ? i0 : i0 + 1 + k);
+      const bool ok = ih >= 0 && ih < g.H;
+      // host: image rows number fewer than 2^31
+      const uint64_t a = reinterpret_cast<uint64_t>(g.act) + (uint64_t)(img * (uint32_t)g.H + (uint32_t)(ok ? ih : 0)) * rowbytes;
+      alo = (uint32_t)a;
+      ahi = (uint32_t)(a >> 32);
+      aok = (uint32_t)(__ballot(ok) & ((1u << BATCH) - 1u));
+    }
 #pragma unroll 1
-    for (int r0 = wave; r0 < rows; r0 += BATCH * NW) {
+    for (int ch = 0; ch < hg.nch; ++ch) {
+      const int idx = ch * 64 + lane;
+      const uint32_t px = fdiv_sel((uint32_t)idx, hg.divPpp), cw = 2u * ((uint32_t)idx - px * (uint32_t)hg.ppp);
+      const int iw = (int)px - g.pW;
+      const bool cok = iw >= 0 && iw < g.W;
+      const bool two = EVEN || cw + 1u < (uint32_t)g.Cw;
+      const uint32_t off = ((cok ? (uint32_t)iw : 0u) * (uint32_t)g.Cw + cw) * 8u;
       u32x4 v[BATCH];
-      uint32_t rok = 0u;
 #pragma unroll
       for (int b = 0; b < BATCH; ++b) {
-        const int r = min(r0 + b * NW, rows - 1);  // past the end: the last row again
-        // image of the row: i0, then `full` rows of each image that follows (branch-free; host: full >= 2)
-        const int t = max(r - rows0, 0);
-        const uint32_t h = __umulhi((uint32_t)t, hg.divFull.mul);
-        const int k = (int)((h + (((uint32_t)t - h) >> 1)) >> hg.divFull.shift);
-        const bool first = r < rows0;
-        const int ih = first ? ih_first + r : t - k * hg.full - g.pH;
-        const int img = first ? i0 : i0 + 1 + k;
-        const bool ok = ih >= 0 && ih < g.H;
-        rok |= (uint32_t)ok << b;
-        const char *src = reinterpret_cast<const char *>(g.act) + ((size_t)img * (size_t)g.H + (size_t)(ok ? ih : 0)) * rowbytes;
+        if (b > 0 && rr + b * NW >= rows) break;  // uniform
+        const char *src = reinterpret_cast<const char *>(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)ahi, b) << 32) |
+                                                         (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)alo, b));
         if constexpr (EVEN) {
           v[b] = *reinterpret_cast<const u32x4 *>(src + off);
         } else {
@@ -121,16 +137,22 @@ __device__ __forceinline__ void load_region(const ConvGeom &g, const HaloGeom &h
           v[b].hi = *reinterpret_cast<const u32x2 *>(src + off + (two ? 8u : 0u));
         }
       }
+      if (pending) {
+        pending = false;
+        between();
+      }
+      const uint64_t p0 = cw + 1u == (uint32_t)g.Cw ? part : ~0ull, p1 = cw + 2u == (uint32_t)g.Cw ? part : ~0ull;
+      char *const dst = sReg + cw * hg.plane + px * 8u + (uint32_t)rr * (uint32_t)hg.Wp * 8u;
 #pragma unroll
       for (int b = 0; b < BATCH; ++b) {
-        const int r = min(r0 + b * NW, rows - 1);
-        const bool ok = cok && ((rok >> b) & 1u);
+        if (b > 0 && rr + b * NW >= rows) break;  // uniform
+        const bool ok = cok && ((aok >> b) & 1u);
         u32x4 x = v[b];
         x.x = ok ? x.x : (uint32_t)p0;
         x.y = ok ? x.y : (uint32_t)(p0 >> 32);
         x.z = ok ? x.z : (uint32_t)p1;
         x.w = ok ? x.w : (uint32_t)(p1 >> 32);
-        char *const d = dst + (uint32_t)r * (uint32_t)hg.Wp * 8u;
+        char *const d = dst + (uint32_t)(b * NW) * (uint32_t)hg.Wp * 8u;
         if (idx < rowitems) {
           *reinterpret_cast<u32x2 *>(d) = x.lo;
           if (two) *reinterpret_cast<u32x2 *>(d + hg.plane) = x.hi;
@@ -138,6 +160,7 @@ __device__ __forceinline__ void load_region(const ConvGeom &g, const HaloGeom &h
       }
     }
   }
+  if (pending) between();  // a wave without rows
 }
 
 template <int WTM, int WTN, int WGM, int WGN, int GM, int EMODE, int MINW>
@@ -148,6 +171,14 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
   // columns of a wave dealt to (block j, lane l): WTN * l + j, so that a lane's columns are consecutive; signs
   // from an LDS region take 32 * j + l (lanes on consecutive pixels: no bank conflicts)
   constexpr bool DEALT = !(GM == GM_HALO && EMODE == EM_SIGN);
+  // One dword of every 64-byte line of the arguments, requested at once: they arrive in one memory round trip
+  // instead of one per group of arguments that the code below happens to need next (each about 500 cycles).
+  {
+    const cu32_args ka = (cu32_args)__builtin_amdgcn_kernarg_segment_ptr();
+    constexpr int LINES = (int)((sizeof(GemmParams) + 63) / 64);
+    static_assert(LINES == 6, "list every line below");
+    asm volatile("" ::"s"(ka[0]), "s"(ka[16]), "s"(ka[32]), "s"(ka[48]), "s"(ka[64]), "s"(ka[80]));
+  }
   extern __shared__ __attribute__((aligned(16))) char smem[];
   float *const sSc = reinterpret_cast<float *>(smem + Cfg::STAGE_BYTES);
   float *const sBi = sSc + BM;
@@ -166,7 +197,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
     const uint32_t q = nwg >> 3, r = nwg & 7u, xcd = bid & 7u, i = bid >> 3;
     bid = xcd * q + min(xcd, r) + i;
   }
-  const int mi = (int)(bid % (uint32_t)p.tilesM), ni = (int)(bid / (uint32_t)p.tilesM);
+  const int ni = (int)fdiv_sel(bid, p.divTilesM), mi = (int)(bid - (uint32_t)ni * (uint32_t)p.tilesM);
   const int m0 = mi * BM, n0 = ni * BN;
   const ConvGeom &g = p.g;
   const HaloGeom &hg = p.halo;
@@ -293,39 +324,40 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
   // A unit is an output row (pooled: a pair of them).  An image's units of this tile need consecutive input
   // rows; images follow each other in LDS.  Region row 0 is input row ih_first of image i0.
   if constexpr (GM == GM_HALO) {
+    // lane 0 decodes the tile's first column, the others its last one
     const int nlast = min(n0 + BN, p.N) - 1;
-    uint32_t i0, oh0, ow0, i1, oh1, ow1;
-    column_pixel(g, (uint32_t)n0, POOL, i0, oh0, ow0);
-    column_pixel(g, (uint32_t)nlast, POOL, i1, oh1, ow1);
-    const int u0 = (int)oh0 >> (POOL ? 1 : 0), u1 = (int)oh1 >> (POOL ? 1 : 0);
+    uint32_t cimg, coh, cow;
+    column_pixel(g, (uint32_t)(lane == 0 ? n0 : nlast), POOL, cimg, coh, cow);
+    const int i0 = __builtin_amdgcn_readlane((int)cimg, 0), i1 = __builtin_amdgcn_readlane((int)cimg, 1);
+    const int u0 = __builtin_amdgcn_readlane((int)coh, 0) >> (POOL ? 1 : 0), u1 = __builtin_amdgcn_readlane((int)coh, 1) >> (POOL ? 1 : 0);
     const int ulast0 = i0 == i1 ? u1 : hg.units - 1;           // last unit of the first image
     const int rows0 = (ulast0 - u0) * hg.ustep + hg.uspan;      // its input rows
-    const int rows = i0 == i1 ? rows0
-                              : rows0 + ((int)(i1 - i0) - 1) * hg.full + u1 * hg.ustep + hg.uspan;
+    const int rows = i0 == i1 ? rows0 : rows0 + (i1 - i0 - 1) * hg.full + u1 * hg.ustep + hg.uspan;
     const int ih_first = u0 * hg.ustep - g.pH;
-    if ((g.Cw & 1) == 0) load_region<T, true>(g, hg, sReg, (int)i0, ih_first, rows0, rows, part, wave, lane);
-    else load_region<T, false>(g, hg, sReg, (int)i0, ih_first, rows0, rows, part, wave, lane);
-    // distance of every word of a patch row from the same lane's pixel under tap (0, 0)
-    for (int w = tid; w < 2 * npieces; w += T) {
-      const uint32_t tap = fdiv((uint32_t)w, g.divCw), cw = (uint32_t)w - tap * (uint32_t)g.Cw;
-      const uint32_t kh = fdiv(tap, g.divKW), kw = tap - kh * (uint32_t)g.kW;
-      sOff[w] = w < p.Kw64 ? cw * hg.plane + (kh * (uint32_t)hg.Wp + kw) * 8u : (uint32_t)g.Cw * hg.plane;
-    }
-    // rows of an odd number of words end in the middle of a piece: the missing word is read from a plane of zeros
-    if (p.Kw64 & 1)
-      for (uint32_t i = (uint32_t)tid * 8u; i < hg.plane; i += T * 8u)
-        *reinterpret_cast<u32x2 *>(sReg + (uint32_t)g.Cw * hg.plane + i) = u32x2{0u, 0u};
-    // region offset of every column's pixel under tap (0, 0)
-    for (int c = tid; c < BN; c += T) {
-      uint32_t img, oh, ow;
-      column_pixel(g, (uint32_t)min(n0 + c, p.N - 1), POOL, img, oh, ow);
-      // row of the pixel's tap (0, 0) inside its image's part of the region
-      const int r = img == i0 ? (int)oh * g.sH - u0 * hg.ustep
-                              : rows0 + (int)(img - i0 - 1u) * hg.full + (int)oh * g.sH;
-      sCol[c] = (uint32_t)(r * hg.Wp + (int)ow * g.sW) * 8u;
-    }
+    auto tables = [&]() {
+      // distance of every word of a patch row from the same lane's pixel under tap (0, 0)
+      for (int w = tid; w < 2 * npieces; w += T) {
+        const uint32_t tap = fdiv_sel((uint32_t)w, g.divCw), cw = (uint32_t)w - tap * (uint32_t)g.Cw;
+        const uint32_t kh = fdiv_sel(tap, g.divKW), kw = tap - kh * (uint32_t)g.kW;
+        sOff[w] = w < p.Kw64 ? cw * hg.plane + (kh * (uint32_t)hg.Wp + kw) * 8u : (uint32_t)g.Cw * hg.plane;
+      }
+      // rows of an odd number of words end in the middle of a piece: the missing word is read from a plane of zeros
+      if (p.Kw64 & 1)
+        for (uint32_t i = (uint32_t)tid * 8u; i < hg.plane; i += T * 8u)
+          *reinterpret_cast<u32x2 *>(sReg + (uint32_t)g.Cw * hg.plane + i) = u32x2{0u, 0u};
+      // region offset of every column's pixel under tap (0, 0)
+      for (int c = tid; c < BN; c += T) {
+        uint32_t img, oh, ow;
+        column_pixel(g, (uint32_t)min(n0 + c, p.N - 1), POOL, img, oh, ow);
+        // row of the pixel's tap (0, 0) inside its image's part of the region
+        const int r = (int)img == i0 ? (int)oh * g.sH - u0 * hg.ustep
+                                     : rows0 + ((int)img - i0 - 1) * hg.full + (int)oh * g.sH;
+        sCol[c] = (uint32_t)(r * hg.Wp + (int)ow * g.sW) * 8u;
+      }
+    };
+    if ((g.Cw & 1) == 0) load_region<T, true>(g, hg, sReg, i0, ih_first, rows0, rows, part, wave, lane, tables);
+    else load_region<T, false>(g, hg, sReg, i0, ih_first, rows0, rows, part, wave, lane, tables);
   }
-
   if (affine && tid < BM) {
     sSc[tid] = fsc;
     sBi[tid] = fbi;
@@ -443,6 +475,7 @@ static bnn_status launch_fp4(GemmParams &p, hipStream_t s) {
   const int64_t blocks = p.tilesM * tn;
   if (blocks > 0x7fffffffLL) return BNN_ERR_UNSUPPORTED;
   p.tilesN = (int)tn;
+  p.divTilesM = FastDiv((uint32_t)p.tilesM);
   const size_t lds = Cfg::FIXED_BYTES + (GM == GM_HALO ? (size_t)p.halo.bytes + (size_t)(p.Kw64 + 1) / 2 * 8 : 0);
   ProfScope ps(KID_XNOR_GEMM_FP4, s);
   hipLaunchKernelGGL((xnor_gemm_fp4_kernel<WTM, WTN, WGM, WGN, GM, EMODE, MINW>), dim3((unsigned)blocks), dim3(Cfg::T),
@@ -488,26 +521,30 @@ static bool halo_region(GemmParams &p, int bn, bool pool) {
   return true;
 }
 
-template <int WTM, int WTN, int WGM, int WGN, int MINW>
+// Signs leave from any shape; maps, and everything on explicit rows, from the two shapes of 64 x 64 outputs per wave
+// on four waves that win there (see below).
+template <int WTM, int WTN, int WGM, int WGN, int MINW, bool MAPS>
 static bnn_status launch_fp4_shape(GemmParams &p, int bmode, int emode, hipStream_t s) {
   using H = Fp4Cfg<WTM, WTN, WGM, WGN, GM_HALO>;
-  const int em = emode == 0 ? EM_MAPS : (p.g.pool ? EM_POOL : EM_SIGN);
-  if (bmode == 0) {
-    const bool v16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0 && p.ldb % 2 == 0;
-    if (em == EM_MAPS)
+  if constexpr (MAPS) {
+    if (bmode == 0) {
+      const bool v16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0 && p.ldb % 2 == 0;
       return v16 ? launch_fp4<WTM, WTN, WGM, WGN, GM_EXPL16, EM_MAPS, MINW>(p, s)
                  : launch_fp4<WTM, WTN, WGM, WGN, GM_EXPL8, EM_MAPS, MINW>(p, s);
-    return BNN_ERR_UNSUPPORTED;
+    }
   }
   p.b_vec16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0;
-  if (halo_region(p, H::BN, em == EM_POOL)) {
-    if (em == EM_MAPS) return launch_fp4<WTM, WTN, WGM, WGN, GM_HALO, EM_MAPS, MINW>(p, s);
-    if (em == EM_SIGN) return launch_fp4<WTM, WTN, WGM, WGN, GM_HALO, EM_SIGN, MINW>(p, s);
-    return launch_fp4<WTM, WTN, WGM, WGN, GM_HALO, EM_POOL, MINW>(p, s);
+  const bool halo = halo_region(p, H::BN, p.g.pool != 0);
+  if constexpr (MAPS) {
+    if (emode == 0)
+      return halo ? launch_fp4<WTM, WTN, WGM, WGN, GM_HALO, EM_MAPS, MINW>(p, s)
+                  : launch_fp4<WTM, WTN, WGM, WGN, GM_ANY, EM_MAPS, MINW>(p, s);
   }
-  if (em == EM_MAPS) return launch_fp4<WTM, WTN, WGM, WGN, GM_ANY, EM_MAPS, MINW>(p, s);
-  if (em == EM_SIGN) return launch_fp4<WTM, WTN, WGM, WGN, GM_ANY, EM_SIGN, MINW>(p, s);
-  return launch_fp4<WTM, WTN, WGM, WGN, GM_ANY, EM_POOL, MINW>(p, s);
+  if (p.g.pool)
+    return halo ? launch_fp4<WTM, WTN, WGM, WGN, GM_HALO, EM_POOL, MINW>(p, s)
+                : launch_fp4<WTM, WTN, WGM, WGN, GM_ANY, EM_POOL, MINW>(p, s);
+  return halo ? launch_fp4<WTM, WTN, WGM, WGN, GM_HALO, EM_SIGN, MINW>(p, s)
+              : launch_fp4<WTM, WTN, WGM, WGN, GM_ANY, EM_SIGN, MINW>(p, s);
 }
 
 bool fp4_applicable(const GemmParams &p) {
@@ -516,21 +553,33 @@ bool fp4_applicable(const GemmParams &p) {
 }
 
 bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, int shape) {
-  if (shape < 0) {
-    // 128 x 256 tiles of 64 x 128 per wave need the fewest expansions per matrix instruction and win once every
-    // compute unit gets two of them (128 x 262144 x 1152 pooled: 23.8 us against 24.6 to 26.4; 256 x 65536 x 2304:
-    // 17.1 against 19.3 to 20.5); with fewer, the same tile on eight waves while every unit gets one
-    // (512 x 16384 x 2304: 12.2 against 12.8; 4608: 18.5 = 18.5), then 128 x 128 (a quarter of that batch:
-    // 10.2 against 13.3 and 14.0 against 18.9).  Up to 64 rows there is only one row of 64 x 256 tiles to fill
-    // (64 x 100352 x 576: 7.6 against 10.2).
-    const int64_t t = (((int64_t)p.M + 127) / 128) * (((int64_t)p.N + 255) / 256);
-    shape = p.M <= 64 ? 3 : t >= 2 * (int64_t)p.n_cu ? 0 : t >= (int64_t)p.n_cu ? 1 : 2;
+  const bool maps = bmode == 0 || emode == 0;
+  if (shape < 0 || (maps && shape < 2)) {
+    const int64_t cu = p.n_cu, c256 = ((int64_t)p.N + 255) / 256;
+    const int64_t t = (((int64_t)p.M + 127) / 128) * c256, t64 = (((int64_t)p.M + 63) / 64) * c256;
+    if (p.M <= 64) {
+      // one row of tiles to fill (64 channels, 100352 pixels, K = 576: 7.0 us against 9.0 to 10.9)
+      shape = 3;
+    } else if (maps) {
+      // Stores of maps want many workgroups in different phases: 64 x 256 tiles, three to a compute unit, while every
+      // unit gets two of them (256 x 200704 x 2304 fp32 maps 64.2 us against 68.1 on 128 x 128 and 67.9 on 128 x 256 by
+      // four waves; 128 x 131072 x 1152: 16.6, 17.3, 17.7), else 128 x 128 (512 x 4096 x 2304: 9.9 against 10.3).
+      // Explicit rows stage B too, which the squarer tile halves (4096^3: 35.1 against 36.6 and 39.3).
+      shape = bmode == 1 && t64 >= 2 * cu ? 3 : 2;
+    } else {
+      // Signs leave little to store: 128 x 256 tiles of 64 x 128 per wave need the fewest expansions per matrix
+      // instruction and win once every compute unit gets two of them (128 x 262144 x 1152 pooled: 22.4 us against
+      // 23.8 to 25.5; 256 x 65536 x 2304: 16.8 against 18.7 to 19.7); with fewer, the same tile on eight waves
+      // while every unit gets one (512 x 16384 x 2304: 11.9 against 12.8; at K = 4608 18.4 against 17.6), then
+      // 128 x 128 (a quarter of that batch: 9.9 against 12.9 and 13.9 against 18.7).
+      shape = t >= 2 * cu ? 0 : t >= cu ? 1 : 2;
+    }
   }
   switch (shape) {
-    case 0: return launch_fp4_shape<2, 4, 2, 2, 2>(p, bmode, emode, s);  // 128 x 256, 4 waves of 64 x 128
-    case 1: return launch_fp4_shape<2, 2, 2, 4, 2>(p, bmode, emode, s);  // 128 x 256, 8 waves of 64 x 64
-    case 2: return launch_fp4_shape<2, 2, 2, 2, 3>(p, bmode, emode, s);  // 128 x 128, 4 waves of 64 x 64
-    default: return launch_fp4_shape<2, 2, 1, 4, 2>(p, bmode, emode, s); // 64 x 256, 4 waves of 64 x 64
+    case 0: return launch_fp4_shape<2, 4, 2, 2, 2, false>(p, bmode, emode, s);  // 128 x 256, 4 waves of 64 x 128
+    case 1: return launch_fp4_shape<2, 2, 2, 4, 2, false>(p, bmode, emode, s);  // 128 x 256, 8 waves of 64 x 64
+    case 2: return launch_fp4_shape<2, 2, 2, 2, 3, true>(p, bmode, emode, s);   // 128 x 128, 4 waves of 64 x 64
+    default: return launch_fp4_shape<2, 2, 1, 4, 2, true>(p, bmode, emode, s);  // 64 x 256, 4 waves of 64 x 64
   }
 }
 
