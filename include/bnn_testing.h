@@ -18,27 +18,22 @@ extern "C" {
 /*
  * Tile configurations of the Xnor-Bitcount GEMM (section 3.2), argument `cfg` below:
  *   -1  the size heuristic (what bnn.h's entry points use)
+ *   vector-ALU tiles (xor + popcount), which the size heuristic does not use:
  *    1  32 x 256 tile      2  32 x 64       3  64 x 256      4  32 x 128      6  64 x 128
- *    7  one wave per 8 x 64 tile, operand B read straight from memory (small problems)
- *    8  one wave per 8 x 128 tile, likewise
- *    9  as 7 with the reduction axis split over the four waves of a workgroup
- *   13 .. 18  long rows, few outputs: one wave per (8 * T) x 64 tile slice, B kept in registers
- *       across the T row groups, the reduction axis split over the S waves of a workgroup:
- *       (T, S) = (4, 4), (4, 8), (2, 8), (2, 4), (4, 2), (2, 2)
- *   19, 20  the latency form of the implicit-GEMM convolution (32 x 64 tiles, one column per lane,
- *       the reduction axis split over 4 / 2 slices inside a workgroup); needs an even number of
- *       words per pixel
  *   21 .. 24  the matrix-core GEMM (packed operands, expanded to 4-bit floating point in the wave that
  *       multiplies them): 128 x 256 tiles on four waves, 128 x 256 on eight (both only with the packed epilogue),
  *       128 x 128, 64 x 256
+ *   25 .. 28  the same for few outputs, the reduction axis split over the waves of a workgroup:
+ *       32 x 32 tiles split 4 / 8 ways, 64 x 64 tiles split 4 / 8 ways
  *   10  the short-row kernel (rows of two or four words, four consecutive columns per lane,
  *       16-byte stores), 8 rows per wave;   11, 12  the same with 16 / 32 rows per wave
  * A value that a call cannot use (the packed epilogue needs a 32- or 64-row tile with two or
- * four column groups, or one of 21 to 24; 7 to 18 exist for an explicit B with int32 / fp32 output only, 10 to 12
- * only where N, the leading dimensions and the pixels per image are multiples of 4) selects the
- * heuristic for that call.
- * `lean`: 1 = convolutions whose geometry allows it gather their patches with the table-driven
- * loader (what bnn.h's entry points do); 0 = always the general loader.
+ * four column groups, or one of 21 to 28; 10 to 12 exist for an explicit B with int32 / fp32 output only,
+ * where N, the leading dimensions and the pixels per image are multiples of 4; 21 to 24 need K below 2^24)
+ * selects the heuristic for that call, and so does any other value.
+ * `lean`: 1 = convolutions whose geometry allows it keep a tile's input region in LDS (matrix cores) or gather
+ * their patches with the table-driven loader (vector ALU), what bnn.h's entry points do; 0 = always the
+ * general gather.
  */
 
 /* bnn_xnor_gemm_epilogue (and, with Y == NULL, bnn_xnor_gemm) on tile configuration cfg. */

@@ -25,11 +25,11 @@ enum KernelId : int {
   KID_CONTROL_CONV_F32 = 13,
   KID_XNOR_GEMM_MFMA_FP4 = 14,
   KID_XNOR_GEMM_LOWK = 15,
-  KID_XNOR_CONV_LATENCY = 16,
   KID_EXPAND_FP4 = 17,
   KID_XNOR_GEMM_MFMA_FP4X = 18,
   KID_XNOR_GEMM_FP4 = 19,
-  KID_COUNT = 20
+  KID_XNOR_GEMM_FP4_SPLIT = 20,
+  KID_COUNT = 21
 };
 
 // Timing hook: records an event pair around a launch when profiling is on.
@@ -151,14 +151,13 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
 bool lowk_applicable(const GemmParams &p);
 bnn_status launch_lowk(GemmParams &p, int groups, hipStream_t s);
 
-// Latency form of the implicit-GEMM convolution (gemm_latency.hip): few output pixels, K split
-// over ks (2 or 4) slices inside a workgroup.  emode as for run_gemm.
-bool latency_applicable(const GemmParams &p);
-bnn_status launch_latency(GemmParams &p, int emode, int ks, hipStream_t s);
-
-// Matrix-core GEMM on packed operands (gemm_fp4.hip): bmode / emode as for run_gemm; shape: tile number.
+// Matrix-core GEMM on packed operands (gemm_fp4.hip): bmode / emode as for run_gemm; shape: tile number or -1;
+// region: convolutions may keep a tile's input region in LDS (false: always the general gather).
 bool fp4_applicable(const GemmParams &p);
-bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, int shape);
+bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, int shape, bool region);
+// The same with the reduction axis split over the waves of a workgroup, for few outputs (gemm_fp4_split.hip).
+bool fp4_split_applicable(const GemmParams &p);  // whether its rule on sizes takes the problem
+bnn_status launch_gemm_fp4_split(GemmParams &p, int bmode, int emode, hipStream_t s, int shape);
 
 // Conv helpers (im2col.hip).  check_conv_geometry validates shapes and 32-bit limits;
 // run_im2col launches encode (+ gather) with already validated arguments.

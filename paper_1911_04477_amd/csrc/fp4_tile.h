@@ -10,6 +10,29 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// fdiv without the branch on a divisor of 1 (uniform divisors: one select).
+__device__ __forceinline__ uint32_t fdiv_sel(uint32_t n, const FastDiv &f) {
+  const uint32_t t = __umulhi(n, f.mul);
+  const uint32_t q = (t + ((n - t) >> 1)) >> f.shift;
+  return f.d == 1 ? n : q;
+}
+
+// Output pixel of GEMM column n: image, row and column of the map.
+__device__ __forceinline__ void column_pixel(const ConvGeom &g, uint32_t n, bool pool, uint32_t &img, uint32_t &oh,
+                                             uint32_t &ow) {
+  // window-major when pooling: column = 4 * window + member
+  const uint32_t j = pool ? n & 3u : 0u, w = pool ? n >> 2 : n;
+  const uint32_t PW = pool ? (uint32_t)g.OW >> 1 : (uint32_t)g.OW, PH = pool ? (uint32_t)g.OH >> 1 : (uint32_t)g.OH;
+  const uint32_t t = fdiv_sel(w, g.divOW);
+  ow = w - t * PW;
+  img = fdiv_sel(t, g.divOH);
+  oh = t - img * PH;
+  if (pool) {
+    ow = 2u * ow + (j & 1u);
+    oh = 2u * oh + (j >> 1);
+  }
+}
+
 // 32 bits -> 32 E2M1 codes (bit 0: +1.0 = 0x2, bit 1: -1.0 = 0xA), value 4j + 3 - s in nibble j of dword s.
 // The bit-field insert is written out: the optimizer splits it into an and and an or with literals.
 __device__ __forceinline__ v8i expand_e2m1(uint32_t x) {

@@ -784,298 +784,6 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void xnor_gemm_kernel(GemmParam
 }
 
 
-// ---- small problems: one independent wave per 8 x (64*TN) tile, no LDS, no barrier -------------
-// When a problem has too few tiles to put two waves on every SIMD, the LDS-staged kernel is
-// bound by its per-chunk latency chain (global load -> LDS -> barrier).  Here every lane reads
-// its own columns' words straight from global memory into registers, DEPTH chunks ahead, and
-// the wave never synchronises with anyone.  A is fetched with scalar loads as above.
-// KS = 4: the four waves of a workgroup share ONE tile and split its K range (problems with
-// fewer tiles than SIMDs but long rows); their partial counts are summed through LDS.
-template <int TN, int DEPTH, int YIELD, int KS>
-__global__ __launch_bounds__(256) void xnor_gemm_direct_kernel(GemmParams p) {
-  static_assert(KS == 1 || KS == 4, "one tile per wave, or one per workgroup");
-  __shared__ int sRed[KS == 4 ? 3 * TM * TN * 64 : 1];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const uint32_t wid = KS == 4 ? blockIdx.x : blockIdx.x * 4u + (uint32_t)wave;  // tile index, M fastest
-  const int mi = (int)(wid % (uint32_t)p.tilesM);
-  const int ni = (int)(wid / (uint32_t)p.tilesM);
-  if (ni >= p.tilesN) return;
-  const int m0 = mi * TM;
-  const int nbase = ni * 64 * TN + lane;
-
-  uint32_t aoffb[TM];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    int m = m0 + i;
-    m = m < p.M ? m : p.M - 1;
-    aoffb[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)m * (uint32_t)p.lda32 * 4u));
-  }
-  const uint32_t Abase_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)p.A);
-  const uint32_t Abase_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uintptr_t)p.A >> 32));
-  const uint64_t Abase0 = ((uint64_t)Abase_hi << 32) | (uint64_t)Abase_lo;
-  const cu32_ptr Ac = (cu32_ptr)(uintptr_t)p.A;
-
-  // this lane's TN rows of B (clamped: columns past N recompute column N-1 and are not stored)
-  const uint64_t *brow[TN];
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    int n = nbase + j * 64;
-    n = n < p.N ? n : p.N - 1;
-    brow[j] = p.B + (int64_t)n * p.ldb;
-  }
-
-  int acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = 0;
-
-  const int nfull_all = p.Kbits / (32 * KC);
-  // this wave's range of full chunks: [cb, cb + nfull)
-  const int per = KS == 4 ? (nfull_all + 3) / 4 : nfull_all;
-  const int cb = KS == 4 ? min(wave * per, nfull_all) : 0;
-  const int nfull = KS == 4 ? min(per, nfull_all - cb) : nfull_all;
-  auto load_b = [&](u32x8 (&b)[TN], int cl) {
-    const int c = cb + cl;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const uint64_t *src = brow[j] + 4 * c;
-      if (p.b_vec16) {
-        b[j].lo = *reinterpret_cast<const u32x4 *>(src);
-        b[j].hi = *reinterpret_cast<const u32x4 *>(src + 2);
-      } else {
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const uint2 v = *reinterpret_cast<const uint2 *>(src + w);
-          b[j][2 * w] = v.x;
-          b[j][2 * w + 1] = v.y;
-        }
-      }
-    }
-  };
-  auto compute = [&](u32x8 (&b)[TN], int cl) {
-    const uint64_t Abase = Abase0 + (uint64_t)(uint32_t)(cb + cl) * 32u;
-    u32x8 a[TM];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-      asm volatile("s_load_dwordx8 %0, %1, %2" : "=s"(a[i]) : "s"(Abase), "s"(aoffb[i]));
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+s"(a[0]), "+s"(a[1]), "+s"(a[2]), "+s"(a[3]), "+s"(a[4]), "+s"(a[5]), "+s"(a[6]), "+s"(a[7]));
-    uint32_t t0, t1;
-#define BNN_BV(j, d) b[j][d]
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      if constexpr (YIELD) {
-        if constexpr (TN == 2) BNN_GEMM_ROW_2(acc[i], a[i], BNN_BV, t0, t1);
-        else BNN_GEMM_ROW_1(acc[i], a[i], BNN_BV, t0, t1);
-      } else {
-        if constexpr (TN == 2) BNN_GEMM_ROW_2_NY(acc[i], a[i], BNN_BV, t0, t1);
-        else BNN_GEMM_ROW_1_NY(acc[i], a[i], BNN_BV, t0, t1);
-      }
-    }
-#undef BNN_BV
-  };
-
-  // software pipeline over full chunks, DEPTH loads in flight (slots indexed statically)
-  u32x8 bq[DEPTH][TN];
-#pragma unroll
-  for (int d = 0; d < DEPTH; ++d)
-    if (d < nfull) load_b(bq[d], d);
-  int c = 0;
-  for (; c + DEPTH <= nfull; c += DEPTH) {
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      compute(bq[d], c + d);
-      if (c + d + DEPTH < nfull) load_b(bq[d], c + d + DEPTH);
-    }
-  }
-#pragma unroll
-  for (int d = 0; d < DEPTH; ++d)
-    if (c + d < nfull) compute(bq[d], c + d);
-
-  // bits past the last full chunk: one dword at a time, both operands masked (first wave only
-  // when the K range is split)
-  if (KS == 1 || wave == 0) {
-    const int kd0 = nfull_all * KC;
-    const int tb32 = p.Kbits & 31;
-    const uint32_t *b32[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) b32[j] = reinterpret_cast<const uint32_t *>(brow[j]);
-#pragma unroll 1
-    for (int kd = kd0; kd < p.Kd; ++kd) {
-      const uint32_t mask = (kd == p.Kd - 1 && tb32) ? ((1u << tb32) - 1u) : 0xffffffffu;
-      uint32_t b[TN];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) b[j] = b32[j][kd] & mask;
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const uint32_t a = Ac[(aoffb[i] >> 2) + kd] & mask;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = popc_acc(a ^ b[j], acc[i][j]);
-      }
-    }
-  }
-  if constexpr (KS == 4) {
-    // every wave of the workgroup is here (the early return above is per workgroup)
-    if (wave > 0) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) sRed[((wave - 1) * TM * TN + i * TN + j) * 64 + lane] = acc[i][j];
-    }
-    __syncthreads();
-    if (wave > 0) return;
-#pragma unroll
-    for (int w = 0; w < 3; ++w)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] += sRed[(w * TM * TN + i * TN + j) * 64 + lane];
-  }
-  store_tile<TN>(acc, m0, nbase);
-}
-
-// ---- few outputs, long rows: K split over the waves of a workgroup -----------------------------
-// A fully-connected layer (a few hundred rows of activations against thousands of filter rows)
-// has too few 8 x 64 tiles to give every SIMD its waves, and when every wave reads its own copy
-// of B straight from memory, as above, B crosses the L2 once per 8 rows of A: at M = 256 that is
-// 32 times the matrix, and that traffic, not the arithmetic, bounds the kernel.  Here a wave
-// keeps its chunk of B in registers while it walks 8 * TMG rows of A (8 at a time through the
-// scalar loads), so B is read once per 8 * TMG rows, and the parallelism lost to the taller tile
-// comes back from the reduction axis: the KS waves of a workgroup share one tile, each takes a
-// contiguous range of K chunks, and their partial counts (additive: section 3.2's sum over the
-// reduction axis) meet in LDS, where every wave adds up and stores its share of the rows.
-template <int TMG, int KS, int YIELD>
-__global__ __launch_bounds__(64 * KS) void xnor_gemm_splitk_kernel(GemmParams p) {
-  constexpr int DEPTH = 2;
-  __shared__ int sRed[KS * TMG * TM * 64];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const uint32_t tile = blockIdx.x;  // M fastest: consecutive workgroups share a B tile
-  const int mi = (int)(tile % (uint32_t)p.tilesM);
-  const int ni = (int)(tile / (uint32_t)p.tilesM);
-  const int m0 = mi * TM * TMG;
-  const int nbase = ni * 64 + lane;
-
-  const uint32_t arow_bytes = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)p.lda32 * 4u));
-  const uint32_t aoff_max = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(p.M - 1) * (uint32_t)p.lda32 * 4u));
-  const uint32_t aoff_tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)min(m0, p.M - 1) * (uint32_t)p.lda32 * 4u));
-  const uint32_t Abase_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)p.A);
-  const uint32_t Abase_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uintptr_t)p.A >> 32));
-  const uint64_t Abase0 = ((uint64_t)Abase_hi << 32) | (uint64_t)Abase_lo;
-  const cu32_ptr Ac = (cu32_ptr)(uintptr_t)p.A;
-
-  // this lane's row of B (clamped: columns past N recompute column N-1 and are not stored)
-  const uint64_t *brow = p.B + (int64_t)min(nbase, p.N - 1) * p.ldb;
-
-  int acc[TMG][TM][1];
-#pragma unroll
-  for (int g = 0; g < TMG; ++g)
-#pragma unroll
-    for (int i = 0; i < TM; ++i) acc[g][i][0] = 0;
-
-  const int nfull_all = p.Kbits / (32 * KC);
-  const int per = (nfull_all + KS - 1) / KS;
-  const int cb = min(wave * per, nfull_all);     // this wave's chunks: [cb, cb + nfull)
-  const int nfull = min(per, nfull_all - cb);
-  auto load_b = [&](u32x8 &b, int cl) {
-    const uint64_t *src = brow + 4 * (cb + cl);
-    if (p.b_vec16) {
-      b.lo = *reinterpret_cast<const u32x4 *>(src);
-      b.hi = *reinterpret_cast<const u32x4 *>(src + 2);
-    } else {
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const uint2 v = *reinterpret_cast<const uint2 *>(src + w);
-        b[2 * w] = v.x;
-        b[2 * w + 1] = v.y;
-      }
-    }
-  };
-  auto compute = [&](const u32x8 &bv, int cl) {
-    const uint64_t Abase = Abase0 + (uint64_t)(uint32_t)(cb + cl) * 32u;
-#pragma unroll
-    for (int g = 0; g < TMG; ++g) {
-      u32x8 a[TM];
-      uint32_t aoff_cur = aoff_tile + (uint32_t)(g * TM) * arow_bytes;
-      asm volatile("" : "+s"(aoff_cur));
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-        asm volatile("s_load_dwordx8 %0, %1, %2" : "=s"(a[i]) : "s"(Abase), "s"(BNN_AOFF(i)));
-      asm volatile("s_waitcnt lgkmcnt(0)"
-                   : "+s"(a[0]), "+s"(a[1]), "+s"(a[2]), "+s"(a[3]), "+s"(a[4]), "+s"(a[5]), "+s"(a[6]), "+s"(a[7]));
-      uint32_t t0, t1;
-#define BNN_BV(j, d) bv[d]
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        if constexpr (YIELD) BNN_GEMM_ROW_1(acc[g][i], a[i], BNN_BV, t0, t1);
-        else BNN_GEMM_ROW_1_NY(acc[g][i], a[i], BNN_BV, t0, t1);
-      }
-#undef BNN_BV
-    }
-  };
-
-  u32x8 bq[DEPTH];
-#pragma unroll
-  for (int d = 0; d < DEPTH; ++d)
-    if (d < nfull) load_b(bq[d], d);
-  int c = 0;
-  for (; c + DEPTH <= nfull; c += DEPTH) {
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      compute(bq[d], c + d);
-      if (c + d + DEPTH < nfull) load_b(bq[d], c + d + DEPTH);
-    }
-  }
-#pragma unroll
-  for (int d = 0; d < DEPTH; ++d)
-    if (c + d < nfull) compute(bq[d], c + d);
-
-  // bits past the last full chunk: one dword at a time, both operands masked (first wave only)
-  if (wave == 0) {
-    const int kd0 = nfull_all * KC;
-    const int tb32 = p.Kbits & 31;
-    const uint32_t *b32 = reinterpret_cast<const uint32_t *>(brow);
-#pragma unroll 1
-    for (int kd = kd0; kd < p.Kd; ++kd) {
-      const uint32_t mask = (kd == p.Kd - 1 && tb32) ? ((1u << tb32) - 1u) : 0xffffffffu;
-      const uint32_t b = b32[kd] & mask;
-#pragma unroll
-      for (int g = 0; g < TMG; ++g) {
-        uint32_t aoff_cur = aoff_tile + (uint32_t)(g * TM) * arow_bytes;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const uint32_t a = Ac[(BNN_AOFF(i) >> 2) + kd] & mask;
-          acc[g][i][0] = popc_acc(a ^ b, acc[g][i][0]);
-        }
-      }
-    }
-  }
-
-  // partial counts -> LDS [slice][row][lane]; every wave then sums the row groups g = wave, wave + KS, ...
-#pragma unroll
-  for (int g = 0; g < TMG; ++g)
-#pragma unroll
-    for (int i = 0; i < TM; ++i) sRed[((wave * TMG + g) * TM + i) * 64 + lane] = acc[g][i][0];
-  __syncthreads();
-#pragma unroll
-  for (int g0 = 0; g0 < TMG; g0 += KS) {
-    const int g = g0 + wave;
-    if (g < TMG && m0 + g * TM < p.M) {  // wave-uniform
-      int tot[TM][1];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        int t = 0;
-#pragma unroll
-        for (int k = 0; k < KS; ++k) t += sRed[((k * TMG + g) * TM + i) * 64 + lane];
-        tot[i][0] = t;
-      }
-      store_tile<1>(tot, m0 + g * TM, nbase);
-    }
-  }
-}
-
 // ---- host side ----------------------------------------------------------------------
 template <int TN, int WM, int WN, int MINW, int BMODE, int EMODE, int YIELD>
 static bnn_status launch_one(GemmParams &p, hipStream_t s, int kid) {
@@ -1123,32 +831,6 @@ static bnn_status launch_cfg(GemmParams &p, int bmode, int emode, hipStream_t s,
   return yield ? launch_one<TN, WM, WN, MINW, 0, 0, 1>(p, s, kid) : launch_one<TN, WM, WN, MINW, 0, 0, 0>(p, s, kid);
 }
 
-template <int TN>
-static bnn_status launch_direct(GemmParams &p, hipStream_t s, int ksplit = -1) {  // ksplit: -1 heuristic, 0 off, 1 on
-  p.tilesM = (p.M + TM - 1) / TM;
-  p.tilesN = (p.N + 64 * TN - 1) / (64 * TN);
-  const int64_t waves = (int64_t)p.tilesM * p.tilesN;
-  if (waves > 0x7fffffffLL) return BNN_ERR_UNSUPPORTED;
-  ProfScope ps(KID_XNOR_GEMM_SMALL, s);
-  const int64_t simds = 4 * (int64_t)p.n_cu;
-  if constexpr (TN == 1) {
-    // fewer tiles than SIMDs and at least four chunks per wave after the split: four waves per tile
-    if (ksplit > 0 || (ksplit < 0 && waves < simds && p.Kbits / (32 * KC) >= 16)) {
-      if (4 * waves >= 2 * simds)
-        hipLaunchKernelGGL((xnor_gemm_direct_kernel<1, 4, 1, 4>), dim3((unsigned)waves), dim3(256), 0, s, p);
-      else
-        hipLaunchKernelGGL((xnor_gemm_direct_kernel<1, 4, 0, 4>), dim3((unsigned)waves), dim3(256), 0, s, p);
-      return launch_status();
-    }
-  }
-  const int64_t blocks = (waves + 3) / 4;
-  if (waves >= 2 * simds)
-    hipLaunchKernelGGL((xnor_gemm_direct_kernel<TN, 4, 1, 1>), dim3((unsigned)blocks), dim3(256), 0, s, p);
-  else
-    hipLaunchKernelGGL((xnor_gemm_direct_kernel<TN, 4, 0, 1>), dim3((unsigned)blocks), dim3(256), 0, s, p);
-  return launch_status();
-}
-
 int device_cu_count() {
   // one slot per device id; concurrent first calls write the same value
   static int cached[64] = {0};
@@ -1162,33 +844,6 @@ int device_cu_count() {
   return cached[dev];
 }
 
-template <int TMG, int KS>
-static bnn_status launch_splitk(GemmParams &p, hipStream_t s) {
-  p.tilesM = (p.M + TM * TMG - 1) / (TM * TMG);
-  p.tilesN = (p.N + 63) / 64;
-  const int64_t tiles = (int64_t)p.tilesM * p.tilesN;
-  if (tiles > 0x7fffffffLL) return BNN_ERR_UNSUPPORTED;
-  ProfScope ps(KID_XNOR_GEMM_SMALL, s);
-  if (tiles * KS >= 2 * 4 * (int64_t)p.n_cu)
-    hipLaunchKernelGGL((xnor_gemm_splitk_kernel<TMG, KS, 1>), dim3((unsigned)tiles), dim3(64 * KS), 0, s, p);
-  else
-    hipLaunchKernelGGL((xnor_gemm_splitk_kernel<TMG, KS, 0>), dim3((unsigned)tiles), dim3(64 * KS), 0, s, p);
-  return launch_status();
-}
-
-static bnn_status launch_splitk_by(GemmParams &p, int tmg, int ks, hipStream_t s) {
-  if (tmg == 4) {
-    if (ks == 8) return launch_splitk<4, 8>(p, s);
-    if (ks == 4) return launch_splitk<4, 4>(p, s);
-    if (ks == 2) return launch_splitk<4, 2>(p, s);
-  } else if (tmg == 2) {
-    if (ks == 8) return launch_splitk<2, 8>(p, s);
-    if (ks == 4) return launch_splitk<2, 4>(p, s);
-    if (ks == 2) return launch_splitk<2, 2>(p, s);
-  }
-  return BNN_ERR_UNSUPPORTED;
-}
-
 bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const GemmTune &tune) {
   int cfg = tune.cfg;
   p.n_cu = device_cu_count();
@@ -1198,7 +853,6 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
     const bool y_ok = !p.Y || (((uintptr_t)p.Y & 127u) == 0 && (planes ? (p.OHW % 32u) == 0 : (p.ldy % 32) == 0));
     p.nt_store = (c_ok && y_ok) ? 1 : 0;
   }
-  const int64_t full = 2 * (int64_t)p.n_cu;  // tiles that give every compute unit two workgroups
   if (bmode == 1 && emode == 0 && p.g.pool == 0 && p.g.kH == 1 && p.g.kW == 1 && p.g.sH == 1 && p.g.sW == 1 &&
       p.g.pH == 0 && p.g.pW == 0) {
     // a stride-1 pointwise convolution over a packed image has nothing to gather: its patch
@@ -1208,8 +862,13 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
     p.ldb = p.g.Cw;
     p.b_vec16 = (p.g.Cw & 1) == 0 ? 1 : 0;
   }
-  if (bmode == 0 && emode == 0 && (cfg < 0 || (cfg >= 10 && cfg <= 12)) && lowk_applicable(p) &&
-      ((int64_t)p.M + 31) / 32 <= 65535) {
+  // a forced value this call cannot use selects the heuristic
+  const bool valu = emode == 0 ? (cfg >= 1 && cfg <= 6 && cfg != 5)
+                               : (cfg == 3 || cfg == 1 || (!p.g.pool && (cfg == 6 || cfg == 4)));
+  const bool short_rows = bmode == 0 && emode == 0 && lowk_applicable(p) && ((int64_t)p.M + 31) / 32 <= 65535;
+  const bool matrix = (cfg >= 21 && cfg <= 24 && fp4_applicable(p)) || (cfg >= 25 && cfg <= 28);
+  if (!valu && !matrix && !(short_rows && cfg >= 10 && cfg <= 12)) cfg = -1;
+  if (short_rows && (cfg < 0 || (cfg >= 10 && cfg <= 12))) {
     // rows of two or four words: bound by the store, see gemm_lowk.hip.  As many rows per wave
     // (32, 16 or 8) as still leave every compute unit a workgroup.
     const int64_t ctiles = ((int64_t)p.N + 255) / 256;
@@ -1219,90 +878,24 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
                                                                                     : 1);
     return launch_lowk(p, groups, s);
   }
-  if (cfg >= 10 && cfg <= 12) cfg = -1;
-  if (bmode == 1 && (cfg == 19 || cfg == 20) && latency_applicable(p)) return launch_latency(p, emode, cfg == 19 ? 4 : 2, s);
-  if (cfg == 19 || cfg == 20) cfg = -1;
-  if (bmode == 1 && cfg < 0 && latency_applicable(p)) {
-    // Few output pixels (small batches, late layers): the latency form, see gemm_latency.hip.  Its
-    // workgroups fill a compute unit each, so it wins while there is at most one per compute unit
-    // (measured on the layers of the stack at batch 1 to 64: 1.5 to 2.2 times faster there, slower
-    // beyond); pooled layers, whose throughput tile is four columns wide, up to two per unit.
-    const int64_t lt = (((int64_t)p.M + 31) / 32) * (((int64_t)p.N + 63) / 64);
-    if (lt <= (int64_t)p.n_cu) return launch_latency(p, emode, 4, s);
-    if (p.g.pool && lt <= 2 * (int64_t)p.n_cu) return launch_latency(p, emode, 2, s);
+  if (!valu) {
+    // The matrix cores; few outputs split the reduction axis, and so do rows too long for exact fp32 sums.
+    p.colperm = (emode == 0 && (p.N & 3) == 0 && (!p.C || (p.ldc & 3) == 0) && (!p.Y || (p.ldy & 3) == 0) &&
+                 (p.img_stride == 0 || ((p.OHW & 3u) == 0 && (p.img_stride & 3) == 0)))
+                    ? 1
+                    : 0;
+    if (cfg >= 25) return launch_gemm_fp4_split(p, bmode, emode, s, cfg - 25);
+    if (cfg < 0 && (fp4_split_applicable(p) || !fp4_applicable(p))) return launch_gemm_fp4_split(p, bmode, emode, s, -1);
+    return launch_gemm_fp4(p, bmode, emode, s, cfg >= 21 ? cfg - 21 : -1, tune.lean != 0);
   }
-  if ((cfg < 0 || (cfg >= 21 && cfg <= 24)) && fp4_applicable(p)) {
-    // The matrix cores, unless the outputs are so few that the kernels below, which split the reduction axis,
-    // occupy the chip better (256 x 1024 x 8192: 7.9 us there, 17 us here).
-    const int64_t t32 = (int64_t)((p.M + 31) / 32) * ((p.N + 127) / 128);
-    if (cfg >= 21 || bmode == 1 || t32 >= full) {
-      p.colperm = (emode == 0 && (p.N & 3) == 0 && (!p.C || (p.ldc & 3) == 0) && (!p.Y || (p.ldy & 3) == 0) &&
-                   (p.img_stride == 0 || ((p.OHW & 3u) == 0 && (p.img_stride & 3) == 0)))
-                      ? 1
-                      : 0;
-      return launch_gemm_fp4(p, bmode, emode, s, cfg >= 21 ? cfg - 21 : -1);
-    }
-  }
-  if (cfg >= 21) cfg = -1;
+  // Vector-ALU tiles, with a forced configuration only: the method's own instructions (xor, popcount), measured beside
+  // the matrix cores.
   if (bmode == 1 && tune.lean) {
     // lean gather: 16-byte pieces never straddle a tap (even Cw), one validity bit per tap in a
     // 32-bit mask, 32-bit byte offsets into the packed image
     const int64_t taps = (int64_t)p.g.kH * p.g.kW;
     const int64_t img_bytes = (int64_t)p.g.Nimg * p.g.H * p.g.W * p.g.Cw * 8;
     if ((p.g.Cw & 1) == 0 && taps <= 32 && img_bytes <= 0xffffffffLL && (p.Kw64 + 3) / 4 <= LEAN_MAX_STAGES) bmode = 2;
-  }
-  if (bmode == 0 && emode == 0 && (cfg == 7 || cfg == 8 || cfg < 0)) {
-    // Too few 32 x 128 tiles to give every SIMD two waves of the LDS-staged kernel: use
-    // independent waves on 8 x 128 (or 8 x 64) tiles instead.
-    const int64_t t32 = (int64_t)((p.M + 31) / 32) * ((p.N + 127) / 128);
-    const int64_t w128 = (int64_t)((p.M + 7) / 8) * ((p.N + 127) / 128);
-    const int nchunks = p.Kbits / (32 * KC);
-    if (cfg < 0 && t32 < full && nchunks >= 16 && ((int64_t)p.M + 32) * p.lda32 * 4 <= 0xffffffffLL) {
-      // long rows, few outputs: the tallest tile (32, 16 or 8 rows per wave, K split 8 / 8 / 4 ways over
-      // the waves of a workgroup) that still gives every SIMD two waves; if none does, the one
-      // with the most waves, the lower tile on a tie.  Measured: 256 x 4096 x 4096 12.8 -> 10.9 us,
-      // 256 x 1024 x 8192 8.4 -> 7.9 us per launch inside a replayed graph (an empty launch: 3.3 us).
-      const int64_t ct = ((int64_t)p.N + 63) / 64;
-      const int64_t w4 = (((int64_t)p.M + 31) / 32) * ct * 8, w2 = (((int64_t)p.M + 15) / 16) * ct * 8,
-                    w1 = (((int64_t)p.M + 7) / 8) * ct * 4;
-      const int64_t want = 2 * 4 * (int64_t)p.n_cu;
-      if (w4 >= want) return launch_splitk<4, 8>(p, s);
-      if (w2 >= want) return launch_splitk<2, 8>(p, s);
-      if (w1 < want && w2 > w1 && w2 >= w4) return launch_splitk<2, 8>(p, s);
-      if (w1 < want && w4 > w1 && w4 > w2) return launch_splitk<4, 8>(p, s);
-      return launch_direct<1>(p, s, 1);
-    }
-    if (cfg == 8 || (cfg < 0 && t32 < full && w128 >= 4 * full)) return launch_direct<2>(p, s);
-    if (cfg == 7 || (cfg < 0 && t32 < full)) return launch_direct<1>(p, s, cfg == 7 ? 0 : -1);
-  }
-  if (bmode == 0 && emode == 0 && cfg == 9) return launch_direct<1>(p, s, 1);  // forced K split
-  if (bmode == 0 && emode == 0 && cfg >= 13 && cfg <= 18) {
-    static const int tm[6] = {4, 4, 2, 2, 4, 2}, ks[6] = {4, 8, 8, 4, 2, 2};
-    return launch_splitk_by(p, tm[cfg - 13], ks[cfg - 13], s);
-  }
-  // a forced value this call cannot use (the one-wave kernels read an explicit B and store
-  // int32 / fp32; anything that is not a tile configuration) selects the heuristic
-  if (cfg == 7 || cfg == 8 || cfg == 9 || cfg == 5 || cfg == 0 || cfg > 9) cfg = -1;
-  if (emode == 1) {
-    // tiles the packed epilogue is written for: 64 x 256 (3), 64 x 128 (6), 32 x 256 (1), 32 x 128 (4);
-    // pooling needs four columns per lane (3 or 1)
-    const bool ok = p.g.pool ? (cfg == 3 || cfg == 1) : (cfg == 3 || cfg == 6 || cfg == 1 || cfg == 4);
-    // 64 x 256 is the fastest tile when a compute unit gets more than two of them; with two or
-    // fewer, 32 x 256 (four waves per workgroup, twice as many workgroups) is as fast or faster
-    const int64_t t256 = (int64_t)((p.M + 63) / 64) * ((p.N + 255) / 256);
-    // ... and without pooling 32 x 128 (again twice as many workgroups) while 32 x 256 would leave
-    // a compute unit two workgroups or fewer
-    const int64_t t32x256 = (int64_t)((p.M + 31) / 32) * ((p.N + 255) / 256);
-    if (!ok) cfg = (!p.g.pool && t32x256 <= full) ? 4 : (t256 <= full ? 1 : 3);
-  }
-  if (cfg < 0) {
-    // Measured on MI355X: 64 x 256 (TN = 4, eight waves per workgroup, six per SIMD) is the
-    // fastest tile when there are enough of them; smaller problems take finer tiles so that
-    // every CU has work.
-    const int64_t t256 = (int64_t)((p.M + 63) / 64) * ((p.N + 255) / 256);
-    const int64_t t128 = (int64_t)((p.M + 63) / 64) * ((p.N + 127) / 128);
-    const int64_t t32 = (int64_t)((p.M + 31) / 32) * ((p.N + 127) / 128);
-    cfg = (p.M >= 64 && t256 >= full) ? 3 : (p.M >= 64 && t128 >= full) ? 6 : (t32 >= full ? 4 : 2);
   }
   switch (cfg) {
     case 1: return launch_cfg<4, 4, 1, 4>(p, bmode, emode, s, KID_XNOR_GEMM);        // 32 x 256

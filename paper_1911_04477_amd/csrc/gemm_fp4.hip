@@ -62,29 +62,6 @@ struct Fp4Cfg {
   static_assert(BM * S % T == 0 && BN * S % T == 0 && T % S == 0, "staging must divide evenly");
 };
 
-// fdiv without the branch on a divisor of 1 (uniform divisors: one select).
-__device__ __forceinline__ uint32_t fdiv_sel(uint32_t n, const FastDiv &f) {
-  const uint32_t t = __umulhi(n, f.mul);
-  const uint32_t q = (t + ((n - t) >> 1)) >> f.shift;
-  return f.d == 1 ? n : q;
-}
-
-// Output pixel of GEMM column n: image, row and column of the map.
-__device__ __forceinline__ void column_pixel(const ConvGeom &g, uint32_t n, bool pool, uint32_t &img, uint32_t &oh,
-                                             uint32_t &ow) {
-  // window-major when pooling: column = 4 * window + member
-  const uint32_t j = pool ? n & 3u : 0u, w = pool ? n >> 2 : n;
-  const uint32_t PW = pool ? (uint32_t)g.OW >> 1 : (uint32_t)g.OW, PH = pool ? (uint32_t)g.OH >> 1 : (uint32_t)g.OH;
-  const uint32_t t = fdiv_sel(w, g.divOW);
-  ow = w - t * PW;
-  img = fdiv_sel(t, g.divOH);
-  oh = t - img * PH;
-  if (pool) {
-    ow = 2u * ow + (j & 1u);
-    oh = 2u * oh + (j >> 1);
-  }
-}
-
 // Copies the input rows 0 .. rows - 1 of a tile's region to LDS planes [word][pixel]; taps outside the image are
 // +1 in every real channel.  EVEN: words per pixel in pairs, 16-byte loads.  A lane keeps one word pair of one
 // region column, the workgroup's waves walk the rows, and up to BATCH loads are in flight per lane; what depends
@@ -524,7 +501,7 @@ static bool halo_region(GemmParams &p, int bn, bool pool) {
 // Signs leave from any shape; maps, and everything on explicit rows, from the two shapes of 64 x 64 outputs per wave
 // on four waves that win there (see below).
 template <int WTM, int WTN, int WGM, int WGN, int MINW, bool MAPS>
-static bnn_status launch_fp4_shape(GemmParams &p, int bmode, int emode, hipStream_t s) {
+static bnn_status launch_fp4_shape(GemmParams &p, int bmode, int emode, hipStream_t s, bool region) {
   using H = Fp4Cfg<WTM, WTN, WGM, WGN, GM_HALO>;
   if constexpr (MAPS) {
     if (bmode == 0) {
@@ -534,7 +511,7 @@ static bnn_status launch_fp4_shape(GemmParams &p, int bmode, int emode, hipStrea
     }
   }
   p.b_vec16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0;
-  const bool halo = halo_region(p, H::BN, p.g.pool != 0);
+  const bool halo = region && halo_region(p, H::BN, p.g.pool != 0);
   if constexpr (MAPS) {
     if (emode == 0)
       return halo ? launch_fp4<WTM, WTN, WGM, WGN, GM_HALO, EM_MAPS, MINW>(p, s)
@@ -549,10 +526,10 @@ static bnn_status launch_fp4_shape(GemmParams &p, int bmode, int emode, hipStrea
 
 bool fp4_applicable(const GemmParams &p) {
   // exact fp32 counts: every partial sum is below 2^24 in magnitude
-  return (int64_t)((p.Kw64 + 1) / 2) * 128 < (1 << 24);
+  return p.Kw64 < (1 << 18) - 2;
 }
 
-bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, int shape) {
+bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, int shape, bool region) {
   const bool maps = bmode == 0 || emode == 0;
   if (shape < 0 || (maps && shape < 2)) {
     const int64_t cu = p.n_cu, c256 = ((int64_t)p.N + 255) / 256;
@@ -576,10 +553,10 @@ bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, i
     }
   }
   switch (shape) {
-    case 0: return launch_fp4_shape<2, 4, 2, 2, 2, false>(p, bmode, emode, s);  // 128 x 256, 4 waves of 64 x 128
-    case 1: return launch_fp4_shape<2, 2, 2, 4, 2, false>(p, bmode, emode, s);  // 128 x 256, 8 waves of 64 x 64
-    case 2: return launch_fp4_shape<2, 2, 2, 2, 3, true>(p, bmode, emode, s);   // 128 x 128, 4 waves of 64 x 64
-    default: return launch_fp4_shape<2, 2, 1, 4, 2, true>(p, bmode, emode, s);  // 64 x 256, 4 waves of 64 x 64
+    case 0: return launch_fp4_shape<2, 4, 2, 2, 2, false>(p, bmode, emode, s, region);  // 128 x 256, 4 waves of 64 x 128
+    case 1: return launch_fp4_shape<2, 2, 2, 4, 2, false>(p, bmode, emode, s, region);  // 128 x 256, 8 waves of 64 x 64
+    case 2: return launch_fp4_shape<2, 2, 2, 2, 3, true>(p, bmode, emode, s, region);   // 128 x 128, 4 waves of 64 x 64
+    default: return launch_fp4_shape<2, 2, 1, 4, 2, true>(p, bmode, emode, s, region);  // 64 x 256, 4 waves of 64 x 64
   }
 }
 

@@ -1,0 +1,364 @@
+// Xnor-Bitcount GEMM (section 3.2) and implicit-GEMM convolution on the matrix cores for few outputs: the
+// reduction axis split over the waves of a workgroup.
+//
+// A fully-connected layer at serving batch, or a convolution over a handful of images, has too few 128 x 128
+// tiles to occupy the chip, and a tile walked by one workgroup lasts as long as its reduction is long.  Here a
+// tile is 32 x 32 or 64 x 64 outputs, KS waves take contiguous ranges of the reduction in chunks of 256 bits, and
+// every wave reads its operands straight from memory in fragment order (lane l: row l % 32, 128-bit half l / 32 of
+// the chunk): no LDS staging, no barrier before the end.  Two chunks are in flight per wave.  The partial sums meet in
+// LDS as integers once; waves 0 .. 3 each finish the accumulator quad q = wave
+// (rows 8q + 4 * (l / 32) + 0..3 of every block).
+//
+// Bound: latency (launch, one memory round trip for the operands, one exchange through LDS).
+#include "common.h"
+#include "fp4_tile.h"
+
+namespace bnn {
+
+enum : int { SG_EXPL16 = 0, SG_EXPL8 = 1, SG_CONV = 2 };
+
+template <int WT, int KS, int GM, int EMODE>
+__global__ __launch_bounds__(64 * KS) void xnor_gemm_fp4_split_kernel(GemmParams p) {
+  constexpr int B32 = 32 * WT;  // rows and columns of the tile
+  constexpr bool CONV = GM == SG_CONV, SIGN = EMODE != 0;
+  __shared__ __attribute__((aligned(16))) int4 sPart[KS * WT * WT * 4 * 64];
+  __shared__ __attribute__((aligned(16))) uint8_t sO[SIGN ? B32 * WT * 4 : 16];  // sign bytes [column][row group of 8]
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ni = (int)fdiv(blockIdx.x, p.divTilesM), mi = (int)(blockIdx.x - (uint32_t)ni * (uint32_t)p.tilesM);
+  const int m0 = mi * B32, n0 = ni * B32;
+  const ConvGeom &g = p.g;
+
+  // ---- this lane's rows and columns: column block j, lane l = tile column WT * l + j ---------------------
+  const char *arow[WT], *brow[WT];
+  int bih[WT], biw[WT];
+#pragma unroll
+  for (int i = 0; i < WT; ++i)
+    arow[i] = reinterpret_cast<const char *>(p.A) + (size_t)min(m0 + 32 * i + l32, p.M - 1) * (size_t)p.lda32 * 4u;
+#pragma unroll
+  for (int j = 0; j < WT; ++j) {
+    const int n = min(n0 + WT * l32 + j, p.N - 1);  // columns past N recompute column N - 1
+    if constexpr (CONV) {
+      uint32_t img, oh, ow;
+      column_pixel(g, (uint32_t)n, g.pool != 0, img, oh, ow);
+      brow[j] = reinterpret_cast<const char *>(g.act + (size_t)img * (size_t)g.H * (size_t)g.W * (size_t)g.Cw);
+      bih[j] = (int)oh * g.sH - g.pH;
+      biw[j] = (int)ow * g.sW - g.pW;
+    } else {
+      brow[j] = reinterpret_cast<const char *>(p.B) + (size_t)n * (size_t)p.ldb * 8u;
+    }
+  }
+
+  // ---- operands of one chunk: words 4c + 2 * half and the next; past the row's end the last word again, masked later
+  const bool a16 = GM == SG_EXPL16 || (CONV && p.b_vec16);
+  const bool cw_even = CONV && (g.Cw & 1) == 0;
+  const uint64_t part = (g.C & 63) ? (1ull << (g.C & 63)) - 1ull : ~0ull;  // real channels of a tap's last word
+  auto load_chunk = [&](int c, u32x4 (&a)[WT], u32x4 (&b)[WT]) {
+    const int w = 4 * c + 2 * half;
+    const uint32_t w0 = (uint32_t)min(w, p.Kw64 - 1), w1 = (uint32_t)min(w + 1, p.Kw64 - 1);
+    if (a16) {
+      const uint32_t o = (uint32_t)min(w, p.Kw64 - 2) * 8u;
+#pragma unroll
+      for (int i = 0; i < WT; ++i) a[i] = *reinterpret_cast<const u32x4 *>(arow[i] + o);
+    } else {
+#pragma unroll
+      for (int i = 0; i < WT; ++i) {
+        a[i].lo = *reinterpret_cast<const u32x2 *>(arow[i] + w0 * 8u);
+        a[i].hi = *reinterpret_cast<const u32x2 *>(arow[i] + w1 * 8u);
+      }
+    }
+    if constexpr (GM == SG_EXPL16) {
+      const uint32_t o = (uint32_t)min(w, p.Kw64 - 2) * 8u;
+#pragma unroll
+      for (int j = 0; j < WT; ++j) b[j] = *reinterpret_cast<const u32x4 *>(brow[j] + o);
+    } else if constexpr (GM == SG_EXPL8) {
+#pragma unroll
+      for (int j = 0; j < WT; ++j) {
+        b[j].lo = *reinterpret_cast<const u32x2 *>(brow[j] + w0 * 8u);
+        b[j].hi = *reinterpret_cast<const u32x2 *>(brow[j] + w1 * 8u);
+      }
+    } else if (cw_even) {  // both words belong to one tap
+      const uint32_t ww = (uint32_t)min(w, p.Kw64 - 2);
+      const uint32_t tap = fdiv_sel(ww, g.divCw), cw = ww - tap * (uint32_t)g.Cw;
+      const uint32_t kh = fdiv_sel(tap, g.divKW), kw = tap - kh * (uint32_t)g.kW;
+      const uint64_t pad = cw + 2u == (uint32_t)g.Cw ? part : ~0ull;
+#pragma unroll
+      for (int j = 0; j < WT; ++j) {
+        const int ih = bih[j] + (int)kh, iw = biw[j] + (int)kw;
+        u32x4 v = {0xffffffffu, 0xffffffffu, (uint32_t)pad, (uint32_t)(pad >> 32)};
+        if (ih >= 0 && ih < g.H && iw >= 0 && iw < g.W)
+          v = *reinterpret_cast<const u32x4 *>(brow[j] + (((size_t)ih * (size_t)g.W + (size_t)iw) * (size_t)g.Cw + cw) * 8u);
+        b[j] = v;
+      }
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t ww = h ? w1 : w0;
+        const uint32_t tap = fdiv_sel(ww, g.divCw), cw = ww - tap * (uint32_t)g.Cw;
+        const uint32_t kh = fdiv_sel(tap, g.divKW), kw = tap - kh * (uint32_t)g.kW;
+        const uint64_t pad = cw + 1u == (uint32_t)g.Cw ? part : ~0ull;  // taps outside the image: +1 in every channel
+#pragma unroll
+        for (int j = 0; j < WT; ++j) {
+          const int ih = bih[j] + (int)kh, iw = biw[j] + (int)kw;
+          u32x2 v = {(uint32_t)pad, (uint32_t)(pad >> 32)};
+          if (ih >= 0 && ih < g.H && iw >= 0 && iw < g.W)
+            v = *reinterpret_cast<const u32x2 *>(brow[j] + (((size_t)ih * (size_t)g.W + (size_t)iw) * (size_t)g.Cw + cw) * 8u);
+          if (h == 0) b[j].lo = v;
+          else b[j].hi = v;
+        }
+      }
+    }
+  };
+  auto mask_chunk = [&](int c, u32x4 (&a)[WT], u32x4 (&b)[WT]) {  // bits past the end of the row become 0 in both operands
+    u32x4 m;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const int left = p.Kbits - (8 * c + 4 * half + d) * 32;  // host: Kbits < 2^24
+      m[d] = left >= 32 ? 0xffffffffu : (left <= 0 ? 0u : (1u << left) - 1u);
+    }
+#pragma unroll
+    for (int i = 0; i < WT; ++i) {
+      a[i] &= m;
+      b[i] &= m;
+    }
+  };
+
+  Fp4Acc<WT, WT> acc;
+  acc.init(0.0f);
+  auto multiply_chunk = [&](const u32x4 (&a)[WT], const u32x4 (&b)[WT]) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      v8i ea[WT], eb[WT];
+#pragma unroll
+      for (int i = 0; i < WT; ++i) {
+        ea[i] = expand_e2m1(a[i][d]);
+        eb[i] = expand_e2m1(b[i][d]);
+      }
+#pragma unroll
+      for (int i = 0; i < WT; ++i)
+#pragma unroll
+        for (int j = 0; j < WT; ++j) acc.v[i][j] = mfma_e2m1(ea[i], eb[j], acc.v[i][j]);
+    }
+  };
+
+  const int nc = (p.Kw64 + 3) >> 2;
+  const int per = (nc + KS - 1) / KS;
+  const int cb = min(wave * per, nc), ce = min(cb + per, nc);
+  u32x4 a0[WT], b0[WT], a1[WT], b1[WT];
+  if (cb < ce) load_chunk(cb, a0, b0);
+  if (cb + 1 < ce) load_chunk(cb + 1, a1, b1);
+  // the finishing waves' affine constants travel with the operands
+  const int mq = m0 + 8 * (wave & 3) + 4 * half;  // first of this lane's rows in row block 0
+  const bool row_affine = SIGN || (p.Y && p.axis == BNN_CH_ROW);
+  float sc[WT][4], bi[WT][4];
+#pragma unroll
+  for (int i = 0; i < WT; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int m = mq + 32 * i + e;
+      const bool on = row_affine && wave < 4 && m < p.M;
+      sc[i][e] = on ? p.scale[m] : 0.0f;  // rows past M: sign bit 0
+      bi[i][e] = on ? p.bias[m] : -1.0f;
+    }
+  // partial sums -> LDS [wave][block][quad][lane], as integers: fp32 holds them exactly for 2^24 values, and a wave
+  // whose range is longer than FLUSH chunks adds up its own slots
+  constexpr int FLUSH = 1 << 15;
+  bool flushed = false;
+  auto flush = [&]() {
+#pragma unroll
+    for (int i = 0; i < WT; ++i)
+#pragma unroll
+      for (int j = 0; j < WT; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const v16f &v = acc.v[i][j];
+          int4 *d = &sPart[((wave * WT * WT + i * WT + j) * 4 + q) * 64 + lane];
+          int4 t = make_int4((int)v[4 * q], (int)v[4 * q + 1], (int)v[4 * q + 2], (int)v[4 * q + 3]);
+          if (flushed) {
+            const int4 o = *d;
+            t = make_int4(t.x + o.x, t.y + o.y, t.z + o.z, t.w + o.w);
+          }
+          *d = t;
+        }
+  };
+#pragma unroll 1
+  for (int c = cb; c < ce; c += 2) {
+    if (c == nc - 1) mask_chunk(c, a0, b0);
+    u32x4 ta[WT], tb[WT];
+#pragma unroll
+    for (int i = 0; i < WT; ++i) {
+      ta[i] = a0[i];
+      tb[i] = b0[i];
+    }
+    if (c + 2 < ce) load_chunk(c + 2, a0, b0);
+    multiply_chunk(ta, tb);
+    if (c + 1 < ce) {
+      if (c + 1 == nc - 1) mask_chunk(c + 1, a1, b1);
+#pragma unroll
+      for (int i = 0; i < WT; ++i) {
+        ta[i] = a1[i];
+        tb[i] = b1[i];
+      }
+      if (c + 3 < ce) load_chunk(c + 3, a1, b1);
+      multiply_chunk(ta, tb);
+    }
+    if (((c - cb + 2) & (FLUSH - 1)) == 0) {
+      flush();
+      flushed = true;
+      acc.init(0.0f);
+    }
+  }
+  flush();
+  __syncthreads();
+
+  // ---- wave q < 4 sums quad q ----------------------------------------------------------------------------------
+  // the rows' padding, 0 bits in both operands, counted +1 each
+  const int corr = (int)((uint32_t)p.Kformula - (uint32_t)nc * 256u);
+  int s[WT][WT][4];
+  if (wave < 4) {  // wave-uniform
+#pragma unroll
+    for (int i = 0; i < WT; ++i)
+#pragma unroll
+      for (int j = 0; j < WT; ++j) {
+        int t[4] = {corr, corr, corr, corr};
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+          const int4 v = sPart[((k * WT * WT + i * WT + j) * 4 + wave) * 64 + lane];
+          t[0] += v.x;
+          t[1] += v.y;
+          t[2] += v.z;
+          t[3] += v.w;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[i][j][e] = t[e];
+      }
+  }
+
+  if constexpr (!SIGN) {
+    if (wave >= 4) return;
+    const int n = n0 + WT * l32;
+    if (n >= p.N) return;
+    int64_t off[WT];
+    float csc[WT], cbi[WT];
+    const bool col_affine = p.Y && p.axis == BNN_CH_COL;
+#pragma unroll
+    for (int j = 0; j < WT; ++j) {
+      const int c = min(n + j, p.N - 1);
+      off[j] = c;
+      if (p.img_stride != 0) {  // NCHW planes
+        const uint32_t img = fdiv((uint32_t)c, p.divOHW);
+        off[j] = (int64_t)img * p.img_stride + ((uint32_t)c - img * p.OHW);
+      }
+      csc[j] = col_affine ? p.scale[c] : 0.0f;
+      cbi[j] = col_affine ? p.bias[c] : 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < WT; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int m = mq + 32 * i + e;
+        if (m >= p.M) continue;
+#pragma unroll
+        for (int j = 0; j < WT; ++j) {
+          if (n + j >= p.N) continue;
+          if (p.C) p.C[(int64_t)m * p.ldc + off[j]] = s[i][j][e];
+          if (p.Y)
+            p.Y[(int64_t)m * p.ldy + off[j]] = row_affine ? fmaf(sc[i][e], (float)s[i][j][e], bi[i][e]) : fmaf(csc[j], (float)s[i][j][e], cbi[j]);
+        }
+      }
+  } else {
+    // four sign bits per column and row block; lanes l and l + 32 hold the two nibbles of a byte.  The members of a
+    // pooling window are consecutive columns: WT in this lane, the others in its neighbours.
+    if (wave < 4) {
+#pragma unroll
+      for (int i = 0; i < WT; ++i)
+#pragma unroll
+        for (int j = 0; j < WT; ++j) {
+          uint32_t nib = 0u;
+#pragma unroll
+          for (int e = 3; e >= 0; --e) {
+            int m = s[i][j][e];
+            if constexpr (EMODE == 2) {
+              if constexpr (WT == 2) m = max(s[i][0][e], s[i][1][e]);
+              else m = max(m, __builtin_amdgcn_mov_dpp(m, 0xB1, 0xF, 0xF, true));        // lane ^ 1
+              m = max(m, __builtin_amdgcn_mov_dpp(m, WT == 2 ? 0xB1 : 0x4E, 0xF, 0xF, true));  // lane ^ 1 / lane ^ 2
+            }
+            nib = 2u * nib + (fmaf(sc[i][e], (float)m, bi[i][e]) >= 0.0f ? 1u : 0u);
+          }
+          const uint32_t other = (uint32_t)__shfl_xor((int)nib, 32);
+          if (half == 0) sO[(WT * l32 + j) * (4 * WT) + 4 * i + wave] = (uint8_t)(nib | (other << 4));
+        }
+    }
+    __syncthreads();
+    // one thread per output pixel and 32 channels
+    const int npix = EMODE == 2 ? B32 / 4 : B32;
+    if (tid < npix * WT) {
+      const int px = tid / WT, i = tid % WT;
+      const uint32_t w = *reinterpret_cast<const uint32_t *>(&sO[(EMODE == 2 ? 4 * px : px) * (4 * WT) + 4 * i]);
+      const int64_t gp = (int64_t)(EMODE == 2 ? n0 >> 2 : n0) + px;
+      const int64_t limit = EMODE == 2 ? (int64_t)(p.N >> 2) : (int64_t)p.N;
+      const int w32 = mi * WT + i;  // 32-channel half word
+      if (gp < limit && w32 < 2 * p.cw_out) {
+        uint32_t *o = reinterpret_cast<uint32_t *>(p.outp) + gp * p.cw_out * 2;
+        o[w32] = w;
+        // an odd number of 32-channel tiles: the last word's upper half holds no channel
+        if (WT == 1 && mi == p.tilesM - 1 && (p.tilesM & 1)) o[w32 + 1] = 0u;
+      }
+    }
+  }
+}
+
+template <int WT, int KS>
+static bnn_status launch_split(GemmParams &p, int bmode, int emode, hipStream_t s) {
+  p.tilesM = (p.M + 32 * WT - 1) / (32 * WT);
+  const int64_t tn = ((int64_t)p.N + 32 * WT - 1) / (32 * WT);
+  const int64_t blocks = p.tilesM * tn;
+  if (blocks > 0x7fffffffLL) return BNN_ERR_UNSUPPORTED;
+  p.tilesN = (int)tn;
+  p.divTilesM = FastDiv((uint32_t)p.tilesM);
+  const dim3 grid((unsigned)blocks), block(64 * KS);
+  ProfScope ps(KID_XNOR_GEMM_FP4_SPLIT, s);
+  if (bmode == 0) {
+    const bool v16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0 && p.ldb % 2 == 0;
+    if (v16) hipLaunchKernelGGL((xnor_gemm_fp4_split_kernel<WT, KS, SG_EXPL16, 0>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((xnor_gemm_fp4_split_kernel<WT, KS, SG_EXPL8, 0>), grid, block, 0, s, p);
+    return launch_status();
+  }
+  p.b_vec16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0;
+  if (emode == 0) hipLaunchKernelGGL((xnor_gemm_fp4_split_kernel<WT, KS, SG_CONV, 0>), grid, block, 0, s, p);
+  else if (p.g.pool) hipLaunchKernelGGL((xnor_gemm_fp4_split_kernel<WT, KS, SG_CONV, 2>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((xnor_gemm_fp4_split_kernel<WT, KS, SG_CONV, 1>), grid, block, 0, s, p);
+  return launch_status();
+}
+
+// Tiles of 32 x 32 outputs per compute unit, cu2 = 2, 4, 8 of them:
+//   up to 2: 32 x 32 tiles, K split 8 ways (512 x 64 x 4608 4.7 us, KS = 4: 5.2, 16: 4.8, 64 x 64 tiles 7.4 to 8.2, the
+//            128 x 128 kernel 12; 1 x 1024 x 8192 3.6 us; 128 x 4096 x 1152 4.3 against 4.4, 5.1 and 6.3);
+//   up to 4: short rows 32 x 32 and 4 ways (128 x 8192 x 1152: 5.2 us against 5.3 on 64 x 64, 6.0 at 8 ways, 6.4 on 128 x 128),
+//            from 9 chunks on 64 x 64 and 8 ways (512 x 2048 x 4608: 7.8 against 9.1 and 12.2);
+//   up to 8: from 9 chunks on 64 x 64 and 4 ways (512 x 4096 x 4608: 11.5 against 12.6 on 128 x 128).
+// Beyond, staged tiles reuse their operands better.  -1: does not apply.
+static int split_shape(const GemmParams &p) {
+  const int64_t t = (((int64_t)p.M + 31) / 32) * (((int64_t)p.N + 31) / 32), cu = p.n_cu;
+  const bool deep = p.Kw64 > 32;  // at least 9 chunks
+  if (t <= 2 * cu) return 1;
+  if (t <= 4 * cu) return deep ? 3 : 0;
+  if (t <= 8 * cu && deep) return 2;
+  // rows beyond the exact range of the other kernel's accumulators
+  return p.Kw64 >= (1 << 18) - 2 ? 2 : -1;
+}
+
+bool fp4_split_applicable(const GemmParams &p) { return split_shape(p) >= 0; }
+
+bnn_status launch_gemm_fp4_split(GemmParams &p, int bmode, int emode, hipStream_t s, int shape) {
+  switch (shape < 0 ? split_shape(p) : shape) {
+    case 0: return launch_split<1, 4>(p, bmode, emode, s);
+    case 1: return launch_split<1, 8>(p, bmode, emode, s);
+    case 2: return launch_split<2, 4>(p, bmode, emode, s);
+    case 3: return launch_split<2, 8>(p, bmode, emode, s);
+    default: return BNN_ERR_UNSUPPORTED;
+  }
+}
+
+}  // namespace bnn

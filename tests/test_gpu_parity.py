@@ -1062,7 +1062,7 @@ def test_heuristic_kernel_selection_on_random_packed_convs():
 
 
 # ---------------------------------------------------------------- matrix-core GEMM on packed operands
-@pytest.mark.parametrize("cfg", [21, 22, 23, 24])
+@pytest.mark.parametrize("cfg", [21, 22, 23, 24, 25, 26, 27, 28])
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (129, 257, 128), (128, 256, 512), (65, 300, 129), (37, 152, 640 + 33),
                                    (200, 515, 1024), (64, 1028, 2321), (257, 130, 512 * 3 + 1)])
 def test_gemm_matrix_core_tiles(M, N, K, cfg):
@@ -1098,7 +1098,7 @@ MATRIX_CONV_CASES = [  # N, C, H, W, D, kH, kW, sH, sW, pH, pW
 ]
 
 
-@pytest.mark.parametrize("cfg", [21, 22, 23, 24])
+@pytest.mark.parametrize("cfg", [21, 22, 23, 24, 25, 26, 27, 28])
 @pytest.mark.parametrize("case", MATRIX_CONV_CASES)
 def test_conv_matrix_core_tiles(case, cfg):
     """int32, fp32, signs and pooled signs against the oracle, bit for bit."""
@@ -1118,3 +1118,20 @@ def test_conv_matrix_core_tiles(case, cfg):
     if ref.shape[2] % 2 == 0 and ref.shape[3] % 2 == 0:
         pref = oracle.pack_nhwc(oracle.scale_bias(oracle.maxpool2x2_i32(ref), d["scale"], d["bias"], "nchw"))
         assert np.array_equal(host(run(out="packed", pool=2)).view(np.uint64), pref)
+
+
+def test_gemm_rows_beyond_the_accumulators_exact_range():
+    """A wave's share of the row holds more than 2^23 values: its fp32 sums go to integers on the way."""
+    K = (1 << 26) + (1 << 24) + 77
+    print(f"gemm K={K}", flush=True)
+    rng = np.random.default_rng(7)
+    Kw = B.packed_words(K)
+    A, Bm = (rng.integers(0, 1 << 64, size=(n, Kw), dtype=np.uint64) for n in (2, 3))
+    A[1] = ~np.uint64(0)  # equal and opposite rows: the largest counts of both signs
+    Bm[1] = ~np.uint64(0)
+    Bm[2] = 0
+    got = host(B.bnn_xnor_gemm(_u64dev(A), _u64dev(Bm), K))
+    A[:, -1] &= np.uint64((1 << (K % 64)) - 1)
+    Bm[:, -1] &= np.uint64((1 << (K % 64)) - 1)
+    assert np.array_equal(got, _popcount_rows(A, Bm, K))
+    assert got[1, 1] == K and got[1, 2] == -K
