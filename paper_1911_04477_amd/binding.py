@@ -104,7 +104,9 @@ def _check(st: int, where: str) -> None:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the current stream of the current device as a raw handle: torch.cuda.current_stream() builds a Stream object
+    # on every call, 2.7 of the 8.4 us that a whole call through this binding took (0.1 us this way)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
