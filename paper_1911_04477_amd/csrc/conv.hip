@@ -155,8 +155,10 @@ __global__ __launch_bounds__(256) void conv2d_f32_sign_kernel(const float *__res
 // A workgroup stages the filter taps of up to 128 channels in LDS ([tap][channel], odd row
 // stride), then each wave walks over its pixel groups: 27 clamped loads per lane, four channel
 // groups x 27 matrix instructions, and the affine map + sign on the vector unit.
-constexpr int C1M_CH = 128;   // channels per workgroup (blockIdx.y)
-constexpr int C1M_RS = 129;   // LDS row stride of the tap-major filter tile
+// NG: channel groups of 32 per workgroup (blockIdx.y).  Four share a patch's loads; with too few pixels to give every
+// SIMD four waves that way (the chains of a group are 27 dependent instructions of 64 clocks), one group per
+// workgroup makes four times as many waves.
+constexpr int C1M_RS(int NG) { return 32 * NG + 1; }  // LDS row stride of the tap-major filter tile
 typedef float c1m_v32f __attribute__((ext_vector_type(32)));
 
 __device__ __forceinline__ uint32_t c1m_spread_nibbles(uint32_t m) {
@@ -167,15 +169,16 @@ __device__ __forceinline__ uint32_t c1m_spread_nibbles(uint32_t m) {
 // Stage the filter taps of channels ch0 .. ch0 + 127 tap-major in LDS (read [channel][tap]
 // contiguously; channels past D are zero) and their scale / bias (past D, or without an affine
 // map: fma(0, acc, -1) < 0, so such bits are 0).
+template <int NG>
 __device__ __forceinline__ void c1m_stage_filters(float *sTap, float *sSc, float *sBi, const float *__restrict__ w,
                                                   const float *__restrict__ scale, const float *__restrict__ bias,
                                                   int ch0, int nch, bool affine) {
   const int tid = threadIdx.x;
-  for (int idx = tid; idx < 27 * C1M_CH; idx += 256) {
+  for (int idx = tid; idx < 27 * 32 * NG; idx += 256) {
     const int ch = idx / 27, k = idx - 27 * ch;
-    sTap[k * C1M_RS + ch] = ch < nch ? w[(size_t)ch0 * 27 + idx] : 0.0f;
+    sTap[k * C1M_RS(NG) + ch] = ch < nch ? w[(size_t)ch0 * 27 + idx] : 0.0f;
   }
-  if (tid < C1M_CH) {
+  if (tid < 32 * NG) {
     const bool real = tid < nch && affine;
     sSc[tid] = real ? scale[ch0 + tid] : 0.0f;
     sBi[tid] = real ? bias[ch0 + tid] : -1.0f;
@@ -216,12 +219,13 @@ __device__ __forceinline__ void c1m_issue_patch(const float *__restrict__ x, uin
 }
 
 // 27 dependent matrix instructions: channel group g (32 channels) x this wave's 64 pixels.
+template <int NG>
 __device__ __forceinline__ c1m_v32f c1m_chain(const float *wg, const float (&xv)[27]) {
   c1m_v32f acc;
 #pragma unroll
   for (int r = 0; r < 32; ++r) acc[r] = 0.0f;
 #pragma unroll
-  for (int k = 0; k < 27; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x1f32(wg[k * C1M_RS], xv[k], acc, 0, 0, 0);
+  for (int k = 0; k < 27; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x1f32(wg[k * C1M_RS(NG)], xv[k], acc, 0, 0, 0);
   return acc;
 }
 
@@ -257,26 +261,26 @@ __device__ __forceinline__ uint32_t c1m_sign_bits(const c1m_v32f &acc, const flo
 // issue time, measured), so nothing is gained by interleaving the sign step with the next chain:
 // the loop is the plain sequence loads, one chain per group of 32 channels followed by its sign
 // step, store, and several resident waves per SIMD cover the load latency.
+template <int NG>
 __global__ __launch_bounds__(256, 4) void conv2d_f32_k27_mfma_sign_kernel(
     const float *__restrict__ x, const float *__restrict__ w, int H, int W, int D, int sH, int sW, int pH, int pW,
     int OH, int OW, const float *__restrict__ scale, const float *__restrict__ bias, uint64_t *__restrict__ outp,
     int cw_out, FastDiv divOW, FastDiv divOH, uint32_t total_pix, uint32_t ngroups, int groups_per_wave) {
-  __shared__ float sTap[27 * C1M_RS];
-  __shared__ __attribute__((aligned(16))) float sSc[C1M_CH];
-  __shared__ __attribute__((aligned(16))) float sBi[C1M_CH];
+  __shared__ float sTap[27 * C1M_RS(NG)];
+  __shared__ __attribute__((aligned(16))) float sSc[32 * NG];
+  __shared__ __attribute__((aligned(16))) float sBi[32 * NG];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, l32 = lane & 31;
-  const int ch0 = C1M_CH * (int)blockIdx.y;
+  const int ch0 = 32 * NG * (int)blockIdx.y;
   const uint32_t g_first = ((uint32_t)blockIdx.x * 4u + (uint32_t)wave) * (uint32_t)groups_per_wave;
   const uint32_t g_end = min(g_first + (uint32_t)groups_per_wave, ngroups);
-  const int word0 = 2 * (int)blockIdx.y;
   // the first patch is requested before the filters are staged, so the two latencies overlap
   // (a wave without pixel groups loads pixel 0's and discards it)
   float xv[27];
   uint32_t inside;
   c1m_issue_patch(x, g_first * 64u + (uint32_t)lane, total_pix, H, W, sH, sW, pH, pW, OH, OW, divOW, divOH, xv, inside);
-  const int nch = min(C1M_CH, D - ch0);  // >= 1 by the grid
-  c1m_stage_filters(sTap, sSc, sBi, w, scale, bias, ch0, nch, true);
+  const int nch = min(32 * NG, D - ch0);  // >= 1 by the grid
+  c1m_stage_filters<NG>(sTap, sSc, sBi, w, scale, bias, ch0, nch, true);
   __syncthreads();  // the only barrier: from here on the waves run independently
 
   for (uint32_t grp = g_first; grp < g_end; ++grp) {  // wave-uniform bounds
@@ -285,17 +289,27 @@ __global__ __launch_bounds__(256, 4) void conv2d_f32_k27_mfma_sign_kernel(
       c1m_issue_patch(x, p, total_pix, H, W, sH, sW, pH, pW, OH, OW, divOW, divOH, xv, inside);
 #pragma unroll
     for (int k = 0; k < 27; ++k) xv[k] = ((inside >> (k % 9)) & 1u) ? xv[k] : 0.0f;
-    uint32_t gw[4] = {0u, 0u, 0u, 0u};
+    uint32_t gw[NG];
 #pragma unroll
-    for (int g = 0; g < C1M_CH / 32; ++g) {
+    for (int g = 0; g < NG; ++g) gw[g] = 0u;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
       if (32 * g >= nch) break;  // workgroup-uniform: groups past the last channel keep zero bits
-      const c1m_v32f acc = c1m_chain(sTap + 32 * g + l32, xv);
+      const c1m_v32f acc = c1m_chain<NG>(sTap + 32 * g + l32, xv);
       gw[g] = c1m_sign_bits(acc, sSc, sBi, g, half);
     }
     if (p < total_pix) {
-      uint64_t *o = outp + (size_t)p * cw_out + word0;
-      o[0] = ((uint64_t)gw[1] << 32) | gw[0];
-      if (word0 + 1 < cw_out) o[1] = ((uint64_t)gw[3] << 32) | gw[2];
+      if constexpr (NG == 4) {
+        const int word0 = 2 * (int)blockIdx.y;
+        uint64_t *o = outp + (size_t)p * cw_out + word0;
+        o[0] = ((uint64_t)gw[1] << 32) | gw[0];
+        if (word0 + 1 < cw_out) o[1] = ((uint64_t)gw[3] << 32) | gw[2];
+      } else {  // a 32-channel half word; the last group also writes the half that holds no channel
+        const int h0 = (int)blockIdx.y;
+        uint32_t *o = reinterpret_cast<uint32_t *>(outp + (size_t)p * cw_out);
+        o[h0] = gw[0];
+        if (h0 + 1 == (int)gridDim.y && h0 + 1 < 2 * cw_out) o[h0 + 1] = 0u;
+      }
     }
   }
 }
@@ -309,13 +323,14 @@ __global__ __launch_bounds__(256) void conv2d_f32_k27_mfma_kernel(const float *_
                                                                   FastDiv divOH, uint32_t total_pix, uint32_t ngroups,
                                                                   int groups_per_wave, float *__restrict__ outf,
                                                                   int has_affine) {
-  __shared__ float sTap[27 * C1M_RS];
-  __shared__ float sSc[C1M_CH], sBi[C1M_CH];
+  constexpr int NG = 1;
+  __shared__ float sTap[27 * C1M_RS(NG)];
+  __shared__ float sSc[32 * NG], sBi[32 * NG];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, l32 = lane & 31;
-  const int ch0 = C1M_CH * (int)blockIdx.y;
-  const int nch = min(C1M_CH, D - ch0);  // >= 1 by the grid
-  c1m_stage_filters(sTap, sSc, sBi, w, scale, bias, ch0, nch, has_affine != 0);
+  const int ch0 = 32 * NG * (int)blockIdx.y;
+  const int nch = min(32 * NG, D - ch0);  // >= 1 by the grid
+  c1m_stage_filters<NG>(sTap, sSc, sBi, w, scale, bias, ch0, nch, has_affine != 0);
   __syncthreads();  // the only barrier
 
   const size_t ohw = (size_t)OH * OW;
@@ -339,15 +354,13 @@ __global__ __launch_bounds__(256) void conv2d_f32_k27_mfma_kernel(const float *_
       const uint32_t qn = fdiv(fdiv(qc, divOW), divOH);
       obase[b] = (size_t)qn * D * ohw + ((size_t)qc - (size_t)qn * ohw);
     }
-#pragma unroll 1
-    for (int g = 0; g < C1M_CH / 32; ++g) {
-      if (32 * g >= nch) break;  // workgroup-uniform
-      const c1m_v32f acc = c1m_chain(sTap + 32 * g + l32, xv);
+    {
+      const c1m_v32f acc = c1m_chain<NG>(sTap + l32, xv);
 #pragma unroll
       for (int b = 0; b < 2; ++b)
 #pragma unroll
         for (int rr = 0; rr < 16; ++rr) {
-          const int chl = 32 * g + 8 * (rr >> 2) + 4 * half + (rr & 3);
+          const int chl = 8 * (rr >> 2) + 4 * half + (rr & 3);
           if (chl < nch && ov[b]) {
             const float a = acc[16 * b + rr];
             outf[obase[b] + (size_t)(ch0 + chl) * ohw] = has_affine ? fmaf(sSc[chl], a, sBi[chl]) : a;
@@ -358,15 +371,20 @@ __global__ __launch_bounds__(256) void conv2d_f32_k27_mfma_kernel(const float *_
 }
 
 // Launch shape of the matrix-core first layer: one wave per `*gpw` groups of 64 pixels (enough
-// groups per wave to amortise the filter staging, enough waves to give every SIMD two).
-static dim3 c1m_grid(int64_t total_pix, int D, int *gpw, int64_t wave_slots = 2048) {
+// groups per wave to amortise the filter staging, enough waves to give every SIMD four).
+static dim3 c1m_grid(int64_t total_pix, int D, int ng, int *gpw) {
   const int64_t ngroups = (total_pix + 63) / 64;
-  int64_t g = ngroups / wave_slots;
+  int64_t g = ngroups / 4096;
   g = g < 1 ? 1 : (g > 8 ? 8 : g);
   *gpw = (int)g;
   const int64_t waves = (ngroups + g - 1) / g;
-  return dim3((unsigned)((waves + 3) / 4), (unsigned)((D + C1M_CH - 1) / C1M_CH));
+  return dim3((unsigned)((waves + 3) / 4), (unsigned)((D + 32 * ng - 1) / (32 * ng)));
 }
+
+// Packed signs: one channel group per workgroup while that does not give a SIMD more than four waves per 128 channels
+// (32 x 32 maps, 128 channels: batch 1 8.7 -> 4.4 us, batch 32 9.3 -> 5.7, batch 64 9.6 -> 8.2; batch 128 13.5 against 14.0,
+// batch 256 22.5 against 27.3: the patch's loads and selects are repeated per group).
+static bool c1m_split(int64_t total_pix) { return (total_pix + 63) / 64 <= 4 * (int64_t)device_cu_count(); }
 
 // Filter bank of a fully-connected layer whose input is a flattened NCHW map [C, H, W],
 // re-ordered to the packed NHWC bit order (h, w, c) of the activations: a common
@@ -558,12 +576,17 @@ extern "C" bnn_status bnn_conv2d_f32_sign(const float *x, const float *w, int N,
     const dim3 block(256);
     if (K == 27 && C == 3 && kH == 3 && kW == 3) {
       int gpw;
-      const dim3 grid = c1m_grid(total, D, &gpw, 4096);  // four resident waves per SIMD
+      const bool split = c1m_split(total);
+      const dim3 grid = c1m_grid(total, D, split ? 1 : 4, &gpw);
       const uint32_t ngroups = (uint32_t)((total + 63) / 64);
       const int cw = (int)bnn_packed_words(D);
       const FastDiv dOW((uint32_t)OW), dOH((uint32_t)OH);
-      hipLaunchKernelGGL(conv2d_f32_k27_mfma_sign_kernel, grid, block, 0, s, x, w, H, W, D, sH, sW, pH, pW, (int)OH,
-                         (int)OW, scale, bias, out_packed, cw, dOW, dOH, (uint32_t)total, ngroups, gpw);
+      if (split)
+        hipLaunchKernelGGL(conv2d_f32_k27_mfma_sign_kernel<1>, grid, block, 0, s, x, w, H, W, D, sH, sW, pH, pW, (int)OH,
+                           (int)OW, scale, bias, out_packed, cw, dOW, dOH, (uint32_t)total, ngroups, gpw);
+      else
+        hipLaunchKernelGGL(conv2d_f32_k27_mfma_sign_kernel<4>, grid, block, 0, s, x, w, H, W, D, sH, sW, pH, pW, (int)OH,
+                           (int)OW, scale, bias, out_packed, cw, dOW, dOH, (uint32_t)total, ngroups, gpw);
     } else {
       const dim3 grid((unsigned)((total + 255) / 256));
       hipLaunchKernelGGL(conv2d_f32_sign_kernel<0>, grid, block, 0, s, x, w, C, H, W, D, kH, kW, sH, sW, pH, pW,
@@ -581,8 +604,10 @@ bnn_status launch_conv2d_f32_k27(const float *x, const float *w, int N, int H, i
                                  int pW, const float *scale, const float *bias, float *out, hipStream_t s) {
   const int64_t OH = bnn_conv_out_dim(H, 3, sH, pH), OW = bnn_conv_out_dim(W, 3, sW, pW);
   const int64_t total = (int64_t)N * OH * OW;
+  // one channel group per workgroup at every size: the stores of the map hide the repeated loads (batch 1 17.6 -> 6.0 us,
+  // batch 64 20.6 -> 13.2, batch 256 42.5 -> 41.5)
   int gpw;
-  const dim3 grid = c1m_grid(total, D, &gpw), block(256);
+  const dim3 grid = c1m_grid(total, D, 1, &gpw), block(256);
   hipLaunchKernelGGL(conv2d_f32_k27_mfma_kernel, grid, block, 0, s, x, w, H, W, D, sH, sW, pH, pW, (int)OH, (int)OW,
                      scale, bias, FastDiv((uint32_t)OW), FastDiv((uint32_t)OH), (uint32_t)total,
                      (uint32_t)((total + 63) / 64), gpw, out, scale ? 1 : 0);

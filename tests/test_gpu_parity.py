@@ -1135,3 +1135,18 @@ def test_gemm_rows_beyond_the_accumulators_exact_range():
     Bm[:, -1] &= np.uint64((1 << (K % 64)) - 1)
     assert np.array_equal(got, _popcount_rows(A, Bm, K))
     assert got[1, 1] == K and got[1, 2] == -K
+
+
+@pytest.mark.parametrize("N,H,W,D", [(1, 7, 9, 33), (2, 16, 16, 96), (1, 8, 8, 200), (70, 32, 32, 40), (5, 33, 31, 64)])
+def test_first_layer_few_and_many_pixels(N, H, W, D):
+    """The 3x3x3 layer with one channel group per workgroup (few pixels) and four (more than 64 per compute unit times
+    four), channel counts off the group of 32; extreme magnitudes, signs and maps against the oracle's fma chains."""
+    print(f"first layer N={N} {H}x{W} D={D}", flush=True)
+    rng = np.random.default_rng(N + H + W + D)
+    x = (rng.standard_normal((N, 3, H, W)) * 2.0 ** rng.integers(-40, 40, size=(N, 3, H, W))).astype(np.float32)
+    w = rng.standard_normal((D, 3, 3, 3)).astype(np.float32)
+    sc, bi = rng.standard_normal(D).astype(np.float32), rng.standard_normal(D).astype(np.float32)
+    ref = oracle.conv2d_f32_seq(x, w, (1, 1), (1, 1), sc, bi)
+    assert np.array_equal(host(B.bnn_conv2d_f32(dev(x), dev(w), (1, 1), (1, 1), dev(sc), dev(bi))), ref)
+    got = as_u64(B.bnn_conv2d_f32_sign(dev(x), dev(w), dev(sc), dev(bi), (1, 1), (1, 1)))
+    assert np.array_equal(got, oracle.pack_nhwc(ref))
