@@ -197,12 +197,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
 #pragma unroll
       for (int i = 0; i < PA; ++i) ra[i] = *reinterpret_cast<const u32x4 *>(ab + (aoff[i] + eo));
     } else {
-      const uint32_t w0 = (uint32_t)min(2 * e, p.Kw64 - 1) * 8u, w1 = (uint32_t)min(2 * e + 1, p.Kw64 - 1) * 8u;
-#pragma unroll
-      for (int i = 0; i < PA; ++i) {
-        ra[i].lo = *reinterpret_cast<const u32x2 *>(ab + (size_t)aoff[i] + w0);
-        ra[i].hi = *reinterpret_cast<const u32x2 *>(ab + (size_t)aoff[i] + w1);
-      }
+      const uint32_t wo = (uint32_t)max(min(2 * e, p.Kw64 - 2), 0) * 8u;
+      load_pieces_any<PA>(ra, p.Kw64 > 1, [&](int i) { return ab + (size_t)aoff[i] + wo; });
     }
   };
   load_a(0);
@@ -233,12 +229,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
 #pragma unroll
       for (int i = 0; i < PB; ++i) rb[i] = *reinterpret_cast<const u32x4 *>(brow[i] + eo);
     } else if constexpr (GM == GM_EXPL8) {
-      const uint32_t w0 = (uint32_t)min(2 * e, p.Kw64 - 1) * 8u, w1 = (uint32_t)min(2 * e + 1, p.Kw64 - 1) * 8u;
-#pragma unroll
-      for (int i = 0; i < PB; ++i) {
-        rb[i].lo = *reinterpret_cast<const u32x2 *>(brow[i] + w0);
-        rb[i].hi = *reinterpret_cast<const u32x2 *>(brow[i] + w1);
-      }
+      const uint32_t wo = (uint32_t)max(min(2 * e, p.Kw64 - 2), 0) * 8u;
+      load_pieces_any<PB>(rb, p.Kw64 > 1, [&](int i) { return brow[i] + wo; });
     } else if constexpr (GM == GM_ANY) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -267,6 +259,15 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
     for (int d = 0; d < 4; ++d) {
       const int left = p.Kbits - (4 * e + d) * 32;  // bits of this dword that exist (host: Kbits < 2^24)
       m[d] = left >= 32 ? 0xffffffffu : (left <= 0 ? 0u : (1u << left) - 1u);
+    }
+    const bool shifted = 2 * e == p.Kw64 - 1 && e > 0;  // a row's odd last word, read as the second of its piece
+    if (!a16 && shifted) {
+#pragma unroll
+      for (int i = 0; i < PA; ++i) ra[i].lo = ra[i].hi;
+    }
+    if (GM == GM_EXPL8 && shifted) {
+#pragma unroll
+      for (int i = 0; i < PB; ++i) rb[i].lo = rb[i].hi;
     }
 #pragma unroll
     for (int i = 0; i < PA; ++i) ra[i] &= m;

@@ -56,28 +56,20 @@ __global__ __launch_bounds__(64 * KS) void xnor_gemm_fp4_split_kernel(GemmParams
   const uint64_t part = (g.C & 63) ? (1ull << (g.C & 63)) - 1ull : ~0ull;  // real channels of a tap's last word
   auto load_chunk = [&](int c, u32x4 (&a)[WT], u32x4 (&b)[WT]) {
     const int w = 4 * c + 2 * half;
-    const uint32_t w0 = (uint32_t)min(w, p.Kw64 - 1), w1 = (uint32_t)min(w + 1, p.Kw64 - 1);
+    const uint32_t wo = (uint32_t)max(min(w, p.Kw64 - 2), 0) * 8u;
     if (a16) {
       const uint32_t o = (uint32_t)min(w, p.Kw64 - 2) * 8u;
 #pragma unroll
       for (int i = 0; i < WT; ++i) a[i] = *reinterpret_cast<const u32x4 *>(arow[i] + o);
     } else {
-#pragma unroll
-      for (int i = 0; i < WT; ++i) {
-        a[i].lo = *reinterpret_cast<const u32x2 *>(arow[i] + w0 * 8u);
-        a[i].hi = *reinterpret_cast<const u32x2 *>(arow[i] + w1 * 8u);
-      }
+      load_pieces_any<WT>(a, p.Kw64 > 1, [&](int i) { return arow[i] + wo; });
     }
     if constexpr (GM == SG_EXPL16) {
       const uint32_t o = (uint32_t)min(w, p.Kw64 - 2) * 8u;
 #pragma unroll
       for (int j = 0; j < WT; ++j) b[j] = *reinterpret_cast<const u32x4 *>(brow[j] + o);
     } else if constexpr (GM == SG_EXPL8) {
-#pragma unroll
-      for (int j = 0; j < WT; ++j) {
-        b[j].lo = *reinterpret_cast<const u32x2 *>(brow[j] + w0 * 8u);
-        b[j].hi = *reinterpret_cast<const u32x2 *>(brow[j] + w1 * 8u);
-      }
+      load_pieces_any<WT>(b, p.Kw64 > 1, [&](int j) { return brow[j] + wo; });
     } else if (cw_even) {  // both words belong to one tap
       const uint32_t ww = (uint32_t)min(w, p.Kw64 - 2);
       const uint32_t tap = fdiv_sel(ww, g.divCw), cw = ww - tap * (uint32_t)g.Cw;
@@ -94,7 +86,7 @@ __global__ __launch_bounds__(64 * KS) void xnor_gemm_fp4_split_kernel(GemmParams
     } else {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const uint32_t ww = h ? w1 : w0;
+        const uint32_t ww = (uint32_t)min(w + h, p.Kw64 - 1);
         const uint32_t tap = fdiv_sel(ww, g.divCw), cw = ww - tap * (uint32_t)g.Cw;
         const uint32_t kh = fdiv_sel(tap, g.divKW), kw = tap - kh * (uint32_t)g.kW;
         const uint64_t pad = cw + 1u == (uint32_t)g.Cw ? part : ~0ull;  // taps outside the image: +1 in every channel
@@ -117,8 +109,11 @@ __global__ __launch_bounds__(64 * KS) void xnor_gemm_fp4_split_kernel(GemmParams
       const int left = p.Kbits - (8 * c + 4 * half + d) * 32;  // host: Kbits < 2^24
       m[d] = left >= 32 ? 0xffffffffu : (left <= 0 ? 0u : (1u << left) - 1u);
     }
+    const bool shifted = 4 * c + 2 * half == p.Kw64 - 1 && p.Kw64 > 1;  // a row's odd last word, read as the second
 #pragma unroll
     for (int i = 0; i < WT; ++i) {
+      if (!a16 && shifted) a[i].lo = a[i].hi;
+      if (GM == SG_EXPL8 && shifted) b[i].lo = b[i].hi;
       a[i] &= m;
       b[i] &= m;
     }
