@@ -110,6 +110,7 @@ extern "C" const char *bnn_kernel_name(int kernel_id) {
     case bnn::KID_PACK_CONV_WEIGHT: return "pack_conv_weight";
     case bnn::KID_ENCODE_NCHW: return "encode_nchw";
     case bnn::KID_IM2COL_GATHER: return "im2col_gather";
+    case bnn::KID_IM2COL_BAND: return "im2col_band";
     case bnn::KID_XNOR_GEMM: return "xnor_gemm";
     case bnn::KID_XNOR_GEMM_SMALL: return "xnor_gemm_small";
     case bnn::KID_XNOR_GEMM_LOWK: return "xnor_gemm_lowk";

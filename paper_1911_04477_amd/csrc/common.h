@@ -29,7 +29,8 @@ enum KernelId : int {
   KID_XNOR_GEMM_MFMA_FP4X = 18,
   KID_XNOR_GEMM_FP4 = 19,
   KID_XNOR_GEMM_FP4_SPLIT = 20,
-  KID_COUNT = 21
+  KID_IM2COL_BAND = 21,
+  KID_COUNT = 22
 };
 
 // Timing hook: records an event pair around a launch when profiling is on.
@@ -159,8 +160,11 @@ bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, i
 bool fp4_split_applicable(const GemmParams &p);  // whether its rule on sizes takes the problem
 bnn_status launch_gemm_fp4_split(GemmParams &p, int bmode, int emode, hipStream_t s, int shape);
 
+// The binarization predicate: +0.0 and -0.0 -> 1, negative and NaN -> 0.
+__device__ __forceinline__ bool sign_bit(float v) { return v >= 0.0f; }
+
 // Conv helpers (im2col.hip).  check_conv_geometry validates shapes and 32-bit limits;
-// run_im2col launches encode (+ gather) with already validated arguments.
+// run_im2col launches encode (+ gather), or both in one kernel, with already validated arguments.
 bnn_status check_conv_geometry(int N, int C, int H, int W, int kH, int kW, int sH, int sW, int pH, int pW);
 bnn_status run_im2col(const float *x, int N, int C, int H, int W, int kH, int kW, int sH, int sW, int pH, int pW,
                       uint64_t *cols, void *workspace, hipStream_t s);

@@ -15,9 +15,6 @@
 
 namespace bnn {
 
-// The binarization predicate: +0.0 and -0.0 -> 1, negative and NaN -> 0.
-__device__ __forceinline__ bool sign_bit(float v) { return v >= 0.0f; }
-
 constexpr int ENC_BLOCK = 256;
 
 constexpr int ENC_WORDS_PER_WAVE = 16;
@@ -243,19 +240,24 @@ extern "C" bnn_status bnn_pack_conv_weight(const float *w, int D, int C, int kH,
 }
 
 namespace bnn {
+// Sizes that launch_encode_nchw takes.
+bool encode_nchw_supported(int N, int C, int H, int W, int OHp, int OWp) {
+  if ((int64_t)N * OHp * OWp > 0x7fffffffLL) return false;
+  if ((int64_t)ENCN_PIX * (2 * bnn_packed_words(C) + 1) * (int64_t)sizeof(uint32_t) > 64 * 1024) return false;  // C > 8128
+  // 32-bit per-lane byte offsets: a workgroup's 64 pixels span at most `span` images past its first
+  const int64_t span = (ENCN_PIX + (int64_t)OHp * OWp - 1) / ((int64_t)OHp * OWp);
+  return (span + 1) * (int64_t)C * H * W * 4 <= 0x7fffffffLL;
+}
+
 // Host launcher used by the im2col / conv drivers.  Arguments are validated by the caller.
 bnn_status launch_encode_nchw(const float *x, int N, int C, int H, int W, int OHp, int OWp, int sH, int sW,
                               uint64_t *out, hipStream_t s) {
   const int64_t total = (int64_t)N * OHp * OWp;
   if (total == 0) return BNN_OK;
-  if (total > 0x7fffffffLL) return BNN_ERR_UNSUPPORTED;
+  if (!encode_nchw_supported(N, C, H, W, OHp, OWp)) return BNN_ERR_UNSUPPORTED;
   const int Cw = (int)bnn_packed_words(C);
   const unsigned blocks = (unsigned)((total + ENCN_PIX - 1) / ENCN_PIX);
   const size_t lds = (size_t)ENCN_PIX * (2 * Cw + 1) * sizeof(uint32_t);
-  if (lds > 64 * 1024) return BNN_ERR_UNSUPPORTED;  // C > 8128 channels
-  // 32-bit per-lane byte offsets: a workgroup's 64 pixels span at most `span` images past its first
-  const int64_t span = (ENCN_PIX + (int64_t)OHp * OWp - 1) / ((int64_t)OHp * OWp);
-  if ((span + 1) * (int64_t)C * H * W * 4 > 0x7fffffffLL) return BNN_ERR_UNSUPPORTED;
   FastDiv dOW((uint32_t)OWp), dOH((uint32_t)OHp);
   ProfScope ps(KID_ENCODE_NCHW, s);
   if (sW > 1 && 4 * Cw <= 65535) {

@@ -306,3 +306,12 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode != 0
     assert "ONE GPU" in r.stderr
+
+
+def test_im2col_size_limits(L):
+    """What the two-launch form cannot address is refused before the form is chosen, also where few rows are read."""
+    im = L.bnn_im2col_packed
+    big = 1 << 40
+    for geo in ((1, 64, 300000, 64, 2, 2, 1000, 1, 0, 0),  # image above 2^31 bytes, 300 of its rows read
+                (1, 8129, 4, 4, 3, 3, 1, 1, 1, 1)):        # 64 packed pixels above the LDS
+        assert im(A16, *geo, A16, A16, big, None) == UNSUPPORTED

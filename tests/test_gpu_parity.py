@@ -1150,3 +1150,28 @@ def test_first_layer_few_and_many_pixels(N, H, W, D):
     assert np.array_equal(host(B.bnn_conv2d_f32(dev(x), dev(w), (1, 1), (1, 1), dev(sc), dev(bi))), ref)
     got = as_u64(B.bnn_conv2d_f32_sign(dev(x), dev(w), dev(sc), dev(bi), (1, 1), (1, 1)))
     assert np.array_equal(got, oracle.pack_nhwc(ref))
+
+
+# ---------------------------------------------------------------- im2col in one launch / in two
+@pytest.mark.parametrize("case", [
+    # N, C, H, W, kH, kW, sH, sW, pH, pW
+    (128, 64, 32, 32, 3, 3, 1, 1, 1, 1),   # two bands per image, halo rows on both sides
+    (250, 3, 9, 11, 3, 3, 1, 1, 1, 1),     # one band per image, a partial granule and an empty one
+    (256, 65, 4, 4, 3, 3, 1, 1, 1, 1),     # a workgroup per compute unit, odd words per pixel
+    (257, 64, 4, 4, 3, 3, 1, 1, 1, 1),     # more images than compute units: two launches
+    (7, 96, 20, 13, 5, 3, 2, 1, 2, 0),     # strides and paddings that differ, last band shorter
+    (3, 130, 17, 9, 2, 2, 3, 2, 0, 1),     # rows that no tap reads
+    (2, 40, 3, 3, 3, 3, 1, 1, 6, 6),       # bands that see padding only
+    (1, 100, 40, 1, 7, 1, 1, 1, 3, 0),     # one column
+    (1, 4096, 5, 5, 3, 3, 1, 1, 1, 1),     # one pixel fills the LDS budget early: two launches
+    (1, 2000, 6, 2, 3, 3, 1, 1, 1, 1),
+    (6, 33, 64, 5, 1, 3, 4, 1, 0, 1),      # row stride above the kernel's height
+])
+def test_im2col_bands(case):
+    """Both sides of the rule that takes small inputs to one launch.  Exact: packed words."""
+    print(f"im2col bands case={case}", flush=True)
+    N, C, H, W, kH, kW, sH, sW, pH, pW = case
+    rng = np.random.default_rng(sum(case))
+    x = inputs.inject_specials(rng.standard_normal((N, C, H, W)).astype(np.float32), 3, frac=0.01)
+    cols = as_u64(B.bnn_im2col_packed(dev(x), kH, kW, (sH, sW), (pH, pW)))
+    assert np.array_equal(cols, oracle.im2col_packed(x, kH, kW, (sH, sW), (pH, pW)))
