@@ -106,7 +106,7 @@ __global__ __launch_bounds__(64 * KS) void xnor_gemm_fp4_split_kernel(GemmParams
     u32x4 m;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-      const int left = p.Kbits - (8 * c + 4 * half + d) * 32;  // host: Kbits < 2^24
+      const int left = (int)((uint32_t)p.Kbits - (uint32_t)(8 * c + 4 * half + d) * 32u);  // any row length
       m[d] = left >= 32 ? 0xffffffffu : (left <= 0 ? 0u : (1u << left) - 1u);
     }
     const bool shifted = 4 * c + 2 * half == p.Kw64 - 1 && p.Kw64 > 1;  // a row's odd last word, read as the second
