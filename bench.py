@@ -3,7 +3,7 @@
 
 A "step" is one pass of the whole hot path over one batch of synthetic input.  The
 default workload is the binarized VGG-small stack at batch 256: real-valued first layer
-with sign-packed output, six binarized 3x3 convolutions as implicit XOR-popcount GEMMs over
+with sign-packed output, five binarized 3x3 convolutions as implicit Xnor-Bitcount GEMMs over
 packed NHWC activations (pool + scale/bias + sign + pack in the GEMM epilogue), the binarized
 FC layer with fp32 epilogue and the fp32 classifier.  `--stack unfused` runs the same network
 through bnn_conv2d (sign-encode, packed operands, int32 NCHW maps, separate glue kernels).
@@ -12,11 +12,10 @@ line; the other configurations, the streaming kernels and the MFMA ablation ride
 
   python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload cfg4|cfg2|cfg3|cfg5a|cfg5b]
 
-The defaults (200 warm-up + 1000 timed steps, about a third of a second of GPU time) matter: a
-GPU that was idle reaches its sustained clocks only after about 35 ms of continuous work (the
-step falls from 0.303 to 0.277 ms over the first 80 steps and stays there), so a run of 5 + 20
-steps of this 0.28 ms step, 7 ms in all, reads 9 % slower than the sustained rate.  Such a run
-prints the 200 + 1000 figure beside its own, as `sustained`.
+The defaults (200 warm-up + 1000 timed steps, about 0.15 seconds of GPU time) matter: a GPU that
+was idle reaches its sustained clocks only after about 35 ms of continuous work, so a run of 5 + 20
+steps reads a few percent off the sustained rate.  Such a run prints the 200 + 1000 figure beside
+its own, as `sustained`.
 """
 from __future__ import annotations
 
@@ -421,7 +420,7 @@ def small_batch_latency(args):
 
 
 def mfma_ablation():
-    """The MFMA ablations beside the VALU GEMM on the GEMM view of cfg 5a and cfg 3: int8 and fp4 with the
+    """The MFMA ablations beside the product path and the VALU GEMM on the GEMM view of cfg 5a and cfg 3: int8 and fp4 with the
     bits expanded on the fly, and fp4 on operands kept expanded in memory (the expansion timed apart)."""
     import torch
     from paper_1911_04477_amd import binding as B
@@ -459,7 +458,7 @@ def mfma_ablation():
                      "expand_B_GBs": round((Bm.numel() * 8 + B4.numel()) / (te / 200) / 1e9, 1)}
         del A, Bm, C, C2, C3, C4, A4, B4
     # the same ablation as a convolution: patches gathered inside the GEMM from a 4-bit NHWC image,
-    # beside the VALU convolution from the 1-bit image (both int32 NCHW out, images already in their format)
+    # beside the product path and the VALU convolution from the 1-bit image (all int32 NCHW out, images in their format)
     for name, (N, Cc, H, W, D) in (("cfg5a_conv_64x256x56x56_to_256", (64, 256, 56, 56, 256)),
                                    ("cfg3_conv_128x128x32x32_to_128", (128, 128, 32, 32, 128))):
         Cw = Cc // 64
@@ -606,7 +605,7 @@ def main():
     dom_s, dom_ops, dom_n = by_name[dom]
     gemm_s = sum(t for _, t, _ in launches)
     method = "one HIP-event pair around each launch inside a pass of the stack (library hook)"
-    matrix = dom == "xnor_gemm_fp4"
+    matrix = dom.startswith("xnor_gemm_fp4")
     peak = FP4_PEAK_TOPS if matrix else VALU_PEAK_TLANEOPS
 
     def rate(ops, t):
@@ -627,7 +626,7 @@ def main():
             per_launch[i]["TBOPS"] = round(launches[i][2] * BOPS_PER_LANEOP / t / 1e12, 1)
         method = "each launch of the step replayed 50x back to back between one HIP-event pair on the launch stream"
     for e, (_, _, ops) in zip(per_launch, launches):
-        e["frac"] = round(e["TBOPS"] / (FP4_PEAK_TOPS if e["kernel"] == "xnor_gemm_fp4" else VALU_PEAK_TLANEOPS * BOPS_PER_LANEOP), 4)
+        e["frac"] = round(e["TBOPS"] / (FP4_PEAK_TOPS if e["kernel"].startswith("xnor_gemm_fp4") else VALU_PEAK_TLANEOPS * BOPS_PER_LANEOP), 4)
     achieved = rate(dom_ops, dom_s)
     probes = valu_probes()
     fracs = [achieved / peak] + [e["frac"] for e in per_launch]
@@ -635,7 +634,8 @@ def main():
         print(f"bench.py: WARNING roofline fraction above 1 ({max(fracs):.4f}): the derived peak is not a ceiling",
               file=sys.stderr)
     roofline = {
-        "kernel": {"xnor_gemm": "xnor_gemm_kernel", "xnor_gemm_fp4": "xnor_gemm_fp4_kernel"}.get(dom, dom),
+        "kernel": {"xnor_gemm": "xnor_gemm_kernel", "xnor_gemm_fp4": "xnor_gemm_fp4_kernel",
+                   "xnor_gemm_fp4_split": "xnor_gemm_fp4_split_kernel"}.get(dom, dom),
         "bound": "mfma" if matrix else "alu", "achieved": round(achieved, 3), "peak": round(peak, 2),
         "unit": "TOP/s" if matrix else "Tlaneop/s", "frac": round(achieved / peak, 4),
         "valu_peak_Tlaneops": round(VALU_PEAK_TLANEOPS, 2), "valu_peak_nominal_4clk": round(VALU_PEAK_NOMINAL_4CLK, 2),

@@ -1,7 +1,12 @@
 // Xnor-Bitcount GEMM (section 3.2 of the paper) for gfx950, in the exclusive-or form
 //     C[m,n] = K - 2 * sum_w popcount(A[m,w] ^ B[n,w]).
 //
-// CDNA4 has no 1-bit matrix instruction, so the contraction runs on the vector ALU:
+// This file holds the vector-ALU form of the GEMM and the rule that picks a kernel for a call (run_gemm).  No call
+// without a forced configuration runs the vector-ALU form any more: the matrix-core kernels (gemm_fp4.hip,
+// gemm_fp4_split.hip) are faster at every size that the short-row kernel (gemm_lowk.hip) leaves.  It stays as the
+// yardstick that computes the method literally and as the second implementation that tests compare with.
+//
+// CDNA4 has no 1-bit matrix instruction; on the vector ALU the contraction costs
 // two lane-instructions per 32 bit-MACs per output (v_xor_b32, then v_bcnt_u32_b32
 // which adds its popcount into the accumulator).  The kernel is built so that the
 // inner loop is almost nothing else:

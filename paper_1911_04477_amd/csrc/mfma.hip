@@ -1,4 +1,4 @@
-// ABLATION, not the main path: the same binarized GEMM on the matrix cores.
+// ABLATIONS, not the main path (gemm_fp4.hip): earlier forms of the binarized GEMM on the matrix cores.
 //
 // CDNA4 has no 1-bit MFMA, so each packed bit is expanded to an int8 (0 or 1) on the fly and
 // V_MFMA_I32_32X32X32_I8 computes S[m,n] = sum_k a_k * b_k, the number of positions where
