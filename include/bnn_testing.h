@@ -56,6 +56,17 @@ BNN_API bnn_status bnn_testing_conv2d_packed(const uint64_t *x_packed, const uin
                                              void *stream);
 
 /*
+ * bnn_testing_conv_region -- host only, launches nothing: the input region that the matrix-core convolution
+ * keeps in LDS for tiles of `columns` output pixels (128 or 256).  Returns 1 and fills region[] with
+ *   0 the bound on a tile's input rows   1 pixels per region row   2 bytes between the planes of two words
+ *   3 bytes of the region,
+ * 0 where such a convolution gathers from memory instead, -1 for arguments bnn_conv2d_packed refuses.
+ */
+#define BNN_TESTING_REGION_VALUES 4
+BNN_API int bnn_testing_conv_region(int N, int C, int H, int W, int kH, int kW, int sH, int sW, int pH, int pW,
+                                    int pool, int columns, int64_t *region);
+
+/*
  * bnn_xnor_gemm_mfma_fp4_expanded on a chosen workgroup tile (rows x columns of C):
  *   -1 the choice of bnn.h's entry point;  0 128 x 128;  1 256 x 128;  2 128 x 256.
  * Other values: BNN_ERR_SHAPE.

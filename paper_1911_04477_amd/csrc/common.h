@@ -155,6 +155,7 @@ bnn_status launch_lowk(GemmParams &p, int groups, hipStream_t s);
 // Matrix-core GEMM on packed operands (gemm_fp4.hip): bmode / emode as for run_gemm; shape: tile number or -1;
 // region: convolutions may keep a tile's input region in LDS (false: always the general gather).
 bool fp4_applicable(const GemmParams &p);
+bool halo_region(GemmParams &p, int bn, bool pool, int64_t &rows);  // host only: p.halo from p.g and p.Kw64
 bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, int shape, bool region);
 // The same with the reduction axis split over the waves of a workgroup, for few outputs (gemm_fp4_split.hip).
 bool fp4_split_applicable(const GemmParams &p);  // whether its rule on sizes takes the problem

@@ -556,6 +556,23 @@ extern "C" bnn_status bnn_testing_conv2d_packed(const uint64_t *x_packed, const 
                             out_packed, scale, bias, stream, tune);
 }
 
+// Declared in bnn_testing.h.
+extern "C" int bnn_testing_conv_region(int N, int C, int H, int W, int kH, int kW, int sH, int sW, int pH, int pW,
+                                       int pool, int columns, int64_t *region) {
+  if (check_conv_geometry(N, C, H, W, kH, kW, sH, sW, pH, pW) != BNN_OK || N == 0 || !region || columns <= 0 ||
+      (pool != 0 && pool != 2))
+    return -1;
+  GemmParams p = {};
+  fill_geom(p.g, nullptr, N, C, H, W, kH, kW, sH, sW, pH, pW, pool);
+  if (pool && ((p.g.OH & 1) || (p.g.OW & 1))) return -1;
+  p.Kw64 = (int)bnn_conv_kwords(C, kH, kW);
+  int64_t rows = 0;
+  if (!halo_region(p, columns, pool != 0, rows)) return 0;
+  const int64_t v[BNN_TESTING_REGION_VALUES] = {rows, p.halo.Wp, p.halo.plane, p.halo.bytes};
+  for (int i = 0; i < BNN_TESTING_REGION_VALUES; ++i) region[i] = v[i];
+  return 1;
+}
+
 extern "C" bnn_status bnn_conv2d_f32_sign(const float *x, const float *w, int N, int C, int H, int W, int D, int kH,
                                           int kW, int sH, int sW, int pH, int pW, const float *scale,
                                           const float *bias, uint64_t *out_packed, void *stream) {

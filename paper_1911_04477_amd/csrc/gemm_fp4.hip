@@ -72,7 +72,7 @@ __device__ __forceinline__ void load_region(const ConvGeom &g, const HaloGeom &h
                                             int rows, uint64_t part, int wave, int lane, const Between &between) {
   constexpr int NW = T / 64, BATCH = 8;
   const int rowitems = hg.Wp * hg.ppp;
-  const uint32_t rowbytes = (uint32_t)g.W * (uint32_t)g.Cw * 8u;
+  const uint32_t rowbytes = (uint32_t)g.W * (uint32_t)g.Cw * 8u;  // host: below 2^32
   bool pending = true;
 #pragma unroll 1
   for (int rr = wave; rr < rows; rr += BATCH * NW) {
@@ -469,8 +469,9 @@ static int64_t cells_touched(int64_t len, int64_t cell) {
   return (len - 2) / cell + 2;
 }
 
-// Fills p.halo for column tiles of bn; whether the region (and the table of word distances) is of a size to keep in LDS.
-static bool halo_region(GemmParams &p, int bn, bool pool) {
+// Fills p.halo for column tiles of bn; whether the region (and the table of word distances) is of a size to keep in LDS
+// and the image's rows are of a length that the copy into it can step over.  rows: upper bound of a tile's input rows.
+bool halo_region(GemmParams &p, int bn, bool pool, int64_t &rows) {
   const ConvGeom &g = p.g;
   HaloGeom &h = p.halo;
   const int us = pool ? 2 : 1;
@@ -481,9 +482,12 @@ static bool halo_region(GemmParams &p, int bn, bool pool) {
   const int64_t nu = cells_touched(bn, ucols);
   const int64_t ni = std::min(nu, cells_touched(bn, ucols * units));
   // the rows of nu units cut into 1 .. ni images: linear in the number of images, so largest at an end
-  const int64_t rows = std::max((nu - 1) * ustep + uspan, (nu - ni) * ustep + ni * uspan);
+  rows = std::max((nu - 1) * ustep + uspan, (nu - ni) * ustep + ni * uspan);
   const int64_t ppp = (g.Cw + 1) / 2;
   if (p.Kw64 > 4096 || rows > 4096 || Wp > 4096 || ppp > 64 || full < 2 || full > (1 << 24)) return false;
+  // load_region's row pitch is a 32-bit number of bytes.  Wp does not bound it: with one output column the image may be
+  // any number of columns wider than what its taps read.
+  if ((int64_t)g.W * g.Cw * 8 > 0xffffffffLL) return false;
   // plane stride in 8-byte words: the word pairs of one pixel that neighbouring lanes write fall on distinct banks
   const int64_t plane8 = (rows * Wp + 31) / 32 * 32 + std::max<int64_t>(1, 16 / ppp);
   const int64_t bytes = (plane8 * 8 * (g.Cw + (p.Kw64 & 1)) + 15) / 16 * 16;
@@ -512,7 +516,8 @@ static bnn_status launch_fp4_shape(GemmParams &p, int bmode, int emode, hipStrea
     }
   }
   p.b_vec16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0;
-  const bool halo = region && halo_region(p, H::BN, p.g.pool != 0);
+  int64_t rows;
+  const bool halo = region && halo_region(p, H::BN, p.g.pool != 0, rows);
   if constexpr (MAPS) {
     if (emode == 0)
       return halo ? launch_fp4<WTM, WTN, WGM, WGN, GM_HALO, EM_MAPS, MINW>(p, s)

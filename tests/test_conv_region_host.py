@@ -4,9 +4,12 @@ The host sizes the region by a bound over all tiles (halo_region in gemm_fp4.hip
 rows and every column's offset from its first and last pixel.  The model states both and checks, for random
 geometries, that no tile needs more rows than the bound and that every tap a column reads lies inside the region on
 the row of its own image."""
+import ctypes
 import random
 
 import pytest
+
+from paper_1911_04477_amd import binding as B
 
 
 def cells_touched(length, cell):
@@ -72,3 +75,13 @@ def test_region_bound_covers_every_tile(seed):
         pool = OH % 2 == 0 and OW % 2 == 0 and rng.random() < 0.6
         check_geometry(rng.randint(1, 9), H, W, kH, kW, sH, sW, pH, pW, pool, rng.choice([64, 128, 256]))
         seen += 1
+
+
+def test_rows_beyond_the_pitch_are_gathered():
+    """Input rows of 4 GiB and more, of which one output column's taps read three pixels: the region would be small,
+    but the pitch that the copy into it steps by is a 32-bit number of bytes."""
+    out = (ctypes.c_int64 * 4)()
+    region = B.lib().bnn_testing_conv_region
+    for H, W, C, taken in ((3, 1 << 29, 1, 0), (3, 1 << 29, 5, 0), (2, (1 << 30) - 1, 4, 0), (3, (1 << 29) - 1, 1, 1),
+                           (2, (1 << 29) - 1, 8, 1)):
+        assert region(1, C, H, W, H, 3, 1, 1 << 30, 0, 0, 0, 256, out) == taken, (H, W, C)

@@ -890,6 +890,25 @@ def test_conv2d_packed_largest_images(N, C):
         torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("cfg", [None, 23, 25])
+def test_conv2d_packed_rows_of_4_gib(cfg):
+    """An input row of 2^29 one-word pixels (2^32 bytes) under one output column: rows 1 and 2 are 4 and 8 GiB
+    into the image.  Counts from the nine pixels that the taps read."""
+    print(f"conv2d_packed rows of 4 GiB cfg={cfg}", flush=True)
+    W, D = 1 << 29, 40000  # enough outputs for the staged tiles
+    rng = np.random.default_rng(29)
+    px = rng.integers(0, 2, (3, 3))
+    w = rng.standard_normal((D, 1, 3, 3)).astype(np.float32)
+    xp = torch.zeros((1, 3, W, 1), dtype=torch.int64, device=DEV)
+    xp[0, :, :3, 0] = torch.from_numpy(px).to(DEV)
+    got = host(B.bnn_conv2d_packed(xp, B.bnn_pack_conv_weight(dev(w)), 1, D, 3, 3, (1, 1 << 30), (0, 0), out="i32",
+                                   cfg=cfg))
+    del xp
+    torch.cuda.empty_cache()
+    ref = (np.where(w[:, 0] >= 0, 1, -1) * (2 * px - 1)).sum(axis=(1, 2))
+    assert np.array_equal(got[0, :, 0, 0], ref)
+
+
 def _pm1_rows(packed, K):
     """Packed rows (uint64 words, element k in bit k % 64 of word k / 64, bit 1 = +1) as +-1 floats."""
     bits = np.unpackbits(np.ascontiguousarray(packed).view(np.uint8), axis=-1, bitorder="little")[:, :K]
