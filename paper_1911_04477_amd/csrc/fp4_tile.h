@@ -54,13 +54,19 @@ __device__ __forceinline__ void load_pieces_any(u32x4 *r, bool wide, At at) {
 
 // 32 bits -> 32 E2M1 codes (bit 0: +1.0 = 0x2, bit 1: -1.0 = 0xA), value 4j + 3 - s in nibble j of dword s.
 // The bit-field insert is written out: the optimizer splits it into an and and an or with literals.
+// A matrix instruction may read a register only two wait states after a vector instruction has written it, and the
+// compiler does not see that the written-out insert is one.  NOW: the codes may go into a matrix instruction at once,
+// the last insert (the others stand before it) is followed by the wait.  Otherwise the caller has at least two
+// instructions in between.
+template <bool NOW>
 __device__ __forceinline__ v8i expand_e2m1(uint32_t x) {
   const uint32_t sign = 0x88888888u, one = 0x22222222u;
   v8i r = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     uint32_t d;
-    asm volatile("v_bfi_b32 %0, %1, %2, %3" : "=v"(d) : "s"(sign), "v"(x << s), "v"(one));
+    if (NOW && s == 3) asm volatile("v_bfi_b32 %0, %1, %2, %3\n\ts_nop 1" : "=v"(d) : "s"(sign), "v"(x << s), "v"(one));
+    else asm volatile("v_bfi_b32 %0, %1, %2, %3" : "=v"(d) : "s"(sign), "v"(x << s), "v"(one));
     r[s] = (int)d;
   }
   return r;
@@ -88,7 +94,9 @@ struct Fp4Acc {
 // bits (xa, xb) into (na, nb) and whatever side(k) issues (staging, reading ahead), k = 0 .. WTM * WTN - 1.
 // Vector instructions issue in the shadow of a matrix instruction (32 clocks), not beside a run of them, so the
 // order is pinned: after each matrix instruction its share of everything else.  (Left to the compiler, the
-// expansions of a step form one block and the matrix instructions another, which do not overlap.)
+// expansions of a step form one block and the matrix instructions another, which do not overlap.)  The order also
+// keeps the operands' wait states: with several column blocks the first matrix instruction of the next step does not
+// read the fragment that was expanded last.
 template <int WTM, int WTN, class Side>
 __device__ __forceinline__ void multiply_and_expand(Fp4Acc<WTM, WTN> &acc, const v8i (&a)[WTM], const v8i (&b)[WTN],
                                                     const uint32_t (&xa)[WTM], const uint32_t (&xb)[WTN], v8i (&na)[WTM],
@@ -103,8 +111,8 @@ __device__ __forceinline__ void multiply_and_expand(Fp4Acc<WTM, WTN> &acc, const
     // fragments k * F / n .. (k + 1) * F / n - 1 of the F = WTM + WTN
 #pragma unroll
     for (int f = k * (WTM + WTN) / (WTM * WTN); f < (k + 1) * (WTM + WTN) / (WTM * WTN); ++f) {
-      if (f < WTM) na[f] = expand_e2m1(xa[f]);
-      else nb[f - WTM] = expand_e2m1(xb[f - WTM]);
+      if (f < WTM) na[f] = expand_e2m1<false>(xa[f]);
+      else nb[f - WTM] = expand_e2m1<WTN == 1>(xb[f - WTM]);
     }
     __builtin_amdgcn_sched_barrier(0);
   }

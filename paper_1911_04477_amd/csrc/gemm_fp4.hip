@@ -383,12 +383,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
     }
 #pragma unroll
     for (int i = 0; i < WTM; ++i) {
-      ea[i] = expand_e2m1(a[i].x);
+      ea[i] = expand_e2m1<true>(a[i].x);
       ya[i] = a[i].y;
     }
 #pragma unroll
     for (int j = 0; j < WTN; ++j) {
-      eb[j] = expand_e2m1(b[j].x);
+      eb[j] = expand_e2m1<true>(b[j].x);
       yb[j] = b[j].y;
     }
   }

@@ -18,7 +18,7 @@ namespace bnn {
 enum : int { SG_EXPL16 = 0, SG_EXPL8 = 1, SG_CONV = 2 };
 
 template <int WT, int KS, int GM, int EMODE>
-__global__ __launch_bounds__(64 * KS) void xnor_gemm_fp4_split_kernel(GemmParams p) {
+__global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmParams p) {
   constexpr int B32 = 32 * WT;  // rows and columns of the tile
   constexpr bool CONV = GM == SG_CONV, SIGN = EMODE != 0;
   __shared__ __attribute__((aligned(16))) int4 sPart[KS * WT * WT * 4 * 64];
@@ -121,20 +121,38 @@ __global__ __launch_bounds__(64 * KS) void xnor_gemm_fp4_split_kernel(GemmParams
 
   Fp4Acc<WT, WT> acc;
   acc.init(0.0f);
+  // the operands of a dword are expanded beside the products of the dword before it
   auto multiply_chunk = [&](const u32x4 (&a)[WT], const u32x4 (&b)[WT]) {
+    v8i ea[WT], eb[WT];
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      v8i ea[WT], eb[WT];
+    for (int i = 0; i < WT; ++i) {
+      ea[i] = expand_e2m1<true>(a[i][0]);
+      eb[i] = expand_e2m1<true>(b[i][0]);
+    }
+#pragma unroll
+    for (int d = 1; d < 4; ++d) {
+      uint32_t xa[WT], xb[WT];
+      v8i na[WT], nb[WT];
 #pragma unroll
       for (int i = 0; i < WT; ++i) {
-        ea[i] = expand_e2m1(a[i][d]);
-        eb[i] = expand_e2m1(b[i][d]);
+        xa[i] = a[i][d];
+        xb[i] = b[i][d];
       }
+      multiply_and_expand<WT, WT>(acc, ea, eb, xa, xb, na, nb, [](int) {});
 #pragma unroll
-      for (int i = 0; i < WT; ++i)
-#pragma unroll
-        for (int j = 0; j < WT; ++j) acc.v[i][j] = mfma_e2m1(ea[i], eb[j], acc.v[i][j]);
+      for (int i = 0; i < WT; ++i) {
+        ea[i] = na[i];
+        eb[i] = nb[i];
+      }
     }
+    // by columns: two matrix instructions stand between the last fragment's expansion and the one that reads it
+#pragma unroll
+    for (int j = 0; j < WT; ++j)
+#pragma unroll
+      for (int i = 0; i < WT; ++i) {
+        acc.v[i][j] = mfma_e2m1(ea[i], eb[j], acc.v[i][j]);
+        asm volatile("" : "+v"(acc.v[i][j]));
+      }
   };
 
   const int nc = (p.Kw64 + 3) >> 2;
