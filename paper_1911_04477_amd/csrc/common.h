@@ -164,6 +164,50 @@ bnn_status launch_gemm_fp4_split(GemmParams &p, int bmode, int emode, hipStream_
 // The binarization predicate: +0.0 and -0.0 -> 1, negative and NaN -> 0.
 __device__ __forceinline__ bool sign_bit(float v) { return v >= 0.0f; }
 
+// Four signs, y[0] first, shifted into R registers in turn: bits[k % R] = 2 * bits[k % R] + (y[k] >= 0), a compare and an
+// add-with-carry each.  A vector instruction may read a carry only two wait states after the vector instruction that
+// wrote it, and inside one asm statement nothing but its own instructions stands between them: the four compares come
+// first, into a carry register each, so that every one has three instructions to its reader.  (256 x 128 x 16 x 16 to 256
+// channels: 12.4 us; compare, s_nop 1, add-with-carry sign by sign: 12.8.)
+template <int R>
+__device__ __forceinline__ void shift_in_signs(uint32_t (&bits)[R], const float (&y)[4]) {
+  static_assert(R == 1 || R == 2 || R == 4, "four signs");
+  uint64_t c0, c1, c2;
+#define BNN_COMPARE4(C0, C1, C2, Y0, Y1, Y2, Y3)                                                              \
+  "v_cmp_le_f32 " C0 ", 0, " Y0 "\n\tv_cmp_le_f32 " C1 ", 0, " Y1 "\n\tv_cmp_le_f32 " C2 ", 0, " Y2           \
+  "\n\tv_cmp_le_f32 vcc, 0, " Y3 "\n\t"
+#define BNN_ADDC(B, C) "v_addc_co_u32 " B ", " C ", " B ", " B ", " C "\n\t"
+  if constexpr (R == 4) {
+    asm(BNN_COMPARE4("%4", "%5", "%6", "%7", "%8", "%9", "%10") BNN_ADDC("%0", "%4") BNN_ADDC("%1", "%5")
+            BNN_ADDC("%2", "%6") BNN_ADDC("%3", "vcc")
+        : "+v"(bits[0]), "+v"(bits[1]), "+v"(bits[2]), "+v"(bits[3]), "=&s"(c0), "=&s"(c1), "=&s"(c2)
+        : "v"(y[0]), "v"(y[1]), "v"(y[2]), "v"(y[3])
+        : "vcc");
+  } else if constexpr (R == 2) {
+    asm(BNN_COMPARE4("%2", "%3", "%4", "%5", "%6", "%7", "%8") BNN_ADDC("%0", "%2") BNN_ADDC("%1", "%3")
+            BNN_ADDC("%0", "%4") BNN_ADDC("%1", "vcc")
+        : "+v"(bits[0]), "+v"(bits[1]), "=&s"(c0), "=&s"(c1), "=&s"(c2)
+        : "v"(y[0]), "v"(y[1]), "v"(y[2]), "v"(y[3])
+        : "vcc");
+  } else {
+    asm(BNN_COMPARE4("%1", "%2", "%3", "%4", "%5", "%6", "%7") BNN_ADDC("%0", "%1") BNN_ADDC("%0", "%2")
+            BNN_ADDC("%0", "%3") BNN_ADDC("%0", "vcc")
+        : "+v"(bits[0]), "=&s"(c0), "=&s"(c1), "=&s"(c2)
+        : "v"(y[0]), "v"(y[1]), "v"(y[2]), "v"(y[3])
+        : "vcc");
+  }
+#undef BNN_COMPARE4
+#undef BNN_ADDC
+}
+
+// Lane exchanges read a register two wait states after it was written at the earliest; the compiler does not see the
+// writes above.
+template <int R>
+__device__ __forceinline__ void settle_signs(uint32_t (&bits)[R]) {
+#pragma unroll
+  for (int j = 0; j < R; ++j) asm("s_nop 1" : "+v"(bits[j]));
+}
+
 // Conv helpers (im2col.hip).  check_conv_geometry validates shapes and 32-bit limits;
 // run_im2col launches encode (+ gather), or both in one kernel, with already validated arguments.
 bnn_status check_conv_geometry(int N, int C, int H, int W, int kH, int kW, int sH, int sW, int pH, int pW);

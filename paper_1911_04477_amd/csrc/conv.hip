@@ -234,23 +234,23 @@ __device__ __forceinline__ c1m_v32f c1m_chain(const float *wg, const float (&xv)
 // its block-0 bits and receives the partner's, l >= 32 likewise with block 1.
 __device__ __forceinline__ uint32_t c1m_sign_bits(const c1m_v32f &acc, const float *sSc, const float *sBi, int g,
                                                   int half) {
-  // rows descend so that every sign is shifted in with one add-with-carry: m = 2 * m + (y >= 0)
-  uint32_t m0 = 0u, m1 = 0u;
+  // rows descend: every sign is shifted in with one add-with-carry, m = 2 * m + (y >= 0)
+  uint32_t m[2] = {0u, 0u};
 #pragma unroll
   for (int q = 3; q >= 0; --q) {
     const float4 sc = *reinterpret_cast<const float4 *>(sSc + 32 * g + 8 * q + 4 * half);
     const float4 bi = *reinterpret_cast<const float4 *>(sBi + 32 * g + 8 * q + 4 * half);
     const float scv[4] = {sc.x, sc.y, sc.z, sc.w}, biv[4] = {bi.x, bi.y, bi.z, bi.w};
 #pragma unroll
-    for (int e = 3; e >= 0; --e) {
+    for (int e = 3; e >= 0; e -= 2) {
       const int rr = 4 * q + e;
-      const float y0 = fmaf(scv[e], acc[rr], biv[e]), y1 = fmaf(scv[e], acc[16 + rr], biv[e]);
-      asm("v_cmp_le_f32 vcc, 0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(m0) : "v"(y0) : "vcc");
-      asm("v_cmp_le_f32 vcc, 0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(m1) : "v"(y1) : "vcc");
+      const float y[4] = {fmaf(scv[e], acc[rr], biv[e]), fmaf(scv[e], acc[16 + rr], biv[e]),
+                          fmaf(scv[e - 1], acc[rr - 1], biv[e - 1]), fmaf(scv[e - 1], acc[15 + rr], biv[e - 1])};
+      shift_in_signs<2>(m, y);
     }
   }
-  const uint32_t own = half ? m1 : m0;
-  const uint32_t got = (uint32_t)__shfl_xor((int)(half ? m0 : m1), 32);
+  const uint32_t own = half ? m[1] : m[0];
+  const uint32_t got = (uint32_t)__shfl_xor((int)(half ? m[0] : m[1]), 32);
   const uint32_t lo = half ? got : own, hi = half ? own : got;  // channels 8q+0..3 / 8q+4..7
   return c1m_spread_nibbles(lo) | (c1m_spread_nibbles(hi) << 4);
 }

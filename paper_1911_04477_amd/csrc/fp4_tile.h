@@ -225,22 +225,16 @@ __device__ __forceinline__ uint64_t sign_word(uint32_t h0, uint32_t h1) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-// bits = 2 * bits + (fma(scale, v, bias) >= 0): rows are taken in descending order, one add-with-carry each.
-__device__ __forceinline__ void shift_in_sign(uint32_t &bits, float scale, float v, float bias) {
-  const float y = fmaf(scale, v, bias);
-  asm("v_cmp_le_f32 vcc, 0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(y) : "vcc");
-}
-
 // Binarizing epilogue: affine map, sign; packed NHWC words.  Tile rows are output channels, 64 of them
 // (WTM = 2): one word per output pixel.
 template <int WTM, int WTN, bool DEALT>
 __device__ __forceinline__ void store_signs(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n0, int lane,
                                             const float *sSc, const float *sBi) {
-  static_assert(WTM == 2 && WTN % 2 == 0, "one 64-channel word per wave");
+  static_assert(WTM == 2 && (WTN == 2 || WTN == 4), "one 64-channel word per wave");
   const int half = lane >> 5, l32 = lane & 31;
   const int word = m0 >> 6;
   if (word >= p.cw_out) return;  // wave-uniform
-  uint32_t bits[WTN];
+  uint32_t bits[WTN];  // rows are taken in descending order
 #pragma unroll
   for (int j = 0; j < WTN; ++j) bits[j] = 0u;
 #pragma unroll
@@ -249,11 +243,16 @@ __device__ __forceinline__ void store_signs(const GemmParams &p, const Fp4Acc<WT
     for (int q = 3; q >= 0; --q) {
       const float4 sc = *reinterpret_cast<const float4 *>(sSc + 32 * i + 8 * q + 4 * half);
       const float4 bi = *reinterpret_cast<const float4 *>(sBi + 32 * i + 8 * q + 4 * half);
+      constexpr int ROWS = 4 / WTN;  // four signs at a time
 #pragma unroll
-      for (int e = 3; e >= 0; --e)
+      for (int e = 3; e >= 0; e -= ROWS) {
+        float y[4];
 #pragma unroll
-        for (int j = 0; j < WTN; ++j) shift_in_sign(bits[j], (&sc.x)[e], acc.v[i][j][4 * q + e], (&bi.x)[e]);
+        for (int k = 0; k < 4; ++k) y[k] = fmaf((&sc.x)[e - k / WTN], acc.v[i][k % WTN][4 * q + e - k / WTN], (&bi.x)[e - k / WTN]);
+        shift_in_signs<WTN>(bits, y);
+      }
     }
+  settle_signs(bits);
   // lanes l and l + 32 hold the two row halves of the same columns: the lower lanes assemble the first half of
   // the columns, the upper lanes the second
 #pragma unroll
@@ -274,13 +273,15 @@ __device__ __forceinline__ void store_signs_pooled(const GemmParams &p, const Fp
   const int half = lane >> 5, l32 = lane & 31;
   const int word = m0 >> 6;
   if (word >= p.cw_out) return;  // wave-uniform
-  uint32_t bits = 0u;
+  // rows are taken in descending order
+  uint32_t bits[1] = {0u};
 #pragma unroll
   for (int i = 1; i >= 0; --i)
 #pragma unroll
     for (int q = 3; q >= 0; --q) {
       const float4 sc = *reinterpret_cast<const float4 *>(sSc + 32 * i + 8 * q + 4 * half);
       const float4 bi = *reinterpret_cast<const float4 *>(sBi + 32 * i + 8 * q + 4 * half);
+      float y[4];
 #pragma unroll
       for (int e = 3; e >= 0; --e) {
         const int r = 4 * q + e;
@@ -293,10 +294,12 @@ __device__ __forceinline__ void store_signs_pooled(const GemmParams &p, const Fp
           const float o = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(m), 0xB1, 0xF, 0xF, true));
           asm("v_max_f32 %0, %0, %1" : "+v"(m) : "v"(o));
         }
-        shift_in_sign(bits, (&sc.x)[e], m, (&bi.x)[e]);
+        y[3 - e] = fmaf((&sc.x)[e], m, (&bi.x)[e]);
       }
+      shift_in_signs<1>(bits, y);
     }
-  const auto x = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
+  settle_signs(bits);
+  const auto x = __builtin_amdgcn_permlane32_swap(bits[0], bits[0], false, false);
   const int w = WTN == 4 ? (n0 >> 2) + l32 : (n0 >> 2) + (l32 >> 1);  // pooled pixel
   if (half == 0 && (WTN == 4 || (l32 & 1) == 0) && w < (p.N >> 2))
     p.outp[(int64_t)w * p.cw_out + word] = sign_word(x[0], x[1]);

@@ -738,24 +738,34 @@ __global__ __launch_bounds__(64 * WM * WN, MINW) void xnor_gemm_kernel(GemmParam
     }
     // Rows run from the last to the first so that each sign is shifted in with one add-with-carry
     // (byte = 2 * byte + bit).  K - 2*acc decreases in acc: the 2x2 max is K - 2*min(acc).
+    auto sign_arg = [&](int i, int a) {
+      const bool row_ok = m0 + i < M;  // rows past M give bit 0
+      return fmaf(row_ok ? scr[i] : 0.0f, (float)(Kformula - 2 * a), row_ok ? bir[i] : -1.0f);
+    };
+    static_assert(TM % 4 == 0, "four signs at a time");
+    if (pool) {
 #pragma unroll
-    for (int i = TM - 1; i >= 0; --i) {
-      const int m = m0 + i;
-      const bool row_ok = m < M;
-      const float sc = row_ok ? scr[i] : 0.0f;
-      const float bi = row_ok ? bir[i] : -1.0f;  // rows past M give bit 0
-      if (pool) {
-        int a = acc[i][0];
+      for (int i = TM - 1; i >= 0; i -= 4) {
+        float y[4];
 #pragma unroll
-        for (int j = 1; j < TN; ++j) a = min(a, acc[i][j]);
-        const float y = fmaf(sc, (float)(Kformula - 2 * a), bi);
-        asm("v_cmp_le_f32 vcc, 0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bytes[0]) : "v"(y) : "vcc");
-      } else {
+        for (int k = 0; k < 4; ++k) {
+          int a = acc[i - k][0];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const float y = fmaf(sc, (float)(Kformula - 2 * acc[i][j]), bi);
-          asm("v_cmp_le_f32 vcc, 0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bytes[j]) : "v"(y) : "vcc");
+          for (int j = 1; j < TN; ++j) a = min(a, acc[i - k][j]);
+          y[k] = sign_arg(i - k, a);
         }
+        uint32_t b[1] = {bytes[0]};
+        shift_in_signs<1>(b, y);
+        bytes[0] = b[0];
+      }
+    } else {
+      constexpr int ROWS = 4 / TN;
+#pragma unroll
+      for (int i = TM - 1; i >= 0; i -= ROWS) {
+        float y[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) y[k] = sign_arg(i - k / TN, acc[i - k / TN][k % TN]);
+        shift_in_signs<TN>(bytes, y);
       }
     }
     __syncthreads();  // every wave is done reading the B tiles: LDS is reused for the output bytes

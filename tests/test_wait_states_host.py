@@ -1,8 +1,11 @@
 """Distances between dependent vector instructions in the compiled kernels.
 
-gfx950 needs two wait states (other instructions, or s_nop) between a vector instruction that writes a register and
-a matrix instruction that reads it.  The compiler keeps them for its own instructions, not around written-out assembly.
-The kernels are compiled here as the library compiles them and every such pair is measured.  CPU only."""
+gfx950 needs two wait states (other instructions, or s_nop) between
+  * a vector instruction that writes a vector register and a matrix instruction that reads it,
+  * a vector instruction that writes a scalar register or vcc and a vector instruction that reads it,
+  * a vector instruction that writes a vector register and a lane-exchange (permlane*_swap, DPP) that reads it.
+The compiler keeps them for its own instructions, not around or inside written-out assembly.  The kernels are
+compiled here as the library compiles them and every such pair is measured.  CPU only."""
 import os
 import re
 import shutil
@@ -75,8 +78,9 @@ def violations(asm):
         if name.startswith("v_") and name != "v_nop":
             w, r = accesses(name, operands(rest))
             matrix = name.startswith("v_mfma")
+            exchange = name.startswith("v_permlane") or "dpp" in name
             for age, reg in pending:
-                if age < NEED and reg in r and matrix:
+                if age < NEED and reg in r and (reg[0] == "s" or matrix or exchange):
                     report(no, line.strip(), age)
             if not matrix:
                 new = [(0, reg) for reg in w]
@@ -109,7 +113,9 @@ def test_the_checker_itself():
     bad = violations("v_bfi_b32 v1, s0, v2, v3\nv_mov_b32 v9, v8\nv_mfma_scale_f32_32x32x64_f8f6f4 a[0:15], v[0:3], v[4:7], a[0:15]")
     assert [(n, a) for n, _, a in bad] == [(3, 1)]
     assert not violations("v_bfi_b32 v1, s0, v2, v3\ns_nop 1\nv_mfma_f32_32x32x1_2b_f32 v[64:95], v1, v4, v[64:95]")
-    assert [a for _, _, a in violations("v_mov_b32 v1, 0\ns_cbranch_scc1 L\ns_nop 7\nL:\nv_mfma_f32_32x32x1_2b_f32 v[64:95], v1, v4, v[64:95]")] == [1]
+    assert [a for _, _, a in violations("v_cmp_le_f32 vcc, 0, v1\nv_addc_co_u32 v0, vcc, v0, v0, vcc")] == [0]
+    assert not violations("v_cmp_le_f32 s[0:1], 0, v1\nv_cmp_le_f32 vcc, 0, v2\ns_nop 0\nv_addc_co_u32 v0, s[0:1], v0, v0, s[0:1]")
+    assert [a for _, _, a in violations("v_mov_b32 v1, 0\ns_cbranch_scc1 L\ns_nop 7\nL:\nv_permlane32_swap_b32 v0, v1")] == [1]
 
 
 @pytest.fixture(scope="module")
