@@ -169,8 +169,15 @@ static inline bool is_pointwise(int kH, int kW, int pH, int pW) { return kH == 1
 //     15.7 us against 19.6; 524 KB, 256 x 128 x 32 x 32: 34.8 against 34.1; 64 x 256 x 56 x 56: 65 against 48);
 //   * where over 48 KB of that are halo rows (32 KB: 4.8 against 5.8 us; 115 KB, 8 x 256 x 56 x 56: 13.7 against 10.3);
 //   * where units stay idle, unless the call is short anyway (up to 64 KB per workgroup; one 128 x 32 x 32 image:
-//     4.2 against 5.3).
-static int band_rows(int N, int C, int H, int W, int kH, int sH, int OH, int64_t Cw) {
+//     4.2 against 5.3);
+//   * where a workgroup emits much more than its share of the chip: the gather spreads the patches over every unit
+//     whatever the bands are.  A workgroup emits BAND_T pieces per 0.4 us; the form gives way where these rounds, and
+//     the reading where units are idle (16 KB per round), exceed the share by more than 7 + 2/5 of it (one row of 4096
+//     pixels, 101 taps: 404 rounds, 153 against 6.3 us; 32 rows of 226 pixels of 64 channels, 101 taps: 13 rounds,
+//     8.1 against 6.0; one 3 x 224 x 224 image, 7x7: 6 rounds, 7.0 against 9.0; 215 rows of 250 pixels, 251 taps: 62
+//     rounds, a share of 52, 29.7 against 33.2).  Of 500 random calls that the other lines pass, 449 are taken, 4 of
+//     them 6 to 18 % slower in this form, and 3 are left that it would have made faster.
+static int band_rows(int N, int C, int H, int W, int kH, int sH, int OH, int OW, int64_t Cw, int64_t per_row) {
   const int cu = device_cu_count();
   if (N > cu) return 0;
   const int R = (OH + cu / N - 1) / (cu / N);
@@ -179,7 +186,12 @@ static int band_rows(int N, int C, int H, int W, int kH, int sH, int OH, int64_t
   if (lds > 64 * 1024) return 0;
   const int64_t wgs = (int64_t)N * ((OH + R - 1) / R);
   if (rows * row_bytes > 384 * 1024 || (rows - (int64_t)R * sH) * row_bytes > 48 * 1024) return 0;
-  return wgs * 8 >= (int64_t)cu * 7 || rows * row_bytes <= 64 * 1024 ? R : 0;
+  const bool idle = wgs * 8 < (int64_t)cu * 7;
+  if (idle && rows * row_bytes > 64 * 1024) return 0;
+  const int64_t rounds = ((int64_t)R * OW * per_row + BAND_T - 1) / BAND_T;
+  const int64_t share = (int64_t)N * OH * OW * per_row / ((int64_t)cu * BAND_T);
+  const int64_t reading = idle ? rows * row_bytes / (16 * 1024) : 0;
+  return 5 * (rounds + reading) <= 5 * 7 + 7 * share ? R : 0;
 }
 
 // Shared by bnn_im2col_packed and bnn_conv2d; arguments already validated.
@@ -203,7 +215,7 @@ bnn_status run_im2col(const float *x, int N, int C, int H, int W, int kH, int kW
   g.divOH = FastDiv((uint32_t)OH);
   g.total = (uint32_t)total;
   if (!encode_nchw_supported(N, C, H, W, H, W)) return BNN_ERR_UNSUPPORTED;
-  if (const int R = band_rows(N, C, H, W, kH, sH, OH, Cw)) {
+  if (const int R = band_rows(N, C, H, W, kH, sH, OH, OW, Cw, per_row)) {
     BandParams b;
     b.g = g;
     b.R = R;

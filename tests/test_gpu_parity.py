@@ -33,6 +33,17 @@ def assert_f32_close(got, ref):
     assert np.allclose(got, ref, rtol=1e-6, atol=1e-30), np.abs(got - ref).max()
 
 
+def kernels_of(call):
+    """call()'s result and the names of the kernels it launched, in order."""
+    B.prof_enable(True)
+    try:
+        B.prof_reset()
+        out = call()
+        return out, [name for name, _ in B.prof_records()]
+    finally:
+        B.prof_enable(False)
+
+
 # ---------------------------------------------------------------- encode (a1)
 @pytest.mark.parametrize("rows,K", [(1, 1), (3, 31), (5, 64), (7, 65), (64, 256), (33, 200), (2, 4097), (130, 1152),
                                      (1000, 63), (17, 1024 + 13)])
@@ -1194,3 +1205,23 @@ def test_im2col_bands(case):
     x = inputs.inject_specials(rng.standard_normal((N, C, H, W)).astype(np.float32), 3, frac=0.01)
     cols = as_u64(B.bnn_im2col_packed(dev(x), kH, kW, (sH, sW), (pH, pW)))
     assert np.array_equal(cols, oracle.im2col_packed(x, kH, kW, (sH, sW), (pH, pW)))
+
+
+@pytest.mark.parametrize("case,bands", [
+    ((1, 1, 1, 4096, 1, 101, 1, 1, 0, 50), False),   # one workgroup would emit every patch
+    ((7, 4, 1, 2000, 1, 25, 1, 1, 0, 12), False),    # one per row
+    ((1, 16, 1, 1024, 1, 9, 1, 1, 0, 4), False),     # little to emit, the reading too
+    ((1, 1, 28, 28, 28, 28, 1, 1, 14, 14), False),   # a patch as large as the image
+    ((1, 4, 3, 300, 1, 9, 1, 1, 0, 4), True),
+    ((200, 1, 1, 500, 1, 51, 1, 1, 0, 25), True),    # as many pieces per workgroup, on every unit
+    ((2, 3, 64, 64, 7, 7, 1, 1, 3, 3), True),
+])
+def test_im2col_bands_emit_no_more_than_their_share(case, bands):
+    """Which of the two forms takes a call whose bands are few or long (256 compute units), and its words."""
+    print(f"im2col choice case={case}", flush=True)
+    N, C, H, W, kH, kW, sH, sW, pH, pW = case
+    x = np.random.default_rng(sum(case)).standard_normal((N, C, H, W)).astype(np.float32)
+    cols, names = kernels_of(lambda: B.bnn_im2col_packed(dev(x), kH, kW, (sH, sW), (pH, pW)))
+    assert np.array_equal(as_u64(cols), oracle.im2col_packed(x, kH, kW, (sH, sW), (pH, pW)))
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert names == (["im2col_band"] if bands else ["encode_nchw", "im2col_gather"])
