@@ -67,6 +67,13 @@ BNN_API int bnn_testing_conv_region(int N, int C, int H, int W, int kH, int kW, 
                                     int pool, int columns, int64_t *region);
 
 /*
+ * bnn_testing_nontemporal_maps -- host only, launches nothing: whether the matrix-core GEMM stores an int32 map
+ * [M, N] of row stride ldc, starting base_bytes past a multiple of 128 bytes, with non-temporal (1) or ordinary
+ * (0) stores; -1 for sizes below 1 or ldc < N.
+ */
+BNN_API int bnn_testing_nontemporal_maps(int M, int N, int K, int64_t ldc, int64_t base_bytes);
+
+/*
  * bnn_xnor_gemm_mfma_fp4_expanded on a chosen workgroup tile (rows x columns of C):
  *   -1 the choice of bnn.h's entry point;  0 128 x 128;  1 256 x 128;  2 128 x 256.
  * Other values: BNN_ERR_SHAPE.

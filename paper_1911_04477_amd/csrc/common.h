@@ -122,7 +122,7 @@ struct GemmParams {
   FastDiv divTilesM;   // matrix-core GEMM only
   int prio_from;       // workgroups with id >= prio_from lower their wave priority as they advance through K
   int n_cu;            // compute units of the device (host only: launch heuristics)
-  int nt_store;        // int32 / fp32 tile stores are line-aligned: use non-temporal stores
+  int nt_store;        // int32 / fp32 tile stores are non-temporal
   int colperm;         // 256-column tiles, int32 / fp32 output: LDS row 64 * j + l holds tile column 4 * l + j,
                        // so a lane's four columns are consecutive and go out as one 16-byte store per row
   ConvGeom g;          // implicit B only

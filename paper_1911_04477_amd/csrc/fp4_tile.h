@@ -131,8 +131,8 @@ __device__ __forceinline__ void settle(Fp4Acc<2, 2> &a) {
 
 // One map (int32, or fp32 through the affine map) of a wave's tile.  AFF: 0 int32, 1 fp32 with per-row
 // constants, 2 fp32 with per-column constants.  VEC: a lane's WTN columns go out as one store.  FULL: no row
-// of the tile is past M.
-template <int WTM, int WTN, int AFF, bool VEC, bool FULL>
+// of the tile is past M.  NT: non-temporal stores.
+template <int WTM, int WTN, int AFF, bool VEC, bool FULL, bool NT>
 __device__ __forceinline__ void store_map(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n, int half,
                                           const float *sSc, const float *sBi, const int64_t (&off)[WTN]) {
   typedef int vi __attribute__((ext_vector_type(WTN)));
@@ -170,8 +170,10 @@ __device__ __forceinline__ void store_map(const GemmParams &p, const Fp4Acc<WTM,
         }
         if (FULL || m0 + 32 * i + 8 * q + 4 * half + e < p.M) {
           const int64_t row = (int64_t)(32 * i + 8 * q + e) * ld;  // uniform
-          if constexpr (VEC) {
+          if constexpr (VEC && NT) {
             __builtin_nontemporal_store(o, reinterpret_cast<vi *>(ptr[0] + row));
+          } else if constexpr (VEC) {
+            *reinterpret_cast<vi *>(ptr[0] + row) = o;
           } else {
 #pragma unroll
             for (int j = 0; j < WTN; ++j)
@@ -182,16 +184,16 @@ __device__ __forceinline__ void store_map(const GemmParams &p, const Fp4Acc<WTM,
     }
 }
 
-template <int WTM, int WTN, int AFF>
+template <int WTM, int WTN, int AFF, bool NT>
 __device__ __forceinline__ void store_map_by(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n, int half,
                                              const float *sSc, const float *sBi, const int64_t (&off)[WTN]) {
-  if (p.colperm && m0 + 32 * WTM <= p.M) store_map<WTM, WTN, AFF, true, true>(p, acc, m0, n, half, sSc, sBi, off);
-  else if (p.colperm) store_map<WTM, WTN, AFF, true, false>(p, acc, m0, n, half, sSc, sBi, off);
-  else store_map<WTM, WTN, AFF, false, false>(p, acc, m0, n, half, sSc, sBi, off);
+  if (p.colperm && m0 + 32 * WTM <= p.M) store_map<WTM, WTN, AFF, true, true, NT>(p, acc, m0, n, half, sSc, sBi, off);
+  else if (p.colperm) store_map<WTM, WTN, AFF, true, false, NT>(p, acc, m0, n, half, sSc, sBi, off);
+  else store_map<WTM, WTN, AFF, false, false, NT>(p, acc, m0, n, half, sSc, sBi, off);
 }
 
 // int32 and / or fp32 output of a wave's tile: rows m0.., columns n0.. (row-major, or NCHW planes).
-template <int WTM, int WTN>
+template <int WTM, int WTN, bool NT>
 __device__ __forceinline__ void store_maps(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n0, int lane,
                                            const float *sSc, const float *sBi) {
   const int half = lane >> 5;
@@ -207,9 +209,9 @@ __device__ __forceinline__ void store_maps(const GemmParams &p, const Fp4Acc<WTM
       off[j] = (int64_t)img * p.img_stride + ((uint32_t)nc - img * p.OHW);
     }
   }
-  if (p.C) store_map_by<WTM, WTN, 0>(p, acc, m0, n, half, sSc, sBi, off);
-  if (p.Y && p.axis == BNN_CH_ROW) store_map_by<WTM, WTN, 1>(p, acc, m0, n, half, sSc, sBi, off);
-  else if (p.Y) store_map_by<WTM, WTN, 2>(p, acc, m0, n, half, sSc, sBi, off);
+  if (p.C) store_map_by<WTM, WTN, 0, NT>(p, acc, m0, n, half, sSc, sBi, off);
+  if (p.Y && p.axis == BNN_CH_ROW) store_map_by<WTM, WTN, 1, NT>(p, acc, m0, n, half, sSc, sBi, off);
+  else if (p.Y) store_map_by<WTM, WTN, 2, NT>(p, acc, m0, n, half, sSc, sBi, off);
 }
 
 // nibble q of a 16-bit mask -> bits 8q .. 8q + 3

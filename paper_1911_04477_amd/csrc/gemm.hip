@@ -859,15 +859,39 @@ int device_cu_count() {
   return cached[dev];
 }
 
+// Whether every row of the maps (every plane, for NCHW maps) starts at a multiple of `ints` 4-byte elements.
+static bool rows_start_every(const GemmParams &p, uint32_t ints) {
+  const bool planes = p.img_stride != 0;
+  auto ok = [&](const void *base, int64_t ld) {
+    return !base || (((uintptr_t)base & (4 * ints - 1)) == 0 && (planes ? p.OHW % ints == 0 : ld % ints == 0));
+  };
+  return ok(p.C, p.ldc) && ok(p.Y, p.ldy);
+}
+
+// Stores of the matrix-core tiles' maps, non-temporal or ordinary.  Measured over 900 random GEMMs and convolutions;
+// "words" are 64-bit words of the reduction per stored output, rows that a tile computes for nothing included.
+//   Rows of whole 128-byte lines: non-temporal (2 to 9 % faster on average).
+//   Rows that start inside a 64-byte half line: a piece of a line written past the L2 costs a line in memory, pieces that
+//     meet in the L2 do not.  Ordinary up to 36 words (64 x 128 x 58 x 58 maps from 1152 bits 41 -> 26 us; 1000 x 50004 x
+//     700 83 -> 39; 256 x 256 x 14 x 14 from 2304 bits 26 -> 24; on average 1.1 to 2.1 times faster by size); with more,
+//     the multiplications hide it and the caches are the operands' (up to 25 % the other way beyond 320 MB).
+//   Rows of whole half lines (28 x 28 maps): the same where the stores decide, below 12 words, and the call's bytes
+//     still fit the last-level cache of 256 MB (64 rows and more: 64 x 28 x 28 from 576 bits, 240 MB: 55.5 -> 43.1 us; 512 x 117200 x 700
+//     60.8 -> 42.0); non-temporal elsewhere (512 x 117200 x 2304 80 us, ordinary 95; 64 x 44 x 44 from 512 bits, 300 MB:
+//     20 %; small calls 1 to 5 %).
+static bool nontemporal_maps(const GemmParams &p, int bmode) {
+  if (rows_start_every(p, 32)) return true;
+  const int64_t words_x_m = (int64_t)p.Kw64 * (((int64_t)p.M + 63) / 64 * 64);
+  if (!rows_start_every(p, 16)) return words_x_m > 36 * (int64_t)p.M;
+  const int64_t out = (int64_t)p.M * p.N * 4 * ((p.C ? 1 : 0) + (p.Y ? 1 : 0));
+  const int64_t in = bmode == 0 ? (int64_t)p.N * p.Kw64 * 8 : (int64_t)p.g.Nimg * p.g.H * p.g.W * p.g.Cw * 8;
+  return words_x_m >= 12 * (int64_t)p.M || p.M < 64 || out + in <= 50000000 || out + in > 256000000;
+}
+
 bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const GemmTune &tune) {
   int cfg = tune.cfg;
   p.n_cu = device_cu_count();
-  {
-    const bool planes = p.img_stride != 0;
-    const bool c_ok = !p.C || (((uintptr_t)p.C & 127u) == 0 && (planes ? (p.OHW % 32u) == 0 : (p.ldc % 32) == 0));
-    const bool y_ok = !p.Y || (((uintptr_t)p.Y & 127u) == 0 && (planes ? (p.OHW % 32u) == 0 : (p.ldy % 32) == 0));
-    p.nt_store = (c_ok && y_ok) ? 1 : 0;
-  }
+  p.nt_store = rows_start_every(p, 32) ? 1 : 0;
   if (bmode == 1 && emode == 0 && p.g.pool == 0 && p.g.kH == 1 && p.g.kW == 1 && p.g.sH == 1 && p.g.sW == 1 &&
       p.g.pH == 0 && p.g.pW == 0) {
     // a stride-1 pointwise convolution over a packed image has nothing to gather: its patch
@@ -899,6 +923,7 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
                  (p.img_stride == 0 || ((p.OHW & 3u) == 0 && (p.img_stride & 3) == 0)))
                     ? 1
                     : 0;
+    p.nt_store = emode == 0 && nontemporal_maps(p, bmode) ? 1 : 0;
     if (cfg >= 25) return launch_gemm_fp4_split(p, bmode, emode, s, cfg - 25);
     if (cfg < 0 && (fp4_split_applicable(p) || !fp4_applicable(p))) return launch_gemm_fp4_split(p, bmode, emode, s, -1);
     return launch_gemm_fp4(p, bmode, emode, s, cfg >= 21 ? cfg - 21 : -1, tune.lean != 0);
@@ -987,4 +1012,16 @@ extern "C" bnn_status bnn_testing_xnor_gemm_epilogue(const uint64_t *A, int64_t 
   GemmTune tune;
   tune.cfg = cfg;
   return gemm_common(A, lda, B, ldb, M, N, K, C, ldc, Y, ldy, scale, bias, axis, stream, tune);
+}
+
+// Declared in bnn_testing.h.
+extern "C" int bnn_testing_nontemporal_maps(int M, int N, int K, int64_t ldc, int64_t base_bytes) {
+  if (M <= 0 || N <= 0 || K <= 0 || ldc < N) return -1;
+  GemmParams p = {};
+  p.M = M;
+  p.N = N;
+  p.Kw64 = (int)bnn_packed_words(K);
+  p.C = reinterpret_cast<int32_t *>((uintptr_t)4096 + (uintptr_t)base_bytes);
+  p.ldc = ldc;
+  return nontemporal_maps(p, 0) ? 1 : 0;
 }

@@ -42,8 +42,9 @@ typedef const uint32_t __attribute__((address_space(4))) *cu32_args;
 // every 16 bytes kH*kW times over, about 200 vector instructions per 512 bits of K beside the 336 of the
 // expansion.
 enum : int { GM_EXPL16 = 0, GM_EXPL8 = 1, GM_HALO = 2, GM_ANY = 3 };
-// What leaves: int32 / fp32 maps; packed signs; packed signs of the 2x2 maximum.
-enum : int { EM_MAPS = 0, EM_SIGN = 1, EM_POOL = 2 };
+// What leaves: int32 / fp32 maps in non-temporal or ordinary stores (two kernels: a choice inside one costs partial row
+// tiles 10 %); packed signs; packed signs of the 2x2 maximum.
+enum : int { EM_MAPS_NT = 0, EM_MAPS = 1, EM_SIGN = 2, EM_POOL = 3 };
 
 template <int WTM_, int WTN_, int WGM_, int WGN_, int GM_>
 struct Fp4Cfg {
@@ -291,7 +292,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
   // the tile's per-row scale / bias, requested now and written to LDS below; rows past M get the constants whose
   // sign bit is 0
   static_assert(BM <= T, "one row per thread");
-  const bool affine = EMODE != EM_MAPS || (p.Y && p.axis == BNN_CH_ROW);  // uniform
+  constexpr bool MAPS = EMODE == EM_MAPS_NT || EMODE == EM_MAPS;
+  const bool affine = !MAPS || (p.Y && p.axis == BNN_CH_ROW);  // uniform
   float fsc = 0.0f, fbi = -1.0f;
   if (affine && tid < BM && m0 + tid < p.M) {
     fsc = p.scale[m0 + tid];
@@ -439,7 +441,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
   settle(acc);
   const int mw = m0 + 32 * WTM * wm, nw = n0 + 32 * WTN * wn;
   const float *sc = sSc + 32 * WTM * wm, *bi = sBi + 32 * WTM * wm;
-  if constexpr (EMODE == EM_MAPS) store_maps<WTM, WTN>(p, acc, mw, nw, lane, sc, bi);
+  if constexpr (MAPS) store_maps<WTM, WTN, EMODE == EM_MAPS_NT>(p, acc, mw, nw, lane, sc, bi);
   else if constexpr (EMODE == EM_SIGN) store_signs<WTM, WTN, DEALT>(p, acc, mw, nw, lane, sc, bi);
   else store_signs_pooled<WTM, WTN>(p, acc, mw, nw, lane, sc, bi);
 }
@@ -459,6 +461,12 @@ static bnn_status launch_fp4(GemmParams &p, hipStream_t s) {
   hipLaunchKernelGGL((xnor_gemm_fp4_kernel<WTM, WTN, WGM, WGN, GM, EMODE, MINW>), dim3((unsigned)blocks), dim3(Cfg::T),
                      lds, s, p);
   return launch_status();
+}
+
+template <int WTM, int WTN, int WGM, int WGN, int GM, int MINW>
+static bnn_status launch_fp4_maps(GemmParams &p, hipStream_t s) {
+  return p.nt_store ? launch_fp4<WTM, WTN, WGM, WGN, GM, EM_MAPS_NT, MINW>(p, s)
+                    : launch_fp4<WTM, WTN, WGM, WGN, GM, EM_MAPS, MINW>(p, s);
 }
 
 // Upper bound of the number of aligned-grid cells of length `cell` that a run of `len` columns starting at a
@@ -511,8 +519,8 @@ static bnn_status launch_fp4_shape(GemmParams &p, int bmode, int emode, hipStrea
   if constexpr (MAPS) {
     if (bmode == 0) {
       const bool v16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0 && p.ldb % 2 == 0;
-      return v16 ? launch_fp4<WTM, WTN, WGM, WGN, GM_EXPL16, EM_MAPS, MINW>(p, s)
-                 : launch_fp4<WTM, WTN, WGM, WGN, GM_EXPL8, EM_MAPS, MINW>(p, s);
+      return v16 ? launch_fp4_maps<WTM, WTN, WGM, WGN, GM_EXPL16, MINW>(p, s)
+                 : launch_fp4_maps<WTM, WTN, WGM, WGN, GM_EXPL8, MINW>(p, s);
     }
   }
   p.b_vec16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0;
@@ -520,8 +528,8 @@ static bnn_status launch_fp4_shape(GemmParams &p, int bmode, int emode, hipStrea
   const bool halo = region && halo_region(p, H::BN, p.g.pool != 0, rows);
   if constexpr (MAPS) {
     if (emode == 0)
-      return halo ? launch_fp4<WTM, WTN, WGM, WGN, GM_HALO, EM_MAPS, MINW>(p, s)
-                  : launch_fp4<WTM, WTN, WGM, WGN, GM_ANY, EM_MAPS, MINW>(p, s);
+      return halo ? launch_fp4_maps<WTM, WTN, WGM, WGN, GM_HALO, MINW>(p, s)
+                  : launch_fp4_maps<WTM, WTN, WGM, WGN, GM_ANY, MINW>(p, s);
   }
   if (p.g.pool)
     return halo ? launch_fp4<WTM, WTN, WGM, WGN, GM_HALO, EM_POOL, MINW>(p, s)

@@ -315,3 +315,27 @@ def test_im2col_size_limits(L):
     for geo in ((1, 64, 300000, 64, 2, 2, 1000, 1, 0, 0),  # image above 2^31 bytes, 300 of its rows read
                 (1, 8129, 4, 4, 3, 3, 1, 1, 1, 1)):        # 64 packed pixels above the LDS
         assert im(A16, *geo, A16, A16, big, None) == UNSUPPORTED
+
+
+@pytest.mark.parametrize("M,N,K,ldc,base,nt", [
+    (512, 4096, 300, 4096, 0, 1),        # whole lines
+    (512, 4096, 300, 4096, 64, 1),       # whole half lines from the base on, a small call
+    (512, 4096, 300, 4096, 16, 0),       # a base inside a half line
+    (1000, 50004, 700, 50004, 0, 0),     # rows start inside half lines
+    (1000, 50004, 2304, 50004, 0, 1),    # ... 36 words, 1024 rows computed for 1000
+    (256, 50180, 2304, 50180, 0, 0),     # ... 36 words per output: the last
+    (256, 50180, 2368, 50180, 0, 1),
+    (512, 100016, 704, 100016, 0, 0),    # whole half lines, 205 MB stored
+    (512, 100016, 768, 100016, 0, 1),    # ... 12 words per output
+    (512, 23024, 704, 23024, 0, 1),      # ... below 50 MB
+    (512, 140016, 704, 140016, 0, 1),    # ... above the last-level cache
+    (32, 1000016, 320, 1000016, 0, 1),   # ... half a tile's rows
+])
+def test_map_stores(L, M, N, K, ldc, base, nt):
+    """Non-temporal stores only where a row's pieces are whole lines, or where the rule says that it does not matter."""
+    assert L.bnn_testing_nontemporal_maps(M, N, K, ldc, base) == nt
+
+
+def test_map_stores_refuses(L):
+    for args in ((0, 8, 8, 8, 0), (8, 0, 8, 8, 0), (8, 8, 0, 8, 0), (8, 8, 8, 7, 0)):
+        assert L.bnn_testing_nontemporal_maps(*args) == -1

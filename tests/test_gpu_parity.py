@@ -1114,6 +1114,31 @@ def test_gemm_matrix_core_tiles(M, N, K, cfg):
         assert np.array_equal(host(Y), oracle.scale_bias(ref, sc, bi, "row" if axis == B.CH_ROW else "col"))
 
 
+@pytest.mark.parametrize("M,N,K,ldc", [
+    (130, 100004, 300, 100004),   # ordinary stores
+    (130, 20004, 2500, 20012),    # rows inside half lines, non-temporal
+    (130, 120016, 300, 120016),   # whole half lines, ordinary
+    (130, 40016, 300, 40016),     # whole half lines, non-temporal
+    (130, 40032, 300, 40064),     # whole lines
+])
+def test_map_store_forms(M, N, K, ldc):
+    """Both forms of the matrix-core tiles' stores at full, partial and padded tiles against the vector-ALU tiles."""
+    print(f"map stores M={M} N={N} K={K} ldc={ldc}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    Ap = torch.randint(-2**62, 2**62, (M, B.packed_words(K)), dtype=torch.int64, device=DEV, generator=g)
+    Bp = torch.randint(-2**62, 2**62, (N, B.packed_words(K)), dtype=torch.int64, device=DEV, generator=g)
+    out = torch.full((2, M, ldc), -7, dtype=torch.int32, device=DEV)
+    for o, cfg in ((out[0], None), (out[1], 3)):
+        _, names = kernels_of(lambda: B.bnn_xnor_gemm(Ap, Bp, K, o[:, :N], cfg=cfg))
+        assert names == ["xnor_gemm" if cfg else "xnor_gemm_fp4"]
+    assert torch.equal(out[0], out[1])
+    assert (out[0, :, N:] == -7).all()
+    sc, bi = torch.rand(M, device=DEV, generator=g) + 0.5, torch.randn(M, device=DEV, generator=g)
+    ys = [B.bnn_xnor_gemm_epilogue(Ap, Bp, K, sc, bi, B.CH_ROW, want_int=True, cfg=cfg) for cfg in (None, 3)]
+    assert torch.equal(ys[0][0], ys[1][0]) and torch.equal(ys[0][1], ys[1][1])
+    assert torch.equal(ys[0][0], out[0, :, :N])
+
+
 MATRIX_CONV_CASES = [  # N, C, H, W, D, kH, kW, sH, sW, pH, pW
     (3, 64, 9, 7, 70, 3, 3, 1, 1, 1, 1),      # one word per pixel: the row ends in the middle of a piece
     (2, 200, 12, 12, 130, 3, 3, 1, 1, 1, 1),  # pad bits inside a tap's last word
