@@ -345,19 +345,28 @@ static bnn_status launch_split(GemmParams &p, int bmode, int emode, hipStream_t 
   return launch_status();
 }
 
-// Tiles of 32 x 32 outputs per compute unit, cu2 = 2, 4, 8 of them:
-//   up to 2: 32 x 32 tiles, K split 8 ways (512 x 64 x 4608 4.7 us, KS = 4: 5.2, 16: 4.8, 64 x 64 tiles 7.4 to 8.2, the
-//            128 x 128 kernel 12; 1 x 1024 x 8192 3.6 us; 128 x 4096 x 1152 4.3 against 4.4, 5.1 and 6.3);
-//   up to 4: short rows 32 x 32 and 4 ways (128 x 8192 x 1152: 5.2 us against 5.3 on 64 x 64, 6.0 at 8 ways, 6.4 on 128 x 128),
-//            from 9 chunks on 64 x 64 and 8 ways (512 x 2048 x 4608: 7.8 against 9.1 and 12.2);
-//   up to 8: from 9 chunks on 64 x 64 and 4 ways (512 x 4096 x 4608: 11.5 against 12.6 on 128 x 128).
+// By tiles of 32 x 32 outputs per compute unit:
+//   up to 2: 32 x 32 tiles, K split 8 ways (512 x 64 x 4608 3.7 us, 64 x 64 tiles 7.4 to 8.2, the 128 x 128 kernel 12;
+//            1 x 1024 x 8192 3.8 us; 128 x 4096 x 1152 3.8 against 4.4, 5.1 and 6.3);
+//   short rows up to 5.5: 32 x 32 tiles and 4 ways (128 x 8192 x 1152: 4.3 us, 64 x 64 5.3, 8 ways 6.0, 128 x 128 6.4; the
+//            staged tiles leave most units idle: 256 x 4384 x 576 4.6 against 5.2, with odd columns 4.6 against 6.1, 64
+//            channels of 56 x 56 from 128 6.4 against 7.4; from 6 the other way: 512 channels of 28 x 28 7.5 against 7.0);
+//   one row or one column of tiles, up to 8: the same whatever the depth, a larger tile has nothing to use twice and
+//            computes rows for nothing (4 x 40000 x 1024: 4.1 us, 64 x 64 split 6.7, 64 x 256 staged 5.4; 4 x 40000 x
+//            4096 6.6, 10.2, 10.4; 32 x 65536 x 4096 12.3, 16.0, 12.5; 40000 x 10 x 2048 5.0, 9.4, 15.7), above 6 from
+//            16 words (4 x 65536 x 1024 5.2 against 5.6, x 300 4.7 against 4.5);
+//   from 9 chunks up to 4: 64 x 64 and 8 ways (512 x 2048 x 4608: 7.7 against 9.1 and 12.2);
+//   from 9 chunks up to 8: 64 x 64 and 4 ways (512 x 4096 x 4608: 10.8 against 12.6 on 128 x 128).
 // Beyond, staged tiles reuse their operands better.  -1: does not apply.
 static int split_shape(const GemmParams &p) {
   const int64_t t = (((int64_t)p.M + 31) / 32) * (((int64_t)p.N + 31) / 32), cu = p.n_cu;
   const bool deep = p.Kw64 > 32;  // at least 9 chunks
+  const bool single = p.M <= 32 || p.N <= 32;
   if (t <= 2 * cu) return 1;
-  if (t <= 4 * cu) return deep ? 3 : 0;
-  if (t <= 8 * cu && deep) return 2;
+  if (!deep && 2 * t <= 11 * cu) return 0;
+  if (single && (t <= 6 * cu || (t <= 8 * cu && p.Kw64 >= 16))) return 0;
+  if (deep && t <= 4 * cu) return 3;
+  if (deep && t <= 8 * cu) return 2;
   // rows beyond the exact range of the other kernel's accumulators
   return p.Kw64 >= (1 << 18) - 2 ? 2 : -1;
 }

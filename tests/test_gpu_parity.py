@@ -1139,6 +1139,30 @@ def test_map_store_forms(M, N, K, ldc):
     assert torch.equal(ys[0][0], out[0, :, :N])
 
 
+@pytest.mark.parametrize("M,N,K,split", [
+    (4, 40000, 1024, True),     # one row of tiles: nothing that a larger tile could use twice
+    (32, 65536, 4096, True),
+    (40000, 10, 2048, True),    # one column of tiles
+    (4, 66000, 1024, False),    # more than eight 32 x 32 tiles per compute unit
+    (4, 50000, 300, False),     # short rows, more than six
+    (256, 4384, 576, True),     # few staged tiles, short rows
+    (250, 5629, 1100, True),    # 5.5 tiles per compute unit
+    (250, 5633, 1100, False),
+    (250, 4385, 2100, True),    # from nine chunks on: up to eight
+])
+def test_gemm_few_rows_or_columns_split_the_reduction(M, N, K, split):
+    """Which kernel takes a call at the edges of the rule (256 compute units), and its counts against the
+    vector-ALU tiles."""
+    print(f"gemm split rule M={M} N={N} K={K}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    Ap = torch.randint(-2**62, 2**62, (M, B.packed_words(K)), dtype=torch.int64, device=DEV, generator=g)
+    Bp = torch.randint(-2**62, 2**62, (N, B.packed_words(K)), dtype=torch.int64, device=DEV, generator=g)
+    got, names = kernels_of(lambda: B.bnn_xnor_gemm(Ap, Bp, K))
+    assert torch.equal(got, B.bnn_xnor_gemm(Ap, Bp, K, cfg=3))
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert names == ["xnor_gemm_fp4_split" if split else "xnor_gemm_fp4"]
+
+
 MATRIX_CONV_CASES = [  # N, C, H, W, D, kH, kW, sH, sW, pH, pW
     (3, 64, 9, 7, 70, 3, 3, 1, 1, 1, 1),      # one word per pixel: the row ends in the middle of a piece
     (2, 200, 12, 12, 130, 3, 3, 1, 1, 1, 1),  # pad bits inside a tap's last word
