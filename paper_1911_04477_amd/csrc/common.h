@@ -123,8 +123,9 @@ struct GemmParams {
   int prio_from;       // workgroups with id >= prio_from lower their wave priority as they advance through K
   int n_cu;            // compute units of the device (host only: launch heuristics)
   int nt_store;        // int32 / fp32 tile stores are non-temporal
-  int colperm;         // 256-column tiles, int32 / fp32 output: LDS row 64 * j + l holds tile column 4 * l + j,
-                       // so a lane's four columns are consecutive and go out as one 16-byte store per row
+  int colperm;         // int32 / fp32 output whose columns and strides are multiples of 4: a lane's columns are
+                       // consecutive and go out as one store per row (vector ALU: in 256-column tiles, LDS row
+                       // 64 * j + l holds tile column 4 * l + j)
   ConvGeom g;          // implicit B only
   HaloGeom halo;       // matrix-core convolution only
   uint64_t *outp;      // packed-sign output [pixels, cw_out] (packed epilogue only)

@@ -36,7 +36,7 @@ __device__ __forceinline__ void column_pixel(const ConvGeom &g, uint32_t n, bool
 // Pieces of rows that are not whole 16-byte pieces (an odd number of words, or rows that start on 8-byte
 // boundaries): still one 16-byte load each, global loads need 4-byte alignment only.  A row's odd last word is read
 // together with the one before it (the caller moves it), so no load goes past the row's end.  wide: the row has two
-// words.  1000 x 3001 x 2321: 11.6 us, 14.2 with two 8-byte loads per piece.
+// words.  1000 x 3001 x 2321: 14.2 -> 11.6 us against two 8-byte loads per piece.
 template <int P, class At>
 __device__ __forceinline__ void load_pieces_any(u32x4 *r, bool wide, At at) {
   typedef u32x4 u32x4_any __attribute__((aligned(4)));
@@ -129,26 +129,32 @@ __device__ __forceinline__ void settle(Fp4Acc<2, 2> &a) {
   asm volatile("s_nop 15\n\ts_nop 15" : "+v"(a.v[0][0]), "+v"(a.v[0][1]), "+v"(a.v[1][0]), "+v"(a.v[1][1]));
 }
 
+// How a lane's WTN columns of a map leave: MS_NT / MS_VEC one non-temporal / ordinary store of consecutive columns
+// per row; MS_ONE one 4-byte store per column and row, neighbouring lanes on neighbouring columns (columns that are not
+// a multiple of 4; against a lane's two columns side by side: 1000 x 3001 x 2321 11.5 -> 10.4 us, 256 x 200001 x 200
+// 42.3 -> 34.5, 128 x 31 x 33 maps from 1152 bits 21.8 -> 17.9).
+enum : int { MS_NT = 0, MS_VEC = 1, MS_ONE = 2 };
+
 // One map (int32, or fp32 through the affine map) of a wave's tile.  AFF: 0 int32, 1 fp32 with per-row
-// constants, 2 fp32 with per-column constants.  VEC: a lane's WTN columns go out as one store.  FULL: no row
-// of the tile is past M.  NT: non-temporal stores.
-template <int WTM, int WTN, int AFF, bool VEC, bool FULL, bool NT>
+// constants, 2 fp32 with per-column constants.  FULL: no row of the tile is past M.
+template <int WTM, int WTN, int AFF, int MS, bool FULL>
 __device__ __forceinline__ void store_map(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n, int half,
                                           const float *sSc, const float *sBi, const int64_t (&off)[WTN]) {
   typedef int vi __attribute__((ext_vector_type(WTN)));
+  constexpr int STEP = MS == MS_ONE ? 32 : 1;  // columns between a lane's
   int32_t *base = AFF == 0 ? p.C : reinterpret_cast<int32_t *>(p.Y);
   const int64_t ld = AFF == 0 ? p.ldc : p.ldy;
   float csc[WTN], cbi[WTN];
   if constexpr (AFF == 2) {
 #pragma unroll
     for (int j = 0; j < WTN; ++j) {
-      csc[j] = p.scale[min(n + j, p.N - 1)];
-      cbi[j] = p.bias[min(n + j, p.N - 1)];
+      csc[j] = p.scale[min(n + STEP * j, p.N - 1)];
+      cbi[j] = p.bias[min(n + STEP * j, p.N - 1)];
     }
   }
   int32_t *ptr[WTN];
 #pragma unroll
-  for (int j = 0; j < (VEC ? 1 : WTN); ++j) ptr[j] = base + off[j] + (int64_t)(m0 + 4 * half) * ld;
+  for (int j = 0; j < (MS == MS_ONE ? WTN : 1); ++j) ptr[j] = base + off[j] + (int64_t)(m0 + 4 * half) * ld;
 #pragma unroll
   for (int i = 0; i < WTM; ++i)
 #pragma unroll
@@ -170,48 +176,48 @@ __device__ __forceinline__ void store_map(const GemmParams &p, const Fp4Acc<WTM,
         }
         if (FULL || m0 + 32 * i + 8 * q + 4 * half + e < p.M) {
           const int64_t row = (int64_t)(32 * i + 8 * q + e) * ld;  // uniform
-          if constexpr (VEC && NT) {
+          if constexpr (MS == MS_NT) {
             __builtin_nontemporal_store(o, reinterpret_cast<vi *>(ptr[0] + row));
-          } else if constexpr (VEC) {
+          } else if constexpr (MS == MS_VEC) {
             *reinterpret_cast<vi *>(ptr[0] + row) = o;
           } else {
 #pragma unroll
             for (int j = 0; j < WTN; ++j)
-              if (n + j < p.N) ptr[j][row] = o[j];
+              if (n + STEP * j < p.N) ptr[j][row] = o[j];
           }
         }
       }
     }
 }
 
-template <int WTM, int WTN, int AFF, bool NT>
+template <int WTM, int WTN, int AFF, int MS>
 __device__ __forceinline__ void store_map_by(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n, int half,
                                              const float *sSc, const float *sBi, const int64_t (&off)[WTN]) {
-  if (p.colperm && m0 + 32 * WTM <= p.M) store_map<WTM, WTN, AFF, true, true, NT>(p, acc, m0, n, half, sSc, sBi, off);
-  else if (p.colperm) store_map<WTM, WTN, AFF, true, false, NT>(p, acc, m0, n, half, sSc, sBi, off);
-  else store_map<WTM, WTN, AFF, false, false, NT>(p, acc, m0, n, half, sSc, sBi, off);
+  if (m0 + 32 * WTM <= p.M) store_map<WTM, WTN, AFF, MS, true>(p, acc, m0, n, half, sSc, sBi, off);
+  else store_map<WTM, WTN, AFF, MS, false>(p, acc, m0, n, half, sSc, sBi, off);
 }
 
 // int32 and / or fp32 output of a wave's tile: rows m0.., columns n0.. (row-major, or NCHW planes).
-template <int WTM, int WTN, bool NT>
+template <int WTM, int WTN, int MS>
 __device__ __forceinline__ void store_maps(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n0, int lane,
                                            const float *sSc, const float *sBi) {
+  constexpr int STEP = MS == MS_ONE ? 32 : 1;
   const int half = lane >> 5;
-  const int n = n0 + WTN * (lane & 31);
+  const int n = n0 + (MS == MS_ONE ? 1 : WTN) * (lane & 31);
   if (m0 >= p.M || n >= p.N) return;
   int64_t off[WTN];
 #pragma unroll
   for (int j = 0; j < WTN; ++j) {
-    const int nc = min(n + j, p.N - 1);
+    const int nc = min(n + STEP * j, p.N - 1);
     off[j] = nc;
     if (p.img_stride != 0) {  // NCHW planes
       const uint32_t img = fdiv((uint32_t)nc, p.divOHW);
       off[j] = (int64_t)img * p.img_stride + ((uint32_t)nc - img * p.OHW);
     }
   }
-  if (p.C) store_map_by<WTM, WTN, 0, NT>(p, acc, m0, n, half, sSc, sBi, off);
-  if (p.Y && p.axis == BNN_CH_ROW) store_map_by<WTM, WTN, 1, NT>(p, acc, m0, n, half, sSc, sBi, off);
-  else if (p.Y) store_map_by<WTM, WTN, 2, NT>(p, acc, m0, n, half, sSc, sBi, off);
+  if (p.C) store_map_by<WTM, WTN, 0, MS>(p, acc, m0, n, half, sSc, sBi, off);
+  if (p.Y && p.axis == BNN_CH_ROW) store_map_by<WTM, WTN, 1, MS>(p, acc, m0, n, half, sSc, sBi, off);
+  else if (p.Y) store_map_by<WTM, WTN, 2, MS>(p, acc, m0, n, half, sSc, sBi, off);
 }
 
 // nibble q of a 16-bit mask -> bits 8q .. 8q + 3

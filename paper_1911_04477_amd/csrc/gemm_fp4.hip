@@ -24,6 +24,7 @@
 // 8*(r/4) + 4*(l/32) + r%4 of column l % 32.  Column block j, lane l of a wave is tile column WTN*(l%32)+j:
 // a lane's WTN columns are consecutive and leave as one 16- or 8-byte store per row, and with columns
 // ordered window-major (column = 4 * window + member) a lane of a 4-block wave holds whole pooling windows.
+// (Columns that leave one by one, and signs from an LDS region: tile column 32*j + l%32.)
 #include <algorithm>
 
 #include "common.h"
@@ -42,9 +43,9 @@ typedef const uint32_t __attribute__((address_space(4))) *cu32_args;
 // every 16 bytes kH*kW times over, about 200 vector instructions per 512 bits of K beside the 336 of the
 // expansion.
 enum : int { GM_EXPL16 = 0, GM_EXPL8 = 1, GM_HALO = 2, GM_ANY = 3 };
-// What leaves: int32 / fp32 maps in non-temporal or ordinary stores (two kernels: a choice inside one costs partial row
+// What leaves: int32 / fp32 maps in one of the three store forms (a kernel each: a choice inside one costs partial row
 // tiles 10 %); packed signs; packed signs of the 2x2 maximum.
-enum : int { EM_MAPS_NT = 0, EM_MAPS = 1, EM_SIGN = 2, EM_POOL = 3 };
+enum : int { EM_MAPS_NT = MS_NT, EM_MAPS_VEC = MS_VEC, EM_MAPS_ONE = MS_ONE, EM_SIGN = 3, EM_POOL = 4 };
 
 template <int WTM_, int WTN_, int WGM_, int WGN_, int GM_>
 struct Fp4Cfg {
@@ -147,8 +148,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
   constexpr int T = Cfg::T, BM = Cfg::BM, BN = Cfg::BN, PA = Cfg::PA, PB = Cfg::PB, S = Cfg::S;
   constexpr bool POOL = EMODE == EM_POOL;
   // columns of a wave dealt to (block j, lane l): WTN * l + j, so that a lane's columns are consecutive; signs
-  // from an LDS region take 32 * j + l (lanes on consecutive pixels: no bank conflicts)
-  constexpr bool DEALT = !(GM == GM_HALO && EMODE == EM_SIGN);
+  // from an LDS region take 32 * j + l (lanes on consecutive pixels: no bank conflicts), and so do 4-byte stores
+  constexpr bool DEALT = EMODE != EM_MAPS_ONE && !(GM == GM_HALO && EMODE == EM_SIGN);
   // One dword of every 64-byte line of the arguments, requested at once: they arrive in one memory round trip
   // instead of one per group of arguments that the code below happens to need next (each about 500 cycles).
   {
@@ -280,19 +281,22 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
   static_assert(RPT % 32 == 0 && (PB == 0 || (32 * WTN) % RPT == 0 || RPT % (32 * WTN) == 0), "constant LDS distances");
   char *const wrA = smem + (pc * Cfg::P16 + (row0 >> 5) * Cfg::R16 + (row0 & 31)) * 16;
   const int col0 = row0 % (32 * WTN);
-  char *const wrB = smem + (pc * Cfg::P16 + (BM / 32 + (row0 / (32 * WTN)) * WTN + col0 % WTN) * Cfg::R16 + col0 / WTN) * 16;
+  const int unitB = DEALT ? (BM / 32 + (row0 / (32 * WTN)) * WTN + col0 % WTN) * Cfg::R16 + col0 / WTN
+                          : (BM / 32 + (row0 >> 5)) * Cfg::R16 + (row0 & 31);
+  char *const wrB = smem + (pc * Cfg::P16 + unitB) * 16;
   auto store_piece = [&](int i, uint32_t buf) {  // i < PA: A, else B
     if (i < PA) {
       *reinterpret_cast<u32x4 *>(wrA + buf + i * (RPT / 32) * Cfg::R16 * 16) = ra[i];
     } else if (i < PA + PB) {
       const int c = (i - PA) * RPT;  // columns from the first one
-      *reinterpret_cast<u32x4 *>(wrB + buf + ((c / (32 * WTN)) * WTN * Cfg::R16 + (c % (32 * WTN)) / WTN) * 16) = rb[i - PA];
+      const int u = DEALT ? (c / (32 * WTN)) * WTN * Cfg::R16 + (c % (32 * WTN)) / WTN : (c / 32) * Cfg::R16;
+      *reinterpret_cast<u32x4 *>(wrB + buf + u * 16) = rb[i - PA];
     }
   };
   // the tile's per-row scale / bias, requested now and written to LDS below; rows past M get the constants whose
   // sign bit is 0
   static_assert(BM <= T, "one row per thread");
-  constexpr bool MAPS = EMODE == EM_MAPS_NT || EMODE == EM_MAPS;
+  constexpr bool MAPS = EMODE < EM_SIGN;
   const bool affine = !MAPS || (p.Y && p.axis == BNN_CH_ROW);  // uniform
   float fsc = 0.0f, fbi = -1.0f;
   if (affine && tid < BM && m0 + tid < p.M) {
@@ -441,7 +445,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
   settle(acc);
   const int mw = m0 + 32 * WTM * wm, nw = n0 + 32 * WTN * wn;
   const float *sc = sSc + 32 * WTM * wm, *bi = sBi + 32 * WTM * wm;
-  if constexpr (MAPS) store_maps<WTM, WTN, EMODE == EM_MAPS_NT>(p, acc, mw, nw, lane, sc, bi);
+  if constexpr (MAPS) store_maps<WTM, WTN, EMODE>(p, acc, mw, nw, lane, sc, bi);
   else if constexpr (EMODE == EM_SIGN) store_signs<WTM, WTN, DEALT>(p, acc, mw, nw, lane, sc, bi);
   else store_signs_pooled<WTM, WTN>(p, acc, mw, nw, lane, sc, bi);
 }
@@ -465,8 +469,9 @@ static bnn_status launch_fp4(GemmParams &p, hipStream_t s) {
 
 template <int WTM, int WTN, int WGM, int WGN, int GM, int MINW>
 static bnn_status launch_fp4_maps(GemmParams &p, hipStream_t s) {
+  if (!p.colperm) return launch_fp4<WTM, WTN, WGM, WGN, GM, EM_MAPS_ONE, MINW>(p, s);
   return p.nt_store ? launch_fp4<WTM, WTN, WGM, WGN, GM, EM_MAPS_NT, MINW>(p, s)
-                    : launch_fp4<WTM, WTN, WGM, WGN, GM, EM_MAPS, MINW>(p, s);
+                    : launch_fp4<WTM, WTN, WGM, WGN, GM, EM_MAPS_VEC, MINW>(p, s);
 }
 
 // Upper bound of the number of aligned-grid cells of length `cell` that a run of `len` columns starting at a

@@ -1116,6 +1116,7 @@ def test_gemm_matrix_core_tiles(M, N, K, cfg):
 
 @pytest.mark.parametrize("M,N,K,ldc", [
     (130, 100004, 300, 100004),   # ordinary stores
+    (132, 100003, 300, 100003),   # 4-byte stores
     (130, 20004, 2500, 20012),    # rows inside half lines, non-temporal
     (130, 120016, 300, 120016),   # whole half lines, ordinary
     (130, 40016, 300, 40016),     # whole half lines, non-temporal
