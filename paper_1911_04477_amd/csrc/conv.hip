@@ -166,7 +166,7 @@ __device__ __forceinline__ uint32_t c1m_spread_nibbles(uint32_t m) {
   return (m & 0xFu) | ((m & 0xF0u) << 4) | ((m & 0xF00u) << 8) | ((m & 0xF000u) << 12);
 }
 
-// Stage the filter taps of channels ch0 .. ch0 + 127 tap-major in LDS (read [channel][tap]
+// Stage the filter taps of channels ch0 .. ch0 + 32 * NG - 1 tap-major in LDS (read [channel][tap]
 // contiguously; channels past D are zero) and their scale / bias (past D, or without an affine
 // map: fma(0, acc, -1) < 0, so such bits are 0).
 template <int NG>
@@ -315,6 +315,7 @@ __global__ __launch_bounds__(256, 4) void conv2d_f32_k27_mfma_sign_kernel(
 }
 
 // fp32 NCHW output (the map itself, with the affine map if has_affine), same chains, no pipelining.
+template <int NG>
 __global__ __launch_bounds__(256) void conv2d_f32_k27_mfma_kernel(const float *__restrict__ x,
                                                                   const float *__restrict__ w, int H, int W, int D,
                                                                   int sH, int sW, int pH, int pW, int OH, int OW,
@@ -323,7 +324,6 @@ __global__ __launch_bounds__(256) void conv2d_f32_k27_mfma_kernel(const float *_
                                                                   FastDiv divOH, uint32_t total_pix, uint32_t ngroups,
                                                                   int groups_per_wave, float *__restrict__ outf,
                                                                   int has_affine) {
-  constexpr int NG = 1;
   __shared__ float sTap[27 * C1M_RS(NG)];
   __shared__ float sSc[32 * NG], sBi[32 * NG];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -354,13 +354,15 @@ __global__ __launch_bounds__(256) void conv2d_f32_k27_mfma_kernel(const float *_
       const uint32_t qn = fdiv(fdiv(qc, divOW), divOH);
       obase[b] = (size_t)qn * D * ohw + ((size_t)qc - (size_t)qn * ohw);
     }
-    {
-      const c1m_v32f acc = c1m_chain<NG>(sTap + l32, xv);
+#pragma unroll 1
+    for (int g = 0; g < NG; ++g) {
+      if (32 * g >= nch) break;  // workgroup-uniform
+      const c1m_v32f acc = c1m_chain<NG>(sTap + 32 * g + l32, xv);
 #pragma unroll
       for (int b = 0; b < 2; ++b)
 #pragma unroll
         for (int rr = 0; rr < 16; ++rr) {
-          const int chl = 8 * (rr >> 2) + 4 * half + (rr & 3);
+          const int chl = 32 * g + 8 * (rr >> 2) + 4 * half + (rr & 3);
           if (chl < nch && ov[b]) {
             const float a = acc[16 * b + rr];
             outf[obase[b] + (size_t)(ch0 + chl) * ohw] = has_affine ? fmaf(sSc[chl], a, sBi[chl]) : a;
@@ -372,9 +374,9 @@ __global__ __launch_bounds__(256) void conv2d_f32_k27_mfma_kernel(const float *_
 
 // Launch shape of the matrix-core first layer: one wave per `*gpw` groups of 64 pixels (enough
 // groups per wave to amortise the filter staging, enough waves to give every SIMD four).
-static dim3 c1m_grid(int64_t total_pix, int D, int ng, int *gpw) {
+static dim3 c1m_grid(int64_t total_pix, int D, int ng, int *gpw, int64_t wave_slots = 4096) {
   const int64_t ngroups = (total_pix + 63) / 64;
-  int64_t g = ngroups / 4096;
+  int64_t g = ngroups / wave_slots;
   g = g < 1 ? 1 : (g > 8 ? 8 : g);
   *gpw = (int)g;
   const int64_t waves = (ngroups + g - 1) / g;
@@ -621,13 +623,21 @@ bnn_status launch_conv2d_f32_k27(const float *x, const float *w, int N, int H, i
                                  int pW, const float *scale, const float *bias, float *out, hipStream_t s) {
   const int64_t OH = bnn_conv_out_dim(H, 3, sH, pH), OW = bnn_conv_out_dim(W, 3, sW, pW);
   const int64_t total = (int64_t)N * OH * OW;
-  // one channel group per workgroup at every size: the stores of the map hide the repeated loads (batch 1 17.6 -> 6.0 us,
-  // batch 64 20.6 -> 13.2, batch 256 42.5 -> 41.5)
+  // One channel group per workgroup: the stores of the map hide the repeated loads (32 x 32 maps, 128 channels: batch 1
+  // 17.6 -> 6.0 us, batch 64 20.6 -> 13.2, batch 256 45.8 -> 38.8; 32 x 128 x 224 x 224 255 -> 219), but not those of many
+  // groups into a large map, which take four (256 x 384 x 32 x 32 132 -> 102 us, 8 x 512 x 224 x 224 237 -> 210, 128 x 1024 x
+  // 56 x 56 474 -> 403; 16 x 256 x 224 x 224 217 against 229, 4 x 384 x 224 x 224 80 against 81).
+  const bool four = D > 256 && total * D * 4 > 350000000;
   int gpw;
-  const dim3 grid = c1m_grid(total, D, 1, &gpw), block(256);
-  hipLaunchKernelGGL(conv2d_f32_k27_mfma_kernel, grid, block, 0, s, x, w, H, W, D, sH, sW, pH, pW, (int)OH, (int)OW,
-                     scale, bias, FastDiv((uint32_t)OW), FastDiv((uint32_t)OH), (uint32_t)total,
-                     (uint32_t)((total + 63) / 64), gpw, out, scale ? 1 : 0);
+  const dim3 grid = c1m_grid(total, D, four ? 4 : 1, &gpw, four ? 2048 : 4096), block(256);
+  const FastDiv dOW((uint32_t)OW), dOH((uint32_t)OH);
+  const uint32_t ngroups = (uint32_t)((total + 63) / 64);
+  if (four)
+    hipLaunchKernelGGL(conv2d_f32_k27_mfma_kernel<4>, grid, block, 0, s, x, w, H, W, D, sH, sW, pH, pW, (int)OH, (int)OW,
+                       scale, bias, dOW, dOH, (uint32_t)total, ngroups, gpw, out, scale ? 1 : 0);
+  else
+    hipLaunchKernelGGL(conv2d_f32_k27_mfma_kernel<1>, grid, block, 0, s, x, w, H, W, D, sH, sW, pH, pW, (int)OH, (int)OW,
+                       scale, bias, dOW, dOH, (uint32_t)total, ngroups, gpw, out, scale ? 1 : 0);
   return launch_status();
 }
 }  // namespace bnn

@@ -1232,6 +1232,22 @@ def test_first_layer_few_and_many_pixels(N, H, W, D):
     assert np.array_equal(got, oracle.pack_nhwc(ref))
 
 
+@pytest.mark.parametrize("N,D", [(4, 449), (4, 256), (3, 449)])
+def test_first_layer_large_maps(N, D):
+    """Maps above and below 350 MB, channel counts on both sides of the rule and off the groups of 32 and 128: the
+    batch repeats one image, whose map the oracle knows."""
+    print(f"first layer large map N={N} D={D}", flush=True)
+    H, W = 223, 227
+    rng = np.random.default_rng(N + D)
+    x = rng.standard_normal((1, 3, H, W)).astype(np.float32)
+    w = rng.standard_normal((D, 3, 3, 3)).astype(np.float32)
+    sc, bi = rng.standard_normal(D).astype(np.float32), rng.standard_normal(D).astype(np.float32)
+    ref = dev(oracle.conv2d_f32_seq(x, w, (1, 1), (1, 1), sc, bi))
+    out = B.bnn_conv2d_f32(dev(x).expand(N, 3, H, W).contiguous(), dev(w), (1, 1), (1, 1), dev(sc), dev(bi))
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref.expand(N, D, H, W))
+
+
 # ---------------------------------------------------------------- im2col in one launch / in two
 @pytest.mark.parametrize("case", [
     # N, C, H, W, kH, kW, sH, sW, pH, pW
