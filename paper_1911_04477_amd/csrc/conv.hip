@@ -384,9 +384,13 @@ static dim3 c1m_grid(int64_t total_pix, int D, int ng, int *gpw, int64_t wave_sl
 }
 
 // Packed signs: one channel group per workgroup while that does not give a SIMD more than four waves per 128 channels
-// (32 x 32 maps, 128 channels: batch 1 8.7 -> 4.4 us, batch 32 9.3 -> 5.7, batch 64 9.6 -> 8.2; batch 128 13.5 against 14.0,
-// batch 256 22.5 against 27.3: the patch's loads and selects are repeated per group).
-static bool c1m_split(int64_t total_pix) { return (total_pix + 63) / 64 <= 4 * (int64_t)device_cu_count(); }
+// (32 x 32 maps, 128 channels: batch 1 8.6 -> 4.3 us, batch 32 9.0 -> 5.6, batch 63 9.2 -> 8.4; batch 128 13.5 against 14.0,
+// batch 256 22.5 against 27.3: the patch's loads and selects are repeated per group) nor six in all (batch 32, 384
+// channels 13.2 -> 11.7; 512 13.2 against 13.7, 1024 21.0 against 26.1; batch 63, 512 21.9 against 26.6).
+static bool c1m_split(int64_t total_pix, int D) {
+  const int64_t pix_groups = (total_pix + 63) / 64, cu = device_cu_count();
+  return pix_groups <= 4 * cu && pix_groups * (((int64_t)D + 31) / 32) <= 24 * cu;
+}
 
 // Filter bank of a fully-connected layer whose input is a flattened NCHW map [C, H, W],
 // re-ordered to the packed NHWC bit order (h, w, c) of the activations: a common
@@ -595,7 +599,7 @@ extern "C" bnn_status bnn_conv2d_f32_sign(const float *x, const float *w, int N,
     const dim3 block(256);
     if (K == 27 && C == 3 && kH == 3 && kW == 3) {
       int gpw;
-      const bool split = c1m_split(total);
+      const bool split = c1m_split(total, D);
       const dim3 grid = c1m_grid(total, D, split ? 1 : 4, &gpw);
       const uint32_t ngroups = (uint32_t)((total + 63) / 64);
       const int cw = (int)bnn_packed_words(D);

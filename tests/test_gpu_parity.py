@@ -1217,10 +1217,11 @@ def test_gemm_rows_beyond_the_accumulators_exact_range():
     assert got[1, 1] == K and got[1, 2] == -K
 
 
-@pytest.mark.parametrize("N,H,W,D", [(1, 7, 9, 33), (2, 16, 16, 96), (1, 8, 8, 200), (70, 32, 32, 40), (5, 33, 31, 64)])
+@pytest.mark.parametrize("N,H,W,D", [(1, 7, 9, 33), (2, 16, 16, 96), (1, 8, 8, 200), (70, 32, 32, 40), (5, 33, 31, 64),
+                                     (24, 32, 32, 500), (24, 32, 32, 530)])
 def test_first_layer_few_and_many_pixels(N, H, W, D):
     """The 3x3x3 layer with one channel group per workgroup (few pixels) and four (more than 64 per compute unit times
-    four), channel counts off the group of 32; extreme magnitudes, signs and maps against the oracle's fma chains."""
+    four, or with many channels fewer), channel counts off the group of 32; extreme magnitudes, signs and maps against the oracle's fma chains."""
     print(f"first layer N={N} {H}x{W} D={D}", flush=True)
     rng = np.random.default_rng(N + H + W + D)
     x = (rng.standard_normal((N, 3, H, W)) * 2.0 ** rng.integers(-40, 40, size=(N, 3, H, W))).astype(np.float32)
