@@ -105,26 +105,36 @@ def test_pack_weight_and_im2col_match_oracle(case):
 
 
 # ---------------------------------------------------------------- GEMM (a3)
+# tile configurations of the GEMM (bnn_testing.h) and the kernel each runs on; 21 and 22 exist with the packed epilogue
+GEMM_KERNELS = {1: "xnor_gemm", 2: "xnor_gemm_small", 3: "xnor_gemm", 4: "xnor_gemm", 6: "xnor_gemm",
+                23: "xnor_gemm_fp4", 24: "xnor_gemm_fp4", 25: "xnor_gemm_fp4_split", 26: "xnor_gemm_fp4_split",
+                27: "xnor_gemm_fp4_split", 28: "xnor_gemm_fp4_split"}
+PACKED_KERNELS = {1: "xnor_gemm", 3: "xnor_gemm", 4: "xnor_gemm", 6: "xnor_gemm", 21: "xnor_gemm_fp4",
+                  22: "xnor_gemm_fp4", **{c: k for c, k in GEMM_KERNELS.items() if c >= 23}}
+
+
 def _gemm_case(M, N, K, seed, cfg=None):
     rng = np.random.default_rng(seed)
     A = inputs.inject_specials(rng.standard_normal((M, K)).astype(np.float32), seed, frac=0.002)
     Bm = inputs.inject_specials(rng.standard_normal((N, K)).astype(np.float32), seed + 1, frac=0.002)
     Ap, Bp = B.bnn_encode(dev(A)), B.bnn_encode(dev(Bm))
-    got = host(B.bnn_xnor_gemm(Ap, Bp, K, cfg=cfg))
-    assert np.array_equal(got, oracle.gemm_pm1(A, Bm))
+    C, names = kernels_of(lambda: B.bnn_xnor_gemm(Ap, Bp, K, cfg=cfg))
+    assert np.array_equal(host(C), oracle.gemm_pm1(A, Bm))
+    if cfg is not None:
+        assert names == [GEMM_KERNELS[cfg]]
 
 
 # K = 130 / 192 (three-word rows: dword-at-a-time tail), 400 / 704 (4n + 3 words: window chunk at an odd word)
 @pytest.mark.parametrize("K", [1, 31, 32, 33, 63, 64, 65, 130, 192, 200, 256, 257, 400, 511, 512, 544, 704, 1152,
                                2304 + 17])
-@pytest.mark.parametrize("cfg", [1, 2, 3, 4, 6, 7, 8, 9, 13, 14, 15, 16, 17, 18])
+@pytest.mark.parametrize("cfg", GEMM_KERNELS)
 def test_gemm_k_sweep_all_tile_configs(K, cfg):
     print(f"gemm K={K} cfg={cfg}", flush=True)
     _gemm_case(37, 150, K, seed=K * 7 + cfg, cfg=cfg)
 
 
 @pytest.mark.parametrize("M,N", [(1, 1), (1, 700), (65, 513), (64, 512), (130, 1030), (257, 64), (33, 65)])
-@pytest.mark.parametrize("cfg", [1, 2, 3, 4, 6, 7, 8, 9, 13, 14, 15, 16, 17, 18])
+@pytest.mark.parametrize("cfg", GEMM_KERNELS)
 def test_gemm_ragged_tiles(M, N, cfg):
     print(f"gemm M={M} N={N} cfg={cfg}", flush=True)
     _gemm_case(M, N, 300, seed=M * 1000 + N + cfg, cfg=cfg)
@@ -268,7 +278,7 @@ def test_gemm_leading_dimensions():
 
 
 @pytest.mark.parametrize("axis", ["row", "col"])
-@pytest.mark.parametrize("cfg", [-1, 1, 2, 3, 4, 6, 7, 8, 9, 13, 14, 15, 16, 17, 18])
+@pytest.mark.parametrize("cfg", [-1, *GEMM_KERNELS])
 @pytest.mark.parametrize("M,N,K", [(37, 150, 300), (130, 515, 1100), (8, 64, 64), (70, 200, 4096 + 77)])
 def test_gemm_fp32_epilogue_both_axes(M, N, K, cfg, axis):
     """y = fma(scale[ch], float(acc), bias[ch]) with the channel along rows or columns, with and
@@ -284,7 +294,8 @@ def test_gemm_fp32_epilogue_both_axes(M, N, K, cfg, axis):
     ref = oracle.gemm_pm1(A, Bm)
     yref = oracle.scale_bias(ref, sc, bi, axis)
     ax = B.CH_ROW if axis == "row" else B.CH_COL
-    C, Y = B.bnn_xnor_gemm_epilogue(Ap, Bp, K, dev(sc), dev(bi), ax, want_int=True, cfg=cfg)
+    (C, Y), names = kernels_of(lambda: B.bnn_xnor_gemm_epilogue(Ap, Bp, K, dev(sc), dev(bi), ax, want_int=True, cfg=cfg))
+    assert cfg < 0 or names == [GEMM_KERNELS[cfg]]
     assert np.array_equal(host(C), ref)
     assert np.array_equal(host(Y), yref)
     C, Y = B.bnn_xnor_gemm_epilogue(Ap, Bp, K, dev(sc), dev(bi), ax, want_int=False, cfg=cfg)
@@ -519,12 +530,11 @@ PACKED_CASES = CONV_CASES + [
 ]
 
 
-@pytest.mark.parametrize("cfg", [1, 3, 4, 6, 9, 19, 20])
+@pytest.mark.parametrize("cfg", PACKED_KERNELS)
 @pytest.mark.parametrize("case", PACKED_CASES[-11:] + PACKED_CASES[1:4])
 def test_conv2d_packed_forced_tiles(case, cfg):
-    """The binarizing epilogue on every tile shape it is written for (the pooled form only
-    exists for the four-column tiles; other requests fall back to a legal tile, and 9, a
-    configuration only the explicit GEMM has, to the heuristic)."""
+    """The binarizing epilogue on every tile shape it is written for (on the vector ALU the pooled form only
+    exists for the four-column tiles; 4 and 6 fall back to the heuristic)."""
     print(f"conv2d_packed forced cfg={cfg} case={case}", flush=True)
     N, C, H, W, D, kH, kW, sH, sW, pH, pW = case
     shape = inputs.ConvShape(*case)
@@ -534,28 +544,32 @@ def test_conv2d_packed_forced_tiles(case, cfg):
     sc, bi = dev(d["scale"]), dev(d["bias"])
     st, pd = (sH, sW), (pH, pW)
     ref = oracle.conv2d_pm1(d["x"], d["w"], st, pd)
-    got = as_u64(B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, scale=sc, bias=bi, out="packed", cfg=cfg))
-    assert np.array_equal(got, oracle.pack_nhwc(oracle.scale_bias(ref, d["scale"], d["bias"], "nchw")))
+    run = lambda **kw: kernels_of(lambda: B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, scale=sc, bias=bi,
+                                                              out="packed", cfg=cfg, **kw))
+    got, names = run()
+    assert np.array_equal(as_u64(got), oracle.pack_nhwc(oracle.scale_bias(ref, d["scale"], d["bias"], "nchw")))
+    assert names == [PACKED_KERNELS[cfg]]
     if shape.OH % 2 == 0 and shape.OW % 2 == 0:
         pref = oracle.scale_bias(oracle.maxpool2x2_i32(ref), d["scale"], d["bias"], "nchw")
-        got = as_u64(B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, pool=2, scale=sc, bias=bi, out="packed",
-                                         cfg=cfg))
-        assert np.array_equal(got, oracle.pack_nhwc(pref))
+        got, names = run(pool=2)
+        assert np.array_equal(as_u64(got), oracle.pack_nhwc(pref))
+        assert cfg in (4, 6) or names == [PACKED_KERNELS[cfg]]
     assert np.array_equal(host(B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, out="i32", cfg=cfg)), ref)
     # the same forced tile through bnn_conv2d (fp32 image in, int32 NCHW out)
     oi, _ = B.bnn_conv2d(dev(d["x"]), wp, D, kH, kW, st, pd, want_int=True, cfg=cfg)
     assert np.array_equal(host(oi), ref)
 
 
-@pytest.mark.parametrize("lean", [1, 0])
+@pytest.mark.parametrize("cfg,lean", [(None, None), (24, 1), (24, 0), (3, 1), (3, 0)])
 @pytest.mark.parametrize("case", PACKED_CASES)
-def test_conv2d_packed_all_output_kinds(case, lean):
-    """lean = 0 forces the general implicit-GEMM gather also where the lean one applies."""
-    print(f"conv2d_packed case={case} lean={lean}", flush=True)
-    _conv2d_packed_all_output_kinds(case, lean=lean)
+def test_conv2d_packed_all_output_kinds(case, cfg, lean):
+    """As an application calls it, and on one staged tile of the matrix cores and one of the vector ALU with both
+    gathers: lean = 0 forces the general one also where the input region (the table-driven gather) applies."""
+    print(f"conv2d_packed case={case} cfg={cfg} lean={lean}", flush=True)
+    _conv2d_packed_all_output_kinds(case, cfg=cfg, lean=lean)
 
 
-def _conv2d_packed_all_output_kinds(case, lean=None):
+def _conv2d_packed_all_output_kinds(case, cfg=None, lean=None):
     N, C, H, W, D, kH, kW, sH, sW, pH, pW = case
     shape = inputs.ConvShape(*case)
     d = inputs.conv_inputs(shape, seed=sum(case) + 2)
@@ -565,14 +579,17 @@ def _conv2d_packed_all_output_kinds(case, lean=None):
     sc, bi = dev(d["scale"]), dev(d["bias"])
     st, pd = (sH, sW), (pH, pW)
     ref = oracle.conv2d_pm1(x, d["w"], st, pd)
-    assert np.array_equal(host(B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, out="i32", lean=lean)), ref)
+    assert np.array_equal(host(B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, out="i32", cfg=cfg, lean=lean)), ref)
     yref = oracle.scale_bias(ref, d["scale"], d["bias"], "nchw")
-    assert np.array_equal(host(B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, scale=sc, bias=bi, out="f32", lean=lean)), yref)
-    got = as_u64(B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, scale=sc, bias=bi, out="packed", lean=lean))
+    assert np.array_equal(host(B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, scale=sc, bias=bi, out="f32", cfg=cfg,
+                                                   lean=lean)), yref)
+    got = as_u64(B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, scale=sc, bias=bi, out="packed", cfg=cfg,
+                                     lean=lean))
     assert np.array_equal(got, oracle.pack_nhwc(yref))
     if shape.OH % 2 == 0 and shape.OW % 2 == 0:
         pref = oracle.scale_bias(oracle.maxpool2x2_i32(ref), d["scale"], d["bias"], "nchw")
-        got = as_u64(B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, pool=2, scale=sc, bias=bi, out="packed", lean=lean))
+        got = as_u64(B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, pool=2, scale=sc, bias=bi, out="packed", cfg=cfg,
+                                         lean=lean))
         assert np.array_equal(got, oracle.pack_nhwc(pref))
 
 
@@ -831,9 +848,10 @@ def _popcount_rows(a_words, b_words, K):
     return (K - 2 * cnt).astype(np.int32)
 
 
-@pytest.mark.parametrize("cfg", [-1, 3, 7, 9, 14, 15])
+@pytest.mark.parametrize("cfg", [-1, 3, 25, 26, 27, 28])
 def test_gemm_very_long_rows(cfg):
-    """K = 2^24 + 77 bits: 65536 full chunks and a ragged tail per row, accumulators in the millions."""
+    """K = 2^24 + 77 bits: 65536 full chunks and a ragged tail per row, accumulators in the millions; beyond the
+    staged matrix-core tiles' range."""
     print(f"gemm long K cfg={cfg}", flush=True)
     M, N, K = 3, 5, (1 << 24) + 77
     rng = np.random.default_rng(77)
@@ -842,7 +860,9 @@ def test_gemm_very_long_rows(cfg):
     Bm[1] = A[0]            # one identical pair: C = K
     Bm[2] = -A[1]           # one opposite pair: C = -K (no zeros in a normal sample)
     Ap, Bp = B.bnn_encode(dev(A)), B.bnn_encode(dev(Bm))
-    got = host(B.bnn_xnor_gemm(Ap, Bp, K, cfg=None if cfg < 0 else cfg))
+    C, names = kernels_of(lambda: B.bnn_xnor_gemm(Ap, Bp, K, cfg=None if cfg < 0 else cfg))
+    assert names == ["xnor_gemm_fp4_split" if cfg < 0 else GEMM_KERNELS[cfg]]
+    got = host(C)
     assert got[0, 1] == K and got[1, 2] == -K
     # rows encoded by the oracle, not by the GPU
     assert np.array_equal(got, _popcount_rows(oracle.encode_rows(A), oracle.encode_rows(Bm), K))
@@ -868,7 +888,7 @@ def test_gemm_many_columns():
 @pytest.mark.parametrize("N,C", [(255, 128), (510, 64)])
 def test_conv2d_packed_largest_images(N, C):
     """Batches at the documented limit of N*C*H*W (2^33 values): 67 / 134 million pixels, a packed input of
-    1 GiB; C = 128 takes the table-driven gather, C = 64 (one word per pixel) the general one.  The batch
+    1 GiB; an even (C = 128) and an odd (C = 64) number of words per pixel.  The batch
     repeats three distinct images, so every image's result is known from the oracle's three."""
     print(f"conv2d_packed largest images N={N} C={C}", flush=True)
     H, W, D, st, pd = 512, 512, 8, (1, 1), (1, 1)
@@ -1042,7 +1062,7 @@ def test_conv2d_f32_real_valued_layer(case, affine):
 # ---------------------------------------------------------------- whatever the size heuristic picks
 def test_heuristic_kernel_selection_on_random_gemm_shapes():
     """Seeded random (M, N, K) on and off every grid through the entry points as an application
-    calls them: the host chooses between the throughput, one-wave, split-K and short-row kernels."""
+    calls them: the host chooses between the staged and the split-K matrix-core tiles and the short-row kernel."""
     rng = np.random.default_rng(1234)
     done = 0
     while done < 80:
@@ -1066,7 +1086,7 @@ def test_heuristic_kernel_selection_on_random_gemm_shapes():
 
 def test_heuristic_kernel_selection_on_random_packed_convs():
     """Seeded random layer shapes (few to many output pixels, scales of both signs) through
-    bnn_conv2d_packed as the stack calls it: latency form, throughput tiles, short-row kernel."""
+    bnn_conv2d_packed as the stack calls it: split-K and staged tiles, short-row kernel."""
     rng = np.random.default_rng(4321)
     for it in range(60):
         N = int(rng.integers(1, 9))
@@ -1092,7 +1112,7 @@ def test_heuristic_kernel_selection_on_random_packed_convs():
 
 
 # ---------------------------------------------------------------- matrix-core GEMM on packed operands
-@pytest.mark.parametrize("cfg", [21, 22, 23, 24, 25, 26, 27, 28])
+@pytest.mark.parametrize("cfg", [23, 24, 25, 26, 27, 28])
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (129, 257, 128), (128, 256, 512), (65, 300, 129), (37, 152, 640 + 33),
                                    (200, 515, 1024), (64, 1028, 2321), (257, 130, 512 * 3 + 1)])
 def test_gemm_matrix_core_tiles(M, N, K, cfg):
@@ -1178,19 +1198,20 @@ MATRIX_CONV_CASES = [  # N, C, H, W, D, kH, kW, sH, sW, pH, pW
 ]
 
 
-@pytest.mark.parametrize("cfg", [21, 22, 23, 24, 25, 26, 27, 28])
+@pytest.mark.parametrize("cfg,lean", [(c, 1) for c in range(21, 29)] + [(c, 0) for c in range(21, 25)])
 @pytest.mark.parametrize("case", MATRIX_CONV_CASES)
-def test_conv_matrix_core_tiles(case, cfg):
-    """int32, fp32, signs and pooled signs against the oracle, bit for bit."""
+def test_conv_matrix_core_tiles(case, cfg, lean):
+    """int32, fp32, signs and pooled signs against the oracle, bit for bit; lean = 0: the staged tiles gather every
+    word from memory also where the input region would fit LDS."""
     N, C, H, W, D, kH, kW, sH, sW, pH, pW = case
-    print(f"conv matrix core {case} cfg={cfg}", flush=True)
+    print(f"conv matrix core {case} cfg={cfg} lean={lean}", flush=True)
     d = inputs.conv_inputs(inputs.ConvShape(*case), seed=sum(case))
     x = inputs.inject_specials(d["x"], 3, frac=0.001)
     st, pd = (sH, sW), (pH, pW)
     ref = oracle.conv2d_pm1(x, d["w"], st, pd)
     xp, wp = _u64dev(oracle.pack_nhwc(x)), B.bnn_pack_conv_weight(dev(d["w"]))
     sc, bi = dev(d["scale"]), dev(d["bias"])
-    run = lambda **kw: B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, scale=sc, bias=bi, cfg=cfg, **kw)
+    run = lambda **kw: B.bnn_conv2d_packed(xp, wp, C, D, kH, kW, st, pd, scale=sc, bias=bi, cfg=cfg, lean=lean, **kw)
     assert np.array_equal(host(run(out="i32")), ref)
     yref = oracle.scale_bias(ref, d["scale"], d["bias"], "nchw")
     assert np.array_equal(host(run(out="f32")), yref)
