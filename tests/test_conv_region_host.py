@@ -1,9 +1,10 @@
-"""The input region that the matrix-core convolution keeps in LDS, modelled on the CPU.
+"""The input region that the matrix-core convolution keeps in LDS.
 
-The host sizes the region by a bound over all tiles (halo_region in gemm_fp4.hip) and the kernel derives each tile's
-rows and every column's offset from its first and last pixel.  The model states both and checks, for random
-geometries, that no tile needs more rows than the bound and that every tap a column reads lies inside the region on
-the row of its own image."""
+The library sizes the region by a bound over all tiles (bnn_testing_conv_region, no GPU) and the kernel derives each
+tile's rows and every column's offset from its first and last pixel.  The kernel's half is modelled here; for random
+geometries no tile may need more rows than the library's bound, and every word that a column reads must lie inside its
+plane of the region, on the row of its own image, and every plane inside the region's bytes.  (The kernel itself is
+compared with the oracle on the GPU.)"""
 import ctypes
 import random
 
@@ -12,23 +13,27 @@ import pytest
 from paper_1911_04477_amd import binding as B
 
 
-def cells_touched(length, cell):
-    if length % cell == 0:
-        return length // cell
-    if cell % length == 0:
-        return 1
-    return (length - 2) // cell + 2
+def region(*args):
+    """bnn_testing_conv_region -> (rows, pixels per row, bytes between planes, bytes), or None / ValueError."""
+    out = (ctypes.c_int64 * 4)()
+    got = B.lib().bnn_testing_conv_region(*args, out)
+    if got < 0:
+        raise ValueError(args)
+    return tuple(out) if got else None
 
 
-def check_geometry(N, H, W, kH, kW, sH, sW, pH, pW, pool, bn):
+def check_geometry(N, C, H, W, kH, kW, sH, sW, pH, pW, pool, bn):
+    r = region(N, C, H, W, kH, kW, sH, sW, pH, pW, 2 if pool else 0, bn)
+    if r is None:
+        return False
+    bound, Wp, plane, nbytes = r
+    words = (C + 63) // 64
+    # a row of an odd number of words reads its missing one from a plane of zeros
+    assert plane * (words + (kH * kW * words) % 2) <= nbytes <= 100 * 1024
     OH, OW = (H + 2 * pH - kH) // sH + 1, (W + 2 * pW - kW) // sW + 1
     us = 2 if pool else 1  # output rows per unit
-    Wp, units, ustep, uspan = (OW - 1) * sW + kW, OH // us, us * sH, (us - 1) * sH + kH
+    units, ustep, uspan = OH // us, us * sH, (us - 1) * sH + kH
     full = (units - 1) * ustep + uspan
-    ucols = us * us * (OW // us)
-    nu = cells_touched(bn, ucols)
-    ni = min(nu, cells_touched(bn, ucols * units))
-    bound = max((nu - 1) * ustep + uspan, (nu - ni) * ustep + ni * uspan)
 
     def pixel(c):
         if not pool:
@@ -58,7 +63,9 @@ def check_geometry(N, H, W, kH, kW, sH, sW, pH, pW, pool, bn):
                     assert (i0 + 1 + k, q - rows0 - k * full - pH) == (img, oh * sH - pH + kh)
                 else:
                     assert (i0, u0 * ustep - pH + q) == (img, oh * sH - pH + kh)
-            assert (r + kH - 1) * Wp + ow * sW + kW - 1 < rows * Wp
+            assert ow * sW + kW <= Wp
+            assert ((r + kH - 1) * Wp + ow * sW + kW) * 8 <= plane
+    return True
 
 
 @pytest.mark.parametrize("seed", range(6))
@@ -73,15 +80,13 @@ def test_region_bound_covers_every_tile(seed):
             continue
         OH, OW = (H + 2 * pH - kH) // sH + 1, (W + 2 * pW - kW) // sW + 1
         pool = OH % 2 == 0 and OW % 2 == 0 and rng.random() < 0.6
-        check_geometry(rng.randint(1, 9), H, W, kH, kW, sH, sW, pH, pW, pool, rng.choice([64, 128, 256]))
-        seen += 1
+        C = rng.choice([1, 64, 65, 128, 300])
+        seen += check_geometry(rng.randint(1, 9), C, H, W, kH, kW, sH, sW, pH, pW, pool, rng.choice([128, 256]))
 
 
 def test_rows_beyond_the_pitch_are_gathered():
     """Input rows of 4 GiB and more, of which one output column's taps read three pixels: the region would be small,
     but the pitch that the copy into it steps by is a 32-bit number of bytes."""
-    out = (ctypes.c_int64 * 4)()
-    region = B.lib().bnn_testing_conv_region
-    for H, W, C, taken in ((3, 1 << 29, 1, 0), (3, 1 << 29, 5, 0), (2, (1 << 30) - 1, 4, 0), (3, (1 << 29) - 1, 1, 1),
-                           (2, (1 << 29) - 1, 8, 1)):
-        assert region(1, C, H, W, H, 3, 1, 1 << 30, 0, 0, 0, 256, out) == taken, (H, W, C)
+    for H, W, C, taken in ((3, 1 << 29, 1, False), (3, 1 << 29, 5, False), (2, (1 << 30) - 1, 4, False),
+                           (3, (1 << 29) - 1, 1, True), (2, (1 << 29) - 1, 8, True)):
+        assert (region(1, C, H, W, H, 3, 1, 1 << 30, 0, 0, 0, 256) is not None) == taken, (H, W, C)
