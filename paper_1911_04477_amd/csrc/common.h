@@ -97,7 +97,7 @@ struct HaloGeom {
   int nch;             // runs of 64 word pairs per region row
   uint32_t plane;      // bytes between the planes of two words
   uint32_t bytes;      // of the region
-  FastDiv divNch, divPpp, divFull;
+  FastDiv divPpp, divFull;
 };
 
 struct GemmParams {

@@ -510,7 +510,6 @@ bool halo_region(GemmParams &p, int bn, bool pool, int64_t &rows) {
   h.nch = (int)((Wp * ppp + 63) / 64);
   h.plane = (uint32_t)(plane8 * 8);
   h.bytes = (uint32_t)bytes;
-  h.divNch = FastDiv((uint32_t)h.nch);
   h.divPpp = FastDiv((uint32_t)h.ppp);
   h.divFull = FastDiv((uint32_t)h.full);
   return true;
