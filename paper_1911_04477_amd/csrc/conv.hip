@@ -568,9 +568,9 @@ extern "C" int bnn_testing_conv_region(int N, int C, int H, int W, int kH, int k
   if (check_conv_geometry(N, C, H, W, kH, kW, sH, sW, pH, pW) != BNN_OK || N == 0 || !region || columns <= 0 ||
       (pool != 0 && pool != 2))
     return -1;
+  if (pool && ((bnn_conv_out_dim(H, kH, sH, pH) & 1) || (bnn_conv_out_dim(W, kW, sW, pW) & 1))) return -1;
   GemmParams p = {};
   fill_geom(p.g, nullptr, N, C, H, W, kH, kW, sH, sW, pH, pW, pool);
-  if (pool && ((p.g.OH & 1) || (p.g.OW & 1))) return -1;
   p.Kw64 = (int)bnn_conv_kwords(C, kH, kW);
   int64_t rows = 0;
   if (!halo_region(p, columns, pool != 0, rows)) return 0;

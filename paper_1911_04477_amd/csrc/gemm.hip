@@ -879,9 +879,9 @@ static bool rows_start_every(const GemmParams &p, uint32_t ints) {
 //     700 83 -> 39; 256 x 256 x 14 x 14 from 2304 bits 26 -> 24; on average 1.1 to 2.1 times faster by size); with more,
 //     the multiplications hide it and the caches are the operands' (up to 25 % the other way beyond 320 MB).
 //   Rows of whole half lines (28 x 28 maps): the same where the stores decide, below 12 words, and the call's bytes
-//     still fit the last-level cache of 256 MB (64 rows and more: 64 x 28 x 28 from 576 bits, 240 MB: 55.5 -> 43.1 us; 512 x 117200 x 700
+//     still fit the last-level cache of 256 MB (64 x 28 x 28 from 576 bits, 240 MB: 55.5 -> 43.1 us; 512 x 117200 x 700
 //     60.8 -> 42.0); non-temporal elsewhere (512 x 117200 x 2304 80 us, ordinary 95; 64 x 44 x 44 from 512 bits, 300 MB:
-//     20 %; small calls 1 to 5 %).
+//     20 %; fewer than 64 rows 13 %; small calls 1 to 5 %).
 static bool nontemporal_maps(const GemmParams &p, int bmode) {
   if (rows_start_every(p, 32)) return true;
   const int64_t words_x_m = (int64_t)p.Kw64 * (((int64_t)p.M + 63) / 64 * 64);

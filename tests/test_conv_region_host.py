@@ -90,3 +90,13 @@ def test_rows_beyond_the_pitch_are_gathered():
     for H, W, C, taken in ((3, 1 << 29, 1, False), (3, 1 << 29, 5, False), (2, (1 << 30) - 1, 4, False),
                            (3, (1 << 29) - 1, 1, True), (2, (1 << 29) - 1, 8, True)):
         assert (region(1, C, H, W, H, 3, 1, 1 << 30, 0, 0, 0, 256) is not None) == taken, (H, W, C)
+
+
+def test_what_the_convolution_refuses_is_refused():
+    for args in ((1, 64, 3, 3, 3, 3, 1, 1, 0, 0, 2, 128),    # one output pixel, pooled
+                 (1, 64, 5, 6, 3, 3, 1, 1, 0, 0, 2, 128),    # three output rows, pooled
+                 (1, 64, 2, 2, 3, 3, 1, 1, 0, 0, 0, 128),    # no output
+                 (0, 64, 4, 4, 3, 3, 1, 1, 0, 0, 0, 128), (1, 64, 4, 4, 3, 3, 1, 1, 0, 0, 1, 128),
+                 (1, 64, 4, 4, 3, 3, 1, 1, 0, 0, 0, 0)):
+        with pytest.raises(ValueError):
+            region(*args)
