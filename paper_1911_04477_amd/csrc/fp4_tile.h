@@ -131,12 +131,15 @@ __device__ __forceinline__ void settle(Fp4Acc<2, 2> &a) {
 
 // How a lane's WTN columns of a map leave: MS_NT / MS_VEC one non-temporal / ordinary store of consecutive columns
 // per row; MS_ONE one 4-byte store per column and row, neighbouring lanes on neighbouring columns (columns that are not
-// a multiple of 4; against a lane's two columns side by side: 1000 x 3001 x 2321 11.5 -> 10.4 us, 256 x 200001 x 200
-// 42.3 -> 34.5, 128 x 31 x 33 maps from 1152 bits 21.8 -> 17.9).
+// a multiple of 4; against a lane's two columns side by side: 1000 x 3001 x 2321 11.3 -> 10.2 us, 256 x 200001 x 200
+// 41.8 -> 34.4, 128 x 31 x 33 maps from 1152 bits 21.7 -> 17.7).
 enum : int { MS_NT = 0, MS_VEC = 1, MS_ONE = 2 };
 
 // One map (int32, or fp32 through the affine map) of a wave's tile.  AFF: 0 int32, 1 fp32 with per-row
 // constants, 2 fp32 with per-column constants.  FULL: no row of the tile is past M.
+// Rows past M and columns past N hold the values of row M - 1 and column N - 1 once more (the staging clamps them), and
+// go to that place: nothing is predicated but whole groups of 8 rows.  (A branch per row and column instead, in code
+// that few waves run: 701 x 2113 x 1220 9.7 us, this way 6.4; 701 x 2112 x 1220 7.2, 6.1.)
 template <int WTM, int WTN, int AFF, int MS, bool FULL>
 __device__ __forceinline__ void store_map(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n, int half,
                                           const float *sSc, const float *sBi, const int64_t (&off)[WTN]) {
@@ -154,11 +157,12 @@ __device__ __forceinline__ void store_map(const GemmParams &p, const Fp4Acc<WTM,
   }
   int32_t *ptr[WTN];
 #pragma unroll
-  for (int j = 0; j < (MS == MS_ONE ? WTN : 1); ++j) ptr[j] = base + off[j] + (int64_t)(m0 + 4 * half) * ld;
+  for (int j = 0; j < (MS == MS_ONE ? WTN : 1); ++j) ptr[j] = base + off[j] + (int64_t)(FULL ? m0 + 4 * half : m0) * ld;
 #pragma unroll
   for (int i = 0; i < WTM; ++i)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
+      if (!FULL && m0 + 32 * i + 8 * q >= p.M) return;  // uniform
       float4 sc, bi;
       if constexpr (AFF == 1) {
         sc = *reinterpret_cast<const float4 *>(sSc + 32 * i + 8 * q + 4 * half);
@@ -174,17 +178,15 @@ __device__ __forceinline__ void store_map(const GemmParams &p, const Fp4Acc<WTM,
           else if constexpr (AFF == 1) o[j] = __float_as_int(fmaf((&sc.x)[e], v, (&bi.x)[e]));
           else o[j] = __float_as_int(fmaf(csc[j], v, cbi[j]));
         }
-        if (FULL || m0 + 32 * i + 8 * q + 4 * half + e < p.M) {
-          const int64_t row = (int64_t)(32 * i + 8 * q + e) * ld;  // uniform
-          if constexpr (MS == MS_NT) {
-            __builtin_nontemporal_store(o, reinterpret_cast<vi *>(ptr[0] + row));
-          } else if constexpr (MS == MS_VEC) {
-            *reinterpret_cast<vi *>(ptr[0] + row) = o;
-          } else {
+        const int64_t row = FULL ? (int64_t)(32 * i + 8 * q + e) * ld  // uniform
+                                 : (int64_t)min(32 * i + 8 * q + 4 * half + e, p.M - 1 - m0) * ld;
+        if constexpr (MS == MS_NT) {
+          __builtin_nontemporal_store(o, reinterpret_cast<vi *>(ptr[0] + row));
+        } else if constexpr (MS == MS_VEC) {
+          *reinterpret_cast<vi *>(ptr[0] + row) = o;
+        } else {
 #pragma unroll
-            for (int j = 0; j < WTN; ++j)
-              if (n + STEP * j < p.N) ptr[j][row] = o[j];
-          }
+          for (int j = 0; j < WTN; ++j) ptr[j][row] = o[j];
         }
       }
     }
@@ -204,7 +206,7 @@ __device__ __forceinline__ void store_maps(const GemmParams &p, const Fp4Acc<WTM
   constexpr int STEP = MS == MS_ONE ? 32 : 1;
   const int half = lane >> 5;
   const int n = n0 + (MS == MS_ONE ? 1 : WTN) * (lane & 31);
-  if (m0 >= p.M || n >= p.N) return;
+  if (m0 >= p.M || (MS == MS_ONE ? n0 : n) >= p.N) return;
   int64_t off[WTN];
 #pragma unroll
   for (int j = 0; j < WTN; ++j) {

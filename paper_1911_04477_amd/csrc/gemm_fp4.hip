@@ -294,14 +294,14 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
     }
   };
   // the tile's per-row scale / bias, requested now and written to LDS below; rows past M get the constants whose
-  // sign bit is 0
+  // sign bit is 0, and in maps, where they are row M - 1 once more, that row's
   static_assert(BM <= T, "one row per thread");
   constexpr bool MAPS = EMODE < EM_SIGN;
   const bool affine = !MAPS || (p.Y && p.axis == BNN_CH_ROW);  // uniform
   float fsc = 0.0f, fbi = -1.0f;
-  if (affine && tid < BM && m0 + tid < p.M) {
-    fsc = p.scale[m0 + tid];
-    fbi = p.bias[m0 + tid];
+  if (affine && tid < BM && (MAPS || m0 + tid < p.M)) {
+    fsc = p.scale[min(m0 + tid, p.M - 1)];
+    fbi = p.bias[min(m0 + tid, p.M - 1)];
   }
 
   // ---- GM_HALO: the tile's input region -> LDS -----------------------------------------------------------

@@ -1141,23 +1141,26 @@ def test_gemm_matrix_core_tiles(M, N, K, cfg):
     (130, 120016, 300, 120016),   # whole half lines, ordinary
     (130, 40016, 300, 40016),     # whole half lines, non-temporal
     (130, 40032, 300, 40064),     # whole lines
+    (701, 2113, 1220, 2113),      # a last wave of 61 rows, 4-byte stores
+    (701, 2116, 1220, 2116),      # ... 8-byte stores
 ])
 def test_map_store_forms(M, N, K, ldc):
-    """Both forms of the matrix-core tiles' stores at full, partial and padded tiles against the vector-ALU tiles."""
+    """The forms of the matrix-core tiles' stores at full, partial and padded tiles against the vector-ALU tiles; nothing
+    past the map is written."""
     print(f"map stores M={M} N={N} K={K} ldc={ldc}", flush=True)
     g = torch.Generator(device=DEV).manual_seed(M + N + K)
     Ap = torch.randint(-2**62, 2**62, (M, B.packed_words(K)), dtype=torch.int64, device=DEV, generator=g)
     Bp = torch.randint(-2**62, 2**62, (N, B.packed_words(K)), dtype=torch.int64, device=DEV, generator=g)
-    out = torch.full((2, M, ldc), -7, dtype=torch.int32, device=DEV)
+    out = [torch.full((M + 8, ldc), -7, dtype=torch.int32, device=DEV) for _ in range(2)]
     for o, cfg in ((out[0], None), (out[1], 3)):
-        _, names = kernels_of(lambda: B.bnn_xnor_gemm(Ap, Bp, K, o[:, :N], cfg=cfg))
+        _, names = kernels_of(lambda: B.bnn_xnor_gemm(Ap, Bp, K, o[:M, :N], cfg=cfg))
         assert names == ["xnor_gemm" if cfg else "xnor_gemm_fp4"]
     assert torch.equal(out[0], out[1])
-    assert (out[0, :, N:] == -7).all()
+    assert (out[0][:, N:] == -7).all() and (out[0][M:] == -7).all()
     sc, bi = torch.rand(M, device=DEV, generator=g) + 0.5, torch.randn(M, device=DEV, generator=g)
     ys = [B.bnn_xnor_gemm_epilogue(Ap, Bp, K, sc, bi, B.CH_ROW, want_int=True, cfg=cfg) for cfg in (None, 3)]
     assert torch.equal(ys[0][0], ys[1][0]) and torch.equal(ys[0][1], ys[1][1])
-    assert torch.equal(ys[0][0], out[0, :, :N])
+    assert torch.equal(ys[0][0], out[0][:M, :N])
 
 
 @pytest.mark.parametrize("M,N,K,split", [
