@@ -873,22 +873,32 @@ static bool rows_start_every(const GemmParams &p, uint32_t ints) {
 
 // Stores of the matrix-core tiles' maps, non-temporal or ordinary.  Measured over 900 random GEMMs and convolutions;
 // "words" are 64-bit words of the reduction per stored output, rows that a tile computes for nothing included.
-//   Rows of whole 128-byte lines: non-temporal (2 to 9 % faster on average).
+//   Rows of whole 128-byte lines: non-temporal (2 to 9 % faster on average), and so up to 32 rows, half a tile (32 x 14 x
+//     14 from 576 bits, 400 MB: 111 us, ordinary 146; 32 x 60 x 60 from 320, 60 MB: 17.4 against 19.9).
 //   Rows that start inside a 64-byte half line: a piece of a line written past the L2 costs a line in memory, pieces that
 //     meet in the L2 do not.  Ordinary up to 36 words (64 x 128 x 58 x 58 maps from 1152 bits 41 -> 26 us; 1000 x 50004 x
 //     700 83 -> 39; 256 x 256 x 14 x 14 from 2304 bits 26 -> 24; on average 1.1 to 2.1 times faster by size); with more,
-//     the multiplications hide it and the caches are the operands' (up to 25 % the other way beyond 320 MB).
+//     the multiplications hide it and the caches are the operands' (up to 25 % the other way beyond 320 MB).  Up to 56
+//     rows the operand's bytes come near the map's and need those caches from half of them on (48 x 1000008 x 1100
+//     66 us, ordinary 80; 56 rows 70 against 85; 40 x 200004 x 700 13.2 against 14.3), but not below (56 x 1000004 x
+//     576 81 against 66); 64 rows go either way (64 x 400004 x 1600 46 against 41, x 1000008 x 1100 82 against 91).
+//     Small calls whose rows are whole 32-byte sectors stay non-temporal from 12 words on: ordinary stores are 0 to 7 %
+//     faster alone, but push out the fp32 image that the same call encodes (74 x 128 x 20 x 39, stride 2, both maps:
+//     18.1 us, ordinary 19.2; 24 x 157 x 52 x 34 to 128 channels 21.0, 23.0).
 //   Rows of whole half lines (28 x 28 maps): the same where the stores decide, below 12 words, and the call's bytes
 //     still fit the last-level cache of 256 MB (64 x 28 x 28 from 576 bits, 240 MB: 55.5 -> 43.1 us; 512 x 117200 x 700
 //     60.8 -> 42.0); non-temporal elsewhere (512 x 117200 x 2304 80 us, ordinary 95; 64 x 44 x 44 from 512 bits, 300 MB:
-//     20 %; fewer than 64 rows 13 %; small calls 1 to 5 %).
+//     20 %; small calls 1 to 5 %).
 static bool nontemporal_maps(const GemmParams &p, int bmode) {
-  if (rows_start_every(p, 32)) return true;
+  if (rows_start_every(p, 32) || p.M <= 32) return true;
   const int64_t words_x_m = (int64_t)p.Kw64 * (((int64_t)p.M + 63) / 64 * 64);
-  if (!rows_start_every(p, 16)) return words_x_m > 36 * (int64_t)p.M;
   const int64_t out = (int64_t)p.M * p.N * 4 * ((p.C ? 1 : 0) + (p.Y ? 1 : 0));
   const int64_t in = bmode == 0 ? (int64_t)p.N * p.Kw64 * 8 : (int64_t)p.g.Nimg * p.g.H * p.g.W * p.g.Cw * 8;
-  return words_x_m >= 12 * (int64_t)p.M || p.M < 64 || out + in <= 50000000 || out + in > 256000000;
+  const bool small = out + in <= 50000000, long_rows = words_x_m >= 12 * (int64_t)p.M;
+  if (!rows_start_every(p, 16))
+    return words_x_m > 36 * (int64_t)p.M || (p.M <= 56 && 2 * in >= out) ||
+           (small && long_rows && rows_start_every(p, 8));
+  return long_rows || small || out + in > 256000000;
 }
 
 bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const GemmTune &tune) {

@@ -325,11 +325,21 @@ def test_im2col_size_limits(L):
     (1000, 50004, 2304, 50004, 0, 1),    # ... 36 words, 1024 rows computed for 1000
     (256, 50180, 2304, 50180, 0, 0),     # ... 36 words per output: the last
     (256, 50180, 2368, 50180, 0, 1),
+    (256, 20008, 768, 20008, 0, 1),      # whole 32-byte sectors, a small call of 12 words
+    (256, 20008, 704, 20008, 0, 0),
+    (256, 60008, 768, 60008, 0, 0),
     (512, 100016, 704, 100016, 0, 0),    # whole half lines, 205 MB stored
     (512, 100016, 768, 100016, 0, 1),    # ... 12 words per output
     (512, 23024, 704, 23024, 0, 1),      # ... below 50 MB
     (512, 140016, 704, 140016, 0, 1),    # ... above the last-level cache
-    (32, 1000016, 320, 1000016, 0, 1),   # ... half a tile's rows
+    (32, 1000016, 320, 1000016, 0, 1),   # half a tile's rows
+    (33, 1000016, 320, 1000016, 0, 0),
+    (32, 1000004, 320, 1000004, 0, 1),
+    (33, 1000004, 320, 1000004, 0, 0),
+    (48, 1000004, 704, 1000004, 0, 0),
+    (48, 1000004, 768, 1000004, 0, 1),   # the operand's bytes from half of the map's, up to 56 rows
+    (56, 1000004, 1100, 1000004, 0, 1),
+    (57, 1000004, 1100, 1000004, 0, 0),
 ])
 def test_map_stores(L, M, N, K, ldc, base, nt):
     """Non-temporal stores only where a row's pieces are whole lines, or where the rule says that it does not matter."""
