@@ -49,6 +49,10 @@ BOPS_PER_LANEOP = 32.0  # 2 lane-instructions (xor, popcount-accumulate) per 32 
 NO_GRAPHS = False
 
 
+MATRIX_KERNELS = ("xnor_gemm_fp4", "conv_chain")  # as the library's timing hook names them
+GEMM_KERNELS = ("xnor_gemm", "conv_chain")
+
+
 def parse_args():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -145,7 +149,8 @@ def kernel_times(fn, reps):
 
 
 def gemm_launches(fn, shapes, reps):
-    """Per-launch (kernel name, seconds, lane-ops) of the step's GEMM launches, in launch order.
+    """Per-launch (kernel name, seconds, lane-ops) of the step's GEMM launches, in launch order; an entry of `shapes` is
+    a launch's (M, N, K), or the list of them where one launch runs several layers.
 
     The library records one HIP-event pair per launch on the launch stream; the GEMM launches of a
     step come in the order of `shapes`."""
@@ -160,13 +165,14 @@ def gemm_launches(fn, shapes, reps):
             B.prof_reset()
             fn()
             torch.cuda.synchronize()
-            rec = [(n, ms / 1e3) for n, ms in B.prof_records() if n.startswith("xnor_gemm")]
+            rec = [(n, ms / 1e3) for n, ms in B.prof_records() if n.startswith(GEMM_KERNELS)]
             assert len(rec) == len(shapes), (len(rec), len(shapes))
             if acc is None:
                 acc = [[n, 0.0] for n, _ in rec]
             for a, (_, t) in zip(acc, rec):
                 a[1] += t
-        return [(n, t / reps, gemm_laneops(*sh)) for (n, t), sh in zip(acc, shapes)]
+        return [(n, t / reps, sum(gemm_laneops(*s) for s in (sh if isinstance(sh, list) else [sh])))
+                for (n, t), sh in zip(acc, shapes)]
     finally:
         B.prof_enable(False)
 
@@ -204,6 +210,10 @@ def build_workload(name, args):
                 shapes.append((L.cout, batch * L.hw * L.hw, L.cin * 9))
             elif L.kind == "bfc":
                 shapes.append((batch, L.cout, L.cin))
+        if getattr(net, "_chain", None):  # the convolutions are one launch
+            first, last, _ = net._chain
+            n = last + 1 - first
+            shapes = [shapes[:n]] + shapes[n:]
         bit_macs = inputs.stack_bit_macs(d["layers"], batch)
 
         def oracle_sample(seconds):
@@ -605,7 +615,7 @@ def main():
     dom_s, dom_ops, dom_n = by_name[dom]
     gemm_s = sum(t for _, t, _ in launches)
     method = "one HIP-event pair around each launch inside a pass of the stack (library hook)"
-    matrix = dom.startswith("xnor_gemm_fp4")
+    matrix = dom.startswith(MATRIX_KERNELS)
     peak = FP4_PEAK_TOPS if matrix else VALU_PEAK_TLANEOPS
 
     def rate(ops, t):
@@ -626,7 +636,7 @@ def main():
             per_launch[i]["TBOPS"] = round(launches[i][2] * BOPS_PER_LANEOP / t / 1e12, 1)
         method = "each launch of the step replayed 50x back to back between one HIP-event pair on the launch stream"
     for e, (_, _, ops) in zip(per_launch, launches):
-        e["frac"] = round(e["TBOPS"] / (FP4_PEAK_TOPS if e["kernel"].startswith("xnor_gemm_fp4") else VALU_PEAK_TLANEOPS * BOPS_PER_LANEOP), 4)
+        e["frac"] = round(e["TBOPS"] / (FP4_PEAK_TOPS if e["kernel"].startswith(MATRIX_KERNELS) else VALU_PEAK_TLANEOPS * BOPS_PER_LANEOP), 4)
     achieved = rate(dom_ops, dom_s)
     probes = valu_probes()
     fracs = [achieved / peak] + [e["frac"] for e in per_launch]
@@ -635,7 +645,7 @@ def main():
               file=sys.stderr)
     roofline = {
         "kernel": {"xnor_gemm": "xnor_gemm_kernel", "xnor_gemm_fp4": "xnor_gemm_fp4_kernel",
-                   "xnor_gemm_fp4_split": "xnor_gemm_fp4_split_kernel"}.get(dom, dom),
+                   "xnor_gemm_fp4_split": "xnor_gemm_fp4_split_kernel", "conv_chain": "conv_chain_kernel"}.get(dom, dom),
         "bound": "mfma" if matrix else "alu", "achieved": round(achieved, 3), "peak": round(peak, 2),
         "unit": "TOP/s" if matrix else "Tlaneop/s", "frac": round(achieved / peak, 4),
         "valu_peak_Tlaneops": round(VALU_PEAK_TLANEOPS, 2), "valu_peak_nominal_4clk": round(VALU_PEAK_NOMINAL_4CLK, 2),

@@ -221,6 +221,31 @@ BNN_API bnn_status bnn_conv2d_packed(const uint64_t *x_packed, const uint64_t *w
                              const float *scale, const float *bias, void *stream);
 
 /*
+ * bnn_conv_chain -- consecutive bnn_conv2d_packed layers (3x3, stride 1, padding 1, packed in and out) in one launch: a
+ * workgroup takes an image through all of them, the maps between them stay on the compute unit.  The same bits as the
+ * layers one by one.
+ *   x_packed    [N, H, W, C / 64] uint64
+ *   layers      n_layers (at most 8) HOST structs; layer i reads the map of layer i - 1.  D output channels, pool 0 or 2
+ *               (H and W of that layer even), scale and bias [D] as in bnn_conv2d_packed, w_chain from
+ *               bnn_pack_conv_chain_weight, bnn_conv_chain_weight_bytes(C, D) bytes (0: not supported), 16-byte aligned.
+ *   out_packed  [N, H', W', D / 64] uint64, the last layer's map
+ *   Channels into every layer are a multiple of 128, out of the last one of 64, at most 512; the maps have to fit
+ *   160 KB of LDS with their tables (BNN_ERR_UNSUPPORTED otherwise).
+ * bnn_conv_chain_pays: 1 where the chain is supported and expected to be faster than the layers one by one on the
+ *   current device, else 0.  An image occupies one compute unit, so that is a question of how many there are.
+ */
+typedef struct {
+  const void *w_chain;
+  const float *scale, *bias;
+  int D, pool;
+} bnn_chain_layer;
+BNN_API size_t bnn_conv_chain_weight_bytes(int C, int D);
+BNN_API bnn_status bnn_pack_conv_chain_weight(const uint64_t *w_packed, int D, int C, void *w_chain, void *stream);
+BNN_API int bnn_conv_chain_pays(int N, int C, int H, int W, int n_layers, const bnn_chain_layer *layers);
+BNN_API bnn_status bnn_conv_chain(const uint64_t *x_packed, int N, int C, int H, int W, int n_layers,
+                                  const bnn_chain_layer *layers, uint64_t *out_packed, void *stream);
+
+/*
  * bnn_conv2d_f32_sign -- real-valued first layer of the stack with binarized output:
  * bnn_conv2d_f32 (same fixed summation order) followed by fma(scale[d], acc, bias[d]) and
  * the sign, written as a packed NHWC image [N, OH, OW, ceil(D/64)].  Limited to

@@ -20,6 +20,12 @@ LIB_PATH = os.path.join(HERE, "libbnn_san.so" if os.environ.get("BNN_SANITIZE") 
 
 _i64, _i32, _p, _sz = ctypes.c_int64, ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t
 
+
+class ChainLayer(ctypes.Structure):
+    """bnn_chain_layer"""
+    _fields_ = [("w_chain", _p), ("scale", _p), ("bias", _p), ("D", _i32), ("pool", _i32)]
+
+
 # name -> (restype, argtypes); the list mirrors include/bnn.h one to one.
 SIGNATURES = {
     "bnn_status_str": (ctypes.c_char_p, [_i32]),
@@ -44,6 +50,10 @@ SIGNATURES = {
     "bnn_conv2d_noalloc": (_i32, [_p, _p] + [_i32] * 11 + [_p, _p, _p, _p, _p]),
     "bnn_conv2d_noalloc_max_bytes": (_sz, []),
     "bnn_conv2d_packed": (_i32, [_p, _p] + [_i32] * 12 + [_p, _p, _p, _p, _p, _p]),
+    "bnn_conv_chain_weight_bytes": (_sz, [_i32, _i32]),
+    "bnn_pack_conv_chain_weight": (_i32, [_p, _i32, _i32, _p, _p]),
+    "bnn_conv_chain_pays": (_i32, [_i32] * 5 + [ctypes.POINTER(ChainLayer)]),
+    "bnn_conv_chain": (_i32, [_p] + [_i32] * 5 + [ctypes.POINTER(ChainLayer), _p, _p]),
     "bnn_conv2d_f32_sign": (_i32, [_p, _p] + [_i32] * 11 + [_p, _p, _p, _p]),
     "bnn_pack_fc_weight_nhwc": (_i32, [_p, _i64, _i32, _i32, _i32, _p, _p]),
     "bnn_maxpool2x2": (_i32, [_p, _i32, _i32, _i32, _i32, _p, _p, _p, _p, _p]),
@@ -396,6 +406,40 @@ def bnn_conv2d_packed(xp: torch.Tensor, w_packed: torch.Tensor, C: int, D: int, 
                                                _ptr(bias), -1 if cfg is None else cfg, 1 if lean is None else lean,
                                                _stream()), "bnn_testing_conv2d_packed")
     return op if op is not None else (oi if oi is not None else of)
+
+
+def bnn_pack_conv_chain_weight(w_packed: torch.Tensor, C: int) -> torch.Tensor:
+    """Filter bank of a 3x3 layer from bnn_pack_conv_weight, in the order in which bnn_conv_chain multiplies it."""
+    _dev(w_packed, torch.int64, "w_packed")
+    D = w_packed.shape[0]
+    assert w_packed.is_contiguous() and w_packed.shape[1] == conv_kwords(C, 3, 3)
+    out = torch.empty(max(16, int(lib().bnn_conv_chain_weight_bytes(C, D))), dtype=torch.uint8, device=w_packed.device)
+    _check(lib().bnn_pack_conv_chain_weight(_ptr(w_packed), D, C, _ptr(out), _stream()), "bnn_pack_conv_chain_weight")
+    return out
+
+
+def conv_chain_layers(layers) -> ctypes.Array:
+    """[(w_chain or None, scale, bias, D, pool)] -> the host array bnn_conv_chain takes (pointers of live tensors)."""
+    return (ChainLayer * len(layers))(*[ChainLayer(_ptr(w), _ptr(s), _ptr(b), D, pool) for w, s, b, D, pool in layers])
+
+
+def bnn_conv_chain_pays(N: int, C: int, H: int, W: int, layers: ctypes.Array) -> bool:
+    return bool(lib().bnn_conv_chain_pays(N, C, H, W, len(layers), layers))
+
+
+def bnn_conv_chain(xp: torch.Tensor, C: int, layers: ctypes.Array, out: torch.Tensor) -> torch.Tensor:
+    """xp: packed NHWC [N, H, W, C / 64] through consecutive 3x3 layers; out: the last layer's packed map."""
+    _dev(xp, torch.int64, "x_packed")
+    _dev(out, torch.int64, "out")
+    N, H, W, Cw = xp.shape
+    assert xp.is_contiguous() and out.is_contiguous() and Cw == packed_words(C)
+    OH, OW = H, W
+    for L in layers:
+        if L.pool:
+            OH, OW = OH // 2, OW // 2
+    assert tuple(out.shape) == (N, OH, OW, packed_words(layers[-1].D))
+    _check(lib().bnn_conv_chain(_ptr(xp), N, C, H, W, len(layers), layers, _ptr(out), _stream()), "bnn_conv_chain")
+    return out
 
 
 def bnn_conv2d_f32_sign(x: torch.Tensor, w: torch.Tensor, scale: torch.Tensor, bias: torch.Tensor, stride=(1, 1),

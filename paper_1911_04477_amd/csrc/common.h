@@ -30,7 +30,8 @@ enum KernelId : int {
   KID_XNOR_GEMM_FP4 = 19,
   KID_XNOR_GEMM_FP4_SPLIT = 20,
   KID_IM2COL_BAND = 21,
-  KID_COUNT = 22
+  KID_CONV_CHAIN = 22,
+  KID_COUNT = 23
 };
 
 // Timing hook: records an event pair around a launch when profiling is on.

@@ -72,6 +72,47 @@ __device__ __forceinline__ v8i expand_e2m1(uint32_t x) {
   return r;
 }
 
+// 32 bits -> 32 codes that are 0 where the bit is 0: the matrix instruction then counts the positions where both bits
+// are 1 (S), and the sum of the +-1 products is K - 2 pa - 2 pb + 4 S with the set bits pa, pb of the two rows.  Half of
+// the products are 0 and none is negative, so the adders toggle less and the chip holds a higher clock under the same
+// loop (512 x 256 x 8 x 8 layer 18.9 -> 17.3 us, 4096^3 34.8 -> 30.2, with nothing else changed), and the expansion is
+// ands: bit 0, 1, 2 of a nibble alone are the codes 0.5, 1, 2.  A keeps the bits in place (the fourth moves to the
+// second's), B swaps the first and the third, so that every product of two set bits is 1.  11 vector instructions per
+// pair of dwords against 14.  NOW as above.
+template <bool NOW>
+__device__ __forceinline__ v8i expand_bits(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, uint32_t m0, uint32_t m2) {
+  v8i r = {0, 0, 0, 0, 0, 0, 0, 0};
+  uint32_t d;
+  asm volatile("v_and_b32 %0, %1, %2" : "=v"(d) : "s"(m0), "v"(x0));
+  r[0] = (int)d;
+  asm volatile("v_and_b32 %0, %1, %2" : "=v"(d) : "s"(0x22222222u), "v"(x1));
+  r[1] = (int)d;
+  asm volatile("v_and_b32 %0, %1, %2" : "=v"(d) : "s"(m2), "v"(x2));
+  r[2] = (int)d;
+  if (NOW) asm volatile("v_and_b32 %0, %1, %2\n\ts_nop 1" : "=v"(d) : "s"(0x22222222u), "v"(x3));
+  else asm volatile("v_and_b32 %0, %1, %2" : "=v"(d) : "s"(0x22222222u), "v"(x3));
+  r[3] = (int)d;
+  return r;
+}
+
+// What a bit becomes: its sign (above), or itself.
+struct SignCodes {
+  template <bool NOW>
+  static __device__ __forceinline__ v8i a(uint32_t x) { return expand_e2m1<NOW>(x); }
+  template <bool NOW>
+  static __device__ __forceinline__ v8i b(uint32_t x) { return expand_e2m1<NOW>(x); }
+};
+struct BitCodes {
+  template <bool NOW>
+  static __device__ __forceinline__ v8i a(uint32_t x) {  // the fewer fragments: 2 shifts
+    return expand_bits<NOW>(x << 2, x, x >> 2, x >> 2, 0x44444444u, 0x11111111u);
+  }
+  template <bool NOW>
+  static __device__ __forceinline__ v8i b(uint32_t x) {
+    return expand_bits<NOW>(x, x, x, x >> 2, 0x11111111u, 0x44444444u);
+  }
+};
+
 // One step of 64 values for a 32 x 32 block: both operands E2M1 (format 4), no block scales.
 __device__ __forceinline__ v16f mfma_e2m1(const v8i &a, const v8i &b, const v16f &c) {
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 4, 4, 0, 0, 0, 0);
@@ -97,7 +138,7 @@ struct Fp4Acc {
 // expansions of a step form one block and the matrix instructions another, which do not overlap.)  The order also
 // keeps the operands' wait states: with several column blocks the first matrix instruction of the next step does not
 // read the fragment that was expanded last.
-template <int WTM, int WTN, class Side>
+template <class Codes, int WTM, int WTN, class Side>
 __device__ __forceinline__ void multiply_and_expand(Fp4Acc<WTM, WTN> &acc, const v8i (&a)[WTM], const v8i (&b)[WTN],
                                                     const uint32_t (&xa)[WTM], const uint32_t (&xb)[WTN], v8i (&na)[WTM],
                                                     v8i (&nb)[WTN], const Side &side) {
@@ -111,8 +152,8 @@ __device__ __forceinline__ void multiply_and_expand(Fp4Acc<WTM, WTN> &acc, const
     // fragments k * F / n .. (k + 1) * F / n - 1 of the F = WTM + WTN
 #pragma unroll
     for (int f = k * (WTM + WTN) / (WTM * WTN); f < (k + 1) * (WTM + WTN) / (WTM * WTN); ++f) {
-      if (f < WTM) na[f] = expand_e2m1<false>(xa[f]);
-      else nb[f - WTM] = expand_e2m1<WTN == 1>(xb[f - WTM]);
+      if (f < WTM) na[f] = Codes::template a<false>(xa[f]);
+      else nb[f - WTM] = Codes::template b<WTN == 1>(xb[f - WTM]);
     }
     __builtin_amdgcn_sched_barrier(0);
   }

@@ -412,7 +412,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
       u32x2 na[WTM], nb[WTN];  // the next piece (past the last one: whatever is there, not used)
       const uint32_t next = k + 1 < S ? rbuf + (k + 1) * Cfg::P16 * 16 : wbuf;
       v8i fa[WTM], fb[WTN];
-      multiply_and_expand<WTM, WTN>(acc, ea, eb, ya, yb, fa, fb, [&](int m) {
+      multiply_and_expand<SignCodes, WTM, WTN>(acc, ea, eb, ya, yb, fa, fb, [&](int m) {
 #pragma unroll
         for (int f = m * FR / MM; f < (m + 1) * FR / MM; ++f) read_frag(f, next, na, nb);
       });
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
         xb[j] = nb[j].x;
         yb[j] = nb[j].y;
       }
-      multiply_and_expand<WTM, WTN>(acc, fa, fb, xa, xb, ea, eb, [&](int m) {
+      multiply_and_expand<SignCodes, WTM, WTN>(acc, fa, fb, xa, xb, ea, eb, [&](int m) {
         if (k == 0) {  // the next stage's pieces, from registers
 #pragma unroll
           for (int i = m * (PA + PB) / MM; i < (m + 1) * (PA + PB) / MM; ++i) store_piece(i, wbuf);

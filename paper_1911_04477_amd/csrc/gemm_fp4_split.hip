@@ -138,7 +138,7 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
         xa[i] = a[i][d];
         xb[i] = b[i][d];
       }
-      multiply_and_expand<WT, WT>(acc, ea, eb, xa, xb, na, nb, [](int) {});
+      multiply_and_expand<SignCodes, WT, WT>(acc, ea, eb, xa, xb, na, nb, [](int) {});
 #pragma unroll
       for (int i = 0; i < WT; ++i) {
         ea[i] = na[i];

@@ -114,7 +114,27 @@ class VggStackFused:
             self.p.append(d)
             self.buf.append(b)
         self._graph = None
+        self._chain = self._find_chain()
         torch.cuda.synchronize(self.dev)
+
+    def _find_chain(self):
+        """(first, last, host array) of the consecutive binarized convolutions that go through bnn_conv_chain in one
+        launch, or None where the layers one by one are expected to be faster (bnn_conv_chain_pays)."""
+        conv = [i for i, L in enumerate(self.layers) if L.kind == "bconv"]
+        if not conv or conv[0] == 0 or conv != list(range(conv[0], conv[-1] + 1)):
+            return None
+        first, last = conv[0], conv[-1]
+        L0 = self.layers[first]
+
+        def array(weights):
+            return B.conv_chain_layers([(w, self.p[i]["scale"], self.p[i]["bias"], self.layers[i].cout,
+                                         2 if self.layers[i].pool else 0) for i, w in zip(conv, weights)])
+
+        if not B.bnn_conv_chain_pays(self.batch, L0.cin, L0.hw, L0.hw, array([None] * len(conv))):
+            return None
+        for i in conv:
+            self.p[i]["wc"] = B.bnn_pack_conv_chain_weight(self.p[i]["wp"], self.layers[i].cin)
+        return first, last, array([self.p[i]["wc"] for i in conv])
 
     def capture(self, x: torch.Tensor) -> None:
         """Record one forward pass reading x (its storage, not its present contents) into a HIP
@@ -143,7 +163,12 @@ class VggStackFused:
     def forward(self, x: torch.Tensor, keep: bool = False):
         h = x
         acts = []
-        for L, p, b in zip(self.layers, self.p, self.buf):
+        chain = None if keep else self._chain  # the maps inside the chain never reach memory
+        for i, (L, p, b) in enumerate(zip(self.layers, self.p, self.buf)):
+            if chain and chain[0] <= i <= chain[1]:
+                if i == chain[0]:
+                    h = B.bnn_conv_chain(h, L.cin, chain[2], self.buf[chain[1]]["yp"])
+                continue
             if L.kind == "conv_f32":
                 h = B.bnn_conv2d_f32_sign(h, p["w"], p["scale"], p["bias"], (1, 1), (1, 1), out=b["yp"])
             elif L.kind == "bconv":
@@ -165,8 +190,12 @@ class VggStackFused:
         return (h, acts) if keep else h
 
     def conv_launches(self):
-        """One closure per binarized convolution that re-issues exactly that layer's launch on the
-        buffers the last forward() left behind (for timing a launch in isolation)."""
+        """One closure per launch of binarized convolutions (a layer's, or the chain's) that re-issues exactly that launch
+        on the buffers the last forward() left behind (for timing a launch in isolation)."""
+        if self._chain:
+            first, last, layers = self._chain
+            return [lambda: B.bnn_conv_chain(self.buf[first - 1]["yp"], self.layers[first].cin, layers,
+                                             self.buf[last]["yp"])]
         out = []
         prev = None
         for L, p, b in zip(self.layers, self.p, self.buf):

@@ -349,3 +349,39 @@ def test_map_stores(L, M, N, K, ldc, base, nt):
 def test_map_stores_refuses(L):
     for args in ((0, 8, 8, 8, 0), (8, 0, 8, 8, 0), (8, 8, 0, 8, 0), (8, 8, 8, 7, 0)):
         assert L.bnn_testing_nontemporal_maps(*args) == -1
+
+
+def _chain_layer(D, pool=0, w=16, s=16, b=16):
+    return B.ChainLayer(w, s, b, D, pool)
+
+
+def test_conv_chain_errors(L):
+    one = (B.ChainLayer * 1)(_chain_layer(128))
+    call = lambda N=1, C=128, H=8, W=8, arr=one, n=None, x=16, out=16: L.bnn_conv_chain(
+        x, N, C, H, W, len(arr) if n is None else n, arr, out, None)
+    assert call(N=0) == OK
+    assert call(N=-1) == SHAPE and call(H=0) == SHAPE and call(C=0) == SHAPE and call(n=0) == SHAPE
+    assert call(x=None) == NULL and call(out=None) == NULL
+    assert L.bnn_conv_chain(16, 1, 128, 8, 8, 1, None, 16, None) == NULL
+    assert call(x=8) == ALIGN and call(out=8) == ALIGN
+    layer = lambda *a, **k: (B.ChainLayer * 1)(_chain_layer(*a, **k))
+    assert call(arr=layer(128, w=None)) == NULL and call(arr=layer(128, s=None)) == NULL and call(arr=layer(128, b=None)) == NULL
+    assert call(arr=layer(128, w=24)) == ALIGN
+    assert call(arr=layer(0)) == SHAPE and call(arr=layer(128, 1)) == SHAPE
+    assert call(arr=layer(128, 2), H=7) == SHAPE and call(arr=layer(128, 2), W=7) == SHAPE  # odd maps do not pool
+    assert call(arr=layer(96)) == UNSUPPORTED and call(arr=layer(576)) == UNSUPPORTED
+    assert call(C=64) == UNSUPPORTED and call(C=640) == UNSUPPORTED
+    assert call(H=64, W=64) == UNSUPPORTED  # 160 KB of LDS
+    assert call(H=300, W=1) == UNSUPPORTED
+    assert call(arr=(B.ChainLayer * 9)(*[_chain_layer(128)] * 9)) == UNSUPPORTED
+    assert call(arr=(B.ChainLayer * 2)(_chain_layer(64), _chain_layer(128))) == UNSUPPORTED  # 64 channels into a layer
+    assert call(N=1 << 30) == UNSUPPORTED
+    assert L.bnn_conv_chain_weight_bytes(128, 128) == 128 * 18 * 8 + 128 * 4
+    assert L.bnn_conv_chain_weight_bytes(64, 128) == 0 and L.bnn_conv_chain_weight_bytes(128, 100) == 0
+    assert L.bnn_pack_conv_chain_weight(16, 0, 128, 16, None) == OK
+    assert L.bnn_pack_conv_chain_weight(16, -1, 128, 16, None) == SHAPE
+    assert L.bnn_pack_conv_chain_weight(16, 128, 64, 16, None) == UNSUPPORTED
+    assert L.bnn_pack_conv_chain_weight(None, 128, 128, 16, None) == NULL
+    assert L.bnn_pack_conv_chain_weight(16, 128, 128, 8, None) == ALIGN
+    assert L.bnn_conv_chain_pays(0, 128, 8, 8, 1, one) == 0 and L.bnn_conv_chain_pays(4, 64, 8, 8, 1, one) == 0
+    assert L.bnn_conv_chain_pays(1, 128, 8, 8, 1, one) == 0  # one image leaves every other unit idle

@@ -723,6 +723,75 @@ def test_cfg4_fused_stack_full_batch_every_layer_every_image(cfg4_b256):
     assert np.array_equal(host(out), ref["out"])
 
 
+CHAIN_CASES = [  # N, C, H, W, [(D, pool)]
+    (3, 128, 8, 8, [(128, 0)]),                                    # one layer: 64 columns, half the waves idle
+    (2, 128, 8, 8, [(64, 2)]),                                     # 64 channels out
+    (2, 128, 32, 32, [(128, 2), (256, 0), (256, 2), (512, 0), (512, 2)]),
+    (1, 128, 7, 9, [(128, 0), (64, 0)]),                           # 63 columns
+    (2, 384, 12, 10, [(384, 2), (128, 0), (256, 0)]),              # six words per pixel; 30 pooled columns
+    (1, 128, 2, 2, [(128, 0), (128, 2), (128, 0)]),                # down to one pixel
+    (1, 512, 6, 6, [(512, 0), (512, 2), (512, 0), (64, 0)]),
+    (1, 128, 33, 31, [(256, 0)]),                                  # 1023 columns
+    (1, 128, 4, 4, [(128, 0)] * 8),                                # the most layers
+]
+
+
+@pytest.mark.parametrize("case", CHAIN_CASES)
+def test_conv_chain(case):
+    """Consecutive layers in one launch, bit for bit against the oracle; scales of both signs, and a layer with affine maps
+    that never or always give +1, hit the boundary exactly, or are not finite."""
+    print(f"conv_chain case={case}", flush=True)
+    N, C, H, W, layers = case
+    rng = np.random.default_rng(sum(case[:4]))
+    h = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    xp = _u64dev(oracle.pack_nhwc(h))
+    arr, keep = [], []
+    for D, pool in layers:
+        w = rng.standard_normal((D, C, 3, 3)).astype(np.float32)
+        sc = (rng.uniform(0.5, 1.5, D) * rng.choice([-1.0, 1.0], D)).astype(np.float32)
+        bi = (rng.standard_normal(D) * 20).astype(np.float32)
+        for i, (s, b) in enumerate([(0.0, -0.0), (-0.0, 1.0), (np.nan, 1.0), (np.inf, 0.5), (1.0, np.inf), (-np.inf, 1.0),
+                                    (1.0, -np.inf), (1e-42, 1e-43), (-3e38, 1e38), (0.25, -0.75), (-0.5, 3.0), (1.0, np.nan),
+                                    (np.inf, -np.inf), (1.0, 1e9), (1.0, -1e9), (1e-45, -1e-45)]):
+            sc[i], bi[i] = s, b
+        acc = oracle.conv2d_pm1(h, w, (1, 1), (1, 1))
+        if pool:
+            acc = oracle.maxpool2x2_i32(acc)
+        h = oracle.scale_bias(acc, sc, bi, "nchw")
+        wc = B.bnn_pack_conv_chain_weight(B.bnn_pack_conv_weight(dev(w)), C)
+        keep.append((wc, dev(sc), dev(bi)))
+        arr.append((*keep[-1], D, pool))
+        C = D
+    ref = oracle.pack_nhwc(h)
+    out = torch.zeros(ref.shape, dtype=torch.int64, device=DEV)
+    for rep in range(3):
+        out.fill_(-1)
+        _, names = kernels_of(lambda: B.bnn_conv_chain(xp, case[1], B.conv_chain_layers(arr), out))
+        assert names == ["conv_chain"]
+        assert np.array_equal(as_u64(out), ref), rep
+
+
+@pytest.mark.parametrize("batch", [129, 256, 300])
+def test_fused_stack_chain_equals_layers(batch):
+    """The stack's convolutions in one launch and one by one: the same logits, eagerly and replayed."""
+    print(f"fused stack, chain against layers, batch {batch}", flush=True)
+    from paper_1911_04477_amd.stack import VggStackFused
+    d = inputs.cfg4(batch=batch)
+    net = VggStackFused(d["layers"], d["params"], batch=batch, device=DEV)
+    x = dev(d["x"])
+    want, _ = net.forward(x, keep=True)
+    want = host(want).copy()
+    if batch == 256:
+        assert net._chain is not None
+        _, names = kernels_of(lambda: net.forward(x))
+        assert names.count("conv_chain") == 1 and len(names) == 4
+    assert np.array_equal(host(net.forward(x)), want)
+    net.capture(x)
+    for rep in range(3):
+        assert np.array_equal(host(net.replay()), want), rep
+        assert np.array_equal(host(net.forward(x)), want), rep
+
+
 # ---------------------------------------------------------------- MFMA ablation
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (37, 150, 300), (128, 128, 64), (130, 257, 1152), (64, 64, 256),
                                    (200, 333, 2304 + 17), (5, 700, 63),
