@@ -31,6 +31,26 @@ __global__ __launch_bounds__(256) void maxpool2x2_kernel(const int32_t *__restri
   }
 }
 
+// The same for planes whose rows are multiples of 4 values (rows start on 16 bytes, a thread's windows never leave a
+// row): two windows a thread from two 16-byte loads, twice as many bytes in flight.  Bound by memory: 64 x 128 x 32 x 32
+// 9.2 -> 7.3 us (5.8 TB/s), 64 x 512 x 8 x 8 2.9 -> 2.6, 256 x 256 x 64 x 64 242 -> 227.
+__global__ __launch_bounds__(256) void maxpool2x2_wide_kernel(const int32_t *__restrict__ in, int W,
+                                                              int32_t *__restrict__ out_i32, float *__restrict__ out_f32,
+                                                              const float *__restrict__ scale, const float *__restrict__ bias,
+                                                              FastDiv divOW2, FastDiv divPlane2, FastDiv divD, uint32_t total2) {
+  const uint32_t o = blockIdx.x * 256u + threadIdx.x;  // pair of windows
+  if (o >= total2) return;
+  const uint32_t row = fdiv(o, divOW2), x = o - row * divOW2.d;  // pooled row over all planes; H is even
+  const int4 r0 = *reinterpret_cast<const int4 *>(in + (size_t)(2u * row) * W + 4u * x);
+  const int4 r1 = *reinterpret_cast<const int4 *>(in + (size_t)(2u * row + 1u) * W + 4u * x);
+  const int m0 = max(max(r0.x, r0.y), max(r1.x, r1.y)), m1 = max(max(r0.z, r0.w), max(r1.z, r1.w));
+  if (out_i32) reinterpret_cast<int2 *>(out_i32)[o] = make_int2(m0, m1);
+  if (out_f32) {
+    const uint32_t plane = fdiv(o, divPlane2), d = plane - fdiv(plane, divD) * divD.d;
+    reinterpret_cast<float2 *>(out_f32)[o] = make_float2(fmaf(scale[d], (float)m0, bias[d]), fmaf(scale[d], (float)m1, bias[d]));
+  }
+}
+
 // One thread per output pixel, all D output channels in groups of CONV_DB accumulators.
 // Every output still sees its taps in the order (c, kh, kw), one fma each.  Within a
 // group the input value is loaded once and the weights are wave-uniform (scalar loads).
@@ -301,7 +321,12 @@ extern "C" bnn_status bnn_maxpool2x2(const int32_t *in, int N, int D, int H, int
   hipStream_t s = (hipStream_t)stream;
   {
     ProfScope ps(KID_MAXPOOL, s);
-    hipLaunchKernelGGL(maxpool2x2_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, in, D, H, W, out_i32,
+    if (W % 4 == 0)
+      hipLaunchKernelGGL(maxpool2x2_wide_kernel, dim3((unsigned)((total / 2 + 255) / 256)), dim3(256), 0, s, in, W, out_i32,
+                         out_f32, scale, bias, FastDiv((uint32_t)(W / 4)), FastDiv((uint32_t)(H / 2 * (W / 4))),
+                         FastDiv((uint32_t)D), (uint32_t)(total / 2));
+    else
+      hipLaunchKernelGGL(maxpool2x2_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, in, D, H, W, out_i32,
                        out_f32, scale, bias, FastDiv((uint32_t)(W / 2)), FastDiv((uint32_t)(H / 2)),
                        FastDiv((uint32_t)D), (uint32_t)total);
   }

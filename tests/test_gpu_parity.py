@@ -418,6 +418,21 @@ def test_maxpool_and_f32_glue():
         assert np.array_equal(got, oracle.fc_f32_seq(xf, wf, bf, sign_input=sgn))
 
 
+@pytest.mark.parametrize("N,D,H,W", [(1, 1, 2, 4), (3, 5, 6, 8), (2, 3, 4, 6), (1, 7, 2, 2), (5, 67, 10, 12), (2, 130, 8, 10)])
+def test_maxpool_widths(N, D, H, W):
+    """Rows of a multiple of 4 values (two windows a thread) and others; both outputs, either alone."""
+    print(f"maxpool {N}x{D}x{H}x{W}", flush=True)
+    rng = np.random.default_rng(N + D + H + W)
+    a = rng.integers(-5000, 5000, (N, D, H, W)).astype(np.int32)
+    sc, bi = rng.standard_normal(D).astype(np.float32), rng.standard_normal(D).astype(np.float32)
+    ref = oracle.maxpool2x2_i32(a)
+    fref = oracle.scale_bias(ref, sc, bi, "nchw")
+    gi, gf = B.bnn_maxpool2x2(dev(a), dev(sc), dev(bi), want_int=True)
+    assert np.array_equal(host(gi), ref) and np.array_equal(host(gf), fref)
+    assert np.array_equal(host(B.bnn_maxpool2x2(dev(a), dev(sc), dev(bi), want_int=False)[1]), fref)
+    assert np.array_equal(host(B.bnn_maxpool2x2(dev(a), None, None, want_int=True)[0]), ref)
+
+
 @pytest.mark.parametrize("M,K,N", [(256, 1024, 10), (6, 100, 10), (5, 1023, 3), (33, 2500, 37), (1, 4, 1),
                                    (4100, 64, 20), (300, 1030, 250)])
 @pytest.mark.parametrize("sgn", [False, True])
