@@ -282,14 +282,12 @@ def build_workload(name, args):
     def fn():
         B.bnn_conv2d(x, wp, shape.D, shape.kH, shape.kW, st, pd, want_int=True, workspace=ws, out_i32=out)
 
-    # the GEMM alone: the same convolution on the packed image the encode left in the workspace
-    fn()
+    # the GEMM alone: the same convolution on the packed image (for a pointwise layer of the pixels it samples)
     if shape.kH == 1:
-        img = ws[:shape.P * B.packed_words(shape.C) * 8].view(torch.int64).view(shape.N, shape.OH, shape.OW, -1)
+        img = B.bnn_im2col_packed(x, 1, 1, st, (0, 0)).view(shape.N, shape.OH, shape.OW, -1)
         gst = (1, 1)
     else:
-        img = ws[:shape.N * shape.H * shape.W * B.packed_words(shape.C) * 8].view(torch.int64).view(shape.N, shape.H,
-                                                                                                   shape.W, -1)
+        img = B.bnn_im2col_packed(x, 1, 1).view(shape.N, shape.H, shape.W, -1)
         gst = st
 
     def gemm_fn():

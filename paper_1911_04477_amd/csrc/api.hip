@@ -120,6 +120,7 @@ extern "C" const char *bnn_kernel_name(int kernel_id) {
     case bnn::KID_XNOR_GEMM_FP4: return "xnor_gemm_fp4";
     case bnn::KID_XNOR_GEMM_FP4_SPLIT: return "xnor_gemm_fp4_split";
     case bnn::KID_CONV_CHAIN: return "conv_chain";
+    case bnn::KID_CONV_POINTWISE: return "conv_pointwise";
     case bnn::KID_EXPAND_FP4: return "expand_fp4";
     case bnn::KID_CONTROL_CONV_F32: return "control_conv_f32";
     case bnn::KID_MAXPOOL: return "maxpool2x2";

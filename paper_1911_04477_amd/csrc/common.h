@@ -31,7 +31,8 @@ enum KernelId : int {
   KID_XNOR_GEMM_FP4_SPLIT = 20,
   KID_IM2COL_BAND = 21,
   KID_CONV_CHAIN = 22,
-  KID_COUNT = 23
+  KID_CONV_POINTWISE = 23,
+  KID_COUNT = 24
 };
 
 // Timing hook: records an event pair around a launch when profiling is on.
@@ -162,6 +163,15 @@ bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, i
 // The same with the reduction axis split over the waves of a workgroup, for few outputs (gemm_fp4_split.hip).
 bool fp4_split_applicable(const GemmParams &p);  // whether its rule on sizes takes the problem
 bnn_status launch_gemm_fp4_split(GemmParams &p, int bmode, int emode, hipStream_t s, int shape);
+
+// How the matrix-core kernels store int32 / fp32 maps (gemm.hip): past the caches; whether columns and strides are
+// multiples of 4, so that a lane's columns can leave together.
+bool nontemporal_maps(const GemmParams &p, int bmode);
+bool map_columns_by_four(const GemmParams &p);
+
+// Pointwise convolution from the fp32 image in one launch (conv_pointwise.hip).
+bool pointwise_applicable(const GemmParams &p);
+bnn_status launch_conv_pointwise(GemmParams &p, const float *x, hipStream_t s);
 
 // The binarization predicate: +0.0 and -0.0 -> 1, negative and NaN -> 0.
 __device__ __forceinline__ bool sign_bit(float v) { return v >= 0.0f; }

@@ -33,11 +33,10 @@ static void fill_geom(ConvGeom &g, const uint64_t *act, int N, int C, int H, int
   g.divOH = FastDiv((uint32_t)(pool ? g.OH / 2 : g.OH));
 }
 
-// GEMM over an already packed NHWC image; arguments validated by the callers.
-static bnn_status conv_from_packed(const uint64_t *act, const uint64_t *w_packed, int N, int C, int H, int W, int D,
-                                   int kH, int kW, int sH, int sW, int pH, int pW, int pool, int32_t *out_i32,
-                                   float *out_f32, uint64_t *out_packed, const float *scale, const float *bias,
-                                   hipStream_t s, const GemmTune &tune) {
+// The GEMM of a convolution over a packed NHWC image; arguments validated by the callers.
+static GemmParams conv_gemm(const uint64_t *act, const uint64_t *w_packed, int N, int C, int H, int W, int D, int kH,
+                            int kW, int sH, int sW, int pH, int pW, int pool, int32_t *out_i32,
+                            float *out_f32, uint64_t *out_packed, const float *scale, const float *bias) {
   const int64_t OH = bnn_conv_out_dim(H, kH, sH, pH), OW = bnn_conv_out_dim(W, kW, sW, pW);
   const int64_t Kw = bnn_conv_kwords(C, kH, kW);
   const int64_t cols = pool ? 4 * ((int64_t)N * (OH / 2) * (OW / 2)) : (int64_t)N * OH * OW;
@@ -65,6 +64,15 @@ static bnn_status conv_from_packed(const uint64_t *act, const uint64_t *w_packed
   fill_geom(p.g, act, N, C, H, W, kH, kW, sH, sW, pH, pW, pool);
   p.outp = out_packed;
   p.cw_out = (int)bnn_packed_words(D);
+  return p;
+}
+
+static bnn_status conv_from_packed(const uint64_t *act, const uint64_t *w_packed, int N, int C, int H, int W, int D,
+                                   int kH, int kW, int sH, int sW, int pH, int pW, int pool, int32_t *out_i32,
+                                   float *out_f32, uint64_t *out_packed, const float *scale, const float *bias,
+                                   hipStream_t s, const GemmTune &tune) {
+  GemmParams p = conv_gemm(act, w_packed, N, C, H, W, D, kH, kW, sH, sW, pH, pW, pool, out_i32, out_f32, out_packed,
+                           scale, bias);
   return run_gemm(p, 1, out_packed ? 1 : 0, s, tune);
 }
 
@@ -434,7 +442,10 @@ static bnn_status conv2d_impl(const float *x, const uint64_t *w_packed, int N, i
   hipStream_t s = (hipStream_t)stream;
   uint64_t *img = reinterpret_cast<uint64_t *>(workspace);
   if (kH == 1 && kW == 1 && pH == 0 && pW == 0) {
-    // no patch expansion: encode only the sampled pixels, then a stride-1 1x1 problem on them
+    // no patch expansion: encode and multiply only the sampled pixels
+    GemmParams p = conv_gemm(nullptr, w_packed, N, C, H, W, D, 1, 1, sH, sW, 0, 0, 0, out_i32, out_f32, nullptr, scale, bias);
+    if (tune.cfg < 0 && pointwise_applicable(p)) return launch_conv_pointwise(p, x, s);
+    // the same in two launches: a stride-1 1x1 problem on the encoded pixels
     const int OH = (int)bnn_conv_out_dim(H, 1, sH, 0), OW = (int)bnn_conv_out_dim(W, 1, sW, 0);
     st = launch_encode_nchw(x, N, C, H, W, OH, OW, sH, sW, img, s);
     if (st != BNN_OK) return st;

@@ -889,7 +889,7 @@ static bool rows_start_every(const GemmParams &p, uint32_t ints) {
 //     still fit the last-level cache of 256 MB (64 x 28 x 28 from 576 bits, 240 MB: 55.5 -> 43.1 us; 512 x 117200 x 700
 //     60.8 -> 42.0); non-temporal elsewhere (512 x 117200 x 2304 80 us, ordinary 95; 64 x 44 x 44 from 512 bits, 300 MB:
 //     20 %; small calls 1 to 5 %).
-static bool nontemporal_maps(const GemmParams &p, int bmode) {
+bool nontemporal_maps(const GemmParams &p, int bmode) {
   if (rows_start_every(p, 32) || p.M <= 32) return true;
   const int64_t words_x_m = (int64_t)p.Kw64 * (((int64_t)p.M + 63) / 64 * 64);
   const int64_t out = (int64_t)p.M * p.N * 4 * ((p.C ? 1 : 0) + (p.Y ? 1 : 0));
@@ -899,6 +899,11 @@ static bool nontemporal_maps(const GemmParams &p, int bmode) {
     return words_x_m > 36 * (int64_t)p.M || (p.M <= 56 && 2 * in >= out) ||
            (small && long_rows && rows_start_every(p, 8));
   return long_rows || small || out + in > 256000000;
+}
+
+bool map_columns_by_four(const GemmParams &p) {
+  return (p.N & 3) == 0 && (!p.C || (p.ldc & 3) == 0) && (!p.Y || (p.ldy & 3) == 0) &&
+         (p.img_stride == 0 || ((p.OHW & 3u) == 0 && (p.img_stride & 3) == 0));
 }
 
 bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const GemmTune &tune) {
@@ -932,10 +937,7 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
   }
   if (!valu) {
     // The matrix cores; few outputs split the reduction axis, and so do rows too long for exact fp32 sums.
-    p.colperm = (emode == 0 && (p.N & 3) == 0 && (!p.C || (p.ldc & 3) == 0) && (!p.Y || (p.ldy & 3) == 0) &&
-                 (p.img_stride == 0 || ((p.OHW & 3u) == 0 && (p.img_stride & 3) == 0)))
-                    ? 1
-                    : 0;
+    p.colperm = emode == 0 && map_columns_by_four(p) ? 1 : 0;
     p.nt_store = emode == 0 && nontemporal_maps(p, bmode) ? 1 : 0;
     if (cfg >= 25) return launch_gemm_fp4_split(p, bmode, emode, s, cfg - 25);
     if (cfg < 0 && (fp4_split_applicable(p) || !fp4_applicable(p))) return launch_gemm_fp4_split(p, bmode, emode, s, -1);

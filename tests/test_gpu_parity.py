@@ -234,6 +234,42 @@ def test_conv2d_pointwise_short_rows(case, cfg):
     assert np.array_equal(host(of), oracle.scale_bias(ref, d["scale"], d["bias"], "nchw"))
 
 
+POINTWISE_CASES = [  # N, C, H, W, D, stride, one launch
+    ((1, 1, 1, 1, 1, 1), True), ((1, 7, 3, 5, 33, 1), True),          # a partial granule, a partial row tile
+    ((3, 200, 12, 12, 70, 2), True), ((3, 200, 11, 9, 70, 2), True),  # 36 and 30 pixels an image: columns by four or one by one
+    ((2, 64, 8, 8, 128, 1), True), ((2, 65, 8, 8, 129, 1), True),     # edges of the word and of the narrow row tile
+    ((5, 256, 7, 7, 300, 1), True), ((1, 257, 9, 8, 513, 1), True),   # one chunk of the reduction and one value more
+    ((2, 500, 6, 10, 256, 1), True), ((4, 1000, 4, 4, 40, 1), True),
+    ((84, 5, 28, 28, 9, 1), True), ((84, 64, 28, 28, 70, 1), True),   # two pixel groups per workgroup
+    ((83, 33, 29, 28, 65, 1), True),
+    ((1, 1024, 4, 4, 12, 1), False), ((1, 2049, 3, 3, 12, 1), False),
+    ((120, 33, 56, 56, 66, 1), False),                                # 150 MB, few channels into twice as many
+]
+
+
+@pytest.mark.parametrize("case,one", POINTWISE_CASES)
+def test_conv2d_pointwise_one_launch(case, one):
+    """Pointwise layers from the fp32 image: encode and multiplication in one launch, or in two by the rule; both maps and
+    each alone, specials among the inputs, against the oracle (large maps: against the two-launch route)."""
+    print(f"conv2d pointwise case={case}", flush=True)
+    N, C, H, W, D, s = case
+    shape = inputs.ConvShape(N, C, H, W, D, 1, 1, s, s, 0, 0)
+    d = inputs.conv_inputs(shape, seed=sum(case) + 5)
+    x = inputs.inject_specials(d["x"], 4, frac=0.01)
+    wp, xd, sc, bi = B.bnn_pack_conv_weight(dev(d["w"])), dev(x), dev(d["scale"]), dev(d["bias"])
+    run = lambda **kw: B.bnn_conv2d(xd, wp, D, 1, 1, (s, s), (0, 0), **kw)
+    (oi, of), names = kernels_of(lambda: run(scale=sc, bias=bi))
+    assert (names == ["conv_pointwise"]) == one, names
+    if one:
+        ref = oracle.conv2d_pm1(x, d["w"], (s, s), (0, 0))
+    else:
+        ref = host(run(cfg=24)[0])
+    assert np.array_equal(host(oi), ref)
+    assert np.array_equal(host(of), oracle.scale_bias(ref, d["scale"], d["bias"], "nchw"))
+    assert np.array_equal(host(run()[0]), ref)
+    assert np.array_equal(host(run(scale=sc, bias=bi, want_int=False)[1]), host(of))
+
+
 def test_gemm_table1_truth_table():
     """Table 1 of the paper through encode + GEMM with K = 1 (63 masked tail bits)."""
     print("gemm truth table", flush=True)
