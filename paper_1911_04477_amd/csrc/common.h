@@ -151,9 +151,10 @@ int device_cu_count();
 // emode 0: int32 / fp32 store; 1: packed sign(fma(scale, acc, bias)) store, optional 2x2 pool.
 bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const GemmTune &tune = GemmTune());
 
-// Short-row GEMM (gemm_lowk.hip): rows of two or four words, explicit B, 16-byte stores.
+// Short-row GEMM (gemm_lowk.hip): rows of at most four words, explicit B, maps; form: see there, -1: its rule's.
 bool lowk_applicable(const GemmParams &p);
-bnn_status launch_lowk(GemmParams &p, int groups, hipStream_t s);
+bool lowk_faster(const GemmParams &p);  // its rule against the other matrix-core kernels
+bnn_status launch_lowk(GemmParams &p, int form, hipStream_t s);
 
 // Matrix-core GEMM on packed operands (gemm_fp4.hip): bmode / emode as for run_gemm; shape: tile number or -1;
 // region: convolutions may keep a tile's input region in LDS (false: always the general gather).
@@ -168,6 +169,7 @@ bnn_status launch_gemm_fp4_split(GemmParams &p, int bmode, int emode, hipStream_
 // multiples of 4, so that a lane's columns can leave together.
 bool nontemporal_maps(const GemmParams &p, int bmode);
 bool map_columns_by_four(const GemmParams &p);
+bool map_rows_start_every(const GemmParams &p, uint32_t ints);  // multiples of `ints` 4-byte elements
 
 // Pointwise convolution from the fp32 image in one launch (conv_pointwise.hip).
 bool pointwise_applicable(const GemmParams &p);

@@ -181,8 +181,8 @@ enum : int { MS_NT = 0, MS_VEC = 1, MS_ONE = 2 };
 // Rows past M and columns past N hold the values of row M - 1 and column N - 1 once more (the staging clamps them), and
 // go to that place: nothing is predicated but whole groups of 8 rows.  (A branch per row and column instead, in code
 // that few waves run: 701 x 2113 x 1220 9.7 us, this way 6.4; 701 x 2112 x 1220 7.2, 6.1.)
-template <int WTM, int WTN, int AFF, int MS, bool FULL>
-__device__ __forceinline__ void store_map(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n, int half,
+template <int WTM, int WTN, int AFF, int MS, bool FULL, class P>
+__device__ __forceinline__ void store_map(const P &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n, int half,
                                           const float *sSc, const float *sBi, const int64_t (&off)[WTN]) {
   typedef int vi __attribute__((ext_vector_type(WTN)));
   constexpr int STEP = MS == MS_ONE ? 32 : 1;  // columns between a lane's
@@ -233,16 +233,17 @@ __device__ __forceinline__ void store_map(const GemmParams &p, const Fp4Acc<WTM,
     }
 }
 
-template <int WTM, int WTN, int AFF, int MS>
-__device__ __forceinline__ void store_map_by(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n, int half,
+template <int WTM, int WTN, int AFF, int MS, class P>
+__device__ __forceinline__ void store_map_by(const P &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n, int half,
                                              const float *sSc, const float *sBi, const int64_t (&off)[WTN]) {
   if (m0 + 32 * WTM <= p.M) store_map<WTM, WTN, AFF, MS, true>(p, acc, m0, n, half, sSc, sBi, off);
   else store_map<WTM, WTN, AFF, MS, false>(p, acc, m0, n, half, sSc, sBi, off);
 }
 
-// int32 and / or fp32 output of a wave's tile: rows m0.., columns n0.. (row-major, or NCHW planes).
-template <int WTM, int WTN, int MS>
-__device__ __forceinline__ void store_maps(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n0, int lane,
+// int32 and / or fp32 output of a wave's tile: rows m0.., columns n0.. (row-major, or NCHW planes).  P: the kernel's
+// arguments, of which these are read: C, Y, ldc, ldy, M, N, scale, bias, axis, img_stride, OHW, divOHW.
+template <int WTM, int WTN, int MS, class P>
+__device__ __forceinline__ void store_maps(const P &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n0, int lane,
                                            const float *sSc, const float *sBi) {
   constexpr int STEP = MS == MS_ONE ? 32 : 1;
   const int half = lane >> 5;

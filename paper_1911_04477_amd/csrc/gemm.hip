@@ -863,7 +863,7 @@ int device_cu_count() {
 }
 
 // Whether every row of the maps (every plane, for NCHW maps) starts at a multiple of `ints` 4-byte elements.
-static bool rows_start_every(const GemmParams &p, uint32_t ints) {
+bool map_rows_start_every(const GemmParams &p, uint32_t ints) {
   const bool planes = p.img_stride != 0;
   auto ok = [&](const void *base, int64_t ld) {
     return !base || (((uintptr_t)base & (4 * ints - 1)) == 0 && (planes ? p.OHW % ints == 0 : ld % ints == 0));
@@ -890,14 +890,14 @@ static bool rows_start_every(const GemmParams &p, uint32_t ints) {
 //     60.8 -> 42.0); non-temporal elsewhere (512 x 117200 x 2304 80 us, ordinary 95; 64 x 44 x 44 from 512 bits, 300 MB:
 //     20 %; small calls 1 to 5 %).
 bool nontemporal_maps(const GemmParams &p, int bmode) {
-  if (rows_start_every(p, 32) || p.M <= 32) return true;
+  if (map_rows_start_every(p, 32) || p.M <= 32) return true;
   const int64_t words_x_m = (int64_t)p.Kw64 * (((int64_t)p.M + 63) / 64 * 64);
   const int64_t out = (int64_t)p.M * p.N * 4 * ((p.C ? 1 : 0) + (p.Y ? 1 : 0));
   const int64_t in = bmode == 0 ? (int64_t)p.N * p.Kw64 * 8 : (int64_t)p.g.Nimg * p.g.H * p.g.W * p.g.Cw * 8;
   const bool small = out + in <= 50000000, long_rows = words_x_m >= 12 * (int64_t)p.M;
-  if (!rows_start_every(p, 16))
+  if (!map_rows_start_every(p, 16))
     return words_x_m > 36 * (int64_t)p.M || (p.M <= 56 && 2 * in >= out) ||
-           (small && long_rows && rows_start_every(p, 8));
+           (small && long_rows && map_rows_start_every(p, 8));
   return long_rows || small || out + in > 256000000;
 }
 
@@ -909,7 +909,7 @@ bool map_columns_by_four(const GemmParams &p) {
 bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const GemmTune &tune) {
   int cfg = tune.cfg;
   p.n_cu = device_cu_count();
-  p.nt_store = rows_start_every(p, 32) ? 1 : 0;
+  p.nt_store = map_rows_start_every(p, 32) ? 1 : 0;
   if (bmode == 1 && emode == 0 && p.g.pool == 0 && p.g.kH == 1 && p.g.kW == 1 && p.g.sH == 1 && p.g.sW == 1 &&
       p.g.pH == 0 && p.g.pW == 0) {
     // a stride-1 pointwise convolution over a packed image has nothing to gather: its patch
@@ -922,19 +922,10 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
   // a forced value this call cannot use selects the heuristic
   const bool valu = emode == 0 ? (cfg >= 1 && cfg <= 6 && cfg != 5)
                                : (cfg == 3 || cfg == 1 || (!p.g.pool && (cfg == 6 || cfg == 4)));
-  const bool short_rows = bmode == 0 && emode == 0 && lowk_applicable(p) && ((int64_t)p.M + 31) / 32 <= 65535;
+  const bool short_rows = bmode == 0 && emode == 0 && lowk_applicable(p);
   const bool matrix = (cfg >= 21 && cfg <= 24 && fp4_applicable(p)) || (cfg >= 25 && cfg <= 28);
-  if (!valu && !matrix && !(short_rows && cfg >= 10 && cfg <= 12)) cfg = -1;
-  if (short_rows && (cfg < 0 || (cfg >= 10 && cfg <= 12))) {
-    // rows of two or four words: bound by the store, see gemm_lowk.hip.  As many rows per wave
-    // (32, 16 or 8) as still leave every compute unit a workgroup.
-    const int64_t ctiles = ((int64_t)p.N + 255) / 256;
-    const int groups = cfg == 12 ? 4 : cfg == 11 ? 2 : cfg == 10 ? 1
-                       : (ctiles * (((int64_t)p.M + 127) / 128) >= (int64_t)p.n_cu  ? 4
-                          : ctiles * (((int64_t)p.M + 63) / 64) >= (int64_t)p.n_cu ? 2
-                                                                                    : 1);
-    return launch_lowk(p, groups, s);
-  }
+  if (!valu && !matrix && !(short_rows && cfg >= 10 && cfg <= 17)) cfg = -1;
+  if (short_rows && (cfg < 0 ? lowk_faster(p) : cfg >= 10 && cfg <= 17)) return launch_lowk(p, cfg < 0 ? -1 : cfg - 10, s);
   if (!valu) {
     // The matrix cores; few outputs split the reduction axis, and so do rows too long for exact fp32 sums.
     p.colperm = emode == 0 && map_columns_by_four(p) ? 1 : 0;

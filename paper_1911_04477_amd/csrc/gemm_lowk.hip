@@ -1,217 +1,202 @@
-// Xnor-Bitcount GEMM (section 3.2) for short reduction axes: rows of two or four 64-bit words
-// (K <= 256), an explicit K-contiguous B, int32 / fp32 output.
+// Xnor-Bitcount GEMM (section 3.2) for short reduction axes on the matrix cores: explicit rows of at most four 64-bit
+// words (K <= 256), int32 / fp32 output.
 //
-// At such K the arithmetic is a few hundred instructions per wave and the problem is bound by
-// writing the int32 / fp32 result (4 bytes out per 2 * ceil(K/32) lane-operations): what matters
-// is the shape of the memory traffic, not the inner loop.
-//   * a lane owns FOUR CONSECUTIVE columns, so every store is 16 bytes per lane and a wave store
-//     covers 1 KB of one output row (the LDS-staged kernel, built for long rows, stores 256 B);
-//   * columns that share a lane must share an image of the NCHW output: the host uses this
-//     kernel only when the columns per image (and the leading dimensions) are multiples of 4,
-//     which also makes every 16-byte store aligned;
-//   * the whole of B a lane needs (4 rows x at most 32 bytes) is requested up front with
-//     8- or 16-byte loads, no LDS, no barrier; A comes in through scalar loads, 8 rows at a
-//     time, exactly as in the long-row kernel, and enters v_xor as the scalar operand;
-//   * a wave computes and stores ROWS rows (one, two or four groups of 8) for its 256 columns, a
-//     workgroup of four waves 4 * ROWS rows; the grid is (column tiles, row tiles);
-//   * the arithmetic (a third of the store time at K = 200) only overlaps the stores if the waves
-//     of a SIMD do not advance in step: workgroups get different wave priorities, and the row
-//     statements carry the one-cycle yield after each pair.
-// Measured on the 51.4 MB int32 output of the 1x1 / K = 200 convolution: 12.9 us (4.0 TB/s; a
-// plain fill of the same buffer 9.1 us; the long-row kernel 17.9 us).
+// One chunk of 256 bits is the whole reduction, so there is nothing to stage or to pipeline: a wave reads the rows of its
+// columns once, expands them once (the operands of all four steps stay in registers), and then walks over blocks of
+// rows: one load of 16 bytes per row, four expansions, the products, and the store of the block.  No LDS but for the
+// affine constants, no barrier, and 150 bytes of arguments (the host copies them for every launch).
+// Bound by the launch for small calls and by the store of the result for large ones.
+#include <algorithm>
+
 #include "common.h"
-#include "gemm_rows.inc"
+#include "fp4_tile.h"
 
 namespace bnn {
 
-using u32x4 = uint32_t __attribute__((ext_vector_type(4)));
-using u32x8 = uint32_t __attribute__((ext_vector_type(8)));
-using i32x4 = int32_t __attribute__((ext_vector_type(4)));
-using f32x4 = float __attribute__((ext_vector_type(4)));
+struct ShortParams {
+  const char *A, *B;
+  int64_t lda, ldb;  // bytes
+  int M, N, Kbits, Kformula, words;
+  int rounds;        // blocks of rows that a wave walks over
+  int abreast;       // the four waves of a workgroup stand side by side, not one above the other
+  int runs;          // an XCD gets a contiguous run of workgroups
+  int axis;
+  int32_t *C;
+  float *Y;
+  int64_t ldc, ldy, img_stride;
+  const float *scale, *bias;
+  uint32_t OHW;
+  FastDiv divOHW, divTilesN;
+};
 
-template <int GROUPS, int HALF>  // GROUPS row groups of 8 per wave; HALF = 1: rows of two words (4 dwords)
-__global__ __launch_bounds__(256) void xnor_gemm_lowk_kernel(GemmParams p) {
-  const int lane = threadIdx.x & 63;
+template <int WTM, int WTN, int MS, bool V16>
+__global__ __launch_bounds__(256, 3) void xnor_gemm_lowk_kernel(ShortParams p) {
+  constexpr int BM = 32 * WTM, BN = 32 * WTN;  // rows and columns of a wave's block
+  __shared__ __attribute__((aligned(16))) float sSc[4][BM], sBi[4][BM];
+  const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int n = ((int)blockIdx.x * 64 + lane) * 4;  // first of this lane's four columns
-  const int m_first = ((int)blockIdx.y * 4 + wave) * (8 * GROUPS);
-  if (m_first >= p.M) return;  // wave-uniform; the kernel has no barrier
-  const bool col_ok = n < p.N;  // N is a multiple of 4: all four columns or none
-  const int nc = col_ok ? n : 0;
+  uint32_t bid = blockIdx.x;
+  if (p.runs) {
+    const uint32_t per = gridDim.x >> 3, r = gridDim.x & 7u, xcd = bid & 7u, i = bid >> 3;
+    bid = xcd * per + min(xcd, r) + i;
+  }
+  const uint32_t mi = fdiv_sel(bid, p.divTilesN);
+  const uint32_t ni = bid - mi * p.divTilesN.d;
+  const int n0 = (int)(p.abreast ? 4 * ni + wave : ni) * BN;
+  const int mstep = p.abreast ? BM : 4 * BM;
+  int m0 = (int)mi * p.rounds * mstep + (p.abreast ? 0 : wave * BM);
+  if (m0 >= p.M || n0 >= p.N) return;  // wave-uniform; the kernel has no barrier
 
-  // ---- B: this lane's four rows, bits past K masked, words past the row zero -------------------
-  constexpr int KD = HALF ? 4 : 8;
-  const int tail_bits = p.Kbits & 63;
-  const uint64_t tail_mask = tail_bits ? ((1ull << tail_bits) - 1ull) : ~0ull;
-  const uint32_t tm_lo = (uint32_t)tail_mask, tm_hi = (uint32_t)(tail_mask >> 32);
-  uint32_t b[4][KD];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const uint64_t *src = p.B + (int64_t)(nc + j) * p.ldb;
-    if (p.b_vec16) {
-#pragma unroll
-      for (int q = 0; q < KD / 4; ++q) {
-        const u32x4 v = *reinterpret_cast<const u32x4 *>(src + 2 * q);
-        b[j][4 * q] = v.x; b[j][4 * q + 1] = v.y; b[j][4 * q + 2] = v.z; b[j][4 * q + 3] = v.w;
-      }
+  // this half's two words of a row; past the row's end whatever is there, masked
+  const int w0 = V16 ? min(2 * half, p.words - 2) : min(2 * half, p.words - 1), w1 = min(2 * half + 1, p.words - 1);
+  auto load = [&](const char *row) {
+    u32x4 v;
+    if constexpr (V16) {
+      v = *reinterpret_cast<const u32x4 *>(row + w0 * 8);
     } else {
-#pragma unroll
-      for (int w = 0; w < KD / 2; ++w) {
-        const uint2 v = *reinterpret_cast<const uint2 *>(src + w);
-        b[j][2 * w] = v.x; b[j][2 * w + 1] = v.y;
-      }
+      v.lo = *reinterpret_cast<const u32x2 *>(row + w0 * 8);
+      v.hi = *reinterpret_cast<const u32x2 *>(row + w1 * 8);
     }
-    b[j][KD - 2] &= tm_lo;
-    b[j][KD - 1] &= tm_hi;
+    return v;
+  };
+  u32x4 mask;  // bits past K become 0 in both operands: +1 * +1, subtracted by the starting value
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const int left = p.Kbits - 32 * (4 * half + d);
+    mask[d] = left >= 32 ? ~0u : (left <= 0 ? 0u : (1u << left) - 1u);
   }
-
-  // ---- output addressing ---------------------------------------------------------------------------
-  // column -> (image, pixel): row-major C is the one-image case (img_stride == 0)
-  uint32_t img = 0, pix = (uint32_t)nc;
-  if (p.img_stride != 0) {
-    img = fdiv((uint32_t)nc, p.divOHW);
-    pix = (uint32_t)nc - img * p.OHW;
+  u32x4 a[WTM], b[WTN];
+#pragma unroll
+  for (int j = 0; j < WTN; ++j) {
+    const int n = min(n0 + (MS == MS_ONE ? 32 * j + l32 : WTN * l32 + j), p.N - 1);
+    b[j] = load(p.B + (size_t)n * (size_t)p.ldb);
   }
-  const int64_t col_off = (int64_t)img * p.img_stride + pix;
-  f32x4 csc = {1.f, 1.f, 1.f, 1.f}, cbi = {0.f, 0.f, 0.f, 0.f};
-  if (p.Y && p.axis == BNN_CH_COL) {
+  auto load_rows = [&](int m) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {  // scale / bias carry no alignment requirement
-      csc[j] = p.scale[nc + j];
-      cbi[j] = p.bias[nc + j];
+    for (int i = 0; i < WTM; ++i) a[i] = load(p.A + (size_t)min(m + 32 * i + l32, p.M - 1) * (size_t)p.lda);
+  };
+  load_rows(m0);
+  const bool affine = p.Y && p.axis == BNN_CH_ROW;  // uniform
+  v8i eb[4][WTN];
+#pragma unroll
+  for (int j = 0; j < WTN; ++j) b[j] &= mask;
+#pragma unroll
+  for (int d = 0; d < 4; ++d)
+#pragma unroll
+    for (int j = 0; j < WTN; ++j) eb[d][j] = expand_e2m1<true>(b[j][d]);
+  const float start = -(float)(256 - p.Kformula);
+  for (int r = 0;;) {
+    if (affine && lane < BM) {  // the wave's own rows: LDS keeps a wave's order
+      sSc[wave][lane] = p.scale[min(m0 + lane, p.M - 1)];
+      sBi[wave][lane] = p.bias[min(m0 + lane, p.M - 1)];
     }
-  }
-
-  const uint32_t Abase_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)p.A);
-  const uint32_t Abase_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uintptr_t)p.A >> 32));
-  const uint64_t Abase = ((uint64_t)Abase_hi << 32) | (uint64_t)Abase_lo;
-  const uint32_t arow_bytes = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)p.lda32 * 4u));
-  const uint32_t aoff_max = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(p.M - 1) * (uint32_t)p.lda32 * 4u));
-
-  // Waves that share a SIMD would otherwise advance in step and all reach their stores together,
-  // after the arithmetic of all of them; with different priorities they finish one after the
-  // other and the stores of the first overlap the arithmetic of the rest.
-  {
-    const int pr = (int)((blockIdx.x + blockIdx.y) & 3u);
-    if (pr == 1) __builtin_amdgcn_s_setprio(1);
-    else if (pr == 2) __builtin_amdgcn_s_setprio(2);
-    else if (pr == 3) __builtin_amdgcn_s_setprio(3);
-  }
+    Fp4Acc<WTM, WTN> acc;
+    acc.init(start);
+    u32x4 x[WTM];
 #pragma unroll
-  for (int g = 0; g < GROUPS; ++g) {
-    const int m0 = m_first + 8 * g;
-    if (m0 >= p.M) break;  // wave-uniform
-    // rows past M re-read row M - 1 and are not stored
-    const uint32_t aoff0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)m0 * (uint32_t)p.lda32 * 4u));
-    int acc[8][4];
+    for (int i = 0; i < WTM; ++i) x[i] = a[i] & mask;
+    const int next = m0 + mstep;
+    const bool more = ++r < p.rounds && next < p.M;  // wave-uniform
+    if (more) load_rows(next);
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int d = 0; d < 4; ++d) {
+      v8i ea[WTM];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = 0;
-    uint32_t t0, t1;
-#define BNN_BV(j, d) b[j][d]
-    if constexpr (HALF) {
-      u32x4 a[8];
+      for (int i = 0; i < WTM; ++i) ea[i] = expand_e2m1<true>(x[i][d]);
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-        asm volatile("s_load_dwordx4 %0, %1, %2" : "=s"(a[i]) : "s"(Abase), "s"(min(aoff0 + (uint32_t)i * arow_bytes, aoff_max)));
-      asm volatile("s_waitcnt lgkmcnt(0)"
-                   : "+s"(a[0]), "+s"(a[1]), "+s"(a[2]), "+s"(a[3]), "+s"(a[4]), "+s"(a[5]), "+s"(a[6]), "+s"(a[7]));
+      for (int i = 0; i < WTM; ++i)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        a[i][2] &= tm_lo;
-        a[i][3] &= tm_hi;
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) BNN_GEMM_HALF_4(acc[i], a[i], BNN_BV, t0, t1);
-    } else {
-      u32x8 a[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        asm volatile("s_load_dwordx8 %0, %1, %2" : "=s"(a[i]) : "s"(Abase), "s"(min(aoff0 + (uint32_t)i * arow_bytes, aoff_max)));
-      asm volatile("s_waitcnt lgkmcnt(0)"
-                   : "+s"(a[0]), "+s"(a[1]), "+s"(a[2]), "+s"(a[3]), "+s"(a[4]), "+s"(a[5]), "+s"(a[6]), "+s"(a[7]));
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        a[i][6] &= tm_lo;
-        a[i][7] &= tm_hi;
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) BNN_GEMM_ROW_4(acc[i], a[i], BNN_BV, t0, t1);
+        for (int j = 0; j < WTN; ++j) acc.v[i][j] = mfma_e2m1(ea[i], eb[d][j], acc.v[i][j]);
     }
-#undef BNN_BV
-    // per-row affine constants of this group: wave-uniform scalar loads, requested together
-    float scr[8], bir[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      scr[i] = 1.0f;
-      bir[i] = 0.0f;
-    }
-    if (p.Y && p.axis == BNN_CH_ROW) {
-      typedef const float __attribute__((address_space(4))) *cf32_ptr;
-      const cf32_ptr cscale = (cf32_ptr)(uintptr_t)p.scale, cbias = (cf32_ptr)(uintptr_t)p.bias;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int mc = min(m0 + i, p.M - 1);
-        scr[i] = cscale[mc];
-        bir[i] = cbias[mc];
-      }
-    }
-    if (!col_ok) continue;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int m = m0 + i;
-      if (m >= p.M) break;  // wave-uniform
-      i32x4 v;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = p.Kformula - 2 * acc[i][j];
-      if (p.C) __builtin_nontemporal_store(v, reinterpret_cast<i32x4 *>(p.C + col_off + (int64_t)m * p.ldc));
-      if (p.Y) {
-        f32x4 y;
-        if (p.axis == BNN_CH_ROW) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) y[j] = fmaf(scr[i], (float)v[j], bir[i]);
-        } else {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) y[j] = fmaf(csc[j], (float)v[j], cbi[j]);
-        }
-        __builtin_nontemporal_store(y, reinterpret_cast<f32x4 *>(p.Y + col_off + (int64_t)m * p.ldy));
-      }
-    }
+    store_maps<WTM, WTN, MS>(p, acc, m0, n0, lane, sSc[wave], sBi[wave]);
+    if (!more) break;
+    m0 = next;
   }
 }
 
 // Whether the short-row kernel can run the problem described by p (explicit B).
-bool lowk_applicable(const GemmParams &p) {
-  if (p.Kw64 != 2 && p.Kw64 != 4) return false;
-  if (p.Kbits > p.Kw64 * 64 || p.Kbits <= (p.Kw64 - 1) * 64) return false;
-  if ((p.N & 3) != 0) return false;
-  if (p.lda32 < 2 * p.Kw64 || p.ldb < p.Kw64) return false;
-  if (p.C && (p.ldc & 3)) return false;
-  if (p.Y && (p.ldy & 3)) return false;
-  if (p.img_stride != 0 && ((p.OHW & 3u) != 0 || (p.img_stride & 3) != 0)) return false;
-  return true;
+bool lowk_applicable(const GemmParams &p) { return p.Kw64 <= 4; }
+
+// What a launch looks like: F_64 blocks of 64 x 64 instead of 32 x 32; F_ABREAST a workgroup's waves side by side instead of
+// one above the other; F_RUNS contiguous runs of workgroups on an XCD.  -1: another kernel is at least as fast.
+// Measured over 27 sizes in every form, rows of one and four words, and 300 random sizes against the vector-ALU
+// kernel that took rows of two and four words before (16-byte stores, 32 rows per wave) and the other matrix-core
+// kernels (us; "before"):
+//   rows that start at whole or half lines: side by side, a workgroup writes 512 or 1024 bytes of a row together.  64 x 64
+//     blocks up to 150 MB (256 x 50176 x 250 14.4 -> 11.7, 4096 x 8192 x 250 30.7 -> 24.3, 600 x 30000 x 250 20.5 -> 15.8),
+//     32 x 32 from there on for whole lines, and beyond the last-level cache for both (256 x 200704 x 250 46.6 -> 36.7;
+//     4096 x 30000 x 250 107 -> 88; 800 x 120016 x 250 84 -> 66; but 2801 x 18768, 210 MB, half lines 40.8 against 36.8);
+//     with up to 64 rows from 80 MB on (64 x 400000 x 250 25.0 -> 20.0, 64 x 64 blocks 21.3);
+//   rows that start elsewhere: side by side and in runs, neighbours share lines (130 x 60004 x 240 15.2 -> 11.0, 700 x 30004 x
+//     240 30.4 -> 18.2, 3000 x 8004 x 240 31.2 -> 18.9, 2856 x 25828 x 240 94 -> 54; without runs 11.6, 19.1, 21.3, 57);
+//     staged tiles where the second row of blocks would be half empty (83 x 31124 x 98 5.9 against 6.8) and for rows of one
+//     and three words, which had them before (642 x 39884 x 170 20.9 against 22.3; others equal);
+//   columns that are no multiple of 4: the staged tiles and the split kernel are equal or faster (256 x 50177 x 50 13.5
+//     against 14.2), except beyond the cache, one above the other in runs (4096 x 30001 x 250 161 -> 95);
+//   small calls: 32 x 32 blocks up to two of 64 x 64 per unit (64 x 64 x 256 4.6 -> 3.0, 256 x 1000 x 200 5.3 -> 3.3); rows of
+//     one and three words have the split kernel up to 300 of them, equal within 5 % either way.
+enum : int { F_64 = 1, F_ABREAST = 2, F_RUNS = 4 };
+static int lowk_rule(const GemmParams &p) {
+  const int64_t t64 = (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 63) / 64), cu = p.n_cu;
+  const int64_t out = (int64_t)p.M * p.N * 4 * ((p.C ? 1 : 0) + (p.Y ? 1 : 0));
+  const bool beyond = out > 256000000, odd_words = p.Kw64 % 2 != 0;
+  if (!map_columns_by_four(p)) return beyond ? F_RUNS : -1;
+  if (odd_words && t64 < 300) return -1;
+  if (t64 <= 2 * cu) return p.N >= p.M ? F_ABREAST : 0;
+  if (!map_rows_start_every(p, 16)) return odd_words || (p.M > 64 && p.M <= 96) ? -1 : F_RUNS | F_ABREAST | F_64;
+  if (beyond) return F_ABREAST;
+  return map_rows_start_every(p, 32) && out >= (p.M > 64 ? 150000000 : 80000000) ? F_ABREAST : F_ABREAST | F_64;
 }
 
-bnn_status launch_lowk(GemmParams &p, int groups, hipStream_t s) {
-  const int64_t tilesN = ((int64_t)p.N + 255) / 256;
-  const int64_t tilesM = ((int64_t)p.M + 32 * groups - 1) / (32 * groups);
-  if (tilesN > 0x7fffffffLL || tilesM > 65535) return BNN_ERR_UNSUPPORTED;
-  p.tilesM = (int)tilesM;
-  p.tilesN = (int)tilesN;
-  ProfScope ps(KID_XNOR_GEMM_LOWK, s);
-  const dim3 grid((unsigned)tilesN, (unsigned)tilesM), block(256);
-  const bool half = p.Kw64 == 2;
-  if (groups == 4) {
-    if (half) hipLaunchKernelGGL((xnor_gemm_lowk_kernel<4, 1>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((xnor_gemm_lowk_kernel<4, 0>), grid, block, 0, s, p);
-  } else if (groups == 2) {
-    if (half) hipLaunchKernelGGL((xnor_gemm_lowk_kernel<2, 1>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((xnor_gemm_lowk_kernel<2, 0>), grid, block, 0, s, p);
-  } else {
-    if (half) hipLaunchKernelGGL((xnor_gemm_lowk_kernel<1, 1>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((xnor_gemm_lowk_kernel<1, 0>), grid, block, 0, s, p);
+bool lowk_faster(const GemmParams &p) { return lowk_rule(p) >= 0; }
+
+template <int WTM, int WTN, bool V16>
+static void launch_forms(const ShortParams &q, const GemmParams &p, dim3 grid, hipStream_t s) {
+  const dim3 block(256);
+  if (!p.colperm && WTN > 1) hipLaunchKernelGGL((xnor_gemm_lowk_kernel<WTM, WTN, MS_ONE, V16>), grid, block, 0, s, q);
+  else if (p.nt_store) hipLaunchKernelGGL((xnor_gemm_lowk_kernel<WTM, WTN, MS_NT, V16>), grid, block, 0, s, q);
+  else hipLaunchKernelGGL((xnor_gemm_lowk_kernel<WTM, WTN, MS_VEC, V16>), grid, block, 0, s, q);
+}
+
+// form: as of lowk_rule; -1: the rule's.
+bnn_status launch_lowk(GemmParams &p, int form, hipStream_t s) {
+  p.colperm = map_columns_by_four(p) ? 1 : 0;
+  p.nt_store = nontemporal_maps(p, 0) ? 1 : 0;
+  if (form < 0) form = std::max(lowk_rule(p), 0);
+  ShortParams q;
+  q.A = reinterpret_cast<const char *>(p.A);
+  q.B = reinterpret_cast<const char *>(p.B);
+  q.lda = p.lda32 * 4;
+  q.ldb = p.ldb * 8;
+  q.M = p.M; q.N = p.N; q.Kbits = p.Kbits; q.Kformula = p.Kformula; q.words = p.Kw64;
+  q.axis = p.axis;
+  q.C = p.C; q.Y = p.Y; q.ldc = p.ldc; q.ldy = p.ldy; q.img_stride = p.img_stride;
+  q.scale = p.scale; q.bias = p.bias;
+  q.OHW = p.OHW; q.divOHW = p.divOHW;
+  // a launch is limited to 2^32 threads: the widest workgroups for more columns than that, several rounds for more rows
+  constexpr int64_t MAX_BLOCKS = 0xffffff;
+  int64_t tilesM, tilesN;
+  auto tiles = [&]() {
+    const int b32 = form & F_64 ? 64 : 32, bn = form & F_ABREAST ? 4 * b32 : b32, bm = form & F_ABREAST ? b32 : 4 * b32;
+    tilesN = ((int64_t)p.N + bn - 1) / bn;
+    tilesM = ((int64_t)p.M + bm - 1) / bm;
+    return tilesM * tilesN;
+  };
+  if (tiles() > MAX_BLOCKS) {
+    form |= F_64 | F_ABREAST;
+    tiles();
   }
+  q.rounds = (int)((tilesM * tilesN + MAX_BLOCKS - 1) / MAX_BLOCKS);
+  tilesM = (tilesM + q.rounds - 1) / q.rounds;
+  if (tilesM * tilesN > MAX_BLOCKS) return BNN_ERR_UNSUPPORTED;
+  q.abreast = form & F_ABREAST ? 1 : 0;
+  q.runs = form & F_RUNS ? 1 : 0;
+  q.divTilesN = FastDiv((uint32_t)tilesN);
+  const bool v16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0 && p.ldb % 2 == 0;
+  const dim3 grid((unsigned)(tilesM * tilesN));
+  ProfScope ps(KID_XNOR_GEMM_LOWK, s);
+  if (!(form & F_64)) v16 ? launch_forms<1, 1, true>(q, p, grid, s) : launch_forms<1, 1, false>(q, p, grid, s);
+  else v16 ? launch_forms<2, 2, true>(q, p, grid, s) : launch_forms<2, 2, false>(q, p, grid, s);
   return launch_status();
 }
 
