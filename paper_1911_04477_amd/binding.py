@@ -86,6 +86,31 @@ CH_NONE, CH_ROW, CH_COL = 0, 1, 2
 _lib: Optional[ctypes.CDLL] = None
 
 
+class _Calls:
+    """The functions of SIGNATURES and TESTING_SIGNATURES whose arguments are integers and raw pointers, called without
+    ctypes' conversions (csrc/fastcall.c)."""
+
+    _KINDS = {_p: "p", _i64: "q", _i32: "i", _sz: "z"}
+
+    def __init__(self, L: ctypes.CDLL):
+        from ._fastcall import Function
+        for name, (res, args) in list(SIGNATURES.items()) + list(TESTING_SIGNATURES.items()):
+            kinds = ["p" if isinstance(a, type) and issubclass(a, ctypes._Pointer) else self._KINDS.get(a) for a in args]
+            if res in (_i32, _i64, _sz) and None not in kinds:
+                address = ctypes.cast(getattr(L, name), ctypes.c_void_p).value
+                setattr(self, name, Function(address, "".join(kinds), "i" if res is _i32 else "q"))
+
+
+_calls: Optional[_Calls] = None
+
+
+def _c() -> _Calls:
+    global _calls
+    if _calls is None:
+        _calls = _Calls(lib())
+    return _calls
+
+
 class BnnError(RuntimeError):
     def __init__(self, status: int, where: str):
         self.status = int(status)
@@ -131,15 +156,15 @@ def _dev(t: torch.Tensor, dtype: torch.dtype, name: str) -> None:
 
 
 def packed_words(K: int) -> int:
-    return int(lib().bnn_packed_words(K))
+    return _c().bnn_packed_words(K)
 
 
 def conv_kwords(C: int, kH: int, kW: int) -> int:
-    return int(lib().bnn_conv_kwords(C, kH, kW))
+    return int(_c().bnn_conv_kwords(C, kH, kW))
 
 
 def conv_out_dim(n: int, k: int, s: int, p: int) -> int:
-    return int(lib().bnn_conv_out_dim(n, k, s, p))
+    return int(_c().bnn_conv_out_dim(n, k, s, p))
 
 
 def bnn_encode(src: torch.Tensor, dst: Optional[torch.Tensor] = None) -> torch.Tensor:
@@ -152,7 +177,7 @@ def bnn_encode(src: torch.Tensor, dst: Optional[torch.Tensor] = None) -> torch.T
         dst = torch.empty((rows, Kw), dtype=torch.int64, device=src.device)
     _dev(dst, torch.int64, "dst")
     assert dst.stride(1) == 1
-    _check(lib().bnn_encode(_ptr(src), rows, K, src.stride(0) if rows > 1 else max(K, src.stride(0)), _ptr(dst),
+    _check(_c().bnn_encode(_ptr(src), rows, K, src.stride(0) if rows > 1 else max(K, src.stride(0)), _ptr(dst),
                             dst.stride(0) if rows > 1 else max(Kw, dst.stride(0)), _stream()), "bnn_encode")
     return dst
 
@@ -162,13 +187,13 @@ def bnn_pack_conv_weight(w: torch.Tensor) -> torch.Tensor:
     assert w.dim() == 4 and w.is_contiguous()
     D, C, kH, kW = w.shape
     out = torch.empty((D, conv_kwords(C, kH, kW)), dtype=torch.int64, device=w.device)
-    _check(lib().bnn_pack_conv_weight(_ptr(w), D, C, kH, kW, _ptr(out), _stream()), "bnn_pack_conv_weight")
+    _check(_c().bnn_pack_conv_weight(_ptr(w), D, C, kH, kW, _ptr(out), _stream()), "bnn_pack_conv_weight")
     return out
 
 
 def im2col_workspace_bytes(x_shape, kH, kW, stride, pad) -> int:
     N, C, H, W = x_shape
-    return int(lib().bnn_im2col_workspace_bytes(N, C, H, W, kH, kW, stride[0], stride[1], pad[0], pad[1]))
+    return int(_c().bnn_im2col_workspace_bytes(N, C, H, W, kH, kW, stride[0], stride[1], pad[0], pad[1]))
 
 
 def bnn_im2col_packed(x: torch.Tensor, kH: int, kW: int, stride=(1, 1), pad=(0, 0),
@@ -182,10 +207,10 @@ def bnn_im2col_packed(x: torch.Tensor, kH: int, kW: int, stride=(1, 1), pad=(0, 
         cols = torch.empty((N * OH * OW, conv_kwords(C, kH, kW)), dtype=torch.int64, device=x.device)
     _dev(cols, torch.int64, "cols")
     assert cols.is_contiguous() and cols.numel() == N * OH * OW * conv_kwords(C, kH, kW)
-    nbytes = int(lib().bnn_im2col_workspace_bytes(*geo))
+    nbytes = int(_c().bnn_im2col_workspace_bytes(*geo))
     if workspace is None:
         workspace = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=x.device)
-    _check(lib().bnn_im2col_packed(_ptr(x), *geo, _ptr(cols), _ptr(workspace), workspace.numel(), _stream()),
+    _check(_c().bnn_im2col_packed(_ptr(x), *geo, _ptr(cols), _ptr(workspace), workspace.numel(), _stream()),
            "bnn_im2col_packed")
     return cols
 
@@ -204,9 +229,9 @@ def bnn_xnor_gemm(A: torch.Tensor, B: torch.Tensor, K: int, C: Optional[torch.Te
     ldb = B.stride(0) if N > 1 else max(B.shape[1], 1)
     ldc = C.stride(0) if M > 1 else max(N, 1)
     if cfg is None:
-        _check(lib().bnn_xnor_gemm(_ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, M, N, K, _stream()), "bnn_xnor_gemm")
+        _check(_c().bnn_xnor_gemm(_ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, M, N, K, _stream()), "bnn_xnor_gemm")
     else:
-        _check(lib().bnn_testing_xnor_gemm_epilogue(_ptr(A), lda, _ptr(B), ldb, M, N, K, _ptr(C), ldc, None, 0, None,
+        _check(_c().bnn_testing_xnor_gemm_epilogue(_ptr(A), lda, _ptr(B), ldb, M, N, K, _ptr(C), ldc, None, 0, None,
                                                     None, CH_NONE, cfg, _stream()), "bnn_testing_xnor_gemm_epilogue")
     return C
 
@@ -220,7 +245,7 @@ def bnn_xnor_gemm_mfma_i8(A: torch.Tensor, B: torch.Tensor, K: int, C: Optional[
         C = torch.empty((M, N), dtype=torch.int32, device=A.device)
     lda = A.stride(0) if M > 1 else max(A.shape[1], 1)
     ldb = B.stride(0) if N > 1 else max(B.shape[1], 1)
-    _check(lib().bnn_xnor_gemm_mfma_i8(_ptr(A), lda, _ptr(B), ldb, _ptr(C), C.stride(0) if M > 1 else max(N, 1), M, N,
+    _check(_c().bnn_xnor_gemm_mfma_i8(_ptr(A), lda, _ptr(B), ldb, _ptr(C), C.stride(0) if M > 1 else max(N, 1), M, N,
                                        K, _stream()), "bnn_xnor_gemm_mfma_i8")
     return C
 
@@ -234,7 +259,7 @@ def bnn_xnor_gemm_mfma_fp4(A: torch.Tensor, B: torch.Tensor, K: int, C: Optional
         C = torch.empty((M, N), dtype=torch.int32, device=A.device)
     lda = A.stride(0) if M > 1 else max(A.shape[1], 1)
     ldb = B.stride(0) if N > 1 else max(B.shape[1], 1)
-    _check(lib().bnn_xnor_gemm_mfma_fp4(_ptr(A), lda, _ptr(B), ldb, _ptr(C), C.stride(0) if M > 1 else max(N, 1), M, N,
+    _check(_c().bnn_xnor_gemm_mfma_fp4(_ptr(A), lda, _ptr(B), ldb, _ptr(C), C.stride(0) if M > 1 else max(N, 1), M, N,
                                         K, _stream()), "bnn_xnor_gemm_mfma_fp4")
     return C
 
@@ -243,12 +268,12 @@ def bnn_expand_fp4(packed: torch.Tensor, K: int, out: Optional[torch.Tensor] = N
     """Ablation: packed sign rows [rows, >= ceil(K/64)] int64 -> E2M1 rows [rows, 32 * ceil(K/64)] uint8."""
     _dev(packed, torch.int64, "packed")
     rows = packed.shape[0]
-    rb = int(lib().bnn_fp4_row_bytes(K))
+    rb = int(_c().bnn_fp4_row_bytes(K))
     if out is None:
         out = torch.empty((rows, rb), dtype=torch.uint8, device=packed.device)
     src_ld = packed.stride(0) if rows > 1 else max(packed.shape[1], 1)
     dst_ld = out.stride(0) if rows > 1 else max(out.shape[1], 16)
-    _check(lib().bnn_expand_fp4(_ptr(packed), rows, K, src_ld, _ptr(out), dst_ld, _stream()), "bnn_expand_fp4")
+    _check(_c().bnn_expand_fp4(_ptr(packed), rows, K, src_ld, _ptr(out), dst_ld, _stream()), "bnn_expand_fp4")
     return out
 
 
@@ -264,10 +289,10 @@ def bnn_xnor_gemm_mfma_fp4_expanded(A4: torch.Tensor, B4: torch.Tensor, K: int, 
     ldb = B4.stride(0) if N > 1 else max(B4.shape[1], 16)
     ldc = C.stride(0) if M > 1 else max(N, 1)
     if tile is None:
-        _check(lib().bnn_xnor_gemm_mfma_fp4_expanded(_ptr(A4), lda, _ptr(B4), ldb, _ptr(C), ldc, M, N, K, _stream()),
+        _check(_c().bnn_xnor_gemm_mfma_fp4_expanded(_ptr(A4), lda, _ptr(B4), ldb, _ptr(C), ldc, M, N, K, _stream()),
                "bnn_xnor_gemm_mfma_fp4_expanded")
     else:
-        _check(lib().bnn_testing_xnor_gemm_mfma_fp4_expanded(_ptr(A4), lda, _ptr(B4), ldb, _ptr(C), ldc, M, N, K, tile,
+        _check(_c().bnn_testing_xnor_gemm_mfma_fp4_expanded(_ptr(A4), lda, _ptr(B4), ldb, _ptr(C), ldc, M, N, K, tile,
                                                              _stream()), "bnn_testing_xnor_gemm_mfma_fp4_expanded")
     return C
 
@@ -282,7 +307,7 @@ def bnn_conv2d_mfma_fp4_expanded(x4: torch.Tensor, w4: torch.Tensor, C: int, D: 
     OH, OW = conv_out_dim(H, kH, stride[0], pad[0]), conv_out_dim(W, kW, stride[1], pad[1])
     if out is None:
         out = torch.empty((N, D, OH, OW), dtype=torch.int32, device=x4.device)
-    _check(lib().bnn_conv2d_mfma_fp4_expanded(_ptr(x4), _ptr(w4), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0],
+    _check(_c().bnn_conv2d_mfma_fp4_expanded(_ptr(x4), _ptr(w4), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0],
                                               pad[1], _ptr(out), _stream()), "bnn_conv2d_mfma_fp4_expanded")
     return out
 
@@ -297,7 +322,7 @@ def bnn_control_conv2d_f32(x: torch.Tensor, w: torch.Tensor, stride=(1, 1), pad=
     OH, OW = conv_out_dim(H, kH, stride[0], pad[0]), conv_out_dim(W, kW, stride[1], pad[1])
     if out is None:
         out = torch.empty((N, D, OH, OW), dtype=torch.float32, device=x.device)
-    _check(lib().bnn_control_conv2d_f32(_ptr(x), _ptr(w), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0], pad[1],
+    _check(_c().bnn_control_conv2d_f32(_ptr(x), _ptr(w), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0], pad[1],
                                         _ptr(out), _stream()), "bnn_control_conv2d_f32")
     return out
 
@@ -316,10 +341,10 @@ def bnn_xnor_gemm_epilogue(A: torch.Tensor, B: torch.Tensor, K: int, scale: torc
     lda = A.stride(0) if M > 1 else max(A.shape[1], 1)
     ldb = B.stride(0) if N > 1 else max(B.shape[1], 1)
     if cfg is None:
-        _check(lib().bnn_xnor_gemm_epilogue(_ptr(A), lda, _ptr(B), ldb, M, N, K, _ptr(C), max(N, 1), _ptr(Y), max(N, 1),
+        _check(_c().bnn_xnor_gemm_epilogue(_ptr(A), lda, _ptr(B), ldb, M, N, K, _ptr(C), max(N, 1), _ptr(Y), max(N, 1),
                                             _ptr(scale), _ptr(bias), axis, _stream()), "bnn_xnor_gemm_epilogue")
     else:
-        _check(lib().bnn_testing_xnor_gemm_epilogue(_ptr(A), lda, _ptr(B), ldb, M, N, K, _ptr(C), max(N, 1), _ptr(Y),
+        _check(_c().bnn_testing_xnor_gemm_epilogue(_ptr(A), lda, _ptr(B), ldb, M, N, K, _ptr(C), max(N, 1), _ptr(Y),
                                                     max(N, 1), _ptr(scale), _ptr(bias), axis, cfg, _stream()),
                "bnn_testing_xnor_gemm_epilogue")
     return C, Y
@@ -327,7 +352,7 @@ def bnn_xnor_gemm_epilogue(A: torch.Tensor, B: torch.Tensor, K: int, scale: torc
 
 def conv2d_workspace_bytes(x_shape, kH, kW, stride, pad) -> int:
     N, C, H, W = x_shape
-    return int(lib().bnn_conv2d_workspace_bytes(N, C, H, W, kH, kW, stride[0], stride[1], pad[0], pad[1]))
+    return int(_c().bnn_conv2d_workspace_bytes(N, C, H, W, kH, kW, stride[0], stride[1], pad[0], pad[1]))
 
 
 def bnn_conv2d(x: torch.Tensor, w_packed: torch.Tensor, D: int, kH: int, kW: int, stride=(1, 1), pad=(0, 0),
@@ -349,11 +374,11 @@ def bnn_conv2d(x: torch.Tensor, w_packed: torch.Tensor, D: int, kH: int, kW: int
     if scale is not None and out_f32 is None:
         out_f32 = torch.empty((N, D, OH, OW), dtype=torch.float32, device=x.device)
     if cfg is None and lean is None:
-        _check(lib().bnn_conv2d(_ptr(x), _ptr(w_packed), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0], pad[1],
+        _check(_c().bnn_conv2d(_ptr(x), _ptr(w_packed), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0], pad[1],
                                 _ptr(out_i32), _ptr(out_f32), _ptr(scale), _ptr(bias), _ptr(workspace),
                                 workspace.numel(), _stream()), "bnn_conv2d")
     else:
-        _check(lib().bnn_testing_conv2d(_ptr(x), _ptr(w_packed), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0],
+        _check(_c().bnn_testing_conv2d(_ptr(x), _ptr(w_packed), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0],
                                         pad[1], _ptr(out_i32), _ptr(out_f32), _ptr(scale), _ptr(bias),
                                         _ptr(workspace), workspace.numel(), -1 if cfg is None else cfg,
                                         1 if lean is None else lean, _stream()), "bnn_testing_conv2d")
@@ -369,7 +394,7 @@ def bnn_conv2d_noalloc(x: torch.Tensor, w_packed: torch.Tensor, D: int, kH: int,
     _dev(w_packed, torch.int64, "w_packed")
     assert x.dim() == 4 and x.is_contiguous() and w_packed.is_contiguous()
     N, C, H, W = x.shape
-    _check(lib().bnn_conv2d_noalloc(_ptr(x), _ptr(w_packed), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0],
+    _check(_c().bnn_conv2d_noalloc(_ptr(x), _ptr(w_packed), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0],
                                     pad[1], _ptr(out_i32), _ptr(out_f32), _ptr(scale), _ptr(bias), _stream()),
            "bnn_conv2d_noalloc")
 
@@ -397,11 +422,11 @@ def bnn_conv2d_packed(xp: torch.Tensor, w_packed: torch.Tensor, C: int, D: int, 
     else:
         raise ValueError(out)
     if cfg is None and lean is None:
-        _check(lib().bnn_conv2d_packed(_ptr(xp), _ptr(w_packed), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0],
+        _check(_c().bnn_conv2d_packed(_ptr(xp), _ptr(w_packed), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0],
                                        pad[1], pool, _ptr(oi), _ptr(of), _ptr(op), _ptr(scale), _ptr(bias), _stream()),
                "bnn_conv2d_packed")
     else:
-        _check(lib().bnn_testing_conv2d_packed(_ptr(xp), _ptr(w_packed), N, C, H, W, D, kH, kW, stride[0], stride[1],
+        _check(_c().bnn_testing_conv2d_packed(_ptr(xp), _ptr(w_packed), N, C, H, W, D, kH, kW, stride[0], stride[1],
                                                pad[0], pad[1], pool, _ptr(oi), _ptr(of), _ptr(op), _ptr(scale),
                                                _ptr(bias), -1 if cfg is None else cfg, 1 if lean is None else lean,
                                                _stream()), "bnn_testing_conv2d_packed")
@@ -413,8 +438,8 @@ def bnn_pack_conv_chain_weight(w_packed: torch.Tensor, C: int) -> torch.Tensor:
     _dev(w_packed, torch.int64, "w_packed")
     D = w_packed.shape[0]
     assert w_packed.is_contiguous() and w_packed.shape[1] == conv_kwords(C, 3, 3)
-    out = torch.empty(max(16, int(lib().bnn_conv_chain_weight_bytes(C, D))), dtype=torch.uint8, device=w_packed.device)
-    _check(lib().bnn_pack_conv_chain_weight(_ptr(w_packed), D, C, _ptr(out), _stream()), "bnn_pack_conv_chain_weight")
+    out = torch.empty(max(16, int(_c().bnn_conv_chain_weight_bytes(C, D))), dtype=torch.uint8, device=w_packed.device)
+    _check(_c().bnn_pack_conv_chain_weight(_ptr(w_packed), D, C, _ptr(out), _stream()), "bnn_pack_conv_chain_weight")
     return out
 
 
@@ -424,7 +449,7 @@ def conv_chain_layers(layers) -> ctypes.Array:
 
 
 def bnn_conv_chain_pays(N: int, C: int, H: int, W: int, layers: ctypes.Array) -> bool:
-    return bool(lib().bnn_conv_chain_pays(N, C, H, W, len(layers), layers))
+    return bool(_c().bnn_conv_chain_pays(N, C, H, W, len(layers), ctypes.addressof(layers)))
 
 
 def bnn_conv_chain(xp: torch.Tensor, C: int, layers: ctypes.Array, out: torch.Tensor) -> torch.Tensor:
@@ -438,7 +463,7 @@ def bnn_conv_chain(xp: torch.Tensor, C: int, layers: ctypes.Array, out: torch.Te
         if L.pool:
             OH, OW = OH // 2, OW // 2
     assert tuple(out.shape) == (N, OH, OW, packed_words(layers[-1].D))
-    _check(lib().bnn_conv_chain(_ptr(xp), N, C, H, W, len(layers), layers, _ptr(out), _stream()), "bnn_conv_chain")
+    _check(_c().bnn_conv_chain(_ptr(xp), N, C, H, W, len(layers), ctypes.addressof(layers), _ptr(out), _stream()), "bnn_conv_chain")
     return out
 
 
@@ -451,7 +476,7 @@ def bnn_conv2d_f32_sign(x: torch.Tensor, w: torch.Tensor, scale: torch.Tensor, b
     OH, OW = conv_out_dim(H, kH, stride[0], pad[0]), conv_out_dim(W, kW, stride[1], pad[1])
     if out is None:
         out = torch.empty((N, OH, OW, packed_words(D)), dtype=torch.int64, device=x.device)
-    _check(lib().bnn_conv2d_f32_sign(_ptr(x), _ptr(w), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0], pad[1],
+    _check(_c().bnn_conv2d_f32_sign(_ptr(x), _ptr(w), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0], pad[1],
                                      _ptr(scale), _ptr(bias), _ptr(out), _stream()), "bnn_conv2d_f32_sign")
     return out
 
@@ -460,7 +485,7 @@ def bnn_pack_fc_weight_nhwc(w: torch.Tensor, C: int, H: int, W: int) -> torch.Te
     _dev(w, torch.float32, "w")
     assert w.dim() == 2 and w.is_contiguous() and w.shape[1] == C * H * W
     out = torch.empty((w.shape[0], H * W * packed_words(C)), dtype=torch.int64, device=w.device)
-    _check(lib().bnn_pack_fc_weight_nhwc(_ptr(w), w.shape[0], C, H, W, _ptr(out), _stream()),
+    _check(_c().bnn_pack_fc_weight_nhwc(_ptr(w), w.shape[0], C, H, W, _ptr(out), _stream()),
            "bnn_pack_fc_weight_nhwc")
     return out
 
@@ -474,7 +499,7 @@ def bnn_maxpool2x2(a: torch.Tensor, scale: Optional[torch.Tensor] = None, bias: 
         out_i32 = torch.empty((N, D, H // 2, W // 2), dtype=torch.int32, device=a.device)
     if scale is not None and out_f32 is None:
         out_f32 = torch.empty((N, D, H // 2, W // 2), dtype=torch.float32, device=a.device)
-    _check(lib().bnn_maxpool2x2(_ptr(a), N, D, H, W, _ptr(out_i32), _ptr(out_f32), _ptr(scale), _ptr(bias),
+    _check(_c().bnn_maxpool2x2(_ptr(a), N, D, H, W, _ptr(out_i32), _ptr(out_f32), _ptr(scale), _ptr(bias),
                                 _stream()), "bnn_maxpool2x2")
     return out_i32, out_f32
 
@@ -487,7 +512,7 @@ def bnn_conv2d_f32(x: torch.Tensor, w: torch.Tensor, stride=(1, 1), pad=(0, 0), 
     OH, OW = conv_out_dim(H, kH, stride[0], pad[0]), conv_out_dim(W, kW, stride[1], pad[1])
     if out is None:
         out = torch.empty((N, D, OH, OW), dtype=torch.float32, device=x.device)
-    _check(lib().bnn_conv2d_f32(_ptr(x), _ptr(w), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0], pad[1],
+    _check(_c().bnn_conv2d_f32(_ptr(x), _ptr(w), N, C, H, W, D, kH, kW, stride[0], stride[1], pad[0], pad[1],
                                 _ptr(scale), _ptr(bias), _ptr(out), _stream()), "bnn_conv2d_f32")
     return out
 
@@ -500,18 +525,18 @@ def bnn_fc_f32(x: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor] = 
     N = w.shape[0]
     if out is None:
         out = torch.empty((M, N), dtype=torch.float32, device=x.device)
-    _check(lib().bnn_fc_f32(_ptr(x), _ptr(w), _ptr(bias), M, K, N, int(sign_input), _ptr(out), _stream()),
+    _check(_c().bnn_fc_f32(_ptr(x), _ptr(w), _ptr(bias), M, K, N, int(sign_input), _ptr(out), _stream()),
            "bnn_fc_f32")
     return out
 
 
 # ---- measurement helpers (include/bnn_testing.h) -----------------------------------
 def prof_enable(on: bool) -> None:
-    _check(lib().bnn_prof_enable(int(on)), "bnn_prof_enable")
+    _check(_c().bnn_prof_enable(int(on)), "bnn_prof_enable")
 
 
 def prof_reset() -> None:
-    _check(lib().bnn_prof_reset(), "bnn_prof_reset")
+    _check(_c().bnn_prof_reset(), "bnn_prof_reset")
 
 
 def prof_records() -> List[Tuple[str, float]]:
@@ -528,10 +553,10 @@ def prof_records() -> List[Tuple[str, float]]:
 def bnn_valu_peak_probe(sink: torch.Tensor, blocks: int, iters: int, kind: int = 0) -> None:
     _dev(sink, torch.int32, "sink")
     assert sink.numel() >= blocks * 256
-    _check(lib().bnn_valu_peak_probe(_ptr(sink), blocks, iters, kind, _stream()), "bnn_valu_peak_probe")
+    _check(_c().bnn_valu_peak_probe(_ptr(sink), blocks, iters, kind, _stream()), "bnn_valu_peak_probe")
 
 
 def bnn_copy_probe(src: torch.Tensor, dst: torch.Tensor) -> None:
     nbytes = src.numel() * src.element_size()
     assert dst.numel() * dst.element_size() >= nbytes
-    _check(lib().bnn_copy_probe(_ptr(src), _ptr(dst), nbytes, _stream()), "bnn_copy_probe")
+    _check(_c().bnn_copy_probe(_ptr(src), _ptr(dst), nbytes, _stream()), "bnn_copy_probe")

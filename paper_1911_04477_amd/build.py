@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -62,6 +63,16 @@ def _compile(src: str) -> str:
     return obj
 
 
+def build_fastcall() -> str:
+    """The binding's call helper, a CPython extension."""
+    out = os.path.join(HERE, "_fastcall.so")
+    tmp = out + ".tmp.%d" % os.getpid()
+    subprocess.check_call(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+                           os.path.join(CSRC, "fastcall.c"), "-o", tmp])
+    os.replace(tmp, out)
+    return out
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
@@ -69,8 +80,9 @@ def build(verbose: bool = False) -> str:
     tmp = LIB + ".tmp.%d" % os.getpid()
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp])
     os.replace(tmp, LIB)
+    fast = build_fastcall()
     if verbose:
-        print("built", LIB)
+        print("built", LIB, fast)
     return LIB
 
 

@@ -385,3 +385,30 @@ def test_conv_chain_errors(L):
     assert L.bnn_pack_conv_chain_weight(16, 128, 128, 8, None) == ALIGN
     assert L.bnn_conv_chain_pays(0, 128, 8, 8, 1, one) == 0 and L.bnn_conv_chain_pays(4, 64, 8, 8, 1, one) == 0
     assert L.bnn_conv_chain_pays(1, 128, 8, 8, 1, one) == 0  # one image leaves every other unit idle
+
+
+def test_binding_calls_equal_ctypes(L):
+    """The binding's call helper against ctypes on functions that launch nothing: values, widths, signs, None, errors."""
+    c = B._c()
+    for k in (-(1 << 63), -1, 0, 1, 64, 65, (1 << 40) + 1, (1 << 63) - 1):
+        assert c.bnn_packed_words(k) == L.bnn_packed_words(k), k
+    for a in ((32, 3, 1, 1), (1 << 33, 1 << 20, 7, 0), (2, 5, 1, 0), (-1, 1, 1, 1)):
+        assert c.bnn_conv_out_dim(*a) == L.bnn_conv_out_dim(*a)
+    for a in ((128, 3, 3), (0, 3, 3), (-5, 1, 1), ((1 << 32) + 64, 1, 1), ((1 << 31) - 1, 2, 1)):  # 32-bit parameters: the low half
+        assert c.bnn_conv_kwords(*a) == L.bnn_conv_kwords(*a)
+    geo = (64, 256, 56, 56, 3, 3, 1, 1, 1, 1)
+    assert c.bnn_conv2d_workspace_bytes(*geo) == L.bnn_conv2d_workspace_bytes(*geo) > 0
+    many = (16, 16, 1, 64, 8, 8, 64, 3, 3, 1, 1, 1, 1, None, None, None, None, 16, 1 << 20, None)  # the longest list: no output
+    assert c.bnn_conv2d(*many) == L.bnn_conv2d(*many) == NULL
+    assert c.bnn_encode(None, 1, 64, 64, 16, 1, None) == NULL and c.bnn_encode(8, 1, 64, 64, 16, 1, None) == ALIGN
+    assert c.bnn_encode(16, 0, 64, 64, 16, 1, None) == OK and c.bnn_encode(16, -1, 64, 64, 16, 1, None) == SHAPE
+    assert c.bnn_fp4_row_bytes(65) == 64
+    import numpy as np
+    assert c.bnn_packed_words(np.int64(129)) == 3 and c.bnn_packed_words(True) == 1
+    for bad in ((), (1, 2), (1.5,), (None,), ("1",)):
+        with pytest.raises(TypeError):
+            c.bnn_packed_words(*bad)
+    with pytest.raises(TypeError):
+        c.bnn_packed_words(K=1)
+    skipped = {n for n in [*B.SIGNATURES, *B.TESTING_SIGNATURES] if not hasattr(c, n)}
+    assert skipped == {"bnn_status_str", "bnn_kernel_name"}, skipped  # what returns a string stays with ctypes
