@@ -25,11 +25,13 @@ extern "C" {
  *       128 x 128, 64 x 256
  *   25 .. 28  the same for few outputs, the reduction axis split over the waves of a workgroup:
  *       32 x 32 tiles split 4 / 8 ways, 64 x 64 tiles split 4 / 8 ways
+ *   29  23 with the operands' bits expanded to 0 and 1 instead of +1 and -1 and the sums corrected by the counts of set
+ *       bits (explicit rows in 16-byte pieces, int32 / fp32 output, K below 2^22)
  *   10 .. 17  the short-row kernel on the matrix cores (rows of at most four words): blocks of 32 x 32 outputs per
  *       wave, +1 of 64 x 64, +2 a workgroup's waves side by side, +4 contiguous runs of workgroups per XCD
  * A value that a call cannot use (the packed epilogue needs a 32- or 64-row tile with two or
  * four column groups, or one of 21 to 28; 10 to 17 exist for an explicit B with int32 / fp32 output only;
- * 21 to 24 need K below 2^24)
+ * 21 to 24 need K below 2^24, 29 what it says)
  * selects the heuristic for that call, and so does any other value.
  * `lean`: 1 = convolutions whose geometry allows it keep a tile's input region in LDS (matrix cores) or gather
  * their patches with the table-driven loader (vector ALU), what bnn.h's entry points do; 0 = always the

@@ -176,14 +176,25 @@ __device__ __forceinline__ void settle(Fp4Acc<2, 2> &a) {
 // 41.8 -> 34.4, 128 x 31 x 33 maps from 1152 bits 21.7 -> 17.7).
 enum : int { MS_NT = 0, MS_VEC = 1, MS_ONE = 2 };
 
+// The result that an accumulator holds; BITS: all but the row's part, over 4 (see BitCodes).
+template <bool BITS>
+__device__ __forceinline__ float4 row_parts(const float *sRa) {
+  return BITS ? *reinterpret_cast<const float4 *>(sRa) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+}
+template <bool BITS>
+__device__ __forceinline__ float result(float acc, float row) {
+  return BITS ? fmaf(4.0f, acc, row) : acc;
+}
+
 // One map (int32, or fp32 through the affine map) of a wave's tile.  AFF: 0 int32, 1 fp32 with per-row
 // constants, 2 fp32 with per-column constants.  FULL: no row of the tile is past M.
 // Rows past M and columns past N hold the values of row M - 1 and column N - 1 once more (the staging clamps them), and
 // go to that place: nothing is predicated but whole groups of 8 rows.  (A branch per row and column instead, in code
 // that few waves run: 701 x 2113 x 1220 9.7 us, this way 6.4; 701 x 2112 x 1220 7.2, 6.1.)
-template <int WTM, int WTN, int AFF, int MS, bool FULL, class P>
+template <int WTM, int WTN, int AFF, int MS, bool BITS, bool FULL, class P>
 __device__ __forceinline__ void store_map(const P &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n, int half,
-                                          const float *sSc, const float *sBi, const int64_t (&off)[WTN]) {
+                                          const float *sSc, const float *sBi, const float *sRa,
+                                          const int64_t (&off)[WTN]) {
   typedef int vi __attribute__((ext_vector_type(WTN)));
   constexpr int STEP = MS == MS_ONE ? 32 : 1;  // columns between a lane's
   int32_t *base = AFF == 0 ? p.C : reinterpret_cast<int32_t *>(p.Y);
@@ -205,6 +216,7 @@ __device__ __forceinline__ void store_map(const P &p, const Fp4Acc<WTM, WTN> &ac
     for (int q = 0; q < 4; ++q) {
       if (!FULL && m0 + 32 * i + 8 * q >= p.M) return;  // uniform
       float4 sc, bi;
+      const float4 ra = row_parts<BITS>(sRa + 32 * i + 8 * q + 4 * half);
       if constexpr (AFF == 1) {
         sc = *reinterpret_cast<const float4 *>(sSc + 32 * i + 8 * q + 4 * half);
         bi = *reinterpret_cast<const float4 *>(sBi + 32 * i + 8 * q + 4 * half);
@@ -214,7 +226,7 @@ __device__ __forceinline__ void store_map(const P &p, const Fp4Acc<WTM, WTN> &ac
         vi o;
 #pragma unroll
         for (int j = 0; j < WTN; ++j) {
-          const float v = acc.v[i][j][4 * q + e];
+          const float v = result<BITS>(acc.v[i][j][4 * q + e], (&ra.x)[e]);
           if constexpr (AFF == 0) o[j] = (int)v;
           else if constexpr (AFF == 1) o[j] = __float_as_int(fmaf((&sc.x)[e], v, (&bi.x)[e]));
           else o[j] = __float_as_int(fmaf(csc[j], v, cbi[j]));
@@ -233,18 +245,19 @@ __device__ __forceinline__ void store_map(const P &p, const Fp4Acc<WTM, WTN> &ac
     }
 }
 
-template <int WTM, int WTN, int AFF, int MS, class P>
+template <int WTM, int WTN, int AFF, int MS, bool BITS, class P>
 __device__ __forceinline__ void store_map_by(const P &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n, int half,
-                                             const float *sSc, const float *sBi, const int64_t (&off)[WTN]) {
-  if (m0 + 32 * WTM <= p.M) store_map<WTM, WTN, AFF, MS, true>(p, acc, m0, n, half, sSc, sBi, off);
-  else store_map<WTM, WTN, AFF, MS, false>(p, acc, m0, n, half, sSc, sBi, off);
+                                             const float *sSc, const float *sBi, const float *sRa,
+                                          const int64_t (&off)[WTN]) {
+  if (m0 + 32 * WTM <= p.M) store_map<WTM, WTN, AFF, MS, BITS, true>(p, acc, m0, n, half, sSc, sBi, sRa, off);
+  else store_map<WTM, WTN, AFF, MS, BITS, false>(p, acc, m0, n, half, sSc, sBi, sRa, off);
 }
 
 // int32 and / or fp32 output of a wave's tile: rows m0.., columns n0.. (row-major, or NCHW planes).  P: the kernel's
 // arguments, of which these are read: C, Y, ldc, ldy, M, N, scale, bias, axis, img_stride, OHW, divOHW.
-template <int WTM, int WTN, int MS, class P>
+template <int WTM, int WTN, int MS, bool BITS = false, class P>
 __device__ __forceinline__ void store_maps(const P &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n0, int lane,
-                                           const float *sSc, const float *sBi) {
+                                           const float *sSc, const float *sBi, const float *sRa = nullptr) {
   constexpr int STEP = MS == MS_ONE ? 32 : 1;
   const int half = lane >> 5;
   const int n = n0 + (MS == MS_ONE ? 1 : WTN) * (lane & 31);
@@ -259,9 +272,9 @@ __device__ __forceinline__ void store_maps(const P &p, const Fp4Acc<WTM, WTN> &a
       off[j] = (int64_t)img * p.img_stride + ((uint32_t)nc - img * p.OHW);
     }
   }
-  if (p.C) store_map_by<WTM, WTN, 0, MS>(p, acc, m0, n, half, sSc, sBi, off);
-  if (p.Y && p.axis == BNN_CH_ROW) store_map_by<WTM, WTN, 1, MS>(p, acc, m0, n, half, sSc, sBi, off);
-  else if (p.Y) store_map_by<WTM, WTN, 2, MS>(p, acc, m0, n, half, sSc, sBi, off);
+  if (p.C) store_map_by<WTM, WTN, 0, MS, BITS>(p, acc, m0, n, half, sSc, sBi, sRa, off);
+  if (p.Y && p.axis == BNN_CH_ROW) store_map_by<WTM, WTN, 1, MS, BITS>(p, acc, m0, n, half, sSc, sBi, sRa, off);
+  else if (p.Y) store_map_by<WTM, WTN, 2, MS, BITS>(p, acc, m0, n, half, sSc, sBi, sRa, off);
 }
 
 // nibble q of a 16-bit mask -> bits 8q .. 8q + 3
@@ -279,9 +292,9 @@ __device__ __forceinline__ uint64_t sign_word(uint32_t h0, uint32_t h1) {
 
 // Binarizing epilogue: affine map, sign; packed NHWC words.  Tile rows are output channels, 64 of them
 // (WTM = 2): one word per output pixel.
-template <int WTM, int WTN, bool DEALT>
+template <int WTM, int WTN, bool DEALT, bool BITS>
 __device__ __forceinline__ void store_signs(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n0, int lane,
-                                            const float *sSc, const float *sBi) {
+                                            const float *sSc, const float *sBi, const float *sRa) {
   static_assert(WTM == 2 && (WTN == 2 || WTN == 4), "one 64-channel word per wave");
   const int half = lane >> 5, l32 = lane & 31;
   const int word = m0 >> 6;
@@ -295,12 +308,16 @@ __device__ __forceinline__ void store_signs(const GemmParams &p, const Fp4Acc<WT
     for (int q = 3; q >= 0; --q) {
       const float4 sc = *reinterpret_cast<const float4 *>(sSc + 32 * i + 8 * q + 4 * half);
       const float4 bi = *reinterpret_cast<const float4 *>(sBi + 32 * i + 8 * q + 4 * half);
+      const float4 ra = row_parts<BITS>(sRa + 32 * i + 8 * q + 4 * half);
       constexpr int ROWS = 4 / WTN;  // four signs at a time
 #pragma unroll
       for (int e = 3; e >= 0; e -= ROWS) {
         float y[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) y[k] = fmaf((&sc.x)[e - k / WTN], acc.v[i][k % WTN][4 * q + e - k / WTN], (&bi.x)[e - k / WTN]);
+        for (int k = 0; k < 4; ++k) {
+          const int r = e - k / WTN;
+          y[k] = fmaf((&sc.x)[r], result<BITS>(acc.v[i][k % WTN][4 * q + r], (&ra.x)[r]), (&bi.x)[r]);
+        }
         shift_in_signs<WTN>(bits, y);
       }
     }
@@ -318,9 +335,9 @@ __device__ __forceinline__ void store_signs(const GemmParams &p, const Fp4Acc<WT
 
 // The same on the 2x2 maximum.  Columns are window-major: a lane of a 4-block wave holds whole windows, a
 // lane of a 2-block wave one row of a window, its neighbour the other.
-template <int WTM, int WTN>
+template <int WTM, int WTN, bool BITS>
 __device__ __forceinline__ void store_signs_pooled(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n0,
-                                                   int lane, const float *sSc, const float *sBi) {
+                                                   int lane, const float *sSc, const float *sBi, const float *sRa) {
   static_assert(WTM == 2 && (WTN == 2 || WTN == 4), "one 64-channel word per wave");
   const int half = lane >> 5, l32 = lane & 31;
   const int word = m0 >> 6;
@@ -333,6 +350,7 @@ __device__ __forceinline__ void store_signs_pooled(const GemmParams &p, const Fp
     for (int q = 3; q >= 0; --q) {
       const float4 sc = *reinterpret_cast<const float4 *>(sSc + 32 * i + 8 * q + 4 * half);
       const float4 bi = *reinterpret_cast<const float4 *>(sBi + 32 * i + 8 * q + 4 * half);
+      const float4 ra = row_parts<BITS>(sRa + 32 * i + 8 * q + 4 * half);
       float y[4];
 #pragma unroll
       for (int e = 3; e >= 0; --e) {
@@ -346,7 +364,7 @@ __device__ __forceinline__ void store_signs_pooled(const GemmParams &p, const Fp
           const float o = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(m), 0xB1, 0xF, 0xF, true));
           asm("v_max_f32 %0, %0, %1" : "+v"(m) : "v"(o));
         }
-        y[3 - e] = fmaf((&sc.x)[e], m, (&bi.x)[e]);
+        y[3 - e] = fmaf((&sc.x)[e], result<BITS>(m, (&ra.x)[e]), (&bi.x)[e]);
       }
       shift_in_signs<1>(bits, y);
     }

@@ -923,16 +923,16 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
   const bool valu = emode == 0 ? (cfg >= 1 && cfg <= 6 && cfg != 5)
                                : (cfg == 3 || cfg == 1 || (!p.g.pool && (cfg == 6 || cfg == 4)));
   const bool short_rows = bmode == 0 && emode == 0 && lowk_applicable(p);
-  const bool matrix = (cfg >= 21 && cfg <= 24 && fp4_applicable(p)) || (cfg >= 25 && cfg <= 28);
+  const bool matrix = (((cfg >= 21 && cfg <= 24) || cfg == 29) && fp4_applicable(p)) || (cfg >= 25 && cfg <= 28);
   if (!valu && !matrix && !(short_rows && cfg >= 10 && cfg <= 17)) cfg = -1;
   if (short_rows && (cfg < 0 ? lowk_faster(p) : cfg >= 10 && cfg <= 17)) return launch_lowk(p, cfg < 0 ? -1 : cfg - 10, s);
   if (!valu) {
     // The matrix cores; few outputs split the reduction axis, and so do rows too long for exact fp32 sums.
     p.colperm = emode == 0 && map_columns_by_four(p) ? 1 : 0;
     p.nt_store = emode == 0 && nontemporal_maps(p, bmode) ? 1 : 0;
-    if (cfg >= 25) return launch_gemm_fp4_split(p, bmode, emode, s, cfg - 25);
+    if (cfg >= 25 && cfg <= 28) return launch_gemm_fp4_split(p, bmode, emode, s, cfg - 25);
     if (cfg < 0 && (fp4_split_applicable(p) || !fp4_applicable(p))) return launch_gemm_fp4_split(p, bmode, emode, s, -1);
-    return launch_gemm_fp4(p, bmode, emode, s, cfg >= 21 ? cfg - 21 : -1, tune.lean != 0);
+    return launch_gemm_fp4(p, bmode, emode, s, cfg >= 29 ? cfg - 25 : cfg >= 21 ? cfg - 21 : -1, tune.lean != 0);
   }
   // Vector-ALU tiles, with a forced configuration only: the method's own instructions (xor, popcount), measured beside
   // the matrix cores.

@@ -19,6 +19,11 @@
 // Values past the end of a row are staged as 0 bits in both operands: each adds (+1)(+1), so the
 // accumulators start at -(padded length - K) and end at the result.
 //
+// Long explicit rows run into the chip's power limit instead: the clock falls as the multipliers' inputs toggle.  Bits
+// as the codes 0 and 1 (BitCodes) let half of the products be zero and hold a higher clock; they sum to S = popcount(a AND b),
+// and the result is K - 2 popcount(a) - 2 popcount(b) + 4 S (section 3.2's sum, since a XOR b counts a + b - 2 (a AND b)).
+// The counts of set bits are taken from the pieces as they are staged.
+//
 // Lanes of a 32 x 32 block: operand fragments hold row (or column) l % 32 of the block, 64-bit word l / 32
 // of the 128-bit piece, one dword of it per instruction; the accumulator's register r holds row
 // 8*(r/4) + 4*(l/32) + r%4 of column l % 32.  Column block j, lane l of a wave is tile column WTN*(l%32)+j:
@@ -26,6 +31,7 @@
 // ordered window-major (column = 4 * window + member) a lane of a 4-block wave holds whole pooling windows.
 // (Columns that leave one by one, and signs from an LDS region: tile column 32*j + l%32.)
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "fp4_tile.h"
@@ -47,7 +53,7 @@ enum : int { GM_EXPL16 = 0, GM_EXPL8 = 1, GM_HALO = 2, GM_ANY = 3 };
 // tiles 10 %); packed signs; packed signs of the 2x2 maximum.
 enum : int { EM_MAPS_NT = MS_NT, EM_MAPS_VEC = MS_VEC, EM_MAPS_ONE = MS_ONE, EM_SIGN = 3, EM_POOL = 4 };
 
-template <int WTM_, int WTN_, int WGM_, int WGN_, int GM_>
+template <int WTM_, int WTN_, int WGM_, int WGN_, int GM_, bool BITS_ = false>
 struct Fp4Cfg {
   static constexpr int WTM = WTM_, WTN = WTN_, WGM = WGM_, WGN = WGN_, S = 4;  // S pieces (512 bits of K) per stage
   static constexpr int T = 64 * WGM * WGN;
@@ -60,7 +66,8 @@ struct Fp4Cfg {
   static constexpr int P16 = REGS * R16 + ((2 - REGS * R16) % 8 + 8) % 8;
   static constexpr int PA = BM * S / T, PB = STAGEB ? BN * S / T : 0;  // pieces per thread and stage
   static constexpr int STAGE_BYTES = 3 * S * P16 * 16;
-  static constexpr int FIXED_BYTES = STAGE_BYTES + 2 * BM * 4 + (GM_ == GM_HALO ? BN * 4 : 0);
+  // scale and bias of every row; GM_HALO: region offset of every column; bits: corrections of rows and columns
+  static constexpr int FIXED_BYTES = STAGE_BYTES + 2 * BM * 4 + (GM_ == GM_HALO ? BN * 4 : 0) + (BITS_ ? (BM + BN) * 4 : 0);
   static_assert(BM * S % T == 0 && BN * S % T == 0 && T % S == 0, "staging must divide evenly");
 };
 
@@ -142,9 +149,11 @@ __device__ __forceinline__ void load_region(const ConvGeom &g, const HaloGeom &h
   if (pending) between();  // a wave without rows
 }
 
-template <int WTM, int WTN, int WGM, int WGN, int GM, int EMODE, int MINW>
+template <int WTM, int WTN, int WGM, int WGN, int GM, int EMODE, int MINW, bool BITS>
 __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(GemmParams p) {
-  using Cfg = Fp4Cfg<WTM, WTN, WGM, WGN, GM>;
+  using Cfg = Fp4Cfg<WTM, WTN, WGM, WGN, GM, BITS>;
+  // BITS: 0 / 1 codes (see launch_gemm_fp4); the set bits of rows and columns are counted as they are staged
+  using Codes = typename std::conditional<BITS, BitCodes, SignCodes>::type;
   constexpr int T = Cfg::T, BM = Cfg::BM, BN = Cfg::BN, PA = Cfg::PA, PB = Cfg::PB, S = Cfg::S;
   constexpr bool POOL = EMODE == EM_POOL;
   // columns of a wave dealt to (block j, lane l): WTN * l + j, so that a lane's columns are consecutive; signs
@@ -162,6 +171,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
   float *const sSc = reinterpret_cast<float *>(smem + Cfg::STAGE_BYTES);
   float *const sBi = sSc + BM;
   uint32_t *const sCol = reinterpret_cast<uint32_t *>(sBi + BM);      // GM_HALO: region offset of every column
+  float *const sRow = sBi + BM;                                         // BITS: parts of rows, then of columns
+  static_assert(!BITS || GM == GM_EXPL16, "sRow lies where sCol does");
   char *const sReg = smem + Cfg::FIXED_BYTES;                           // GM_HALO: [word][pixel] 8-byte words
   uint32_t *const sOff = reinterpret_cast<uint32_t *>(sReg + p.halo.bytes);  // GM_HALO: distance of every word of a row
   const int tid = threadIdx.x;
@@ -284,10 +295,24 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
   const int unitB = DEALT ? (BM / 32 + (row0 / (32 * WTN)) * WTN + col0 % WTN) * Cfg::R16 + col0 / WTN
                           : (BM / 32 + (row0 >> 5)) * Cfg::R16 + (row0 & 31);
   char *const wrB = smem + (pc * Cfg::P16 + unitB) * 16;
+  // set bits of this thread's pieces, counted on the way; what lies past the row's end is 0
+  uint32_t cntA[PA], cntB[NB];
+#pragma unroll
+  for (int i = 0; i < PA; ++i) cntA[i] = 0u;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) cntB[i] = 0u;
+  auto count = [](const u32x4 &v, uint32_t n) {
+    n += __popc(v.x);
+    n += __popc(v.y);
+    n += __popc(v.z);
+    return n + __popc(v.w);
+  };
   auto store_piece = [&](int i, uint32_t buf) {  // i < PA: A, else B
     if (i < PA) {
+      if constexpr (BITS) cntA[i] = count(ra[i], cntA[i]);
       *reinterpret_cast<u32x4 *>(wrA + buf + i * (RPT / 32) * Cfg::R16 * 16) = ra[i];
     } else if (i < PA + PB) {
+      if constexpr (BITS) cntB[i - PA] = count(rb[i - PA], cntB[i - PA]);
       const int c = (i - PA) * RPT;  // columns from the first one
       const int u = DEALT ? (c / (32 * WTN)) * WTN * Cfg::R16 + (c % (32 * WTN)) / WTN : (c / 32) * Cfg::R16;
       *reinterpret_cast<u32x4 *>(wrB + buf + u * 16) = rb[i - PA];
@@ -347,8 +372,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
     sBi[tid] = fbi;
   }
 
+  // SignCodes: the result, less the padding.  BitCodes count S, C = K - 2 * (set bits of the row) - 2 * (set bits of the
+  // column) + 4 S: the column's part is added at the end, the row's in the epilogue.
   Fp4Acc<WTM, WTN> acc;
-  acc.init(-(float)(npieces * 128 - p.Kformula));
+  acc.init(BITS ? 0.0f : -(float)(npieces * 128 - p.Kformula));
 
   // Stage st sits in LDS buffer st % 3.  It is written during piece 0 of the stage before it, a barrier stands
   // between pieces 1 and 2, and piece 3 already reads ahead into the next stage; the buffer that a stage is
@@ -365,7 +392,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
   __syncthreads();
   const char *regB[WTN];
   const uint32_t *const offp = sOff + (lane >> 5);
-  uint32_t woff = 0u;  // GM_HALO: distance of this lane's word of the piece that is read next
+  uint32_t woff = 0u;  // of a region: distance of this lane's word of the piece that is read next
   if constexpr (GM == GM_HALO) {
 #pragma unroll
     for (int j = 0; j < WTN; ++j)
@@ -389,12 +416,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
     }
 #pragma unroll
     for (int i = 0; i < WTM; ++i) {
-      ea[i] = expand_e2m1<true>(a[i].x);
+      ea[i] = Codes::template a<true>(a[i].x);
       ya[i] = a[i].y;
     }
 #pragma unroll
     for (int j = 0; j < WTN; ++j) {
-      eb[j] = expand_e2m1<true>(b[j].x);
+      eb[j] = Codes::template b<true>(b[j].x);
       yb[j] = b[j].y;
     }
   }
@@ -402,7 +429,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
 #pragma unroll 1
   for (int st = 0; st < nst; ++st) {
     const uint32_t wbuf = rbuf == 2 * BUF ? 0u : rbuf + BUF;  // the next stage's
-    if (st + 2 == nst) mask_stage(st + 1);
+    if (st + 2 == nst || (BITS && st + 1 == nst)) mask_stage(st + 1);  // past the last stage: all 0, nothing more is counted
 #pragma unroll
     for (int k = 0; k < S; ++k) {
       const int q = st * S + k;
@@ -412,7 +439,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
       u32x2 na[WTM], nb[WTN];  // the next piece (past the last one: whatever is there, not used)
       const uint32_t next = k + 1 < S ? rbuf + (k + 1) * Cfg::P16 * 16 : wbuf;
       v8i fa[WTM], fb[WTN];
-      multiply_and_expand<SignCodes, WTM, WTN>(acc, ea, eb, ya, yb, fa, fb, [&](int m) {
+      multiply_and_expand<Codes, WTM, WTN>(acc, ea, eb, ya, yb, fa, fb, [&](int m) {
 #pragma unroll
         for (int f = m * FR / MM; f < (m + 1) * FR / MM; ++f) read_frag(f, next, na, nb);
       });
@@ -427,7 +454,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
         xb[j] = nb[j].x;
         yb[j] = nb[j].y;
       }
-      multiply_and_expand<SignCodes, WTM, WTN>(acc, fa, fb, xa, xb, ea, eb, [&](int m) {
+      multiply_and_expand<Codes, WTM, WTN>(acc, fa, fb, xa, xb, ea, eb, [&](int m) {
         if (k == 0) {  // the next stage's pieces, from registers
 #pragma unroll
           for (int i = m * (PA + PB) / MM; i < (m + 1) * (PA + PB) / MM; ++i) store_piece(i, wbuf);
@@ -442,18 +469,47 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
     rbuf = wbuf;
   }
 
+  if constexpr (BITS) {
+    // the four threads that staged a row add up its bits
+    auto sum4 = [](uint32_t n) {
+      n += (uint32_t)__builtin_amdgcn_mov_dpp((int)n, 0xB1, 0xF, 0xF, true);
+      return n + (uint32_t)__builtin_amdgcn_mov_dpp((int)n, 0x4E, 0xF, 0xF, true);
+    };
+    static_assert(S == 4, "four threads to a row");
+#pragma unroll
+    for (int i = 0; i < PA; ++i) {
+      const uint32_t n = sum4(cntA[i]);
+      if (pc == 0) sRow[row0 + i * RPT] = -2.0f * (float)n;
+    }
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+      const uint32_t n = sum4(cntB[i]);
+      if (pc == 0) sRow[BM + row0 + i * RPT] = 0.25f * (float)p.Kformula - 0.5f * (float)n;
+    }
+    __syncthreads();
+  }
   settle(acc);
+  if constexpr (BITS) {  // the columns' part
+#pragma unroll
+    for (int j = 0; j < WTN; ++j) {
+      const float c = sRow[BM + wn * WTN * 32 + (DEALT ? WTN * (lane & 31) + j : 32 * j + (lane & 31))];
+#pragma unroll
+      for (int i = 0; i < WTM; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc.v[i][j][r] += c;
+    }
+  }
   const int mw = m0 + 32 * WTM * wm, nw = n0 + 32 * WTN * wn;
-  const float *sc = sSc + 32 * WTM * wm, *bi = sBi + 32 * WTM * wm;
-  if constexpr (MAPS) store_maps<WTM, WTN, EMODE>(p, acc, mw, nw, lane, sc, bi);
-  else if constexpr (EMODE == EM_SIGN) store_signs<WTM, WTN, DEALT>(p, acc, mw, nw, lane, sc, bi);
-  else store_signs_pooled<WTM, WTN>(p, acc, mw, nw, lane, sc, bi);
+  const float *sc = sSc + 32 * WTM * wm, *bi = sBi + 32 * WTM * wm, *rc = sRow + 32 * WTM * wm;
+  if constexpr (MAPS) store_maps<WTM, WTN, EMODE, BITS>(p, acc, mw, nw, lane, sc, bi, rc);
+  else if constexpr (EMODE == EM_SIGN) store_signs<WTM, WTN, DEALT, BITS>(p, acc, mw, nw, lane, sc, bi, rc);
+  else store_signs_pooled<WTM, WTN, BITS>(p, acc, mw, nw, lane, sc, bi, rc);
 }
 
 // ---- host side -----------------------------------------------------------------------------------------
-template <int WTM, int WTN, int WGM, int WGN, int GM, int EMODE, int MINW>
+template <int WTM, int WTN, int WGM, int WGN, int GM, int EMODE, int MINW, bool BITS = false>
 static bnn_status launch_fp4(GemmParams &p, hipStream_t s) {
-  using Cfg = Fp4Cfg<WTM, WTN, WGM, WGN, GM>;
+  using Cfg = Fp4Cfg<WTM, WTN, WGM, WGN, GM, BITS>;
   p.tilesM = (p.M + Cfg::BM - 1) / Cfg::BM;
   const int64_t tn = ((int64_t)p.N + Cfg::BN - 1) / Cfg::BN;
   const int64_t blocks = p.tilesM * tn;
@@ -462,16 +518,16 @@ static bnn_status launch_fp4(GemmParams &p, hipStream_t s) {
   p.divTilesM = FastDiv((uint32_t)p.tilesM);
   const size_t lds = Cfg::FIXED_BYTES + (GM == GM_HALO ? (size_t)p.halo.bytes + (size_t)(p.Kw64 + 1) / 2 * 8 : 0);
   ProfScope ps(KID_XNOR_GEMM_FP4, s);
-  hipLaunchKernelGGL((xnor_gemm_fp4_kernel<WTM, WTN, WGM, WGN, GM, EMODE, MINW>), dim3((unsigned)blocks), dim3(Cfg::T),
-                     lds, s, p);
+  hipLaunchKernelGGL((xnor_gemm_fp4_kernel<WTM, WTN, WGM, WGN, GM, EMODE, MINW, BITS>), dim3((unsigned)blocks),
+                     dim3(Cfg::T), lds, s, p);
   return launch_status();
 }
 
-template <int WTM, int WTN, int WGM, int WGN, int GM, int MINW>
+template <int WTM, int WTN, int WGM, int WGN, int GM, int MINW, bool BITS = false>
 static bnn_status launch_fp4_maps(GemmParams &p, hipStream_t s) {
-  if (!p.colperm) return launch_fp4<WTM, WTN, WGM, WGN, GM, EM_MAPS_ONE, MINW>(p, s);
-  return p.nt_store ? launch_fp4<WTM, WTN, WGM, WGN, GM, EM_MAPS_NT, MINW>(p, s)
-                    : launch_fp4<WTM, WTN, WGM, WGN, GM, EM_MAPS_VEC, MINW>(p, s);
+  if (!p.colperm) return launch_fp4<WTM, WTN, WGM, WGN, GM, EM_MAPS_ONE, MINW, BITS>(p, s);
+  return p.nt_store ? launch_fp4<WTM, WTN, WGM, WGN, GM, EM_MAPS_NT, MINW, BITS>(p, s)
+                    : launch_fp4<WTM, WTN, WGM, WGN, GM, EM_MAPS_VEC, MINW, BITS>(p, s);
 }
 
 // Upper bound of the number of aligned-grid cells of length `cell` that a run of `len` columns starting at a
@@ -547,7 +603,13 @@ bool fp4_applicable(const GemmParams &p) {
   return p.Kw64 < (1 << 18) - 2;
 }
 
+// The 128 x 128 tile of bits (BitCodes): rows of whole 16-byte pieces, partial sums that are multiples of 1/4 exact below 2^22.
+static bool bits_applicable(const GemmParams &p, int bmode) {
+  return bmode == 0 && p.Kw64 % 2 == 0 && p.lda32 % 4 == 0 && p.ldb % 2 == 0 && p.Kw64 < (1 << 16) - 2;
+}
+
 bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, int shape, bool region) {
+  if (shape >= 4 && !bits_applicable(p, bmode)) shape = -1;
   const bool maps = bmode == 0 || emode == 0;
   if (shape < 0 || (maps && shape < 2)) {
     const int64_t cu = p.n_cu, c256 = ((int64_t)p.N + 255) / 256;
@@ -561,6 +623,12 @@ bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, i
       // four waves; 128 x 131072 x 1152: 16.6, 17.3, 17.7), else 128 x 128 (512 x 4096 x 2304: 9.9 against 10.3).
       // Explicit rows stage B too, which the squarer tile halves (4096^3: 35.1 against 36.6 and 39.3).
       shape = bmode == 1 && t64 >= 2 * cu ? 3 : 2;
+      // Long explicit rows on a full chip, where the sign codes hold the clock down (8192^3 232 -> 211 us, 4096 x 60000 x 2048
+      // 273 -> 253, 1000 x 9000 x 4096 26.1 -> 23.8, 512 x 20000 x 2304 18.0 -> 16.3, 4096^3 33.9 -> 32.1).  Counting and the
+      // corrections cost a tile about 1000 clocks: shorter rows gain nothing (4096 x 8192 x 1536 38.5 against 38.8, 2048 x
+      // 4096 x 1280 10.7 against 11.4), nor do tiles that leave units idle (512 x 4096 x 2304 8.6 against 8.9).
+      if (bits_applicable(p, bmode) && p.Kw64 >= 32 && 5 * (((int64_t)p.M + 127) / 128) * (((int64_t)p.N + 127) / 128) >= 6 * cu)
+        shape = 4;
     } else {
       // Signs leave little to store: 128 x 256 tiles of 64 x 128 per wave need the fewest expansions per matrix
       // instruction and win once every compute unit gets two of them (128 x 262144 x 1152 pooled: 22.4 us against
@@ -574,6 +642,7 @@ bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, i
     case 0: return launch_fp4_shape<2, 4, 2, 2, 2, false>(p, bmode, emode, s, region);  // 128 x 256, 4 waves of 64 x 128
     case 1: return launch_fp4_shape<2, 2, 2, 4, 2, false>(p, bmode, emode, s, region);  // 128 x 256, 8 waves of 64 x 64
     case 2: return launch_fp4_shape<2, 2, 2, 2, 3, true>(p, bmode, emode, s, region);   // 128 x 128, 4 waves of 64 x 64
+    case 4: return launch_fp4_maps<2, 2, 2, 2, GM_EXPL16, 3, true>(p, s);                // 128 x 128, bits
     default: return launch_fp4_shape<2, 2, 1, 4, 2, true>(p, bmode, emode, s, region);  // 64 x 256, 4 waves of 64 x 64
   }
 }

@@ -255,6 +255,35 @@ def test_gemm_short_rows_rule(M, N, K, short):
     assert torch.equal(got, B.bnn_xnor_gemm(A, Bm, K, cfg=3))
 
 
+@pytest.mark.parametrize("M,N,K,pad", [(1, 1, 1, 1), (127, 129, 127, 0), (129, 132, 128, 2), (130, 255, 129, 1), (64, 300, 513, 1),
+                                       (257, 128, 640, 0), (100, 260, 4097, 1),
+                                       (2200, 2176, 1984, 1), (2200, 2176, 1985, 0), (2200, 2176, 2050, 1)])  # both sides of the rule
+def test_gemm_bit_codes(M, N, K, pad):
+    """Rows expanded to 0 / 1 and corrected by their counts: edges of the tile, of a stage (512 bits) and of a word, odd
+    columns, padded rows, garbage past K, both maps with the channel along either axis; all bits set and none."""
+    print(f"bit codes {M}x{N}x{K} +{pad}", flush=True)
+    rng = np.random.default_rng(M + N + K)
+    A, Bm = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    A[0], Bm[0] = -1, 1
+    A[-1], Bm[-1] = 1, -1
+
+    def operand(a):
+        w = np.concatenate([as_u64(B.bnn_encode(dev(a))), np.full((len(a), pad), 0x5A5A, np.uint64)], axis=1)
+        if K % 64:
+            w[:, (K - 1) // 64] |= np.uint64(0xFFFFFFFFFFFFFFFF >> (K % 64) << (K % 64)) & np.uint64(0x9669C33CA55A0FF0)
+        return dev(w.view(np.int64))
+    Ap, Bp = operand(A), operand(Bm)
+    ref = oracle.gemm_pm1(A, Bm) if M * N * K < 1 << 28 else host(B.bnn_xnor_gemm(Ap, Bp, K, cfg=3))
+    for c in (None, 29):
+        assert np.array_equal(host(B.bnn_xnor_gemm(Ap, Bp, K, cfg=c)), ref)
+        for axis, ch in (("row", M), ("col", N)):
+            sc, bi = rng.standard_normal(ch).astype(np.float32), rng.standard_normal(ch).astype(np.float32)
+            Ci, Y = B.bnn_xnor_gemm_epilogue(Ap, Bp, K, dev(sc), dev(bi), B.CH_ROW if axis == "row" else B.CH_COL,
+                                             want_int=True, cfg=c)
+            assert np.array_equal(host(Ci), ref)
+            assert np.array_equal(host(Y), oracle.scale_bias(ref, sc, bi, axis))
+
+
 @pytest.mark.parametrize("cfg", [-1, 10, 11, 12, 3])
 @pytest.mark.parametrize("case", [(3, 200, 12, 12, 70, 1, 1, 2, 2, 0, 0),    # 36 pixels per image: short-row kernel
                                   (2, 200, 10, 10, 17, 1, 1, 2, 2, 0, 0),    # 25 pixels per image: not a multiple of 4
