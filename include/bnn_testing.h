@@ -33,9 +33,9 @@ extern "C" {
  * four column groups, or one of 21 to 28; 10 to 17 exist for an explicit B with int32 / fp32 output only;
  * 21 to 24 need K below 2^24, 29 what it says)
  * selects the heuristic for that call, and so does any other value.
- * `lean`: 1 = convolutions whose geometry allows it keep a tile's input region in LDS (matrix cores) or gather
- * their patches with the table-driven loader (vector ALU), what bnn.h's entry points do; 0 = always the
- * general gather.
+ * `lean`: 1 = convolutions whose geometry allows it keep a tile's input region in LDS (matrix cores; with cfg = -1 where
+ * it also pays, what bnn.h's entry points do) or gather their patches with the table-driven loader (vector ALU);
+ * 0 = always the general gather.
  */
 
 /* bnn_xnor_gemm_epilogue (and, with Y == NULL, bnn_xnor_gemm) on tile configuration cfg. */

@@ -608,35 +608,96 @@ static bool bits_applicable(const GemmParams &p, int bmode) {
   return bmode == 0 && p.Kw64 % 2 == 0 && p.lda32 % 4 == 0 && p.ldb % 2 == 0 && p.Kw64 < (1 << 16) - 2;
 }
 
+// Workgroups that a compute unit holds with their input regions in LDS, at most three; 0: the region is not for LDS.
+template <int WTM, int WTN, int WGM, int WGN>
+static int held_with_regions(GemmParams &p) {
+  using H = Fp4Cfg<WTM, WTN, WGM, WGN, GM_HALO>;
+  int64_t rows;
+  if (!halo_region(p, H::BN, p.g.pool != 0, rows)) return 0;
+  return std::min(3, 160 * 1024 / (H::FIXED_BYTES + (int)p.halo.bytes + (p.Kw64 + 1) / 2 * 8));
+}
+
+// Tile of a convolution, and whether its input region is kept in LDS (`region`: allowed to).
+static int conv_shape(GemmParams &p, int emode, bool &region) {
+  const ConvGeom &g = p.g;
+  auto count = [&](int bm, int bn) { return (((int64_t)p.M + bm - 1) / bm) * (((int64_t)p.N + bn - 1) / bn); };
+  auto per_unit = [&](int bm, int bn) { return (count(bm, bn) + p.n_cu - 1) / p.n_cu; };
+  const int64_t n = per_unit(128, 128), taps = (int64_t)g.kH * g.kW, steps = (int64_t)g.sH * g.sW;
+  // No pixel under two taps: a region's pixels are then copied to be read once, and the ones that the stride skips are copied
+  // for nothing (1 x 1 by stride 2, 128 x 128 tiles gathering against holding regions: 512 x 4096 x 704 20.9 us against 26.2,
+  // 128 x 86016 x 192 packed 10.1 against 12.0).  Where it skips none the copy pays when its lanes, a region row's word
+  // pairs at a time, are busy (2 x 2 by stride 2, 256 channels of 32 x 32: 23.6 against 20.9; 192 channels of 8 x 8 16.4
+  // against 19.8).  Without a stride it is the copy's latency that counts, while there are few tiles (1 x 1 of 128
+  // channels, 1.8 tiles a unit: 5.4 against 6.2; 512 channels, 5.6 tiles: 16.1 against 14.4).
+  const int64_t pairs = ((int64_t)(g.OW - 1) * g.sW + g.kW) * ((g.Cw + 1) / 2);
+  const bool idle = 2 * pairs < (pairs + 63) / 64 * 64;
+  const bool once = taps < steps || (taps == steps && (steps > 1 ? idle : emode != 0 && n <= 2));
+  // Regions that leave a unit one workgroup where it has several tiles to do cost more than gathering, which a stride of 2
+  // makes cheap (3 x 3 by stride 2, 704 channels, three 128 x 128 tiles: 40.4 against 53.7; 512 channels, two of 128 x 256:
+  // 34.5 against 37.3); with more taps a pixel it takes the third tile (3 x 3, 1024 channels of 56 x 56: 89.9 against
+  // 102.8 with five, but 65.6 against 62.2 on two of 128 x 256).
+  auto gather = [&](int held, int64_t tiles, bool third) {
+    return held == 0 || once || (held == 1 && tiles >= 2 && (taps < 4 * steps || (third && tiles >= 3)));
+  };
+  auto held_if = [&](int held) { return region ? held : 0; };
+  if (p.M <= 64) {
+    // one row of tiles to fill (64 channels, 100352 pixels, K = 576: 7.0 us against 9.0 to 10.9)
+    const int held = held_if(held_with_regions<2, 2, 1, 4>(p));
+    const int64_t tiles = per_unit(64, 256);
+    region = once ? held >= std::min<int64_t>(tiles, 3) : !gather(held, tiles, false);
+    return 3;
+  }
+  const int held128 = held_if(held_with_regions<2, 2, 2, 2>(p));
+  if (emode == 0) {
+    // Stores of maps want many workgroups in different phases: 64 x 256 tiles while every unit gets two of them and their
+    // larger regions do not keep workgroups out (256 x 200704 x 2304 fp32 maps 64.2 us against 68.1 on 128 x 128 and 67.9 on
+    // 128 x 256 by four waves; 128 x 131072 x 1152: 16.6, 17.3, 17.7; but 3 x 3 by stride 2 from 512 channels of 8 x 8, one
+    // against two held: 119 against 74), else 128 x 128 (512 x 4096 x 2304: 9.9 against 10.3).
+    if (!once && count(64, 256) >= 2 * (int64_t)p.n_cu) {
+      const int held = held_if(held_with_regions<2, 2, 1, 4>(p));
+      if (held > 0 && held >= held128) {
+        region = !gather(held, per_unit(64, 256), false);
+        return 3;
+      }
+    }
+    region = !gather(held128, n, true);
+    return 2;
+  }
+  // Signs leave little to store, so what counts is expansions per matrix instruction and full rounds of tiles.  128 x 256
+  // tiles of 64 x 128 per wave need the fewest expansions, two of them to a compute unit; 128 x 128 tiles fit three times and
+  // fill odd counts up to five.  3 x 3 layers, 128 x 128 tiles against 128 x 256, by the number of 128 x 128 tiles per unit:
+  // 0.5 9.9 us against 12.9; 1.6 12.3 against 11.6; 2.0 17.5 against 16.0 (pooled 19.5 against 18.4); 2.4 15.9 against 18.5 and
+  // 25.3 against 30.1; 3.6 24.0 against 21.8; 4.4 21.2 against 23.3 and 23.7 against 24.8; 5.2 28.0 against 25.0; from there
+  // the larger one (7.8 35.6 against 30.2), but for a few per cent either way where the last round is short.
+  if (n <= 5 && n % 2 == 1) {
+    region = !gather(held128, n, true);
+    return 2;
+  }
+  const int64_t tiles = per_unit(128, 256);
+  region = !gather(held_if(held_with_regions<2, 4, 2, 2>(p)), tiles, false);
+  // One 128 x 256 tile to a unit: eight waves gather faster than four (3 x 3 by stride 2, 1024 channels: 38.1 against 40.6), and
+  // they copy faster the regions of small maps, several images to a tile (256 channels of 8 x 8: 13.4 against 13.9, 384:
+  // 15.9 against 16.4), until the reduction is long (512: 18.9 against 18.4).
+  const bool small = !g.pool && (int64_t)g.OH * g.OW <= 64 && p.Kw64 < 72;
+  return n == 2 && (!region || small) ? 1 : 0;
+}
+
 bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, int shape, bool region) {
   if (shape >= 4 && !bits_applicable(p, bmode)) shape = -1;
-  const bool maps = bmode == 0 || emode == 0;
-  if (shape < 0 || (maps && shape < 2)) {
-    const int64_t cu = p.n_cu, c256 = ((int64_t)p.N + 255) / 256;
-    const int64_t t = (((int64_t)p.M + 127) / 128) * c256, t64 = (((int64_t)p.M + 63) / 64) * c256;
-    if (p.M <= 64) {
-      // one row of tiles to fill (64 channels, 100352 pixels, K = 576: 7.0 us against 9.0 to 10.9)
-      shape = 3;
-    } else if (maps) {
-      // Stores of maps want many workgroups in different phases: 64 x 256 tiles, three to a compute unit, while every
-      // unit gets two of them (256 x 200704 x 2304 fp32 maps 64.2 us against 68.1 on 128 x 128 and 67.9 on 128 x 256 by
-      // four waves; 128 x 131072 x 1152: 16.6, 17.3, 17.7), else 128 x 128 (512 x 4096 x 2304: 9.9 against 10.3).
+  if (bmode == 0) {
+    if (shape < 2) {
       // Explicit rows stage B too, which the squarer tile halves (4096^3: 35.1 against 36.6 and 39.3).
-      shape = bmode == 1 && t64 >= 2 * cu ? 3 : 2;
-      // Long explicit rows on a full chip, where the sign codes hold the clock down (8192^3 232 -> 211 us, 4096 x 60000 x 2048
+      shape = p.M <= 64 ? 3 : 2;
+      // Long ones on a full chip, where the sign codes hold the clock down (8192^3 232 -> 211 us, 4096 x 60000 x 2048
       // 273 -> 253, 1000 x 9000 x 4096 26.1 -> 23.8, 512 x 20000 x 2304 18.0 -> 16.3, 4096^3 33.9 -> 32.1).  Counting and the
       // corrections cost a tile about 1000 clocks: shorter rows gain nothing (4096 x 8192 x 1536 38.5 against 38.8, 2048 x
       // 4096 x 1280 10.7 against 11.4), nor do tiles that leave units idle (512 x 4096 x 2304 8.6 against 8.9).
-      if (bits_applicable(p, bmode) && p.Kw64 >= 32 && 5 * (((int64_t)p.M + 127) / 128) * (((int64_t)p.N + 127) / 128) >= 6 * cu)
+      if (shape == 2 && bits_applicable(p, bmode) && p.Kw64 >= 32 &&
+          5 * (((int64_t)p.M + 127) / 128) * (((int64_t)p.N + 127) / 128) >= 6 * (int64_t)p.n_cu)
         shape = 4;
-    } else {
-      // Signs leave little to store: 128 x 256 tiles of 64 x 128 per wave need the fewest expansions per matrix
-      // instruction and win once every compute unit gets two of them (128 x 262144 x 1152 pooled: 22.4 us against
-      // 23.8 to 25.5; 256 x 65536 x 2304: 16.8 against 18.7 to 19.7); with fewer, the same tile on eight waves
-      // while every unit gets one (512 x 16384 x 2304: 11.9 against 12.8; at K = 4608 18.4 against 17.6), then
-      // 128 x 128 (a quarter of that batch: 9.9 against 12.9 and 13.9 against 18.7).
-      shape = t >= 2 * cu ? 0 : t >= cu ? 1 : 2;
     }
+  } else if (shape < 0 || (emode == 0 && shape < 2)) {
+    shape = conv_shape(p, emode, region);
   }
   switch (shape) {
     case 0: return launch_fp4_shape<2, 4, 2, 2, 2, false>(p, bmode, emode, s, region);  // 128 x 256, 4 waves of 64 x 128

@@ -1418,6 +1418,42 @@ def test_conv_matrix_core_tiles(case, cfg, lean):
         assert np.array_equal(host(run(out="packed", pool=2)).view(np.uint64), pref)
 
 
+CONV_RULE_CASES = [  # C, H, W, kernel, stride
+    (192, 9, 11, 1, 2), (704, 14, 14, 1, 2), (100, 8, 17, 1, 3), (128, 12, 12, 2, 2), (256, 32, 32, 2, 2),   # read once
+    (256, 8, 8, 3, 1), (512, 8, 8, 3, 1),                       # small maps: four or eight waves
+    (512, 14, 14, 3, 2), (704, 13, 13, 3, 2), (1024, 8, 8, 3, 2), (704, 28, 28, 3, 1),  # regions held twice, once, never
+]
+
+
+@pytest.mark.parametrize("tiles", [0.8, 1.9, 2.7, 4.5, 6.2])
+@pytest.mark.parametrize("D", [40, 200])
+@pytest.mark.parametrize("case", CONV_RULE_CASES)
+def test_conv_tile_rule(case, D, tiles):
+    """Every tile and gather that the rule picks by sizes against the staged 128 x 128 tile with the general gather and
+    against a vector-ALU tile (integers: bit for bit)."""
+    C, H, W, k, s = case
+    p = k // 2 if k != 2 else 0
+    OH, OW = (H + 2 * p - k) // s + 1, (W + 2 * p - k) // s + 1
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    N = max(1, round(tiles * cu * 128 / ((D + 127) // 128) / (OH * OW)))
+    print(f"conv tile rule {case} D={D} N={N}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(sum(case) + D + N)
+    Cw = B.packed_words(C)
+    r = lambda *n: torch.randint(-2**63, 2**63 - 1, n, dtype=torch.int64, device=DEV, generator=g)
+    x, w = r(N, H, W, Cw), r(D, k * k, Cw)
+    if C % 64:
+        x[..., -1] &= (1 << C % 64) - 1
+        w[..., -1] &= (1 << C % 64) - 1
+    w = w.reshape(D, k * k * Cw)
+    sc, bi = torch.randn(D, device=DEV, generator=g), torch.randn(D, device=DEV, generator=g)
+    run = lambda **kw: B.bnn_conv2d_packed(x, w, C, D, k, k, (s, s), (p, p), scale=sc, bias=bi, **kw)
+    pools = [0, 2] if OH % 2 == 0 and OW % 2 == 0 else [0]
+    for kw in [dict(out="i32"), dict(out="f32")] + [dict(out="packed", pool=q) for q in pools]:
+        got = run(**kw)
+        assert torch.equal(got, run(cfg=23, lean=0, **kw)), kw
+        assert torch.equal(got, run(cfg=3, lean=0, **kw)), kw
+
+
 def test_gemm_rows_beyond_the_accumulators_exact_range():
     """A wave's share of the row holds more than 2^23 values: its fp32 sums go to integers on the way."""
     K = (1 << 26) + (1 << 24) + 77
