@@ -159,10 +159,15 @@ bnn_status launch_lowk(GemmParams &p, int form, hipStream_t s);
 // Matrix-core GEMM on packed operands (gemm_fp4.hip): bmode / emode as for run_gemm; shape: tile number or -1;
 // region: convolutions may keep a tile's input region in LDS (false: always the general gather).
 bool fp4_applicable(const GemmParams &p);
+// Whether the copy of a region row, its word pairs at a time, leaves more than half of the lanes idle.
+inline bool halo_lanes_idle(const ConvGeom &g) {
+  const int64_t pairs = ((int64_t)(g.OW - 1) * g.sW + g.kW) * ((g.Cw + 1) / 2);
+  return 2 * pairs < (pairs + 63) / 64 * 64;
+}
 bool halo_region(GemmParams &p, int bn, bool pool, int64_t &rows);  // host only: p.halo from p.g and p.Kw64
 bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, int shape, bool region);
 // The same with the reduction axis split over the waves of a workgroup, for few outputs (gemm_fp4_split.hip).
-bool fp4_split_applicable(const GemmParams &p);  // whether its rule on sizes takes the problem
+bool fp4_split_applicable(const GemmParams &p, int bmode);  // whether its rule on sizes takes the problem
 bnn_status launch_gemm_fp4_split(GemmParams &p, int bmode, int emode, hipStream_t s, int shape);
 
 // How the matrix-core kernels store int32 / fp32 maps (gemm.hip): past the caches; whether columns and strides are

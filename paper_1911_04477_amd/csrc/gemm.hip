@@ -931,7 +931,7 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
     p.colperm = emode == 0 && map_columns_by_four(p) ? 1 : 0;
     p.nt_store = emode == 0 && nontemporal_maps(p, bmode) ? 1 : 0;
     if (cfg >= 25 && cfg <= 28) return launch_gemm_fp4_split(p, bmode, emode, s, cfg - 25);
-    if (cfg < 0 && (fp4_split_applicable(p) || !fp4_applicable(p))) return launch_gemm_fp4_split(p, bmode, emode, s, -1);
+    if (cfg < 0 && (fp4_split_applicable(p, bmode) || !fp4_applicable(p))) return launch_gemm_fp4_split(p, bmode, emode, s, -1);
     return launch_gemm_fp4(p, bmode, emode, s, cfg >= 29 ? cfg - 25 : cfg >= 21 ? cfg - 21 : -1, tune.lean != 0);
   }
   // Vector-ALU tiles, with a forced configuration only: the method's own instructions (xor, popcount), measured beside

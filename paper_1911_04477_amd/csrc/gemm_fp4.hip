@@ -629,9 +629,7 @@ static int conv_shape(GemmParams &p, int emode, bool &region) {
   // pairs at a time, are busy (2 x 2 by stride 2, 256 channels of 32 x 32: 23.6 against 20.9; 192 channels of 8 x 8 16.4
   // against 19.8).  Without a stride it is the copy's latency that counts, while there are few tiles (1 x 1 of 128
   // channels, 1.8 tiles a unit: 5.4 against 6.2; 512 channels, 5.6 tiles: 16.1 against 14.4).
-  const int64_t pairs = ((int64_t)(g.OW - 1) * g.sW + g.kW) * ((g.Cw + 1) / 2);
-  const bool idle = 2 * pairs < (pairs + 63) / 64 * 64;
-  const bool once = taps < steps || (taps == steps && (steps > 1 ? idle : emode != 0 && n <= 2));
+  const bool once = taps < steps || (taps == steps && (steps > 1 ? halo_lanes_idle(g) : emode != 0 && n <= 2));
   // Regions that leave a unit one workgroup where it has several tiles to do cost more than gathering, which a stride of 2
   // makes cheap (3 x 3 by stride 2, 704 channels, three 128 x 128 tiles: 40.4 against 53.7; 512 channels, two of 128 x 256:
   // 34.5 against 37.3); with more taps a pixel it takes the third tile (3 x 3, 1024 channels of 56 x 56: 89.9 against

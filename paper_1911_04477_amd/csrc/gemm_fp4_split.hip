@@ -158,9 +158,18 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
   const int nc = (p.Kw64 + 3) >> 2;
   const int per = (nc + KS - 1) / KS;
   const int cb = min(wave * per, nc), ce = min(cb + per, nc);
-  u32x4 a0[WT], b0[WT], a1[WT], b1[WT];
-  if (cb < ce) load_chunk(cb, a0, b0);
-  if (cb + 1 < ce) load_chunk(cb + 1, a1, b1);
+  // 64 x 64 explicit tiles leave the loop between its chunks, which keeps their accumulators where they are (256 x 4096 x 4096
+  // 7.2 -> 6.8 us, 512 x 2048 x 4608 7.5 -> 7.1); the others are up to 3 % faster with a condition around the second chunk.
+  constexpr bool LEAVE = WT == 2 && !CONV;
+  u32x4 a0[WT], b0[WT], a1[WT], b1[WT], ab[2][WT], bb[2][WT];
+  if constexpr (LEAVE) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (cb + u < ce) load_chunk(cb + u, ab[u], bb[u]);
+  } else {
+    if (cb < ce) load_chunk(cb, a0, b0);
+    if (cb + 1 < ce) load_chunk(cb + 1, a1, b1);
+  }
   // the finishing waves' affine constants travel with the operands
   const int mq = m0 + 8 * (wave & 3) + 4 * half;  // first of this lane's rows in row block 0
   const bool row_affine = SIGN || (p.Y && p.axis == BNN_CH_ROW);
@@ -197,24 +206,40 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
   };
 #pragma unroll 1
   for (int c = cb; c < ce; c += 2) {
-    if (c == nc - 1) mask_chunk(c, a0, b0);
-    u32x4 ta[WT], tb[WT];
+    if constexpr (LEAVE) {
 #pragma unroll
-    for (int i = 0; i < WT; ++i) {
-      ta[i] = a0[i];
-      tb[i] = b0[i];
-    }
-    if (c + 2 < ce) load_chunk(c + 2, a0, b0);
-    multiply_chunk(ta, tb);
-    if (c + 1 < ce) {
-      if (c + 1 == nc - 1) mask_chunk(c + 1, a1, b1);
+      for (int u = 0; u < 2; ++u) {
+        if (u > 0 && c + u >= ce) break;  // uniform
+        if (c + u == nc - 1) mask_chunk(c + u, ab[u], bb[u]);
+        u32x4 ta[WT], tb[WT];
+#pragma unroll
+        for (int i = 0; i < WT; ++i) {
+          ta[i] = ab[u][i];
+          tb[i] = bb[u][i];
+        }
+        if (c + u + 2 < ce) load_chunk(c + u + 2, ab[u], bb[u]);
+        multiply_chunk(ta, tb);
+      }
+    } else {
+      if (c == nc - 1) mask_chunk(c, a0, b0);
+      u32x4 ta[WT], tb[WT];
 #pragma unroll
       for (int i = 0; i < WT; ++i) {
-        ta[i] = a1[i];
-        tb[i] = b1[i];
+        ta[i] = a0[i];
+        tb[i] = b0[i];
       }
-      if (c + 3 < ce) load_chunk(c + 3, a1, b1);
+      if (c + 2 < ce) load_chunk(c + 2, a0, b0);
       multiply_chunk(ta, tb);
+      if (c + 1 < ce) {
+        if (c + 1 == nc - 1) mask_chunk(c + 1, a1, b1);
+#pragma unroll
+        for (int i = 0; i < WT; ++i) {
+          ta[i] = a1[i];
+          tb[i] = b1[i];
+        }
+        if (c + 3 < ce) load_chunk(c + 3, a1, b1);
+        multiply_chunk(ta, tb);
+      }
     }
     if (((c - cb + 2) & (FLUSH - 1)) == 0) {
       flush();
@@ -345,36 +370,54 @@ static bnn_status launch_split(GemmParams &p, int bmode, int emode, hipStream_t 
   return launch_status();
 }
 
-// By tiles of 32 x 32 outputs per compute unit:
-//   up to 2: 32 x 32 tiles, K split 8 ways (512 x 64 x 4608 3.7 us, 64 x 64 tiles 7.4 to 8.2, the 128 x 128 kernel 12;
-//            1 x 1024 x 8192 3.8 us; 128 x 4096 x 1152 3.8 against 4.4, 5.1 and 6.3);
-//   short rows up to 5.5: 32 x 32 tiles and 4 ways (128 x 8192 x 1152: 4.3 us, 64 x 64 5.3, 8 ways 6.0, 128 x 128 6.4; the
-//            staged tiles leave most units idle: 256 x 4384 x 576 4.6 against 5.2, with odd columns 4.6 against 6.1, 64
-//            channels of 56 x 56 from 128 6.4 against 7.4; from 6 the other way: 512 channels of 28 x 28 7.5 against 7.0);
-//   one row or one column of tiles, up to 8: the same whatever the depth, a larger tile has nothing to use twice and
-//            computes rows for nothing (4 x 40000 x 1024: 4.1 us, 64 x 64 split 6.7, 64 x 256 staged 5.4; 4 x 40000 x
-//            4096 6.6, 10.2, 10.4; 32 x 65536 x 4096 12.3, 16.0, 12.5; 40000 x 10 x 2048 5.0, 9.4, 15.7), above 6 from
-//            16 words (4 x 65536 x 1024 5.2 against 5.6, x 300 4.7 against 4.5);
-//   from 9 chunks up to 4: 64 x 64 and 8 ways (512 x 2048 x 4608: 7.7 against 9.1 and 12.2);
-//   from 9 chunks up to 8: 64 x 64 and 4 ways (512 x 4096 x 4608: 10.8 against 12.6 on 128 x 128).
-// Beyond, staged tiles reuse their operands better.  -1: does not apply.
-static int split_shape(const GemmParams &p) {
+// By t, tiles of 32 x 32 outputs per compute unit.  Up to 2 latency is all there is: 32 x 32 tiles, K split 8 ways up to 1
+// (1 x 1024 x 8192 3.7 us, 4 ways 4.0; a 3 x 3 layer of 512 channels, 6 images of 4 x 4, 4.9 against 5.0), then 4 (3 x 3 of 320
+// channels at t = 1.1 5.4 against 6.1, 1024 x 485 x 2560 4.5 against 4.7; 64 x 64 tiles 7.4 and 5.9, staged ones 11 and 8), but
+// for the longest gathers (5 x 5 of 512 channels, t = 1.8 11.1 against 10.8).
+// Beyond, a 32 x 32 tile reads twice the operands of a 64 x 64 one for its outputs (32 lines for every load instruction,
+// about 1.1 us for each workgroup that a unit gets at K = 4096) and a 64 x 64 one pays a larger exchange (1.2 us),
+// so it depends on t times the words of a row:
+//   up to 4, where a unit has one 64 x 64 tile: below 240 words 32 x 32 (300 x 2164 x 4096 6.5 against 7.0; 512 x 1551 x 2304 5.2
+//            against 6.0), above 64 x 64 (256 x 4096 x 4096 6.8 against 7.5, 512 x 1124 x 9216 9.0 against 9.9); convolutions
+//            only up to t = 3, the third workgroup (3 x 3 of 512 channels 7.7 against 8.5; 5 x 5 of 100 channels, t = 3.2 7.1
+//            against 6.6), and their 64 x 64 tiles take 8 ways, which share the gather (1024 channels of 8 x 8, t = 3.4: 10.4 against
+//            10.9); short rows 32 x 32 (3 x 3 of 128 channels, t = 3.3 5.3 against 5.4);
+//   up to 8, where it has two: 32 x 32 below 320 words up to 6 (512 x 2380 x 4096 8.7 against 9.7; 64 x 20268 x 2304 6.5 against
+//            7.8), for convolutions up to 5 (3 x 3 of 256 channels of 7 x 7, t = 4.5 7.3 against 8.9, t = 5.9 7.8 against 7.4),
+//            unless of an odd number of words a pixel, gathered word by word; short ones up to 5.5 (t = 5.4 7.2 against 8.0);
+//   short rows beyond that: 64 x 64 for convolutions of small maps, whose regions staged tiles copy with most lanes idle (192
+//            channels of 4 x 4, t = 5.8 8.2 against 10.6 on 128 x 128; 64 of 8 x 8, t = 7.8 5.9 against 6.5; but 100 of 56 x
+//            56, t = 6.1 8.8 against 7.9), else 128 x 128 (100 x 14516 x 512 5.2 against 6.3);
+//   one row or one column of tiles, up to 8: 32 x 32, a larger tile has nothing to use twice and computes rows for nothing
+//            (4 x 40000 x 1024: 4.1 us, 64 x 64 split 6.7, 64 x 256 staged 5.4; 4 x 40000 x 4096 6.6, 10.2, 10.4; 32 x 65536 x
+//            4096 12.3, 16.0, 12.5; 40000 x 10 x 2048 5.0, 9.4, 15.7), above 6 from 16 words (4 x 65536 x 1024 5.2 against 5.6,
+//            x 300 4.7 against 4.5).
+// From 8 on staged tiles reuse their operands better.  -1: does not apply.
+static int split_shape(const GemmParams &p, int bmode) {
   const int64_t t = (((int64_t)p.M + 31) / 32) * (((int64_t)p.N + 31) / 32), cu = p.n_cu;
-  const bool deep = p.Kw64 > 32;  // at least 9 chunks
-  const bool single = p.M <= 32 || p.N <= 32;
-  if (t <= 2 * cu) return 1;
-  if (!deep && 2 * t <= 11 * cu) return 0;
+  const int64_t words = t * p.Kw64 / cu;  // of the tiles of a unit
+  const bool conv = bmode != 0, single = p.M <= 32 || p.N <= 32, short_rows = p.Kw64 <= 32;
+  if (t <= cu || (t <= 2 * cu && conv && p.Kw64 > 160)) return 1;
+  if (t <= 2 * cu) return 0;
   if (single && (t <= 6 * cu || (t <= 8 * cu && p.Kw64 >= 16))) return 0;
-  if (deep && t <= 4 * cu) return 3;
-  if (deep && t <= 8 * cu) return 2;
+  if (short_rows && 2 * t <= 11 * cu) return 0;
+  if (t <= 4 * cu) {
+    if (words <= 240 && (!conv || t <= 3 * cu)) return 0;
+    return conv ? 3 : 2;
+  }
+  if (t <= 8 * cu) {
+    if (short_rows) return conv && p.Kw64 >= 9 && halo_lanes_idle(p.g) ? 2 : -1;
+    if (words <= 320 && (conv ? !(p.g.Cw & 1) && t <= 5 * cu : t <= 6 * cu)) return 0;
+    return 2;
+  }
   // rows beyond the exact range of the other kernel's accumulators
   return p.Kw64 >= (1 << 18) - 2 ? 2 : -1;
 }
 
-bool fp4_split_applicable(const GemmParams &p) { return split_shape(p) >= 0; }
+bool fp4_split_applicable(const GemmParams &p, int bmode) { return split_shape(p, bmode) >= 0; }
 
 bnn_status launch_gemm_fp4_split(GemmParams &p, int bmode, int emode, hipStream_t s, int shape) {
-  switch (shape < 0 ? split_shape(p) : shape) {
+  switch (shape < 0 ? split_shape(p, bmode) : shape) {
     case 0: return launch_split<1, 4>(p, bmode, emode, s);
     case 1: return launch_split<1, 8>(p, bmode, emode, s);
     case 2: return launch_split<2, 4>(p, bmode, emode, s);

@@ -1454,6 +1454,22 @@ def test_conv_tile_rule(case, D, tiles):
         assert torch.equal(got, run(cfg=3, lean=0, **kw)), kw
 
 
+@pytest.mark.parametrize("tiles", [0.9, 1.5, 2.6, 3.9, 4.6, 5.8, 7.9])
+@pytest.mark.parametrize("M,K", [(33, 640), (100, 1600), (256, 2048), (300, 2111), (512, 4096), (96, 9300)])
+def test_gemm_split_rule(M, K, tiles):
+    """Every split that the rule picks by 32 x 32 tiles a unit and words a row, whole and half pieces, against a staged tile and
+    a vector-ALU tile (integers: bit for bit)."""
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    N = max(33, int(tiles * cu / ((M + 31) // 32) * 32) - 3)
+    print(f"split rule {M}x{N}x{K}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    r = lambda n: torch.randint(-2**63, 2**63 - 1, (n, B.packed_words(K)), dtype=torch.int64, device=DEV, generator=g)
+    A, Bm = r(M), r(N)
+    got = B.bnn_xnor_gemm(A, Bm, K)
+    assert torch.equal(got, B.bnn_xnor_gemm(A, Bm, K, cfg=23))
+    assert torch.equal(got, B.bnn_xnor_gemm(A, Bm, K, cfg=3))
+
+
 def test_gemm_rows_beyond_the_accumulators_exact_range():
     """A wave's share of the row holds more than 2^23 values: its fp32 sums go to integers on the way."""
     K = (1 << 26) + (1 << 24) + 77
