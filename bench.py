@@ -212,8 +212,8 @@ def build_workload(name, args):
                 shapes.append((batch, L.cout, L.cin))
         if getattr(net, "_chain", None):  # the convolutions are one launch
             first, last, _ = net._chain
-            n = last + 1 - first
-            shapes = [shapes[:n]] + shapes[n:]
+            k, n = sum(L.kind == "bconv" for L in d["layers"][:first]), last + 1 - first
+            shapes = shapes[:k] + [shapes[k:k + n]] + shapes[k + n:]
         bit_macs = inputs.stack_bit_macs(d["layers"], batch)
 
         def oracle_sample(seconds):
@@ -623,11 +623,11 @@ def main():
     per_launch = [{"kernel": n, "ms": round(t * 1e3, 4), "TBOPS": round(ops * BOPS_PER_LANEOP / t / 1e12, 1)}
                   for n, t, ops in launches]
     if wl.get("replay"):
-        # the stack's convolution launches, each replayed back to back between one event pair
-        idx = [i for i, (n, _, _) in enumerate(launches) if n == dom][:len(wl["replay"])]
-        assert len(idx) == len(wl["replay"]), (len(idx), len(wl["replay"]))
+        # the stack's convolution launches, the first ones of the step, each replayed back to back between one event pair
+        idx = list(range(len(wl["replay"])))
+        assert len(idx) <= len(launches), (len(idx), len(launches))
         rt = replay_launches(wl["replay"])
-        dom_s = sum(rt) + sum(t for i, (n, t, _) in enumerate(launches) if n == dom and i not in idx)
+        dom_s = sum(rt[i] if i < len(rt) else t for i, (n, t, _) in enumerate(launches) if n == dom)
         gemm_s = gemm_s - sum(launches[i][1] for i in idx) + sum(rt)
         for i, t in zip(idx, rt):
             per_launch[i]["ms_replayed"] = round(t * 1e3, 4)

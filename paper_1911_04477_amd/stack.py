@@ -118,23 +118,25 @@ class VggStackFused:
         torch.cuda.synchronize(self.dev)
 
     def _find_chain(self):
-        """(first, last, host array) of the consecutive binarized convolutions that go through bnn_conv_chain in one
-        launch, or None where the layers one by one are expected to be faster (bnn_conv_chain_pays)."""
+        """(first, last, host array) of the last consecutive binarized convolutions that go through bnn_conv_chain in one
+        launch, as many of them as are expected to be faster than the layers one by one (bnn_conv_chain_pays), or None.
+        Two maps of 128 channels of 32 x 32 do not fit LDS: the sixth convolution of the larger stack stays outside (its pass
+        at batch 256 143 -> 121 us)."""
         conv = [i for i, L in enumerate(self.layers) if L.kind == "bconv"]
-        if not conv or conv[0] == 0 or conv != list(range(conv[0], conv[-1] + 1)):
+        if not conv or conv != list(range(conv[0], conv[-1] + 1)):
             return None
-        first, last = conv[0], conv[-1]
-        L0 = self.layers[first]
 
-        def array(weights):
+        def array(some, weights):
             return B.conv_chain_layers([(w, self.p[i]["scale"], self.p[i]["bias"], self.layers[i].cout,
-                                         2 if self.layers[i].pool else 0) for i, w in zip(conv, weights)])
+                                         2 if self.layers[i].pool else 0) for i, w in zip(some, weights)])
 
-        if not B.bnn_conv_chain_pays(self.batch, L0.cin, L0.hw, L0.hw, array([None] * len(conv))):
-            return None
-        for i in conv:
-            self.p[i]["wc"] = B.bnn_pack_conv_chain_weight(self.p[i]["wp"], self.layers[i].cin)
-        return first, last, array([self.p[i]["wc"] for i in conv])
+        for first in conv:
+            L0, some = self.layers[first], list(range(first, conv[-1] + 1))
+            if first > 0 and B.bnn_conv_chain_pays(self.batch, L0.cin, L0.hw, L0.hw, array(some, [None] * len(some))):
+                for i in some:
+                    self.p[i]["wc"] = B.bnn_pack_conv_chain_weight(self.p[i]["wp"], self.layers[i].cin)
+                return first, conv[-1], array(some, [self.p[i]["wc"] for i in some])
+        return None
 
     def capture(self, x: torch.Tensor) -> None:
         """Record one forward pass reading x (its storage, not its present contents) into a HIP
@@ -192,13 +194,14 @@ class VggStackFused:
     def conv_launches(self):
         """One closure per launch of binarized convolutions (a layer's, or the chain's) that re-issues exactly that launch
         on the buffers the last forward() left behind (for timing a launch in isolation)."""
-        if self._chain:
-            first, last, layers = self._chain
-            return [lambda: B.bnn_conv_chain(self.buf[first - 1]["yp"], self.layers[first].cin, layers,
-                                             self.buf[last]["yp"])]
         out = []
         prev = None
-        for L, p, b in zip(self.layers, self.p, self.buf):
+        for i, (L, p, b) in enumerate(zip(self.layers, self.p, self.buf)):
+            if self._chain and i == self._chain[0]:
+                first, last, layers = self._chain
+                out.append(lambda: B.bnn_conv_chain(self.buf[first - 1]["yp"], self.layers[first].cin, layers,
+                                                    self.buf[last]["yp"]))
+                break
             if L.kind == "bconv":
                 src = prev
 

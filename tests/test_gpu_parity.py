@@ -896,12 +896,13 @@ def test_conv_chain(case):
         assert np.array_equal(as_u64(out), ref), rep
 
 
-@pytest.mark.parametrize("batch", [129, 256, 300])
-def test_fused_stack_chain_equals_layers(batch):
-    """The stack's convolutions in one launch and one by one: the same logits, eagerly and replayed."""
-    print(f"fused stack, chain against layers, batch {batch}", flush=True)
+@pytest.mark.parametrize("batch,reading", [(129, "A"), (256, "A"), (300, "A"), (256, "B")])
+def test_fused_stack_chain_equals_layers(batch, reading):
+    """The stack's convolutions in one launch and one by one: the same logits, eagerly and replayed; the larger stack's first
+    binarized convolution stays outside."""
+    print(f"fused stack, chain against layers, batch {batch}, reading {reading}", flush=True)
     from paper_1911_04477_amd.stack import VggStackFused
-    d = inputs.cfg4(batch=batch)
+    d = inputs.cfg4(batch=batch, reading=reading)
     net = VggStackFused(d["layers"], d["params"], batch=batch, device=DEV)
     x = dev(d["x"])
     want, _ = net.forward(x, keep=True)
@@ -909,7 +910,8 @@ def test_fused_stack_chain_equals_layers(batch):
     if batch == 256:
         assert net._chain is not None
         _, names = kernels_of(lambda: net.forward(x))
-        assert names.count("conv_chain") == 1 and len(names) == 4
+        assert names.count("conv_chain") == 1 and len(names) == (4 if reading == "A" else 5)
+        assert len(net.conv_launches()) == (1 if reading == "A" else 2)
     assert np.array_equal(host(net.forward(x)), want)
     net.capture(x)
     for rep in range(3):
