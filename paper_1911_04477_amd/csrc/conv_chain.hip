@@ -559,15 +559,19 @@ extern "C" int bnn_conv_chain_pays(int N, int C, int H, int W, int n_layers, con
   // waves of a SIMD share its matrix unit (64 clocks of 2.4 GHz per matrix instruction of both); as often as images need
   // the units.  Measured 57 us for up to 256 images, whatever their number.
   int64_t chain = 8000, layered = 0;
+  const int64_t cu = device_cu_count(), rounds = (N + cu - 1) / cu;
   for (int i = 0; i < n_layers; ++i) {
     const ChainLayer &L = p.l[i];
-    const int64_t rounds = (L.tiles + CHAIN_WAVES - 1) / CHAIN_WAVES, pieces = 9 * (L.Cw / 2);
-    chain += 3300 + rounds * pieces * (L.wide ? 16 : 8) * 64 * 10 / 24;
-    // Layer by layer: 4 us for a launch and a tile's ends, and 0.41 us per 10^9 multiply-adds (256 images: 20.1, 12.1,
-    // 17.6, 12.5, 19.5 us).
-    layered += 4000 + (int64_t)N * L.P * L.D * 576 * L.Cw / 1000000 * 41 / 100;
+    const int64_t turns = (L.tiles + CHAIN_WAVES - 1) / CHAIN_WAVES, pieces = 9 * (L.Cw / 2);
+    chain += 3300 + turns * pieces * (L.wide ? 16 : 8) * 64 * 10 / 24;
+    // Layer by layer: 4 us for a launch and a tile's ends, and 0.41 us per 10^9 multiply-adds of the tiles of 128 x 128
+    // that a unit gets at most (256 images: 20.1, 12.1, 17.6, 12.5, 19.5 us).  The pass of the whole stack, layers against
+    // chain: 128 images, the last that fill the units evenly, 83.8 us against 83.9; 130 105.5, 87.8; 200 114, 93; 257, a
+    // second round of images, 147, 151; 320 153, 155; 384 164, 157; 512 191, 166.
+    const int64_t bm = L.D <= 64 ? 64 : 128;
+    const int64_t t = ((L.D + bm - 1) / bm) * (((int64_t)N * L.P + 127) / 128), each = (t + cu - 1) / cu;
+    layered += 4000 + each * cu * bm * 128 / 1000 * (576 * L.Cw) / 1000 * 41 / 100;
   }
-  const int64_t cu = device_cu_count(), rounds = (N + cu - 1) / cu;
   return rounds * chain < layered ? 1 : 0;
 }
 
