@@ -276,10 +276,11 @@ __global__ __launch_bounds__(CHAIN_T, 2) void conv_chain_kernel(ChainParams p) {
   auto thresholds = [&](float *d, const ChainLayer &L, int threads) {
     if (tid >= threads) return;
     for (int c = tid; c < L.D; c += threads) {
-      const float scale = d[c], s = scale < 0.0f ? -1.0f : 1.0f;
-      const int t = sign_threshold(scale, d[L.D + c], 576 * L.Cw);
-      d[c] = s;
-      d[L.D + c] = -0.25f * ((float)t + 2.0f * s * (float)__float_as_int(d[2 * L.D + c]));
+      const float scale = d[c];
+      const int t = sign_threshold(scale, d[L.D + c], 576 * L.Cw), ones2 = 2 * __float_as_int(d[2 * L.D + c]);
+      d[c] = scale < 0.0f ? -1.0f : 1.0f;
+      // From an integer: never -0.  The epilogue keeps the sign bit of direction * acc + this, and -1 * 0 + -0 has it set.
+      d[L.D + c] = 0.25f * (float)(scale < 0.0f ? ones2 - t : -ones2 - t);
     }
   };
 

@@ -896,6 +896,35 @@ def test_conv_chain(case):
         assert np.array_equal(as_u64(out), ref), rep
 
 
+@pytest.mark.parametrize("pool", [0, 2])
+def test_conv_chain_zero_at_negative_scale(pool):
+    """A layer's affine map that is exactly 0 is +1 also where scale is negative and the boundary lies at minus twice the set
+    bits of the filter row: the accumulator and the threshold are then both 0.  Filters of 0 to 15 set bits, scales of both
+    signs, the boundary at each of them."""
+    print(f"conv_chain zero at a negative scale, pool={pool}", flush=True)
+    rng = np.random.default_rng(41 + pool)
+    N, C, H, W, D = 2, 128, 16, 16, 128
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    w = np.full((D, C * 9), -1.0, np.float32)
+    ones = np.arange(D) % 16
+    for d in range(D):
+        w[d, rng.choice(C * 9, ones[d], replace=False)] = 1.0
+    w = w.reshape(D, C, 3, 3)
+    sc = np.where(np.arange(D) < D // 2, -0.5, 0.5).astype(np.float32)
+    bi = (sc * 2.0 * ones).astype(np.float32)  # 0 at an accumulator of -2 * ones
+    acc = oracle.conv2d_pm1(x, w, (1, 1), (1, 1))
+    if pool:
+        acc = oracle.maxpool2x2_i32(acc)
+    y = oracle.scale_bias(acc, sc, bi, "nchw")
+    zeros = (y == 0).reshape(N, D, -1).sum(axis=(0, 2))
+    assert (zeros[sc < 0] > 0).sum() >= 16 and (zeros[sc > 0] > 0).sum() >= 16  # the boundary is met, not only stood beside
+    ref = oracle.pack_nhwc(y)
+    wc, dsc, dbi = B.bnn_pack_conv_chain_weight(B.bnn_pack_conv_weight(dev(w)), C), dev(sc), dev(bi)
+    out = torch.zeros(ref.shape, dtype=torch.int64, device=DEV)
+    B.bnn_conv_chain(_u64dev(oracle.pack_nhwc(x)), C, B.conv_chain_layers([(wc, dsc, dbi, D, pool)]), out)
+    assert np.array_equal(as_u64(out), ref)
+
+
 @pytest.mark.parametrize("batch,reading", [(129, "A"), (256, "A"), (300, "A"), (256, "B")])
 def test_fused_stack_chain_equals_layers(batch, reading):
     """The stack's convolutions in one launch and one by one: the same logits, eagerly and replayed; the larger stack's first
