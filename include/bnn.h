@@ -165,9 +165,9 @@ BNN_API bnn_status bnn_xnor_gemm_epilogue(const uint64_t *A, int64_t lda, const 
  *   out_i32   [N, D, OH, OW] int32 or NULL;  out_f32 same shape fp32 or NULL (not both NULL)
  *   scale, bias  [D] fp32, required iff out_f32 != NULL:
  *             out_f32 = fma(scale[d], (float)acc, bias[d])
- *   workspace at least bnn_conv2d_workspace_bytes(...) bytes (device, 16-byte aligned): scratch for
- *             the packed NHWC image (1 bit per input value) the GEMM gathers its taps from; no patch
- *             matrix is materialised.  Contents undefined afterwards (pointwise layers mostly leave it alone).
+ *   workspace at least bnn_conv2d_workspace_bytes(...) bytes (device, 16-byte aligned): it
+ *             receives the packed NHWC image (1 bit per input value; of a 1x1 layer without padding
+ *             the pixels that it samples); no patch matrix is materialised.
  */
 BNN_API bnn_status bnn_conv2d(const float *x, const uint64_t *w_packed, int N, int C, int H, int W, int D,
                       int kH, int kW, int sH, int sW, int pH, int pW, int32_t *out_i32,

@@ -178,7 +178,7 @@ bool map_rows_start_every(const GemmParams &p, uint32_t ints);  // multiples of 
 
 // Pointwise convolution from the fp32 image in one launch (conv_pointwise.hip).
 bool pointwise_applicable(const GemmParams &p);
-bnn_status launch_conv_pointwise(GemmParams &p, const float *x, hipStream_t s);
+bnn_status launch_conv_pointwise(GemmParams &p, const float *x, uint64_t *img, hipStream_t s);
 
 // The binarization predicate: +0.0 and -0.0 -> 1, negative and NaN -> 0.
 __device__ __forceinline__ bool sign_bit(float v) { return v >= 0.0f; }

@@ -444,7 +444,7 @@ static bnn_status conv2d_impl(const float *x, const uint64_t *w_packed, int N, i
   if (kH == 1 && kW == 1 && pH == 0 && pW == 0) {
     // no patch expansion: encode and multiply only the sampled pixels
     GemmParams p = conv_gemm(nullptr, w_packed, N, C, H, W, D, 1, 1, sH, sW, 0, 0, 0, out_i32, out_f32, nullptr, scale, bias);
-    if (tune.cfg < 0 && pointwise_applicable(p)) return launch_conv_pointwise(p, x, s);
+    if (tune.cfg < 0 && pointwise_applicable(p)) return launch_conv_pointwise(p, x, img, s);
     // the same in two launches: a stride-1 1x1 problem on the encoded pixels
     const int OH = (int)bnn_conv_out_dim(H, 1, sH, 0), OW = (int)bnn_conv_out_dim(W, 1, sW, 0);
     st = launch_encode_nchw(x, N, C, H, W, OH, OW, sH, sW, img, s);

@@ -4,7 +4,7 @@
 // Bound by memory: 4 bytes read per input value used (whole 128-byte lines where a stride skips columns), 4 or 8
 // written per output; the multiplication is a few thousand clocks a workgroup.  Encoding in a launch of its own reads
 // while nothing is written, and the multiplication after it writes while nothing is read; here some workgroups of a
-// unit read while others write, the packed image makes no round trip, and there is one launch instead of two.
+// unit read while others write, the packed image is not read back, and there is one launch instead of two.
 #include <algorithm>
 
 #include "common.h"
@@ -15,6 +15,7 @@ namespace bnn {
 struct PointwiseParams {
   GemmParams p;  // A, M, N, Kw64, lda32, Kformula, outputs; p.g: the image's geometry (act unused)
   const float *x;
+  uint64_t *img; // the sampled pixels' words leave there too: bnn_conv2d's workspace receives the packed image
   int rs;        // dwords between two pixels' rows in LDS
   int chunks;    // of 256 bits of a row
   int ytiles;    // workgroups that share a pixel tile's output channels
@@ -69,13 +70,24 @@ __global__ __launch_bounds__(256, 3) void conv_pointwise_kernel(PointwiseParams 
     }
   }
 
+  __syncthreads();  // the pixels' bits are there
+  if (blockIdx.y == 0) {
+    // The packed image, whole lines.  64 x 200 x 56 x 56 by stride 2: 33.5 us without it, 33.75 with; 240 random layers 0.7 % on
+    // average, to 6 % (behind the multiplication 1.0 and 1.8 %, half words straight from the encoding lanes 2.5 %).
+    const uint32_t Cw = (uint32_t)g.Cw, words = (uint32_t)min(64 * NC, p.N - n0) * Cw;
+    uint64_t *const out = q.img + (size_t)n0 * Cw;
+    for (uint32_t j = threadIdx.x; j < words; j += 256u) {
+      const uint32_t pix = fdiv_sel(j, g.divCw), cw = j - pix * Cw;
+      out[j] = *reinterpret_cast<const uint64_t *>(sB + pix * (uint32_t)q.rs + 2u * cw);
+    }
+  }
+
   // ---- multiply: a wave 32 * WTM channels x 64 pixels at a time ------------------------------------------
   constexpr int BM = 4 / NC * 32 * WTM;
   const int wr = wave / NC, nw = n0 + 64 * (wave % NC);
   const bool a16 = p.b_vec16 != 0;  // uniform: rows of A may be read with 16-byte loads
   const bool affine = p.Y != nullptr;
   for (int m_tile = (int)blockIdx.y * BM; m_tile < p.M; m_tile += q.ytiles * BM) {
-    __syncthreads();  // the pixels' bits are there; the last round's constants have been read
     if (affine && threadIdx.x < BM) {
       const int m = min(m_tile + (int)threadIdx.x, p.M - 1);
       sSc[threadIdx.x] = p.scale[m];
@@ -127,6 +139,7 @@ __global__ __launch_bounds__(256, 3) void conv_pointwise_kernel(PointwiseParams 
     }
     __syncthreads();  // the constants are there
     store_maps<WTM, 2, MS>(p, acc, m0, nw, lane, sSc + 32 * WTM * wr, sBi + 32 * WTM * wr);
+    if (m_tile + q.ytiles * BM < p.M) __syncthreads();  // the constants have been read
   }
 }
 
@@ -157,14 +170,16 @@ bool pointwise_applicable(const GemmParams &p) {
   return !(g.C > 32 && g.C <= 64 && p.M >= 2 * g.C && bytes >= 150000000);
 }
 
-// p: the GEMM of the sampled pixels (as for run_gemm, maps only); p.g: the image as it is, OH x OW sampled by sH, sW.
-bnn_status launch_conv_pointwise(GemmParams &p, const float *x, hipStream_t s) {
+// p: the GEMM of the sampled pixels (as for run_gemm, maps only); p.g: the image as it is, OH x OW sampled by sH, sW;
+// img: receives their words.
+bnn_status launch_conv_pointwise(GemmParams &p, const float *x, uint64_t *img, hipStream_t s) {
   PointwiseParams q;
   p.colperm = map_columns_by_four(p) ? 1 : 0;
   p.nt_store = nontemporal_maps(p, 1) ? 1 : 0;
   p.b_vec16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0;
   q.p = p;
   q.x = x;
+  q.img = img;
   q.chunks = (p.Kw64 + 3) / 4;
   q.rs = 8 * q.chunks + 4;  // rows of 16-byte pieces, on distinct banks
   const int64_t cu = device_cu_count();

@@ -344,6 +344,22 @@ def test_conv2d_pointwise_one_launch(case, one):
     assert np.array_equal(host(run(scale=sc, bias=bi, want_int=False)[1]), host(of))
 
 
+@pytest.mark.parametrize("case", [c for c, _ in POINTWISE_CASES] + [(2, 200, 9, 7, 33, 1, 3)])
+def test_conv2d_workspace_receives_the_packed_image(case):
+    """What bnn_conv2d leaves in the workspace: the packed image, of a pointwise layer the pixels that it samples; nothing
+    behind it."""
+    print(f"conv2d workspace case={case}", flush=True)
+    N, C, H, W, D, s, k = case if len(case) == 7 else (*case, 1)
+    g = torch.Generator(device=DEV).manual_seed(sum(case))
+    x = torch.randn(N, C, H, W, device=DEV, generator=g)
+    wp = B.bnn_pack_conv_weight(torch.randn(D, C, k, k, device=DEV, generator=g))
+    want = B.bnn_im2col_packed(x, 1, 1, (s, s) if k == 1 else (1, 1), (0, 0)).view(-1)
+    ws = torch.full((max(16, B.conv2d_workspace_bytes(x.shape, k, k, (s, s), (k // 2, k // 2))) + 64,), 0x5A, dtype=torch.uint8, device=DEV)
+    B.bnn_conv2d(x, wp, D, k, k, (s, s), (k // 2, k // 2), workspace=ws)
+    assert torch.equal(ws[:8 * want.numel()].view(torch.int64), want)
+    assert bool((ws[8 * want.numel():] == 0x5A).all())
+
+
 def test_gemm_table1_truth_table():
     """Table 1 of the paper through encode + GEMM with K = 1 (63 masked tail bits)."""
     print("gemm truth table", flush=True)
