@@ -443,9 +443,27 @@ def bnn_pack_conv_chain_weight(w_packed: torch.Tensor, C: int) -> torch.Tensor:
     return out
 
 
+def _chain_weight(w: torch.Tensor, C: int, D: int) -> None:
+    _dev(w, torch.uint8, "w_chain")
+    need = int(_c().bnn_conv_chain_weight_bytes(C, D))
+    if not w.is_contiguous() or w.numel() < need:
+        raise ValueError(f"w_chain: {need} contiguous bytes for {C} to {D} channels")
+
+
 def conv_chain_layers(layers) -> ctypes.Array:
-    """[(w_chain or None, scale, bias, D, pool)] -> the host array bnn_conv_chain takes (pointers of live tensors)."""
-    return (ChainLayer * len(layers))(*[ChainLayer(_ptr(w), _ptr(s), _ptr(b), D, pool) for w, s, b, D, pool in layers])
+    """[(w_chain or None, scale, bias, D, pool)] -> the host array bnn_conv_chain takes.  It holds the tensors whose
+    addresses it contains (`tensors`), so they live as long as it does.  w_chain None: for bnn_conv_chain_pays alone."""
+    layers = [tuple(L) for L in layers]
+    for i, (w, s, b, D, pool) in enumerate(layers):
+        for t, name in ((s, "scale"), (b, "bias")):
+            _dev(t, torch.float32, name)
+            if not t.is_contiguous() or t.numel() < D:
+                raise ValueError(f"{name}: {D} contiguous values")
+        if w is not None and i > 0:  # the first layer's: where its input channels are known
+            _chain_weight(w, layers[i - 1][3], D)
+    out = (ChainLayer * len(layers))(*[ChainLayer(_ptr(w), _ptr(s), _ptr(b), D, pool) for w, s, b, D, pool in layers])
+    out.tensors = [L[:3] for L in layers]
+    return out
 
 
 def bnn_conv_chain_pays(N: int, C: int, H: int, W: int, layers: ctypes.Array) -> bool:
@@ -458,6 +476,9 @@ def bnn_conv_chain(xp: torch.Tensor, C: int, layers: ctypes.Array, out: torch.Te
     _dev(out, torch.int64, "out")
     N, H, W, Cw = xp.shape
     assert xp.is_contiguous() and out.is_contiguous() and Cw == packed_words(C)
+    held = getattr(layers, "tensors", None)  # an array of another origin is the caller's own
+    if held and held[0][0] is not None:
+        _chain_weight(held[0][0], C, layers[0].D)
     OH, OW = H, W
     for L in layers:
         if L.pool:

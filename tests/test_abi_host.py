@@ -412,3 +412,49 @@ def test_binding_calls_equal_ctypes(L):
         c.bnn_packed_words(K=1)
     skipped = {n for n in [*B.SIGNATURES, *B.TESTING_SIGNATURES] if not hasattr(c, n)}
     assert skipped == {"bnn_status_str", "bnn_kernel_name"}, skipped  # what returns a string stays with ctypes
+
+
+class _Gpu:
+    """What the binding looks at of a GPU tensor."""
+    is_cuda = True
+
+    def __init__(self, dtype, n, contiguous=True):
+        self.dtype, self.n, self.contiguous = dtype, n, contiguous
+
+    def data_ptr(self):
+        return 4096
+
+    def numel(self):
+        return self.n
+
+    def is_contiguous(self):
+        return self.contiguous
+
+
+def test_conv_chain_layers_hold_and_check_their_tensors():
+    """The host array keeps what it points to alive, and takes tensors of the types and sizes that the kernel reads only."""
+    import gc
+    import weakref
+    import torch
+    f32 = lambda n=128: _Gpu(torch.float32, n)
+    u8 = lambda C=128, D=128: _Gpu(torch.uint8, B.lib().bnn_conv_chain_weight_bytes(C, D))
+    w, s, b = u8(), f32(), f32()
+    refs = [weakref.ref(t) for t in (w, s, b)]
+    arr = B.conv_chain_layers([(w, s, b, 128, 0)])
+    del w, s, b
+    gc.collect()
+    assert all(r() is not None for r in refs)
+    del arr
+    gc.collect()
+    assert all(r() is None for r in refs)
+    ok = (u8(), f32(), f32(), 128, 0)
+    assert len(B.conv_chain_layers([ok, (u8(128, 64), f32(64), f32(64), 64, 0)])) == 2
+    B.conv_chain_layers([(None, f32(), f32(), 128, 0)])
+    for bad in (_Gpu(torch.float64, 128), torch.zeros(128)):  # type; not on a GPU
+        for layer in ((u8(), bad, f32(), 128, 0), (u8(), f32(), bad, 128, 0), (bad, f32(), f32(), 128, 0)):
+            with pytest.raises(TypeError):
+                B.conv_chain_layers([ok, layer])
+    for layer in ((u8(), f32(127), f32(), 128, 0), (u8(), f32(), _Gpu(torch.float32, 128, False), 128, 0),
+                  (u8(128, 64), f32(), f32(), 128, 0), (u8(128, 256), f32(256), f32(256), 320, 0)):
+        with pytest.raises(ValueError):
+            B.conv_chain_layers([ok, layer])
