@@ -211,7 +211,7 @@ def build_workload(name, args):
             elif L.kind == "bfc":
                 shapes.append((batch, L.cout, L.cin))
         if getattr(net, "_chain", None):  # the convolutions are one launch
-            first, last, _ = net._chain
+            first, last = net._chain.first, net._chain.last
             k, n = sum(L.kind == "bconv" for L in d["layers"][:first]), last + 1 - first
             shapes = shapes[:k] + [shapes[k:k + n]] + shapes[k + n:]
         bit_macs = inputs.stack_bit_macs(d["layers"], batch)

@@ -433,12 +433,15 @@ def bnn_conv2d_packed(xp: torch.Tensor, w_packed: torch.Tensor, C: int, D: int, 
     return op if op is not None else (oi if oi is not None else of)
 
 
-def bnn_pack_conv_chain_weight(w_packed: torch.Tensor, C: int) -> torch.Tensor:
+def bnn_pack_conv_chain_weight(w_packed: torch.Tensor, C: int, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Filter bank of a 3x3 layer from bnn_pack_conv_weight, in the order in which bnn_conv_chain multiplies it."""
     _dev(w_packed, torch.int64, "w_packed")
     D = w_packed.shape[0]
     assert w_packed.is_contiguous() and w_packed.shape[1] == conv_kwords(C, 3, 3)
-    out = torch.empty(max(16, int(_c().bnn_conv_chain_weight_bytes(C, D))), dtype=torch.uint8, device=w_packed.device)
+    if out is None:
+        out = torch.empty(max(16, int(_c().bnn_conv_chain_weight_bytes(C, D))), dtype=torch.uint8, device=w_packed.device)
+    else:
+        _chain_weight(out, C, D)
     _check(_c().bnn_pack_conv_chain_weight(_ptr(w_packed), D, C, _ptr(out), _stream()), "bnn_pack_conv_chain_weight")
     return out
 

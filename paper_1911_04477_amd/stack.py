@@ -78,11 +78,68 @@ class VggStack:
         return (h, acts) if keep else h
 
 
+class _ChainWeight:
+    """A layer's packed filters and the copy of them in the order in which bnn_conv_chain multiplies.  The copy follows
+    in-place changes of the filters by torch's version counter (inference tensors have none: it is renewed every time)."""
+
+    def __init__(self, wp: torch.Tensor, cin: int):
+        self.wp, self.cin, self.counted = wp, cin, not wp.is_inference()
+        self.version = wp._version if self.counted else None
+        self.wc = B.bnn_pack_conv_chain_weight(wp, cin)
+
+    def refresh(self) -> None:
+        if self.counted and self.wp._version == self.version:
+            return
+        self.version = self.wp._version if self.counted else None
+        B.bnn_pack_conv_chain_weight(self.wp, self.cin, out=self.wc)
+
+
+class _Chain:
+    """Layers first .. last of a net through bnn_conv_chain, from the parameters that it holds when a pass is issued."""
+
+    def __init__(self, first: int, last: int):
+        self.first, self.last = first, last
+        self.weights: Dict[int, _ChainWeight] = {}
+        self.array = None
+
+    def __getstate__(self):  # a copied net packs its own
+        return {"first": self.first, "last": self.last, "weights": {}, "array": None}
+
+    def host_array(self, net: "VggStackFused"):
+        """Packed again, or built again, where a parameter has been changed or replaced since the last pass."""
+        held = self.array.tensors if self.array is not None else None
+        same = held is not None
+        for k, i in enumerate(range(self.first, self.last + 1)):
+            p = net.p[i]
+            w = self.weights.get(i)
+            if w is None or w.wp is not p["wp"]:  # w holds its tensor: the identity is not another's
+                self.weights[i], same = _ChainWeight(p["wp"], net.layers[i].cin), False
+            else:
+                w.refresh()
+            same = same and held[k][1] is p["scale"] and held[k][2] is p["bias"]
+        if not same:
+            self.array = _chain_array(net, {i: w.wc for i, w in self.weights.items()}, self.first, self.last)
+        return self.array
+
+    def run(self, net: "VggStackFused", x: torch.Tensor) -> torch.Tensor:
+        return B.bnn_conv_chain(x, net.layers[self.first].cin, self.host_array(net), net.buf[self.last]["yp"])
+
+
+def _chain_array(net: "VggStackFused", weights: Dict[int, torch.Tensor], first: int, last: int):
+    return B.conv_chain_layers([(weights.get(i), net.p[i]["scale"], net.p[i]["bias"], net.layers[i].cout,
+                                 2 if net.layers[i].pool else 0) for i in range(first, last + 1)])
+
+
 class VggStackFused:
     """The same stack with activations kept packed between layers (1 bit per activation):
     real-valued first layer with binarized output, binarized convolutions whose GEMM store
     does max-pool + affine + sign + pack, and the binarized FC on the packed map with its
-    weight re-ordered to the (h, w, c) bit order.  Same arithmetic, same results."""
+    weight re-ordered to the (h, w, c) bit order.  Same arithmetic, same results.
+
+    A pass takes the parameters that p holds when it is issued.  Layers that go through bnn_conv_chain multiply a
+    re-ordered copy of p[i]["wp"], which follows a replaced tensor and in-place changes that torch counts (copy_, indexing,
+    other operators; in replay() of the tensors that were captured), not writes past torch's version counter (through
+    .data, or by a raw address)."""
 
     def __init__(self, layers: Sequence, params: Sequence[Dict[str, np.ndarray]], batch: int, device="cuda:0"):
         self.layers = list(layers)
@@ -98,7 +155,8 @@ class VggStackFused:
                 b["yp"] = torch.empty((batch, L.hw, L.hw, B.packed_words(L.cout)), dtype=torch.int64, device=self.dev)
                 hw_c = (L.cout, L.hw, L.hw)
             elif L.kind == "bconv":
-                d["wp"] = B.bnn_pack_conv_weight(d["w"])
+                with torch.inference_mode(False):  # a version counter: see _ChainWeight
+                    d["wp"] = B.bnn_pack_conv_weight(d["w"])
                 o = L.hw // 2 if L.pool else L.hw
                 b["yp"] = torch.empty((batch, o, o, B.packed_words(L.cout)), dtype=torch.int64, device=self.dev)
                 hw_c = (L.cout, o, o)
@@ -118,24 +176,19 @@ class VggStackFused:
         torch.cuda.synchronize(self.dev)
 
     def _find_chain(self):
-        """(first, last, host array) of the last consecutive binarized convolutions that go through bnn_conv_chain in one
-        launch, as many of them as are expected to be faster than the layers one by one (bnn_conv_chain_pays), or None.
+        """The last consecutive binarized convolutions that go through bnn_conv_chain in one launch, as many of them as are
+        expected to be faster than the layers one by one (bnn_conv_chain_pays), or None.
         Two maps of 128 channels of 32 x 32 do not fit LDS: the sixth convolution of the larger stack stays outside (its pass
         at batch 256 143 -> 121 us)."""
         conv = [i for i, L in enumerate(self.layers) if L.kind == "bconv"]
         if not conv or conv != list(range(conv[0], conv[-1] + 1)):
             return None
-
-        def array(some, weights):
-            return B.conv_chain_layers([(w, self.p[i]["scale"], self.p[i]["bias"], self.layers[i].cout,
-                                         2 if self.layers[i].pool else 0) for i, w in zip(some, weights)])
-
         for first in conv:
-            L0, some = self.layers[first], list(range(first, conv[-1] + 1))
-            if first > 0 and B.bnn_conv_chain_pays(self.batch, L0.cin, L0.hw, L0.hw, array(some, [None] * len(some))):
-                for i in some:
-                    self.p[i]["wc"] = B.bnn_pack_conv_chain_weight(self.p[i]["wp"], self.layers[i].cin)
-                return first, conv[-1], array(some, [self.p[i]["wc"] for i in some])
+            L0 = self.layers[first]
+            if first > 0 and B.bnn_conv_chain_pays(self.batch, L0.cin, L0.hw, L0.hw, _chain_array(self, {}, first, conv[-1])):
+                chain = _Chain(first, conv[-1])
+                chain.host_array(self)
+                return chain
         return None
 
     def capture(self, x: torch.Tensor) -> None:
@@ -154,11 +207,16 @@ class VggStackFused:
         with torch.cuda.graph(g):
             self._graph_out = self.forward(x)
         self._graph = g
+        # what the graph reads: its tensors live as long as it does, and replay() keeps the copies in step with the filters
+        self._graph_weights = list(self._chain.weights.values()) if self._chain else []
+        self._graph_array = self._chain.array if self._chain else None
 
     def replay(self) -> torch.Tensor:
         """Re-run the captured pass on the current contents of the captured input."""
         if self._graph is None:
             raise RuntimeError("capture() first")
+        for w in self._graph_weights:
+            w.refresh()
         self._graph.replay()
         return self._graph_out
 
@@ -167,9 +225,9 @@ class VggStackFused:
         acts = []
         chain = None if keep else self._chain  # the maps inside the chain never reach memory
         for i, (L, p, b) in enumerate(zip(self.layers, self.p, self.buf)):
-            if chain and chain[0] <= i <= chain[1]:
-                if i == chain[0]:
-                    h = B.bnn_conv_chain(h, L.cin, chain[2], self.buf[chain[1]]["yp"])
+            if chain and chain.first <= i <= chain.last:
+                if i == chain.first:
+                    h = chain.run(self, h)
                 continue
             if L.kind == "conv_f32":
                 h = B.bnn_conv2d_f32_sign(h, p["w"], p["scale"], p["bias"], (1, 1), (1, 1), out=b["yp"])
@@ -197,10 +255,8 @@ class VggStackFused:
         out = []
         prev = None
         for i, (L, p, b) in enumerate(zip(self.layers, self.p, self.buf)):
-            if self._chain and i == self._chain[0]:
-                first, last, layers = self._chain
-                out.append(lambda: B.bnn_conv_chain(self.buf[first - 1]["yp"], self.layers[first].cin, layers,
-                                                    self.buf[last]["yp"]))
+            if self._chain and i == self._chain.first:
+                out.append(lambda: self._chain.run(self, self.buf[self._chain.first - 1]["yp"]))
                 break
             if L.kind == "bconv":
                 src = prev

@@ -964,6 +964,50 @@ def test_fused_stack_chain_equals_layers(batch, reading):
         assert np.array_equal(host(net.forward(x)), want), rep
 
 
+@pytest.mark.parametrize("inference", [False, True])
+def test_fused_stack_chain_follows_its_parameters(inference):
+    """Parameters of layers inside the chain that are changed in place or replaced after construction count from the next
+    pass on, eagerly as in the layers one by one; a captured pass reads the tensors that it was captured with."""
+    print(f"fused stack, chain follows its parameters, inference mode {inference}", flush=True)
+    import copy
+    from paper_1911_04477_amd.stack import VggStackFused
+    batch = 160
+    d, e = inputs.cfg4(batch=batch), inputs.cfg4(batch=batch, seed=inputs.BASE_SEED + 77)
+    x = dev(d["x"])
+    with torch.inference_mode(inference):
+        net = VggStackFused(d["layers"], d["params"], batch=batch, device=DEV)
+        other = VggStackFused(e["layers"], e["params"], batch=batch, device=DEV)
+        assert net._chain is not None
+        layers = lambda: host(net.forward(x, keep=True)[0]).copy()
+        i, j = net._chain.first + 1, net._chain.last
+        first = layers()
+        net.capture(x)
+
+        def check(replayed):
+            want = layers()
+            _, names = kernels_of(lambda: net.forward(x))
+            assert names.count("conv_chain") == 1
+            assert np.array_equal(host(net.forward(x)), want)
+            assert np.array_equal(host(net.replay()), want if replayed is None else replayed)
+            return want
+        assert np.array_equal(check(None), first)
+        net.p[i]["wp"].copy_(other.p[i]["wp"])              # in place: the captured pass follows
+        a = check(None)
+        net.p[j]["scale"].neg_()
+        net.p[j]["bias"][3:40] += 25.0
+        b = check(None)
+        net.p[j]["wp"] = other.p[j]["wp"].clone()           # another tensor: the captured pass keeps its own
+        c = check(b)
+        net.p[j]["scale"], net.p[j]["bias"] = net.p[j]["scale"].abs(), net.p[j]["bias"] * 2 - 1
+        net.p[i] = dict(net.p[i], wp=net.p[i]["wp"].flip(0).contiguous())
+        f = check(b)
+        assert len({v.tobytes() for v in (first, a, b, c, f)}) == 5  # every change showed
+        net._graph = net._graph_out = None
+        net._graph_weights = net._graph_array = None
+        twin = copy.deepcopy(net)
+        assert np.array_equal(host(twin.forward(x)), f) and twin.p[j]["wp"] is not net.p[j]["wp"]
+
+
 # ---------------------------------------------------------------- MFMA ablation
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (37, 150, 300), (128, 128, 64), (130, 257, 1152), (64, 64, 256),
                                    (200, 333, 2304 + 17), (5, 700, 63),
