@@ -33,8 +33,10 @@ typedef int64_t (*any_function)(int64_t, int64_t, int64_t, int64_t, int64_t, int
                                 int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t,
                                 int64_t, int64_t, int64_t, int64_t);
 
-/* As ctypes converts: an integer's low bits; None only for a pointer. */
-static int convert(PyObject *o, char type, int64_t *v) {
+static PyObject *argument_error; /* ctypes.ArgumentError, what such calls have always raised, and a TypeError */
+
+/* As ctypes converts: an integer's low bits; None only for a pointer.  at: position of the argument. */
+static int convert(PyObject *o, char type, Py_ssize_t at, int64_t *v) {
   if (PyLong_Check(o)) {
     *v = (int64_t)PyLong_AsUnsignedLongLongMask(o);
     return 0;
@@ -43,10 +45,15 @@ static int convert(PyObject *o, char type, int64_t *v) {
     *v = 0;
     return 0;
   }
-  o = PyNumber_Index(o); /* numpy integers and the like */
-  if (!o) return -1;
-  *v = (int64_t)PyLong_AsUnsignedLongLongMask(o);
-  Py_DECREF(o);
+  PyObject *i = PyNumber_Index(o); /* numpy integers and the like */
+  if (!i) {
+    if (PyErr_ExceptionMatches(PyExc_TypeError))
+      PyErr_Format(argument_error, "argument %zd: %s expected instead of %.200s", at + 1,
+                   type == 'p' ? "an address or None" : "an integer", Py_TYPE(o)->tp_name);
+    return -1;
+  }
+  *v = (int64_t)PyLong_AsUnsignedLongLongMask(i);
+  Py_DECREF(i);
   return 0;
 }
 
@@ -59,7 +66,7 @@ static PyObject *function_call(PyObject *self, PyObject *const *args, size_t nar
   }
   int64_t a[MAX_ARGS] = {0};
   for (Py_ssize_t i = 0; i < n; ++i)
-    if (convert(args[i], f->args[i], &a[i])) return NULL;
+    if (convert(args[i], f->args[i], i, &a[i])) return NULL;
   int64_t r;
   Py_BEGIN_ALLOW_THREADS
   r = ((any_function)f->address)(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10], a[11], a[12], a[13],
@@ -105,6 +112,16 @@ static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", NULL, -1
 
 PyMODINIT_FUNC PyInit__fastcall(void) {
   if (PyType_Ready(&function_type) < 0) return NULL;
+  if (!argument_error) {
+    PyObject *ctypes = PyImport_ImportModule("ctypes");
+    PyObject *base = ctypes ? PyObject_GetAttrString(ctypes, "ArgumentError") : NULL;
+    PyObject *bases = base ? PyTuple_Pack(2, base, PyExc_TypeError) : NULL;
+    if (bases) argument_error = PyErr_NewException("_fastcall.ArgumentError", bases, NULL);
+    Py_XDECREF(bases);
+    Py_XDECREF(base);
+    Py_XDECREF(ctypes);
+    if (!argument_error) return NULL;
+  }
   PyObject *m = PyModule_Create(&module);
   if (!m) return NULL;
   Py_INCREF(&function_type);

@@ -414,6 +414,17 @@ def test_binding_calls_equal_ctypes(L):
     assert skipped == {"bnn_status_str", "bnn_kernel_name"}, skipped  # what returns a string stays with ctypes
 
 
+def test_binding_refuses_arguments_as_ctypes_does(L):
+    """A wrong argument type is ctypes.ArgumentError with the helper and without (the helper's is a TypeError as well)."""
+    import ctypes
+    for f in (B._c(), L):
+        for bad in ((1.5,), (None,), ("1",)):
+            with pytest.raises(ctypes.ArgumentError):
+                f.bnn_packed_words(*bad)
+        with pytest.raises(ctypes.ArgumentError):
+            f.bnn_encode(1.5, 1, 64, 64, 16, 1, None)
+
+
 class _Gpu:
     """What the binding looks at of a GPU tensor."""
     is_cuda = True
