@@ -9,7 +9,9 @@ built, loading fails loudly.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
+import warnings
 from typing import List, Optional, Tuple
 
 import torch
@@ -86,6 +88,21 @@ CH_NONE, CH_ROW, CH_COL = 0, 1, 2
 _lib: Optional[ctypes.CDLL] = None
 
 
+FASTCALL_PATH = LIB_PATH.replace("libbnn", "_fastcall")
+
+
+def _fastcall():
+    """The call helper, or None (with a warning) where only libbnn has been built."""
+    if not os.path.exists(FASTCALL_PATH):
+        warnings.warn(f"{FASTCALL_PATH} is missing: build it with `python paper_1911_04477_amd/build.py`; until then calls "
+                      "go through ctypes, 0.4 to 0.9 us slower each", RuntimeWarning, stacklevel=4)
+        return None
+    spec = importlib.util.spec_from_file_location("paper_1911_04477_amd._fastcall", FASTCALL_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    return module
+
+
 class _Calls:
     """The functions of SIGNATURES and TESTING_SIGNATURES whose arguments are integers and raw pointers, called without
     ctypes' conversions (csrc/fastcall.c)."""
@@ -93,12 +110,14 @@ class _Calls:
     _KINDS = {_p: "p", _i64: "q", _i32: "i", _sz: "z"}
 
     def __init__(self, L: ctypes.CDLL):
-        from ._fastcall import Function
+        fast = _fastcall()
         for name, (res, args) in list(SIGNATURES.items()) + list(TESTING_SIGNATURES.items()):
-            kinds = ["p" if isinstance(a, type) and issubclass(a, ctypes._Pointer) else self._KINDS.get(a) for a in args]
-            if res in (_i32, _i64, _sz) and None not in kinds:
-                address = ctypes.cast(getattr(L, name), ctypes.c_void_p).value
-                setattr(self, name, Function(address, "".join(kinds), "i" if res is _i32 else "q"))
+            args = [_p if isinstance(a, type) and issubclass(a, ctypes._Pointer) else a for a in args]
+            if res not in (_i32, _i64, _sz) or any(a not in self._KINDS for a in args):
+                continue
+            address = ctypes.cast(getattr(L, name), ctypes.c_void_p).value
+            setattr(self, name, fast.Function(address, "".join(self._KINDS[a] for a in args), "i" if res is _i32 else "q")
+                    if fast else ctypes.CFUNCTYPE(res, *args)(address))
 
 
 _calls: Optional[_Calls] = None

@@ -2,14 +2,18 @@
 from __future__ import annotations
 
 import os
+import platform
+import shutil
 import subprocess
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
+from typing import Optional, Sequence
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbnn.so")
+FASTCALL = os.path.join(HERE, "_fastcall.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["api.hip", "encode.hip", "im2col.hip", "gemm.hip", "gemm_lowk.hip", "gemm_fp4.hip", "gemm_fp4_split.hip", "conv.hip", "conv_chain.hip", "conv_pointwise.hip", "glue.hip", "mfma.hip", "control.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -33,6 +37,7 @@ EXTRA_FLAGS = {"conv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 #   LD_PRELOAD="$(gcc -print-file-name=libasan.so) $(gcc -print-file-name=libubsan.so)" ASAN_OPTIONS=detect_leaks=0 \
 #       BNN_SANITIZE=1 python -m pytest tests/test_abi_host.py
 SAN_LIB = os.path.join(HERE, "libbnn_san.so")
+SAN_FASTCALL = os.path.join(HERE, "_fastcall_san.so")
 SAN_HOST_FLAGS = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined", "-Xarch_host",
                   "-fno-omit-frame-pointer", "-g"]
 
@@ -54,6 +59,7 @@ def build_sanitized() -> str:
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-Xarch_host", "-fsanitize=address",
                            "-Xarch_host", "-fsanitize=undefined", *objs, "-o", tmp])
     os.replace(tmp, SAN_LIB)
+    build_fastcall(SAN_FASTCALL, ("-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined"))
     return SAN_LIB
 
 
@@ -63,12 +69,18 @@ def _compile(src: str) -> str:
     return obj
 
 
-def build_fastcall() -> str:
-    """The binding's call helper, a CPython extension."""
-    out = os.path.join(HERE, "_fastcall.so")
+def build_fastcall(out: str = FASTCALL, flags: Sequence[str] = ("-O2",)) -> Optional[str]:
+    """The binding's call helper, a CPython extension.  None where it cannot be built (no Python headers, not x86-64): the
+    binding then calls through ctypes."""
+    if os.path.exists(out):
+        os.remove(out)  # not one of another source
+    include = sysconfig.get_paths()["include"]
+    if platform.machine() != "x86_64" or not os.path.exists(os.path.join(include, "Python.h")):
+        print("call helper not built: it needs x86-64 and", os.path.join(include, "Python.h"))
+        return None
+    cc = [shutil.which("gcc")] if shutil.which("gcc") else [HIPCC, "-x", "c"]
     tmp = out + ".tmp.%d" % os.getpid()
-    subprocess.check_call(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
-                           os.path.join(CSRC, "fastcall.c"), "-o", tmp])
+    subprocess.check_call([*cc, *flags, "-Wall", "-shared", "-fPIC", "-I", include, os.path.join(CSRC, "fastcall.c"), "-o", tmp])
     os.replace(tmp, out)
     return out
 

@@ -425,6 +425,37 @@ def test_binding_refuses_arguments_as_ctypes_does(L):
             f.bnn_encode(1.5, 1, 64, 64, 16, 1, None)
 
 
+def test_binding_without_its_call_helper(L, monkeypatch, tmp_path):
+    """Where only libbnn has been built the binding says so and calls through ctypes: the same functions, the same values."""
+    import ctypes
+    monkeypatch.setattr(B, "FASTCALL_PATH", str(tmp_path / "_fastcall.so"))
+    with pytest.warns(RuntimeWarning, match="build.py"):
+        c = B._Calls(L)
+    fast = B._c()
+    assert {n for n in vars(c)} == {n for n in vars(fast)}
+    for k in (-1, 1, 65, (1 << 40) + 1):
+        assert c.bnn_packed_words(k) == fast.bnn_packed_words(k)
+    geo = (64, 256, 56, 56, 3, 3, 1, 1, 1, 1)
+    assert c.bnn_conv2d_workspace_bytes(*geo) == fast.bnn_conv2d_workspace_bytes(*geo)
+    many = (16, 16, 1, 64, 8, 8, 64, 3, 3, 1, 1, 1, 1, None, None, None, None, 16, 1 << 20, None)
+    assert c.bnn_conv2d(*many) == NULL and c.bnn_encode(8, 1, 64, 64, 16, 1, None) == ALIGN
+    arr = (B.ChainLayer * 2)(_chain_layer(128), _chain_layer(128, 2))
+    for n in (1, 256):
+        args = (n, 128, 16, 16, 2, ctypes.addressof(arr))
+        assert c.bnn_conv_chain_pays(*args) == fast.bnn_conv_chain_pays(*args) == L.bnn_conv_chain_pays(*args[:-1], arr)
+
+
+def test_call_helper_build(monkeypatch, tmp_path):
+    """The helper builds with the library's own compiler where there is no gcc, and is left out, an old one with it, where
+    there are no Python headers."""
+    from paper_1911_04477_amd import build
+    out = tmp_path / "_fastcall.so"
+    monkeypatch.setattr(build.shutil, "which", lambda name: None)
+    assert build.build_fastcall(str(out)) == str(out) and out.exists()
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert build.build_fastcall(str(out)) is None and not out.exists()
+
+
 class _Gpu:
     """What the binding looks at of a GPU tensor."""
     is_cuda = True
