@@ -18,7 +18,7 @@ extern "C" const char *bnn_status_str(bnn_status s) {
   return "BNN_ERR_UNKNOWN";
 }
 
-extern "C" int64_t bnn_packed_words(int64_t K) { return K <= 0 ? 0 : (K + 63) / 64; }
+extern "C" int64_t bnn_packed_words(int64_t K) { return K <= 0 ? 0 : (K - 1) / 64 + 1; }
 
 extern "C" int64_t bnn_conv_kwords(int C, int kH, int kW) {
   if (C <= 0 || kH <= 0 || kW <= 0) return 0;
