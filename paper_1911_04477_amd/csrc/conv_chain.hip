@@ -486,7 +486,8 @@ static size_t chain_plan(ChainParams &p, int N, int C, int H, int W, int n_layer
   checked = BNN_ERR_NULL;
   if (!layers) return 0;
   checked = BNN_ERR_UNSUPPORTED;
-  if (n_layers > CHAIN_MAX_LAYERS || (int64_t)N * H * W * (C / 64) > 0x7fffffffLL) return 0;
+  if (n_layers > CHAIN_MAX_LAYERS) return 0;
+  const int C0 = C, H0 = H, W0 = W;
   p.layers = n_layers;
   p.H = H;
   p.W = W;
@@ -547,6 +548,7 @@ static size_t chain_plan(ChainParams &p, int N, int C, int H, int W, int n_layer
   p.thr = (uint32_t)at;
   at += thr;
   if (at > 160 * 1024) return 0;
+  if ((int64_t)N * H0 * W0 * (C0 / 64) > 0x7fffffffLL) return 0;  // H0 and W0 are at most 256 here
   checked = BNN_OK;
   return at;
 }

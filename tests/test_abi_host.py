@@ -387,6 +387,16 @@ def test_conv_chain_errors(L):
     assert L.bnn_conv_chain_pays(1, 128, 8, 8, 1, one) == 0  # one image leaves every other unit idle
 
 
+@pytest.mark.parametrize("N,H,W", [(2**31 - 1, 2**31 - 1, 2**31 - 1), (2**31 - 1, 2**30, 2**30), (65536, 65536, 2**31 - 1),
+                                   (2**31 - 1, 256, 2), (2**31 - 1, 2, 2)])
+def test_conv_chain_sizes_beyond_64_bits(L, N, H, W):
+    """Refused without computing a product that does not fit (the sanitizer build ends the run where one does)."""
+    one = (B.ChainLayer * 1)(_chain_layer(128))
+    for C in (128, 512):
+        assert L.bnn_conv_chain(16, N, C, H, W, 1, one, 16, None) == UNSUPPORTED
+        assert L.bnn_conv_chain_pays(N, C, H, W, 1, one) == 0
+
+
 def test_binding_calls_equal_ctypes(L):
     """The binding's call helper against ctypes on functions that launch nothing: values, widths, signs, None, errors."""
     c = B._c()
