@@ -609,10 +609,10 @@ static bool bits_applicable(const GemmParams &p, int bmode) {
 }
 
 // Workgroups that a compute unit holds with their input regions in LDS, at most three; 0: the region is not for LDS.
+// rows: upper bound of a tile's input rows.
 template <int WTM, int WTN, int WGM, int WGN>
-static int held_with_regions(GemmParams &p) {
+static int held_with_regions(GemmParams &p, int64_t &rows) {
   using H = Fp4Cfg<WTM, WTN, WGM, WGN, GM_HALO>;
-  int64_t rows;
   if (!halo_region(p, H::BN, p.g.pool != 0, rows)) return 0;
   return std::min(3, 160 * 1024 / (H::FIXED_BYTES + (int)p.halo.bytes + (p.Kw64 + 1) / 2 * 8));
 }
@@ -638,21 +638,22 @@ static int conv_shape(GemmParams &p, int emode, bool &region) {
     return held == 0 || once || (held == 1 && tiles >= 2 && (taps < 4 * steps || (third && tiles >= 3)));
   };
   auto held_if = [&](int held) { return region ? held : 0; };
+  int64_t rows = 0;
   if (p.M <= 64) {
     // one row of tiles to fill (64 channels, 100352 pixels, K = 576: 7.0 us against 9.0 to 10.9)
-    const int held = held_if(held_with_regions<2, 2, 1, 4>(p));
+    const int held = held_if(held_with_regions<2, 2, 1, 4>(p, rows));
     const int64_t tiles = per_unit(64, 256);
     region = once ? held >= std::min<int64_t>(tiles, 3) : !gather(held, tiles, false);
     return 3;
   }
-  const int held128 = held_if(held_with_regions<2, 2, 2, 2>(p));
+  const int held128 = held_if(held_with_regions<2, 2, 2, 2>(p, rows));
   if (emode == 0) {
     // Stores of maps want many workgroups in different phases: 64 x 256 tiles while every unit gets two of them and their
     // larger regions do not keep workgroups out (256 x 200704 x 2304 fp32 maps 64.2 us against 68.1 on 128 x 128 and 67.9 on
     // 128 x 256 by four waves; 128 x 131072 x 1152: 16.6, 17.3, 17.7; but 3 x 3 by stride 2 from 512 channels of 8 x 8, one
     // against two held: 119 against 74), else 128 x 128 (512 x 4096 x 2304: 9.9 against 10.3).
     if (!once && count(64, 256) >= 2 * (int64_t)p.n_cu) {
-      const int held = held_if(held_with_regions<2, 2, 1, 4>(p));
+      const int held = held_if(held_with_regions<2, 2, 1, 4>(p, rows));
       if (held > 0 && held >= held128) {
         region = !gather(held, per_unit(64, 256), false);
         return 3;
@@ -672,12 +673,16 @@ static int conv_shape(GemmParams &p, int emode, bool &region) {
     return 2;
   }
   const int64_t tiles = per_unit(128, 256);
-  region = !gather(held_if(held_with_regions<2, 4, 2, 2>(p)), tiles, false);
-  // One 128 x 256 tile to a unit: eight waves gather faster than four (3 x 3 by stride 2, 1024 channels: 38.1 against 40.6), and
-  // they copy faster the regions of small maps, several images to a tile (256 channels of 8 x 8: 13.4 against 13.9, 384:
-  // 15.9 against 16.4), until the reduction is long (512: 18.9 against 18.4).
-  const bool small = !g.pool && (int64_t)g.OH * g.OW <= 64 && p.Kw64 < 72;
-  return n == 2 && (!region || small) ? 1 : 0;
+  region = !gather(held_if(held_with_regions<2, 4, 2, 2>(p, rows)), tiles, false);
+  // One 128 x 256 tile to a unit: eight waves gather faster than four (3 x 3 by stride 2, 1024 channels: 38.1 against 40.6).
+  // Regions they copy faster, four multiply faster, so it is the rows copied (many where the maps are small) against the
+  // words of the reduction.  By 197 layers with one tile to a unit and 59 with two, eight waves against four: 3 x 3 by stride 2 of
+  // 100 channels of 2 x 2, 320 rows 14.8 against 18.1; of 192 channels of 17 x 16, 40 rows 11.6 against 12.6; pooled of 256
+  // channels of 8 x 8, 38 rows 12.5 against 12.7, of 20 x 20 (stride 1), 18 rows 11.5 against 10.8; of 512 channels of 8 x 8 (stride 1),
+  // pooled, 40 rows 18.4 against 17.4; two tiles: 128 channels of 2 x 3, 174 rows 16.7 against 18.2, of 6 x 6 pooled, 50 rows
+  // 13.2 against 12.6.  At most 4 % (5 % with two) from the better one.
+  if (n == 2) return !region || 2 * rows >= 16 + p.Kw64 + (g.pool ? 16 : 0) ? 1 : 0;
+  return n == 4 && region && 4 * rows >= 96 + 7 * (int64_t)p.Kw64 ? 1 : 0;
 }
 
 bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, int shape, bool region) {

@@ -1008,6 +1008,27 @@ def test_fused_stack_chain_follows_its_parameters(inference):
         assert np.array_equal(host(twin.forward(x)), f) and twin.p[j]["wp"] is not net.p[j]["wp"]
 
 
+@pytest.mark.parametrize("N,C,H,W,D,k,s,pool", [
+    (3000, 64, 3, 3, 300, 3, 2, 0), (258, 256, 7, 7, 1024, 3, 2, 2), (617, 192, 16, 17, 200, 3, 3, 2),  # many rows: eight waves
+    (60, 192, 16, 16, 300, 3, 1, 2), (50, 128, 28, 28, 96, 3, 1, 0),                                    # few: four
+    (3904, 64, 3, 3, 1024, 3, 2, 2), (1540, 192, 8, 9, 512, 3, 2, 0),                                   # two tiles a unit
+    (429, 128, 11, 11, 1024, 5, 2, 2), (347, 192, 12, 12, 256, 3, 1, 0)])
+def test_conv_sign_tiles_by_rows_and_words(N, C, H, W, D, k, s, pool):
+    """Packed outputs on both sides of the line between four and eight waves for a 128 x 256 tile, against a vector-ALU tile."""
+    print(f"sign tiles {N}x{C}x{H}x{W} -> {D} k{k} s{s} pool={pool}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N + C + D)
+    x = torch.randn(N, C, H, W, device=DEV, generator=g)
+    xp = B.bnn_im2col_packed(x, 1, 1).view(N, H, W, -1)
+    wp = B.bnn_pack_conv_weight(torch.randn(D, C, k, k, device=DEV, generator=g))
+    sc, bi = torch.randn(D, device=DEV, generator=g), torch.randn(D, device=DEV, generator=g)
+    run = lambda cfg=None: B.bnn_conv2d_packed(xp, wp, C, D, k, k, (s, s), (k // 2, k // 2), pool=pool, scale=sc, bias=bi, cfg=cfg)
+    got, names = kernels_of(run)
+    assert names == ["xnor_gemm_fp4"]
+    assert torch.equal(got, run(cfg=3))
+    for cfg in (21, 22):
+        assert torch.equal(got, run(cfg=cfg)), cfg
+
+
 # ---------------------------------------------------------------- MFMA ablation
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (37, 150, 300), (128, 128, 64), (130, 257, 1152), (64, 64, 256),
                                    (200, 333, 2304 + 17), (5, 700, 63),
