@@ -373,7 +373,8 @@ static bnn_status launch_split(GemmParams &p, int bmode, int emode, hipStream_t 
 // By t, tiles of 32 x 32 outputs per compute unit.  Up to 2 latency is all there is: 32 x 32 tiles, K split 8 ways up to 1
 // (1 x 1024 x 8192 3.7 us, 4 ways 4.0; a 3 x 3 layer of 512 channels, 6 images of 4 x 4, 4.9 against 5.0), then 4 (3 x 3 of 320
 // channels at t = 1.1 5.4 against 6.1, 1024 x 485 x 2560 4.5 against 4.7; 64 x 64 tiles 7.4 and 5.9, staged ones 11 and 8), but
-// for the longest gathers (5 x 5 of 512 channels, t = 1.8 11.1 against 10.8).
+// for the longest gathers (5 x 5 of 512 channels, t = 1.8 11.1 against 10.8), which are shorter where a pixel has an odd number of
+// words and is gathered word by word (5 x 5 of 320 channels, t = 1.4 9.5 against 8.9).
 // Beyond, a 32 x 32 tile reads twice the operands of a 64 x 64 one for its outputs (32 lines for every load instruction,
 // about 1.1 us for each workgroup that a unit gets at K = 4096) and a 64 x 64 one pays a larger exchange (1.2 us),
 // so it depends on t times the words of a row:
@@ -381,13 +382,18 @@ static bnn_status launch_split(GemmParams &p, int bmode, int emode, hipStream_t 
 //            against 6.0), above 64 x 64 (256 x 4096 x 4096 6.8 against 7.5, 512 x 1124 x 9216 9.0 against 9.9); convolutions
 //            only up to t = 3, the third workgroup (3 x 3 of 512 channels 7.7 against 8.5; 5 x 5 of 100 channels, t = 3.2 7.1
 //            against 6.6), and their 64 x 64 tiles take 8 ways, which share the gather (1024 channels of 8 x 8, t = 3.4: 10.4 against
-//            10.9); short rows 32 x 32 (3 x 3 of 128 channels, t = 3.3 5.3 against 5.4);
+//            10.9), signs of an odd number of words a pixel from 200 words (3 x 3 of 704 channels, t = 2.2 10.2 against 9.3); short
+//            rows 32 x 32 (3 x 3 of 128 channels, t = 3.3 5.3 against 5.4);
 //   up to 8, where it has two: 32 x 32 below 320 words up to 6 (512 x 2380 x 4096 8.7 against 9.7; 64 x 20268 x 2304 6.5 against
 //            7.8), for convolutions up to 5 (3 x 3 of 256 channels of 7 x 7, t = 4.5 7.3 against 8.9, t = 5.9 7.8 against 7.4),
 //            unless of an odd number of words a pixel, gathered word by word; short ones up to 5.5 (t = 5.4 7.2 against 8.0);
 //   short rows beyond that: 64 x 64 for convolutions of small maps, whose regions staged tiles copy with most lanes idle (192
 //            channels of 4 x 4, t = 5.8 8.2 against 10.6 on 128 x 128; 64 of 8 x 8, t = 7.8 5.9 against 6.5; but 100 of 56 x
-//            56, t = 6.1 8.8 against 7.9), else 128 x 128 (100 x 14516 x 512 5.2 against 6.3);
+//            56, t = 6.1 8.8 against 7.9), as long as a unit holds its tiles, two of them (96 channels are two tiles high: 100 of 10
+//            x 10, t = 6.6 9.1 against 7.0; signs of the smallest maps then take 32 x 32: 128 of 2 x 2 9.3, 7.7, staged 11.4), and not
+//            for fp32 maps from 64 pixels on, whose stores staged tiles overlap (128 of 10 x 10, t = 7.1 9.0 against 8.6, of 16
+//            x 16 8.8, 8.0), from 36 on without a stride and with few words (64 of 7 x 7, t = 6.1 8.8 against 8.1, 192 of 7 x 7 9.4, 10.1);
+//            else 128 x 128 (100 x 14516 x 512 5.2 against 6.3);
 //   one row or one column of tiles, up to 8: 32 x 32, a larger tile has nothing to use twice and computes rows for nothing
 //            (4 x 40000 x 1024: 4.1 us, 64 x 64 split 6.7, 64 x 256 staged 5.4; 4 x 40000 x 4096 6.6, 10.2, 10.4; 32 x 65536 x
 //            4096 12.3, 16.0, 12.5; 40000 x 10 x 2048 5.0, 9.4, 15.7), above 6 from 16 words (4 x 65536 x 1024 5.2 against 5.6,
@@ -397,17 +403,23 @@ static int split_shape(const GemmParams &p, int bmode) {
   const int64_t t = (((int64_t)p.M + 31) / 32) * (((int64_t)p.N + 31) / 32), cu = p.n_cu;
   const int64_t words = t * p.Kw64 / cu;  // of the tiles of a unit
   const bool conv = bmode != 0, single = p.M <= 32 || p.N <= 32, short_rows = p.Kw64 <= 32;
-  if (t <= cu || (t <= 2 * cu && conv && p.Kw64 > 160)) return 1;
+  const bool odd = conv && (p.g.Cw & 1), signs = p.outp != nullptr;
+  if (t <= cu || (t <= 2 * cu && conv && p.Kw64 > (odd ? 110 : 160))) return 1;
   if (t <= 2 * cu) return 0;
   if (single && (t <= 6 * cu || (t <= 8 * cu && p.Kw64 >= 16))) return 0;
   if (short_rows && 2 * t <= 11 * cu) return 0;
   if (t <= 4 * cu) {
-    if (words <= 240 && (!conv || t <= 3 * cu)) return 0;
+    if (words <= (odd && signs ? 200 : 240) && (!conv || t <= 3 * cu)) return 0;
     return conv ? 3 : 2;
   }
   if (t <= 8 * cu) {
-    if (short_rows) return conv && p.Kw64 >= 9 && halo_lanes_idle(p.g) ? 2 : -1;
-    if (words <= 320 && (conv ? !(p.g.Cw & 1) && t <= 5 * cu : t <= 6 * cu)) return 0;
+    if (short_rows) {
+      if (!conv || p.Kw64 < 9 || !halo_lanes_idle(p.g)) return -1;
+      const int64_t pixels = (int64_t)p.g.OH * p.g.OW;
+      if ((((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 63) / 64) > 2 * cu) return signs && pixels <= 32 ? 0 : -1;
+      return p.Y && pixels >= (p.g.sH * p.g.sW == 1 && p.Kw64 <= 18 ? 36 : 64) ? -1 : 2;
+    }
+    if (words <= 320 && (conv ? !odd && t <= 5 * cu : t <= 6 * cu)) return 0;
     return 2;
   }
   // rows beyond the exact range of the other kernel's accumulators

@@ -1582,6 +1582,30 @@ def test_gemm_split_rule(M, K, tiles):
     assert torch.equal(got, B.bnn_xnor_gemm(A, Bm, K, cfg=3))
 
 
+@pytest.mark.parametrize("N,C,H,W,D,k,s,pool,out,split", [
+    (381, 100, 7, 7, 96, 3, 1, 0, "packed", False),    # more than two 64 x 64 tiles a unit, since 96 rows are two tiles high
+    (419, 100, 7, 9, 200, 3, 2, 0, "packed", True),    # the same, smallest maps: 32 x 32
+    (435, 192, 7, 7, 96, 3, 1, 0, "i32", False),
+    (569, 128, 15, 15, 128, 3, 3, 0, "packed", True),  # two a unit
+    (168, 64, 7, 7, 192, 3, 1, 0, "f32", False), (168, 64, 7, 7, 192, 3, 1, 0, "i32", True),  # stores of fp32 maps
+    (65, 100, 10, 10, 300, 3, 1, 0, "f32", False), (34, 128, 21, 21, 1024, 3, 3, 0, "f32", True),
+    (89, 704, 8, 9, 300, 3, 2, 0, "packed", True), (13, 320, 16, 16, 96, 5, 1, 2, "packed", True)])  # long rows, odd words
+def test_conv_split_rule(N, C, H, W, D, k, s, pool, out, split):
+    """Which kernel takes convolutions of few tiles and short rows (256 compute units), and its values against a vector-ALU
+    tile."""
+    print(f"conv split rule {N}x{C}x{H}x{W} -> {D} k{k} s{s} pool={pool} {out}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N + C + D)
+    x = torch.randn(N, C, H, W, device=DEV, generator=g)
+    xp = B.bnn_im2col_packed(x, 1, 1).view(N, H, W, -1)
+    wp = B.bnn_pack_conv_weight(torch.randn(D, C, k, k, device=DEV, generator=g))
+    sc, bi = torch.randn(D, device=DEV, generator=g), torch.randn(D, device=DEV, generator=g)
+    run = lambda cfg=None: B.bnn_conv2d_packed(xp, wp, C, D, k, k, (s, s), (k // 2, k // 2), pool=pool, scale=sc, bias=bi, out=out, cfg=cfg)
+    got, names = kernels_of(run)
+    assert torch.equal(got, run(cfg=3))
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert names == ["xnor_gemm_fp4_split" if split else "xnor_gemm_fp4"]
+
+
 def test_gemm_rows_beyond_the_accumulators_exact_range():
     """A wave's share of the row holds more than 2^23 values: its fp32 sums go to integers on the way."""
     K = (1 << 26) + (1 << 24) + 77
