@@ -292,9 +292,9 @@ __device__ __forceinline__ uint64_t sign_word(uint32_t h0, uint32_t h1) {
 
 // Binarizing epilogue: affine map, sign; packed NHWC words.  Tile rows are output channels, 64 of them
 // (WTM = 2): one word per output pixel.
-template <int WTM, int WTN, bool DEALT, bool BITS>
+template <int WTM, int WTN, bool DEALT>
 __device__ __forceinline__ void store_signs(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n0, int lane,
-                                            const float *sSc, const float *sBi, const float *sRa) {
+                                            const float *sSc, const float *sBi) {
   static_assert(WTM == 2 && (WTN == 2 || WTN == 4), "one 64-channel word per wave");
   const int half = lane >> 5, l32 = lane & 31;
   const int word = m0 >> 6;
@@ -308,7 +308,6 @@ __device__ __forceinline__ void store_signs(const GemmParams &p, const Fp4Acc<WT
     for (int q = 3; q >= 0; --q) {
       const float4 sc = *reinterpret_cast<const float4 *>(sSc + 32 * i + 8 * q + 4 * half);
       const float4 bi = *reinterpret_cast<const float4 *>(sBi + 32 * i + 8 * q + 4 * half);
-      const float4 ra = row_parts<BITS>(sRa + 32 * i + 8 * q + 4 * half);
       constexpr int ROWS = 4 / WTN;  // four signs at a time
 #pragma unroll
       for (int e = 3; e >= 0; e -= ROWS) {
@@ -316,7 +315,7 @@ __device__ __forceinline__ void store_signs(const GemmParams &p, const Fp4Acc<WT
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const int r = e - k / WTN;
-          y[k] = fmaf((&sc.x)[r], result<BITS>(acc.v[i][k % WTN][4 * q + r], (&ra.x)[r]), (&bi.x)[r]);
+          y[k] = fmaf((&sc.x)[r], acc.v[i][k % WTN][4 * q + r], (&bi.x)[r]);
         }
         shift_in_signs<WTN>(bits, y);
       }
@@ -335,9 +334,9 @@ __device__ __forceinline__ void store_signs(const GemmParams &p, const Fp4Acc<WT
 
 // The same on the 2x2 maximum.  Columns are window-major: a lane of a 4-block wave holds whole windows, a
 // lane of a 2-block wave one row of a window, its neighbour the other.
-template <int WTM, int WTN, bool BITS>
+template <int WTM, int WTN>
 __device__ __forceinline__ void store_signs_pooled(const GemmParams &p, const Fp4Acc<WTM, WTN> &acc, int m0, int n0,
-                                                   int lane, const float *sSc, const float *sBi, const float *sRa) {
+                                                   int lane, const float *sSc, const float *sBi) {
   static_assert(WTM == 2 && (WTN == 2 || WTN == 4), "one 64-channel word per wave");
   const int half = lane >> 5, l32 = lane & 31;
   const int word = m0 >> 6;
@@ -350,7 +349,6 @@ __device__ __forceinline__ void store_signs_pooled(const GemmParams &p, const Fp
     for (int q = 3; q >= 0; --q) {
       const float4 sc = *reinterpret_cast<const float4 *>(sSc + 32 * i + 8 * q + 4 * half);
       const float4 bi = *reinterpret_cast<const float4 *>(sBi + 32 * i + 8 * q + 4 * half);
-      const float4 ra = row_parts<BITS>(sRa + 32 * i + 8 * q + 4 * half);
       float y[4];
 #pragma unroll
       for (int e = 3; e >= 0; --e) {
@@ -364,7 +362,7 @@ __device__ __forceinline__ void store_signs_pooled(const GemmParams &p, const Fp
           const float o = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(m), 0xB1, 0xF, 0xF, true));
           asm("v_max_f32 %0, %0, %1" : "+v"(m) : "v"(o));
         }
-        y[3 - e] = fmaf((&sc.x)[e], result<BITS>(m, (&ra.x)[e]), (&bi.x)[e]);
+        y[3 - e] = fmaf((&sc.x)[e], m, (&bi.x)[e]);
       }
       shift_in_signs<1>(bits, y);
     }

@@ -172,7 +172,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
   float *const sBi = sSc + BM;
   uint32_t *const sCol = reinterpret_cast<uint32_t *>(sBi + BM);      // GM_HALO: region offset of every column
   float *const sRow = sBi + BM;                                         // BITS: parts of rows, then of columns
-  static_assert(!BITS || GM == GM_EXPL16, "sRow lies where sCol does");
+  static_assert(!BITS || (GM == GM_EXPL16 && EMODE < EM_SIGN), "sRow lies where sCol does; only maps know the corrections");
   char *const sReg = smem + Cfg::FIXED_BYTES;                           // GM_HALO: [word][pixel] 8-byte words
   uint32_t *const sOff = reinterpret_cast<uint32_t *>(sReg + p.halo.bytes);  // GM_HALO: distance of every word of a row
   const int tid = threadIdx.x;
@@ -500,10 +500,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, MINW) void xnor_gemm_fp4_kernel(Gem
     }
   }
   const int mw = m0 + 32 * WTM * wm, nw = n0 + 32 * WTN * wn;
-  const float *sc = sSc + 32 * WTM * wm, *bi = sBi + 32 * WTM * wm, *rc = sRow + 32 * WTM * wm;
-  if constexpr (MAPS) store_maps<WTM, WTN, EMODE, BITS>(p, acc, mw, nw, lane, sc, bi, rc);
-  else if constexpr (EMODE == EM_SIGN) store_signs<WTM, WTN, DEALT, BITS>(p, acc, mw, nw, lane, sc, bi, rc);
-  else store_signs_pooled<WTM, WTN, BITS>(p, acc, mw, nw, lane, sc, bi, rc);
+  const float *sc = sSc + 32 * WTM * wm, *bi = sBi + 32 * WTM * wm;
+  if constexpr (MAPS) store_maps<WTM, WTN, EMODE, BITS>(p, acc, mw, nw, lane, sc, bi, sRow + 32 * WTM * wm);
+  else if constexpr (EMODE == EM_SIGN) store_signs<WTM, WTN, DEALT>(p, acc, mw, nw, lane, sc, bi);
+  else store_signs_pooled<WTM, WTN>(p, acc, mw, nw, lane, sc, bi);
 }
 
 // ---- host side -----------------------------------------------------------------------------------------
