@@ -1,10 +1,10 @@
 // Xnor-Bitcount GEMM (section 3.2) for short reduction axes on the matrix cores: explicit rows of at most four 64-bit
 // words (K <= 256), int32 / fp32 output.
 //
-// One chunk of 256 bits is the whole reduction, so there is nothing to stage or to pipeline: a wave reads the rows of both
-// operands of its block straight into registers, one load of 16 bytes each, expands them, multiplies and stores the block.
-// No loop, no LDS but for the affine constants, no barrier, and 150 bytes of arguments (the host copies them for every
-// launch).
+// One chunk of 256 bits is the whole reduction, so there is nothing to stage or to pipeline: a wave reads the rows of its
+// columns once, expands them once (the operands of all four steps stay in registers), and then walks over blocks of
+// rows: one load of 16 bytes per row, four expansions, the products, and the store of the block.  No LDS but for the
+// affine constants, no barrier, and 150 bytes of arguments (the host copies them for every launch).
 // Bound by the launch for small calls and by the store of the result for large ones.
 #include <algorithm>
 
@@ -17,6 +17,7 @@ struct ShortParams {
   const char *A, *B;
   int64_t lda, ldb;  // bytes
   int M, N, Kbits, Kformula, words;
+  int rounds;        // blocks of rows that a wave walks over
   int abreast;       // the four waves of a workgroup stand side by side, not one above the other
   int runs;          // an XCD gets a contiguous run of workgroups
   int axis;
@@ -42,7 +43,8 @@ __global__ __launch_bounds__(256, 3) void xnor_gemm_lowk_kernel(ShortParams p) {
   const uint32_t mi = fdiv_sel(bid, p.divTilesN);
   const uint32_t ni = bid - mi * p.divTilesN.d;
   const int n0 = (int)(p.abreast ? 4 * ni + wave : ni) * BN;
-  const int m0 = (int)(p.abreast ? mi : 4 * mi + wave) * BM;
+  const int mstep = p.abreast ? BM : 4 * BM;
+  int m0 = (int)mi * p.rounds * mstep + (p.abreast ? 0 : wave * BM);
   if (m0 >= p.M || n0 >= p.N) return;  // wave-uniform; the kernel has no barrier
 
   // this half's two words of a row; past the row's end whatever is there, masked
@@ -69,8 +71,11 @@ __global__ __launch_bounds__(256, 3) void xnor_gemm_lowk_kernel(ShortParams p) {
     const int n = min(n0 + (MS == MS_ONE ? 32 * j + l32 : WTN * l32 + j), p.N - 1);
     b[j] = load(p.B + (size_t)n * (size_t)p.ldb);
   }
+  auto load_rows = [&](int m) {
 #pragma unroll
-  for (int i = 0; i < WTM; ++i) a[i] = load(p.A + (size_t)min(m0 + 32 * i + l32, p.M - 1) * (size_t)p.lda);
+    for (int i = 0; i < WTM; ++i) a[i] = load(p.A + (size_t)min(m + 32 * i + l32, p.M - 1) * (size_t)p.lda);
+  };
+  load_rows(m0);
   const bool affine = p.Y && p.axis == BNN_CH_ROW;  // uniform
   v8i eb[4][WTN];
 #pragma unroll
@@ -79,28 +84,34 @@ __global__ __launch_bounds__(256, 3) void xnor_gemm_lowk_kernel(ShortParams p) {
   for (int d = 0; d < 4; ++d)
 #pragma unroll
     for (int j = 0; j < WTN; ++j) eb[d][j] = expand_e2m1<true>(b[j][d]);
-  if (affine) {  // the wave's own rows: LDS keeps a wave's order, and the compiler keeps it across the fence
-    if (lane < BM) {
+  const float start = -(float)(256 - p.Kformula);
+  for (int r = 0;;) {
+    if (affine && lane < BM) {  // the wave's own rows: LDS keeps a wave's order
       sSc[wave][lane] = p.scale[min(m0 + lane, p.M - 1)];
       sBi[wave][lane] = p.bias[min(m0 + lane, p.M - 1)];
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    Fp4Acc<WTM, WTN> acc;
+    acc.init(start);
+    u32x4 x[WTM];
+#pragma unroll
+    for (int i = 0; i < WTM; ++i) x[i] = a[i] & mask;
+    const int next = m0 + mstep;
+    const bool more = ++r < p.rounds && next < p.M;  // wave-uniform
+    if (more) load_rows(next);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      v8i ea[WTM];
+#pragma unroll
+      for (int i = 0; i < WTM; ++i) ea[i] = expand_e2m1<true>(x[i][d]);
+#pragma unroll
+      for (int i = 0; i < WTM; ++i)
+#pragma unroll
+        for (int j = 0; j < WTN; ++j) acc.v[i][j] = mfma_e2m1(ea[i], eb[d][j], acc.v[i][j]);
+    }
+    store_maps<WTM, WTN, MS>(p, acc, m0, n0, lane, sSc[wave], sBi[wave]);
+    if (!more) break;
+    m0 = next;
   }
-  Fp4Acc<WTM, WTN> acc;
-  acc.init(-(float)(256 - p.Kformula));
-#pragma unroll
-  for (int i = 0; i < WTM; ++i) a[i] &= mask;
-#pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    v8i ea[WTM];
-#pragma unroll
-    for (int i = 0; i < WTM; ++i) ea[i] = expand_e2m1<true>(a[i][d]);
-#pragma unroll
-    for (int i = 0; i < WTM; ++i)
-#pragma unroll
-      for (int j = 0; j < WTN; ++j) acc.v[i][j] = mfma_e2m1(ea[i], eb[d][j], acc.v[i][j]);
-  }
-  store_maps<WTM, WTN, MS>(p, acc, m0, n0, lane, sSc[wave], sBi[wave]);
 }
 
 // Whether the short-row kernel can run the problem described by p (explicit B).
@@ -162,25 +173,27 @@ bnn_status launch_lowk(GemmParams &p, int form, hipStream_t s) {
   q.C = p.C; q.Y = p.Y; q.ldc = p.ldc; q.ldy = p.ldy; q.img_stride = p.img_stride;
   q.scale = p.scale; q.bias = p.bias;
   q.OHW = p.OHW; q.divOHW = p.divOHW;
-  // a launch is limited to 2^32 threads: the widest workgroups beyond.  (More of those than that, with operand A of at
-  // most 4 GiB, is an output of 500 GB and more.)
+  // a launch is limited to 2^32 threads: the widest workgroups for more columns than that, several rounds for more rows
   constexpr int64_t MAX_BLOCKS = 0xffffff;
-  int64_t blocks, tilesN;
-  auto count = [&]() {
+  int64_t tilesM, tilesN;
+  auto tiles = [&]() {
     const int b32 = form & F_64 ? 64 : 32, bn = form & F_ABREAST ? 4 * b32 : b32, bm = form & F_ABREAST ? b32 : 4 * b32;
     tilesN = ((int64_t)p.N + bn - 1) / bn;
-    blocks = ((int64_t)p.M + bm - 1) / bm * tilesN;
-    return blocks;
+    tilesM = ((int64_t)p.M + bm - 1) / bm;
+    return tilesM * tilesN;
   };
-  if (count() > MAX_BLOCKS) {
+  if (tiles() > MAX_BLOCKS) {
     form |= F_64 | F_ABREAST;
-    if (count() > MAX_BLOCKS) return BNN_ERR_UNSUPPORTED;
+    tiles();
   }
+  q.rounds = (int)((tilesM * tilesN + MAX_BLOCKS - 1) / MAX_BLOCKS);
+  tilesM = (tilesM + q.rounds - 1) / q.rounds;
+  if (tilesM * tilesN > MAX_BLOCKS) return BNN_ERR_UNSUPPORTED;
   q.abreast = form & F_ABREAST ? 1 : 0;
   q.runs = form & F_RUNS ? 1 : 0;
   q.divTilesN = FastDiv((uint32_t)tilesN);
   const bool v16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0 && p.ldb % 2 == 0;
-  const dim3 grid((unsigned)blocks);
+  const dim3 grid((unsigned)(tilesM * tilesN));
   ProfScope ps(KID_XNOR_GEMM_LOWK, s);
   if (!(form & F_64)) v16 ? launch_forms<1, 1, true>(q, p, grid, s) : launch_forms<1, 1, false>(q, p, grid, s);
   else v16 ? launch_forms<2, 2, true>(q, p, grid, s) : launch_forms<2, 2, false>(q, p, grid, s);

@@ -387,11 +387,6 @@ def test_conv_chain_errors(L):
     assert L.bnn_conv_chain_pays(1, 128, 8, 8, 1, one) == 0  # one image leaves every other unit idle
 
 
-def test_short_row_gemm_beyond_a_launch(L):
-    """More of the widest workgroups than a launch may have (2^32 threads): outputs of 500 GB and more are refused."""
-    assert L.bnn_xnor_gemm(16, 1, 16, 1, 16, 1 << 30, 1 << 20, 1 << 30, 64, None) == UNSUPPORTED
-
-
 @pytest.mark.parametrize("N,H,W", [(2**31 - 1, 2**31 - 1, 2**31 - 1), (2**31 - 1, 2**30, 2**30), (65536, 65536, 2**31 - 1),
                                    (2**31 - 1, 256, 2), (2**31 - 1, 2, 2)])
 def test_conv_chain_sizes_beyond_64_bits(L, N, H, W):
