@@ -28,9 +28,11 @@ extern "C" {
  *   29  23 with the operands' bits expanded to 0 and 1 instead of +1 and -1 and the sums corrected by the counts of set
  *       bits (explicit rows in 16-byte pieces, int32 / fp32 output, K below 2^22)
  *   10 .. 17  the short-row kernel on the matrix cores (rows of at most four words): blocks of 32 x 32 outputs per
- *       wave, +1 of 64 x 64, +2 a workgroup's waves side by side, +4 contiguous runs of workgroups per XCD
+ *       wave, +1 of 64 x 64, +2 a workgroup's waves side by side, +4 contiguous runs of workgroups per XCD;
+ *       30 .. 37  the same with three blocks of rows per wave
+ *   18  the kernel for at most 16 such rows by very many columns (two or four words, columns and strides multiples of 4)
  * A value that a call cannot use (the packed epilogue needs a 32- or 64-row tile with two or
- * four column groups, or one of 21 to 28; 10 to 17 exist for an explicit B with int32 / fp32 output only;
+ * four column groups, or one of 21 to 28; 10 to 18 and 30 to 37 exist for an explicit B with int32 / fp32 output only;
  * 21 to 24 need K below 2^24, 29 what it says)
  * selects the heuristic for that call, and so does any other value.
  * `lean`: 1 = convolutions whose geometry allows it keep a tile's input region in LDS (matrix cores; with cfg = -1 where

@@ -119,6 +119,7 @@ extern "C" const char *bnn_kernel_name(int kernel_id) {
     case bnn::KID_XNOR_GEMM_MFMA_FP4X: return "xnor_gemm_mfma_fp4_expanded";
     case bnn::KID_XNOR_GEMM_FP4: return "xnor_gemm_fp4";
     case bnn::KID_XNOR_GEMM_FP4_SPLIT: return "xnor_gemm_fp4_split";
+    case bnn::KID_XNOR_GEMM_FEWROWS: return "xnor_gemm_fewrows";
     case bnn::KID_CONV_CHAIN: return "conv_chain";
     case bnn::KID_CONV_POINTWISE: return "conv_pointwise";
     case bnn::KID_EXPAND_FP4: return "expand_fp4";

@@ -32,7 +32,8 @@ enum KernelId : int {
   KID_IM2COL_BAND = 21,
   KID_CONV_CHAIN = 22,
   KID_CONV_POINTWISE = 23,
-  KID_COUNT = 24
+  KID_XNOR_GEMM_FEWROWS = 24,
+  KID_COUNT = 25
 };
 
 // Timing hook: records an event pair around a launch when profiling is on.
@@ -154,7 +155,12 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
 // Short-row GEMM (gemm_lowk.hip): rows of at most four words, explicit B, maps; form: see there, -1: its rule's.
 bool lowk_applicable(const GemmParams &p);
 bool lowk_faster(const GemmParams &p);  // its rule against the other matrix-core kernels
-bnn_status launch_lowk(GemmParams &p, int form, hipStream_t s);
+bnn_status launch_lowk(GemmParams &p, int form, hipStream_t s, int rounds = 1);
+
+// Short rows, few of them, by very many columns (gemm_fewrows.hip).
+bool fewrows_applicable(const GemmParams &p);
+bool fewrows_faster(const GemmParams &p);  // its rule, for applicable problems
+bnn_status launch_fewrows(GemmParams &p, hipStream_t s);
 
 // Matrix-core GEMM on packed operands (gemm_fp4.hip): bmode / emode as for run_gemm; shape: tile number or -1;
 // region: convolutions may keep a tile's input region in LDS (false: always the general gather).

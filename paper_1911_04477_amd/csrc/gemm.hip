@@ -2,8 +2,8 @@
 //     C[m,n] = K - 2 * sum_w popcount(A[m,w] ^ B[n,w]).
 //
 // This file holds the vector-ALU form of the GEMM and the rule that picks a kernel for a call (run_gemm).  No call
-// without a forced configuration runs the vector-ALU form any more: of the sizes that the short-row kernel
-// (gemm_lowk.hip) leaves, the matrix-core kernels (gemm_fp4.hip, gemm_fp4_split.hip) were faster at all that were
+// without a forced configuration runs the vector-ALU form any more: of the sizes that the short-row kernels
+// (gemm_lowk.hip, gemm_fewrows.hip) leave, the matrix-core kernels (gemm_fp4.hip, gemm_fp4_split.hip) were faster at all that were
 // compared (1 to 4096 rows, 1 to 400000 columns, 128 to 9216 bits, layers of 8 to 512 channels), but for up to 8 rows
 // of 40000 to 50000 columns and at most 512 bits, where a former one-wave form of the vector ALU took 3.4 to 3.6 us
 // against 3.6 to 4.4.  It stays as the yardstick that computes the method literally and as the second implementation
@@ -924,8 +924,12 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
                                : (cfg == 3 || cfg == 1 || (!p.g.pool && (cfg == 6 || cfg == 4)));
   const bool short_rows = bmode == 0 && emode == 0 && lowk_applicable(p);
   const bool matrix = (((cfg >= 21 && cfg <= 24) || cfg == 29) && fp4_applicable(p)) || (cfg >= 25 && cfg <= 28);
-  if (!valu && !matrix && !(short_rows && cfg >= 10 && cfg <= 17)) cfg = -1;
-  if (short_rows && (cfg < 0 ? lowk_faster(p) : cfg >= 10 && cfg <= 17)) return launch_lowk(p, cfg < 0 ? -1 : cfg - 10, s);
+  const bool few_rows = short_rows && fewrows_applicable(p);
+  const bool lowk = short_rows && ((cfg >= 10 && cfg <= 17) || (cfg >= 30 && cfg <= 37));
+  if (!valu && !matrix && !lowk && !(few_rows && cfg == 18)) cfg = -1;
+  if (few_rows && (cfg < 0 ? fewrows_faster(p) : cfg == 18)) return launch_fewrows(p, s);
+  if (lowk) return launch_lowk(p, cfg % 10, s, cfg < 30 ? 1 : 3);
+  if (short_rows && cfg < 0 && lowk_faster(p)) return launch_lowk(p, -1, s);
   if (!valu) {
     // The matrix cores; few outputs split the reduction axis, and so do rows too long for exact fp32 sums.
     p.colperm = emode == 0 && map_columns_by_four(p) ? 1 : 0;

@@ -2,9 +2,13 @@
 // words (K <= 256), int32 / fp32 output.
 //
 // One chunk of 256 bits is the whole reduction, so there is nothing to stage or to pipeline: a wave reads the rows of its
-// columns once, expands them once (the operands of all four steps stay in registers), and then walks over blocks of
-// rows: one load of 16 bytes per row, four expansions, the products, and the store of the block.  No LDS but for the
-// affine constants, no barrier, and 150 bytes of arguments (the host copies them for every launch).
+// columns once, expands them once (the operands of all four steps stay in registers), and takes a block of rows, one load of
+// 16 bytes per row, four expansions, the products, and the store of the block; or several blocks, where there would be more
+// workgroups than a launch may have.  No LDS but for the affine constants, no barrier, and 150 bytes of arguments (the host
+// copies them for every launch).
+// Without the loop over blocks the kernel takes 42 registers instead of 168, and small calls 0.4 us less (64 x 64 x 256 2.7 ->
+// 2.3); but its stores then come from eight waves a SIMD instead of three, and beyond the caches that costs more (4096 x 30001 x
+// 250 94 -> 162 us, 4096 x 30000 x 250 86 -> 113; with LDS held back so that three fit, 95 and 110).
 // Bound by the launch for small calls and by the store of the result for large ones.
 #include <algorithm>
 
@@ -90,6 +94,7 @@ __global__ __launch_bounds__(256, 3) void xnor_gemm_lowk_kernel(ShortParams p) {
       sSc[wave][lane] = p.scale[min(m0 + lane, p.M - 1)];
       sBi[wave][lane] = p.bias[min(m0 + lane, p.M - 1)];
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the compiler keeps the order, too
     Fp4Acc<WTM, WTN> acc;
     acc.init(start);
     u32x4 x[WTM];
@@ -126,13 +131,21 @@ bool lowk_applicable(const GemmParams &p) { return p.Kw64 <= 4; }
 //     blocks up to 150 MB (256 x 50176 x 250 14.4 -> 11.7, 4096 x 8192 x 250 30.7 -> 24.3, 600 x 30000 x 250 20.5 -> 15.8),
 //     32 x 32 from there on for whole lines, and beyond the last-level cache for both (256 x 200704 x 250 46.6 -> 36.7;
 //     4096 x 30000 x 250 107 -> 88; 800 x 120016 x 250 84 -> 66; but 2801 x 18768, 210 MB, half lines 40.8 against 36.8);
-//     with up to 64 rows from 80 MB on (64 x 400000 x 250 25.0 -> 20.0, 64 x 64 blocks 21.3);
+//     with 49 to 64 rows from 80 MB on (64 x 400000 x 250 25.0 -> 20.0, 64 x 64 blocks 21.3), with fewer never (17 x 3148928 x
+//     128 70 against 45, 41 x 2200448 x 64 94, 70);
 //   rows that start elsewhere: side by side and in runs, neighbours share lines (130 x 60004 x 240 15.2 -> 11.0, 700 x 30004 x
 //     240 30.4 -> 18.2, 3000 x 8004 x 240 31.2 -> 18.9, 2856 x 25828 x 240 94 -> 54; without runs 11.6, 19.1, 21.3, 57);
 //     staged tiles where the second row of blocks would be half empty (83 x 31124 x 98 5.9 against 6.8) and for rows of one
 //     and three words, which had them before (642 x 39884 x 170 20.9 against 22.3; others equal);
+//     staged tiles also for 17 to 32 rows, half a block (32 x 948728 x 128 37.7 against 43.4, 30 x 5801148 x 78 225, 270) from 32 MB on (21 x 472760 x 66
+//     12.6, 13.8; but 19 x 325160 x 200 11.4 against 9.6);
 //   columns that are no multiple of 4: the staged tiles and the split kernel are equal or faster (256 x 50177 x 50 13.5
-//     against 14.2), except beyond the cache, one above the other in runs (4096 x 30001 x 250 161 -> 95);
+//     against 14.2), except beyond the cache, where rows share lines and it counts which workgroups of an XCD run together
+//     (70 sizes of 256 to 700 MB): from 250 to 2100 rows 32 x 32 side by side in runs from 275 MB on (987 x 140757 x 64 107, staged
+//     140, one above the other 170; 1689 x 52870 x 256 76, 92, 84; but 541 x 119587 x 64, 258 MB, 52 against 44 staged); more rows one
+//     above the other in runs (4096 x 30001 x 250 95, staged 161), staged below 300 MB, or 330 MB with few columns (15380 x 4763 x
+//     100 55 against 71; 200000 x 401 x 128 73 against 109); fewer rows staged (36 x 3408733 x 53 152 against 237 one above the
+//     other, 165 x 852363 x 256 157, 199);
 //   small calls: 32 x 32 blocks up to two of 64 x 64 per unit (64 x 64 x 256 4.6 -> 3.0, 256 x 1000 x 200 5.3 -> 3.3); rows of
 //     one and three words have the split kernel up to 300 of them, equal within 5 % either way.
 enum : int { F_64 = 1, F_ABREAST = 2, F_RUNS = 4 };
@@ -140,10 +153,16 @@ static int lowk_rule(const GemmParams &p) {
   const int64_t t64 = (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 63) / 64), cu = p.n_cu;
   const int64_t out = (int64_t)p.M * p.N * 4 * ((p.C ? 1 : 0) + (p.Y ? 1 : 0));
   const bool beyond = out > 256000000, odd_words = p.Kw64 % 2 != 0;
-  if (!map_columns_by_four(p)) return beyond ? F_RUNS : -1;
+  if (!map_columns_by_four(p)) {
+    if (p.M < 250 || out < 275000000) return -1;
+    if (p.M <= 2100) return F_RUNS | F_ABREAST;
+    return p.N >= 2000 && out >= (p.N >= 14000 ? 300000000 : 330000000) ? F_RUNS : -1;
+  }
   if (odd_words && t64 < 300) return -1;
   if (t64 <= 2 * cu) return p.N >= p.M ? F_ABREAST : 0;
-  if (!map_rows_start_every(p, 16)) return odd_words || (p.M > 64 && p.M <= 96) ? -1 : F_RUNS | F_ABREAST | F_64;
+  if (!map_rows_start_every(p, 16))
+    return odd_words || (p.M > 64 && p.M <= 96) || (p.M > 16 && p.M <= 32 && out >= 32000000) ? -1 : F_RUNS | F_ABREAST | F_64;
+  if (p.M <= 48) return F_ABREAST | F_64;
   if (beyond) return F_ABREAST;
   return map_rows_start_every(p, 32) && out >= (p.M > 64 ? 150000000 : 80000000) ? F_ABREAST : F_ABREAST | F_64;
 }
@@ -158,8 +177,8 @@ static void launch_forms(const ShortParams &q, const GemmParams &p, dim3 grid, h
   else hipLaunchKernelGGL((xnor_gemm_lowk_kernel<WTM, WTN, MS_VEC, V16>), grid, block, 0, s, q);
 }
 
-// form: as of lowk_rule; -1: the rule's.
-bnn_status launch_lowk(GemmParams &p, int form, hipStream_t s) {
+// form: as of lowk_rule; -1: the rule's.  rounds: blocks of rows per wave at least.
+bnn_status launch_lowk(GemmParams &p, int form, hipStream_t s, int rounds) {
   p.colperm = map_columns_by_four(p) ? 1 : 0;
   p.nt_store = nontemporal_maps(p, 0) ? 1 : 0;
   if (form < 0) form = std::max(lowk_rule(p), 0);
@@ -186,9 +205,9 @@ bnn_status launch_lowk(GemmParams &p, int form, hipStream_t s) {
     form |= F_64 | F_ABREAST;
     tiles();
   }
-  q.rounds = (int)((tilesM * tilesN + MAX_BLOCKS - 1) / MAX_BLOCKS);
+  const int64_t rows = MAX_BLOCKS / tilesN;  // of workgroups; N is below 2^31: at least one
+  q.rounds = (int)std::max<int64_t>(rounds, (tilesM + rows - 1) / rows);
   tilesM = (tilesM + q.rounds - 1) / q.rounds;
-  if (tilesM * tilesN > MAX_BLOCKS) return BNN_ERR_UNSUPPORTED;
   q.abreast = form & F_ABREAST ? 1 : 0;
   q.runs = form & F_RUNS ? 1 : 0;
   q.divTilesN = FastDiv((uint32_t)tilesN);

@@ -210,12 +210,12 @@ def test_gemm_short_rows_kernel(M, N, K, cfg):
         assert np.array_equal(host(Y), oracle.scale_bias(ref, sc, bi, axis))
 
 
-@pytest.mark.parametrize("cfg", [-1, *range(10, 18)])
+@pytest.mark.parametrize("cfg", [-1, *range(10, 18), *range(30, 38)])
 @pytest.mark.parametrize("M,N,K,pa,pb", [(1, 1, 1, 0, 0), (33, 31, 64, 0, 0), (31, 129, 63, 1, 2), (65, 64, 65, 0, 1), (64, 300, 128, 2, 2),
                                          (130, 257, 129, 0, 0), (32, 513, 191, 1, 0), (300, 36, 192, 0, 0), (513, 65, 193, 0, 0),
                                          (257, 130, 256, 0, 2)])
 def test_gemm_short_rows_matrix_cores(M, N, K, pa, pb, cfg):
-    """Rows of one to four words in every launch form: edges of both block sizes, odd columns, padded operands, garbage past
+    """Rows of one to four words in every launch form, with one block of rows a wave and with several: edges of both block sizes, odd columns, padded operands, garbage past
     K, both maps with the channel along either axis."""
     print(f"short rows {M}x{N}x{K} +{pa} +{pb} cfg={cfg}", flush=True)
     rng = np.random.default_rng(M + N + K)
@@ -239,11 +239,54 @@ def test_gemm_short_rows_matrix_cores(M, N, K, pa, pb, cfg):
         assert np.array_equal(host(Y), oracle.scale_bias(ref, sc, bi, axis))
 
 
+@pytest.mark.parametrize("M,N,K,pa,pb", [(1, 4, 128, 0, 0), (7, 1020, 65, 0, 2), (8, 1024, 100, 1, 1), (9, 1028, 128, 0, 1), (16, 2052, 256, 2, 0),
+                                         (15, 516, 193, 1, 3), (2, 3000, 256, 0, 2)])
+def test_gemm_few_short_rows(M, N, K, pa, pb):
+    """At most 16 rows of two or four words: edges of the groups of rows and of the workgroup's columns, padded operands, garbage
+    past K, both maps with the channel along either axis."""
+    print(f"few short rows {M}x{N}x{K} +{pa} +{pb}", flush=True)
+    rng = np.random.default_rng(M + N + K)
+    A, Bm = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+
+    def operand(a, pad):
+        w = np.concatenate([as_u64(B.bnn_encode(dev(a))), np.full((len(a), pad), 0x5A5A, np.uint64)], axis=1)
+        if K % 64:
+            w[:, (K - 1) // 64] |= np.uint64(0xFFFFFFFFFFFFFFFF >> (K % 64) << (K % 64)) & np.uint64(0x9669C33CA55A0FF0)
+        return dev(w.view(np.int64))
+    Ap, Bp, ref = operand(A, pa), operand(Bm, pb), oracle.gemm_pm1(A, Bm)
+    out, names = kernels_of(lambda: B.bnn_xnor_gemm(Ap, Bp, K, cfg=18))
+    assert names == ["xnor_gemm_fewrows"] and np.array_equal(host(out), ref)
+    for axis, ch in (("row", M), ("col", N)):
+        sc, bi = rng.standard_normal(ch).astype(np.float32), rng.standard_normal(ch).astype(np.float32)
+        Ci, Y = B.bnn_xnor_gemm_epilogue(Ap, Bp, K, dev(sc), dev(bi), B.CH_ROW if axis == "row" else B.CH_COL, want_int=True, cfg=18)
+        assert np.array_equal(host(Ci), ref)
+        assert np.array_equal(host(Y), oracle.scale_bias(ref, sc, bi, axis))
+
+
+@pytest.mark.parametrize("M,N,K,kernel", [
+    (1, 32768, 128, "fewrows"), (1, 32764, 128, "lowk"), (8, 147456, 100, "fewrows"), (8, 147452, 100, "lowk"), (16, 589824, 256, "fewrows"),
+    (16, 589820, 256, "lowk"), (17, 600000, 128, "lowk"), (2, 400001, 128, "fp4"), (2, 400000, 64, "lowk"), (13, 2097156, 70, "lowk"),
+    (24, 400004, 100, "fp4"), (24, 300004, 100, "lowk"), (33, 400004, 100, "lowk"),                                          # rows inside half lines
+    (200, 400001, 100, "fp4"), (300, 230001, 100, "lowk"), (300, 229001, 100, "fp4"),             # odd columns, 275 MB
+    (5000, 15001, 100, "lowk"), (6000, 13001, 100, "fp4"), (60000, 1301, 100, "fp4"), (6001, 13999, 64, "lowk")])
+def test_gemm_short_rows_rule_by_rows(M, N, K, kernel):
+    """Which kernel takes short rows by their number (256 compute units), and its values against a vector-ALU tile's."""
+    print(f"short rows rule by rows {M}x{N}x{K}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    r = lambda n: torch.randint(-2**63, 2**63 - 1, (n, B.packed_words(K)), dtype=torch.int64, device=DEV, generator=g)
+    A, Bm = r(M), r(N)
+    got, names = kernels_of(lambda: B.bnn_xnor_gemm(A, Bm, K))
+    assert torch.equal(got, B.bnn_xnor_gemm(A, Bm, K, cfg=3))
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert names[0].startswith("xnor_gemm_" + kernel), names
+
+
 @pytest.mark.parametrize("M,N,K,short", [
     (64, 64, 256, True), (64, 64, 64, False), (64, 63, 256, False),           # small calls: even words, columns by four
     (512, 4096, 60, True), (512, 4112, 190, True), (256, 4112, 190, False),   # odd words from 300 blocks on
     (300, 20004, 128, True), (300, 20004, 64, False), (96, 40004, 128, False), # rows inside half lines
-    (2048, 31264, 128, True), (2048, 31265, 100, True), (2048, 31252, 50, False)])             # beyond 256 MB
+    (2048, 31264, 128, True), (2048, 31252, 50, False),                                        # beyond 256 MB
+    (2048, 33573, 100, True), (2048, 33569, 100, False)])                                      # columns not by four: 275 MB
 def test_gemm_short_rows_rule(M, N, K, short):
     """Which kernel takes short rows, and its values against a vector-ALU tile's."""
     print(f"short rows rule {M}x{N}x{K}", flush=True)
