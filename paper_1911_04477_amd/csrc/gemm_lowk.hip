@@ -141,11 +141,12 @@ bool lowk_applicable(const GemmParams &p) { return p.Kw64 <= 4; }
 //     12.6, 13.8; but 19 x 325160 x 200 11.4 against 9.6);
 //   columns that are no multiple of 4: the staged tiles and the split kernel are equal or faster (256 x 50177 x 50 13.5
 //     against 14.2), except beyond the cache, where rows share lines and it counts which workgroups of an XCD run together
-//     (70 sizes of 256 to 700 MB): from 250 to 2100 rows 32 x 32 side by side in runs from 275 MB on (987 x 140757 x 64 107, staged
+//     (70 sizes of 256 to 700 MB): from 257 to 2100 rows 32 x 32 side by side in runs from 275 MB on (987 x 140757 x 64 107, staged
 //     140, one above the other 170; 1689 x 52870 x 256 76, 92, 84; but 541 x 119587 x 64, 258 MB, 52 against 44 staged); more rows one
 //     above the other in runs (4096 x 30001 x 250 95, staged 161), staged below 300 MB, or 330 MB with few columns (15380 x 4763 x
 //     100 55 against 71; 200000 x 401 x 128 73 against 109); fewer rows staged (36 x 3408733 x 53 152 against 237 one above the
-//     other, 165 x 852363 x 256 157, 199);
+//     other, 165 x 852363 x 256 157, 199; 256 x 332765 x 100
+//     87, 119; but 260 x 347289 x 200 93, 74);
 //   small calls: 32 x 32 blocks up to two of 64 x 64 per unit (64 x 64 x 256 4.6 -> 3.0, 256 x 1000 x 200 5.3 -> 3.3); rows of
 //     one and three words have the split kernel up to 300 of them, equal within 5 % either way.
 enum : int { F_64 = 1, F_ABREAST = 2, F_RUNS = 4 };
@@ -154,7 +155,7 @@ static int lowk_rule(const GemmParams &p) {
   const int64_t out = (int64_t)p.M * p.N * 4 * ((p.C ? 1 : 0) + (p.Y ? 1 : 0));
   const bool beyond = out > 256000000, odd_words = p.Kw64 % 2 != 0;
   if (!map_columns_by_four(p)) {
-    if (p.M < 250 || out < 275000000) return -1;
+    if (p.M <= 256 || out < 275000000) return -1;
     if (p.M <= 2100) return F_RUNS | F_ABREAST;
     return p.N >= 2000 && out >= (p.N >= 14000 ? 300000000 : 330000000) ? F_RUNS : -1;
   }

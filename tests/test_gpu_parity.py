@@ -267,7 +267,7 @@ def test_gemm_few_short_rows(M, N, K, pa, pb):
     (1, 32768, 128, "fewrows"), (1, 32764, 128, "lowk"), (8, 147456, 100, "fewrows"), (8, 147452, 100, "lowk"), (16, 589824, 256, "fewrows"),
     (16, 589820, 256, "lowk"), (17, 600000, 128, "lowk"), (2, 400001, 128, "fp4"), (2, 400000, 64, "lowk"), (13, 2097156, 70, "lowk"),
     (24, 400004, 100, "fp4"), (24, 300004, 100, "lowk"), (33, 400004, 100, "lowk"),                                          # rows inside half lines
-    (200, 400001, 100, "fp4"), (300, 230001, 100, "lowk"), (300, 229001, 100, "fp4"),             # odd columns, 275 MB
+    (200, 400001, 100, "fp4"), (256, 300001, 100, "fp4"), (257, 300001, 100, "lowk"), (300, 230001, 100, "lowk"), (300, 229001, 100, "fp4"),             # odd columns, 275 MB
     (5000, 15001, 100, "lowk"), (6000, 13001, 100, "fp4"), (60000, 1301, 100, "fp4"), (6001, 13999, 64, "lowk")])
 def test_gemm_short_rows_rule_by_rows(M, N, K, kernel):
     """Which kernel takes short rows by their number (256 compute units), and its values against a vector-ALU tile's."""
