@@ -232,7 +232,9 @@ BNN_API bnn_status bnn_conv2d_packed(const uint64_t *x_packed, const uint64_t *w
  *   Channels into every layer are a multiple of 128, out of the last one of 64, at most 512; the maps have to fit
  *   160 KB of LDS with their tables (BNN_ERR_UNSUPPORTED otherwise).
  * bnn_conv_chain_pays: 1 where the chain is supported and expected to be faster than the layers one by one on the
- *   current device, else 0.  An image occupies one compute unit, so that is a question of how many there are.
+ *   current device, else 0.  An image occupies one compute unit, so that is a question of how many there are.  The
+ *   times it compares are those of 32 x 32 maps at the start: chains of smaller maps get 0 at some sizes where 1 would
+ *   be right; bnn_conv_chain runs them all the same.
  */
 typedef struct {
   const void *w_chain;

@@ -75,8 +75,9 @@ __device__ __forceinline__ v8i expand_e2m1(uint32_t x) {
 // 32 bits -> 32 codes that are 0 where the bit is 0: the matrix instruction then counts the positions where both bits
 // are 1 (S), and the sum of the +-1 products is K - 2 pa - 2 pb + 4 S with the set bits pa, pb of the two rows.  Half of
 // the products are 0 and none is negative, so the adders toggle less and the chip holds a higher clock under the same
-// loop (512 x 256 x 8 x 8 layer 18.9 -> 17.3 us, 4096^3 34.8 -> 30.2, with nothing else changed), and the expansion is
-// ands: bit 0, 1, 2 of a nibble alone are the codes 0.5, 1, 2.  A keeps the bits in place (the fourth moves to the
+// loop (with the counting of set bits: 8192^3 232 -> 211 us, 4096^3 33.9 -> 32.1).  Long explicit rows and the chain of
+// convolutions use these codes; the tiles of single convolutions do not (2 to 3 % at most, the counting takes it back).  The
+// expansion is ands: bit 0, 1, 2 of a nibble alone are the codes 0.5, 1, 2.  A keeps the bits in place (the fourth moves to the
 // second's), B swaps the first and the third, so that every product of two set bits is 1.  11 vector instructions per
 // pair of dwords against 14.  NOW as above.
 template <bool NOW>

@@ -159,7 +159,7 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
   const int per = (nc + KS - 1) / KS;
   const int cb = min(wave * per, nc), ce = min(cb + per, nc);
   // 64 x 64 explicit tiles leave the loop between its chunks, which keeps their accumulators where they are (256 x 4096 x 4096
-  // 7.2 -> 6.8 us, 512 x 2048 x 4608 7.5 -> 7.1); the others are up to 3 % faster with a condition around the second chunk.
+  // 7.2 -> 6.8 us in turn on one card, 7.2 on another; 512 x 2048 x 4608 7.5 -> 7.1); the others are up to 3 % faster with a condition around the second chunk.
   constexpr bool LEAVE = WT == 2 && !CONV;
   u32x4 a0[WT], b0[WT], a1[WT], b1[WT], ab[2][WT], bb[2][WT];
   if constexpr (LEAVE) {
