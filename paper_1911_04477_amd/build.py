@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbnn.so")
 FASTCALL = os.path.join(HERE, "_fastcall.so")
 OBJ_DIR = os.path.join(HERE, "_build")
-SOURCES = ["api.hip", "encode.hip", "im2col.hip", "gemm.hip", "gemm_lowk.hip", "gemm_fewrows.hip", "gemm_fp4.hip", "gemm_fp4_split.hip", "conv.hip", "conv_chain.hip", "conv_pointwise.hip", "glue.hip", "mfma.hip", "control.hip"]
+SOURCES = ["api.hip", "encode.hip", "im2col.hip", "gemm.hip", "gemm_lowk.hip", "gemm_fewrows.hip", "gemm_fp4.hip", "gemm_fp4_split.hip", "conv.hip", "conv_first_sign.hip", "conv_chain.hip", "conv_pointwise.hip", "glue.hip", "mfma.hip", "control.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # Packed-FP32 VALU forms are disabled for all device code of this library.
@@ -25,10 +25,10 @@ FLAGS = [
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 
-# conv.hip: the matrix-core first layer reads its accumulators on the vector unit; keeping them in
+# conv.hip, conv_first_sign.hip: the matrix-core first layer reads its accumulators on the vector unit; keeping them in
 # ordinary vector registers (not accumulation registers) saves a move per element, and those
 # moves queue behind the matrix instruction in flight.
-EXTRA_FLAGS = {"conv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+EXTRA_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("conv.hip", "conv_first_sign.hip")}
 
 
 # Checker build of the HOST side (argument validation, dispatch, launch code) with AddressSanitizer

@@ -243,4 +243,9 @@ bnn_status run_im2col(const float *x, int N, int C, int H, int W, int kH, int kW
 bnn_status launch_conv2d_f32_k27(const float *x, const float *w, int N, int H, int W, int D, int sH, int sW, int pH,
                                  int pW, const float *scale, const float *bias, float *out, hipStream_t s);
 
+// Signs of the 3x3x3 layer for more than a few pixels (conv_first_sign.hip).
+bool first_sign_f16_applicable(int N, int H, int W, int D, int sH, int sW, int pH, int pW);
+bnn_status launch_first_sign_f16(const float *x, const float *w, int N, int H, int W, int D, int sH, int sW, int pH, int pW,
+                                 const float *scale, const float *bias, uint64_t *out, hipStream_t s);
+
 }  // namespace bnn

@@ -12,6 +12,7 @@
 
 #include "common.h"
 #include "bnn_testing.h"
+#include "conv_first.h"
 
 namespace bnn {
 
@@ -149,137 +150,22 @@ __global__ __launch_bounds__(256) void conv2d_f32_sign_kernel(const float *__res
   }
 }
 
-// ---- the 3x3x3 layer (K = 27) on the fp32 matrix cores --------------------------------------
-// V_MFMA_F32_32X32X1_2B_F32 multiplies a 32 x 1 column by a 1 x 32 row and adds the 32 x 32
-// product to its accumulator, for two independent blocks at once; one reduction step at a time,
-// each output element goes through exactly the fused multiply-add chain over (c, kh, kw) that
-// the general kernel above runs (checked bit for bit against fmaf chains, denormals, infinities
-// and signed zeros included), at twice the rate of unpacked vector multiply-adds.
-//   rows (operand A)    : 32 output channels; lanes l and l + 32 hold the same filter tap
-//   columns (operand B) : the wave's 64 pixels, block 0 = pixels 0..31, block 1 = pixels 32..63;
-//                         lane l supplies the patch value of pixel l
-//   accumulators        : register r of block b, lane l = channel 8*(r/4) + 4*(l/32) + r%4 of
-//                         pixel 32*b + l%32
-// A workgroup stages the filter taps of up to 128 channels in LDS ([tap][channel], odd row
-// stride), then each wave walks over its pixel groups: 27 clamped loads per lane, four channel
-// groups x 27 matrix instructions, and the affine map + sign on the vector unit.
-// NG: channel groups of 32 per workgroup (blockIdx.y).  Four share a patch's loads; with too few pixels to give every
-// SIMD four waves that way (the chains of a group are 27 dependent instructions of 64 clocks), one group per
-// workgroup makes four times as many waves.
-constexpr int C1M_RS(int NG) { return 32 * NG + 1; }  // LDS row stride of the tap-major filter tile
-typedef float c1m_v32f __attribute__((ext_vector_type(32)));
-
-__device__ __forceinline__ uint32_t c1m_spread_nibbles(uint32_t m) {
-  // nibble q of a 16-bit mask -> bits 8q .. 8q+3
-  return (m & 0xFu) | ((m & 0xF0u) << 4) | ((m & 0xF00u) << 8) | ((m & 0xF000u) << 12);
-}
-
-// Stage the filter taps of channels ch0 .. ch0 + 32 * NG - 1 tap-major in LDS (read [channel][tap]
-// contiguously; channels past D are zero) and their scale / bias (past D, or without an affine
-// map: fma(0, acc, -1) < 0, so such bits are 0).
-template <int NG>
-__device__ __forceinline__ void c1m_stage_filters(float *sTap, float *sSc, float *sBi, const float *__restrict__ w,
-                                                  const float *__restrict__ scale, const float *__restrict__ bias,
-                                                  int ch0, int nch, bool affine) {
-  const int tid = threadIdx.x;
-  for (int idx = tid; idx < 27 * 32 * NG; idx += 256) {
-    const int ch = idx / 27, k = idx - 27 * ch;
-    sTap[k * C1M_RS(NG) + ch] = ch < nch ? w[(size_t)ch0 * 27 + idx] : 0.0f;
-  }
-  if (tid < 32 * NG) {
-    const bool real = tid < nch && affine;
-    sSc[tid] = real ? scale[ch0 + tid] : 0.0f;
-    sBi[tid] = real ? bias[ch0 + tid] : -1.0f;
-  }
-}
-
-// Issue the 27 loads of pixel p's patch: every tap unconditionally from a clamped (always
-// readable) position; bit r of `inside` says whether tap (r / 3, r % 3) lies in the image.
-__device__ __forceinline__ void c1m_issue_patch(const float *__restrict__ x, uint32_t p, uint32_t total_pix, int H,
-                                                int W, int sH, int sW, int pH, int pW, int OH, int OW, FastDiv divOW,
-                                                FastDiv divOH, float (&raw)[27], uint32_t &inside) {
-  const bool pv = p < total_pix;
-  const uint32_t pc = pv ? p : 0u;
-  const uint32_t t = fdiv(pc, divOW);
-  const uint32_t ow = pc - t * OW;
-  const uint32_t n = fdiv(t, divOH);
-  const uint32_t oh = t - n * OH;
-  const int ih0 = (int)(oh * sH) - pH, iw0 = (int)(ow * sW) - pW;
-  const float *xn = x + (size_t)n * 3 * H * W;
-  uint32_t rok = 0, cok = 0;
-  int roff[3], coff[3];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const int ih = ih0 + j, iw = iw0 + j;
-    rok |= (uint32_t)(pv && ih >= 0 && ih < H) << j;
-    cok |= (uint32_t)(iw >= 0 && iw < W) << j;
-    roff[j] = (ih < 0 ? 0 : (ih >= H ? H - 1 : ih)) * W;
-    coff[j] = iw < 0 ? 0 : (iw >= W ? W - 1 : iw);
-  }
-  inside = 0;
-#pragma unroll
-  for (int r = 0; r < 9; ++r) inside |= (((rok >> (r / 3)) & (cok >> (r % 3))) & 1u) << r;
-#pragma unroll
-  for (int k = 0; k < 27; ++k) {
-    const int c = k / 9, r = k % 9;
-    raw[k] = xn[(size_t)c * H * W + roff[r / 3] + coff[r % 3]];
-  }
-}
-
-// 27 dependent matrix instructions: channel group g (32 channels) x this wave's 64 pixels.
-template <int NG>
-__device__ __forceinline__ c1m_v32f c1m_chain(const float *wg, const float (&xv)[27]) {
-  c1m_v32f acc;
-#pragma unroll
-  for (int r = 0; r < 32; ++r) acc[r] = 0.0f;
-#pragma unroll
-  for (int k = 0; k < 27; ++k) acc = __builtin_amdgcn_mfma_f32_32x32x1f32(wg[k * C1M_RS(NG)], xv[k], acc, 0, 0, 0);
-  return acc;
-}
-
-// Affine map and sign of one channel group's accumulators -> the 32 channel bits of this
-// lane's own pixel.  Lanes l and l + 32 hold the two channel halves of a pixel: l < 32 keeps
-// its block-0 bits and receives the partner's, l >= 32 likewise with block 1.
-__device__ __forceinline__ uint32_t c1m_sign_bits(const c1m_v32f &acc, const float *sSc, const float *sBi, int g,
-                                                  int half) {
-  // rows descend: every sign is shifted in with one add-with-carry, m = 2 * m + (y >= 0)
-  uint32_t m[2] = {0u, 0u};
-#pragma unroll
-  for (int q = 3; q >= 0; --q) {
-    const float4 sc = *reinterpret_cast<const float4 *>(sSc + 32 * g + 8 * q + 4 * half);
-    const float4 bi = *reinterpret_cast<const float4 *>(sBi + 32 * g + 8 * q + 4 * half);
-    const float scv[4] = {sc.x, sc.y, sc.z, sc.w}, biv[4] = {bi.x, bi.y, bi.z, bi.w};
-#pragma unroll
-    for (int e = 3; e >= 0; e -= 2) {
-      const int rr = 4 * q + e;
-      const float y[4] = {fmaf(scv[e], acc[rr], biv[e]), fmaf(scv[e], acc[16 + rr], biv[e]),
-                          fmaf(scv[e - 1], acc[rr - 1], biv[e - 1]), fmaf(scv[e - 1], acc[15 + rr], biv[e - 1])};
-      shift_in_signs<2>(m, y);
-    }
-  }
-  const uint32_t own = half ? m[1] : m[0];
-  const uint32_t got = (uint32_t)__shfl_xor((int)(half ? m[0] : m[1]), 32);
-  const uint32_t lo = half ? got : own, hi = half ? own : got;  // channels 8q+0..3 / 8q+4..7
-  return c1m_spread_nibbles(lo) | (c1m_spread_nibbles(hi) << 4);
-}
-
-// Packed-sign output.
-// On this chip the fp32 matrix instructions and the vector ALU do not run side by side (vector
+// ---- the 3x3x3 layer (K = 27) on the fp32 matrix cores: conv_first.h --------------------------
+// Packed-sign output for few pixels (conv_first_sign.hip takes the others): one group of 32 channels per workgroup, since the
+// chains of a group are 27 dependent instructions of 64 clocks (batch 1 of the 32 x 32, 128-channel layer: four groups 8.6 us,
+// one 4.3).  On this chip the fp32 matrix instructions and the vector ALU do not run side by side (vector
 // instructions placed between the matrix instructions of a chain lengthen it by their full
-// issue time, measured), so nothing is gained by interleaving the sign step with the next chain:
-// the loop is the plain sequence loads, one chain per group of 32 channels followed by its sign
-// step, store, and several resident waves per SIMD cover the load latency.
-template <int NG>
+// issue time, measured), so the loop is the plain sequence loads, chain, sign step, store.
 __global__ __launch_bounds__(256, 4) void conv2d_f32_k27_mfma_sign_kernel(
     const float *__restrict__ x, const float *__restrict__ w, int H, int W, int D, int sH, int sW, int pH, int pW,
     int OH, int OW, const float *__restrict__ scale, const float *__restrict__ bias, uint64_t *__restrict__ outp,
     int cw_out, FastDiv divOW, FastDiv divOH, uint32_t total_pix, uint32_t ngroups, int groups_per_wave) {
-  __shared__ float sTap[27 * C1M_RS(NG)];
-  __shared__ __attribute__((aligned(16))) float sSc[32 * NG];
-  __shared__ __attribute__((aligned(16))) float sBi[32 * NG];
+  __shared__ float sTap[27 * C1M_RS(1)];
+  __shared__ __attribute__((aligned(16))) float sSc[32];
+  __shared__ __attribute__((aligned(16))) float sBi[32];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, l32 = lane & 31;
-  const int ch0 = 32 * NG * (int)blockIdx.y;
+  const int ch0 = 32 * (int)blockIdx.y;
   const uint32_t g_first = ((uint32_t)blockIdx.x * 4u + (uint32_t)wave) * (uint32_t)groups_per_wave;
   const uint32_t g_end = min(g_first + (uint32_t)groups_per_wave, ngroups);
   // the first patch is requested before the filters are staged, so the two latencies overlap
@@ -287,8 +173,7 @@ __global__ __launch_bounds__(256, 4) void conv2d_f32_k27_mfma_sign_kernel(
   float xv[27];
   uint32_t inside;
   c1m_issue_patch(x, g_first * 64u + (uint32_t)lane, total_pix, H, W, sH, sW, pH, pW, OH, OW, divOW, divOH, xv, inside);
-  const int nch = min(32 * NG, D - ch0);  // >= 1 by the grid
-  c1m_stage_filters<NG>(sTap, sSc, sBi, w, scale, bias, ch0, nch, true);
+  c1m_stage_filters<1>(sTap, sSc, sBi, w, scale, bias, ch0, min(32, D - ch0), true);
   __syncthreads();  // the only barrier: from here on the waves run independently
 
   for (uint32_t grp = g_first; grp < g_end; ++grp) {  // wave-uniform bounds
@@ -297,27 +182,13 @@ __global__ __launch_bounds__(256, 4) void conv2d_f32_k27_mfma_sign_kernel(
       c1m_issue_patch(x, p, total_pix, H, W, sH, sW, pH, pW, OH, OW, divOW, divOH, xv, inside);
 #pragma unroll
     for (int k = 0; k < 27; ++k) xv[k] = ((inside >> (k % 9)) & 1u) ? xv[k] : 0.0f;
-    uint32_t gw[NG];
-#pragma unroll
-    for (int g = 0; g < NG; ++g) gw[g] = 0u;
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      if (32 * g >= nch) break;  // workgroup-uniform: groups past the last channel keep zero bits
-      const c1m_v32f acc = c1m_chain<NG>(sTap + 32 * g + l32, xv);
-      gw[g] = c1m_sign_bits(acc, sSc, sBi, g, half);
-    }
-    if (p < total_pix) {
-      if constexpr (NG == 4) {
-        const int word0 = 2 * (int)blockIdx.y;
-        uint64_t *o = outp + (size_t)p * cw_out + word0;
-        o[0] = ((uint64_t)gw[1] << 32) | gw[0];
-        if (word0 + 1 < cw_out) o[1] = ((uint64_t)gw[3] << 32) | gw[2];
-      } else {  // a 32-channel half word; the last group also writes the half that holds no channel
-        const int h0 = (int)blockIdx.y;
-        uint32_t *o = reinterpret_cast<uint32_t *>(outp + (size_t)p * cw_out);
-        o[h0] = gw[0];
-        if (h0 + 1 == (int)gridDim.y && h0 + 1 < 2 * cw_out) o[h0 + 1] = 0u;
-      }
+    const c1m_v32f acc = c1m_chain<1>(sTap + l32, xv);
+    const uint32_t word = c1m_sign_bits(acc, sSc, sBi, 0, half);
+    if (p < total_pix) {  // a 32-channel half word; the last group also writes the half that holds no channel
+      const int h0 = (int)blockIdx.y;
+      uint32_t *o = reinterpret_cast<uint32_t *>(outp + (size_t)p * cw_out);
+      o[h0] = word;
+      if (h0 + 1 == (int)gridDim.y && h0 + 1 < 2 * cw_out) o[h0 + 1] = 0u;
     }
   }
 }
@@ -389,15 +260,6 @@ static dim3 c1m_grid(int64_t total_pix, int D, int ng, int *gpw, int64_t wave_sl
   *gpw = (int)g;
   const int64_t waves = (ngroups + g - 1) / g;
   return dim3((unsigned)((waves + 3) / 4), (unsigned)((D + 32 * ng - 1) / (32 * ng)));
-}
-
-// Packed signs: one channel group per workgroup while that does not give a SIMD more than four waves per 128 channels
-// (32 x 32 maps, 128 channels: batch 1 8.6 -> 4.3 us, batch 32 9.0 -> 5.6, batch 63 9.2 -> 8.4; batch 128 13.5 against 14.0,
-// batch 256 22.5 against 27.3: the patch's loads and selects are repeated per group) nor six in all (batch 32, 384
-// channels 13.2 -> 11.7; 512 13.2 against 13.7, 1024 21.0 against 26.1; batch 63, 512 21.9 against 26.6).
-static bool c1m_split(int64_t total_pix, int D) {
-  const int64_t pix_groups = (total_pix + 63) / 64, cu = device_cu_count();
-  return pix_groups <= 4 * cu && pix_groups * (((int64_t)D + 31) / 32) <= 24 * cu;
 }
 
 // Filter bank of a fully-connected layer whose input is a flattened NCHW map [C, H, W],
@@ -609,18 +471,13 @@ extern "C" bnn_status bnn_conv2d_f32_sign(const float *x, const float *w, int N,
     ProfScope ps(KID_CONV_F32_SIGN, s);
     const dim3 block(256);
     if (K == 27 && C == 3 && kH == 3 && kW == 3) {
+      if (first_sign_f16_applicable(N, H, W, D, sH, sW, pH, pW))
+        return launch_first_sign_f16(x, w, N, H, W, D, sH, sW, pH, pW, scale, bias, out_packed, s);
       int gpw;
-      const bool split = c1m_split(total, D);
-      const dim3 grid = c1m_grid(total, D, split ? 1 : 4, &gpw);
-      const uint32_t ngroups = (uint32_t)((total + 63) / 64);
-      const int cw = (int)bnn_packed_words(D);
-      const FastDiv dOW((uint32_t)OW), dOH((uint32_t)OH);
-      if (split)
-        hipLaunchKernelGGL(conv2d_f32_k27_mfma_sign_kernel<1>, grid, block, 0, s, x, w, H, W, D, sH, sW, pH, pW, (int)OH,
-                           (int)OW, scale, bias, out_packed, cw, dOW, dOH, (uint32_t)total, ngroups, gpw);
-      else
-        hipLaunchKernelGGL(conv2d_f32_k27_mfma_sign_kernel<4>, grid, block, 0, s, x, w, H, W, D, sH, sW, pH, pW, (int)OH,
-                           (int)OW, scale, bias, out_packed, cw, dOW, dOH, (uint32_t)total, ngroups, gpw);
+      const dim3 grid = c1m_grid(total, D, 1, &gpw);
+      hipLaunchKernelGGL(conv2d_f32_k27_mfma_sign_kernel, grid, block, 0, s, x, w, H, W, D, sH, sW, pH, pW, (int)OH, (int)OW,
+                         scale, bias, out_packed, (int)bnn_packed_words(D), FastDiv((uint32_t)OW), FastDiv((uint32_t)OH),
+                         (uint32_t)total, (uint32_t)((total + 63) / 64), gpw);
     } else {
       const dim3 grid((unsigned)((total + 255) / 256));
       hipLaunchKernelGGL(conv2d_f32_sign_kernel<0>, grid, block, 0, s, x, w, C, H, W, D, kH, kW, sH, sW, pH, pW,

@@ -1711,6 +1711,71 @@ def test_first_layer_few_and_many_pixels(N, H, W, D):
     assert np.array_equal(got, oracle.pack_nhwc(ref))
 
 
+@pytest.mark.parametrize("N,H,W,D,stride,pad", [
+    (24, 32, 32, 96, 1, 1),     # workgroups of four waves, two of 64 channels, the second half empty
+    (13, 63, 65, 130, 1, 2),    # 64 pixels cross rows and images, one word and two channels
+    (64, 32, 33, 250, 1, 1),    # eight waves, the last group of 32 channels partial
+    (150, 61, 59, 257, 2, 0),   # 16 waves, one channel in the last workgroup
+    (513, 32, 32, 10, 1, 1),    # several groups of pixels a wave, the last wave without any
+    (4000, 5, 7, 40, 4, 1)])    # 64 pixels cross many images
+def test_first_layer_signs_from_split_products(N, H, W, D, stride, pad):
+    """Enough pixels for the half-precision kernel: its bits are those of the fma chains.  Ordinary values, where a few
+    outputs a wave are in doubt, then images with an area of zeros and channels that have no bias."""
+    print(f"first layer signs N={N} {H}x{W} D={D} stride={stride} pad={pad}", flush=True)
+    rng = np.random.default_rng(N + H + W + D)
+    x = rng.standard_normal((N, 3, H, W)).astype(np.float32)
+    w = rng.standard_normal((D, 3, 3, 3)).astype(np.float32)
+    sc, bi = rng.standard_normal(D).astype(np.float32), 0.1 * rng.standard_normal(D).astype(np.float32)
+    for part in range(2):
+        if part == 1:
+            x[:, :, : (H + 1) // 2, : (W + 1) // 2] = 0.0
+            bi[::3] = 0.0
+            sc[::4] = 0.0
+        ref = oracle.conv2d_f32_seq(x, w, (stride, stride), (pad, pad), sc, bi)
+        got = as_u64(B.bnn_conv2d_f32_sign(dev(x), dev(w), dev(sc), dev(bi), (stride, stride), (pad, pad)))
+        assert np.array_equal(got, oracle.pack_nhwc(ref))
+
+
+@pytest.mark.parametrize("kind", ["specials", "nan", "ties", "large", "tiny", "filters", "scales"])
+@pytest.mark.parametrize("N,D", [(24, 96), (64, 256)])
+def test_first_layer_signs_beyond_the_bound(N, D, kind):
+    """Inputs whose signs the half-precision products cannot prove, in a few pixels or in all of them: the chains decide."""
+    print(f"first layer signs N={N} D={D} {kind}", flush=True)
+    rng = np.random.default_rng(N + D)
+    x = rng.standard_normal((N, 3, 32, 32)).astype(np.float32)
+    w = rng.standard_normal((D, 3, 3, 3)).astype(np.float32)
+    sc, bi = (rng.random(D) + 0.5).astype(np.float32), 0.1 * rng.standard_normal(D).astype(np.float32)
+    if kind == "specials":
+        x = inputs.inject_specials(x, 3, frac=0.002)
+    elif kind == "nan":
+        x.reshape(-1)[:: 5] = np.nan
+    elif kind == "ties":  # sums that are exactly 0, where the order of a sum in fp32 does not matter either
+        x, w = rng.integers(-2, 3, x.shape).astype(np.float32), rng.integers(-2, 3, w.shape).astype(np.float32)
+        sc, bi = np.ones(D, np.float32), np.zeros(D, np.float32)
+    elif kind == "large":  # beyond fp16, and near its end
+        x *= np.float32(1e6)
+        x[: N // 2] *= np.float32(0.02)
+    elif kind == "tiny":  # below fp16; subnormal; with and without a bias beside them
+        x *= np.float32(1e-9)
+        x[: N // 3] *= np.float32(1e-31)
+        bi[::2] = 0.0
+    elif kind == "filters":
+        w[1] *= np.float32(1e30)
+        w[2, 0, 0, 0] = np.inf
+        w[33, 1, 1, 1] = np.nan
+        w[40] *= np.float32(1e-42)
+        w[41] = 0.0
+        w[D - 1] *= np.float32(1e-20)
+    else:
+        sc[:8] = [0.0, -0.0, 1e30, -1e-30, np.inf, np.nan, 1e-44, -1.0]
+        bi[:4] = [0.0, -0.0, -1e30, 1e-40]
+        sc[40:48], bi[40:48] = 0.0, [0.0, -0.0, 1e-45, -1e-45, np.inf, -np.inf, np.nan, -3.0]
+    with np.errstate(all="ignore"):
+        ref = oracle.conv2d_f32_seq(x, w, (1, 1), (1, 1), sc, bi)
+    got = as_u64(B.bnn_conv2d_f32_sign(dev(x), dev(w), dev(sc), dev(bi), (1, 1), (1, 1)))
+    assert np.array_equal(got, oracle.pack_nhwc(ref))
+
+
 @pytest.mark.parametrize("N,D", [(4, 449), (4, 256), (3, 449)])
 def test_first_layer_large_maps(N, D):
     """Maps above and below 350 MB, channel counts on both sides of the rule and off the groups of 32 and 128: the
