@@ -129,6 +129,7 @@ struct GemmParams {
   int colperm;         // int32 / fp32 output whose columns and strides are multiples of 4: a lane's columns are
                        // consecutive and go out as one store per row (vector ALU: in 256-column tiles, LDS row
                        // 64 * j + l holds tile column 4 * l + j)
+  int pairs;           // split-K kernel: two consecutive columns of a row are 8 aligned bytes of a map
   ConvGeom g;          // implicit B only
   HaloGeom halo;       // matrix-core convolution only
   uint64_t *outp;      // packed-sign output [pixels, cw_out] (packed epilogue only)

@@ -10,6 +10,8 @@
 // (rows 8q + 4 * (l / 32) + 0..3 of every block).
 //
 // Bound: latency (launch, one memory round trip for the operands, one exchange through LDS).
+#include <type_traits>
+
 #include "common.h"
 #include "fp4_tile.h"
 
@@ -26,7 +28,7 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
   const int tid = threadIdx.x;
   const int lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int ni = (int)fdiv(blockIdx.x, p.divTilesM), mi = (int)(blockIdx.x - (uint32_t)ni * (uint32_t)p.tilesM);
+  const int ni = (int)fdiv_sel(blockIdx.x, p.divTilesM), mi = (int)(blockIdx.x - (uint32_t)ni * (uint32_t)p.tilesM);
   const int m0 = mi * B32, n0 = ni * B32;
   const ConvGeom &g = p.g;
 
@@ -47,6 +49,20 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
       biw[j] = (int)ow * g.sW - g.pW;
     } else {
       brow[j] = reinterpret_cast<const char *>(p.B) + (size_t)n * (size_t)p.ldb * 8u;
+    }
+  }
+
+  // The columns' affine constants, requested before the operands: after them, a wait for the first operands could not
+  // tell how many loads follow.  (Requested when they are used: a memory round trip, 256 x 4096 x 4096 8.1 -> 7.0 us.)
+  float csc[WT], cbi[WT];
+#pragma unroll
+  for (int j = 0; j < WT; ++j) csc[j] = cbi[j] = 0.0f;
+  if (!SIGN && p.Y && p.axis == BNN_CH_COL) {  // uniform
+#pragma unroll
+    for (int j = 0; j < WT; ++j) {
+      const int n = min(n0 + WT * l32 + j, p.N - 1);
+      csc[j] = p.scale[n];
+      cbi[j] = p.bias[n];
     }
   }
 
@@ -170,7 +186,7 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
     if (cb < ce) load_chunk(cb, a0, b0);
     if (cb + 1 < ce) load_chunk(cb + 1, a1, b1);
   }
-  // the finishing waves' affine constants travel with the operands
+  // the finishing waves' affine constants of the rows travel with the operands
   const int mq = m0 + 8 * (wave & 3) + 4 * half;  // first of this lane's rows in row block 0
   const bool row_affine = SIGN || (p.Y && p.axis == BNN_CH_ROW);
   float sc[WT][4], bi[WT][4];
@@ -183,9 +199,11 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
       sc[i][e] = on ? p.scale[m] : 0.0f;  // rows past M: sign bit 0
       bi[i][e] = on ? p.bias[m] : -1.0f;
     }
-  // partial sums -> LDS [wave][block][quad][lane], as integers: fp32 holds them exactly for 2^24 values, and a wave
-  // whose range is longer than FLUSH chunks adds up its own slots
+  // Partial sums -> LDS [wave][block][quad][lane].  64 x 64 tiles of maps leave them as the accumulators hold them while the padded row
+  // has at most 2^24 values: sums are exact then (64 conversions a wave less).  Else as integers, and a wave whose range
+  // is longer than FLUSH chunks adds up its own slots.
   constexpr int FLUSH = 1 << 15;
+  const bool as_int = WT == 1 || SIGN || nc > (1 << 16);
   bool flushed = false;
   auto flush = [&]() {
 #pragma unroll
@@ -247,7 +265,20 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
       acc.init(0.0f);
     }
   }
-  flush();
+  if (as_int) {  // uniform
+    flush();
+  } else {
+#pragma unroll
+    for (int i = 0; i < WT; ++i)
+#pragma unroll
+      for (int j = 0; j < WT; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const v16f &v = acc.v[i][j];
+          reinterpret_cast<float4 *>(sPart)[((wave * WT * WT + i * WT + j) * 4 + q) * 64 + lane] =
+              make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+        }
+  }
   __syncthreads();
 
   // ---- wave q < 4 sums quad q ----------------------------------------------------------------------------------
@@ -260,13 +291,27 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
 #pragma unroll
       for (int j = 0; j < WT; ++j) {
         int t[4] = {corr, corr, corr, corr};
+        if (as_int) {
 #pragma unroll
-        for (int k = 0; k < KS; ++k) {
-          const int4 v = sPart[((k * WT * WT + i * WT + j) * 4 + wave) * 64 + lane];
-          t[0] += v.x;
-          t[1] += v.y;
-          t[2] += v.z;
-          t[3] += v.w;
+          for (int k = 0; k < KS; ++k) {
+            const int4 v = sPart[((k * WT * WT + i * WT + j) * 4 + wave) * 64 + lane];
+            t[0] += v.x;
+            t[1] += v.y;
+            t[2] += v.z;
+            t[3] += v.w;
+          }
+        } else {
+          float u[4] = {(float)corr, (float)corr, (float)corr, (float)corr};
+#pragma unroll
+          for (int k = 0; k < KS; ++k) {
+            const float4 v = reinterpret_cast<const float4 *>(sPart)[((k * WT * WT + i * WT + j) * 4 + wave) * 64 + lane];
+            u[0] += v.x;
+            u[1] += v.y;
+            u[2] += v.z;
+            u[3] += v.w;
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) t[e] = (int)u[e];
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) s[i][j][e] = t[e];
@@ -274,37 +319,49 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
   }
 
   if constexpr (!SIGN) {
-    if (wave >= 4) return;
+    if (wave >= 4 || m0 + 8 * wave >= p.M) return;  // uniform
     const int n = n0 + WT * l32;
     if (n >= p.N) return;
+    // Columns past N hold column N - 1 once more and go there; rows past M (of partial tiles) don't: with few rows, they would
+    // all write the same line (1 x 1024 x 8192 3.75 us, 4.1).
     int64_t off[WT];
-    float csc[WT], cbi[WT];
-    const bool col_affine = p.Y && p.axis == BNN_CH_COL;
 #pragma unroll
     for (int j = 0; j < WT; ++j) {
       const int c = min(n + j, p.N - 1);
       off[j] = c;
       if (p.img_stride != 0) {  // NCHW planes
-        const uint32_t img = fdiv((uint32_t)c, p.divOHW);
+        const uint32_t img = fdiv_sel((uint32_t)c, p.divOHW);
         off[j] = (int64_t)img * p.img_stride + ((uint32_t)c - img * p.OHW);
       }
-      csc[j] = col_affine ? p.scale[c] : 0.0f;
-      cbi[j] = col_affine ? p.bias[c] : 0.0f;
     }
+    const bool full = WT > 1 && m0 + B32 <= p.M;  // uniform; one block: no second copy of its few stores
+    auto store = [&](auto *base, int64_t ld, auto value) {
+      using V = typename std::remove_pointer<decltype(base)>::type;
+      typedef V vec __attribute__((ext_vector_type(WT)));
+      V *ptr[WT];
 #pragma unroll
-    for (int i = 0; i < WT; ++i)
+      for (int j = 0; j < WT; ++j) ptr[j] = base + off[j] + (int64_t)mq * ld;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int m = mq + 32 * i + e;
-        if (m >= p.M) continue;
+      for (int i = 0; i < WT; ++i) {
 #pragma unroll
-        for (int j = 0; j < WT; ++j) {
-          if (n + j >= p.N) continue;
-          if (p.C) p.C[(int64_t)m * p.ldc + off[j]] = s[i][j][e];
-          if (p.Y)
-            p.Y[(int64_t)m * p.ldy + off[j]] = row_affine ? fmaf(sc[i][e], (float)s[i][j][e], bi[i][e]) : fmaf(csc[j], (float)s[i][j][e], cbi[j]);
+        for (int e = 0; e < 4; ++e) {
+          if (!full && mq + 32 * i + e >= p.M) continue;
+          const int64_t row = (int64_t)(32 * i + e) * ld;  // uniform
+          if (WT > 1 && p.pairs) {  // uniform
+            vec v;
+#pragma unroll
+            for (int j = 0; j < WT; ++j) v[j] = value(i, j, e);
+            *reinterpret_cast<vec *>(ptr[0] + row) = v;
+          } else {
+#pragma unroll
+            for (int j = 0; j < WT; ++j) ptr[j][row] = value(i, j, e);
+          }
         }
       }
+    };
+    if (p.C) store(p.C, p.ldc, [&](int i, int j, int e) { return s[i][j][e]; });
+    if (row_affine) store(p.Y, p.ldy, [&](int i, int j, int e) { return fmaf(sc[i][e], (float)s[i][j][e], bi[i][e]); });
+    else if (p.Y) store(p.Y, p.ldy, [&](int i, int j, int e) { return fmaf(csc[j], (float)s[i][j][e], cbi[j]); });
   } else {
     // four sign bits per column and row block; lanes l and l + 32 hold the two nibbles of a byte.  The members of a
     // pooling window are consecutive columns: WT in this lane, the others in its neighbours.
@@ -355,6 +412,8 @@ static bnn_status launch_split(GemmParams &p, int bmode, int emode, hipStream_t 
   if (blocks > 0x7fffffffLL) return BNN_ERR_UNSUPPORTED;
   p.tilesN = (int)tn;
   p.divTilesM = FastDiv((uint32_t)p.tilesM);
+  p.pairs = p.N % 2 == 0 && (!p.C || p.ldc % 2 == 0) && (!p.Y || p.ldy % 2 == 0) &&
+            (p.img_stride == 0 || (p.OHW % 2 == 0 && p.img_stride % 2 == 0));
   const dim3 grid((unsigned)blocks), block(64 * KS);
   ProfScope ps(KID_XNOR_GEMM_FP4_SPLIT, s);
   if (bmode == 0) {
