@@ -31,6 +31,7 @@ extern "C" {
  *       wave, +1 of 64 x 64, +2 a workgroup's waves side by side, +4 contiguous runs of workgroups per XCD;
  *       30 .. 37  the same with three blocks of rows per wave
  *   18  the kernel for at most 16 such rows by very many columns (two or four words, columns and strides multiples of 4)
+ *   19  convolutions of at most 256 channels, 1 x 1 or 3 x 3, whose taps go straight from memory to the matrix cores
  * A value that a call cannot use (the packed epilogue needs a 32- or 64-row tile with two or
  * four column groups, or one of 21 to 28; 10 to 18 and 30 to 37 exist for an explicit B with int32 / fp32 output only;
  * 21 to 24 need K below 2^24, 29 what it says)
@@ -69,6 +70,14 @@ BNN_API bnn_status bnn_testing_conv2d_packed(const uint64_t *x_packed, const uin
 #define BNN_TESTING_REGION_VALUES 4
 BNN_API int bnn_testing_conv_region(int N, int C, int H, int W, int kH, int kW, int sH, int sW, int pH, int pW,
                                     int pool, int columns, int64_t *region);
+
+/*
+ * bnn_testing_conv_word -- host only, launches nothing: whether a convolution of a packed image (packed: packed output, else
+ * maps) goes to the kernel of configuration 19 on a device of `units` compute units: 2 it does, 1 it could, 0 it cannot,
+ * -1 for arguments bnn_conv2d_packed refuses.  (A pointwise map without stride or padding is an explicit GEMM before that.)
+ */
+BNN_API int bnn_testing_conv_word(int N, int C, int H, int W, int D, int kH, int kW, int sH, int sW, int pH, int pW, int pool,
+                                  int packed, int units);
 
 /*
  * bnn_testing_nontemporal_maps -- host only, launches nothing: whether the matrix-core GEMM stores an int32 map

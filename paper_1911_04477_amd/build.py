@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbnn.so")
 FASTCALL = os.path.join(HERE, "_fastcall.so")
 OBJ_DIR = os.path.join(HERE, "_build")
-SOURCES = ["api.hip", "encode.hip", "im2col.hip", "gemm.hip", "gemm_lowk.hip", "gemm_fewrows.hip", "gemm_fp4.hip", "gemm_fp4_split.hip", "conv.hip", "conv_first_sign.hip", "conv_chain.hip", "conv_pointwise.hip", "glue.hip", "mfma.hip", "control.hip"]
+SOURCES = ["api.hip", "encode.hip", "im2col.hip", "gemm.hip", "gemm_lowk.hip", "gemm_fewrows.hip", "gemm_fp4.hip", "gemm_fp4_split.hip", "conv.hip", "conv_first_sign.hip", "conv_chain.hip", "conv_pointwise.hip", "conv_word.hip", "glue.hip", "mfma.hip", "control.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # Packed-FP32 VALU forms are disabled for all device code of this library.

@@ -452,6 +452,20 @@ extern "C" int bnn_testing_conv_region(int N, int C, int H, int W, int kH, int k
   return 1;
 }
 
+// Declared in bnn_testing.h.
+extern "C" int bnn_testing_conv_word(int N, int C, int H, int W, int D, int kH, int kW, int sH, int sW, int pH, int pW, int pool,
+                                     int packed, int units) {
+  if (check_conv_geometry(N, C, H, W, kH, kW, sH, sW, pH, pW) != BNN_OK || N == 0 || D <= 0 || units <= 0 ||
+      (pool != 0 && pool != 2) || (pool && !packed))
+    return -1;
+  if (pool && ((bnn_conv_out_dim(H, kH, sH, pH) & 1) || (bnn_conv_out_dim(W, kW, sW, pW) & 1))) return -1;
+  if (conv_limits(N, C, H, W, D, kH, kW, sH, sW, pH, pW) != BNN_OK) return -1;
+  GemmParams p = conv_gemm(nullptr, nullptr, N, C, H, W, D, kH, kW, sH, sW, pH, pW, pool, nullptr, nullptr, nullptr, nullptr,
+                           nullptr);
+  p.n_cu = units;
+  return !conv_word_applicable(p, 1) ? 0 : conv_word_faster(p, packed) ? 2 : 1;
+}
+
 extern "C" bnn_status bnn_conv2d_f32_sign(const float *x, const float *w, int N, int C, int H, int W, int D, int kH,
                                           int kW, int sH, int sW, int pH, int pW, const float *scale,
                                           const float *bias, uint64_t *out_packed, void *stream) {

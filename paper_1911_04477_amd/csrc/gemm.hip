@@ -925,8 +925,9 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
   const bool short_rows = bmode == 0 && emode == 0 && lowk_applicable(p);
   const bool matrix = (((cfg >= 21 && cfg <= 24) || cfg == 29) && fp4_applicable(p)) || (cfg >= 25 && cfg <= 28);
   const bool few_rows = short_rows && fewrows_applicable(p);
+  const bool word = conv_word_applicable(p, bmode);
   const bool lowk = short_rows && ((cfg >= 10 && cfg <= 17) || (cfg >= 30 && cfg <= 37));
-  if (!valu && !matrix && !lowk && !(few_rows && cfg == 18)) cfg = -1;
+  if (!valu && !matrix && !lowk && !(few_rows && cfg == 18) && !(word && cfg == 19)) cfg = -1;
   if (few_rows && (cfg < 0 ? fewrows_faster(p) : cfg == 18)) return launch_fewrows(p, s);
   if (lowk) return launch_lowk(p, cfg % 10, s, cfg < 30 ? 1 : 3);
   if (short_rows && cfg < 0 && lowk_faster(p)) return launch_lowk(p, -1, s);
@@ -934,6 +935,7 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
     // The matrix cores; few outputs split the reduction axis, and so do rows too long for exact fp32 sums.
     p.colperm = emode == 0 && map_columns_by_four(p) ? 1 : 0;
     p.nt_store = emode == 0 && nontemporal_maps(p, bmode) ? 1 : 0;
+    if (word && (cfg < 0 ? tune.lean != 0 && conv_word_faster(p, emode) : cfg == 19)) return launch_conv_word(p, emode, s);
     if (cfg >= 25 && cfg <= 28) return launch_gemm_fp4_split(p, bmode, emode, s, cfg - 25);
     if (cfg < 0 && (fp4_split_applicable(p, bmode) || !fp4_applicable(p))) return launch_gemm_fp4_split(p, bmode, emode, s, -1);
     return launch_gemm_fp4(p, bmode, emode, s, cfg >= 29 ? cfg - 25 : cfg >= 21 ? cfg - 21 : -1, tune.lean != 0);

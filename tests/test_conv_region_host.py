@@ -100,3 +100,25 @@ def test_what_the_convolution_refuses_is_refused():
                  (1, 64, 4, 4, 3, 3, 1, 1, 0, 0, 0, 0)):
         with pytest.raises(ValueError):
             region(*args)
+
+
+@pytest.mark.parametrize("N,C,H,W,D,k,packed,want", [
+    (7, 64, 32, 32, 64, 3, 1, 1), (8, 64, 32, 32, 64, 3, 1, 2),        # one word: t = 1.75, 2
+    (10, 64, 32, 16, 128, 3, 0, 1), (11, 64, 32, 16, 128, 3, 0, 2),    # maps: 2.5, 2.75
+    (10, 65, 32, 32, 64, 3, 1, 1), (11, 65, 32, 32, 64, 3, 1, 2),      # two words: 2.5, 2.75
+    (16, 128, 32, 32, 64, 3, 0, 1), (17, 128, 32, 32, 64, 3, 0, 2),    # maps: 4, 4.25
+    (48, 129, 32, 32, 64, 3, 1, 1), (49, 192, 32, 32, 64, 3, 0, 2),    # three words: u = 0.75, 0.766
+    (64, 256, 32, 32, 64, 3, 1, 1), (65, 256, 32, 32, 64, 3, 1, 2), (128, 256, 32, 32, 64, 3, 0, 2),  # four: 1, 1.016, 2
+    (129, 256, 32, 32, 64, 3, 0, 1), (192, 256, 32, 32, 64, 3, 1, 1), (193, 256, 32, 32, 64, 3, 1, 2),  # 2.016, 3, 3.016
+    (250, 128, 7, 7, 128, 3, 1, 1), (168, 128, 7, 8, 128, 3, 1, 2),    # small maps: t = 6, 4.6
+    (1, 256, 1, 1, 1, 1, 1, 2), (1, 257, 32, 32, 64, 1, 1, 0), (200, 64, 32, 32, 64, 5, 1, 0)])
+def test_conv_word_rule_lines(N, C, H, W, D, k, packed, want):
+    """Both sides of every line of the rule for the kernel whose taps go straight to the matrix cores, on 256 compute units."""
+    assert B.lib().bnn_testing_conv_word(N, C, H, W, D, k, k, 1, 1, k // 2, k // 2, 0, packed, 256) == want
+
+
+def test_conv_word_offsets_fit_32_bits():
+    """64 columns span at most 63 / (OH OW) + 2 images; their bytes are a 32-bit offset in the kernel."""
+    f = lambda N, H, s: B.lib().bnn_testing_conv_word(N, 1, H, H, 64, 3, 3, s, s, 1, 1, 0, 1, 256)
+    assert f(70, 2100, 2100) > 0 and f(70, 2900, 2900) == 0  # one output pixel an image: 65 images
+    assert f(2, 16300, 5) > 0 and f(2, 16400, 5) == 0        # two images and a bit

@@ -779,6 +779,47 @@ def _conv2d_packed_all_output_kinds(case, cfg=None, lean=None):
         assert np.array_equal(got, oracle.pack_nhwc(pref))
 
 
+@pytest.mark.parametrize("case", [
+    (2, 64, 9, 11, 64, 3, 3, 1, 1, 1, 1),      # one word, whole
+    (3, 37, 14, 20, 70, 3, 3, 1, 1, 1, 1),     # one word, partial; a second row tile of six channels
+    (1, 5, 6, 6, 33, 3, 3, 2, 2, 1, 1),        # fewer columns than a wave
+    (2, 128, 10, 26, 130, 3, 3, 1, 1, 1, 1),   # two words, columns past one workgroup
+    (5, 100, 13, 12, 64, 3, 3, 2, 1, 0, 1),    # the second partial, strides and padding of their own
+    (3, 192, 16, 12, 65, 3, 3, 1, 1, 1, 1),    # three words: 512 columns a workgroup
+    (2, 129, 22, 25, 32, 3, 3, 1, 1, 1, 1),    # one channel in the third
+    (3, 256, 14, 14, 128, 3, 3, 1, 1, 1, 1),   # four words
+    (70, 200, 3, 3, 40, 3, 3, 1, 1, 1, 1),     # 64 columns cross many images
+    (4, 64, 9, 9, 96, 1, 1, 1, 1, 0, 0), (3, 130, 8, 10, 40, 1, 1, 2, 2, 0, 0), (2, 97, 7, 6, 64, 1, 1, 1, 1, 1, 1),
+    (3, 250, 12, 12, 129, 1, 1, 1, 2, 0, 0),   # 1 x 1 of every number of words; padding; strides
+    (1, 60, 1, 70, 64, 3, 3, 1, 1, 1, 1), (40, 256, 1, 1, 64, 3, 3, 1, 1, 1, 1)])
+def test_conv_word_kernel_all_output_kinds(case):
+    """The kernel whose taps go straight to the matrix cores, forced: maps in every store form, signs, pooled signs."""
+    print(f"conv word kernel case={case}", flush=True)
+    assert B.lib().bnn_testing_conv_word(*case, 0, 1, 256) > 0
+    _conv2d_packed_all_output_kinds(case, cfg=19)
+
+
+@pytest.mark.parametrize("N,C,H,W,D,k,out", [
+    (17, 64, 32, 32, 64, 3, "packed"), (24, 40, 32, 32, 64, 3, "i32"), (24, 128, 16, 32, 128, 3, "packed"),
+    (40, 128, 16, 33, 64, 3, "f32"), (52, 192, 32, 31, 64, 3, "packed"), (70, 256, 32, 31, 64, 3, "f32"),
+    (200, 256, 32, 32, 64, 3, "packed"), (1, 64, 5, 5, 8, 1, "packed")])
+def test_conv_word_rule(N, C, H, W, D, k, out):
+    """Layers of every number of words that the rule takes there (on 256 compute units), as an application calls them: the
+    batch repeats two images that the oracle knows."""
+    print(f"conv word rule N={N} C={C} {H}x{W} D={D} {out}", flush=True)
+    case = (2, C, H, W, D, k, k, 1, 1, k // 2, k // 2)
+    assert B.lib().bnn_testing_conv_word(N, *case[1:], 0, out == "packed", 256) == 2
+    d = inputs.conv_inputs(inputs.ConvShape(*case), seed=N)
+    xp = _u64dev(oracle.pack_nhwc(d["x"])).repeat((N + 1) // 2, 1, 1, 1)[:N].contiguous()
+    got = B.bnn_conv2d_packed(xp, B.bnn_pack_conv_weight(dev(d["w"])), C, D, k, k, (1, 1), (k // 2, k // 2),
+                              scale=dev(d["scale"]), bias=dev(d["bias"]), out=out)
+    ref = oracle.conv2d_pm1(d["x"], d["w"], (1, 1), (k // 2, k // 2))
+    yref = oracle.scale_bias(ref, d["scale"], d["bias"], "nchw")
+    want = {"i32": ref, "f32": yref, "packed": oracle.pack_nhwc(yref)}[out]
+    got = as_u64(got) if out == "packed" else host(got)
+    assert all(np.array_equal(got[n], want[n % 2]) for n in range(N))
+
+
 def _random_geometries(n, seed):
     rng = np.random.default_rng(seed)
     out = []
