@@ -90,6 +90,7 @@ _lib: Optional[ctypes.CDLL] = None
 
 
 FASTCALL_PATH = LIB_PATH.replace("libbnn", "_fastcall")
+TENSORCALL_PATH = os.path.join(HERE, "_tensorcall.so")
 
 
 def _fastcall():
@@ -129,6 +130,38 @@ def _c() -> _Calls:
     if _calls is None:
         _calls = _Calls(lib())
     return _calls
+
+
+class _Tensors:
+    """Calls from the tensors themselves (csrc/tensorcall.cpp): a status, or None where the call is not a plain one and the
+    function of this module has to look at it.  Where the extension has not been built every call is of that kind."""
+
+    FUNCTIONS = ("gemm", "epilogue", "encode", "conv2d", "conv2d_packed", "im2col", "f32_sign", "conv2d_f32", "maxpool", "fc")
+
+    def __init__(self, L: ctypes.CDLL, path: str):
+        module = None
+        if os.path.exists(path):
+            try:
+                spec = importlib.util.spec_from_file_location("paper_1911_04477_amd._tensorcall", path)
+                module = importlib.util.module_from_spec(spec)
+                spec.loader.exec_module(module)
+            except ImportError as e:  # of another torch
+                module = None
+                warnings.warn(f"{path} does not load ({e}): build it again; calls take 1 to 2 us longer", RuntimeWarning, stacklevel=4)
+        if module is not None:
+            module.bind(*[ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in module.names])
+        for f in self.FUNCTIONS:
+            setattr(self, f, getattr(module, f) if module is not None else lambda *args: None)
+
+
+_tensors: Optional[_Tensors] = None
+
+
+def _t() -> _Tensors:
+    global _tensors
+    if _tensors is None:
+        _tensors = _Tensors(lib(), TENSORCALL_PATH)
+    return _tensors
 
 
 class BnnError(RuntimeError):
@@ -189,6 +222,11 @@ def conv_out_dim(n: int, k: int, s: int, p: int) -> int:
 
 def bnn_encode(src: torch.Tensor, dst: Optional[torch.Tensor] = None) -> torch.Tensor:
     """src fp32 [rows, K] (row stride = src.stride(0)) -> int64-typed packed words [rows, Kw]."""
+    if dst is not None:
+        st = _t().encode(src, dst)
+        if st is not None:
+            _check(st, "bnn_encode")
+            return dst
     _dev(src, torch.float32, "src")
     assert src.dim() == 2 and src.stride(1) == 1
     rows, K = src.shape
@@ -218,6 +256,11 @@ def im2col_workspace_bytes(x_shape, kH, kW, stride, pad) -> int:
 
 def bnn_im2col_packed(x: torch.Tensor, kH: int, kW: int, stride=(1, 1), pad=(0, 0),
                       cols: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
+    if cols is not None and workspace is not None:
+        st = _t().im2col(x, kH, kW, stride, pad, cols, workspace)
+        if st is not None:
+            _check(st, "bnn_im2col_packed")
+            return cols
     _dev(x, torch.float32, "x")
     assert x.dim() == 4 and x.is_contiguous()
     N, C, H, W = x.shape
@@ -239,6 +282,11 @@ def bnn_xnor_gemm(A: torch.Tensor, B: torch.Tensor, K: int, C: Optional[torch.Te
                   cfg: Optional[int] = None) -> torch.Tensor:
     """A [M, >=Kw], B [N, >=Kw] packed (int64-typed) -> int32 [M, N].
     cfg (tests only): the same call through bnn_testing_xnor_gemm_epilogue on that tile configuration."""
+    if C is not None and cfg is None:
+        st = _t().gemm(A, B, K, C)
+        if st is not None:
+            _check(st, "bnn_xnor_gemm")
+            return C
     _dev(A, torch.int64, "A")
     _dev(B, torch.int64, "B")
     M, N = A.shape[0], B.shape[0]
@@ -350,6 +398,11 @@ def bnn_control_conv2d_f32(x: torch.Tensor, w: torch.Tensor, stride=(1, 1), pad=
 def bnn_xnor_gemm_epilogue(A: torch.Tensor, B: torch.Tensor, K: int, scale: torch.Tensor, bias: torch.Tensor,
                            axis: int, want_int: bool = False, out_y: Optional[torch.Tensor] = None,
                            cfg: Optional[int] = None) -> Tuple[Optional[torch.Tensor], torch.Tensor]:
+    if out_y is not None and not want_int and cfg is None:
+        st = _t().epilogue(A, B, K, scale, bias, axis, out_y)
+        if st is not None:
+            _check(st, "bnn_xnor_gemm_epilogue")
+            return None, out_y
     _dev(A, torch.int64, "A")
     _dev(B, torch.int64, "B")
     M, N = A.shape[0], B.shape[0]
@@ -381,6 +434,12 @@ def bnn_conv2d(x: torch.Tensor, w_packed: torch.Tensor, D: int, kH: int, kW: int
                out_f32: Optional[torch.Tensor] = None, cfg: Optional[int] = None, lean: Optional[int] = None):
     """Returns (out_i32 or None, out_f32 or None), both NCHW.
     cfg / lean (tests only): the same call through bnn_testing_conv2d."""
+    if (workspace is not None and (out_i32 is not None or not want_int) and (out_f32 is not None or scale is None)
+            and cfg is None and lean is None):
+        st = _t().conv2d(x, w_packed, D, kH, kW, stride, pad, out_i32, out_f32, scale, bias, workspace)
+        if st is not None:
+            _check(st, "bnn_conv2d")
+            return out_i32, out_f32
     _dev(x, torch.float32, "x")
     _dev(w_packed, torch.int64, "w_packed")
     assert x.dim() == 4 and x.is_contiguous() and w_packed.is_contiguous()
@@ -425,6 +484,12 @@ def bnn_conv2d_packed(xp: torch.Tensor, w_packed: torch.Tensor, C: int, D: int, 
                       cfg: Optional[int] = None, lean: Optional[int] = None):
     """xp: packed NHWC [N, H, W, Cw] (int64-typed).  out = "packed" | "i32" | "f32".
     cfg / lean (tests only): the same call through bnn_testing_conv2d_packed."""
+    if out_buf is not None and cfg is None and lean is None and out in ("packed", "i32", "f32"):
+        st = _t().conv2d_packed(xp, w_packed, C, D, kH, kW, stride, pad, pool, out_buf if out == "i32" else None,
+                                out_buf if out == "f32" else None, out_buf if out == "packed" else None, scale, bias)
+        if st is not None:
+            _check(st, "bnn_conv2d_packed")
+            return out_buf
     _dev(xp, torch.int64, "x_packed")
     _dev(w_packed, torch.int64, "w_packed")
     assert xp.dim() == 4 and xp.is_contiguous() and w_packed.is_contiguous()
@@ -513,6 +578,11 @@ def bnn_conv_chain(xp: torch.Tensor, C: int, layers: ctypes.Array, out: torch.Te
 
 def bnn_conv2d_f32_sign(x: torch.Tensor, w: torch.Tensor, scale: torch.Tensor, bias: torch.Tensor, stride=(1, 1),
                         pad=(0, 0), out: Optional[torch.Tensor] = None) -> torch.Tensor:
+    if out is not None:
+        st = _t().f32_sign(x, w, scale, bias, stride, pad, out)
+        if st is not None:
+            _check(st, "bnn_conv2d_f32_sign")
+            return out
     _dev(x, torch.float32, "x")
     _dev(w, torch.float32, "w")
     N, C, H, W = x.shape
@@ -536,6 +606,11 @@ def bnn_pack_fc_weight_nhwc(w: torch.Tensor, C: int, H: int, W: int) -> torch.Te
 
 def bnn_maxpool2x2(a: torch.Tensor, scale: Optional[torch.Tensor] = None, bias: Optional[torch.Tensor] = None,
                    want_int: bool = True, out_i32=None, out_f32=None):
+    if (out_i32 is not None or not want_int) and (out_f32 is not None or scale is None):
+        st = _t().maxpool(a, out_i32, out_f32, scale, bias)
+        if st is not None:
+            _check(st, "bnn_maxpool2x2")
+            return out_i32, out_f32
     _dev(a, torch.int32, "in")
     assert a.dim() == 4 and a.is_contiguous()
     N, D, H, W = a.shape
@@ -549,6 +624,11 @@ def bnn_maxpool2x2(a: torch.Tensor, scale: Optional[torch.Tensor] = None, bias: 
 
 
 def bnn_conv2d_f32(x: torch.Tensor, w: torch.Tensor, stride=(1, 1), pad=(0, 0), scale=None, bias=None, out=None):
+    if out is not None:
+        st = _t().conv2d_f32(x, w, scale, bias, stride, pad, out)
+        if st is not None:
+            _check(st, "bnn_conv2d_f32")
+            return out
     _dev(x, torch.float32, "x")
     _dev(w, torch.float32, "w")
     N, C, H, W = x.shape
@@ -563,6 +643,11 @@ def bnn_conv2d_f32(x: torch.Tensor, w: torch.Tensor, stride=(1, 1), pad=(0, 0), 
 
 def bnn_fc_f32(x: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor] = None, sign_input: bool = False,
                out=None):
+    if out is not None:
+        st = _t().fc(x, w, bias, int(sign_input), out)
+        if st is not None:
+            _check(st, "bnn_fc_f32")
+            return out
     _dev(x, torch.float32, "x")
     _dev(w, torch.float32, "w")
     M, K = x.shape

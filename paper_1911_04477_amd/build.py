@@ -14,6 +14,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbnn.so")
 FASTCALL = os.path.join(HERE, "_fastcall.so")
+TENSORCALL = os.path.join(HERE, "_tensorcall.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["api.hip", "encode.hip", "im2col.hip", "gemm.hip", "gemm_lowk.hip", "gemm_fewrows.hip", "gemm_fp4.hip", "gemm_fp4_split.hip", "conv.hip", "conv_first_sign.hip", "conv_chain.hip", "conv_pointwise.hip", "conv_word.hip", "glue.hip", "mfma.hip", "control.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -87,10 +88,34 @@ def build_fastcall(out: str = FASTCALL, flags: Sequence[str] = ("-O2",)) -> Opti
     return out
 
 
+def build_tensorcall(out: str = TENSORCALL) -> Optional[str]:
+    """The binding's calls from tensors, a CPython extension against torch's own headers.  None where it cannot be built: the
+    binding then converts tensors itself."""
+    if os.path.exists(out):
+        os.remove(out)  # not one of another source
+    import torch
+    home, include = os.path.dirname(torch.__file__), sysconfig.get_paths()["include"]
+    if not all(os.path.exists(f) for f in (os.path.join(include, "Python.h"), os.path.join(home, "include", "c10", "hip", "HIPStream.h"))):
+        print("calls from tensors not built: they need the headers of Python and of torch for ROCm")
+        return None
+    cxx = [shutil.which("g++")] if shutil.which("g++") else [HIPCC]
+    tmp, lib = out + ".tmp.%d" % os.getpid(), os.path.join(home, "lib")
+    subprocess.check_call([
+        *cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+        "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", include, "-I", os.path.join(ROOT, "include"),
+        "-isystem", os.path.join(home, "include"), "-isystem", os.path.join(home, "include", "torch", "csrc", "api", "include"),
+        "-isystem", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), os.path.join(CSRC, "tensorcall.cpp"), "-o", tmp,
+        "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath," + lib])
+    os.replace(tmp, out)
+    return out
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
+        tensors = ex.submit(build_tensorcall)
         objs = list(ex.map(_compile, SOURCES))
+        tensors.result()
     tmp = LIB + ".tmp.%d" % os.getpid()
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp])
     os.replace(tmp, LIB)

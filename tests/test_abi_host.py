@@ -466,6 +466,40 @@ def test_call_helper_build(monkeypatch, tmp_path):
     assert build.build_fastcall(str(out)) is None and not out.exists()
 
 
+def test_tensor_calls_build_and_absence(L, monkeypatch, tmp_path):
+    """Left out, an old one with it, where torch's headers or Python's are missing; without it, or with one of another torch, every
+    call is left to the binding's own code."""
+    from paper_1911_04477_amd import build
+    out = tmp_path / "_tensorcall.so"
+    out.write_text("an old one")
+    with monkeypatch.context() as m:
+        m.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+        assert build.build_tensorcall(str(out)) is None and not out.exists()
+    assert {f: getattr(B._Tensors(L, str(out)), f)(1, 2) for f in B._Tensors.FUNCTIONS} == dict.fromkeys(B._Tensors.FUNCTIONS)
+    out.write_text("not a library")
+    with pytest.warns(RuntimeWarning, match="does not load"):
+        assert B._Tensors(L, str(out)).gemm(1, 2, 3, 4) is None
+
+
+@pytest.mark.skipif(not os.path.exists(B.TENSORCALL_PATH), reason="not built")
+def test_tensor_calls_decline_what_is_not_plain(L):
+    """CPU tensors, other types, other counts of arguments, numbers of other types: None, and nothing is called."""
+    import numpy as np
+    import torch
+    t = B._t()
+    a, c, f = torch.zeros(2, 1, dtype=torch.int64), torch.zeros(2, 2, dtype=torch.int32), torch.zeros(2, 64)
+    x, w, xp = torch.zeros(1, 3, 4, 4), torch.zeros(2, 3, 3, 3), torch.zeros(1, 4, 4, 1, dtype=torch.int64)
+    for name, args in (("gemm", (a, a, 64, c)), ("gemm", (a, a, 64)), ("gemm", ()), ("gemm", (None, a, 64, c)), ("gemm", (a, a, 64.0, c)),
+                       ("gemm", (a, a, np.int64(64), c)), ("gemm", (a, a, 1 << 70, c)), ("epilogue", (a, a, 64, f, f, 2, f)), ("encode", (f, a)),
+                       ("conv2d", (x, a, 2, 3, 3, (1, 1), (1, 1), c, None, None, None, f)),
+                       ("conv2d_packed", (xp, a, 3, 2, 3, 3, [1, 1], (1, 1), 0, c, None, None, None, None)),
+                       ("im2col", (x, 3, 3, (1, 1), (1, 1), a, f)), ("f32_sign", (x, w, f, f, (1, 1), (1, 1), a)),
+                       ("conv2d_f32", (x, w, None, None, (1, 1), (1, 1), x)), ("maxpool", (c, c, None, None, None)), ("fc", (f, f, None, 0, f))):
+        assert getattr(t, name)(*args) is None, (name, args)
+    with pytest.raises(TypeError):
+        t.gemm(a, a, K=64, C=c)
+
+
 class _Gpu:
     """What the binding looks at of a GPU tensor."""
     is_cuda = True

@@ -1,6 +1,8 @@
 """GPU parity: every entry point of the C ABI against the CPU oracle, element by element,
 on the same seeded host-generated inputs.  Integer / packed outputs must be bit-exact;
 the fp32 epilogue must match within 1e-6 relative (it is in fact built to be bit-exact)."""
+import os
+
 import numpy as np
 import pytest
 import torch
@@ -660,6 +662,117 @@ def test_cfg4_stack_full_batch_every_layer_every_image(cfg4_b256):
     del acts
     out2 = host(net.forward(dev(d["x"])))
     assert np.array_equal(out, out2)
+
+
+# ---------------------------------------------------------------- calls from tensors
+class _OwnCode:
+    """The binding without csrc/tensorcall.cpp."""
+
+    def __enter__(self):
+        self.kept = B._t()
+        B._tensors = B._Tensors(B.lib(), "/nowhere")
+
+    def __exit__(self, *exc):
+        B._tensors = self.kept
+
+
+def _plain_and_odd_calls():
+    """name -> call(fresh outputs) -> outputs; every entry point with outputs given, plain and in forms of their own."""
+    g = torch.Generator(device=DEV).manual_seed(5)
+    r = lambda *s: torch.randn(*s, device=DEV, generator=g)
+    e = lambda *s, dt=torch.int32: torch.full(s, 7, dtype=dt, device=DEV)
+    i64, f32 = torch.int64, torch.float32
+    A, W = B.bnn_encode(r(5, 130)), B.bnn_encode(r(9, 130))
+    wide = torch.zeros(10, 8, dtype=i64, device=DEV)
+    wide[::2, :3] = A
+    sc, bi, sc9, bi9 = r(6), r(6), r(9), r(9)
+    x, xp, wp = r(2, 70, 6, 8), B.bnn_im2col_packed(r(2, 70, 6, 8), 1, 1).view(2, 6, 8, 2), B.bnn_pack_conv_weight(r(6, 70, 3, 3))
+    ws = e(1 << 16, dt=torch.uint8)
+    img, taps = r(2, 3, 7, 9), torch.nn.Parameter(r(6, 3, 3, 3))
+    acc = torch.randint(-50, 50, (2, 6, 4, 6), device=DEV, generator=g, dtype=torch.int32)
+    geo = dict(stride=(1, 1), pad=(1, 1))
+    return {
+        "gemm": lambda: B.bnn_xnor_gemm(A, W, 130, C=e(5, 9)),
+        "gemm rows apart": lambda: B.bnn_xnor_gemm(wide[::2], W, 130, C=e(5, 20)[:, :9]),
+        "gemm one row": lambda: B.bnn_xnor_gemm(A[:1], W[:1], 130, C=e(1, 1)),
+        "gemm nothing": lambda: B.bnn_xnor_gemm(A[:0], W, 130, C=e(0, 9)),
+        "gemm numpy K": lambda: B.bnn_xnor_gemm(A, W, np.int64(130), C=e(5, 9)),
+        "epilogue columns": lambda: B.bnn_xnor_gemm_epilogue(A, W, 130, sc9, bi9, B.CH_COL, out_y=e(5, 9, dt=f32)),
+        "epilogue rows": lambda: B.bnn_xnor_gemm_epilogue(A, W, 130, sc, bi, B.CH_ROW, out_y=e(5, 9, dt=f32)),
+        "encode": lambda: B.bnn_encode(x.view(12, 560), e(12, 9, dt=i64)),
+        "encode strided": lambda: B.bnn_encode(x.view(12, 560)[::2, :65], e(6, 4, dt=i64)[:, :2]),
+        "encode one row": lambda: B.bnn_encode(x.view(1, -1), e(1, 105, dt=i64)),
+        "conv2d": lambda: B.bnn_conv2d(x, wp, 6, 3, 3, (1, 1), (1, 1), workspace=ws, out_i32=e(2, 6, 6, 8)),
+        "conv2d both": lambda: B.bnn_conv2d(x, wp, 6, 3, 3, (2, 1), (0, 1), sc, bi, workspace=ws, out_i32=e(2, 6, 2, 8), out_f32=e(2, 6, 2, 8, dt=f32)),
+        "conv2d lists": lambda: B.bnn_conv2d(x, wp, 6, 3, 3, [1, 1], [1, 1], sc, bi, want_int=False, workspace=ws, out_f32=e(2, 6, 6, 8, dt=f32)),
+        "packed": lambda: B.bnn_conv2d_packed(xp, wp, 70, 6, 3, 3, **geo, scale=sc, bias=bi, out_buf=e(2, 6, 8, 1, dt=i64)),
+        "packed pool": lambda: B.bnn_conv2d_packed(xp, wp, 70, 6, 3, 3, **geo, pool=2, scale=sc, bias=bi, out_buf=e(2, 3, 4, 1, dt=i64)),
+        "packed i32": lambda: B.bnn_conv2d_packed(xp, wp, 70, 6, 3, 3, **geo, out="i32", out_buf=e(2, 6, 6, 8)),
+        "packed f32": lambda: B.bnn_conv2d_packed(xp, wp, 70, 6, 3, 3, **geo, out="f32", scale=sc, bias=bi, out_buf=e(2, 6, 6, 8, dt=f32)),
+        "im2col": lambda: B.bnn_im2col_packed(x, 3, 3, (2, 1), (1, 0), cols=e(2 * 3 * 6, 18, dt=i64), workspace=ws),
+        "f32 sign": lambda: B.bnn_conv2d_f32_sign(img, taps, sc, bi, (1, 1), (1, 1), out=e(2, 7, 9, 1, dt=i64)),
+        "f32": lambda: B.bnn_conv2d_f32(img, taps, (1, 1), (1, 1), sc, bi, out=e(2, 6, 7, 9, dt=f32)),
+        "f32 no affine map": lambda: B.bnn_conv2d_f32(img, taps, (2, 2), (0, 0), out=e(2, 6, 3, 4, dt=f32)),
+        "pool": lambda: B.bnn_maxpool2x2(acc, sc, bi, out_i32=e(2, 6, 2, 3), out_f32=e(2, 6, 2, 3, dt=f32)),
+        "pool i32": lambda: B.bnn_maxpool2x2(acc, out_i32=e(2, 6, 2, 3)),
+        "fc": lambda: B.bnn_fc_f32(x.view(4, -1), r(3, 1680), r(3), sign_input=True, out=e(4, 3, dt=f32)),
+        # refused, by the binding or by the library
+        "no K": lambda: B.bnn_xnor_gemm(A, W, 0, C=e(5, 9)), "K beyond the rows": lambda: B.bnn_xnor_gemm(A, W, 300, C=e(5, 9)),
+        "CPU": lambda: B.bnn_xnor_gemm(A.cpu(), W, 130, C=e(5, 9)), "type": lambda: B.bnn_encode(x.view(12, 560).half(), e(12, 9, dt=i64)),
+        "shape of y": lambda: B.bnn_xnor_gemm_epilogue(A, W, 130, sc9, bi9, B.CH_COL, out_y=e(9, 5, dt=f32)),
+        "columns apart": lambda: B.bnn_encode(x.view(12, 560)[:, ::2], e(12, 5, dt=i64)),
+        "not contiguous": lambda: B.bnn_conv2d(x.transpose(2, 3), wp, 6, 3, 3, (1, 1), (1, 1), workspace=ws, out_i32=e(2, 6, 8, 6)),
+        "channels": lambda: B.bnn_conv2d_packed(xp, wp, 200, 6, 3, 3, **geo, out="i32", out_buf=e(2, 6, 6, 8)),
+        "workspace": lambda: B.bnn_conv2d(x, wp, 6, 3, 3, (1, 1), (1, 1), workspace=ws[:16], out_i32=e(2, 6, 6, 8)),
+        "cols": lambda: B.bnn_im2col_packed(x, 3, 3, (1, 1), (1, 1), cols=e(3, 18, dt=i64), workspace=ws),
+        "no scale": lambda: B.bnn_conv2d_packed(xp, wp, 70, 6, 3, 3, **geo, out_buf=e(2, 6, 8, 1, dt=i64)),
+        "stride": lambda: B.bnn_conv2d_packed(xp, wp, 70, 6, 3, 3, stride=(0, 1), out="i32", out_buf=e(2, 6, 6, 8)),
+        "odd map": lambda: B.bnn_maxpool2x2(acc[:, :, :3].contiguous(), out_i32=e(2, 6, 1, 3)),
+        "outputs of another kind": lambda: B.bnn_conv2d_packed(xp, wp, 70, 6, 3, 3, out="u8", out_buf=e(1)),
+    }
+
+
+def _outcome(call):
+    try:
+        out = call()
+    except Exception as ex:
+        return type(ex), str(ex)
+    out = out if isinstance(out, tuple) else (out,)
+    torch.cuda.synchronize()
+    return [None if t is None else t.clone() for t in out]
+
+
+def test_calls_from_tensors_equal_the_bindings_own():
+    """The same values, the same exceptions with the same text, with csrc/tensorcall.cpp and without."""
+    print("calls from tensors", flush=True)
+    assert os.path.exists(B.TENSORCALL_PATH)
+    fast = {k: _outcome(c) for k, c in _plain_and_odd_calls().items()}
+    with _OwnCode():
+        own = {k: _outcome(c) for k, c in _plain_and_odd_calls().items()}
+    for k in own:
+        a, b = fast[k], own[k]
+        if isinstance(a, tuple) or isinstance(b, tuple):
+            assert a == b, k
+        else:
+            assert len(a) == len(b) and all((s is None and t is None) or torch.equal(s, t) for s, t in zip(a, b)), k
+    refused = [k for k, v in own.items() if isinstance(v, tuple)]
+    assert refused == list(own)[list(own).index("no K"):]
+
+
+def test_calls_from_tensors_follow_the_current_stream():
+    """A call is ordered behind what its stream holds: on a side stream after a long product that makes its input."""
+    print("calls from tensors: stream", flush=True)
+    side = torch.cuda.Stream()
+    big = torch.randn(4096, 4096, device=DEV)
+    dst = torch.empty(4096, 64, dtype=torch.int64, device=DEV)
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        y = big
+        for _ in range(8):
+            y = torch.tanh(y @ big)
+        B.bnn_encode(y, dst)
+    torch.cuda.current_stream().wait_stream(side)
+    assert torch.equal(dst, B.bnn_encode(y))
 
 
 # ---------------------------------------------------------------- timing hook
