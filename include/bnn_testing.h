@@ -32,6 +32,7 @@ extern "C" {
  *       30 .. 37  the same with three blocks of rows per wave
  *   18  the kernel for at most 16 such rows by very many columns (two or four words, columns and strides multiples of 4)
  *   19  convolutions of at most 256 channels, 1 x 1 or 3 x 3, whose taps go straight from memory to the matrix cores
+ *   40, 41  bnn_conv2d in one launch, the tile encoding the input rows that it reads, the reduction split 4 / 8 ways
  * A value that a call cannot use (the packed epilogue needs a 32- or 64-row tile with two or
  * four column groups, or one of 21 to 28; 10 to 18 and 30 to 37 exist for an explicit B with int32 / fp32 output only;
  * 21 to 24 need K below 2^24, 29 what it says)
@@ -129,6 +130,13 @@ BNN_API bnn_status bnn_valu_peak_probe(int32_t *sink, int blocks, int iters, int
  * for achievable HBM bandwidth and for scaling hardware byte counters.
  */
 BNN_API bnn_status bnn_copy_probe(const void *src, void *dst, size_t n_bytes, void *stream);
+
+/* Convolutions from the fp32 image in one launch, K split 4 or 8 ways (shapes 0, 1): the one that bnn_conv2d takes on a device
+ * of `units` compute units, or for shape >= 0 that one where it can be taken; -1 where it is not, or for invalid arguments.
+ * rows receives the first and the last input row, counted over all images, of the tile that begins at output pixel `pixel`, and
+ * the most rows that the launch has room for. */
+BNN_API int bnn_testing_conv_image(int N, int C, int H, int W, int D, int kH, int kW, int sH, int sW, int pH, int pW,
+                                   int units, int shape, int pixel, int64_t *rows);
 
 #ifdef __cplusplus
 }

@@ -182,6 +182,12 @@ bnn_status launch_gemm_fp4(GemmParams &p, int bmode, int emode, hipStream_t s, i
 bool fp4_split_applicable(const GemmParams &p, int bmode);  // whether its rule on sizes takes the problem
 bnn_status launch_gemm_fp4_split(GemmParams &p, int bmode, int emode, hipStream_t s, int shape);
 
+// Convolution from the fp32 image in one launch, by the split kernel (gemm_fp4_split.hip): K split 4 or 8 ways (0, 1;
+// asked for, or -1: by its rule), -1 where it does not apply.
+int conv_image_shape(const GemmParams &p, int shape);
+void conv_image_rows(const GemmParams &p, int pixel, int64_t *rows);  // as bnn_testing_conv_image has it
+bnn_status launch_conv_image(const GemmParams &p, const float *x, uint64_t *img, int shape, hipStream_t s);
+
 // How the matrix-core kernels store int32 / fp32 maps (gemm.hip): past the caches; whether columns and strides are
 // multiples of 4, so that a lane's columns can leave together.
 bool nontemporal_maps(const GemmParams &p, int bmode);

@@ -314,6 +314,12 @@ static bnn_status conv2d_impl(const float *x, const uint64_t *w_packed, int N, i
     return conv_from_packed(img, w_packed, N, C, OH, OW, D, 1, 1, 1, 1, 0, 0, 0, out_i32, out_f32, nullptr, scale,
                             bias, s, tune);
   }
+  if (tune.cfg < 0 ? tune.lean != 0 : tune.cfg == 40 || tune.cfg == 41) {
+    GemmParams p = conv_gemm(nullptr, w_packed, N, C, H, W, D, kH, kW, sH, sW, pH, pW, 0, out_i32, out_f32, nullptr, scale, bias);
+    p.n_cu = device_cu_count();
+    const int shape = conv_image_shape(p, tune.cfg < 0 ? -1 : tune.cfg - 40);
+    if (shape >= 0) return launch_conv_image(p, x, img, shape, s);
+  }
   st = launch_encode_nchw(x, N, C, H, W, H, W, 1, 1, img, s);
   if (st != BNN_OK) return st;
   return conv_from_packed(img, w_packed, N, C, H, W, D, kH, kW, sH, sW, pH, pW, 0, out_i32, out_f32, nullptr, scale,
@@ -464,6 +470,20 @@ extern "C" int bnn_testing_conv_word(int N, int C, int H, int W, int D, int kH, 
                            nullptr);
   p.n_cu = units;
   return !conv_word_applicable(p, 1) ? 0 : conv_word_faster(p, packed) ? 2 : 1;
+}
+
+// Declared in bnn_testing.h.
+extern "C" int bnn_testing_conv_image(int N, int C, int H, int W, int D, int kH, int kW, int sH, int sW, int pH, int pW,
+                                      int units, int shape, int pixel, int64_t *rows) {
+  if (check_conv_geometry(N, C, H, W, kH, kW, sH, sW, pH, pW) != BNN_OK || N == 0 || D <= 0 || units <= 0 || !rows || shape > 1 ||
+      conv_limits(N, C, H, W, D, kH, kW, sH, sW, pH, pW) != BNN_OK)
+    return -1;
+  GemmParams p = conv_gemm(nullptr, nullptr, N, C, H, W, D, kH, kW, sH, sW, pH, pW, 0, nullptr, nullptr, nullptr, nullptr, nullptr);
+  p.n_cu = units;
+  if (pixel < 0 || pixel >= p.N) return -1;
+  const int r = conv_image_shape(p, shape);
+  if (r >= 0) conv_image_rows(p, pixel, rows);
+  return r;
 }
 
 extern "C" bnn_status bnn_conv2d_f32_sign(const float *x, const float *w, int N, int C, int H, int W, int D, int kH,

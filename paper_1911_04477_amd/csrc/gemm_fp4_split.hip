@@ -10,6 +10,13 @@
 // (rows 8q + 4 * (l / 32) + 0..3 of every block).
 //
 // Bound: latency (launch, one memory round trip for the operands, one exchange through LDS).
+//
+// A convolution from an fp32 image that small (SG_IMAGE) is one launch: the tile encodes the input rows that it reads into LDS
+// and takes its columns from there, and the first row of tiles writes the packed image out.  In a launch of its own the encode is
+// 2.3 us and a gap of about as much, for 0.3 us of loads.  One 256 x 16 x 16 image to 256 channels, 3 x 3: 7.3 -> 5.4 us in a
+// graph; the addresses of the 32 planes of a granule as a running sum, not as products: 5.7 -> 5.4.
+#include <algorithm>
+#include <numeric>
 #include <type_traits>
 
 #include "common.h"
@@ -17,12 +24,51 @@
 
 namespace bnn {
 
-enum : int { SG_EXPL16 = 0, SG_EXPL8 = 1, SG_CONV = 2 };
+enum : int { SG_EXPL16 = 0, SG_EXPL8 = 1, SG_CONV = 2, SG_IMAGE = 3 };
 
-template <int WT, int KS, int GM, int EMODE>
-__global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmParams p) {
+// SG_IMAGE: the fp32 image of a convolution, encoded by the tile that reads it.
+struct ImageParams : GemmParams {
+  const float *x;   // [Nimg, C, H, W]
+  uint64_t *img;    // its packed pixels leave there: bnn_conv2d's workspace receives them
+  FastDiv divHW;
+  uint32_t HW;
+};
+
+// fdiv_sel, for the host too.
+__host__ __device__ inline uint32_t image_div(uint32_t n, const FastDiv &f) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return fdiv_sel(n, f);
+#else
+  return n / f.d;
+#endif
+}
+
+// Input rows, of the rows of all images one after the other, that the output pixels n0 .. n0 + cols - 1 read (taps outside an
+// image moved to its first or last row), and the rows up to where the next tile's begin, so that the tiles of an image read all
+// of it.
+__host__ __device__ inline void image_rows(const ConvGeom &g, uint32_t n0, uint32_t cols, uint32_t total, int &r0, int &r1) {
+  const uint32_t end = n0 + cols;
+  const uint32_t t0 = image_div(n0, g.divOW), t1 = image_div((end < total ? end : total) - 1u, g.divOW);
+  const int i0 = (int)image_div(t0, g.divOH), i1 = (int)image_div(t1, g.divOH);
+  const int a = ((int)t0 - i0 * g.OH) * g.sH - g.pH, b = ((int)t1 - i1 * g.OH) * g.sH - g.pH + g.kH - 1;
+  r0 = i0 * g.H + (a < 0 ? 0 : a < g.H ? a : g.H - 1);
+  r1 = i1 * g.H + (b < 0 ? 0 : b < g.H ? b : g.H - 1);
+  if (end >= total) {
+    r1 = g.Nimg * g.H - 1;
+  } else {
+    const uint32_t t2 = image_div(end, g.divOW);
+    const int i2 = (int)image_div(t2, g.divOH);
+    const int c = ((int)t2 - i2 * g.OH) * g.sH - g.pH;
+    const int next = i2 * g.H + (c < 0 ? 0 : c < g.H ? c : g.H - 1) - 1;
+    r1 = r1 > next ? r1 : next;
+  }
+}
+
+template <int WT, int KS, int GM, int EMODE, class Params = GemmParams>
+__global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(Params p) {
   constexpr int B32 = 32 * WT;  // rows and columns of the tile
-  constexpr bool CONV = GM == SG_CONV, SIGN = EMODE != 0;
+  constexpr bool IMAGE = GM == SG_IMAGE, CONV = GM == SG_CONV || IMAGE, SIGN = EMODE != 0;
+  extern __shared__ __attribute__((aligned(16))) uint32_t sImg[];  // IMAGE: [pixel][2 * Cw]
   __shared__ __attribute__((aligned(16))) int4 sPart[KS * WT * WT * 4 * 64];
   __shared__ __attribute__((aligned(16))) uint8_t sO[SIGN ? B32 * WT * 4 : 16];  // sign bytes [column][row group of 8]
   const int tid = threadIdx.x;
@@ -34,7 +80,9 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
 
   // ---- this lane's rows and columns: column block j, lane l = tile column WT * l + j ---------------------
   const char *arow[WT], *brow[WT];
-  int bih[WT], biw[WT];
+  int bih[WT], biw[WT], bpx[WT];
+  int r0 = 0, r1 = 0;
+  if constexpr (IMAGE) image_rows(g, (uint32_t)n0, (uint32_t)B32, (uint32_t)p.N, r0, r1);  // uniform
 #pragma unroll
   for (int i = 0; i < WT; ++i)
     arow[i] = reinterpret_cast<const char *>(p.A) + (size_t)min(m0 + 32 * i + l32, p.M - 1) * (size_t)p.lda32 * 4u;
@@ -44,7 +92,8 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
     if constexpr (CONV) {
       uint32_t img, oh, ow;
       column_pixel(g, (uint32_t)n, g.pool != 0, img, oh, ow);
-      brow[j] = reinterpret_cast<const char *>(g.act + (size_t)img * (size_t)g.H * (size_t)g.W * (size_t)g.Cw);
+      if constexpr (IMAGE) bpx[j] = ((int)img * g.H - r0) * g.W;  // of the region
+      else brow[j] = reinterpret_cast<const char *>(g.act + (size_t)img * (size_t)g.H * (size_t)g.W * (size_t)g.Cw);
       bih[j] = (int)oh * g.sH - g.pH;
       biw[j] = (int)ow * g.sW - g.pW;
     } else {
@@ -70,7 +119,11 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
   const bool a16 = GM == SG_EXPL16 || (CONV && p.b_vec16);
   const bool cw_even = CONV && (g.Cw & 1) == 0;
   const uint64_t part = (g.C & 63) ? (1ull << (g.C & 63)) - 1ull : ~0ull;  // real channels of a tap's last word
-  auto load_chunk = [&](int c, u32x4 (&a)[WT], u32x4 (&b)[WT]) {
+  // IMAGE: a tap's pixel in LDS, of taps outside the image the nearest one inside (not used)
+  auto tap_pixel = [&](int j, int ih, int iw) {
+    return bpx[j] + min(max(ih, 0), g.H - 1) * g.W + min(max(iw, 0), g.W - 1);
+  };
+  auto load_rows = [&](int c, u32x4 (&a)[WT]) {
     const int w = 4 * c + 2 * half;
     const uint32_t wo = (uint32_t)max(min(w, p.Kw64 - 2), 0) * 8u;
     if (a16) {
@@ -80,11 +133,15 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
     } else {
       load_pieces_any<WT>(a, p.Kw64 > 1, [&](int i) { return arow[i] + wo; });
     }
+  };
+  auto load_columns = [&](int c, u32x4 (&b)[WT]) {
+    const int w = 4 * c + 2 * half;
     if constexpr (GM == SG_EXPL16) {
       const uint32_t o = (uint32_t)min(w, p.Kw64 - 2) * 8u;
 #pragma unroll
       for (int j = 0; j < WT; ++j) b[j] = *reinterpret_cast<const u32x4 *>(brow[j] + o);
     } else if constexpr (GM == SG_EXPL8) {
+      const uint32_t wo = (uint32_t)max(min(w, p.Kw64 - 2), 0) * 8u;
       load_pieces_any<WT>(b, p.Kw64 > 1, [&](int j) { return brow[j] + wo; });
     } else if (cw_even) {  // both words belong to one tap
       const uint32_t ww = (uint32_t)min(w, p.Kw64 - 2);
@@ -95,7 +152,11 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
       for (int j = 0; j < WT; ++j) {
         const int ih = bih[j] + (int)kh, iw = biw[j] + (int)kw;
         u32x4 v = {0xffffffffu, 0xffffffffu, (uint32_t)pad, (uint32_t)(pad >> 32)};
-        if (ih >= 0 && ih < g.H && iw >= 0 && iw < g.W)
+        const bool inside = ih >= 0 && ih < g.H && iw >= 0 && iw < g.W;
+        if constexpr (IMAGE) {
+          const u32x4 t = *reinterpret_cast<const u32x4 *>(sImg + 2 * (tap_pixel(j, ih, iw) * g.Cw + (int)cw));
+          v = inside ? t : v;
+        } else if (inside)
           v = *reinterpret_cast<const u32x4 *>(brow[j] + (((size_t)ih * (size_t)g.W + (size_t)iw) * (size_t)g.Cw + cw) * 8u);
         b[j] = v;
       }
@@ -110,13 +171,21 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
         for (int j = 0; j < WT; ++j) {
           const int ih = bih[j] + (int)kh, iw = biw[j] + (int)kw;
           u32x2 v = {(uint32_t)pad, (uint32_t)(pad >> 32)};
-          if (ih >= 0 && ih < g.H && iw >= 0 && iw < g.W)
+          const bool inside = ih >= 0 && ih < g.H && iw >= 0 && iw < g.W;
+          if constexpr (IMAGE) {
+            const u32x2 t = *reinterpret_cast<const u32x2 *>(sImg + 2 * (tap_pixel(j, ih, iw) * g.Cw + (int)cw));
+            v = inside ? t : v;
+          } else if (inside)
             v = *reinterpret_cast<const u32x2 *>(brow[j] + (((size_t)ih * (size_t)g.W + (size_t)iw) * (size_t)g.Cw + cw) * 8u);
           if (h == 0) b[j].lo = v;
           else b[j].hi = v;
         }
       }
     }
+  };
+  auto load_chunk = [&](int c, u32x4 (&a)[WT], u32x4 (&b)[WT]) {
+    load_rows(c, a);
+    load_columns(c, b);
   };
   auto mask_chunk = [&](int c, u32x4 (&a)[WT], u32x4 (&b)[WT]) {  // bits past the end of the row become 0 in both operands
     u32x4 m;
@@ -182,6 +251,9 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
 #pragma unroll
     for (int u = 0; u < 2; ++u)
       if (cb + u < ce) load_chunk(cb + u, ab[u], bb[u]);
+  } else if constexpr (IMAGE) {
+    if (cb < ce) load_rows(cb, a0);
+    if (cb + 1 < ce) load_rows(cb + 1, a1);
   } else {
     if (cb < ce) load_chunk(cb, a0, b0);
     if (cb + 1 < ce) load_chunk(cb + 1, a1, b1);
@@ -199,6 +271,49 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
       sc[i][e] = on ? p.scale[m] : 0.0f;  // rows past M: sign bit 0
       bi[i][e] = on ? p.bias[m] : -1.0f;
     }
+  if constexpr (IMAGE) {
+    // ---- the region's pixels -> sImg: a wave 64 pixels x 32 channels at a time -------------------------------
+    const int npx = (r1 - r0 + 1) * g.W, np = (npx + 63) >> 6, dw = 2 * g.Cw;
+    const uint32_t px0 = (uint32_t)r0 * (uint32_t)g.W, i0 = fdiv_sel(px0, p.divHW);
+    const float *const base = p.x + (size_t)i0 * (size_t)g.C * (size_t)p.HW;  // the host: 32 bits reach the region's images
+    int gr = 0, chunk = wave;  // granule of 32 channels, chunk of 64 pixels
+    for (;; chunk += KS) {
+      while (chunk >= np && gr < dw) {
+        chunk -= np;
+        ++gr;
+      }
+      if (gr >= dw) break;
+      const int px = 64 * chunk + lane;
+      const uint32_t q = px0 + (uint32_t)min(px, npx - 1), qi = fdiv_sel(q, p.divHW);
+      const uint32_t off = ((qi - i0) * (uint32_t)g.C - qi) * p.HW + q;
+      const int left = g.C - 32 * gr;
+      const float *plane = base + (size_t)(32 * gr) * p.HW;
+      uint32_t bits = 0u;
+      auto take = [&](auto count, auto whole) {
+        constexpr int N = decltype(count)::value;
+        float v[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+          v[k] = plane[off];
+          if (decltype(whole)::value || k < left - 1) plane += p.HW;  // channels past C: the last one once more, masked
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) bits |= (uint32_t)sign_bit(v[k]) << k;
+      };
+      if (left >= 32) take(std::integral_constant<int, 32>(), std::true_type());
+      else if (left > 8) take(std::integral_constant<int, 32>(), std::false_type());
+      else if (left > 0) take(std::integral_constant<int, 8>(), std::false_type());
+      if (left < 32) bits &= left > 0 ? (1u << left) - 1u : 0u;
+      if (px < npx) sImg[px * dw + gr] = bits;
+    }
+    __syncthreads();
+    if (mi == 0) {
+      uint64_t *const o = p.img + (size_t)px0 * (size_t)g.Cw;
+      for (int k = tid; k < npx * g.Cw; k += 64 * KS) o[k] = reinterpret_cast<const uint64_t *>(sImg)[k];
+    }
+    if (cb < ce) load_columns(cb, b0);
+    if (cb + 1 < ce) load_columns(cb + 1, b1);
+  }
   // Partial sums -> LDS [wave][block][quad][lane].  64 x 64 tiles of maps leave them as the accumulators hold them while the padded row
   // has at most 2^24 values: sums are exact then (64 conversions a wave less).  Else as integers, and a wave whose range
   // is longer than FLUSH chunks adds up its own slots.
@@ -404,8 +519,8 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(GemmPar
   }
 }
 
-template <int WT, int KS>
-static bnn_status launch_split(GemmParams &p, int bmode, int emode, hipStream_t s) {
+template <int WT>
+static bnn_status split_tiles(GemmParams &p) {
   p.tilesM = (p.M + 32 * WT - 1) / (32 * WT);
   const int64_t tn = ((int64_t)p.N + 32 * WT - 1) / (32 * WT);
   const int64_t blocks = p.tilesM * tn;
@@ -414,7 +529,14 @@ static bnn_status launch_split(GemmParams &p, int bmode, int emode, hipStream_t 
   p.divTilesM = FastDiv((uint32_t)p.tilesM);
   p.pairs = p.N % 2 == 0 && (!p.C || p.ldc % 2 == 0) && (!p.Y || p.ldy % 2 == 0) &&
             (p.img_stride == 0 || (p.OHW % 2 == 0 && p.img_stride % 2 == 0));
-  const dim3 grid((unsigned)blocks), block(64 * KS);
+  return BNN_OK;
+}
+
+template <int WT, int KS>
+static bnn_status launch_split(GemmParams &p, int bmode, int emode, hipStream_t s) {
+  const bnn_status st = split_tiles<WT>(p);
+  if (st != BNN_OK) return st;
+  const dim3 grid((unsigned)p.tilesM * (unsigned)p.tilesN), block(64 * KS);
   ProfScope ps(KID_XNOR_GEMM_FP4_SPLIT, s);
   if (bmode == 0) {
     const bool v16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0 && p.ldb % 2 == 0;
@@ -495,6 +617,87 @@ bnn_status launch_gemm_fp4_split(GemmParams &p, int bmode, int emode, hipStream_
     case 3: return launch_split<2, 8>(p, bmode, emode, s);
     default: return BNN_ERR_UNSUPPORTED;
   }
+}
+
+// ---- convolution from the fp32 image in one launch ---------------------------------------------------------
+// Most input rows of a tile of 32 output pixels, which begins at a multiple of 32.  In one image its ends are as far apart as
+// its first and last output row by the stride and a window, and moving them into the image brings them no further apart; an
+// image's end between them counts the whole image, less as much as the last one's end lies above the first one's begin there,
+// but for what moving them into the image takes from that.  Linear between the numbers of images a tile may touch: the largest
+// is at an end.
+static int64_t image_rows_most(const ConvGeom &g) {
+  const int64_t OW = g.OW, OH = g.OH, H = g.H, start = OW - std::gcd((int64_t)32, OW);  // last column that a tile may begin in
+  auto most = [&](int64_t pixels, int64_t window) {
+    const int64_t d = std::min<int64_t>((start + pixels - 1) / OW, (int64_t)g.Nimg * OH - 1);  // output rows apart
+    const int64_t moved = std::max<int64_t>(0, g.pH - (window - 1)) + std::max<int64_t>(0, (OH - 1) * g.sH - g.pH - (H - 1));
+    int64_t rows = 0;
+    for (const int64_t i : {d / OH, (d + OH - 1) / OH}) {
+      const int64_t apart = (d - i * OH) * g.sH + window - 1;
+      rows = std::max(rows, i * H + (apart < 0 ? std::min<int64_t>(0, apart + moved) : apart) + 1);
+    }
+    return rows;
+  };
+  // to where the next tile's begin; the last tile's: to the image's end
+  const int64_t rows = std::max(most(32, g.kH), most(33, 1)) + g.sH - 1;
+  return std::min<int64_t>(rows, (int64_t)g.Nimg * H);
+}
+
+bool encode_nchw_supported(int N, int C, int H, int W, int OHp, int OWp);
+
+static int64_t image_pixels(const GemmParams &p) { return image_rows_most(p.g) * p.g.W; }
+
+// By t, tiles of 32 x 32 outputs per compute unit, and b, the fp32 values in KB that a tile encodes: a launch and the gap before it
+// are gone (about 2.5 us in a graph, 4 in a stream), and every row of tiles encodes its columns' pixels again, on its own, at
+// about 50 KB a microsecond.  In graphs, two launches against one:
+//   t up to 1, 8 ways: b 32 (128 x 16 x 16 to 256, 3 x 3) 6.4, 4.6 us; 65 (256 x 16 x 16 to 256) 7.3, 5.4; 131 (512 x 8 x 8 to 512) 9.5,
+//     7.2; 136 (3 x 256 x 13 x 19 to 35, 5 x 5) 10.3, 8.4; 123 (3 x 128 x 6 x 40 to 256, 5 x 5, t = 0.7) 7.4, 6.6; but 172 (128 x 39 x
+//     48 to 256, 5 x 5 by 2) 7.3, 7.45; 287 (5 x 256 x 7 x 40 to 64, 5 x 5) 10.1, 11.9;
+//   t up to 2, 4 ways: b 12 (28 x 64 x 8 x 6 to 256) 6.9, 5.5; 32 (8 x 128 x 16 x 16 to 256) 7.4, 5.8; 65 (8 x 256 x 16 x 16 to 256) 8.6, 7.3; but
+//     123 (8 x 99 x 25 x 52 to 64, 5 x 5) 9.3, 13.8; 184 (2 x 256 x 12 x 45 to 256, t = 1.06) 8.3, 10.5;
+//   t up to 3, the same up to 24: 21 (57 x 64 x 6 x 14 to 256, t = 2.7) 7.7, 6.6; but 54 (34 x 64 x 62 x 18 to 64 by 2, t = 2.3) 9.3, 9.3;
+//   beyond, two launches: t = 3.5, b 43 8.8, 9.8; t = 4, 49 8.3, 9.5; t = 16, 65 15.5, 30.7.
+// shape >= 0: that one where the kernel can take the problem.
+int conv_image_shape(const GemmParams &p, int shape) {
+  const ConvGeom &g = p.g;
+  if (!encode_nchw_supported(g.Nimg, g.C, g.H, g.W, g.H, g.W)) return -1;  // what the encode refuses stays refused
+  const int64_t px = image_pixels(p), hw = (int64_t)g.H * g.W;
+  // LDS; 32-bit offsets over the images of a region
+  if (px * g.Cw * 8 > 24576 || (px / hw + 2) * hw * g.C >= (1LL << 30)) return -1;
+  if (shape >= 0) return shape;
+  const int64_t t = (((int64_t)p.M + 31) / 32) * (((int64_t)p.N + 31) / 32), bytes = 4 * px * g.C;
+  const int64_t cu = p.n_cu, kb = 1024;
+  if (t <= cu) return bytes <= 160 * kb ? 1 : -1;
+  return (t <= 2 * cu && bytes <= 80 * kb) || (t <= 3 * cu && bytes <= 24 * kb) ? 0 : -1;
+}
+
+void conv_image_rows(const GemmParams &p, int pixel, int64_t *rows) {
+  int r0, r1;
+  image_rows(p.g, (uint32_t)pixel, 32u, (uint32_t)p.N, r0, r1);
+  rows[0] = r0;
+  rows[1] = r1;
+  rows[2] = image_rows_most(p.g);
+}
+
+template <int KS>
+static bnn_status launch_image(ImageParams &p, hipStream_t s) {
+  const bnn_status st = split_tiles<1>(p);
+  if (st != BNN_OK) return st;
+  p.b_vec16 = p.Kw64 % 2 == 0 && p.lda32 % 4 == 0;
+  const dim3 grid((unsigned)p.tilesM * (unsigned)p.tilesN), block(64 * KS);
+  ProfScope ps(KID_XNOR_GEMM_FP4_SPLIT, s);
+  hipLaunchKernelGGL((xnor_gemm_fp4_split_kernel<1, KS, SG_IMAGE, 0, ImageParams>), grid, block,
+                     (size_t)(image_pixels(p) * p.g.Cw * 8), s, p);
+  return launch_status();
+}
+
+bnn_status launch_conv_image(const GemmParams &p, const float *x, uint64_t *img, int shape, hipStream_t s) {
+  ImageParams q;
+  static_cast<GemmParams &>(q) = p;
+  q.x = x;
+  q.img = img;
+  q.HW = (uint32_t)p.g.H * (uint32_t)p.g.W;
+  q.divHW = FastDiv(q.HW);
+  return shape == 0 ? launch_image<4>(q, s) : launch_image<8>(q, s);
 }
 
 }  // namespace bnn

@@ -122,3 +122,47 @@ def test_conv_word_offsets_fit_32_bits():
     f = lambda N, H, s: B.lib().bnn_testing_conv_word(N, 1, H, H, 64, 3, 3, s, s, 1, 1, 0, 1, 256)
     assert f(70, 2100, 2100) > 0 and f(70, 2900, 2900) == 0  # one output pixel an image: 65 images
     assert f(2, 16300, 5) > 0 and f(2, 16400, 5) == 0        # two images and a bit
+
+
+def image(N, C, H, W, D, kH, kW, sH, sW, pH, pW, shape=-1, pixel=0):
+    """bnn_testing_conv_image on 256 compute units -> (shape, first row, last row, rows with room)."""
+    out = (ctypes.c_int64 * 3)()
+    r = B.lib().bnn_testing_conv_image(N, C, H, W, D, kH, kW, sH, sW, pH, pW, 256, shape, pixel, out)
+    return (r, *out)
+
+
+def test_image_tiles_have_room_for_the_rows_they_read():
+    """Every tile of random small convolutions: the rows between its first and its last tap (outside the image: the nearest
+    row) are among those that it encodes, these fit the launch's LDS, and the tiles together encode the whole image."""
+    rng = random.Random(7)
+    tiles = 0
+    while tiles < 3000:
+        N, H, W = rng.choice([1, 2, 3, 7]), rng.randint(1, 14), rng.randint(1, 14)
+        kH, kW, sH, sW, pH, pW = (rng.randint(a, b) for a, b in ((1, 6), (1, 6), (1, 7), (1, 7), (0, 7), (0, 7)))
+        if H + 2 * pH < kH or W + 2 * pW < kW:
+            continue
+        OH, OW = (H + 2 * pH - kH) // sH + 1, (W + 2 * pW - kW) // sW + 1
+        done = -1
+        for n0 in range(0, N * OH * OW, 32):
+            shape, r0, r1, most = image(N, 64, H, W, 40, kH, kW, sH, sW, pH, pW, shape=1, pixel=n0)
+            assert shape == 1 and 0 <= r0 <= r1 < N * H and r1 - r0 + 1 <= most and r0 <= done + 1
+            done, tiles = max(done, r1), tiles + 1
+            for q in range(n0, min(N * OH * OW, n0 + 32)):
+                n, oh = q // (OH * OW), q // OW % OH
+                first, last = (n * H + min(max(oh * sH - pH + k, 0), H - 1) for k in (0, kH - 1))
+                assert r0 <= first and last <= r1
+        assert done == N * H - 1
+
+
+@pytest.mark.parametrize("case,want", [
+    ((16, 128, 16, 16, 64, 3, 1), 1), ((17, 128, 16, 16, 64, 3, 1), 0),   # t = 1, 1.06
+    ((32, 128, 16, 16, 64, 3, 1), 0), ((33, 128, 16, 16, 64, 3, 1), -1),  # 2, 2.06: b = 32
+    ((48, 96, 16, 16, 64, 3, 1), 0), ((48, 97, 16, 16, 64, 3, 1), -1),    # t = 3: b = 24, 24.25
+    ((49, 96, 16, 16, 64, 3, 1), -1),                                     # t = 3.06
+    ((1, 213, 32, 64, 32, 3, 1), 1), ((1, 214, 32, 64, 32, 3, 1), -1),    # t up to 1: b = 159.75, 160.5
+    ((32, 256, 16, 20, 32, 3, 1), -1), ((32, 256, 16, 16, 33, 3, 1), 0),  # above: b = 80 (of five rows, 100), 64
+    ((1, 8129, 1, 1, 8, 3, 1), -1)])                                      # more channels than the encode takes
+def test_image_rule_lines(case, want):
+    """Both sides of every line of the rule for convolutions in one launch, on 256 compute units."""
+    N, C, H, W, D, k, s = case
+    assert image(N, C, H, W, D, k, k, s, s, k // 2, k // 2)[0] == want

@@ -1,6 +1,7 @@
 """GPU parity: every entry point of the C ABI against the CPU oracle, element by element,
 on the same seeded host-generated inputs.  Integer / packed outputs must be bit-exact;
 the fp32 epilogue must match within 1e-6 relative (it is in fact built to be bit-exact)."""
+import ctypes
 import os
 
 import numpy as np
@@ -405,6 +406,39 @@ def test_conv2d_workspace_receives_the_packed_image(case):
     B.bnn_conv2d(x, wp, D, k, k, (s, s), (k // 2, k // 2), workspace=ws)
     assert torch.equal(ws[:8 * want.numel()].view(torch.int64), want)
     assert bool((ws[8 * want.numel():] == 0x5A).all())
+
+
+@pytest.mark.parametrize("case", [
+    (2, 64, 9, 11, 64, 3, 3, 1, 1, 1, 1),      # one word a pixel, whole
+    (3, 37, 14, 20, 70, 3, 3, 1, 1, 1, 1),     # partial granule of channels; a row tile of six channels
+    (1, 5, 6, 6, 33, 3, 3, 2, 2, 1, 1),        # few channels, fewer columns than a tile
+    (5, 100, 13, 12, 64, 5, 3, 2, 1, 0, 1),    # strides, windows and padding of their own; two words
+    (2, 129, 11, 8, 40, 3, 3, 1, 1, 1, 1),     # three words a pixel, one channel in the third
+    (2, 512, 8, 8, 96, 3, 3, 1, 1, 1, 1),      # two pieces of the encode to a wave
+    (40, 200, 3, 3, 40, 3, 3, 1, 1, 1, 1),     # a tile's pixels lie in five images
+    (3, 64, 8, 9, 64, 2, 2, 5, 5, 0, 0),       # rows that no window reads, between windows and behind the last
+    (4, 70, 3, 5, 32, 5, 5, 2, 2, 4, 4),       # windows that lie outside the image
+    (3, 130, 8, 10, 40, 1, 1, 2, 2, 1, 1), (1, 60, 1, 70, 64, 3, 3, 1, 1, 1, 1), (20, 256, 1, 1, 64, 3, 3, 1, 1, 1, 1)])
+def test_conv2d_in_one_launch(case):
+    """Convolutions whose tiles encode the rows that they read, forced and as an application calls them: both maps and the
+    packed image in the workspace, values of every kind that the sign rule names among the inputs."""
+    print(f"conv2d one launch case={case}", flush=True)
+    N, C, H, W, D, kH, kW, sH, sW, pH, pW = case
+    rows = (ctypes.c_int64 * 3)()
+    d = inputs.conv_inputs(inputs.ConvShape(*case), seed=sum(case))
+    x = inputs.inject_specials(d["x"], 3, frac=0.02)
+    ref = oracle.conv2d_pm1(x, d["w"], (sH, sW), (pH, pW))
+    xd, wp, sc, bi = dev(x), B.bnn_pack_conv_weight(dev(d["w"])), dev(d["scale"]), dev(d["bias"])
+    want = oracle.pack_nhwc(x).reshape(-1)
+    nbytes = B.conv2d_workspace_bytes(x.shape, kH, kW, (sH, sW), (pH, pW))
+    for cfg in (40, 41, None):
+        assert B.lib().bnn_testing_conv_image(*case, 256, -1 if cfg is None else cfg - 40, 0, rows) >= 0
+        ws = torch.full((max(16, nbytes) + 64,), 0x5A, dtype=torch.uint8, device=DEV)
+        oi, of = B.bnn_conv2d(xd, wp, D, kH, kW, (sH, sW), (pH, pW), sc, bi, workspace=ws, cfg=cfg)
+        assert np.array_equal(host(oi), ref)
+        assert np.array_equal(host(of), oracle.scale_bias(ref, d["scale"], d["bias"], "nchw"))
+        assert np.array_equal(as_u64(ws[:8 * want.size].view(torch.int64)), want)
+        assert bool((ws[max(16, nbytes):] == 0x5A).all())
 
 
 def test_gemm_table1_truth_table():
