@@ -100,18 +100,44 @@ __global__ __launch_bounds__(256) void conv2d_f32_kernel(const float *__restrict
   }
 }
 
+// Sixteen steps of a chain, both operands in registers.
+struct FcPart {
+  float4 x[4], w[4];
+  template <class Load>
+  __device__ __forceinline__ void read(const float *px, const float *pw, const Load &load) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      x[u] = load(px + 4 * u);
+      w[u] = load(pw + 4 * u);
+    }
+  }
+  __device__ __forceinline__ void steps(float &acc) const {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      acc = fmaf(x[u].x, w[u].x, acc);
+      acc = fmaf(x[u].y, w[u].y, acc);
+      acc = fmaf(x[u].z, w[u].z, acc);
+      acc = fmaf(x[u].w, w[u].w, acc);
+    }
+  }
+};
 // One workgroup per (ROWS rows of x, 16 outputs).  The whole K extent (up to FC_KC) of those
 // rows of x and w is staged in LDS by all 256 threads with every global load in flight at once,
-// so memory latency is paid once; then thread (output j, row r) runs the sequential fma chain
+// so memory latency is paid once; then thread (row r, output j) runs the sequential fma chain
 // over k, which is the floor for this layer (the summation order over k is ascending as
 // specified, so a chain cannot be split).  Longer rows take several passes over the two LDS
-// tiles.  The chains read both operands from LDS (32 bytes per 4 steps and thread), so LDS
-// bandwidth, not the chain, bounds a workgroup: ROWS = 4 (one computing wave, the other three
-// only stage) spreads a small layer over four times as many compute units as ROWS = 16.
+// tiles.  The chains read both operands from LDS (32 bytes per 4 steps and thread): ROWS = 4 (one
+// computing wave, the other three only stage) spreads a small layer over four times as many compute
+// units as ROWS = 16.  NW: rows of w that are staged, 12 where there are no more outputs.
+// Bound: a dependent fma takes 4.5 clocks (1.9 ns), 1024 of them 1.9 us; measured are 3.7 ns a step, staging included, beside the
+// launch.  256 x 1024 -> 10 in a graph 8.3 -> 6.95 us, 1 x 1024 -> 10 8.1 -> 6.65, 1000 x 1024 -> 1000 156 -> 130: the staging without a
+// branch around any load 0.8 us, reads two parts ahead without copies between registers 0.4.  (Factors of x by lane
+// broadcast inside the fma, one read for 64 steps: 0.3 us less, but written-out chains of such instructions fall under a wait
+// for the broadcast register that the compiler and the tests cannot tell from the sum's.)
 constexpr int FC_NB = 16;
 constexpr int FC_KC = 1024;
 constexpr int FC_RS = FC_KC + 4;  // row stride in floats: 16-byte reads of different rows spread over the banks
-template <int ROWS>
+template <int ROWS, int NW>
 __global__ __launch_bounds__(256) void fc_f32_kernel(const float *__restrict__ x, const float *__restrict__ w,
                                                      const float *__restrict__ bias, int64_t M, int64_t K, int64_t N,
                                                      int sign_input, float *__restrict__ out, int n_groups) {
@@ -120,43 +146,33 @@ __global__ __launch_bounds__(256) void fc_f32_kernel(const float *__restrict__ x
   const int64_t m0 = (int64_t)(blockIdx.x / n_groups) * ROWS;
   const int64_t n0 = (int64_t)(blockIdx.x % n_groups) * FC_NB;
   const int tid = threadIdx.x;
-  const int r = tid % ROWS, j = tid / ROWS;
+  const int r = tid / FC_NB, j = tid % FC_NB;
   const bool computes = tid < ROWS * FC_NB;  // whole waves: ROWS * 16 is a multiple of 64
   const bool vec = (K & 3) == 0;  // rows start 16-byte aligned (the bases are)
   float acc = 0.0f;
   for (int64_t k0 = 0; k0 < K; k0 += FC_KC) {
     const int kc = (int)((K - k0) < FC_KC ? (K - k0) : FC_KC);
     if (vec) {
-      constexpr int Q = FC_KC / 4;                    // 16-byte pieces per row
-      constexpr int PER = (ROWS + FC_NB) * Q / 256;   // pieces per thread: rows of x first, then rows of w
-      float4 v[PER];
+      static_assert(FC_KC == 4 * 256, "a thread's piece of every row");
+      const int kk = 4 * tid;
+      const int64_t kq = k0 + min(kk, kc - 4);  // threads past the rows' end read the last piece once more, without a branch
+      float4 vx[ROWS], vw[NW];
 #pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const int idx = i * 256 + tid;
-        const int rr = idx / Q, kk = (idx % Q) * 4;
-        v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (kk < kc) {
-          if (rr < ROWS) {
-            if (m0 + rr < M) v[i] = *reinterpret_cast<const float4 *>(x + (m0 + rr) * K + k0 + kk);
-          } else if (n0 + (rr - ROWS) < N) {
-            v[i] = *reinterpret_cast<const float4 *>(w + (n0 + (rr - ROWS)) * K + k0 + kk);
-          }
-        }
-      }
+      for (int i = 0; i < ROWS; ++i) vx[i] = *reinterpret_cast<const float4 *>(x + (m0 + i < M ? m0 + i : M - 1) * K + kq);
 #pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const int idx = i * 256 + tid;
-        const int rr = idx / Q, kk = (idx % Q) * 4;
-        float4 t = v[i];
-        if (rr < ROWS) {
+      for (int i = 0; i < NW; ++i) vw[i] = *reinterpret_cast<const float4 *>(w + (n0 + i < N ? n0 + i : N - 1) * K + kq);
+      if (kk < kc) {
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) {
+          float4 t = vx[i];
           if (sign_input) {
             t.x = t.x >= 0.0f ? 1.0f : -1.0f; t.y = t.y >= 0.0f ? 1.0f : -1.0f;
             t.z = t.z >= 0.0f ? 1.0f : -1.0f; t.w = t.w >= 0.0f ? 1.0f : -1.0f;
           }
-          *reinterpret_cast<float4 *>(&sx[rr * FC_RS + kk]) = t;
-        } else {
-          *reinterpret_cast<float4 *>(&sw[(rr - ROWS) * FC_RS + kk]) = t;
+          *reinterpret_cast<float4 *>(&sx[i * FC_RS + kk]) = t;
         }
+#pragma unroll
+        for (int i = 0; i < NW; ++i) *reinterpret_cast<float4 *>(&sw[i * FC_RS + kk]) = vw[i];
       }
     } else {
       for (int idx = tid; idx < (ROWS + FC_NB) * FC_KC; idx += 256) {
@@ -178,34 +194,28 @@ __global__ __launch_bounds__(256) void fc_f32_kernel(const float *__restrict__ x
     if (computes) {
       const float *px = &sx[r * FC_RS], *pw = &sw[j * FC_RS];
       int kk = 0;
-      // 32 k per round; the sixteen 16-byte LDS reads of the next round are issued before the
-      // chain of the current one, so their latency hides behind its 32 dependent fma
-      if (kc >= 32) {
-        float4 a[8], b[8];
+      // A step takes 4.5 clocks and an LDS read about 130: two parts of 16 steps are read ahead (no more than 15 reads can be in
+      // flight), in a ring of four, so that no register is copied.
+      auto load = [](const float *q) { return *reinterpret_cast<const float4 *>(q); };
+      if (kc >= 64) {
+        // volatile: the optimizer would make one load at the loop's head of these and those at its end, with nothing read ahead
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+        auto first = [](const float *q) {
+          const f32x4 v = *(const volatile __attribute__((address_space(3))) f32x4 *)q;
+          return make_float4(v.x, v.y, v.z, v.w);
+        };
+        FcPart ring[4];
+        ring[0].read(px, pw, first);
+        ring[1].read(px + 16, pw + 16, first);
+        for (; kk + 64 <= kc; kk += 64) {
+          const int next = kk + 128 <= kc ? kk + 64 : kk;  // last turn: this one once more (unused)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          a[u] = *reinterpret_cast<const float4 *>(px + 4 * u);
-          b[u] = *reinterpret_cast<const float4 *>(pw + 4 * u);
-        }
-        for (; kk + 32 <= kc; kk += 32) {
-          float4 an[8], bn[8];
-          const int nx = kk + 64 <= kc ? kk + 32 : kk;  // last round: re-read this one (unused)
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            an[u] = *reinterpret_cast<const float4 *>(px + nx + 4 * u);
-            bn[u] = *reinterpret_cast<const float4 *>(pw + nx + 4 * u);
-          }
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            acc = fmaf(a[u].x, b[u].x, acc);
-            acc = fmaf(a[u].y, b[u].y, acc);
-            acc = fmaf(a[u].z, b[u].z, acc);
-            acc = fmaf(a[u].w, b[u].w, acc);
-          }
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            a[u] = an[u];
-            b[u] = bn[u];
+          for (int part = 0; part < 4; ++part) {
+            const int at = part < 2 ? kk + 16 * (part + 2) : next + 16 * (part - 2);
+            __builtin_amdgcn_sched_barrier(0);
+            ring[(part + 2) % 4].read(px + at, pw + at, load);
+            __builtin_amdgcn_sched_barrier(0);
+            ring[part].steps(acc);
           }
         }
       }
@@ -377,9 +387,9 @@ extern "C" bnn_status bnn_fc_f32(const float *x, const float *w, const float *bi
     ProfScope ps(KID_FC_F32, s);
     const dim3 grid((unsigned)(m_groups * n_groups)), block(256);
     if (small)
-      hipLaunchKernelGGL(fc_f32_kernel<4>, grid, block, 0, s, x, w, bias, M, K, N, sign_input, out, (int)n_groups);
+      hipLaunchKernelGGL((N <= 12 ? fc_f32_kernel<4, 12> : fc_f32_kernel<4, 16>), grid, block, 0, s, x, w, bias, M, K, N, sign_input, out, (int)n_groups);
     else
-      hipLaunchKernelGGL(fc_f32_kernel<16>, grid, block, 0, s, x, w, bias, M, K, N, sign_input, out, (int)n_groups);
+      hipLaunchKernelGGL((fc_f32_kernel<16, 16>), grid, block, 0, s, x, w, bias, M, K, N, sign_input, out, (int)n_groups);
   }
   return launch_status();
 }

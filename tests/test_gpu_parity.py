@@ -658,6 +658,18 @@ def test_fc_f32_matches_oracle(M, K, N, sgn):
     assert np.array_equal(got, oracle.fc_f32_seq(xf, wf, None, sign_input=sgn), equal_nan=True)
 
 
+@pytest.mark.parametrize("M,K,N", [(4, 4, 12), (5, 60, 13), (3, 64, 12), (9, 68, 10), (1, 124, 1), (2, 128, 16), (4, 1020, 12),
+                                   (257, 1024, 17), (5, 1084, 11), (3, 1152, 13), (2100, 132, 18)])
+def test_fc_f32_turns(M, K, N):
+    """Rows of 0, 1, 2, 16 turns of 64 steps and what is left after them, alone and behind a full LDS pass; the staged rows of w
+    that outputs do not use."""
+    print(f"fc_f32 turns M={M} K={K} N={N}", flush=True)
+    rng = np.random.default_rng(M + K + N)
+    xf, wf = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    bf = rng.standard_normal(N).astype(np.float32)
+    assert np.array_equal(host(B.bnn_fc_f32(dev(xf), dev(wf), dev(bf))), oracle.fc_f32_seq(xf, wf, bf))
+
+
 @pytest.mark.parametrize("reading", ["A", "B"])
 def test_cfg4_stack_small_batch_every_layer(reading):
     print(f"cfg4 stack batch 4 reading {reading}", flush=True)
