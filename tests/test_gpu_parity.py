@@ -58,6 +58,40 @@ def test_encode_matches_oracle(rows, K):
     assert np.array_equal(got, oracle.encode_rows(x))
 
 
+@pytest.mark.parametrize("rows,K,gap,dst_gap", [
+    (1, 1024, 0, 0), (3, 1000, 0, 0), (5, 1030, 0, 0), (40, 64, 0, 0), (17, 128, 12, 0), (33, 960, 4, 3), (7, 2047, 1, 1),
+    (2, 4032, 0, 2), (9, 1088, 0, 0), (70, 65, 0, 0), (15, 64, 0, 0), (6, 3000, 0, 0)])
+def test_encode_waves_of_whole_and_partial_words(rows, K, gap, dst_gap):
+    """16 words a wave: inside a row, up to its end (whole or not), over rows with and without a gap, and fewer than 16."""
+    print(f"encode waves rows={rows} K={K} gaps {gap} {dst_gap}", flush=True)
+    rng = np.random.default_rng(rows + K)
+    x = inputs.inject_specials(rng.standard_normal((rows, K + gap)).astype(np.float32), K, frac=0.01)
+    Kw = B.packed_words(K)
+    dst = torch.full((rows, Kw + dst_gap), -1, dtype=torch.int64, device=DEV)
+    B.bnn_encode(dev(x)[:, :K], dst[:, :Kw])
+    out = as_u64(dst)
+    assert np.array_equal(out[:, :Kw], oracle.encode_rows(np.ascontiguousarray(x[:, :K])))
+    assert np.all(out[:, Kw:] == np.uint64(0xFFFFFFFFFFFFFFFF))
+
+
+def test_encode_more_words_than_a_launch_has_threads_for():
+    print("encode 2^31 + 1000 rows of one value", flush=True)
+    rows = 2 ** 31 + 1000
+    src = torch.empty((rows, 1), dtype=torch.float32, device=DEV).fill_(-1.0)
+    at = torch.randint(0, rows, (100000,), device=DEV, generator=torch.Generator(device=DEV).manual_seed(1))
+    at[:2000] = torch.arange(rows - 2000, rows, device=DEV)
+    src[at] = 1.0
+    dst = torch.full((rows, 1), -1, dtype=torch.int64, device=DEV)
+    B.bnn_encode(src, dst)
+    assert bool((dst[at] == 1).all())
+    ones, step = 0, 2 ** 28
+    for r in range(0, rows, step):
+        part = dst[r:r + step]
+        assert bool(((part == 0) | (part == 1)).all())
+        ones += int(part.sum())
+    assert ones == int(torch.unique(at).numel())
+
+
 def test_encode_strided_src_and_dst():
     print("encode strided", flush=True)
     rng = np.random.default_rng(5)
