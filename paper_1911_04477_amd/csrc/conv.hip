@@ -209,17 +209,23 @@ __global__ __launch_bounds__(256) void conv2d_f32_k27_mfma_kernel(const float *_
   const int half = lane >> 5, l32 = lane & 31;
   const int ch0 = 32 * NG * (int)blockIdx.y;
   const int nch = min(32 * NG, D - ch0);  // >= 1 by the grid
+  const uint32_t g_first = ((uint32_t)blockIdx.x * 4u + (uint32_t)wave) * (uint32_t)groups_per_wave;
+  // One channel group: the first patch is requested before the filters, as in the kernel above.  Four: 14 filter values a thread
+  // beside it cost more than they hide (8 x 512 x 224 x 224 213 us, 220).
+  constexpr bool AHEAD = NG == 1;
+  float xv[27];
+  uint32_t inside;
+  if (AHEAD)
+    c1m_issue_patch(x, g_first * 64u + (uint32_t)lane, total_pix, H, W, sH, sW, pH, pW, OH, OW, divOW, divOH, xv, inside);
   c1m_stage_filters<NG>(sTap, sSc, sBi, w, scale, bias, ch0, nch, has_affine != 0);
   __syncthreads();  // the only barrier
 
   const size_t ohw = (size_t)OH * OW;
-  const uint32_t g_first = ((uint32_t)blockIdx.x * 4u + (uint32_t)wave) * (uint32_t)groups_per_wave;
   for (int gi = 0; gi < groups_per_wave; ++gi) {
     const uint32_t grp = g_first + (uint32_t)gi;
     if (grp >= ngroups) break;  // wave-uniform
-    float xv[27];
-    uint32_t inside;
-    c1m_issue_patch(x, grp * 64u + (uint32_t)lane, total_pix, H, W, sH, sW, pH, pW, OH, OW, divOW, divOH, xv, inside);
+    if (!AHEAD || gi > 0)
+      c1m_issue_patch(x, grp * 64u + (uint32_t)lane, total_pix, H, W, sH, sW, pH, pW, OH, OW, divOW, divOH, xv, inside);
 #pragma unroll
     for (int k = 0; k < 27; ++k) xv[k] = ((inside >> (k % 9)) & 1u) ? xv[k] : 0.0f;
     // NCHW offsets of (image, channel 0, pixel) for the two pixels this lane holds results of
