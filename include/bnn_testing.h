@@ -81,6 +81,12 @@ BNN_API int bnn_testing_conv_word(int N, int C, int H, int W, int D, int kH, int
                                   int packed, int units);
 
 /*
+ * bnn_testing_conv_word_nontemporal -- host only, launches nothing: whether that kernel stores an int32 map of whole 16-byte
+ * pieces with non-temporal (1) or ordinary (0) stores; -1 where it cannot take the call.
+ */
+BNN_API int bnn_testing_conv_word_nontemporal(int N, int C, int H, int W, int D, int kH, int kW, int sH, int sW, int pH, int pW);
+
+/*
  * bnn_testing_nontemporal_maps -- host only, launches nothing: whether the matrix-core GEMM stores an int32 map
  * [M, N] of row stride ldc, starting base_bytes past a multiple of 128 bytes, with non-temporal (1) or ordinary
  * (0) stores; -1 for sizes below 1 or ldc < N.

@@ -190,7 +190,7 @@ bnn_status launch_conv_image(const GemmParams &p, const float *x, uint64_t *img,
 
 // How the matrix-core kernels store int32 / fp32 maps (gemm.hip): past the caches; whether columns and strides are
 // multiples of 4, so that a lane's columns can leave together.
-bool nontemporal_maps(const GemmParams &p, int bmode);
+bool nontemporal_maps(const GemmParams &p, int bmode, bool word = false);  // word: conv_word.hip's kernel
 bool map_columns_by_four(const GemmParams &p);
 bool map_rows_start_every(const GemmParams &p, uint32_t ints);  // multiples of `ints` 4-byte elements
 

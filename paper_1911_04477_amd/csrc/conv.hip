@@ -479,6 +479,16 @@ extern "C" int bnn_testing_conv_word(int N, int C, int H, int W, int D, int kH, 
 }
 
 // Declared in bnn_testing.h.
+extern "C" int bnn_testing_conv_word_nontemporal(int N, int C, int H, int W, int D, int kH, int kW, int sH, int sW, int pH, int pW) {
+  if (check_conv_geometry(N, C, H, W, kH, kW, sH, sW, pH, pW) != BNN_OK || N == 0 || D <= 0 ||
+      conv_limits(N, C, H, W, D, kH, kW, sH, sW, pH, pW) != BNN_OK)
+    return -1;
+  const GemmParams p = conv_gemm(nullptr, nullptr, N, C, H, W, D, kH, kW, sH, sW, pH, pW, 0, reinterpret_cast<int32_t *>((uintptr_t)4096),
+                                 nullptr, nullptr, nullptr, nullptr);
+  return !conv_word_applicable(p, 1) ? -1 : nontemporal_maps(p, 1, true) ? 1 : 0;
+}
+
+// Declared in bnn_testing.h.
 extern "C" int bnn_testing_conv_image(int N, int C, int H, int W, int D, int kH, int kW, int sH, int sW, int pH, int pW,
                                       int units, int shape, int pixel, int64_t *rows) {
   if (check_conv_geometry(N, C, H, W, kH, kW, sH, sW, pH, pW) != BNN_OK || N == 0 || D <= 0 || units <= 0 || !rows || shape > 1 ||

@@ -885,18 +885,21 @@ bool map_rows_start_every(const GemmParams &p, uint32_t ints) {
 //     Small calls whose rows are whole 32-byte sectors stay non-temporal from 12 words on: ordinary stores are 0 to 7 %
 //     faster alone, but push out the fp32 image that the same call encodes (74 x 128 x 20 x 39, stride 2, both maps:
 //     18.1 us, ordinary 19.2; 24 x 157 x 52 x 34 to 128 channels 21.0, 23.0).
+//     word: conv_word.hip's kernel has at most 36 words and no tiles to hide such stores behind: rows computed for nothing
+//     don't count (256 channels, 163 x 19 x 36 to 435 83 -> 56 us, 45 x 58 x 42 to 160 36.9 -> 26.2, 387 x 37 x 20 to 60
+//     37.2 -> 27.1), but up to 56 rows as above (48 x 46 x 18 to 48 9.6 against 10.05 ordinary).
 //   Rows of whole half lines (28 x 28 maps): the same where the stores decide, below 12 words, and the call's bytes
 //     still fit the last-level cache of 256 MB (64 x 28 x 28 from 576 bits, 240 MB: 55.5 -> 43.1 us; 512 x 117200 x 700
 //     60.8 -> 42.0); non-temporal elsewhere (512 x 117200 x 2304 80 us, ordinary 95; 64 x 44 x 44 from 512 bits, 300 MB:
 //     20 %; small calls 1 to 5 %).
-bool nontemporal_maps(const GemmParams &p, int bmode) {
+bool nontemporal_maps(const GemmParams &p, int bmode, bool word) {
   if (map_rows_start_every(p, 32) || p.M <= 32) return true;
   const int64_t words_x_m = (int64_t)p.Kw64 * (((int64_t)p.M + 63) / 64 * 64);
   const int64_t out = (int64_t)p.M * p.N * 4 * ((p.C ? 1 : 0) + (p.Y ? 1 : 0));
   const int64_t in = bmode == 0 ? (int64_t)p.N * p.Kw64 * 8 : (int64_t)p.g.Nimg * p.g.H * p.g.W * p.g.Cw * 8;
   const bool small = out + in <= 50000000, long_rows = words_x_m >= 12 * (int64_t)p.M;
   if (!map_rows_start_every(p, 16))
-    return words_x_m > 36 * (int64_t)p.M || (p.M <= 56 && 2 * in >= out) ||
+    return (words_x_m > 36 * (int64_t)p.M && !(word && p.M > 56)) || (p.M <= 56 && 2 * in >= out) ||
            (small && long_rows && map_rows_start_every(p, 8));
   return long_rows || small || out + in > 256000000;
 }
@@ -934,8 +937,9 @@ bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const Ge
   if (!valu) {
     // The matrix cores; few outputs split the reduction axis, and so do rows too long for exact fp32 sums.
     p.colperm = emode == 0 && map_columns_by_four(p) ? 1 : 0;
-    p.nt_store = emode == 0 && nontemporal_maps(p, bmode) ? 1 : 0;
-    if (word && (cfg < 0 ? tune.lean != 0 && conv_word_faster(p, emode) : cfg == 19)) return launch_conv_word(p, emode, s);
+    const bool by_word = word && (cfg < 0 ? tune.lean != 0 && conv_word_faster(p, emode) : cfg == 19);
+    p.nt_store = emode == 0 && nontemporal_maps(p, bmode, by_word) ? 1 : 0;
+    if (by_word) return launch_conv_word(p, emode, s);
     if (cfg >= 25 && cfg <= 28) return launch_gemm_fp4_split(p, bmode, emode, s, cfg - 25);
     if (cfg < 0 && (fp4_split_applicable(p, bmode) || !fp4_applicable(p))) return launch_gemm_fp4_split(p, bmode, emode, s, -1);
     return launch_gemm_fp4(p, bmode, emode, s, cfg >= 29 ? cfg - 25 : cfg >= 21 ? cfg - 21 : -1, tune.lean != 0);

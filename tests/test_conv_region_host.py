@@ -117,6 +117,14 @@ def test_conv_word_rule_lines(N, C, H, W, D, k, packed, want):
     assert B.lib().bnn_testing_conv_word(N, C, H, W, D, k, k, 1, 1, k // 2, k // 2, 0, packed, 256) == want
 
 
+@pytest.mark.parametrize("N,C,H,W,D,want", [
+    (163, 256, 19, 36, 435, 0), (163, 256, 19, 36, 512, 0), (387, 256, 37, 20, 60, 0), (223, 192, 58, 10, 57, 0),  # rows computed for nothing
+    (48, 256, 46, 18, 56, 1), (163, 256, 32, 8, 435, 1), (4, 128, 18, 12, 65, 1)])  # few rows; whole lines; small calls
+def test_conv_word_map_stores(N, C, H, W, D, want):
+    """Pieces of lines are stored past the caches only where the rule says that it does not matter."""
+    assert B.lib().bnn_testing_conv_word_nontemporal(N, C, H, W, D, 3, 3, 1, 1, 1, 1) == want
+
+
 def test_conv_word_offsets_fit_32_bits():
     """64 columns span at most 63 / (OH OW) + 2 images; their bytes are a 32-bit offset in the kernel."""
     f = lambda N, H, s: B.lib().bnn_testing_conv_word(N, 1, H, H, 64, 3, 3, s, s, 1, 1, 0, 1, 256)
