@@ -220,22 +220,27 @@ bool conv_word_applicable(const GemmParams &p, int bmode) {
 //      4.4 6.4, 6.2, 6.9 8.0, 6.2, 115 32.1, 29.6);
 // (up to three words: maps so small that a region's lanes idle stay on the split-K tiles where those take them, from 5.5 to 8
 // tiles a unit, which their tests state: 216 x 128 x 6 x 8 -> 166 7.6 us against 5.4);
-//   3: from u = 0.75 (0.56 7.8 against 8.0 and 9.9, 7.9; 0.67 8.5, 8.2; 0.98 9.7, 8.9; 2.3 14.7, 12.4; 14 50.5, 42.0);
+//   3: from u = 0.75 (0.56 7.8 against 8.0 and 9.9, 7.9; 0.67 8.5, 8.2; 0.98 9.7, 8.9; 2.3 14.7, 12.4; 14 50.5, 42.0), maps not
+//      with a second workgroup of 512 pixels on less than half of the units (u 2.08 16.6, 17.9; 2.4 17.2, 18.3; 2.9 17.7, 17.7; 3.05
+//      19.5, 16.9);
 //   4: its codes let one workgroup of 512 pixels run beside another, so it is whole rounds of them, two a unit: from u = 1 (0.95
-//      8.8 against 9.6, 1.04 11.6, 9.5, 1.98 12.0, 9.9) to 2 (2.2 14.9, 15.3; 2.6 15.3, 15.4; maps 2.2 17.5, 19.7; 2.6 19.2, 20.3), and
-//      from 3 on (3.03 18.5, 15.5; 3.06 23.2, 19.7; 4.7 23.4, 21.8 and 28.5, 29.0; 7.9 31.7, 29.5; 12 65.9, 60.4).
+//      8.8 against 9.6, 1.04 11.6, 9.5) up to one a unit (1.98 12.0, 9.9; 2.2 14.9, 15.3; 2.6 15.3, 15.4; maps 1.97 16.1, 15.1; 259 of them,
+//      33 on the 32 units of an XCD, 17.0, 18.2; 2.2 17.5, 19.7; 2.6 19.2, 20.3), and from one and a half on (3.03 18.5, 15.5; 3.06
+//      23.2, 19.7; 4.7 23.4, 21.8; 7.9 31.7, 29.5; 12 65.9, 60.4), but maps not with the first eighth of a third (4.1 24.4, 25.7; 4.3
+//      28.6, 29.4; 4.4 23.7, 25.8; 4.65 27.0, 26.4).
 bool conv_word_faster(const GemmParams &p, int emode) {
   if (p.g.kH == 1) return true;
   const int64_t cu = p.n_cu;
   const int64_t tiles = (((int64_t)p.M + 31) / 32) * (((int64_t)p.N + 31) / 32);
   const int64_t wide = (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 255) / 256);
+  const int64_t groups = (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 511) / 512);
   const bool signs = emode != 0;
   if (p.g.Cw < 4 && 2 * tiles > 11 * cu && fp4_split_applicable(p, 1)) return false;
   switch (p.g.Cw) {
     case 1: return signs ? 5 * tiles > 9 * cu : 2 * tiles > 5 * cu;
     case 2: return signs ? 10 * tiles > 27 * cu : tiles > 4 * cu;
-    case 3: return 4 * wide > 3 * cu;
-    default: return wide > cu && (wide <= 2 * cu || wide > 3 * cu);
+    case 3: return 4 * wide > 3 * cu && (signs || groups <= cu || 2 * groups > 3 * cu);
+    default: return wide > cu && (groups <= cu || 2 * groups > 3 * cu) && (signs || groups <= 2 * cu || 4 * groups > 9 * cu);
   }
 }
 

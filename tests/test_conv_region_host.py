@@ -118,6 +118,15 @@ def test_conv_word_rule_lines(N, C, H, W, D, k, packed, want):
 
 
 @pytest.mark.parametrize("N,C,H,W,D,want", [
+    (128, 192, 32, 32, 64, 2), (129, 192, 32, 32, 64, 1), (192, 129, 32, 32, 64, 1), (193, 129, 32, 32, 64, 2),  # three words: 1, 1.5
+    (77, 256, 8, 30, 435, 1), (256, 256, 32, 32, 64, 2), (257, 256, 32, 32, 64, 1),  # four: 259 workgroups; two a unit ...
+    (288, 256, 32, 32, 64, 1), (289, 256, 32, 32, 64, 2)])                           # ... and an eighth of a third
+def test_conv_word_rule_lines_of_maps(N, C, H, W, D, want):
+    """Maps of a few more workgroups of 512 pixels than one or two a unit: those left over last as long as all others."""
+    assert B.lib().bnn_testing_conv_word(N, C, H, W, D, 3, 3, 1, 1, 1, 1, 0, 0, 256) == want
+
+
+@pytest.mark.parametrize("N,C,H,W,D,want", [
     (163, 256, 19, 36, 435, 0), (163, 256, 19, 36, 512, 0), (387, 256, 37, 20, 60, 0), (223, 192, 58, 10, 57, 0),  # rows computed for nothing
     (48, 256, 46, 18, 56, 1), (163, 256, 32, 8, 435, 1), (4, 128, 18, 12, 65, 1)])  # few rows; whole lines; small calls
 def test_conv_word_map_stores(N, C, H, W, D, want):
