@@ -128,7 +128,9 @@ struct FcPart {
 // specified, so a chain cannot be split).  Longer rows take several passes over the two LDS
 // tiles.  The chains read both operands from LDS (32 bytes per 4 steps and thread): ROWS = 4 (one
 // computing wave, the other three only stage) spreads a small layer over four times as many compute
-// units as ROWS = 16.  NW: rows of w that are staged, 12 where there are no more outputs.
+// units as ROWS = 16.  NW: rows of w that are staged, 12 where there are no more outputs.  VEC: rows are whole 16-byte pieces; a
+// kernel each, since in one the two ways of staging cost each other registers (1 x 1024 -> 10 6.6 us alone, 7.5 together; 1 x 127 -> 10
+// 3.6 us a value of every row at a time, 10.2 with a bound around every load).
 // Bound: a dependent fma takes 4.5 clocks (1.9 ns), 1024 of them 1.9 us; measured are 3.7 ns a step, staging included, beside the
 // launch.  256 x 1024 -> 10 in a graph 8.3 -> 6.95 us, 1 x 1024 -> 10 8.1 -> 6.65, 1000 x 1024 -> 1000 156 -> 130: the staging without a
 // branch around any load 0.8 us, reads two parts ahead without copies between registers 0.4.  (Factors of x by lane
@@ -137,7 +139,7 @@ struct FcPart {
 constexpr int FC_NB = 16;
 constexpr int FC_KC = 1024;
 constexpr int FC_RS = FC_KC + 4;  // row stride in floats: 16-byte reads of different rows spread over the banks
-template <int ROWS, int NW>
+template <int ROWS, int NW, bool VEC>
 __global__ __launch_bounds__(256) void fc_f32_kernel(const float *__restrict__ x, const float *__restrict__ w,
                                                      const float *__restrict__ bias, int64_t M, int64_t K, int64_t N,
                                                      int sign_input, float *__restrict__ out, int n_groups) {
@@ -148,11 +150,10 @@ __global__ __launch_bounds__(256) void fc_f32_kernel(const float *__restrict__ x
   const int tid = threadIdx.x;
   const int r = tid / FC_NB, j = tid % FC_NB;
   const bool computes = tid < ROWS * FC_NB;  // whole waves: ROWS * 16 is a multiple of 64
-  const bool vec = (K & 3) == 0;  // rows start 16-byte aligned (the bases are)
   float acc = 0.0f;
   for (int64_t k0 = 0; k0 < K; k0 += FC_KC) {
     const int kc = (int)((K - k0) < FC_KC ? (K - k0) : FC_KC);
-    if (vec) {
+    if constexpr (VEC) {  // rows start 16-byte aligned (the bases are)
       static_assert(FC_KC == 4 * 256, "a thread's piece of every row");
       const int kk = 4 * tid;
       const int64_t kq = k0 + min(kk, kc - 4);  // threads past the rows' end read the last piece once more, without a branch
@@ -175,19 +176,17 @@ __global__ __launch_bounds__(256) void fc_f32_kernel(const float *__restrict__ x
         for (int i = 0; i < NW; ++i) *reinterpret_cast<float4 *>(&sw[i * FC_RS + kk]) = vw[i];
       }
     } else {
-      for (int idx = tid; idx < (ROWS + FC_NB) * FC_KC; idx += 256) {
-        const int rr = idx / FC_KC, kk = idx % FC_KC;
-        float t = 0.0f;
-        if (kk < kc) {
-          if (rr < ROWS) {
-            if (m0 + rr < M) t = x[(m0 + rr) * K + k0 + kk];
-            if (sign_input) t = t >= 0.0f ? 1.0f : -1.0f;
-          } else if (n0 + (rr - ROWS) < N) {
-            t = w[(n0 + (rr - ROWS)) * K + k0 + kk];
-          }
-        }
-        if (rr < ROWS) sx[rr * FC_RS + kk] = t;
-        else sw[(rr - ROWS) * FC_RS + kk] = t;
+#pragma unroll 1
+      for (int kk = tid; kk < kc; kk += 256) {  // a value of every row at a time, as above
+        float vx[ROWS], vw[NW];
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) vx[i] = x[(m0 + i < M ? m0 + i : M - 1) * K + k0 + kk];
+#pragma unroll
+        for (int i = 0; i < NW; ++i) vw[i] = w[(n0 + i < N ? n0 + i : N - 1) * K + k0 + kk];
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) sx[i * FC_RS + kk] = sign_input ? (vx[i] >= 0.0f ? 1.0f : -1.0f) : vx[i];
+#pragma unroll
+        for (int i = 0; i < NW; ++i) sw[i * FC_RS + kk] = vw[i];
       }
     }
     __syncthreads();
@@ -386,10 +385,11 @@ extern "C" bnn_status bnn_fc_f32(const float *x, const float *w, const float *bi
   {
     ProfScope ps(KID_FC_F32, s);
     const dim3 grid((unsigned)(m_groups * n_groups)), block(256);
-    if (small)
-      hipLaunchKernelGGL((N <= 12 ? fc_f32_kernel<4, 12> : fc_f32_kernel<4, 16>), grid, block, 0, s, x, w, bias, M, K, N, sign_input, out, (int)n_groups);
-    else
-      hipLaunchKernelGGL((fc_f32_kernel<16, 16>), grid, block, 0, s, x, w, bias, M, K, N, sign_input, out, (int)n_groups);
+    const bool vec = (K & 3) == 0;
+    auto *const kernel = !small    ? (vec ? fc_f32_kernel<16, 16, true> : fc_f32_kernel<16, 16, false>)
+                         : N <= 12 ? (vec ? fc_f32_kernel<4, 12, true> : fc_f32_kernel<4, 12, false>)
+                                   : (vec ? fc_f32_kernel<4, 16, true> : fc_f32_kernel<4, 16, false>);
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, x, w, bias, M, K, N, sign_input, out, (int)n_groups);
   }
   return launch_status();
 }

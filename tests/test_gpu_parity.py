@@ -704,6 +704,20 @@ def test_fc_f32_turns(M, K, N):
     assert np.array_equal(host(B.bnn_fc_f32(dev(xf), dev(wf), dev(bf))), oracle.fc_f32_seq(xf, wf, bf))
 
 
+@pytest.mark.parametrize("M,K,N", [(1, 1, 1), (4, 3, 12), (5, 63, 13), (3, 255, 12), (2, 257, 10), (3, 1023, 12), (6, 1025, 16),
+                                   (5, 2046, 11), (2100, 131, 18), (2300, 33, 16)])
+@pytest.mark.parametrize("sgn", [False, True])
+def test_fc_f32_rows_off_16_bytes(M, K, N, sgn):
+    """Rows of no multiple of four values, staged a value of every row at a time: every form, one to four turns of 256 values, one and
+    two LDS passes, rows of x and w past the last."""
+    print(f"fc_f32 odd rows M={M} K={K} N={N} sign={sgn}", flush=True)
+    rng = np.random.default_rng(M + K + N)
+    xf, wf = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    bf = rng.standard_normal(N).astype(np.float32)
+    got = host(B.bnn_fc_f32(dev(xf), dev(wf), dev(bf), sign_input=sgn))
+    assert np.array_equal(got, oracle.fc_f32_seq(xf, wf, bf, sign_input=sgn))
+
+
 @pytest.mark.parametrize("reading", ["A", "B"])
 def test_cfg4_stack_small_batch_every_layer(reading):
     print(f"cfg4 stack batch 4 reading {reading}", flush=True)
