@@ -73,6 +73,7 @@ TESTING_SIGNATURES = {
     "bnn_testing_conv_image": (_i32, [_i32] * 14 + [ctypes.POINTER(_i64)]),
     "bnn_testing_conv_word": (_i32, [_i32] * 14),
     "bnn_testing_conv_word_nontemporal": (_i32, [_i32] * 11),
+    "bnn_testing_first_sign": (_i32, [_i32] * 9),
     "bnn_testing_conv_region": (_i32, [_i32] * 12 + [ctypes.POINTER(_i64)]),
     "bnn_testing_nontemporal_maps": (_i32, [_i32, _i32, _i32, _i64, _i64]),
     "bnn_testing_xnor_gemm_mfma_fp4_expanded": (_i32, [_p, _i64, _p, _i64, _p, _i64, _i64, _i64, _i64, _i32, _p]),

@@ -255,9 +255,9 @@ bnn_status run_im2col(const float *x, int N, int C, int H, int W, int kH, int kW
 bnn_status launch_conv2d_f32_k27(const float *x, const float *w, int N, int H, int W, int D, int sH, int sW, int pH,
                                  int pW, const float *scale, const float *bias, float *out, hipStream_t s);
 
-// Signs of the 3x3x3 layer for more than a few pixels (conv_first_sign.hip).
-bool first_sign_f16_applicable(int N, int H, int W, int D, int sH, int sW, int pH, int pW);
+// Signs of the 3x3x3 layer for more than a few pixels (conv_first_sign.hip), by workgroups of 4, 8 or 16 waves (0, 1, 2; -1: not).
+int first_sign_f16(int N, int H, int W, int D, int sH, int sW, int pH, int pW, int units);
 bnn_status launch_first_sign_f16(const float *x, const float *w, int N, int H, int W, int D, int sH, int sW, int pH, int pW,
-                                 const float *scale, const float *bias, uint64_t *out, hipStream_t s);
+                                 const float *scale, const float *bias, uint64_t *out, int shape, hipStream_t s);
 
 }  // namespace bnn

@@ -502,6 +502,13 @@ extern "C" int bnn_testing_conv_image(int N, int C, int H, int W, int D, int kH,
   return r;
 }
 
+// Declared in bnn_testing.h.
+extern "C" int bnn_testing_first_sign(int N, int H, int W, int D, int sH, int sW, int pH, int pW, int units) {
+  if (check_conv_geometry(N, 3, H, W, 3, 3, sH, sW, pH, pW) != BNN_OK || N == 0 || D <= 0 || units <= 0) return -1;
+  const int shape = first_sign_f16(N, H, W, D, sH, sW, pH, pW, units);
+  return shape < 0 ? 0 : 2 + shape;
+}
+
 extern "C" bnn_status bnn_conv2d_f32_sign(const float *x, const float *w, int N, int C, int H, int W, int D, int kH,
                                           int kW, int sH, int sW, int pH, int pW, const float *scale,
                                           const float *bias, uint64_t *out_packed, void *stream) {
@@ -521,8 +528,8 @@ extern "C" bnn_status bnn_conv2d_f32_sign(const float *x, const float *w, int N,
     ProfScope ps(KID_CONV_F32_SIGN, s);
     const dim3 block(256);
     if (K == 27 && C == 3 && kH == 3 && kW == 3) {
-      if (first_sign_f16_applicable(N, H, W, D, sH, sW, pH, pW))
-        return launch_first_sign_f16(x, w, N, H, W, D, sH, sW, pH, pW, scale, bias, out_packed, s);
+      const int shape = first_sign_f16(N, H, W, D, sH, sW, pH, pW, device_cu_count());
+      if (shape >= 0) return launch_first_sign_f16(x, w, N, H, W, D, sH, sW, pH, pW, scale, bias, out_packed, shape, s);
       int gpw;
       const dim3 grid = c1m_grid(total, D, 1, &gpw);
       hipLaunchKernelGGL(conv2d_f32_k27_mfma_sign_kernel, grid, block, 0, s, x, w, H, W, D, sH, sW, pH, pW, (int)OH, (int)OW,

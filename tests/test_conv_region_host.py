@@ -141,6 +141,16 @@ def test_conv_word_offsets_fit_32_bits():
     assert f(2, 16300, 5) > 0 and f(2, 16400, 5) == 0        # two images and a bit
 
 
+@pytest.mark.parametrize("N,H,W,D,want", [
+    (48, 32, 32, 128, 0), (49, 32, 32, 128, 2), (192, 32, 32, 32, 0), (193, 32, 32, 32, 2),  # q = 12, 12.25; 12, 12.06
+    (108, 32, 32, 128, 2), (109, 32, 32, 128, 3),                                               # 27, 27.25: one round of eight waves
+    (128, 32, 32, 128, 3), (129, 32, 32, 128, 4), (257, 32, 32, 128, 3), (640, 32, 32, 128, 3),  # one, two, three, five
+    (641, 32, 32, 128, 4), (769, 32, 32, 128, 4), (64, 32, 32, 250, 3), (128, 32, 32, 200, 4)])  # six, seven; 256 channels
+def test_first_sign_forms(N, H, W, D, want):
+    """Both sides of every line between the forms of the first layer's signs, on 256 compute units."""
+    assert B.lib().bnn_testing_first_sign(N, H, W, D, 1, 1, 1, 1, 256) == want
+
+
 def image(N, C, H, W, D, kH, kW, sH, sW, pH, pW, shape=-1, pixel=0):
     """bnn_testing_conv_image on 256 compute units -> (shape, first row, last row, rows with room)."""
     out = (ctypes.c_int64 * 3)()

@@ -2024,6 +2024,117 @@ def test_first_layer_signs_beyond_the_bound(N, D, kind):
     assert np.array_equal(got, oracle.pack_nhwc(ref))
 
 
+FIRST_FORMS = [  # images of 32 x 32, channels, form
+    (80, 90, 2), (64, 250, 3), (128, 200, 4),
+    (600, 40, 3), (512, 40, 4)]  # two groups of pixels a wave
+
+
+def _first_signs(N, D, form, x, w, sc, bi):
+    """The signs of N images of 32 x 32, the ones of x over and over, in the form that the sizes are for, against the oracle's."""
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert B.lib().bnn_testing_first_sign(N, 32, 32, D, 1, 1, 1, 1, 256) == form
+    with np.errstate(all="ignore"):
+        ref = oracle.pack_nhwc(oracle.conv2d_f32_seq(x, w, (1, 1), (1, 1), sc, bi))
+    xs = dev(x).repeat((N + len(x) - 1) // len(x), 1, 1, 1)[:N].contiguous()
+    got = as_u64(B.bnn_conv2d_f32_sign(xs, dev(w), dev(sc), dev(bi), (1, 1), (1, 1)))
+    bad = [n for n in range(N) if not np.array_equal(got[n], ref[n % len(x)])]
+    assert not bad, bad
+
+
+@pytest.mark.parametrize("kind", ["zeros", "zeros and biases", "sizes", "sizes and biases", "nans", "pruned", "one filter", "infinities",
+                                  "ties", "specials"])
+@pytest.mark.parametrize("N,D,form", FIRST_FORMS)
+def test_first_layer_signs_of_whole_areas_in_doubt(N, D, form, kind):
+    """What leaves more pixels in doubt than the half-precision kernel computes one by one, in every form of it: areas of zeros, sizes
+    from 2^-140 to 2^120, NaN, channels without a filter, one filter that the bound does not cover."""
+    print(f"first layer signs, areas: N={N} D={D} {kind}", flush=True)
+    rng = np.random.default_rng(N + D)
+    x = rng.standard_normal((16, 3, 32, 32)).astype(np.float32)
+    w = rng.standard_normal((D, 3, 3, 3)).astype(np.float32)
+    sc, bi = (rng.random(D) + 0.5).astype(np.float32), 0.1 * rng.standard_normal(D).astype(np.float32)
+    sc[::5] *= np.float32(-1)
+    if kind in ("zeros", "sizes", "one filter", "ties"):
+        bi[:] = 0.0
+    if kind.startswith("zeros"):
+        x[::2] = 0.0
+        x[1::4, :, 5:20, 7:] = -0.0
+        x[3, :, 8, 8] = 1e-30
+        bi[1::3], bi[2::9], bi[8::9] = 0.0, -0.0, -1e-38
+        if kind == "zeros":
+            bi[:] = np.where(np.arange(D) % 2, np.float32(0.0), np.float32(-0.0))
+    elif kind.startswith("sizes"):
+        x *= np.float32(2.0) ** np.array([-140, -100, -60, -49, -47, -30, -14, -3, -2, 0, 13, 16, 40, 59, 62, 120], np.float32).reshape(16, 1, 1, 1)
+        x[4, :, :, 16:] *= np.float32(2.0**60)  # both in the pixels of one wave
+        x[9, :, 10:20] = 0.0
+        if kind != "sizes":
+            bi *= np.float32(2.0) ** rng.integers(-60, 30, D).astype(np.float32)
+            bi[::4] = 0.0
+    elif kind == "nans":
+        x[::2, 1, ::3] = np.nan
+        x[1, 0, 4, 4] = np.nan
+    elif kind == "pruned":
+        w[::3] = 0.0
+        w[4, 0] = -0.0
+        sc[1::7], bi[::2] = 0.0, 0.0
+        x[::5] = 0.0
+        x[1] = np.inf
+    elif kind == "one filter":
+        w[35, 1, 1, 1] = np.inf
+        w[3] *= np.float32(1e-30)
+        x[::3] = 0.0
+        x[1::3, :, 3:9] = np.nan
+    elif kind == "infinities":
+        x[::2].reshape(-1)[::997] = np.inf
+        x[1::2].reshape(-1)[::53] = -np.inf
+    elif kind == "ties":
+        x, w = rng.integers(-2, 3, x.shape).astype(np.float32), rng.integers(-2, 3, w.shape).astype(np.float32)
+        sc[:] = 1.0
+    else:
+        x = inputs.inject_specials(x, 3, frac=0.1)
+    _first_signs(N, D, form, x, w, sc, bi)
+
+
+@pytest.mark.parametrize("biased", [False, True])
+def test_first_layer_signs_decided_by_subnormal_halves(biased):
+    """Patches whose high halves cancel under the filter and whose low halves, subnormal in fp16, turn the sum against a 27th value:
+    matrix instructions that took them as zeros would find the other sign, far beyond the bound."""
+    print(f"first layer signs, subnormal halves biased={biased}", flush=True)
+    N, D = 8256, 808  # one pixel an image
+    rng = np.random.default_rng(3)
+    w0 = np.tile(np.array([1, -1], np.float32), 13)
+    a = (rng.integers(1024, 1229, (N, 13)) * 2.0**-12).astype(np.float32)  # fp16 holds them: 0.25 to 0.3
+    low = (rng.random((N, 26)) * 2e-5 + 3e-5).astype(np.float32)          # below half an ulp of fp16 there (2^-13), and below 2^-14
+    x = np.empty((N, 27), np.float32)
+    x[:, :26] = np.repeat(a, 2, axis=1) + low * w0
+    x[:, 26] = -0.5 * low.sum(axis=1)
+    w = np.concatenate([w0, [1.0]]).astype(np.float32) * rng.choice([-1, 1], (D, 1)).astype(np.float32) * (rng.random((D, 1)) + 0.5).astype(np.float32)
+    order = rng.permutation(27)
+    x, w = x[:, order].reshape(N, 3, 3, 3), w[:, order].reshape(D, 3, 3, 3)
+    sc, bi = np.ones(D, np.float32), np.zeros(D, np.float32)
+    if biased:
+        bi[1::2] = 1e-5 * rng.standard_normal(D // 2).astype(np.float32)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert B.lib().bnn_testing_first_sign(N, 3, 3, D, 1, 1, 0, 0, 256) >= 2
+    ref = oracle.conv2d_f32_seq(x, w, (1, 1), (0, 0), sc, bi)
+    assert np.array_equal(ref[:, :, 0, 0] >= 0, np.broadcast_to(w.reshape(D, 27)[:, np.argwhere(order == 26)[0, 0]] > 0, (N, D)))
+    got = as_u64(B.bnn_conv2d_f32_sign(dev(x), dev(w), dev(sc), dev(bi), (1, 1), (0, 0)))
+    assert np.array_equal(got, oracle.pack_nhwc(ref))
+
+
+@pytest.mark.parametrize("e", range(-24, -1, 3))
+def test_first_layer_signs_of_small_values(e):
+    """Values about 2^e: halves of fp16 that are subnormal, low ones and high ones, with biases as small and with none."""
+    print(f"first layer signs, values about 2^{e}", flush=True)
+    rng = np.random.default_rng(100 + e)
+    N, D = 80, 90
+    x = (rng.standard_normal((16, 3, 32, 32)) * 2.0**e).astype(np.float32)
+    w = rng.standard_normal((D, 3, 3, 3)).astype(np.float32)
+    for none in (False, True):
+        sc, bi = (rng.random(D) + 0.5).astype(np.float32), (rng.standard_normal(D) * 2.0 ** (e + 2)).astype(np.float32)
+        bi[:: 1 if none else 3] = 0.0
+        _first_signs(N, D, 2, x, w, sc, bi)
+
+
 @pytest.mark.parametrize("N,D", [(4, 449), (4, 256), (3, 449)])
 def test_first_layer_large_maps(N, D):
     """Maps above and below 350 MB, channel counts on both sides of the rule and off the groups of 32 and 128: the
