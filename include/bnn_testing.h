@@ -145,7 +145,7 @@ BNN_API int bnn_testing_conv_image(int N, int C, int H, int W, int D, int kH, in
                                    int units, int shape, int pixel, int64_t *rows);
 
 /* The form in which bnn_conv2d_f32_sign takes a 3 x 3 layer of three channels on a device of `units` compute units: 0 fused
- * multiply-add chains for every output, one group of 32 channels a workgroup; 2, 3, 4 half-precision products by workgroups of 4, 8, 16
+ * multiply-add chains for every output, one group of 32 channels a workgroup, 1 four groups; 2, 3, 4 half-precision products by workgroups of 4, 8, 16
  * waves; -1 for invalid arguments.  Host only, launches nothing. */
 BNN_API int bnn_testing_first_sign(int N, int H, int W, int D, int sH, int sW, int pH, int pW, int units);
 

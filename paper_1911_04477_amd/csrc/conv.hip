@@ -151,21 +151,23 @@ __global__ __launch_bounds__(256) void conv2d_f32_sign_kernel(const float *__res
 }
 
 // ---- the 3x3x3 layer (K = 27) on the fp32 matrix cores: conv_first.h --------------------------
-// Packed-sign output for few pixels (conv_first_sign.hip takes the others): one group of 32 channels per workgroup, since the
-// chains of a group are 27 dependent instructions of 64 clocks (batch 1 of the 32 x 32, 128-channel layer: four groups 8.6 us,
-// one 4.3).  On this chip the fp32 matrix instructions and the vector ALU do not run side by side (vector
-// instructions placed between the matrix instructions of a chain lengthen it by their full
+// Packed-sign output for few pixels, and for images beyond the 32-bit offsets of conv_first_sign.hip, which takes the others.  NG:
+// groups of 32 channels per workgroup.  Few pixels: one, since the chains of a group are 27 dependent instructions of 64 clocks
+// (batch 1 of the 32 x 32, 128-channel layer: four groups 8.6 us, one 4.3).  Very large images: four, which share a patch's loads (256
+// images of 32 x 32 22.5 us, one 27.3) and keep blockIdx.y small.  On this chip the fp32 matrix instructions and the vector ALU do
+// not run side by side (vector instructions placed between the matrix instructions of a chain lengthen it by their full
 // issue time, measured), so the loop is the plain sequence loads, chain, sign step, store.
+template <int NG>
 __global__ __launch_bounds__(256, 4) void conv2d_f32_k27_mfma_sign_kernel(
     const float *__restrict__ x, const float *__restrict__ w, int H, int W, int D, int sH, int sW, int pH, int pW,
     int OH, int OW, const float *__restrict__ scale, const float *__restrict__ bias, uint64_t *__restrict__ outp,
     int cw_out, FastDiv divOW, FastDiv divOH, uint32_t total_pix, uint32_t ngroups, int groups_per_wave) {
-  __shared__ float sTap[27 * C1M_RS(1)];
-  __shared__ __attribute__((aligned(16))) float sSc[32];
-  __shared__ __attribute__((aligned(16))) float sBi[32];
+  __shared__ float sTap[27 * C1M_RS(NG)];
+  __shared__ __attribute__((aligned(16))) float sSc[32 * NG];
+  __shared__ __attribute__((aligned(16))) float sBi[32 * NG];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, l32 = lane & 31;
-  const int ch0 = 32 * (int)blockIdx.y;
+  const int ch0 = 32 * NG * (int)blockIdx.y;
   const uint32_t g_first = ((uint32_t)blockIdx.x * 4u + (uint32_t)wave) * (uint32_t)groups_per_wave;
   const uint32_t g_end = min(g_first + (uint32_t)groups_per_wave, ngroups);
   // the first patch is requested before the filters are staged, so the two latencies overlap
@@ -173,7 +175,8 @@ __global__ __launch_bounds__(256, 4) void conv2d_f32_k27_mfma_sign_kernel(
   float xv[27];
   uint32_t inside;
   c1m_issue_patch(x, g_first * 64u + (uint32_t)lane, total_pix, H, W, sH, sW, pH, pW, OH, OW, divOW, divOH, xv, inside);
-  c1m_stage_filters<1>(sTap, sSc, sBi, w, scale, bias, ch0, min(32, D - ch0), true);
+  const int nch = min(32 * NG, D - ch0);  // >= 1 by the grid
+  c1m_stage_filters<NG>(sTap, sSc, sBi, w, scale, bias, ch0, nch, true);
   __syncthreads();  // the only barrier: from here on the waves run independently
 
   for (uint32_t grp = g_first; grp < g_end; ++grp) {  // wave-uniform bounds
@@ -182,13 +185,23 @@ __global__ __launch_bounds__(256, 4) void conv2d_f32_k27_mfma_sign_kernel(
       c1m_issue_patch(x, p, total_pix, H, W, sH, sW, pH, pW, OH, OW, divOW, divOH, xv, inside);
 #pragma unroll
     for (int k = 0; k < 27; ++k) xv[k] = ((inside >> (k % 9)) & 1u) ? xv[k] : 0.0f;
-    const c1m_v32f acc = c1m_chain<1>(sTap + l32, xv);
-    const uint32_t word = c1m_sign_bits(acc, sSc, sBi, 0, half);
-    if (p < total_pix) {  // a 32-channel half word; the last group also writes the half that holds no channel
-      const int h0 = (int)blockIdx.y;
+    uint32_t gw[NG];
+#pragma unroll
+    for (int c = 0; c < NG; ++c) gw[c] = 0u;
+#pragma unroll
+    for (int c = 0; c < NG; ++c) {
+      if (32 * c >= nch) break;  // workgroup-uniform: groups past the last channel keep zero bits
+      gw[c] = c1m_sign_bits(c1m_chain<NG>(sTap + 32 * c + l32, xv), sSc, sBi, c, half);
+    }
+    if (p < total_pix) {  // 32-channel half words; the last group also writes the half that holds no channel
       uint32_t *o = reinterpret_cast<uint32_t *>(outp + (size_t)p * cw_out);
-      o[h0] = word;
-      if (h0 + 1 == (int)gridDim.y && h0 + 1 < 2 * cw_out) o[h0 + 1] = 0u;
+#pragma unroll
+      for (int c = 0; c < NG; ++c) {
+        const int h0 = NG * (int)blockIdx.y + c;
+        if (32 * c >= nch) break;
+        o[h0] = gw[c];
+        if (32 * (h0 + 1) >= D && h0 + 1 < 2 * cw_out) o[h0 + 1] = 0u;
+      }
     }
   }
 }
@@ -266,6 +279,14 @@ static dim3 c1m_grid(int64_t total_pix, int D, int ng, int *gpw, int64_t wave_sl
   *gpw = (int)g;
   const int64_t waves = (ngroups + g - 1) / g;
   return dim3((unsigned)((waves + 3) / 4), (unsigned)((D + 32 * ng - 1) / (32 * ng)));
+}
+
+// Chains for the signs of more than a few pixels: four channel groups per workgroup from more than 24 pairs of 64 pixels and 32
+// channels a unit on, or 12 if a SIMD gets more than four waves per 128 channels (32 x 32 maps, 128 channels: batch 63 9.2 us, one group
+// 8.4; batch 128 13.5 against 14.0; batch 63, 512 channels 21.9, 26.6).
+static bool first_chains_by_four(int64_t total_pix, int D, int64_t cu) {
+  const int64_t groups = (total_pix + 63) / 64, q = groups * (((int64_t)D + 31) / 32);
+  return q > 24 * cu || (q > 12 * cu && groups > 4 * cu);
 }
 
 // Filter bank of a fully-connected layer whose input is a flattened NCHW map [C, H, W],
@@ -506,7 +527,8 @@ extern "C" int bnn_testing_conv_image(int N, int C, int H, int W, int D, int kH,
 extern "C" int bnn_testing_first_sign(int N, int H, int W, int D, int sH, int sW, int pH, int pW, int units) {
   if (check_conv_geometry(N, 3, H, W, 3, 3, sH, sW, pH, pW) != BNN_OK || N == 0 || D <= 0 || units <= 0) return -1;
   const int shape = first_sign_f16(N, H, W, D, sH, sW, pH, pW, units);
-  return shape < 0 ? 0 : 2 + shape;
+  const int64_t total = (int64_t)N * bnn_conv_out_dim(H, 3, sH, pH) * bnn_conv_out_dim(W, 3, sW, pW);
+  return shape >= 0 ? 2 + shape : first_chains_by_four(total, D, units) ? 1 : 0;
 }
 
 extern "C" bnn_status bnn_conv2d_f32_sign(const float *x, const float *w, int N, int C, int H, int W, int D, int kH,
@@ -530,11 +552,12 @@ extern "C" bnn_status bnn_conv2d_f32_sign(const float *x, const float *w, int N,
     if (K == 27 && C == 3 && kH == 3 && kW == 3) {
       const int shape = first_sign_f16(N, H, W, D, sH, sW, pH, pW, device_cu_count());
       if (shape >= 0) return launch_first_sign_f16(x, w, N, H, W, D, sH, sW, pH, pW, scale, bias, out_packed, shape, s);
+      const bool four = first_chains_by_four(total, D, device_cu_count());
       int gpw;
-      const dim3 grid = c1m_grid(total, D, 1, &gpw);
-      hipLaunchKernelGGL(conv2d_f32_k27_mfma_sign_kernel, grid, block, 0, s, x, w, H, W, D, sH, sW, pH, pW, (int)OH, (int)OW,
-                         scale, bias, out_packed, (int)bnn_packed_words(D), FastDiv((uint32_t)OW), FastDiv((uint32_t)OH),
-                         (uint32_t)total, (uint32_t)((total + 63) / 64), gpw);
+      const dim3 grid = c1m_grid(total, D, four ? 4 : 1, &gpw);
+      hipLaunchKernelGGL((four ? conv2d_f32_k27_mfma_sign_kernel<4> : conv2d_f32_k27_mfma_sign_kernel<1>), grid, block, 0, s, x, w, H,
+                         W, D, sH, sW, pH, pW, (int)OH, (int)OW, scale, bias, out_packed, (int)bnn_packed_words(D),
+                         FastDiv((uint32_t)OW), FastDiv((uint32_t)OH), (uint32_t)total, (uint32_t)((total + 63) / 64), gpw);
     } else {
       const dim3 grid((unsigned)((total + 255) / 256));
       hipLaunchKernelGGL(conv2d_f32_sign_kernel<0>, grid, block, 0, s, x, w, C, H, W, D, kH, kW, sH, sW, pH, pW,

@@ -151,6 +151,15 @@ def test_first_sign_forms(N, H, W, D, want):
     assert B.lib().bnn_testing_first_sign(N, H, W, D, 1, 1, 1, 1, 256) == want
 
 
+def test_first_sign_forms_of_very_large_images():
+    """64 pixels that span 4 GiB are left to the chains: four channel groups a workgroup as soon as there is work for them, so that no
+    channel count is refused that a launch has room for."""
+    form = lambda N, H, D, s: B.lib().bnn_testing_first_sign(N, H, H, D, s, s, 0, 0, 256)
+    assert form(60, 2300, 98336, 2300) >= 2 and form(60, 2400, 98304, 2400) == 0 and form(60, 2400, 98336, 2400) == 0
+    assert form(60, 2400, 196608, 2400) == 0 and form(60, 2400, 196609, 2400) == 1 and form(1, 2400, 2200000, 2400) == 1
+    assert form(1, 13300, 64, 1) >= 2 and form(1, 13400, 64, 1) == 1
+
+
 def image(N, C, H, W, D, kH, kW, sH, sW, pH, pW, shape=-1, pixel=0):
     """bnn_testing_conv_image on 256 compute units -> (shape, first row, last row, rows with room)."""
     out = (ctypes.c_int64 * 3)()

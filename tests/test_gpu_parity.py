@@ -2135,6 +2135,24 @@ def test_first_layer_signs_of_small_values(e):
         _first_signs(N, D, 2, x, w, sc, bi)
 
 
+@pytest.mark.parametrize("N,D,stride,form", [(3, 196900, 2400, 1), (3, 100, 2400, 0), (1, 2200000, 2400, 1)])
+def test_first_layer_signs_of_very_large_images(N, D, stride, form):
+    """Images whose offsets conv_first_sign.hip does not hold: the chains, by four channel groups a workgroup where there are many
+    channels, the last group partial."""
+    print(f"first layer signs, very large images N={N} D={D}", flush=True)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert B.lib().bnn_testing_first_sign(N, 2400, 2400, D, stride, stride, 1, 1, 256) == form
+    rng = np.random.default_rng(N + D)
+    x = np.zeros((N, 3, 2400, 2400), np.float32)
+    x[:, :, :8, :8] = rng.standard_normal((N, 3, 8, 8))
+    w = rng.standard_normal((D, 3, 3, 3)).astype(np.float32)
+    sc, bi = rng.standard_normal(D).astype(np.float32), rng.standard_normal(D).astype(np.float32)
+    ref = oracle.conv2d_f32_seq(np.ascontiguousarray(x[:, :, :2, :2]), w, (4, 4), (1, 1), sc, bi)  # the one pixel a stride leaves
+    assert ref.shape[2:] == (1, 1)
+    got = as_u64(B.bnn_conv2d_f32_sign(dev(x), dev(w), dev(sc), dev(bi), (stride, stride), (1, 1)))
+    assert np.array_equal(got, oracle.pack_nhwc(ref))
+
+
 @pytest.mark.parametrize("N,D", [(4, 449), (4, 256), (3, 449)])
 def test_first_layer_large_maps(N, D):
     """Maps above and below 350 MB, channel counts on both sides of the rule and off the groups of 32 and 128: the
