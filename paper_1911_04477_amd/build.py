@@ -93,19 +93,28 @@ def build_tensorcall(out: str = TENSORCALL) -> Optional[str]:
     binding then converts tensors itself."""
     if os.path.exists(out):
         os.remove(out)  # not one of another source
-    import torch
+    try:
+        import torch
+    except ImportError as e:
+        print("calls from tensors not built: no torch (%s)" % e)
+        return None
     home, include = os.path.dirname(torch.__file__), sysconfig.get_paths()["include"]
     if not all(os.path.exists(f) for f in (os.path.join(include, "Python.h"), os.path.join(home, "include", "c10", "hip", "HIPStream.h"))):
         print("calls from tensors not built: they need the headers of Python and of torch for ROCm")
         return None
     cxx = [shutil.which("g++")] if shutil.which("g++") else [HIPCC]
     tmp, lib = out + ".tmp.%d" % os.getpid(), os.path.join(home, "lib")
-    subprocess.check_call([
+    command = [
         *cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
         "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", include, "-I", os.path.join(ROOT, "include"),
         "-isystem", os.path.join(home, "include"), "-isystem", os.path.join(home, "include", "torch", "csrc", "api", "include"),
         "-isystem", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), os.path.join(CSRC, "tensorcall.cpp"), "-o", tmp,
-        "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath," + lib])
+        "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath," + lib]
+    try:
+        subprocess.check_call(command)
+    except (OSError, subprocess.CalledProcessError) as e:
+        print("calls from tensors not built:", e)
+        return None
     os.replace(tmp, out)
     return out
 
@@ -115,13 +124,12 @@ def build(verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
         tensors = ex.submit(build_tensorcall)
         objs = list(ex.map(_compile, SOURCES))
-        tensors.result()
-    tmp = LIB + ".tmp.%d" % os.getpid()
-    subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp])
-    os.replace(tmp, LIB)
-    fast = build_fastcall()
+        tmp = LIB + ".tmp.%d" % os.getpid()
+        subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp])
+        os.replace(tmp, LIB)
+        built = [LIB, build_fastcall(), tensors.result()]
     if verbose:
-        print("built", LIB, fast)
+        print("built", *built)
     return LIB
 
 

@@ -481,6 +481,30 @@ def test_tensor_calls_build_and_absence(L, monkeypatch, tmp_path):
         assert B._Tensors(L, str(out)).gemm(1, 2, 3, 4) is None
 
 
+@pytest.mark.parametrize("missing", ["torch", "compiler", "compiles"])
+def test_library_builds_without_tensor_calls(monkeypatch, tmp_path, missing):
+    """No torch, no compiler for the extension or one that fails on it: the library and the call helper are built all the same."""
+    import subprocess
+    import sys
+    from paper_1911_04477_amd import build
+    for name in ("LIB", "FASTCALL", "TENSORCALL", "OBJ_DIR"):
+        monkeypatch.setattr(build, name, str(tmp_path / name))
+    monkeypatch.setattr(build, "build_fastcall", lambda: open(build.FASTCALL, "w").close())
+    monkeypatch.setattr(build.build_tensorcall, "__defaults__", (build.TENSORCALL,) + build.build_tensorcall.__defaults__[1:])
+    monkeypatch.setattr(build, "_compile", lambda src: src)
+    if missing == "torch":
+        monkeypatch.setitem(sys.modules, "torch", None)
+
+    def check_call(command):
+        if any("tensorcall.cpp" in c for c in command):
+            raise FileNotFoundError(command[0]) if missing == "compiler" else subprocess.CalledProcessError(1, command)
+        open(command[-1], "w").close()
+
+    monkeypatch.setattr(build.subprocess, "check_call", check_call)
+    assert build.build() == build.LIB
+    assert sorted(p.name for p in tmp_path.iterdir()) == ["FASTCALL", "LIB", "OBJ_DIR"]
+
+
 @pytest.mark.skipif(not os.path.exists(B.TENSORCALL_PATH), reason="not built")
 def test_tensor_calls_decline_what_is_not_plain(L):
     """CPU tensors, other types, other counts of arguments, numbers of other types: None, and nothing is called."""
