@@ -16,6 +16,8 @@ from typing import List, Optional, Tuple
 
 import torch
 
+from .build import tensorcall_built_for
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 # BNN_SANITIZE=1 (host-only checks, see build.py): the build whose host code carries ASan / UBSan
 LIB_PATH = os.path.join(HERE, "libbnn_san.so" if os.environ.get("BNN_SANITIZE") == "1" else "libbnn.so")
@@ -137,7 +139,8 @@ def _c() -> _Calls:
 
 class _Tensors:
     """Calls from the tensors themselves (csrc/tensorcall.cpp): a status, or None where the call is not a plain one and the
-    function of this module has to look at it.  Where the extension has not been built every call is of that kind."""
+    function of this module has to look at it.  Where the extension has not been built, or for another torch, every call is of that
+    kind."""
 
     FUNCTIONS = ("gemm", "epilogue", "encode", "conv2d", "conv2d_packed", "im2col", "f32_sign", "conv2d_f32", "maxpool", "fc")
 
@@ -148,7 +151,9 @@ class _Tensors:
                 spec = importlib.util.spec_from_file_location("paper_1911_04477_amd._tensorcall", path)
                 module = importlib.util.module_from_spec(spec)
                 spec.loader.exec_module(module)
-            except ImportError as e:  # of another torch
+                if module.built_for != tensorcall_built_for(torch):  # it would read tensors at wrong places
+                    raise ImportError(f"built for {module.built_for}")
+            except (ImportError, AttributeError) as e:  # of another torch or Python
                 module = None
                 warnings.warn(f"{path} does not load ({e}): build it again; calls take 1 to 2 us longer", RuntimeWarning, stacklevel=4)
         if module is not None:

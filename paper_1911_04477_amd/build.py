@@ -5,6 +5,7 @@ import os
 import platform
 import shutil
 import subprocess
+import sys
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 from typing import Optional, Sequence
@@ -88,6 +89,11 @@ def build_fastcall(out: str = FASTCALL, flags: Sequence[str] = ("-O2",)) -> Opti
     return out
 
 
+def tensorcall_built_for(torch) -> str:
+    """What _tensorcall.so is good for: it reads tensors through accessors compiled into it, so one build of torch and one Python."""
+    return " ".join((torch.__version__, str(torch.version.git_version), sys.implementation.cache_tag))
+
+
 def build_tensorcall(out: str = TENSORCALL) -> Optional[str]:
     """The binding's calls from tensors, a CPython extension against torch's own headers.  None where it cannot be built: the
     binding then converts tensors itself."""
@@ -106,6 +112,7 @@ def build_tensorcall(out: str = TENSORCALL) -> Optional[str]:
     tmp, lib = out + ".tmp.%d" % os.getpid(), os.path.join(home, "lib")
     command = [
         *cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+        '-DBNN_BUILT_FOR="%s"' % tensorcall_built_for(torch),
         "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", include, "-I", os.path.join(ROOT, "include"),
         "-isystem", os.path.join(home, "include"), "-isystem", os.path.join(home, "include", "torch", "csrc", "api", "include"),
         "-isystem", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), os.path.join(CSRC, "tensorcall.cpp"), "-o", tmp,
@@ -134,7 +141,6 @@ def build(verbose: bool = False) -> str:
 
 
 if __name__ == "__main__":
-    import sys
     if "--sanitize" in sys.argv[1:]:
         print("built", build_sanitized())
     else:

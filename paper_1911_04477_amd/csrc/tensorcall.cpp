@@ -4,7 +4,8 @@
 // calls (about 50 ns each, 20 to 30 of them) was 1.6 to 2 us beside it.  Here it is 0.2: one call from the binding with the
 // tensors themselves.  Each function returns the status of the call, or None for anything but the plain case (tensors of
 // the binding's types on the GPU, given outputs, integers, pairs of integers); the binding's own code then takes the call,
-// and raises what it raises.  bind(): addresses of the library's functions, in the order of `names`.
+// and raises what it raises.  bind(): addresses of the library's functions, in the order of `names`.  built_for: the torch and the
+// Python of whose objects this file's accessors know the layout; the binding uses it with no other.
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <algorithm>
@@ -314,5 +315,6 @@ PyMODINIT_FUNC PyInit__tensorcall() {
   if (!t) return nullptr;
   for (size_t i = 0; i < sizeof(names) / sizeof(names[0]); ++i) PyTuple_SET_ITEM(t, i, PyUnicode_FromString(names[i]));
   if (PyModule_AddObject(m, "names", t) < 0) return nullptr;
+  if (PyModule_AddStringConstant(m, "built_for", BNN_BUILT_FOR) < 0) return nullptr;
   return m;
 }

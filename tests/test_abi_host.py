@@ -481,6 +481,20 @@ def test_tensor_calls_build_and_absence(L, monkeypatch, tmp_path):
         assert B._Tensors(L, str(out)).gemm(1, 2, 3, 4) is None
 
 
+@pytest.mark.skipif(not os.path.exists(B.TENSORCALL_PATH), reason="not built")
+def test_tensor_calls_of_another_torch_are_declined(L, monkeypatch):
+    """An extension that loads but was built for another torch, another build of it or another Python is not called."""
+    import sys
+    import torch
+    for module, name, value in ((torch, "__version__", "2.9.0"), (torch.version, "git_version", "0" * 40), (sys.implementation, "cache_tag", "cpython-399")):
+        with monkeypatch.context() as m:
+            m.setattr(module, name, value)
+            with pytest.warns(RuntimeWarning, match="built for"):
+                t = B._Tensors(L, B.TENSORCALL_PATH)
+        assert all(getattr(t, f).__name__ == "<lambda>" for f in t.FUNCTIONS)
+    assert B._Tensors(L, B.TENSORCALL_PATH).gemm.__name__ == "gemm"
+
+
 @pytest.mark.parametrize("missing", ["torch", "compiler", "compiles"])
 def test_library_builds_without_tensor_calls(monkeypatch, tmp_path, missing):
     """No torch, no compiler for the extension or one that fails on it: the library and the call helper are built all the same."""
