@@ -95,7 +95,7 @@ _lib: Optional[ctypes.CDLL] = None
 
 
 FASTCALL_PATH = LIB_PATH.replace("libbnn", "_fastcall")
-TENSORCALL_PATH = os.path.join(HERE, "_tensorcall.so")
+TENSORCALL_PATH = LIB_PATH.replace("libbnn", "_tensorcall")
 
 
 def _fastcall():

@@ -40,6 +40,7 @@ EXTRA_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("conv.hip", "
 #       BNN_SANITIZE=1 python -m pytest tests/test_abi_host.py
 SAN_LIB = os.path.join(HERE, "libbnn_san.so")
 SAN_FASTCALL = os.path.join(HERE, "_fastcall_san.so")
+SAN_TENSORCALL = os.path.join(HERE, "_tensorcall_san.so")
 # The run ends at the first finding.  Enums are left out: a C caller may hand over any int, and the library says so; so are the types of
 # called functions (kernels picked by an expression), which gcc's runtime, preloaded above, does not know.
 SAN_HOST_FLAGS = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined", "-Xarch_host",
@@ -65,7 +66,9 @@ def build_sanitized() -> str:
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-Xarch_host", "-fsanitize=address",
                            "-Xarch_host", "-fsanitize=undefined", *objs, "-o", tmp])
     os.replace(tmp, SAN_LIB)
-    build_fastcall(SAN_FASTCALL, ("-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined"))
+    checks = ("-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined")
+    build_fastcall(SAN_FASTCALL, checks)
+    build_tensorcall(SAN_TENSORCALL, (*checks, "-fno-sanitize=vptr"))  # torch's types are not all there to compare with
     return SAN_LIB
 
 
@@ -96,7 +99,7 @@ def tensorcall_built_for(torch) -> str:
     return " ".join((torch.__version__, str(torch.version.git_version), sys.implementation.cache_tag))
 
 
-def build_tensorcall(out: str = TENSORCALL) -> Optional[str]:
+def build_tensorcall(out: str = TENSORCALL, flags: Sequence[str] = ("-O2",)) -> Optional[str]:
     """The binding's calls from tensors, a CPython extension against torch's own headers.  None where it cannot be built: the
     binding then converts tensors itself."""
     if os.path.exists(out):
@@ -113,7 +116,7 @@ def build_tensorcall(out: str = TENSORCALL) -> Optional[str]:
     cxx = [shutil.which("g++")] if shutil.which("g++") else [HIPCC]
     tmp, lib = out + ".tmp.%d" % os.getpid(), os.path.join(home, "lib")
     command = [
-        *cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+        *cxx, *flags, "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
         '-DBNN_BUILT_FOR="%s"' % tensorcall_built_for(torch),
         "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", include, "-I", os.path.join(ROOT, "include"),
         "-isystem", os.path.join(home, "include"), "-isystem", os.path.join(home, "include", "torch", "csrc", "api", "include"),
