@@ -100,13 +100,20 @@ uint64_t *u64(const at::Tensor &t) { return static_cast<uint64_t *>(t.data_ptr()
 // rows of a matrix: one row may have any stride
 int64_t row_stride(const at::Tensor &t, int64_t least) { return t.size(0) > 1 ? t.stride(0) : least; }
 
+// Other threads run meanwhile; held again also where the call throws.
+struct Released {
+  PyThreadState *state = PyEval_SaveThread();
+  ~Released() { PyEval_RestoreThread(state); }
+};
+
 template <class Call>
 PyObject *launch(const Call &call) {
   void *const stream = c10::hip::getCurrentHIPStream().stream();
   bnn_status st;
-  Py_BEGIN_ALLOW_THREADS
-  st = call(stream);
-  Py_END_ALLOW_THREADS
+  {
+    Released released;
+    st = call(stream);
+  }
   return PyLong_FromLong((long)st);
 }
 

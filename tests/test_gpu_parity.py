@@ -853,6 +853,27 @@ def test_calls_from_tensors_equal_the_bindings_own():
     assert refused == list(own)[list(own).index("no K"):]
 
 
+def test_calls_from_tensors_survive_what_a_call_throws(tmp_path):
+    """A C++ exception out of the library (memory, a lock) is declined like anything else, with the interpreter's lock held again.
+    The functions called throw before anything is launched."""
+    import importlib.util
+    import subprocess
+    print("calls from tensors: exception", flush=True)
+    (tmp_path / "throws.cpp").write_text('#include <stdexcept>\nextern "C" int throws() { throw std::runtime_error("no memory"); }\n')
+    subprocess.check_call(["g++", "-shared", "-fPIC", "-o", str(tmp_path / "throws.so"), str(tmp_path / "throws.cpp")])
+    path = tmp_path / "_tensorcall.so"  # a copy of its own, bound to nothing yet
+    path.write_bytes(open(B.TENSORCALL_PATH, "rb").read())
+    spec = importlib.util.spec_from_file_location("a_copy._tensorcall", str(path))
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    L = ctypes.CDLL(str(tmp_path / "throws.so"))
+    module.bind(*[ctypes.cast(L.throws, ctypes.c_void_p).value for _ in module.names])
+    A, C = torch.zeros(4, 1, dtype=torch.int64, device=DEV), torch.zeros(4, 4, dtype=torch.int32, device=DEV)
+    for _ in range(3):
+        assert module.gemm(A, A, 64, C) is None
+    assert B.bnn_xnor_gemm(A, A, 64, C=C) is C and host(C).tolist() == [[64] * 4] * 4
+
+
 def test_calls_from_tensors_follow_the_current_stream():
     """A call is ordered behind what its stream holds: on a side stream after a long product that makes its input."""
     print("calls from tensors: stream", flush=True)
