@@ -1967,8 +1967,8 @@ def test_gemm_rows_beyond_the_accumulators_exact_range():
 @pytest.mark.parametrize("N,H,W,D", [(1, 7, 9, 33), (2, 16, 16, 96), (1, 8, 8, 200), (70, 32, 32, 40), (5, 33, 31, 64),
                                      (24, 32, 32, 500), (24, 32, 32, 530)])
 def test_first_layer_few_and_many_pixels(N, H, W, D):
-    """The 3x3x3 layer with one channel group per workgroup (few pixels) and four (more than 64 per compute unit times
-    four, or with many channels fewer), channel counts off the group of 32; extreme magnitudes, signs and maps against the oracle's fma chains."""
+    """The 3x3x3 layer with few pixels (chains, one channel group per workgroup) and with many (signs: half-precision products), channel
+    counts off the group of 32; extreme magnitudes, signs and maps against the oracle's fma chains."""
     print(f"first layer N={N} {H}x{W} D={D}", flush=True)
     rng = np.random.default_rng(N + H + W + D)
     x = (rng.standard_normal((N, 3, H, W)) * 2.0 ** rng.integers(-40, 40, size=(N, 3, H, W))).astype(np.float32)
@@ -1980,17 +1980,24 @@ def test_first_layer_few_and_many_pixels(N, H, W, D):
     assert np.array_equal(got, oracle.pack_nhwc(ref))
 
 
-@pytest.mark.parametrize("N,H,W,D,stride,pad", [
-    (24, 32, 32, 96, 1, 1),     # workgroups of four waves, two of 64 channels, the second half empty
-    (13, 63, 65, 130, 1, 2),    # 64 pixels cross rows and images, one word and two channels
-    (64, 32, 33, 250, 1, 1),    # eight waves, the last group of 32 channels partial
-    (150, 61, 59, 257, 2, 0),   # 16 waves, one channel in the last workgroup
-    (513, 32, 32, 10, 1, 1),    # several groups of pixels a wave, the last wave without any
-    (4000, 5, 7, 40, 4, 1)])    # 64 pixels cross many images
-def test_first_layer_signs_from_split_products(N, H, W, D, stride, pad):
+def _first_form(N, H, W, D, stride, pad, form):
+    """These sizes are for that form of the first layer's signs (on 256 compute units)."""
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert B.lib().bnn_testing_first_sign(N, H, W, D, stride, stride, pad, pad, 256) == form
+
+
+@pytest.mark.parametrize("N,H,W,D,stride,pad,form", [
+    (72, 32, 32, 96, 1, 1, 2),     # workgroups of four waves, two of 64 channels, the second half empty
+    (13, 63, 65, 130, 1, 2, 2),    # 64 pixels cross rows and images, one word and two channels
+    (64, 32, 33, 250, 1, 1, 4),    # 16 waves, the last group of 32 channels partial
+    (150, 61, 59, 257, 2, 0, 3),   # eight waves, one channel in the last workgroup
+    (513, 32, 32, 10, 1, 1, 3),    # several groups of pixels a wave, the last wave without any
+    (4000, 5, 7, 448, 4, 1, 2)])   # 64 pixels cross many images
+def test_first_layer_signs_from_split_products(N, H, W, D, stride, pad, form):
     """Enough pixels for the half-precision kernel: its bits are those of the fma chains.  Ordinary values, where a few
     outputs a wave are in doubt, then images with an area of zeros and channels that have no bias."""
     print(f"first layer signs N={N} {H}x{W} D={D} stride={stride} pad={pad}", flush=True)
+    _first_form(N, H, W, D, stride, pad, form)
     rng = np.random.default_rng(N + H + W + D)
     x = rng.standard_normal((N, 3, H, W)).astype(np.float32)
     w = rng.standard_normal((D, 3, 3, 3)).astype(np.float32)
@@ -2006,10 +2013,12 @@ def test_first_layer_signs_from_split_products(N, H, W, D, stride, pad):
 
 
 @pytest.mark.parametrize("kind", ["specials", "nan", "ties", "large", "tiny", "filters", "scales"])
-@pytest.mark.parametrize("N,D", [(24, 96), (64, 256)])
-def test_first_layer_signs_beyond_the_bound(N, D, kind):
-    """Inputs whose signs the half-precision products cannot prove, in a few pixels or in all of them: the chains decide."""
+@pytest.mark.parametrize("N,D,form", [(24, 96, 0), (72, 96, 2), (64, 256, 3)])
+def test_first_layer_signs_beyond_the_bound(N, D, form, kind):
+    """Inputs whose signs the half-precision products cannot prove, in a few pixels or in all of them: the chains decide.  And a call
+    that is left to the chains from the start."""
     print(f"first layer signs N={N} D={D} {kind}", flush=True)
+    _first_form(N, 32, 32, D, 1, 1, form)
     rng = np.random.default_rng(N + D)
     x = rng.standard_normal((N, 3, 32, 32)).astype(np.float32)
     w = rng.standard_normal((D, 3, 3, 3)).astype(np.float32)
@@ -2052,8 +2061,7 @@ FIRST_FORMS = [  # images of 32 x 32, channels, form
 
 def _first_signs(N, D, form, x, w, sc, bi):
     """The signs of N images of 32 x 32, the ones of x over and over, in the form that the sizes are for, against the oracle's."""
-    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
-        assert B.lib().bnn_testing_first_sign(N, 32, 32, D, 1, 1, 1, 1, 256) == form
+    _first_form(N, 32, 32, D, 1, 1, form)
     with np.errstate(all="ignore"):
         ref = oracle.pack_nhwc(oracle.conv2d_f32_seq(x, w, (1, 1), (1, 1), sc, bi))
     xs = dev(x).repeat((N + len(x) - 1) // len(x), 1, 1, 1)[:N].contiguous()
@@ -2134,8 +2142,7 @@ def test_first_layer_signs_decided_by_subnormal_halves(biased):
     sc, bi = np.ones(D, np.float32), np.zeros(D, np.float32)
     if biased:
         bi[1::2] = 1e-5 * rng.standard_normal(D // 2).astype(np.float32)
-    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
-        assert B.lib().bnn_testing_first_sign(N, 3, 3, D, 1, 1, 0, 0, 256) >= 2
+    _first_form(N, 3, 3, D, 1, 0, 2)
     ref = oracle.conv2d_f32_seq(x, w, (1, 1), (0, 0), sc, bi)
     assert np.array_equal(ref[:, :, 0, 0] >= 0, np.broadcast_to(w.reshape(D, 27)[:, np.argwhere(order == 26)[0, 0]] > 0, (N, D)))
     got = as_u64(B.bnn_conv2d_f32_sign(dev(x), dev(w), dev(sc), dev(bi), (1, 1), (0, 0)))
@@ -2161,8 +2168,7 @@ def test_first_layer_signs_of_very_large_images(N, D, stride, form):
     """Images whose offsets conv_first_sign.hip does not hold: the chains, by four channel groups a workgroup where there are many
     channels, the last group partial."""
     print(f"first layer signs, very large images N={N} D={D}", flush=True)
-    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
-        assert B.lib().bnn_testing_first_sign(N, 2400, 2400, D, stride, stride, 1, 1, 256) == form
+    _first_form(N, 2400, 2400, D, stride, 1, form)
     rng = np.random.default_rng(N + D)
     x = np.zeros((N, 3, 2400, 2400), np.float32)
     x[:, :, :8, :8] = rng.standard_normal((N, 3, 8, 8))
