@@ -401,36 +401,30 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(Params 
   const int corr = (int)((uint32_t)p.Kformula - (uint32_t)nc * 256u);
   int s[WT][WT][4];
   if (wave < 4) {  // wave-uniform
+    auto sum = [&](auto first, auto four) {
+      using V4 = decltype(four);
 #pragma unroll
-    for (int i = 0; i < WT; ++i)
+      for (int i = 0; i < WT; ++i)
 #pragma unroll
-      for (int j = 0; j < WT; ++j) {
-        int t[4] = {corr, corr, corr, corr};
-        if (as_int) {
-#pragma unroll
-          for (int k = 0; k < KS; ++k) {
-            const int4 v = sPart[((k * WT * WT + i * WT + j) * 4 + wave) * 64 + lane];
-            t[0] += v.x;
-            t[1] += v.y;
-            t[2] += v.z;
-            t[3] += v.w;
-          }
-        } else {
-          float u[4] = {(float)corr, (float)corr, (float)corr, (float)corr};
+        for (int j = 0; j < WT; ++j) {
+          V4 t = {first, first, first, first};
 #pragma unroll
           for (int k = 0; k < KS; ++k) {
-            const float4 v = reinterpret_cast<const float4 *>(sPart)[((k * WT * WT + i * WT + j) * 4 + wave) * 64 + lane];
-            u[0] += v.x;
-            u[1] += v.y;
-            u[2] += v.z;
-            u[3] += v.w;
+            const V4 v = reinterpret_cast<const V4 *>(sPart)[((k * WT * WT + i * WT + j) * 4 + wave) * 64 + lane];
+            t.x += v.x;
+            t.y += v.y;
+            t.z += v.z;
+            t.w += v.w;
           }
-#pragma unroll
-          for (int e = 0; e < 4; ++e) t[e] = (int)u[e];
+          s[i][j][0] = (int)t.x;
+          s[i][j][1] = (int)t.y;
+          s[i][j][2] = (int)t.z;
+          s[i][j][3] = (int)t.w;
         }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s[i][j][e] = t[e];
-      }
+    };
+    // one branch around all: inside, it kept the reads of a block behind the sums of the one before
+    if (as_int) sum(corr, int4());
+    else sum((float)corr, float4());
   }
 
   if constexpr (!SIGN) {
@@ -449,30 +443,38 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(Params 
         off[j] = (int64_t)img * p.img_stride + ((uint32_t)c - img * p.OHW);
       }
     }
-    const bool full = WT > 1 && m0 + B32 <= p.M;  // uniform; one block: no second copy of its few stores
+    const bool full = m0 + B32 <= p.M;
     auto store = [&](auto *base, int64_t ld, auto value) {
       using V = typename std::remove_pointer<decltype(base)>::type;
       typedef V vec __attribute__((ext_vector_type(WT)));
       V *ptr[WT];
 #pragma unroll
       for (int j = 0; j < WT; ++j) ptr[j] = base + off[j] + (int64_t)mq * ld;
+      auto rows = [&](auto whole, auto pairs) {
 #pragma unroll
-      for (int i = 0; i < WT; ++i) {
+        for (int i = 0; i < WT; ++i) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (!full && mq + 32 * i + e >= p.M) continue;
-          const int64_t row = (int64_t)(32 * i + e) * ld;  // uniform
-          if (WT > 1 && p.pairs) {  // uniform
-            vec v;
+          for (int e = 0; e < 4; ++e) {
+            if (!decltype(whole)::value && mq + 32 * i + e >= p.M) continue;
+            const int64_t row = (int64_t)(32 * i + e) * ld;  // uniform
+            if constexpr (decltype(pairs)::value) {
+              vec v;
 #pragma unroll
-            for (int j = 0; j < WT; ++j) v[j] = value(i, j, e);
-            *reinterpret_cast<vec *>(ptr[0] + row) = v;
-          } else {
+              for (int j = 0; j < WT; ++j) v[j] = value(i, j, e);
+              *reinterpret_cast<vec *>(ptr[0] + row) = v;
+            } else {
 #pragma unroll
-            for (int j = 0; j < WT; ++j) ptr[j][row] = value(i, j, e);
+              for (int j = 0; j < WT; ++j) ptr[j][row] = value(i, j, e);
+            }
           }
         }
-      }
+      };
+      // both uniform, and branched on once: around each store they cost 8 rows by two branches
+      const std::true_type yes;
+      const std::false_type no;
+      if constexpr (WT == 1) rows(no, no);  // no second copy of its few stores
+      else if (p.pairs) full ? rows(yes, yes) : rows(no, yes);
+      else full ? rows(yes, no) : rows(no, no);
     };
     if (p.C) store(p.C, p.ldc, [&](int i, int j, int e) { return s[i][j][e]; });
     if (row_affine) store(p.Y, p.ldy, [&](int i, int j, int e) { return fmaf(sc[i][e], (float)s[i][j][e], bi[i][e]); });

@@ -1834,6 +1834,28 @@ def test_gemm_few_rows_or_columns_split_the_reduction(M, N, K, split):
         assert names == ["xnor_gemm_fp4_split" if split else "xnor_gemm_fp4"]
 
 
+@pytest.mark.parametrize("cfg", [25, 26, 27, 28])
+@pytest.mark.parametrize("M,N,ldc", [(64, 64, 64), (128, 63, 63), (128, 66, 67), (70, 64, 66), (97, 61, 64), (33, 65, 65), (1, 2, 2)])
+def test_split_map_store_forms(M, N, ldc, cfg):
+    """Whole and partial tiles of rows, pairs of columns and single ones, maps and both affine axes, against the vector-ALU
+    tiles (integers, and one fma of them: bit for bit); nothing past the map is written."""
+    print(f"split map stores M={M} N={N} ldc={ldc} cfg={cfg}", flush=True)
+    K = 641
+    g = torch.Generator(device=DEV).manual_seed(M + N + ldc)
+    A, Bm = (torch.randint(-2**62, 2**62, (n, B.packed_words(K)), dtype=torch.int64, device=DEV, generator=g) for n in (M, N))
+    out = [torch.full((M + 8, ldc), -7, dtype=torch.int32, device=DEV) for _ in range(2)]
+    for o, c in zip(out, (cfg, 3)):
+        _, names = kernels_of(lambda: B.bnn_xnor_gemm(A, Bm, K, o[:M, :N], cfg=c))
+        assert names == [GEMM_KERNELS[c]]
+    assert torch.equal(out[0], out[1])
+    assert (out[0][:, N:] == -7).all() and (out[0][M:] == -7).all()
+    for axis, n in ((B.CH_ROW, M), (B.CH_COL, N)):
+        sc, bi = torch.rand(n, device=DEV, generator=g) + 0.5, torch.randn(n, device=DEV, generator=g)
+        ys = [B.bnn_xnor_gemm_epilogue(A, Bm, K, sc, bi, axis, want_int=True, cfg=c) for c in (cfg, 3)]
+        assert torch.equal(ys[0][0], ys[1][0]) and torch.equal(ys[0][1], ys[1][1])
+        assert torch.equal(ys[0][0], out[0][:M, :N])
+
+
 MATRIX_CONV_CASES = [  # N, C, H, W, D, kH, kW, sH, sW, pH, pW
     (3, 64, 9, 7, 70, 3, 3, 1, 1, 1, 1),      # one word per pixel: the row ends in the middle of a piece
     (2, 200, 12, 12, 130, 3, 3, 1, 1, 1, 1),  # pad bits inside a tap's last word
