@@ -73,8 +73,8 @@ BNN_API int bnn_testing_conv_region(int N, int C, int H, int W, int kH, int kW, 
                                     int pool, int columns, int64_t *region);
 
 /*
- * bnn_testing_conv_word -- host only, launches nothing: whether a convolution of a packed image (packed: packed output, else
- * maps) goes to the kernel of configuration 19 on a device of `units` compute units: 2 it does, 1 it could, 0 it cannot,
+ * bnn_testing_conv_word -- host only, launches nothing: whether a convolution of a packed image (packed 1: packed output, 0: an
+ * int32 map, 2: an int32 and an fp32 map) goes to the kernel of configuration 19 on a device of `units` compute units: 2 it does, 1 it could, 0 it cannot,
  * -1 for arguments bnn_conv2d_packed refuses.  (A pointwise map without stride or padding is an explicit GEMM before that.)
  */
 BNN_API int bnn_testing_conv_word(int N, int C, int H, int W, int D, int kH, int kW, int sH, int sW, int pH, int pW, int pool,

@@ -153,7 +153,7 @@ int device_cu_count();
 // emode 0: int32 / fp32 store; 1: packed sign(fma(scale, acc, bias)) store, optional 2x2 pool.
 bnn_status run_gemm(GemmParams &p, int bmode, int emode, hipStream_t s, const GemmTune &tune = GemmTune());
 
-// Convolution of an image of one word per pixel (conv_word.hip), taps straight from memory.
+// Convolution of an image of one to four words per pixel (conv_word.hip), taps straight from memory.
 bool conv_word_applicable(const GemmParams &p, int bmode);
 bool conv_word_faster(const GemmParams &p, int emode);  // its rule against the other matrix-core kernels
 bnn_status launch_conv_word(GemmParams &p, int emode, hipStream_t s);

@@ -489,14 +489,15 @@ extern "C" int bnn_testing_conv_region(int N, int C, int H, int W, int kH, int k
 extern "C" int bnn_testing_conv_word(int N, int C, int H, int W, int D, int kH, int kW, int sH, int sW, int pH, int pW, int pool,
                                      int packed, int units) {
   if (check_conv_geometry(N, C, H, W, kH, kW, sH, sW, pH, pW) != BNN_OK || N == 0 || D <= 0 || units <= 0 ||
-      (pool != 0 && pool != 2) || (pool && !packed))
+      (pool != 0 && pool != 2) || (pool && packed != 1) || packed < 0 || packed > 2)
     return -1;
   if (pool && ((bnn_conv_out_dim(H, kH, sH, pH) & 1) || (bnn_conv_out_dim(W, kW, sW, pW) & 1))) return -1;
   if (conv_limits(N, C, H, W, D, kH, kW, sH, sW, pH, pW) != BNN_OK) return -1;
-  GemmParams p = conv_gemm(nullptr, nullptr, N, C, H, W, D, kH, kW, sH, sW, pH, pW, pool, nullptr, nullptr, nullptr, nullptr,
-                           nullptr);
+  const uintptr_t i32 = packed == 1 ? 0 : 4096, f32 = packed == 2 ? 4096 : 0;  // not read
+  GemmParams p = conv_gemm(nullptr, nullptr, N, C, H, W, D, kH, kW, sH, sW, pH, pW, pool, reinterpret_cast<int32_t *>(i32),
+                           reinterpret_cast<float *>(f32), nullptr, nullptr, nullptr);
   p.n_cu = units;
-  return !conv_word_applicable(p, 1) ? 0 : conv_word_faster(p, packed) ? 2 : 1;
+  return !conv_word_applicable(p, 1) ? 0 : conv_word_faster(p, packed == 1) ? 2 : 1;
 }
 
 // Declared in bnn_testing.h.

@@ -211,12 +211,20 @@ bool conv_word_applicable(const GemmParams &p, int bmode) {
   return span < 4294967296.0;
 }
 
-// By t, tiles of 32 x 32 outputs per compute unit, and u, tiles of 64 x 256, against the kernels that take the call otherwise.
-// 1 x 1: always (1 x 15 x 18 x 29 3.3 -> 3.0 us; maps by stride 2 5.9 -> 4.1, 7.6 -> 4.7; a pointwise map without a stride is an
-// explicit GEMM and does not get here).  3 x 3, by words of a pixel:
-//   1: signs from t = 1.8 (1.4 to 1.8 within 1 %, 2.1 4.2 against 3.8, 6.2 5.4, 3.8, 31 8.7, 5.8), maps, whose split tiles
-//      have a shorter epilogue, from 2.5 (2.0 4.0 against 4.4, 2.5 4.5, 4.6, 2.7 4.9, 4.5, 13 7.7, 5.4, 95 22.7, 20.5);
-//   2: signs from t = 2.7 (2.2 4.4 against 4.5, 2.9 4.6, 4.5, 5.7 6.1, 4.6, 64 12.0, 9.8), maps from 4 (3.7 5.2 against 5.6,
+// By t, tiles of 32 x 32 outputs per compute unit, and u, tiles of 64 x 256, against the kernels that take the call otherwise (u's, the
+// other's time first).  Both maps of a call are twice the epilogue, and more than three rows of tiles (192 channels) load and
+// expand a column as often: maps then need more work.
+// 1 x 1: signs and one word always (1 x 15 x 18 x 29 3.3 -> 3.0 us; maps by stride 2 5.9 -> 4.1, 7.6 -> 4.7; a pointwise map without a
+//   stride is an explicit GEMM and does not get here); maps of more words to at most 32 channels or, in whole rows of tiles, 160 pixels
+//   (256 x 60 pixels to 64 3.3, 2.9; 45 pixels to 52 3.15, 3.4), else of two and three words from t = 1.6 (D = 256, t = 1.2 3.45, 3.9; 1.8
+//   3.55, 3.5), up to 128 channels 0.9 (0.3 3.3, 3.4; 1.25 3.65, 3.45), of four from 2 (256 x 7 x 14 x 9 to 128, t = 0.12 3.15, 3.7; 1.1
+//   3.5, 4.05; 2.1 3.9, 3.7), of small images to many channels 3 (18 pixels, t = 2.0 3.8, 4.3; 9 pixels 4.0, 5.4; 24, t = 4.2 5.2, 4.0).
+// 3 x 3, by words of a pixel:
+//   1: signs from t = 1.8, up to 64 channels 2 (1.9 3.8 against 3.95, 2.06 4.15, 3.8; 6.2 5.4, 3.8; 31 8.7, 5.8), maps, whose split tiles
+//      have a shorter epilogue, from 2.5 (2.0 4.0 against 4.4, 2.5 4.5, 4.6, 2.7 4.9, 4.5, 13 7.7, 5.4, 95 22.7, 20.5), both of more than
+//      32 channels from 3.2 (2.7 9.0 against 9.6, 3.6 9.8, 9.55; 12 channels, 3.2 8.7, 8.2), any to more than 192 from 4 (3.1 4.5 against
+//      4.8, 4.2 5.2, 4.7; both 2.75 8.5, 10.3, 4.6 9.7, 8.7 to 9.9);
+//   2: signs from t = 3 (2.2 4.4 against 4.5, 2.85 4.4, 4.65, 3.3 4.8, 4.6, 5.7 6.1, 4.6, 64 12.0, 9.8), maps from 4 (3.7 5.2 against 5.6,
 //      4.4 6.4, 6.2, 6.9 8.0, 6.2, 115 32.1, 29.6);
 // (up to three words: maps so small that a region's lanes idle stay on the split-K tiles where those take them, from 5.5 to 8
 // tiles a unit, which their tests state: 216 x 128 x 6 x 8 -> 166 7.6 us against 5.4);
@@ -227,18 +235,30 @@ bool conv_word_applicable(const GemmParams &p, int bmode) {
 //      8.8 against 9.6, 1.04 11.6, 9.5) up to one a unit (1.98 12.0, 9.9; 2.2 14.9, 15.3; 2.6 15.3, 15.4; maps 1.97 16.1, 15.1; 259 of them,
 //      33 on the 32 units of an XCD, 17.0, 18.2; 2.2 17.5, 19.7; 2.6 19.2, 20.3), and from one and a half on (3.03 18.5, 15.5; 3.06
 //      23.2, 19.7; 4.7 23.4, 21.8; 7.9 31.7, 29.5; 12 65.9, 60.4), but maps not with the first eighth of a third (4.1 24.4, 25.7; 4.3
-//      28.6, 29.4; 4.4 23.7, 25.8; 4.65 27.0, 26.4).
+//      28.6, 29.4; 4.4 23.7, 25.8; 4.65 27.0, 26.4);
+//   3 and 4: both maps not from 1.7 workgroups of 512 pixels a unit on, where their stores are the time (1.6 39.0, 36.8; 1.9 43.6,
+//      46.1; 3.1 60.9, 66.4; 4.2 78.5, 87.0), unless the other kernel's go past the caches in pieces of lines (102, 87).
 bool conv_word_faster(const GemmParams &p, int emode) {
-  if (p.g.kH == 1) return true;
+  const ConvGeom &g = p.g;
   const int64_t cu = p.n_cu;
   const int64_t tiles = (((int64_t)p.M + 31) / 32) * (((int64_t)p.N + 31) / 32);
   const int64_t wide = (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 255) / 256);
   const int64_t groups = (((int64_t)p.M + 63) / 64) * (((int64_t)p.N + 511) / 512);
-  const bool signs = emode != 0;
-  if (p.g.Cw < 4 && 2 * tiles > 11 * cu && fp4_split_applicable(p, 1)) return false;
-  switch (p.g.Cw) {
-    case 1: return signs ? 5 * tiles > 9 * cu : 2 * tiles > 5 * cu;
-    case 2: return signs ? 10 * tiles > 27 * cu : tiles > 4 * cu;
+  const bool signs = emode != 0, both = p.C && p.Y, tall = p.M > 192;
+  if (g.kH == 1) {
+    if (signs || g.Cw == 1 || p.M <= 32 || (p.M >= 64 && p.N <= 160)) return true;
+    if (tall && (int64_t)g.OH * g.OW < 64) return tiles > 3 * cu;
+    return 10 * tiles > (g.Cw == 4 ? 20 : p.M > 128 ? 16 : 9) * cu;
+  }
+  if (g.Cw < 4 && 2 * tiles > 11 * cu && fp4_split_applicable(p, 1)) return false;
+  if (g.Cw > 2 && both && 10 * groups > 17 * cu &&
+      !(map_columns_by_four(p) && nontemporal_maps(p, 1) && !nontemporal_maps(p, 1, true)))
+    return false;
+  switch (g.Cw) {
+    case 1:
+      if (signs) return p.M <= 64 ? tiles >= 2 * cu : 5 * tiles > 9 * cu;
+      return tall ? tiles > 4 * cu : both && p.M > 32 ? 5 * tiles > 16 * cu : 2 * tiles > 5 * cu;
+    case 2: return tiles > (signs ? 3 : 4) * cu;
     case 3: return 4 * wide > 3 * cu && (signs || groups <= cu || 2 * groups > 3 * cu);
     default: return wide > cu && (groups <= cu || 2 * groups > 3 * cu) && (signs || groups <= 2 * cu || 4 * groups > 9 * cu);
   }

@@ -105,7 +105,7 @@ def test_what_the_convolution_refuses_is_refused():
 @pytest.mark.parametrize("N,C,H,W,D,k,packed,want", [
     (7, 64, 32, 32, 64, 3, 1, 1), (8, 64, 32, 32, 64, 3, 1, 2),        # one word: t = 1.75, 2
     (10, 64, 32, 16, 128, 3, 0, 1), (11, 64, 32, 16, 128, 3, 0, 2),    # maps: 2.5, 2.75
-    (10, 65, 32, 32, 64, 3, 1, 1), (11, 65, 32, 32, 64, 3, 1, 2),      # two words: 2.5, 2.75
+    (12, 65, 32, 32, 64, 3, 1, 1), (13, 65, 32, 32, 64, 3, 1, 2),      # two words: 3, 3.25
     (16, 128, 32, 32, 64, 3, 0, 1), (17, 128, 32, 32, 64, 3, 0, 2),    # maps: 4, 4.25
     (48, 129, 32, 32, 64, 3, 1, 1), (49, 192, 32, 32, 64, 3, 0, 2),    # three words: u = 0.75, 0.766
     (64, 256, 32, 32, 64, 3, 1, 1), (65, 256, 32, 32, 64, 3, 1, 2), (128, 256, 32, 32, 64, 3, 0, 2),  # four: 1, 1.016, 2
@@ -124,6 +124,26 @@ def test_conv_word_rule_lines(N, C, H, W, D, k, packed, want):
 def test_conv_word_rule_lines_of_maps(N, C, H, W, D, want):
     """Maps of a few more workgroups of 512 pixels than one or two a unit: those left over last as long as all others."""
     assert B.lib().bnn_testing_conv_word(N, C, H, W, D, 3, 3, 1, 1, 1, 1, 0, 0, 256) == want
+
+
+@pytest.mark.parametrize("N,C,H,W,D,k,s,outputs,want", [
+    (64, 64, 15, 8, 64, 3, 1, 1, 1), (64, 64, 15, 8, 65, 3, 1, 1, 2),            # signs of one word: t = 1.875, 2.8
+    (8, 64, 32, 16, 192, 3, 1, 0, 2), (8, 64, 32, 16, 193, 3, 1, 0, 1), (9, 64, 32, 16, 256, 3, 1, 0, 2),      # a map: 3, 3.5, 4.5
+    (16, 64, 32, 16, 128, 3, 1, 2, 2), (12, 64, 32, 16, 128, 3, 1, 2, 1), (13, 64, 32, 16, 128, 3, 1, 2, 2),   # both: 4, 3, 3.25
+    (48, 64, 32, 16, 32, 3, 1, 2, 2), (24, 64, 32, 16, 33, 3, 1, 2, 1),          # to 32 and 33 channels: 3
+    (8, 64, 32, 16, 256, 3, 1, 2, 1), (9, 64, 32, 16, 256, 3, 1, 2, 2),          # to 256 channels: 4, 4.5
+    (217, 192, 32, 32, 64, 3, 1, 2, 2), (218, 192, 32, 32, 64, 3, 1, 2, 1), (218, 192, 32, 32, 64, 3, 1, 0, 2),  # 1.7 workgroups a unit
+    (218, 256, 32, 32, 64, 3, 1, 2, 1), (161, 256, 44, 10, 301, 3, 1, 2, 2),      # four; pieces of lines
+    (1, 256, 31, 10, 64, 1, 2, 0, 2), (1, 256, 21, 31, 64, 1, 2, 0, 1), (1, 256, 21, 31, 32, 1, 2, 0, 2),      # 1 x 1: 160 pixels, 176
+    (64, 256, 31, 15, 64, 1, 2, 0, 1), (65, 256, 31, 15, 64, 1, 2, 0, 2),        # four words: t = 2
+    (25, 128, 31, 15, 128, 1, 2, 0, 2), (14, 128, 31, 15, 128, 1, 2, 0, 1), (15, 128, 31, 15, 128, 1, 2, 0, 2),  # two: 1.6, 0.9, 0.94
+    (20, 128, 31, 15, 129, 1, 2, 0, 1), (21, 128, 31, 15, 129, 1, 2, 0, 2),      # to 129 channels: 1.56, 1.64
+    (1, 256, 17, 9, 63, 1, 2, 0, 1), (1, 256, 17, 9, 64, 1, 2, 0, 2),            # 45 pixels: not to part of a tile's channels
+    (64, 128, 11, 15, 256, 1, 2, 0, 1), (65, 128, 11, 15, 256, 1, 2, 0, 2),      # 48 pixels to 256 channels: 3
+    (1, 64, 21, 31, 64, 1, 2, 0, 2), (1, 256, 21, 31, 64, 1, 2, 1, 2)])          # one word, signs
+def test_conv_word_rule_lines_of_outputs(N, C, H, W, D, k, s, outputs, want):
+    """Signs (1), a map (0) and both maps (2), few and many channels: both sides of every line between them."""
+    assert B.lib().bnn_testing_conv_word(N, C, H, W, D, k, k, s, s, k // 2, k // 2, 0, outputs, 256) == want
 
 
 @pytest.mark.parametrize("N,C,H,W,D,want", [
