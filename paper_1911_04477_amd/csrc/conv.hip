@@ -170,13 +170,15 @@ __global__ __launch_bounds__(256, 4) void conv2d_f32_k27_mfma_sign_kernel(
   const int ch0 = 32 * NG * (int)blockIdx.y;
   const uint32_t g_first = ((uint32_t)blockIdx.x * 4u + (uint32_t)wave) * (uint32_t)groups_per_wave;
   const uint32_t g_end = min(g_first + (uint32_t)groups_per_wave, ngroups);
+  const int nch = min(32 * NG, D - ch0);  // >= 1 by the grid
   // the first patch is requested before the filters are staged, so the two latencies overlap
   // (a wave without pixel groups loads pixel 0's and discards it)
+  C1mFilters<NG> filters;
+  filters.request(w, scale, bias, ch0, nch, true);
   float xv[27];
   uint32_t inside;
   c1m_issue_patch(x, g_first * 64u + (uint32_t)lane, total_pix, H, W, sH, sW, pH, pW, OH, OW, divOW, divOH, xv, inside);
-  const int nch = min(32 * NG, D - ch0);  // >= 1 by the grid
-  c1m_stage_filters<NG>(sTap, sSc, sBi, w, scale, bias, ch0, nch, true);
+  filters.stage(sTap, sSc, sBi, nch, true);
   __syncthreads();  // the only barrier: from here on the waves run independently
 
   for (uint32_t grp = g_first; grp < g_end; ++grp) {  // wave-uniform bounds
@@ -223,14 +225,16 @@ __global__ __launch_bounds__(256) void conv2d_f32_k27_mfma_kernel(const float *_
   const int ch0 = 32 * NG * (int)blockIdx.y;
   const int nch = min(32 * NG, D - ch0);  // >= 1 by the grid
   const uint32_t g_first = ((uint32_t)blockIdx.x * 4u + (uint32_t)wave) * (uint32_t)groups_per_wave;
-  // One channel group: the first patch is requested before the filters, as in the kernel above.  Four: 14 filter values a thread
-  // beside it cost more than they hide (8 x 512 x 224 x 224 213 us, 220).
+  // One channel group: the first patch is requested before the filters are staged, as in the kernel above.  Four: 14 filter values a
+  // thread beside it cost more than they hide (8 x 512 x 224 x 224 213 us, 220).
   constexpr bool AHEAD = NG == 1;
+  C1mFilters<NG> filters;
+  filters.request(w, scale, bias, ch0, nch, has_affine != 0);
   float xv[27];
   uint32_t inside;
   if (AHEAD)
     c1m_issue_patch(x, g_first * 64u + (uint32_t)lane, total_pix, H, W, sH, sW, pH, pW, OH, OW, divOW, divOH, xv, inside);
-  c1m_stage_filters<NG>(sTap, sSc, sBi, w, scale, bias, ch0, nch, has_affine != 0);
+  filters.stage(sTap, sSc, sBi, nch, has_affine != 0);
   __syncthreads();  // the only barrier
 
   const size_t ohw = (size_t)OH * OW;

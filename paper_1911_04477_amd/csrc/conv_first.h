@@ -27,37 +27,41 @@ __device__ __forceinline__ uint32_t c1m_spread_nibbles(uint32_t m) {
   return (m & 0xFu) | ((m & 0xF0u) << 4) | ((m & 0xF00u) << 8) | ((m & 0xF000u) << 12);
 }
 
-// Stage the filter taps of channels ch0 .. ch0 + 32 * NG - 1 tap-major in LDS (read [channel][tap]
-// contiguously; channels past D are zero) and their scale / bias (past D, or without an affine
+// The filter taps of channels ch0 .. ch0 + 32 * NG - 1, staged tap-major in LDS (read [channel][tap]
+// contiguously; channels past D are zero), and their scale / bias (past D, or without an affine
 // map: fma(0, acc, -1) < 0, so such bits are 0).  Every load is issued before the first is waited for: a loop over them, with a
 // condition around each, was four memory round trips one after the other (signs of one 32 x 32
-// image, 128 channels 4.15 -> 3.7 us; fp32 maps of 64, with the first patch requested before them, 13.4 -> 12.6).
+// image, 128 channels 4.15 -> 3.7 us).  With one channel group they are requested ahead of the first patch and staged behind it: loads
+// return in order, so that the wait for these leaves the patch in flight.  (The patch first: the slow ones among its loads, which
+// the chain of matrix instructions hides, delayed the staging; fp32 maps of 70 images of 32 x 16 by stride 2 6.85 us, 6.2 so.)
 template <int NG>
-__device__ __forceinline__ void c1m_stage_filters(float *sTap, float *sSc, float *sBi, const float *__restrict__ w,
-                                                  const float *__restrict__ scale, const float *__restrict__ bias,
-                                                  int ch0, int nch, bool affine) {
-  constexpr int ALL = 27 * 32 * NG, PER = (ALL + 255) / 256;
-  const int tid = threadIdx.x, real = 27 * nch;
-  const float *const wc = w + (size_t)ch0 * 27;
-  float v[PER];
+struct C1mFilters {
+  static constexpr int ALL = 27 * 32 * NG, PER = (ALL + 255) / 256;
+  float v[PER], sc, bi;
+  __device__ __forceinline__ void request(const float *__restrict__ w, const float *__restrict__ scale,
+                                          const float *__restrict__ bias, int ch0, int nch, bool affine) {
+    const int tid = threadIdx.x;
+    const float *const wc = w + (size_t)ch0 * 27;
 #pragma unroll
-  for (int i = 0; i < PER; ++i) v[i] = wc[min(tid + 256 * i, real - 1)];
-  float sc = 0.0f, bi = -1.0f;
-  if (affine) {  // uniform
-    const int ch = ch0 + min(tid, nch - 1);
-    sc = scale[ch];
-    bi = bias[ch];
+    for (int i = 0; i < PER; ++i) v[i] = wc[min(tid + 256 * i, 27 * nch - 1)];
+    // no condition around the loads: a wait for older ones could not tell how many follow
+    const int ch = affine ? ch0 + min(tid, nch - 1) : 0;
+    sc = (affine ? scale : w)[ch];
+    bi = (affine ? bias : w)[ch];
   }
+  __device__ __forceinline__ void stage(float *sTap, float *sSc, float *sBi, int nch, bool affine) const {
+    const int tid = threadIdx.x;
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int idx = tid + 256 * i, ch = idx / 27, k = idx - 27 * ch;
-    if (i + 1 < PER || idx < ALL) sTap[k * C1M_RS(NG) + ch] = idx < real ? v[i] : 0.0f;
+    for (int i = 0; i < PER; ++i) {
+      const int idx = tid + 256 * i, ch = idx / 27, k = idx - 27 * ch;
+      if (i + 1 < PER || idx < ALL) sTap[k * C1M_RS(NG) + ch] = idx < 27 * nch ? v[i] : 0.0f;
+    }
+    if (tid < 32 * NG) {
+      sSc[tid] = affine && tid < nch ? sc : 0.0f;
+      sBi[tid] = affine && tid < nch ? bi : -1.0f;
+    }
   }
-  if (tid < 32 * NG) {
-    sSc[tid] = tid < nch ? sc : 0.0f;
-    sBi[tid] = tid < nch ? bi : -1.0f;
-  }
-}
+};
 
 // Issue the 27 loads of pixel p's patch: every tap unconditionally from a clamped (always
 // readable) position; bit r of `inside` says whether tap (r / 3, r % 3) lies in the image.
