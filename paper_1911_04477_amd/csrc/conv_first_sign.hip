@@ -454,9 +454,10 @@ __global__ __launch_bounds__(T, T == 256 ? 5 : 4) void conv2d_f32_k27_f16_sign_k
 }
 
 // -1: does not apply.  By q, pairs of 64 pixels and 32 channels per compute unit:
-//   up to 12 the chains alone, a workgroup per pair and four, are as fast and the same whatever the values (128 channels of 32 x 32: 12
-//   images 4.5 us against 5.3, 32 5.0, 5.5, in zeros 6.4; 48 6.2, 6.1, 7.9; 56 7.7, 6.3, 7.9; 64 channels, 96 images 6.2, 6.3; 256
-//   channels, 4 images 4.4, 5.0, 24 6.3, 6.25; 192 channels, 30 images 6.2, 5.9);
+//   up to 8, two waves a SIMD, the chains alone, a workgroup per pair and four, are 5 % faster and the same whatever the values (128
+//   channels of 32 x 32: 17 images 4.9 us against 5.3, 32 5.0, 5.3; 64 channels: 38 images 4.75, 5.5); their third wave makes it
+//   6.3 at once (33 images 6.3, 5.75; 48 6.35 to 6.55, 6.55; 64 channels, 97 images 7.1, 6.7), and only areas of zeros stay faster (48
+//   images of them 7.9 here);
 //   up to 27 workgroups of four waves and 64 channels, which spread best (128 channels: 64 images 6.4 against 7.9 by eight
 //   waves and 128 channels, 96 7.5, 8.0, 128 8.8, 7.8; 256 channels: 48 images 7.5, 8.6, 64 9.1, 8.7);
 //   beyond, workgroups of 16 waves, one to a unit, split the filters least often (256 images, 128 channels 9.9 us; eight
@@ -465,7 +466,7 @@ __global__ __launch_bounds__(T, T == 256 ? 5 : 4) void conv2d_f32_k27_f16_sign_k
 // The chains for every output (the kernel before this one): 64 images 7.9, 128 12.6, 192 16.5, 256 20.2, 768 53.1 (23.7 here).
 static int first_sign_shape(int64_t groups, int D, int64_t cu) {
   const int64_t q = groups * (((int64_t)D + 31) / 32);
-  if (q <= 12 * cu) return -1;
+  if (q <= 8 * cu) return -1;
   if (q <= 27 * cu) return 0;
   const int64_t halves = (groups * (((int64_t)D + 127) / 128) + 8 * cu - 1) / (8 * cu);
   return halves % 2 == 1 && halves <= 5 ? 1 : 2;

@@ -162,7 +162,7 @@ def test_conv_word_offsets_fit_32_bits():
 
 
 @pytest.mark.parametrize("N,H,W,D,want", [
-    (48, 32, 32, 128, 0), (49, 32, 32, 128, 2), (192, 32, 32, 32, 0), (193, 32, 32, 32, 2),  # q = 12, 12.25; 12, 12.06
+    (32, 32, 32, 128, 0), (33, 32, 32, 128, 2), (128, 32, 32, 32, 0), (129, 32, 32, 32, 2),  # q = 8, 8.25; 8, 8.06
     (108, 32, 32, 128, 2), (109, 32, 32, 128, 3),                                               # 27, 27.25: one round of eight waves
     (128, 32, 32, 128, 3), (129, 32, 32, 128, 4), (257, 32, 32, 128, 3), (640, 32, 32, 128, 3),  # one, two, three, five
     (641, 32, 32, 128, 4), (769, 32, 32, 128, 4), (64, 32, 32, 250, 3), (128, 32, 32, 200, 4)])  # six, seven; 256 channels
