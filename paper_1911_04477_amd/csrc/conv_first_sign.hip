@@ -456,8 +456,8 @@ __global__ __launch_bounds__(T, T == 256 ? 5 : 4) void conv2d_f32_k27_f16_sign_k
 // -1: does not apply.  By q, pairs of 64 pixels and 32 channels per compute unit:
 //   up to 8, two waves a SIMD, the chains alone, a workgroup per pair and four, are 5 % faster and the same whatever the values (128
 //   channels of 32 x 32: 17 images 4.9 us against 5.3, 32 5.0, 5.3; 64 channels: 38 images 4.75, 5.5); their third wave makes it
-//   6.3 at once (33 images 6.3, 5.75; 48 6.35 to 6.55, 6.55; 64 channels, 97 images 7.1, 6.7), and only areas of zeros stay faster (48
-//   images of them 7.9 here);
+//   6.3 at once (33 images 6.3, 5.75; 48 6.35 to 6.55, 6.55; 64 channels, 97 images 7.1, 6.7), and only areas of zeros without a
+//   bias stay faster (48 images of them 7.9 here);
 //   up to 27 workgroups of four waves and 64 channels, which spread best (128 channels: 64 images 6.4 against 7.9 by eight
 //   waves and 128 channels, 96 7.5, 8.0, 128 8.8, 7.8; 256 channels: 48 images 7.5, 8.6, 64 9.1, 8.7);
 //   beyond, workgroups of 16 waves, one to a unit, split the filters least often (256 images, 128 channels 9.9 us; eight

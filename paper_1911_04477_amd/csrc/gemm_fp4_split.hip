@@ -6,7 +6,7 @@
 // tile is 32 x 32 or 64 x 64 outputs, KS waves take contiguous ranges of the reduction in chunks of 256 bits, and
 // every wave reads its operands straight from memory in fragment order (lane l: row l % 32, 128-bit half l / 32 of
 // the chunk): no LDS staging, no barrier before the end.  Two chunks are in flight per wave.  The partial sums meet in
-// LDS as integers once; waves 0 .. 3 each finish the accumulator quad q = wave
+// LDS once, as integers or, maps of 64 x 64 tiles, as the accumulators' fp32; waves 0 .. 3 each finish the accumulator quad q = wave
 // (rows 8q + 4 * (l / 32) + 0..3 of every block).
 //
 // Bound: latency (launch, one memory round trip for the operands, one exchange through LDS).
@@ -102,7 +102,8 @@ __global__ __launch_bounds__(64 * KS, 2) void xnor_gemm_fp4_split_kernel(Params 
   }
 
   // The columns' affine constants, requested before the operands: after them, a wait for the first operands could not
-  // tell how many loads follow.  (Requested when they are used: a memory round trip, 256 x 4096 x 4096 8.1 -> 7.0 us.)
+  // tell how many loads follow.  (Requested when they are used: a memory round trip, 256 x 4096 x 4096 8.1 -> 7.0 us; 6.3 with
+  // the branches of the exchange and the stores taken once.)
   float csc[WT], cbi[WT];
 #pragma unroll
   for (int j = 0; j < WT; ++j) csc[j] = cbi[j] = 0.0f;

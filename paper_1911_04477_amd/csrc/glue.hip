@@ -193,8 +193,8 @@ __global__ __launch_bounds__(256) void fc_f32_kernel(const float *__restrict__ x
     if (computes) {
       const float *px = &sx[r * FC_RS], *pw = &sw[j * FC_RS];
       int kk = 0;
-      // A step takes 4.5 clocks and an LDS read about 130: two parts of 16 steps are read ahead (no more than 15 reads can be in
-      // flight), in a ring of four, so that no register is copied.
+      // A step takes 4.5 clocks and an LDS read about 130: two parts of 16 steps are read ahead (16 reads; a wait can tell at most
+      // 15 in flight from the ones before them), in a ring of four, so that no register is copied.
       auto load = [](const float *q) { return *reinterpret_cast<const float4 *>(q); };
       if (kc >= 64) {
         // volatile: the optimizer would make one load at the loop's head of these and those at its end, with nothing read ahead
